@@ -120,10 +120,10 @@ def pass_rows(timer, cfg, label, mode, layout, plan, d_in, d_w, d_g, bufs, resid
     for what, fn in calls:
         ms, reps = timer.run(fn)
         rec, treps = timer.trace(fn, 2 if ms > 50 else 3)
-        steps = rl.steps_of_pass(rec, treps, cfg, N, layout, what)
+        steps = rl.steps_of_pass(rec, treps, cfg, N, layout, what, tiles=plan.tiles if mode == "fft" else None)
         row = {"config": label, "layer": cfg.name, "mode": mode, "pass": what, "ms": ms, "timed_reps": reps}
         if mode == "fft":
-            row["kernel_spectra"] = layout + (", resident" if resident else ", transformed inside the pass")
+            row["kernel_spectra"] = ("of tiles" if plan.tiles else layout) + (", resident" if resident else ", transformed inside the pass")
         if what != "kernel_spectra":
             row["voxels_per_s"] = cfg.out_voxels / (ms * 1e-3)
             row["effective_tflops"] = 2.0 * cfg.macs / (ms * 1e-3) / 1e12
@@ -156,7 +156,7 @@ def layer_rows(timer, cfg, label, variants, meaningful=True):
     for mode, layout, resident, memo in variants:
         p = znn.Plan(cfg.fan_in, cfg.fan_out, cfg.image, cfg.kernel, mode)
         if mode == "fft":
-            if layout is not None:
+            if layout not in (None, "auto"):
                 p.set_spectra_layout(layout)
             layout = p.spectra_layout
             if memo:
@@ -244,7 +244,7 @@ def main():
     # ---- config 5: per-pass table in every variant (also generates its tensors, once)
     c5_rows, (inp, w, gout), (d_in, d_w, d_g), (out, gin, gw) = layer_rows(
         timer, cfg, "C5", [] if args.headline_only else
-        [("fft", "folded", True, True), ("fft", "full", True, True), ("direct", None, False, False)])
+        [("fft", "auto", True, True), ("fft", "folded", True, True), ("fft", "full", True, True), ("direct", None, False, False)])
     log("config 5 tensors and table: %.1f s" % (time.perf_counter() - t0))
 
     # ---- the per-layer choice between the methods (Section 4), measured on this shape
@@ -291,7 +291,8 @@ def main():
     kernels = [{"kernel": k, "launches_per_step": n_ / treps, "ms_per_launch": t_ / n_, "ms_per_step": t_ / treps}
                for k, (n_, t_) in agg.items()]
     top = max(kernels, key=lambda r: r["ms_per_step"])
-    what = {"spectral mac forward": "fwd", "spectral mac backward": "bwd"}.get(top["kernel"].split(" (")[0], "wgrad_memo")
+    what = {"spectral mac forward": "fwd", "spectral mac backward": "bwd", "spectral products forward": "fwd",
+            "spectral products backward": "bwd"}.get(top["kernel"].split(" (")[0], "wgrad_memo")
     if top["kernel"].startswith("direct forward"):
         what = "fwd"
     elif top["kernel"].startswith("direct backward"):
@@ -299,7 +300,8 @@ def main():
     key = rl.step_of(top["kernel"], what)
     if key == "F-mac" and "MFMA" in top["kernel"]:
         key = "F-mac/mfma"
-    bound, work = rl.work_of(cfg, N, layout or "folded", what)[key]
+    tiles = plan.tiles if method == "fft" else None
+    bound, work = rl.work_of(cfg, N, layout or "folded", what, tiles)[key]
     roof = {"kernel": top["kernel"], "ms": top["ms_per_launch"], "launches_per_step": top["launches_per_step"]}
     roof.update(rl.price(bound, work, top["ms_per_launch"]))
     roof["algorithmic_work_per_launch"] = work
@@ -329,9 +331,10 @@ def main():
         "dtype": "f32", "data": "synthetic",
         "config": {"workload": "config 5: wide 3D layer f=120 -> f'=120, n=96^3, k=7^3, n'=90^3, one training round "
                                "(kernel transforms + forward + backward + kernel gradient) by the method the autotuner "
-                               "picks: " + (("FFT, kernel spectra resident in HBM as " + layout + " spectra, node spectra memoized")
-                                            if method == "fft" else "direct"),
+                               "picks: " + (("FFT, kernel spectra resident in HBM " + ("at tile length" if tiles else "as " + layout + " spectra") +
+                                             ", node spectra memoized") if method == "fft" else "direct"),
                    "global_batch": 1, "method": method, "kernel_spectra": layout,
+                   "tiles": None if not tiles else {"lengths": tiles[0], "counts": tiles[1]},
                    "autotune_ms": {"direct": [round(v, 3) for v in tune_ms[0]], "fft": [round(v, 3) for v in tune_ms[1]]}},
         "effective_tflops": 3 * 2.0 * cfg.macs / (ms_per_step * 1e-3) / 1e12,
         "per_mode": per_mode,

@@ -89,7 +89,11 @@ int  znn_plan_workspace_bytes(const znn_plan* plan, int32_t pass, size_t* bytes)
  *                       axis to have an FFT extent divisible by 4 and at most 16 taps one
  *                       voxel apart along it (ZNN_EUNSUPPORTED otherwise).
  *   ZNN_SPECTRA_AUTO    the library's choice: folded where it applies and the layer has
- *                       enough frequencies to fill the chip, else full.  This is what
+ *                       enough frequencies to fill the chip, else full -- or, in a buffer of
+ *                       that size, the spectra of the kernels at the length of short tiles, with
+ *                       all passes on overlapping tiles of the images (overlap-save), where that
+ *                       is expected to be faster (znn_plan_tiles).  With AUTO the contents of the
+ *                       spectra and memo buffers are private to the library.  This is what
  *                       znn_plan_create selects.
  * The choice is stored in the plan when it is created or set and read from there by the size
  * queries, the kernel transform and both multiply-accumulates.  znn_plan_set_spectra_layout
@@ -101,6 +105,9 @@ int  znn_plan_workspace_bytes(const znn_plan* plan, int32_t pass, size_t* bytes)
 typedef enum { ZNN_SPECTRA_AUTO = 0, ZNN_SPECTRA_FULL = 1, ZNN_SPECTRA_FOLDED = 2 } znn_spectra_layout;
 int  znn_plan_set_spectra_layout(znn_plan* plan, int32_t layout);
 int  znn_plan_spectra_layout(const znn_plan* plan, int32_t* layout);
+/* Tiles of the FFT method per axis: transform lengths and how many cover an image.  Both {0,0,0}
+ * for plans whose transforms take the whole volume, and for direct plans.  Host only. */
+int  znn_plan_tiles(const znn_plan* plan, znn_vec3* length, znn_vec3* count);
 /* Bytes of the kernel spectra in the plan's layout. */
 int  znn_plan_spectra_bytes(const znn_plan* plan, size_t* bytes);
 

@@ -29,7 +29,7 @@ EXPORTS = [
     "znn_maxfilter3d_sparse_fwd", "znn_maxfilter3d_sparse_bwd", "znn_maxpool3d_fwd", "znn_maxpool3d_bwd",
     "znn_transfer_fn_fwd", "znn_transfer_fn_bwd", "znn_cross_entropy_loss_grad",
     "znn_autotune_round_workspace_bytes", "znn_autotune_round", "znn_accumulate",
-    "znn_plan_set_spectra_layout", "znn_plan_spectra_layout", "znn_conv3d_fwd_static",
+    "znn_plan_set_spectra_layout", "znn_plan_spectra_layout", "znn_plan_tiles", "znn_conv3d_fwd_static",
 ]
 STATIC_SCRATCH_BYTES = 32 * 1024 * 1024
 SPECTRA_LAYOUTS = {"auto": 0, "full": 1, "folded": 2}
@@ -85,6 +85,7 @@ def lib():
         L.znn_plan_spectra_bytes.argtypes = [vp, ctypes.POINTER(sz)]
         L.znn_plan_set_spectra_layout.argtypes = [vp, i32]
         L.znn_plan_spectra_layout.argtypes = [vp, ctypes.POINTER(i32)]
+        L.znn_plan_tiles.argtypes = [vp, ctypes.POINTER(Vec3), ctypes.POINTER(Vec3)]
         L.znn_conv_prepare_kernels.argtypes = [vp, vp, vp, sz, vp, sz, vp]
         L.znn_conv_release_kernels.argtypes = [vp]
         for name in ("znn_conv3d_fwd", "znn_conv3d_bwd", "znn_conv3d_wgrad"):
@@ -217,6 +218,13 @@ class Plan:
         v = ctypes.c_int32(-1)
         _check(lib().znn_plan_spectra_layout(self._h, ctypes.byref(v)))
         return {1: "full", 2: "folded"}[v.value]
+
+    @property
+    def tiles(self):
+        """(transform lengths, tiles) per axis of the FFT method on overlapping tiles, None on whole volumes."""
+        m, t = Vec3(), Vec3()
+        _check(lib().znn_plan_tiles(self._h, ctypes.byref(m), ctypes.byref(t)))
+        return ((m.z, m.y, m.x), (t.z, t.y, t.x)) if m.x else None
 
     def _workspace(self, which: int, device):
         """Grows (never shrinks) a torch byte buffer used as the caller workspace."""

@@ -10,7 +10,7 @@
 #include <tuple>
 #include <vector>
 
-#include "znn_internal.h"
+#include "fft_tile.h"
 
 #include <algorithm>
 
@@ -99,6 +99,7 @@ const Tuning& tuning()
         v.fft_lds_kb = num("ZNN_FFT_LDS_KB", 0);
         if (v.fft_lds_kb < 8 || v.fft_lds_kb > 64) v.fft_lds_kb = 0;
         v.fft_no_fused_xy = flag("ZNN_FFT_NO_FUSED_XY");
+        v.fft_no_tiles = flag("ZNN_FFT_NO_TILES");
         v.fft_lds_passes = flag("ZNN_FFT_LDS_PASSES");
         return v;
     }();
@@ -189,6 +190,91 @@ static int validate_desc(const znn_conv_desc* d, Geom* g)
     return ZNN_OK;
 }
 
+// ---------------------------------------------------------------- FFT method: whole volumes or tiles
+// How the library runs a layer by the FFT method when the layout of the kernel spectra is left to it.
+struct FftWay { Fold fold; Tiling tile; };
+
+// Seconds of a training round on whole volumes, from the rates of those kernels: 12 ps per spectrum element and forward
+// transform, 8.5 ps inverse; per edge and element 0.35 ps per multiply-accumulate with the kernel spectra rebuilt on the matrix
+// cores, 0.7 on the vector ALUs, 1.7 streamed in full, and 0.6 for the kernel gradient; 16 launches.
+static double whole_volume_seconds(const Geom& g, const Fold& F)
+{
+    const double sv = (double)g.svol(), nodes = g.f + g.fo, pairs = (double)g.f * g.fo;
+    const double mac = !F.on ? 1.7e-12 : fft_mac_mfma_supported(F.taps, F.N, F.P) ? 0.35e-12 : 0.7e-12;
+    return sv * (1.5 * nodes * 12e-12 + nodes * 8.5e-12 + pairs * (2.0 * mac + 0.6e-12));
+}
+
+static FftWay fft_way(const Geom& g)
+{
+    FftWay w = {fold_default(g), Tiling{}};
+    if (tuning().fft_no_tiles) return w;
+    // the spectra live in the buffer that the layout's size query describes
+    w.tile = tile_search(g, fft_spectra_bytes(g, w.fold));
+    if (!w.tile.on) return w;
+    const double whole = whole_volume_seconds(g, w.fold) + 16 * 4e-6, tiles = w.tile.seconds + 11 * 4e-6;
+    if (log_enabled())
+        fprintf(stderr, "znn: fft %d -> %d of %dx%dx%d: tiles %dx%dx%d, %d of them, %.1f us; whole volumes %.1f us\n", g.f, g.fo,
+                g.nz, g.ny, g.nx, w.tile.M[0], w.tile.M[1], w.tile.M[2], w.tile.tiles, tiles * 1e6, whole * 1e6);
+    if (whole < tiles) w.tile.on = false;
+    return w;
+}
+
+static size_t fft_pass_bytes(const Geom& g, const FftWay& w, int pass, bool resident)
+{
+    if (!w.tile.on) return fft_workspace(g, w.fold, pass, resident).total;
+    const size_t need = tile_workspace_bytes(g, w.tile, pass, resident);
+    // forward and backward report no less than the whole-volume passes would take, so that the tiles of a layer
+    // with much overlap come in fewer chunks
+    return pass == ZNN_PASS_WGRAD ? std::max(need, align256(sizeof(float2) * (size_t)g.svol()) * (g.f + g.fo))
+                                  : std::max(need, fft_workspace(g, w.fold, pass, resident).total);
+}
+
+static size_t fft_memo_bytes(const Geom& g, const FftWay& w)
+{
+    const size_t whole = align256(sizeof(float2) * (size_t)(g.f + g.fo) * g.svol());
+    return w.tile.on ? std::max(whole, tile_node_bytes(g, w.tile, g.f) + tile_node_bytes(g, w.tile, g.fo)) : whole;
+}
+
+// the half of a memo buffer that holds the spectra of the output gradients
+static float2* memo_gradients(const Geom& g, const FftWay& w, float2* memo)
+{
+    if (!w.tile.on) return memo + (size_t)g.f * g.svol();
+    return (float2*)((char*)memo + tile_node_bytes(g, w.tile, g.f));
+}
+
+static int run_kernel_spectra(const Geom& g, const FftWay& y, const float* w, float2* What, hipStream_t s)
+{
+    return y.tile.on ? tile_kernel_spectra(g, y.tile, w, What, s) : fft_kernel_spectra(g, y.fold, w, What, s);
+}
+
+static int run_fft_fwd(const Geom& g, const FftWay& y, const float* in, const float* w, const float2* resident, float* out,
+                       void* ws, float2* memo_in, hipStream_t s)
+{
+    if (!y.tile.on) return fft_fwd(g, y.fold, in, w, resident, out, ws, memo_in, s);
+    return tile_fwd(g, y.tile, in, w, resident, out, ws, fft_pass_bytes(g, y, ZNN_PASS_FWD, resident != nullptr), memo_in, s);
+}
+
+static int run_fft_bwd(const Geom& g, const FftWay& y, const float* gout, const float* w, const float2* resident, float* gin,
+                       void* ws, float2* memo_gout, hipStream_t s)
+{
+    if (!y.tile.on) return fft_bwd(g, y.fold, gout, w, resident, gin, ws, memo_gout, s);
+    return tile_bwd(g, y.tile, gout, w, resident, gin, ws, fft_pass_bytes(g, y, ZNN_PASS_BWD, resident != nullptr), memo_gout, s);
+}
+
+static int run_fft_wgrad(const Geom& g, const FftWay& y, const float* in, const float* gout, float* gw, void* ws, hipStream_t s)
+{
+    return y.tile.on ? tile_wgrad(g, y.tile, in, gout, gw, ws, s) : fft_wgrad(g, in, gout, gw, ws, s);
+}
+
+static int run_fft_wgrad_from_spectra(const Geom& g, const FftWay& y, const float2* Ihat, const float2* Ghat, float* gw,
+                                      void* ws, hipStream_t s)
+{
+    return y.tile.on ? tile_wgrad_from_spectra(g, y.tile, Ihat, Ghat, gw, ws, s)
+                     : fft_wgrad_from_spectra(g, Ihat, Ghat, gw, ws, s);
+}
+
+static FftWay way_of(const znn_plan* p) { return FftWay{p->fold, p->tile}; }
+
 static bool aligned256(const void* p) { return ((uintptr_t)p & 255) == 0; }
 
 static int check_ws(const znn_plan* p, int pass, void* ws, size_t ws_bytes)
@@ -261,9 +347,12 @@ int znn_plan_create(const znn_conv_desc* desc, znn_plan** plan)
     p->desc = *desc;
     p->g = g;
     p->mode = mode;
-    p->fold = mode == ZNN_FFT ? fold_default(g) : fold_full();
+    const FftWay way = mode == ZNN_FFT ? fft_way(g) : FftWay{fold_full(), Tiling{}};
+    p->fold = way.fold;
+    p->tile = way.tile;
     p->resident = nullptr;
     p->memo = nullptr;
+    p->memo_bytes = 0;
     p->memo_has_in = p->memo_has_gout = false;
     *plan = p;
     return ZNN_OK;
@@ -290,7 +379,7 @@ int znn_plan_workspace_bytes(const znn_plan* plan, int32_t pass, size_t* bytes)
     if (!plan || !bytes) return fail(ZNN_EINVAL, "NULL argument");
     if (pass < ZNN_PASS_FWD || pass > ZNN_PASS_WGRAD) return fail(ZNN_EINVAL, "unknown pass %d", pass);
     if (plan->mode == ZNN_DIRECT) *bytes = direct_workspace_bytes(plan->g, pass);
-    else *bytes = fft_workspace(plan->g, plan->fold, pass, plan->resident != nullptr).total;
+    else *bytes = fft_pass_bytes(plan->g, way_of(plan), pass, plan->resident != nullptr);
     return ZNN_OK;
 }
 
@@ -298,6 +387,15 @@ int znn_plan_spectra_bytes(const znn_plan* plan, size_t* bytes)
 {
     if (!plan || !bytes) return fail(ZNN_EINVAL, "NULL argument");
     *bytes = fft_spectra_bytes(plan->g, plan->fold);
+    return ZNN_OK;
+}
+
+int znn_plan_tiles(const znn_plan* plan, znn_vec3* length, znn_vec3* count)
+{
+    if (!plan || !length || !count) return fail(ZNN_EINVAL, "NULL argument");
+    const Tiling& L = plan->tile;
+    *length = L.on ? znn_vec3{L.M[0], L.M[1], L.M[2]} : znn_vec3{0, 0, 0};
+    *count = L.on ? znn_vec3{L.T[0], L.T[1], L.T[2]} : znn_vec3{0, 0, 0};
     return ZNN_OK;
 }
 
@@ -314,15 +412,22 @@ int znn_plan_set_spectra_layout(znn_plan* plan, int32_t layout)
     if (plan->mode != ZNN_FFT) return fail(ZNN_EINVAL, "kernel spectra exist only for the FFT method");
     if (plan->resident)
         return fail(ZNN_EINVAL, "resident kernel spectra are attached in the current layout; release them first");
-    if (layout == ZNN_SPECTRA_AUTO) plan->fold = fold_default(plan->g);
-    else if (layout == ZNN_SPECTRA_FULL) plan->fold = fold_full();
+    if (layout == ZNN_SPECTRA_AUTO) {
+        FftWay way = fft_way(plan->g);
+        // an attached memo buffer that was sized for whole volumes keeps them
+        if (plan->memo && plan->memo_bytes < fft_memo_bytes(plan->g, way)) way.tile.on = false;
+        plan->fold = way.fold;
+        plan->tile = way.tile;
+    } else if (layout == ZNN_SPECTRA_FULL) { plan->fold = fold_full(); plan->tile.on = false; }
     else if (layout == ZNN_SPECTRA_FOLDED) {
         const Fold F = fold_forced(plan->g);
         if (!F.on)
             return fail(ZNN_EUNSUPPORTED, "half spectra need a slowest axis whose FFT extent is divisible by 4 "
                                           "with at most %d taps one voxel apart", kMaxFoldedTaps);
         plan->fold = F;
+        plan->tile.on = false;
     } else return fail(ZNN_EINVAL, "unknown spectra layout %d", layout);
+    plan->memo_has_in = plan->memo_has_gout = false;    // spectra of another layout
     return ZNN_OK;
 }
 
@@ -336,7 +441,7 @@ int znn_conv_prepare_kernels(znn_plan* plan, const float* w, void* spectra, size
     if (!spectra) return fail(ZNN_EWORKSPACE, "spectra buffer is NULL");
     if (!aligned256(spectra)) return fail(ZNN_EWORKSPACE, "spectra buffer is not 256-byte aligned");
     if (spectra_bytes < need) return fail(ZNN_EWORKSPACE, "spectra buffer has %zu bytes, %zu needed", spectra_bytes, need);
-    int rc = fft_kernel_spectra(plan->g, plan->fold, w, (float2*)spectra, (hipStream_t)stream);
+    int rc = run_kernel_spectra(plan->g, way_of(plan), w, (float2*)spectra, (hipStream_t)stream);
     if (rc != ZNN_OK) return rc;
     plan->resident = (const float2*)spectra;
     return ZNN_OK;
@@ -345,7 +450,7 @@ int znn_conv_prepare_kernels(znn_plan* plan, const float* w, void* spectra, size
 int znn_plan_memo_bytes(const znn_plan* plan, size_t* bytes)
 {
     if (!plan || !bytes) return fail(ZNN_EINVAL, "NULL argument");
-    *bytes = align256(sizeof(float2) * (size_t)(plan->g.f + plan->g.fo) * plan->g.svol());
+    *bytes = fft_memo_bytes(plan->g, way_of(plan));
     return ZNN_OK;
 }
 
@@ -361,6 +466,7 @@ int znn_conv_set_memo(znn_plan* plan, void* memo, size_t memo_bytes)
     if (!aligned256(memo)) return fail(ZNN_EWORKSPACE, "memo buffer is not 256-byte aligned");
     if (memo_bytes < need) return fail(ZNN_EWORKSPACE, "memo buffer has %zu bytes, %zu needed", memo_bytes, need);
     plan->memo = (float2*)memo;
+    plan->memo_bytes = memo_bytes;
     return ZNN_OK;
 }
 
@@ -373,8 +479,8 @@ int znn_conv3d_wgrad_memo(znn_plan* plan, float* gw, void* ws, size_t ws_bytes, 
     int rc = check_ws(plan, ZNN_PASS_WGRAD, ws, ws_bytes);
     if (rc != ZNN_OK) return rc;
     const float2* Ihat = plan->memo;
-    const float2* Ghat = plan->memo + (size_t)plan->g.f * plan->g.svol();
-    return fft_wgrad_from_spectra(plan->g, Ihat, Ghat, gw, ws, (hipStream_t)stream);
+    const float2* Ghat = memo_gradients(plan->g, way_of(plan), plan->memo);
+    return run_fft_wgrad_from_spectra(plan->g, way_of(plan), Ihat, Ghat, gw, ws, (hipStream_t)stream);
 }
 
 int znn_conv_release_kernels(znn_plan* plan)
@@ -392,7 +498,7 @@ int znn_conv3d_fwd(znn_plan* plan, const float* in, const float* w, float* out,
     int rc = check_ws(plan, ZNN_PASS_FWD, ws, ws_bytes);
     if (rc != ZNN_OK) return rc;
     if (plan->mode == ZNN_DIRECT) return direct_fwd(plan->g, in, w, out, ws, (hipStream_t)stream);
-    rc = fft_fwd(plan->g, plan->fold, in, w, plan->resident, out, ws, plan->memo, (hipStream_t)stream);
+    rc = run_fft_fwd(plan->g, way_of(plan), in, w, plan->resident, out, ws, plan->memo, (hipStream_t)stream);
     if (plan->memo) plan->memo_has_in = rc == ZNN_OK;
     return rc;
 }
@@ -405,8 +511,8 @@ int znn_conv3d_bwd(znn_plan* plan, const float* gout, const float* w, float* gin
     int rc = check_ws(plan, ZNN_PASS_BWD, ws, ws_bytes);
     if (rc != ZNN_OK) return rc;
     if (plan->mode == ZNN_DIRECT) return direct_bwd(plan->g, gout, w, gin, ws, (hipStream_t)stream);
-    rc = fft_bwd(plan->g, plan->fold, gout, w, plan->resident, gin, ws,
-                 plan->memo ? plan->memo + (size_t)plan->g.f * plan->g.svol() : nullptr, (hipStream_t)stream);
+    rc = run_fft_bwd(plan->g, way_of(plan), gout, w, plan->resident, gin, ws,
+                     plan->memo ? memo_gradients(plan->g, way_of(plan), plan->memo) : nullptr, (hipStream_t)stream);
     if (plan->memo) plan->memo_has_gout = rc == ZNN_OK;
     return rc;
 }
@@ -418,7 +524,7 @@ int znn_conv3d_wgrad(znn_plan* plan, const float* in, const float* gout, float* 
     int rc = check_ws(plan, ZNN_PASS_WGRAD, ws, ws_bytes);
     if (rc != ZNN_OK) return rc;
     if (plan->mode == ZNN_DIRECT) return direct_wgrad(plan->g, in, gout, gw, ws, (hipStream_t)stream);
-    return fft_wgrad(plan->g, in, gout, gw, ws, (hipStream_t)stream);
+    return run_fft_wgrad(plan->g, way_of(plan), in, gout, gw, ws, (hipStream_t)stream);
 }
 
 // ---------------------------------------------------------------- autotuner
@@ -436,13 +542,13 @@ static size_t tune_tensor_bytes(const Geom& g, size_t off[6])
 
 static size_t tune_scratch_bytes(const Geom& g, bool fft_ok)
 {
-    const Fold F = fold_default(g);
+    const FftWay F = fft_way(g);
     size_t m = 0;
     for (int pass = 0; pass < 3; ++pass) {
         size_t d = direct_workspace_bytes(g, pass);
         if (d > m) m = d;
         if (fft_ok) {
-            size_t f = fft_workspace(g, F, pass, false).total;
+            size_t f = fft_pass_bytes(g, F, pass, false);
             if (f > m) m = f;
         }
     }
@@ -493,7 +599,7 @@ int znn_autotune(const znn_conv_desc* desc, void* ws, size_t ws_bytes, void* str
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
         return fail(ZNN_EHIP, "hipEventCreate failed");
     const int warm = 2, timed = 5;
-    const Fold F = fold_default(g);
+    const FftWay F = fft_way(g);
     for (int m = 0; m < 2; ++m)
         for (int p = 0; p < 3; ++p) ms[m][p] = INFINITY;
     rc = ZNN_OK;
@@ -507,9 +613,9 @@ int znn_autotune(const znn_conv_desc* desc, void* ws, size_t ws_bytes, void* str
                     else if (pass == 1) rc = direct_bwd(g, gout, w, gin, scr, s);
                     else rc = direct_wgrad(g, in, gout, gw, scr, s);
                 } else {
-                    if (pass == 0) rc = fft_fwd(g, F, in, w, nullptr, out, scr, nullptr, s);
-                    else if (pass == 1) rc = fft_bwd(g, F, gout, w, nullptr, gin, scr, nullptr, s);
-                    else rc = fft_wgrad(g, in, gout, gw, scr, s);
+                    if (pass == 0) rc = run_fft_fwd(g, F, in, w, nullptr, out, scr, nullptr, s);
+                    else if (pass == 1) rc = run_fft_bwd(g, F, gout, w, nullptr, gin, scr, nullptr, s);
+                    else rc = run_fft_wgrad(g, F, in, gout, gw, scr, s);
                 }
             }
             if (rc != ZNN_OK) break;
@@ -543,19 +649,19 @@ struct RoundNeeds {
 static RoundNeeds round_needs(const Geom& g, bool fft_ok)
 {
     RoundNeeds r = {};
-    const Fold F = fold_default(g);
+    const FftWay F = fft_way(g);
     size_t d = 0, f = 0, fm = 0;
     for (int pass = 0; pass < 3; ++pass) {
         d = std::max(d, direct_workspace_bytes(g, pass));
         if (fft_ok) {
-            f = std::max(f, fft_workspace(g, F, pass, false).total);
-            fm = std::max(fm, fft_workspace(g, F, pass, true).total);
+            f = std::max(f, fft_pass_bytes(g, F, pass, false));
+            fm = std::max(fm, fft_pass_bytes(g, F, pass, true));
         }
     }
     r.total[ZNN_STRATEGY_DIRECT] = d;
     r.total[ZNN_STRATEGY_FFT] = f;
     r.total[ZNN_STRATEGY_FFT_MEMO] = fft_ok
-        ? fm + fft_spectra_bytes(g, F) + align256(sizeof(float2) * (size_t)(g.f + g.fo) * g.svol()) : 0;
+        ? fm + fft_spectra_bytes(g, F.fold) + fft_memo_bytes(g, F) : 0;
     return r;
 }
 
@@ -613,13 +719,13 @@ int znn_autotune_round(const znn_conv_desc* desc, uint64_t memory_budget, void* 
     if ((rc = fill_pattern(w, (long)g.fo * g.f * g.kvol(), 1.0f / std::sqrt((float)(g.f * g.kvol())), s)) != ZNN_OK) return rc;
     if ((rc = fill_pattern(gout, (long)g.fo * g.ovol(), 1.0f, s)) != ZNN_OK) return rc;
     // memoized strategy: [pass workspace | kernel spectra | node spectra]
-    const Fold F = fold_default(g);
+    const FftWay F = fft_way(g);
     size_t memo_ws = 0;
     if (fft_ok)
-        for (int pass = 0; pass < 3; ++pass) memo_ws = std::max(memo_ws, fft_workspace(g, F, pass, true).total);
+        for (int pass = 0; pass < 3; ++pass) memo_ws = std::max(memo_ws, fft_pass_bytes(g, F, pass, true));
     float2* What = (float2*)(scr + memo_ws);
-    float2* Ihat = (float2*)(scr + memo_ws + fft_spectra_bytes(g, F));
-    float2* Ghat = Ihat + (size_t)g.f * g.svol();
+    float2* Ihat = (float2*)(scr + memo_ws + fft_spectra_bytes(g, F.fold));
+    float2* Ghat = memo_gradients(g, F, Ihat);
 
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
@@ -634,14 +740,14 @@ int znn_autotune_round(const znn_conv_desc* desc, uint64_t memory_budget, void* 
                 if (rc == ZNN_OK) rc = direct_bwd(g, gout, w, gin, scr, s);
                 if (rc == ZNN_OK) rc = direct_wgrad(g, in, gout, gw, scr, s);
             } else if (t == ZNN_STRATEGY_FFT) {
-                rc = fft_fwd(g, F, in, w, nullptr, out, scr, nullptr, s);
-                if (rc == ZNN_OK) rc = fft_bwd(g, F, gout, w, nullptr, gin, scr, nullptr, s);
-                if (rc == ZNN_OK) rc = fft_wgrad(g, in, gout, gw, scr, s);
+                rc = run_fft_fwd(g, F, in, w, nullptr, out, scr, nullptr, s);
+                if (rc == ZNN_OK) rc = run_fft_bwd(g, F, gout, w, nullptr, gin, scr, nullptr, s);
+                if (rc == ZNN_OK) rc = run_fft_wgrad(g, F, in, gout, gw, scr, s);
             } else {
-                rc = fft_kernel_spectra(g, F, w, What, s);
-                if (rc == ZNN_OK) rc = fft_fwd(g, F, in, nullptr, What, out, scr, Ihat, s);
-                if (rc == ZNN_OK) rc = fft_bwd(g, F, gout, nullptr, What, gin, scr, Ghat, s);
-                if (rc == ZNN_OK) rc = fft_wgrad_from_spectra(g, Ihat, Ghat, gw, scr, s);
+                rc = run_kernel_spectra(g, F, w, What, s);
+                if (rc == ZNN_OK) rc = run_fft_fwd(g, F, in, nullptr, What, out, scr, Ihat, s);
+                if (rc == ZNN_OK) rc = run_fft_bwd(g, F, gout, nullptr, What, gin, scr, Ghat, s);
+                if (rc == ZNN_OK) rc = run_fft_wgrad_from_spectra(g, F, Ihat, Ghat, gw, scr, s);
             }
         }
         if (rc != ZNN_OK) break;

@@ -1,0 +1,23 @@
+// FFT method on overlapping tiles (fft_tile.hip): the tiling of a layer and the three passes on it.
+#pragma once
+
+#include "znn_internal.h"
+
+namespace znn {
+
+// the library's choice of tile lengths for a layer whose kernel spectra may take `spectra_bytes` (on = false: none does)
+Tiling tile_search(const Geom& g, size_t spectra_bytes);
+size_t tile_kernel_bytes(const Geom& g, const Tiling& L);               // spectra of all kernels
+size_t tile_node_bytes(const Geom& g, const Tiling& L, int maps);       // spectra of `maps` images or gradients
+size_t tile_workspace_bytes(const Geom& g, const Tiling& L, int pass, bool resident);
+int tile_kernel_spectra(const Geom& g, const Tiling& L, const float* w, float2* What, hipStream_t s);
+// ws_bytes: what the caller's workspace holds; results are taken in as many chunks of maps as it asks for
+int tile_fwd(const Geom& g, const Tiling& L, const float* in, const float* w, const float2* resident, float* out,
+             void* ws, size_t ws_bytes, float2* memo_in, hipStream_t s);
+int tile_bwd(const Geom& g, const Tiling& L, const float* gout, const float* w, const float2* resident, float* gin,
+             void* ws, size_t ws_bytes, float2* memo_gout, hipStream_t s);
+int tile_wgrad(const Geom& g, const Tiling& L, const float* in, const float* gout, float* gw, void* ws, hipStream_t s);
+int tile_wgrad_from_spectra(const Geom& g, const Tiling& L, const float2* U, const float2* V, float* gw, void* scratch,
+                            hipStream_t s);
+
+}  // namespace znn

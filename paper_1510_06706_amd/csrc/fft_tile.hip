@@ -1,0 +1,1130 @@
+// FFT method on overlapping tiles (overlap-save / overlap-add).
+//
+// The transform of a whole volume needs one product per edge and frequency of the VOLUME; cut into tiles of
+// M voxels per axis that advance by B = M - S + 1 (S = s (k - 1) + 1: span of the kernel), a layer needs one
+// product per edge, tile and frequency of a TILE instead.  The number of products grows by (M / B)^3, but
+// the kernel spectra shrink by the ratio of the volumes (96^3 images, 7^3 kernels, M = 24: 0.86 GB instead of 52 GB,
+// or of 3.8 GB transformed along two axes), the tile index becomes a matrix dimension -- the multiply-accumulate of
+// a frequency is a matrix product [f'][f] x [f][tiles], that of the kernel gradient [f'][tiles] x [tiles][f] --
+// and matrix products run on the matrix cores, with every spectrum element read once per pass instead of once
+// per result node.  A tile's 3D transform fits one workgroup's LDS, so it is one trip through memory.
+//
+//   forward   out on [t B, t B + B) = crop_{[S-1, M)} IFFT( sum_i W^[j][i] U^[i][t] ),   U = in on [t B, t B + M)
+//   backward  gin += at t B           IFFT( sum_j conj(W^[j][i]) V^[j][t] ),             V = gout on [t B, t B + B) from S - 1 on
+//   gradient  gw  = lags s a of       IFFT( sum_t V^[j][t] conj(U^[i][t]) )
+// (derivation: circular products of length M are free of wrap-around because B + S - 1 = M).
+//
+// Spectra are stored in blocks of 16 frequencies, [frequency block][map][tile][16]: a tile's transform stores full
+// 128-byte lines, and the matrix product of a block reads its operands as runs of 128 bytes.
+#include "fft_reg_impl.h"
+#include "fft_tile.h"
+
+#include <algorithm>
+#include <cmath>
+
+namespace znn {
+
+namespace {
+
+constexpr int kTileThreads = 512;           // most threads of a transform workgroup
+constexpr int kTileEntries = 16;            // most tiles of a transform workgroup
+constexpr size_t kTileLds = 60 * 1024;   // LDS of a transform workgroup: two fit a compute unit
+
+// ---------------------------------------------------------------- transforms of tiles
+// An entry is one tile of one map (for kernels: one kernel).  Axis order z, y, x everywhere.
+struct TileGeom {
+    int M[3], Mxh;              // transform lengths, M[2] / 2 + 1
+    int T[3], hop[3];           // tiles per axis, voxels from one tile to the next
+    int n[3];                   // extents of the real maps
+    int w[3];                   // samples a tile holds per axis: element o + i * sp of the transform, i < w
+    int o[3], sp[3];
+    unsigned mask[3];           // bit m: element m holds a sample
+    int entries, per_wg;        // entries in all, entries per workgroup
+    int vw, clip;               // samples per memory access along x: 4, 2 or 1; tiles reach beyond the map
+    int rows_per_step, step[3]; // rows a workgroup's threads cover at a time, and that as (entries, z, y)
+    FastDiv fw[3], fwx, fMxh, fcol;     // divisions by w, w[2] / vw, Mxh, My * Mxh
+};
+struct TileFwd { const float* src; float2* dst; TileGeom G; };
+struct TileInv { const float2* src; float* dst; TileGeom G; float scale; int splits; long split_stride; };
+
+struct EntryInfo { long base; int v[3]; int ok; };
+
+// where an entry's samples lie in the real maps, and how many of them per axis exist
+__device__ __forceinline__ EntryInfo entry_info(const TileGeom& G, int e)
+{
+    EntryInfo I;
+    I.ok = e < G.entries;
+    if (!I.ok) { I.base = 0; I.v[0] = I.v[1] = I.v[2] = 0; return I; }
+    const int T = G.T[0] * G.T[1] * G.T[2];
+    const int map = e / T;
+    int t = e - map * T;
+    const int tz = t / (G.T[1] * G.T[2]);
+    t -= tz * G.T[1] * G.T[2];
+    const int ty = t / G.T[2], tx = t - ty * G.T[2];
+    const int z0 = tz * G.hop[0], y0 = ty * G.hop[1], x0 = tx * G.hop[2];
+    I.base = (((long)map * G.n[0] + z0) * G.n[1] + y0) * (long)G.n[2] + x0;
+    I.v[0] = min(G.w[0], G.n[0] - z0);
+    I.v[1] = min(G.w[1], G.n[1] - y0);
+    I.v[2] = min(G.w[2], G.n[2] - x0);
+    return I;
+}
+
+template <int M, int DIR>
+__device__ __forceinline__ void fft_inplace(float2 (&v)[M])
+{
+    if constexpr (M > 1) {
+        float2 w[M];
+        passes<M, DIR, M, 1>(v, w);
+        if constexpr (count_passes(M) % 2 == 1) {
+#pragma unroll
+            for (int m = 0; m < M; ++m) v[m] = w[m];
+        }
+    }
+}
+
+// real row of M samples at `row` (masked) -> M/2 + 1 coefficients in the same words, by one thread
+template <int M, bool FULL>
+__device__ __forceinline__ void row_r2c(float2* row, unsigned mask)
+{
+    constexpr int H = M / 2;
+    float2 Z[H];
+#pragma unroll
+    for (int m = 0; m < H; ++m) {
+        const float2 v = row[m];
+        Z[m].x = FULL || ((mask >> (2 * m)) & 1u) ? v.x : 0.f;
+        Z[m].y = FULL || ((mask >> (2 * m + 1)) & 1u) ? v.y : 0.f;
+    }
+    fft_inplace<H, -1>(Z);
+    row[0] = make_float2(Z[0].x + Z[0].y, 0.f);
+    row[H] = make_float2(Z[0].x - Z[0].y, 0.f);
+#pragma unroll
+    for (int k = 1; k < H; ++k) {
+        const float2 a = Z[k], b = Z[H - k];
+        const float2 e = make_float2(a.x + b.x, a.y - b.y);
+        const float2 d = make_float2(a.x - b.x, a.y + b.y);
+        const float wc = TwTable<M>::t.c[k], ws = -TwTable<M>::t.s[k];
+        row[k] = make_float2(0.5f * (e.x + wc * d.y + ws * d.x), 0.5f * (e.y + ws * d.y - wc * d.x));
+    }
+}
+
+// M/2 + 1 coefficients -> M real samples (times M) in the same words
+template <int M>
+__device__ __forceinline__ void row_c2r(float2* row)
+{
+    constexpr int H = M / 2;
+    float2 X[H + 1], Z[H];
+#pragma unroll
+    for (int k = 0; k <= H; ++k) X[k] = row[k];
+    Z[0] = make_float2(X[0].x + X[H].x, X[0].x - X[H].x);
+#pragma unroll
+    for (int k = 1; k < H; ++k) {
+        const float2 a = X[k], b = X[H - k];
+        const float2 e = make_float2(a.x + b.x, a.y - b.y);            // X[k] + conj X[H-k]
+        const float2 d = make_float2(a.x - b.x, a.y + b.y);            // X[k] - conj X[H-k]
+        const float wc = TwTable<M>::t.c[k], ws = TwTable<M>::t.s[k];  // w^-k
+        Z[k] = make_float2(e.x - wc * d.y - ws * d.x, e.y + wc * d.x - ws * d.y);     // e + i w^-k d
+    }
+    fft_inplace<H, +1>(Z);
+#pragma unroll
+    for (int m = 0; m < H; ++m) row[m] = Z[m];
+}
+
+template <int M, bool FULL>
+__device__ __forceinline__ void rows_r2c(float2* lds, const TileGeom& G)
+{
+    const int rows = G.per_wg * G.w[0] * G.w[1];
+    for (int u = threadIdx.x; u < rows; u += blockDim.x) {
+        const int q = (int)fdiv((unsigned)u, G.fw[1]), y = u - q * G.w[1];
+        const int b = (int)fdiv((unsigned)q, G.fw[0]), z = q - b * G.w[0];
+        row_r2c<M, FULL>(lds + ((b * G.w[0] + z) * G.M[1] + G.o[1] + y * G.sp[1]) * G.Mxh, G.mask[2]);
+    }
+}
+
+template <int M>
+__device__ __forceinline__ void rows_c2r(float2* lds, const TileGeom& G)
+{
+    const int rows = G.per_wg * G.w[0] * G.w[1];
+    for (int u = threadIdx.x; u < rows; u += blockDim.x) {
+        const int q = (int)fdiv((unsigned)u, G.fw[1]), y = u - q * G.w[1];
+        const int b = (int)fdiv((unsigned)q, G.fw[0]), z = q - b * G.w[0];
+        row_c2r<M>(lds + ((b * G.w[0] + z) * G.M[1] + G.o[1] + y * G.sp[1]) * G.Mxh);
+    }
+}
+
+// transforms along y, in place, of the planes z that hold samples; forward reads, inverse writes only the
+// rows of mask[1]
+template <int M, int DIR, bool FULL>
+__device__ __forceinline__ void columns_y(float2* lds, const TileGeom& G)
+{
+    const int cols = G.per_wg * G.w[0] * G.Mxh;
+    for (int u = threadIdx.x; u < cols; u += blockDim.x) {
+        const int q = (int)fdiv((unsigned)u, G.fMxh), k = u - q * G.Mxh;
+        const int b = (int)fdiv((unsigned)q, G.fw[0]), z = q - b * G.w[0];
+        float2* c = lds + (b * G.w[0] + z) * G.M[1] * G.Mxh + k;
+        float2 v[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+            v[m] = FULL || ((G.mask[1] >> m) & 1u) ? c[m * G.Mxh] : make_float2(0.f, 0.f);
+        fft_inplace<M, DIR>(v);
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+            if (DIR < 0 || ((G.mask[1] >> m) & 1u)) c[m * G.Mxh] = v[m];
+    }
+}
+
+// Frequency w = m P + p of an entry lies at block w / 16, element w % 16.  (m P) mod 16 takes four values (P = My Mxh is
+// a multiple of 4), so a thread keeps four byte offsets and the rest is uniform: block (m P) / 16 is a scalar address.
+struct BlockOffsets {
+    unsigned at[4];
+    __device__ __forceinline__ BlockOffsets(int p, int P, unsigned blk_bytes)
+    {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int t = p + ((r * P) & 15);
+            at[r] = (unsigned)(t >> 4) * blk_bytes + (unsigned)(t & 15) * 8u;
+        }
+    }
+};
+
+// forward transforms along z and the store of the spectra
+template <int M, bool FULL>
+__device__ __forceinline__ void columns_z_store(const float2* lds, float2* dst, const TileGeom& G, int e0)
+{
+    const int P = G.M[1] * G.Mxh;
+    const int cols = G.per_wg * P;
+    const unsigned blk = (unsigned)G.entries * 128u;
+    for (int u = threadIdx.x; u < cols; u += blockDim.x) {
+        const int b = (int)fdiv((unsigned)u, G.fcol), p = u - b * P;
+        if (e0 + b >= G.entries) break;
+        const float2* c = lds + b * G.w[0] * P + p;
+        float2 v[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            v[m] = make_float2(0.f, 0.f);
+            if (FULL || ((G.mask[0] >> m) & 1u)) { v[m] = *c; c += P; }
+        }
+        fft_inplace<M, -1>(v);
+        char* d = reinterpret_cast<char*>(dst + (long)e0 * 16);
+        const BlockOffsets off(p, P, blk);
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+            *reinterpret_cast<float2*>(d + (long)((m * P) >> 4) * blk + (off.at[m & 3] + (unsigned)b * 128u)) = v[m];
+    }
+}
+
+// load of the spectra (splits: partial sums to be added, in ascending order) and inverse transforms along z
+template <int M, bool SPLIT>
+__device__ __forceinline__ void load_columns_z(float2* lds, const TileInv& I, int e0)
+{
+    const TileGeom& G = I.G;
+    const int P = G.M[1] * G.Mxh;
+    const int cols = G.per_wg * P;
+    const unsigned blk = (unsigned)G.entries * 128u;
+    for (int u = threadIdx.x; u < cols; u += blockDim.x) {
+        const int b = (int)fdiv((unsigned)u, G.fcol), p = u - b * P;
+        if (e0 + b >= G.entries) break;
+        const char* s = reinterpret_cast<const char*>(I.src + (long)e0 * 16);
+        const BlockOffsets off(p, P, blk);
+        float2 v[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+            v[m] = *reinterpret_cast<const float2*>(s + (long)((m * P) >> 4) * blk + (off.at[m & 3] + (unsigned)b * 128u));
+        for (int r = 1; SPLIT && r < I.splits; ++r) {
+            s += I.split_stride * 8;
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+                v[m] = cadd(v[m], *reinterpret_cast<const float2*>(s + (long)((m * P) >> 4) * blk + (off.at[m & 3] + (unsigned)b * 128u)));
+        }
+        fft_inplace<M, +1>(v);
+        float2* c = lds + b * G.w[0] * P + p;
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+            if ((G.mask[0] >> m) & 1u) { *c = v[m]; c += P; }
+    }
+}
+
+// 2D layers have no z transform: the spectra go from or to LDS as they are
+__device__ __forceinline__ void store_plane(const float2* lds, float2* dst, const TileGeom& G, int e0)
+{
+    const int P = G.M[1] * G.Mxh, total = min(G.per_wg, G.entries - e0) * P;
+#pragma unroll 8
+    for (int u = threadIdx.x; u < total; u += blockDim.x) {
+        const int b = (int)fdiv((unsigned)u, G.fcol), p = u - b * P;
+        dst[((long)(p >> 4) * G.entries + e0 + b) * 16 + (p & 15)] = lds[u];
+    }
+}
+
+__device__ __forceinline__ void load_plane(float2* lds, const TileInv& I, int e0)
+{
+    constexpr int kLoads = 16;
+    const TileGeom& G = I.G;
+    const int P = G.M[1] * G.Mxh, total = min(G.per_wg, G.entries - e0) * P;
+    for (int u0 = threadIdx.x; u0 < total; u0 += kLoads * blockDim.x) {
+        float2 v[kLoads];
+        const float2* s = I.src;
+        for (int r = 0; r < I.splits; ++r, s += I.split_stride) {
+            float2 t[kLoads];
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) {
+                const int u = min(u0 + i * (int)blockDim.x, total - 1);
+                const int b = (int)fdiv((unsigned)u, G.fcol), p = u - b * P;
+                t[i] = s[((long)(p >> 4) * G.entries + e0 + b) * 16 + (p & 15)];
+            }
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) v[i] = r ? cadd(v[i], t[i]) : t[i];
+        }
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i)
+            if (u0 + i * (int)blockDim.x < total) lds[u0 + i * blockDim.x] = v[i];
+    }
+}
+
+// The samples of the workgroup's entries travel VW at a time (VW divides the window along x), kBatch accesses per thread
+// in flight: a workgroup waits for memory once or twice, not once per few rows.
+constexpr int kBatch = 12;
+typedef float floatu4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float floatu2 __attribute__((ext_vector_type(2), aligned(4)));
+template <int VW> struct VecOf;
+template <> struct VecOf<4> { typedef floatu4 type; };
+template <> struct VecOf<2> { typedef floatu2 type; };
+template <> struct VecOf<1> { typedef float type; };
+
+// A thread's x position stays fixed; its rows are `rows_per_step` apart, and (entry, z, y) are stepped in mixed radix
+// without divisions (32-bit multiplications by constants of the launch would run at a quarter of the rate).
+struct RowWalk {
+    int x, b, z, y;
+    bool idle;
+    __device__ __forceinline__ RowWalk(const TileGeom& G, int vw)
+    {
+        const int t = threadIdx.x, r = (int)fdiv((unsigned)t, G.fwx);
+        x = (t - r * (G.w[2] / vw)) * vw;
+        const int q = (int)fdiv((unsigned)r, G.fw[1]);
+        y = r - q * G.w[1];
+        b = (int)fdiv((unsigned)q, G.fw[0]);
+        z = q - b * G.w[0];
+        idle = r >= G.rows_per_step;
+    }
+    __device__ __forceinline__ void step(const TileGeom& G)
+    {
+        y += G.step[2];
+        const int cy = y >= G.w[1] ? 1 : 0;
+        y -= cy ? G.w[1] : 0;
+        z += G.step[1] + cy;
+        const int cz = z >= G.w[0] ? 1 : 0;
+        z -= cz ? G.w[0] : 0;
+        b += G.step[0] + cz;
+    }
+    __device__ __forceinline__ int lds_at(const TileGeom& G) const
+    {
+        const int row = (int)__umul24(__umul24(b, G.w[0]) + z, G.M[1]) + G.o[1] + (int)__umul24(y, G.sp[1]);
+        return (int)__umul24(row, 2 * G.Mxh) + G.o[2] + x * G.sp[2];
+    }
+    // samples of the row from x on that exist
+    __device__ __forceinline__ int left(const EntryInfo& E) const { return y < E.v[1] && z < E.v[0] ? E.v[2] - x : 0; }
+    __device__ __forceinline__ long at(const TileGeom& G, const EntryInfo& E) const
+    {
+        return E.base + ((long)(z * G.n[1] + y) * G.n[2] + x);
+    }
+};
+
+// All loads of a batch are unconditional (a branch around one makes the compiler wait for it before the next: 25 000
+// clocks per tile instead of 2 500): coordinates outside the map are clamped into it and the values replaced by zeros.
+// CLIP: some tiles of the launch reach beyond the map; a row that ends inside the vector is loaded from further left
+// (every tile holds at least VW samples per row) and shifted.
+template <int VW, bool CLIP>
+__device__ __forceinline__ void load_samples(float* lf, const float* __restrict__ src, const TileGeom& G, const EntryInfo* info)
+{
+    typedef typename VecOf<VW>::type vec;
+    RowWalk R(G, VW);
+    if (R.idle) return;
+    while (R.b < G.per_wg) {
+        vec v[kBatch];
+        int at[kBatch];                 // LDS word, and from bit 16 on the samples that exist; -1: no row left
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            const EntryInfo& E = info[min(R.b, G.per_wg - 1)];
+            at[i] = R.b < G.per_wg ? R.lds_at(G) : -1;
+            if constexpr (CLIP) {
+                const int left = min(VW, max(0, R.left(E)));
+                if (R.b < G.per_wg) at[i] |= left << 16;
+                const int z = max(0, min(R.z, E.v[0] - 1)), y = max(0, min(R.y, E.v[1] - 1));
+                const int x = left > 0 ? R.x - (VW - left) : 0;
+                v[i] = *reinterpret_cast<const vec*>(src + E.base + ((long)(z * G.n[1] + y) * G.n[2] + x));
+            } else {
+                v[i] = *reinterpret_cast<const vec*>(src + (R.b < G.per_wg ? R.at(G, E) : 0));
+            }
+            R.step(G);
+        }
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)
+            if (at[i] >= 0) {
+                float t[VW];
+                __builtin_memcpy(t, &v[i], sizeof(vec));
+                if constexpr (CLIP) {
+                    const int left = at[i] >> 16, d = VW - left;
+                    if constexpr (VW >= 2) {
+#pragma unroll
+                        for (int bit = 1; bit < VW; bit *= 2)
+#pragma unroll
+                            for (int c = 0; c + bit < VW; ++c) t[c] = d & bit ? t[c + bit] : t[c];      // ascending: reads what is not yet shifted
+                    }
+#pragma unroll
+                    for (int c = 0; c < VW; ++c) t[c] = c < left ? t[c] : 0.f;
+                }
+#pragma unroll
+                for (int c = 0; c < VW; ++c) lf[(at[i] & 0xffff) + c * G.sp[2]] = t[c];
+            }
+    }
+}
+
+template <int VW>
+__device__ __forceinline__ void store_samples(const float* lf, float* dst, float scale, const TileGeom& G, const EntryInfo* info)
+{
+    typedef typename VecOf<VW>::type vec;
+    RowWalk R(G, VW);
+    if (R.idle) return;
+#pragma unroll 4
+    while (R.b < G.per_wg) {
+        const EntryInfo& E = info[R.b];
+        const int at = R.lds_at(G), left = R.left(E);
+        float* p = dst + R.at(G, E);
+        float v[VW];
+#pragma unroll
+        for (int c = 0; c < VW; ++c) v[c] = scale * lf[at + c * G.sp[2]];
+        if (left >= VW) {
+            vec t;
+            __builtin_memcpy(&t, v, sizeof(vec));
+            *reinterpret_cast<vec*>(p) = t;
+        } else {
+#pragma unroll
+            for (int c = 0; c < VW; ++c)
+                if (c < left) p[c] = v[c];
+        }
+        R.step(G);
+    }
+}
+
+// one pass of a workgroup, by the transform length of its axis (LONG: the kernel instance that also takes length 32)
+#define ZNN_TILE_SWITCH(LONG, L, CALL1, CALL)                             \
+    switch (L) {                                                          \
+        case 1: CALL1; break;                                             \
+        case 8: CALL(8); break;                                           \
+        case 12: CALL(12); break;                                         \
+        case 16: CALL(16); break;                                         \
+        case 20: CALL(20); break;                                         \
+        case 24: CALL(24); break;                                         \
+        default: if constexpr (LONG) CALL(32); break;                     \
+    }
+
+typedef __attribute__((address_space(1))) const void* global_cptr;
+typedef __attribute__((address_space(3))) void* lds_ptr;
+
+// Workgroup barrier for data in LDS only: __syncthreads() would also wait for every load and store in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Bound by the store of the spectra (8 bytes per frequency) and the transforms; the tile's samples come in as rows of
+// neighbouring lanes, one row, then one column per thread is transformed in registers.
+template <bool LONG, bool FULL>
+__global__ void __launch_bounds__(kTileThreads, LONG ? 2 : 4) k_tile_fwd(TileFwd A)
+{
+    extern __shared__ float2 lds[];
+    __shared__ EntryInfo info[kTileEntries];
+    const TileGeom& G = A.G;
+    float* lf = reinterpret_cast<float*>(lds);
+    const int e0 = blockIdx.x * G.per_wg;
+    if ((int)threadIdx.x < G.per_wg) info[threadIdx.x] = entry_info(G, e0 + threadIdx.x);
+    lds_barrier();
+    if (G.clip) {
+        if (G.vw == 4) load_samples<4, true>(lf, A.src, G, info);
+        else if (G.vw == 2) load_samples<2, true>(lf, A.src, G, info);
+        else load_samples<1, true>(lf, A.src, G, info);
+    } else {
+        if (G.vw == 4) load_samples<4, false>(lf, A.src, G, info);
+        else if (G.vw == 2) load_samples<2, false>(lf, A.src, G, info);
+        else load_samples<1, false>(lf, A.src, G, info);
+    }
+    lds_barrier();
+#define ZNN_CALL(L) rows_r2c<L, FULL>(lds, G)
+    ZNN_TILE_SWITCH(LONG, G.M[2], (void)0, ZNN_CALL)
+#undef ZNN_CALL
+    lds_barrier();
+    if (G.M[1] > 1) {
+#define ZNN_CALL(L) columns_y<L, -1, FULL>(lds, G)
+        ZNN_TILE_SWITCH(LONG, G.M[1], (void)0, ZNN_CALL)
+#undef ZNN_CALL
+        lds_barrier();
+    }
+#define ZNN_CALL(L) columns_z_store<L, FULL>(lds, A.dst, G, e0)
+    ZNN_TILE_SWITCH(LONG, G.M[0], store_plane(lds, A.dst, G, e0), ZNN_CALL)
+#undef ZNN_CALL
+}
+
+template <bool LONG, bool SPLIT>
+__global__ void __launch_bounds__(kTileThreads, LONG ? 2 : 4) k_tile_inv(TileInv A)
+{
+    extern __shared__ float2 lds[];
+    __shared__ EntryInfo info[kTileEntries];
+    const TileGeom& G = A.G;
+    const float* lf = reinterpret_cast<const float*>(lds);
+    const int e0 = blockIdx.x * G.per_wg;
+    if ((int)threadIdx.x < G.per_wg) info[threadIdx.x] = entry_info(G, e0 + threadIdx.x);
+#define ZNN_CALL(L) (load_columns_z<L, SPLIT>)(lds, A, e0)
+    ZNN_TILE_SWITCH(LONG, G.M[0], load_plane(lds, A, e0), ZNN_CALL)
+#undef ZNN_CALL
+    lds_barrier();
+    if (G.M[1] > 1) {
+#define ZNN_CALL(L) columns_y<L, +1, true>(lds, G)
+        ZNN_TILE_SWITCH(LONG, G.M[1], (void)0, ZNN_CALL)
+#undef ZNN_CALL
+        lds_barrier();
+    }
+#define ZNN_CALL(L) rows_c2r<L>(lds, G)
+    ZNN_TILE_SWITCH(LONG, G.M[2], (void)0, ZNN_CALL)
+#undef ZNN_CALL
+    lds_barrier();
+    if (G.vw == 4) store_samples<4>(lf, A.dst, A.scale, G, info);
+    else if (G.vw == 2) store_samples<2>(lf, A.dst, A.scale, G, info);
+    else store_samples<1>(lf, A.dst, A.scale, G, info);
+}
+
+// gin[x] = sum over the tiles that cover x, in ascending order (overlap-add).  Bound by the read of the tiles.
+struct TileAdd { const float* src; float* dst; int M[3], T[3], hop[3], n[3]; FastDiv fhop[3], fnx; int xy, zs; };
+
+// tiles lo .. hi along axis d cover coordinate c
+__device__ __forceinline__ void tiles_over(const TileAdd& A, int d, int c, int& lo, int& hi)
+{
+    hi = min((int)fdiv((unsigned)c, A.fhop[d]), A.T[d] - 1);
+    const int first = c - A.M[d] + 1;                   // first tile start that still covers c
+    lo = first <= 0 ? 0 : (int)fdiv((unsigned)(first + A.hop[d] - 1), A.fhop[d]);
+}
+
+// At most two tiles per axis (M <= 2 B): a thread keeps the places of its (y, x) in the four tiles of a layer of tiles --
+// places that do not exist repeat one that does, with weight zero, so that no load is conditional -- and walks zs values of
+// z, whose one or two layers are uniform: 520 -> 290 us for 125 tiles of 24^3 of 120 maps against one thread per voxel.
+__global__ void __launch_bounds__(256) k_tile_add2(TileAdd A)
+{
+    const int u = blockIdx.x * 256 + threadIdx.x;
+    if (u >= A.xy) return;
+    const long map = blockIdx.z;
+    const int y = (int)fdiv((unsigned)u, A.fnx), x = u - y * A.n[2];
+    int blo, bhi, dlo, dhi;
+    tiles_over(A, 1, y, blo, bhi);
+    tiles_over(A, 2, x, dlo, dhi);
+    const int vol = A.M[0] * A.M[1] * A.M[2];
+    int at[4];
+    float weight[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int b = min(blo + (i >> 1), bhi), d = min(dlo + (i & 1), dhi);
+        at[i] = (b * A.T[2] + d) * vol + (y - b * A.hop[1]) * A.M[2] + (x - d * A.hop[2]);
+        weight[i] = blo + (i >> 1) <= bhi && dlo + (i & 1) <= dhi ? 1.f : 0.f;
+    }
+    const long layer = (long)A.T[1] * A.T[2] * vol;
+    const float* base = A.src + map * (A.T[0] * layer);
+    const int z1 = min(A.n[0], ((int)blockIdx.y + 1) * A.zs);
+#pragma unroll 4
+    for (int z = blockIdx.y * A.zs; z < z1; ++z) {
+        int lo, hi;
+        tiles_over(A, 0, z, lo, hi);
+        const float* p = base + lo * layer + (z - lo * A.hop[0]) * (A.M[1] * A.M[2]);
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum = fmaf(weight[i], p[at[i]], sum);
+        if (hi > lo) {
+            p = base + hi * layer + (z - hi * A.hop[0]) * (A.M[1] * A.M[2]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sum = fmaf(weight[i], p[at[i]], sum);
+        }
+        A.dst[(map * A.n[0] + z) * (long)A.xy + u] = sum;
+    }
+}
+
+__global__ void __launch_bounds__(256) k_tile_add(TileAdd A)
+{
+    const int u = blockIdx.x * 256 + threadIdx.x;
+    if (u >= A.xy) return;
+    const int z = blockIdx.y;
+    const long map = blockIdx.z;
+    const int y = (int)fdiv((unsigned)u, A.fnx), x = u - y * A.n[2];
+    int lo[3], hi[3];
+    tiles_over(A, 0, z, lo[0], hi[0]);
+    tiles_over(A, 1, y, lo[1], hi[1]);
+    tiles_over(A, 2, x, lo[2], hi[2]);
+    const long vol = (long)A.M[0] * A.M[1] * A.M[2];
+    const float* base = A.src + map * ((long)A.T[0] * A.T[1] * A.T[2] * vol);
+    float sum = 0.f;
+    for (int a = lo[0]; a <= hi[0]; ++a)
+        for (int b = lo[1]; b <= hi[1]; ++b)
+            for (int d = lo[2]; d <= hi[2]; ++d)
+                sum += base[(((long)a * A.T[1] + b) * A.T[2] + d) * vol +
+                            ((z - a * A.hop[0]) * A.M[1] + (y - b * A.hop[1])) * A.M[2] + (x - d * A.hop[2])];
+    A.dst[(map * A.n[0] + z) * (long)A.xy + u] = sum;
+}
+
+// ---------------------------------------------------------------- matrix products per frequency
+// C[m][n] = sum_k A[m][k] B[k][n] (CONJ: conj(A)) for every frequency, on v_mfma_f32_16x16x4_f32.  A workgroup owns
+// 16 MT x 16 NT results of a block of 16 frequencies, each of its four waves four of the frequencies (real and imaginary
+// part in accumulators of their own).  A chunk of four k -- the depth of one MFMA -- of both operands is copied to LDS as
+// it lies in memory (runs of 16 frequencies = 128 bytes; 16 bytes per lane, no registers) while the chunk before it is
+// used.  A lane reads the two frequencies of its row and k with one 16-byte access; the eight 16-byte pieces of a run are
+// stored in an order that depends on the row (piece ^ (row / 2) % 8), so that sixteen rows cover all banks, and the results
+// leave through LDS in the same arrangement, as full lines.  All workgroups of a block run on one XCD next to each
+// other in time.
+// Tried: operands straight from global memory to the lanes of v_mfma_f32_4x4x1_16B_f32, whose sixteen blocks are the
+// sixteen frequencies: neighbouring lanes then lie in different rows, 64 cache accesses per load, 3.3 ms per product
+// of 96^3 images and 120 x 120 maps; the same through LDS: 1.42 ms (the short MFMAs issue at 80 % of their rate, and the
+// results leave as 8-byte pieces).
+struct TileProduct {
+    const float2* A; const float2* B; float2* C;
+    long blkA, blkB, blkC, splitC;      // elements from one frequency block (split of k) to the next
+    int am, ak, bn, bk, cm, cn;         // element strides
+    int M, N, K;
+    int gm, gn, splits, blocks;         // workgroups along m and n of a block, splits of k, frequency blocks
+    int run;                            // workgroups per XCD
+};
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kChunk = 4;
+
+template <int MT, int NT, bool CONJ>
+__global__ void __launch_bounds__(256, 2) k_tile_product(TileProduct P)
+{
+    constexpr int RA = 16 * MT, RB = 16 * NT;               // rows of A and B in LDS
+    constexpr int LA = RA * kChunk / 8 / 4, LB = RB * kChunk / 8 / 4;       // copies of 1 KiB (8 rows) per wave and chunk
+    __shared__ float4 buf0[(RA + RB) * kChunk * 8];
+    __shared__ float4 buf1[(RA + RB) * kChunk * 8];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // consecutive workgroups go to the eight XCDs in turn: each XCD takes a contiguous run of (block, tile) pairs
+    const int per = P.gm * P.gn * P.splits;
+    const int id = (blockIdx.x & 7) * P.run + (blockIdx.x >> 3);
+    const int blk = id / per;
+    if (blk >= P.blocks) return;
+    int q = id - blk * per;
+    const int split = q / (P.gm * P.gn);
+    q -= split * P.gm * P.gn;
+    const int gi = q / P.gn, gj = q - gi * P.gn;
+    const int m0 = gi * RA, n0 = gj * RB;
+    const int kper = ((P.K + P.splits - 1) / P.splits + kChunk - 1) / kChunk * kChunk;
+    const int k0 = split * kper, k1 = min(P.K, k0 + kper);
+
+    const char* A = reinterpret_cast<const char*>(P.A + blk * P.blkA);
+    const char* B = reinterpret_cast<const char*>(P.B + blk * P.blkB);
+    // copy c of a chunk: k = c / (R / 8), rows 8 (c % (R / 8)) .. + 7; the lane fills piece slot lane % 8 of row lane / 8
+    unsigned ao[LA], bo[LB];
+#pragma unroll
+    for (int c = 0; c < LA; ++c) {
+        const int row = 8 * ((wave * LA + c) % (RA / 8)) + (lane >> 3);
+        ao[c] = (unsigned)(min(m0 + row, P.M - 1) * P.am) * 8u + (unsigned)(((lane & 7) ^ ((row >> 1) & 7)) * 16);
+    }
+#pragma unroll
+    for (int c = 0; c < LB; ++c) {
+        const int row = 8 * ((wave * LB + c) % (RB / 8)) + (lane >> 3);
+        bo[c] = (unsigned)(min(n0 + row, P.N - 1) * P.bn) * 8u + (unsigned)(((lane & 7) ^ ((row >> 1) & 7)) * 16);
+    }
+    auto copy = [&](float4* buf, int k) {
+#pragma unroll
+        for (int c = 0; c < LA; ++c) {
+            const int kk = min(k + (wave * LA + c) / (RA / 8), k1 - 1);
+            __builtin_amdgcn_global_load_lds((global_cptr)(A + (long)kk * (P.ak * 8) + ao[c]), (lds_ptr)(buf + (wave * LA + c) * 64), 16, 0, 0);
+        }
+#pragma unroll
+        for (int c = 0; c < LB; ++c) {
+            const int kk = min(k + (wave * LB + c) / (RB / 8), k1 - 1);
+            __builtin_amdgcn_global_load_lds((global_cptr)(B + (long)kk * (P.bk * 8) + bo[c]),
+                                             (lds_ptr)(buf + RA * kChunk * 8 + (wave * LB + c) * 64), 16, 0, 0);
+        }
+    };
+
+    f32x4 re[4][MT][NT], im[4][MT][NT];                     // [frequency]
+#pragma unroll
+    for (int f = 0; f < 4; ++f)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) re[f][i][t] = im[f][i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int row = lane & 15, kl = lane >> 4;
+    const int at0 = row * 8 + ((2 * wave) ^ (row >> 1)), at1 = row * 8 + ((2 * wave + 1) ^ (row >> 1));
+    auto chunk = [&](const float4* buf, int k) {
+        const float4* pa = buf + kl * RA * 8;
+        const float4* pb = buf + (RA * kChunk + kl * RB) * 8;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {                       // frequencies 2 h, 2 h + 1 of the wave
+            const int at = h ? at1 : at0;
+            float4 a[MT], b[NT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[i] = pa[i * 128 + at];
+            if (k + kChunk > k1 && k + kl >= k1) {          // behind the last k
+#pragma unroll
+                for (int i = 0; i < MT; ++i) a[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+#pragma unroll
+            for (int t = 0; t < NT; ++t) b[t] = pb[t * 128 + at];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const float n0_ = -a[i].y, n1_ = -a[i].w;
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    f32x4 &r0 = re[2 * h][i][t], &i0 = im[2 * h][i][t], &r1 = re[2 * h + 1][i][t], &i1 = im[2 * h + 1][i][t];
+                    r0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].x, b[t].x, r0, 0, 0, 0);
+                    i0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].x, b[t].y, i0, 0, 0, 0);
+                    r1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].z, b[t].z, r1, 0, 0, 0);
+                    i1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].z, b[t].w, i1, 0, 0, 0);
+                    r0 = __builtin_amdgcn_mfma_f32_16x16x4f32(CONJ ? a[i].y : n0_, b[t].y, r0, 0, 0, 0);
+                    i0 = __builtin_amdgcn_mfma_f32_16x16x4f32(CONJ ? n0_ : a[i].y, b[t].x, i0, 0, 0, 0);
+                    r1 = __builtin_amdgcn_mfma_f32_16x16x4f32(CONJ ? a[i].w : n1_, b[t].w, r1, 0, 0, 0);
+                    i1 = __builtin_amdgcn_mfma_f32_16x16x4f32(CONJ ? n1_ : a[i].w, b[t].z, i1, 0, 0, 0);
+                }
+            }
+        }
+    };
+    // never taken: tells the optimizer that LDS holds data
+    if (P.K < 0) buf0[threadIdx.x] = buf1[threadIdx.x] = *reinterpret_cast<const float4*>(A + threadIdx.x * 16);
+    if (k0 < k1) copy(buf0, k0);
+    int k = k0;
+    for (; k + kChunk < k1; k += 2 * kChunk) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        copy(buf1, k + kChunk);
+        chunk(buf0, k);
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (k + 2 * kChunk < k1) copy(buf0, k + 2 * kChunk);
+        chunk(buf1, k + kChunk);
+    }
+    if (k < k1) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        chunk(buf0, k);
+    }
+    // results: lane (n = lane % 16, q = lane / 16) holds rows 4 q .. 4 q + 3 of a tile.  SR rows at a time go through LDS.
+    constexpr int SR = 8 * RB <= (RA + RB) * kChunk ? 8 : 4;
+    float2* C = P.C + blk * P.blkC + split * P.splitC;
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int part = 0; part < 16 / SR; ++part) {
+            const int mrow = m0 + 16 * i + SR * part;
+            __syncthreads();
+            if (mrow < P.M && (lane >> 4) * 4 / SR == part) {
+                const int q4 = (lane >> 4) % (SR / 4);
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float4* o = buf0 + ((4 * q4 + r) * RB + 16 * t) * 8;
+                        o[at0] = make_float4(re[0][i][t][r], im[0][i][t][r], re[1][i][t][r], im[1][i][t][r]);
+                        o[at1] = make_float4(re[2][i][t][r], im[2][i][t][r], re[3][i][t][r], im[3][i][t][r]);
+                    }
+            }
+            __syncthreads();
+#pragma unroll 4
+            for (int u = threadIdx.x; u < SR * RB * 8; u += 256) {
+                const int m = u / (RB * 8), n = (u / 8) % RB, piece = (u & 7) ^ ((n >> 1) & 7);
+                if (mrow + m < P.M && n0 + n < P.N)
+                    *reinterpret_cast<float4*>(C + (long)(mrow + m) * P.cm + (long)(n0 + n) * P.cn + piece * 2) = buf0[u];
+            }
+        }
+}
+
+// ---------------------------------------------------------------- launches
+TileGeom base_geom(const Tiling& L)
+{
+    TileGeom G = {};
+    for (int d = 0; d < 3; ++d) G.M[d] = L.M[d];
+    G.Mxh = L.M[2] / 2 + 1;
+    return G;
+}
+
+unsigned mask_of(int o, int w, int sp)
+{
+    unsigned m = 0;
+    for (int i = 0; i < w; ++i) m |= 1u << (o + i * sp);
+    return m;
+}
+
+// Fills what follows from the fields set by the caller; returns threads and LDS bytes of a workgroup.  Entries per
+// workgroup: as many as keep the threads of the column passes busiest within 40 KiB of LDS (four workgroups per compute
+// unit; a single larger tile still leaves two), while the launch has two workgroups per compute unit.
+void finish_geom(TileGeom& G, long entries, int* threads, size_t* lds)
+{
+    G.entries = (int)entries;
+    const size_t one = sizeof(float2) * (size_t)G.w[0] * G.M[1] * G.Mxh;     // the planes along z that hold samples
+    const int cols = G.M[0] > 1 ? G.M[1] * G.Mxh : G.Mxh;
+    int nb = 1;
+    double best = 0;
+    for (int c = 1; c <= kTileEntries; ++c) {
+        if (c > 1 && (c * one > 40 * 1024 || (entries + c - 1) / c < 512 || c * cols > 320)) break;
+        const int t = (c * cols + 63) / 64 * 64;
+        const double use = (double)(c * cols) / t;
+        if (use > best + 0.02) { best = use; nb = c; }
+    }
+    G.per_wg = nb;
+    for (int d = 0; d < 3; ++d) {
+        G.fw[d] = make_fastdiv((unsigned)G.w[d]);
+        G.mask[d] = mask_of(G.o[d], G.w[d], G.sp[d]);
+    }
+    const int last = std::min(G.w[2], G.n[2] - (G.T[2] - 1) * G.hop[2]);        // samples per row of the last tile along x
+    G.vw = G.sp[2] > 1 ? 1 : G.w[2] % 4 == 0 && last >= 4 ? 4 : G.w[2] % 2 == 0 && last >= 2 ? 2 : 1;
+    G.clip = entries % nb != 0;
+    for (int d = 0; d < 3; ++d) G.clip |= G.n[d] - (G.T[d] - 1) * G.hop[d] < G.w[d];
+    G.fwx = make_fastdiv((unsigned)(G.w[2] / G.vw));
+    G.fMxh = make_fastdiv((unsigned)G.Mxh);
+    G.fcol = make_fastdiv((unsigned)(G.M[1] * G.Mxh));
+    *threads = std::min(kTileThreads, std::max(128, (nb * cols + 63) / 64 * 64));
+    *lds = nb * one;
+    G.rows_per_step = *threads / (G.w[2] / G.vw);
+    G.step[2] = G.rows_per_step % G.w[1];
+    G.step[1] = G.rows_per_step / G.w[1] % G.w[0];
+    G.step[0] = G.rows_per_step / G.w[1] / G.w[0];
+}
+
+bool has_long(const TileGeom& G) { return G.M[0] > 24 || G.M[1] > 24 || G.M[2] > 24; }
+
+int forward_tiles(const char* name, TileGeom G, long entries, const float* src, float2* dst, hipStream_t s)
+{
+    TileFwd A;
+    int threads; size_t lds;
+    finish_geom(G, entries, &threads, &lds);
+    A.src = src; A.dst = dst; A.G = G;
+    const dim3 grid((unsigned)((entries + G.per_wg - 1) / G.per_wg)), block(threads);
+    bool full = true;
+    for (int d = 0; d < 3; ++d) full = full && G.w[d] == G.M[d];
+    if (has_long(G)) {
+        if (full) ZNN_LAUNCH(name, s, (k_tile_fwd<true, true>), grid, block, lds, A);
+        else      ZNN_LAUNCH(name, s, (k_tile_fwd<true, false>), grid, block, lds, A);
+    } else {
+        if (full) ZNN_LAUNCH(name, s, (k_tile_fwd<false, true>), grid, block, lds, A);
+        else      ZNN_LAUNCH(name, s, (k_tile_fwd<false, false>), grid, block, lds, A);
+    }
+    return check_launch(name);
+}
+
+int inverse_tiles(const char* name, TileGeom G, long entries, const float2* src, float* dst, float scale, int splits,
+                  long split_stride, hipStream_t s)
+{
+    TileInv A;
+    int threads; size_t lds;
+    finish_geom(G, entries, &threads, &lds);
+    A.src = src; A.dst = dst; A.G = G; A.scale = scale; A.splits = splits; A.split_stride = split_stride;
+    const dim3 grid((unsigned)((entries + G.per_wg - 1) / G.per_wg)), block(threads);
+    if (has_long(G)) {
+        if (splits > 1) ZNN_LAUNCH(name, s, (k_tile_inv<true, true>), grid, block, lds, A);
+        else            ZNN_LAUNCH(name, s, (k_tile_inv<true, false>), grid, block, lds, A);
+    } else {
+        if (splits > 1) ZNN_LAUNCH(name, s, (k_tile_inv<false, true>), grid, block, lds, A);
+        else            ZNN_LAUNCH(name, s, (k_tile_inv<false, false>), grid, block, lds, A);
+    }
+    return check_launch(name);
+}
+
+template <int MT, int NT>
+int product_of(const char* name, bool conj, TileProduct P, hipStream_t s)
+{
+    P.gm = (P.M + 16 * MT - 1) / (16 * MT);
+    P.gn = (P.N + 16 * NT - 1) / (16 * NT);
+    const long run = ((long)P.blocks * P.gm * P.gn * P.splits + 7) / 8, grid = run * 8;
+    if (grid >= 2147483647L) return fail(ZNN_EUNSUPPORTED, "too many tiles for one launch");
+    P.run = (int)run;
+    if (conj) ZNN_LAUNCH(name, s, (k_tile_product<MT, NT, true>), dim3((unsigned)grid), dim3(256), 0, P);
+    else      ZNN_LAUNCH(name, s, (k_tile_product<MT, NT, false>), dim3((unsigned)grid), dim3(256), 0, P);
+    return check_launch(name);
+}
+
+// Result tiles of a workgroup by the work they leave: MFMAs, copies of the operands and a fixed part per workgroup
+// (measured shares at 16 to 144 rows and columns); 40 x 40 results are 3 workgroups of 48 x 16 instead of 4 of 32 x 32.
+int product(const char* name, bool conj, const TileProduct& P, hipStream_t s)
+{
+    const int mt = (P.M + 15) / 16, nt = (P.N + 15) / 16;
+    auto cost = [&](int a, int b) { return (double)((mt + a - 1) / a) * ((nt + b - 1) / b) * (a * b + 0.35 * (a + b) + 0.5); };
+    const int shapes[][2] = {{2, 2}, {3, 1}, {1, 3}, {2, 1}, {1, 2}};
+    int best = 0;
+    for (int i = 1; i < 5; ++i)
+        if (cost(shapes[i][0], shapes[i][1]) < cost(shapes[best][0], shapes[best][1])) best = i;
+    switch (best) {
+        case 0: return product_of<2, 2>(name, conj, P, s);
+        case 1: return product_of<3, 1>(name, conj, P, s);
+        case 2: return product_of<1, 3>(name, conj, P, s);
+        case 3: return product_of<2, 1>(name, conj, P, s);
+        default: return product_of<1, 2>(name, conj, P, s);
+    }
+}
+
+constexpr int kLengths[] = {8, 12, 16, 20, 24, 32};
+
+size_t spectra_of(const Tiling& L, long entries) { return align256(sizeof(float2) * 16 * (size_t)L.blocks * entries); }
+
+}  // namespace
+
+// ---------------------------------------------------------------- the tiling of a layer
+// Seconds that a training round spends on tiles, from the rates the kernels reach on layers that fill the chip: transforms
+// 3.0 (forward) and 2.6 TB/s (inverse) of spectra, products 4.5 TB/s and 110 TFLOP/s (result tiles of 16 x 16), the sum of
+// overlapping tiles 4.2 TB/s.  Node spectra count one and a half times: rounds with and without memoized ones.
+static double round_seconds(const Geom& g, const Tiling& L)
+{
+    auto up16 = [](double v) { return std::ceil(v / 16.0) * 16.0; };
+    const double w = 8.0 * 16.0 * L.blocks, T = L.tiles, nodes = g.f + g.fo, pairs = (double)g.f * g.fo;
+    const double vol = (double)L.M[0] * L.M[1] * L.M[2];
+    const double transforms = w * (1.5 * T * nodes / 3.0e12 + T * nodes / 2.6e12 + 1.5 * pairs / 3.3e12 + pairs / 3.0e12);
+    const double products = w * (3.0 * pairs + 3.0 * T * nodes) / 4.5e12 +
+                            w * (up16(g.fo) * up16(T) * g.f + up16(g.f) * up16(T) * g.fo + up16(g.f) * up16(g.fo) * T) / 110e12;
+    const double sum = T > 1 ? 8.0 * vol * T * g.f / 4.2e12 : 0.0;
+    return transforms + products + sum;
+}
+
+Tiling tile_search(const Geom& g, size_t spectra_bytes)
+{
+    Tiling best = {};
+    const int n[3] = {g.nz, g.ny, g.nx}, o[3] = {g.oz, g.oy, g.ox};
+    const int S[3] = {g.spz * (g.kz - 1) + 1, g.spy * (g.ky - 1) + 1, g.spx * (g.kx - 1) + 1};
+    double best_t = 0;
+    auto lengths = [&](int d, int* out) {
+        int c = 0;
+        if (d < 2 && n[d] == 1) { out[c++] = 1; return c; }
+        for (int M : kLengths)
+            if (M >= S[d]) {
+                out[c++] = M;
+                if (M - S[d] + 1 >= o[d]) break;     // one tile covers the axis: a longer one is only padding
+            }
+        return c;
+    };
+    int lz[8], ly[8], lx[8];
+    const int cz = lengths(0, lz), cy = lengths(1, ly), cx = lengths(2, lx);
+    for (int a = 0; a < cz; ++a)
+        for (int b = 0; b < cy; ++b)
+            for (int c = 0; c < cx; ++c) {
+                Tiling L = {};
+                const int M[3] = {lz[a], ly[b], lx[c]};
+                L.on = true;
+                long T = 1;
+                for (int d = 0; d < 3; ++d) {
+                    L.M[d] = M[d];
+                    L.B[d] = M[d] - S[d] + 1;
+                    L.T[d] = (o[d] + L.B[d] - 1) / L.B[d];
+                    T *= L.T[d];
+                }
+                const long omega = (long)M[0] * M[1] * (M[2] / 2 + 1);
+                if (omega * (long)sizeof(float2) > (long)kTileLds) continue;
+                L.tiles = (int)T;
+                L.blocks = (int)((omega + 15) / 16);
+                // entries are counted in 32 bits and an operand of a frequency block is addressed with 32-bit byte offsets
+                const double most = std::max((double)T * std::max(g.f, g.fo), (double)g.f * g.fo);
+                if (most >= 3e7 || (M[1] * (M[2] / 2 + 1) / 16 + 2) * most * 128.0 >= 4294967296.0) continue;
+                if (tile_kernel_bytes(g, L) > spectra_bytes) continue;
+                const double t = round_seconds(g, L);
+                if (best_t == 0 || t < best_t) { best = L; best_t = t; }
+            }
+    best.seconds = best_t;
+    return best;
+}
+
+size_t tile_kernel_bytes(const Geom& g, const Tiling& L) { return spectra_of(L, (long)g.f * g.fo); }
+size_t tile_node_bytes(const Geom&, const Tiling& L, int maps) { return spectra_of(L, (long)maps * L.tiles); }
+
+// splits of the tile index in the kernel gradient: enough waves to fill the chip
+static int gradient_splits(const Geom& g, const Tiling& L)
+{
+    const long waves = (long)L.blocks * ((g.f + 15) / 16) * ((g.fo + 15) / 16);
+    const int most = std::max(1, L.tiles / 16);
+    return (int)std::max(1L, std::min((long)std::min(most, 16), 2048 / std::max(1L, waves)));
+}
+
+// real tiles of the backward pass before their overlapping parts are summed
+static size_t add_bytes(const Tiling& L, int maps)
+{
+    if (L.tiles == 1) return 0;     // nothing overlaps: the inverse transform writes the result itself
+    return align256(sizeof(float) * (size_t)L.M[0] * L.M[1] * L.M[2] * L.tiles * maps);
+}
+
+static size_t result_bytes(const Geom& g, const Tiling& L, int pass, int maps)
+{
+    return tile_node_bytes(g, L, maps) + (pass == ZNN_PASS_BWD ? add_bytes(L, maps) : 0);
+}
+
+// result maps per chunk: as few equal chunks as `bytes` of scratch allow (0: not even one map fits)
+static int chunk_of(const Geom& g, const Tiling& L, int pass, size_t bytes)
+{
+    const int outs = pass == ZNN_PASS_FWD ? g.fo : g.f;
+    for (int n = 1; n <= outs; ++n) {
+        const int c = (outs + n - 1) / n;
+        if (result_bytes(g, L, pass, c) <= bytes) return c;
+    }
+    return 0;
+}
+
+size_t tile_workspace_bytes(const Geom& g, const Tiling& L, int pass, bool resident)
+{
+    if (pass == ZNN_PASS_WGRAD)
+        return tile_node_bytes(g, L, g.f) + tile_node_bytes(g, L, g.fo) + gradient_splits(g, L) * tile_kernel_bytes(g, L);
+    const int outs = pass == ZNN_PASS_FWD ? g.fo : g.f;
+    const size_t operands = tile_node_bytes(g, L, pass == ZNN_PASS_FWD ? g.f : g.fo) + (resident ? 0 : tile_kernel_bytes(g, L));
+    // the real tiles of the backward pass take the place of the operands (see tile_bwd)
+    return tile_node_bytes(g, L, outs) + std::max(operands, pass == ZNN_PASS_BWD ? add_bytes(L, outs) : 0);
+}
+
+int tile_kernel_spectra(const Geom& g, const Tiling& L, const float* w, float2* What, hipStream_t s)
+{
+    TileGeom G = base_geom(L);
+    const int k[3] = {g.kz, g.ky, g.kx}, sp[3] = {g.spz, g.spy, g.spx};
+    for (int d = 0; d < 3; ++d) { G.T[d] = 1; G.hop[d] = 0; G.n[d] = G.w[d] = k[d]; G.o[d] = 0; G.sp[d] = sp[d]; }
+    return forward_tiles("fft of kernels (tiles)", G, (long)g.f * g.fo, w, What, s);
+}
+
+static int tile_images(const Geom& g, const Tiling& L, const float* in, float2* U, hipStream_t s)
+{
+    TileGeom G = base_geom(L);
+    const int n[3] = {g.nz, g.ny, g.nx};
+    for (int d = 0; d < 3; ++d) { G.T[d] = L.T[d]; G.hop[d] = L.B[d]; G.n[d] = n[d]; G.w[d] = L.M[d]; G.o[d] = 0; G.sp[d] = 1; }
+    return forward_tiles("fft of image tiles", G, (long)g.f * L.tiles, in, U, s);
+}
+
+static int tile_gradients(const Geom& g, const Tiling& L, const float* gout, float2* V, hipStream_t s)
+{
+    TileGeom G = base_geom(L);
+    const int o[3] = {g.oz, g.oy, g.ox};
+    for (int d = 0; d < 3; ++d) {
+        G.T[d] = L.T[d]; G.hop[d] = L.B[d]; G.n[d] = o[d]; G.w[d] = L.B[d]; G.o[d] = L.M[d] - L.B[d]; G.sp[d] = 1;
+    }
+    return forward_tiles("fft of gradient tiles", G, (long)g.fo * L.tiles, gout, V, s);
+}
+
+static float inv_volume(const Tiling& L) { return (float)(1.0 / ((double)L.M[0] * L.M[1] * L.M[2])); }
+
+int tile_fwd(const Geom& g, const Tiling& L, const float* in, const float* w, const float2* resident, float* out,
+             void* ws, size_t ws_bytes, float2* memo_in, hipStream_t s)
+{
+    char* p = (char*)ws;
+    char* const end = p + ws_bytes;
+    float2* U = memo_in;
+    if (!U) { U = (float2*)p; p += tile_node_bytes(g, L, g.f); }
+    const float2* What = resident;
+    int rc = tile_images(g, L, in, U, s);
+    if (rc != ZNN_OK) return rc;
+    if (!What) {
+        What = (const float2*)p;
+        rc = tile_kernel_spectra(g, L, w, (float2*)p, s);
+        if (rc != ZNN_OK) return rc;
+        p += tile_kernel_bytes(g, L);
+    }
+    const int chunk = chunk_of(g, L, ZNN_PASS_FWD, (size_t)(end - p));
+    if (chunk < 1) return fail(ZNN_EWORKSPACE, "workspace too small for one result map");
+    for (int j0 = 0; j0 < g.fo; j0 += chunk) {
+        const int nj = std::min(chunk, g.fo - j0);
+        TileProduct P = {};
+        P.A = What + (long)j0 * g.f * 16; P.am = g.f * 16; P.ak = 16; P.blkA = (long)g.f * g.fo * 16;
+        P.B = U; P.bk = L.tiles * 16; P.bn = 16; P.blkB = (long)g.f * L.tiles * 16;
+        P.C = (float2*)p; P.cm = L.tiles * 16; P.cn = 16; P.blkC = (long)nj * L.tiles * 16;
+        P.M = nj; P.N = L.tiles; P.K = g.f; P.blocks = L.blocks; P.splits = 1;
+        rc = product("spectral products forward (tiles)", false, P, s);
+        if (rc != ZNN_OK) return rc;
+        TileGeom G = base_geom(L);
+        const int o[3] = {g.oz, g.oy, g.ox};
+        for (int d = 0; d < 3; ++d) {
+            G.T[d] = L.T[d]; G.hop[d] = L.B[d]; G.n[d] = o[d]; G.w[d] = L.B[d]; G.o[d] = L.M[d] - L.B[d]; G.sp[d] = 1;
+        }
+        rc = inverse_tiles("inverse fft of image tiles", G, (long)nj * L.tiles, (const float2*)p,
+                           out + (long)j0 * g.ovol(), inv_volume(L), 1, 0, s);
+        if (rc != ZNN_OK) return rc;
+    }
+    return ZNN_OK;
+}
+
+int tile_bwd(const Geom& g, const Tiling& L, const float* gout, const float* w, const float2* resident, float* gin,
+             void* ws, size_t ws_bytes, float2* memo_gout, hipStream_t s)
+{
+    char* p = (char*)ws;
+    char* const end = p + ws_bytes;
+    float2* V = memo_gout;
+    if (!V) { V = (float2*)p; p += tile_node_bytes(g, L, g.fo); }
+    const float2* What = resident;
+    int rc = tile_gradients(g, L, gout, V, s);
+    if (rc != ZNN_OK) return rc;
+    if (!What) {
+        What = (const float2*)p;
+        rc = tile_kernel_spectra(g, L, w, (float2*)p, s);
+        if (rc != ZNN_OK) return rc;
+        p += tile_kernel_bytes(g, L);
+    }
+    const bool one = L.tiles == 1;
+    // The real tiles of the whole result take the start of the workspace, over the operands that lie there and have been
+    // used by then; where that leaves no room for the spectra of the whole result, it comes in chunks of maps with spectra
+    // and tiles behind the operands.
+    int chunk = g.f;
+    char* result = std::max(p, (char*)ws + add_bytes(L, g.f));
+    float* tiles = (float*)ws;
+    if (tile_node_bytes(g, L, g.f) > (size_t)(end - (char*)ws) || result > end - tile_node_bytes(g, L, g.f)) {
+        chunk = chunk_of(g, L, ZNN_PASS_BWD, (size_t)(end - p));
+        if (chunk < 1) return fail(ZNN_EWORKSPACE, "workspace too small for one result map");
+        result = p;
+        tiles = (float*)(p + tile_node_bytes(g, L, chunk));
+    }
+    const int n[3] = {g.nz, g.ny, g.nx};
+    for (int i0 = 0; i0 < g.f; i0 += chunk) {
+        const int ni = std::min(chunk, g.f - i0);
+        TileProduct P = {};
+        P.A = What + (long)i0 * 16; P.am = 16; P.ak = g.f * 16; P.blkA = (long)g.f * g.fo * 16;
+        P.B = V; P.bk = L.tiles * 16; P.bn = 16; P.blkB = (long)g.fo * L.tiles * 16;
+        P.C = (float2*)result; P.cm = L.tiles * 16; P.cn = 16; P.blkC = (long)ni * L.tiles * 16;
+        P.M = ni; P.N = L.tiles; P.K = g.fo; P.blocks = L.blocks; P.splits = 1;
+        rc = product("spectral products backward (tiles)", true, P, s);
+        if (rc != ZNN_OK) return rc;
+        TileGeom G = base_geom(L);
+        for (int d = 0; d < 3; ++d) {
+            G.T[d] = 1; G.hop[d] = 0; G.o[d] = 0; G.sp[d] = 1;
+            G.n[d] = G.w[d] = one ? n[d] : L.M[d];
+        }
+        rc = inverse_tiles("inverse fft of gradient tiles", G, (long)ni * L.tiles, (const float2*)result,
+                           one ? gin + (long)i0 * g.nvol() : tiles, inv_volume(L), 1, 0, s);
+        if (rc != ZNN_OK) return rc;
+        if (one) continue;
+        TileAdd A = {};
+        A.src = tiles; A.dst = gin + (long)i0 * g.nvol();
+        for (int d = 0; d < 3; ++d) {
+            A.M[d] = L.M[d]; A.T[d] = L.T[d]; A.hop[d] = L.B[d]; A.n[d] = n[d];
+            A.fhop[d] = make_fastdiv((unsigned)L.B[d]);
+        }
+        A.xy = g.ny * g.nx;
+        A.fnx = make_fastdiv((unsigned)g.nx);
+        bool two = true;
+        for (int d = 0; d < 3; ++d) two = two && L.M[d] <= 2 * L.B[d];
+        // z values per workgroup: few enough for four workgroups per compute unit
+        A.zs = two ? (int)std::max(1L, std::min(16L, (long)((A.xy + 255) / 256) * ni * g.nz / 1024)) : 1;
+        const dim3 grid((unsigned)((A.xy + 255) / 256), (unsigned)((g.nz + A.zs - 1) / A.zs), (unsigned)ni);
+        if (two) ZNN_LAUNCH("sum of overlapping tiles", s, k_tile_add2, grid, dim3(256), 0, A);
+        else     ZNN_LAUNCH("sum of overlapping tiles", s, k_tile_add, grid, dim3(256), 0, A);
+        rc = check_launch("sum of overlapping tiles");
+        if (rc != ZNN_OK) return rc;
+    }
+    return ZNN_OK;
+}
+
+int tile_wgrad_from_spectra(const Geom& g, const Tiling& L, const float2* U, const float2* V, float* gw, void* scratch,
+                            hipStream_t s)
+{
+    TileProduct P = {};
+    P.splits = gradient_splits(g, L);
+    P.A = U; P.am = L.tiles * 16; P.ak = 16; P.blkA = (long)g.f * L.tiles * 16;
+    P.B = V; P.bn = L.tiles * 16; P.bk = 16; P.blkB = (long)g.fo * L.tiles * 16;
+    P.C = (float2*)scratch; P.cm = 16; P.cn = g.f * 16; P.blkC = (long)g.f * g.fo * 16;
+    P.splitC = P.blkC * L.blocks;
+    P.M = g.f; P.N = g.fo; P.K = L.tiles; P.blocks = L.blocks;
+    int rc = product("spectral products of the kernel gradient (tiles)", true, P, s);
+    if (rc != ZNN_OK) return rc;
+    TileGeom G = base_geom(L);
+    const int k[3] = {g.kz, g.ky, g.kx}, sp[3] = {g.spz, g.spy, g.spx};
+    for (int d = 0; d < 3; ++d) { G.T[d] = 1; G.hop[d] = 0; G.n[d] = G.w[d] = k[d]; G.o[d] = 0; G.sp[d] = sp[d]; }
+    return inverse_tiles("inverse fft of kernel gradients (tiles)", G, (long)g.f * g.fo, (const float2*)scratch, gw,
+                         inv_volume(L), P.splits, P.splitC, s);
+}
+
+int tile_wgrad(const Geom& g, const Tiling& L, const float* in, const float* gout, float* gw, void* ws, hipStream_t s)
+{
+    char* p = (char*)ws;
+    float2* U = (float2*)p; p += tile_node_bytes(g, L, g.f);
+    float2* V = (float2*)p; p += tile_node_bytes(g, L, g.fo);
+    int rc = tile_images(g, L, in, U, s);
+    if (rc == ZNN_OK) rc = tile_gradients(g, L, gout, V, s);
+    if (rc != ZNN_OK) return rc;
+    return tile_wgrad_from_spectra(g, L, U, V, gw, p, s);
+}
+
+}  // namespace znn

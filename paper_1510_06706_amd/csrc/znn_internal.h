@@ -91,6 +91,7 @@ struct Tuning {
     bool fft_no_mac_inverse;    // ZNN_FFT_NO_MAC_INVERSE: inverse transform along z as a pass of its own, never inside the multiply-accumulate
     bool fft_no_taps_pass;      // ZNN_FFT_NO_TAPS_PASS: kernels take the general fused x/y pass
     int  fft_lds_kb;            // ZNN_FFT_LDS_KB: LDS per workgroup of the LDS passes (pencils per workgroup follow); 0 = per pass kind
+    bool fft_no_tiles;          // ZNN_FFT_NO_TILES: whole-volume transforms where the library would choose tiles
     bool fft_lds_passes;        // ZNN_FFT_LDS_PASSES: LDS passes instead of register passes
 };
 const Tuning& tuning();
@@ -117,6 +118,10 @@ Fold fold_full();
 Fold fold_default(const Geom& g);
 // Half spectra whenever the folded multiply-accumulate can take the layer at all (on = false if not).
 Fold fold_forced(const Geom& g);
+
+// Tiling of a layer whose FFT passes run on overlapping tiles (fft_tile.hip): transform lengths M, voxels B by
+// which tiles advance, T tiles per axis (z, y, x); blocks of 16 frequencies per tile spectrum.
+struct Tiling { bool on; int M[3], B[3], T[3]; int tiles, blocks; double seconds; };    // seconds: expected per round
 
 struct FftWorkspace {
     size_t total;
@@ -240,7 +245,9 @@ struct znn_plan {
     znn::Geom g;
     int mode;                    // ZNN_DIRECT or ZNN_FFT
     znn::Fold fold;              // layout of this layer's kernel spectra (FFT method)
+    znn::Tiling tile;            // overlapping tiles instead of whole volumes (FFT method, layout left to the library)
     const float2* resident;      // kernel spectra held by the caller, or nullptr
     float2* memo;                // caller's buffer for memoized node spectra, or nullptr
+    size_t memo_bytes;           // and its size
     bool memo_has_in, memo_has_gout;
 };

@@ -8,6 +8,8 @@ Steps (rows of the hot path) and what bounds them:
   F-img / F-inv             HBM; per node volume one read of the image (4 n^3 bytes; 4 n'^3 for an output
                             gradient) and one write of its spectrum (8 N_w bytes), resp. the reverse.
   F-ker                     HBM; the kernel spectra are written once in the plan's layout.
+  FFT method on tiles       products per edge, tile and frequency on the fp32 matrix cores (8 FLOP each); transforms and
+                            the sum of overlapping tiles: bytes moved once (``work_of_tiles``).
   F-mac, full spectra       HBM; every kernel-spectrum element is streamed once (8 bytes) and used in one
                             complex multiply-add (8 FLOP); node spectra read and written once.
   F-mac, half spectra       fp32 vector ALU.  FLOPs are the ones the kernel executes: a thread handles
@@ -69,8 +71,20 @@ def flops4_wgrad_dft(taps: int) -> float:
     return 42.0 + 8.0 * (taps - 1)
 
 
+# the FFT method on overlapping tiles
+TILE_STEPS = {
+    "fft of kernels (tiles)": "F-ker", "fft of image tiles": "F-img", "fft of gradient tiles": "F-img",
+    "spectral products forward (tiles)": "F-mac", "spectral products backward (tiles)": "F-mac",
+    "spectral products of the kernel gradient (tiles)": "F-wgrad products",
+    "inverse fft of image tiles": "F-inv", "inverse fft of gradient tiles": "F-inv",
+    "sum of overlapping tiles": "F-add", "inverse fft of kernel gradients (tiles)": "F-wgrad inverse",
+}
+
+
 # kernel role (name the library records per launch) -> step of the hot path, per pass
 def step_of(name: str, what: str) -> str:
+    if name in TILE_STEPS:
+        return TILE_STEPS[name]
     if name.startswith("direct forward"):
         return "D-fwd"
     if name.startswith("direct backward"):
@@ -100,12 +114,32 @@ def step_of(name: str, what: str) -> str:
     return name
 
 
-def work_of(cfg, N, layout: str, what: str):
+def work_of_tiles(cfg, tiles, what: str):
+    """The same for a layer on overlapping tiles; tiles = (lengths, counts) per axis.  Products: 8 FLOP per edge, tile
+    and frequency; transforms: samples and spectra moved once; the sum: every tile voxel read, every result written."""
+    M, T = tiles
+    nt, omega, tvol = T[0] * T[1] * T[2], spectrum_elems(M), M[0] * M[1] * M[2]
+    f, fo, pairs = cfg.fan_in, cfg.fan_out, cfg.fan_in * cfg.fan_out
+    n, no, k = (float(v[0] * v[1] * v[2]) for v in (cfg.image, cfg.out, cfg.kernel))
+    node = 8.0 * omega * nt
+    w = OrderedDict()
+    w["F-mac"] = w["F-wgrad products"] = ("mfma", 8.0 * pairs * nt * omega)
+    w["F-ker"] = w["F-wgrad inverse"] = ("hbm", pairs * (4.0 * k + 8.0 * omega))
+    w["F-img"] = ("hbm", {"fwd": f * (4.0 * n + node), "bwd": fo * (4.0 * no + node)}.get(
+        what, f * (4.0 * n + node) + fo * (4.0 * no + node)))
+    w["F-inv"] = ("hbm", fo * (4.0 * no + node) if what == "fwd" else f * ((4.0 * tvol * nt if nt > 1 else 4.0 * n) + node))
+    w["F-add"] = ("hbm", 4.0 * f * (tvol * nt + n))
+    return w
+
+
+def work_of(cfg, N, layout: str, what: str, tiles=None):
     """{step: (bound, algorithmic work per pass)}: FLOP for "mfma"/"alu", bytes for "hbm".
 
     cfg: layer shape; N: FFT extents; layout: "full" | "folded" (kernel spectra);
-    what: "fwd" | "bwd" | "wgrad" | "wgrad_memo" | "kernel_spectra".
+    what: "fwd" | "bwd" | "wgrad" | "wgrad_memo" | "kernel_spectra"; tiles: (lengths, counts) or None.
     """
+    if tiles is not None:
+        return work_of_tiles(cfg, tiles, what)
     f, fo = cfg.fan_in, cfg.fan_out
     n = 1
     for v in cfg.image:
@@ -179,10 +213,10 @@ def price(bound: str, work: float, ms: float):
             "work": "FLOPs the kernel executes"}
 
 
-def steps_of_pass(records, reps, cfg, N, layout, what, extra_work=None):
+def steps_of_pass(records, reps, cfg, N, layout, what, extra_work=None, tiles=None):
     """records: [(kernel role, ms)] of `reps` traced runs of one pass -> [{step, kernels, launches, ms, ...}]
     with every step priced against its roofline, in launch order of first appearance."""
-    model = dict(work_of(cfg, N, layout, what)) if cfg is not None else {}
+    model = dict(work_of(cfg, N, layout, what, tiles)) if cfg is not None else {}
     if extra_work:
         model.update(extra_work)
     agg = OrderedDict()

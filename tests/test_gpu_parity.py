@@ -602,3 +602,32 @@ def test_training_round_with_memoized_spectra_matches_the_oracle(mode):
                 for k in g:
                     assert rel_err(host(grads[l][k]), g[k]) <= 1e-3, (rnd, l, k)
                     assert rel_err(host(net.params[l][k]), p64[l][k]) <= 1e-3, (rnd, l, k)
+
+
+@pytest.mark.parametrize("f,fo,n,k,s", [
+    (5, 7, (9, 11, 13), (3, 3, 3), (1, 1, 1)),          # one tile, maps no multiple of anything
+    (17, 33, (20, 30, 26), (2, 5, 3), (1, 1, 1)),       # several tiles, last ones clipped on every axis
+    (40, 24, (1, 70, 66), (1, 5, 5), (1, 1, 1)),        # 2D: 48 x 16 blocks of results
+    (3, 50, (1, 90, 95), (1, 11, 11), (1, 1, 1)),       # 2D, length 32, 16 x 48 blocks
+    (3, 2, (60, 50, 44), (3, 3, 3), (1, 1, 1)),         # few maps, many tiles: the tile index is split in the gradient
+    (30, 30, (1, 40, 40), (1, 13, 13), (1, 1, 1)),      # tiles that overlap by more than half
+    (30, 30, (30, 30, 30), (7, 7, 7), (1, 1, 1)),
+    (6, 5, (20, 22, 21), (2, 3, 2), (3, 2, 4)),         # sparse taps along all axes
+    (1, 1, (40, 60, 9), (2, 2, 2), (1, 1, 1)),
+])
+def test_fft_layers_on_overlapping_tiles_match_the_oracle(f, fo, n, k, s):
+    print("case", f, fo, n, k, s, flush=True)
+    cfg = synth.LayerShape("t", f, fo, n, k, 1.0 / np.sqrt(f * np.prod(k)), 900 + f, s)
+    inp, w, gout = synth.layer_tensors(cfg)
+    p = znn.Plan(f, fo, n, k, "fft", s)
+    assert p.tiles is not None
+    d_in, d_w, d_g = dev(inp), dev(w), dev(gout)
+    out, gin, gw = host(p.fwd(d_in, d_w)), host(p.bwd(d_g, d_w)), host(p.wgrad(d_in, d_g))
+    for got, ref in ((out, oracle.conv3d_fwd(inp, w, s)), (gin, oracle.conv3d_bwd(gout, w, n, s)),
+                     (gw, oracle.conv3d_wgrad(inp, gout, s))):
+        assert rel_err(got, ref) <= 1e-5
+    p.prepare_kernels(d_w)                   # the memoized schedule gives the same bits
+    p.enable_memo()
+    assert np.array_equal(out, host(p.fwd(d_in, None))) and np.array_equal(gin, host(p.bwd(d_g, None)))
+    assert np.array_equal(gw, host(p.wgrad_memo()))
+    p.close()
