@@ -128,39 +128,6 @@ static DescKey key_of(const znn_conv_desc& d)
                    d.sparsity.z, d.sparsity.y, d.sparsity.x);
 }
 
-// Cost model behind mode = auto when no measurement is cached, calibrated on the five
-// benchmark configurations and the layers of the benchmark networks.  Direct: a dense fp32
-// contraction at about 92 effective TFLOP/s, scaled down when the output has too few voxel
-// tiles (times the shares its input maps can be split into) to occupy the 256 compute units.  FFT: the two multiply-accumulates and the pruned
-// DFTs of the kernel gradient are ALU work (kernel taps folded in) or stream the full kernel
-// spectra from HBM (small layers, extents not divisible by 4), the node transforms move
-// 16 bytes per frequency and pass at about 3.5 TB/s effective; both pay per launch.
-static int model_choice(const Geom& g)
-{
-    const double macs = (double)g.f * g.fo * (double)g.ovol() * (double)g.kvol();
-    const double tiles = std::ceil((double)g.ovol() / 128.0) * std::ceil((double)g.fo / 128.0);
-    const double nchunk = std::ceil(g.f / 4.0);
-    const double splits = tiles >= 256.0 ? 1.0 : std::min(nchunk, std::ceil(768.0 / tiles));
-    const double util = std::min(1.0, tiles * splits / 1024.0);
-    const double t_direct = 3.0 * 2.0 * macs / (92e12 * util) + 7 * 10e-6;
-    const double sv = (double)g.svol();
-    const double pairs = (double)g.f * g.fo;
-    const int taps = g.Nz > 1 ? g.kz : g.ky;
-    const int N = g.Nz > 1 ? g.Nz : g.Ny;
-    const int sp = g.Nz > 1 ? g.spz : g.spy;
-    const double P = g.Nz > 1 ? (double)g.Ny * g.Nxh : (double)g.Nxh;
-    const double mac_blocks = std::ceil(P / 64.0) * std::ceil(N / 32.0) * std::ceil(std::min(g.f, g.fo) / 4.0);
-    const bool folded = N % 4 == 0 && taps <= 16 && taps < N && sp == 1 && mac_blocks >= 128.0;
-    double t_mac;
-    // the folded multiply-accumulate needs about four workgroups per compute unit to reach its rate
-    if (folded) t_mac = 2.0 * 8.0 * taps * sv * pairs / (55e12 * std::min(1.0, mac_blocks / 1024.0)) + 8.0 * taps * P * pairs / 3e12;
-    else t_mac = 8.0 * sv * pairs * (1.0 / 4.5e12 + 2.0 / 5.5e12 + 0.3 / 5e12);
-    const double t_dft = (taps / 4.0 + 2.0) * 8.0 * sv * pairs / 45e12;
-    const double t_nodes = 3.0 * (g.f + g.fo) * 3.0 * 16.0 * sv / 3.5e12;
-    const double t_fft = t_mac + t_dft + t_nodes + 25 * 6e-6;
-    return t_fft < t_direct ? ZNN_FFT : ZNN_DIRECT;
-}
-
 static int validate_desc(const znn_conv_desc* d, Geom* g)
 {
     if (!d) return fail(ZNN_EINVAL, "descriptor is NULL");
@@ -217,6 +184,19 @@ static FftWay fft_way(const Geom& g)
                 g.nz, g.ny, g.nx, w.tile.M[0], w.tile.M[1], w.tile.M[2], w.tile.tiles, tiles * 1e6, whole * 1e6);
     if (whole < tiles) w.tile.on = false;
     return w;
+}
+
+// Choice behind mode = auto when no measurement is cached: the expected time of a training round by either method, each
+// from the work of the kernels that would run (the searches for their tiles price it) with the factor and the constant
+// that fit 360 layers of nets of width 6 to 64 measured by znn_autotune; picking by it costs 1 % over always
+// picking the faster method there.
+static int model_choice(const Geom& g)
+{
+    if (g.Nz > kMaxFftExtent || g.Ny > kMaxFftExtent || g.Nx > kMaxFftExtent) return ZNN_DIRECT;
+    const FftWay w = fft_way(g);
+    const double fft = w.tile.on ? w.tile.seconds : whole_volume_seconds(g, w.fold);
+    const double direct = mfma_conv_seconds(g, false) + mfma_conv_seconds(g, true) + mfma_wgrad_seconds(g);
+    return 1.2 * fft + 80e-6 < 1.1 * direct + 16e-6 ? ZNN_FFT : ZNN_DIRECT;
 }
 
 static size_t fft_pass_bytes(const Geom& g, const FftWay& w, int pass, bool resident)

@@ -137,6 +137,7 @@ struct TileChoice {
     bool tail;          // NJ full tiles and an 8-map block (direct_mfma_tail_impl.h)
     int cps, splits;    // input-map chunks per workgroup and number of such shares
     size_t lds;
+    double cost;        // expected clocks of the launch
 };
 
 constexpr int kCUs = 256;
@@ -228,6 +229,7 @@ TileChoice search_tile(int fM, int fK, int dz, int dy, int dx, int kz, int ky, i
                     best.tail = tail;
                     best.cps = cps; best.splits = splits;
                     best.lds = lds;
+                    best.cost = cost;
                 }
             }
         }
@@ -285,6 +287,15 @@ bool mfma_conv_supported(const Geom& g, bool backward)
     const long svol = backward ? g.ovol() : g.nvol();
     // the halo loader addresses the chunk's four source maps with one 32-bit byte offset
     return c.ok && svol < (1L << 28);
+}
+
+// Expected seconds of the pass: the search's clocks, the sum of the shares, weight packing.
+double mfma_conv_seconds(const Geom& g, bool backward)
+{
+    const TileChoice c = choose_for(g, backward);
+    if (!c.ok) return 2.0 * g.f * g.fo * (double)g.ovol() * g.kvol() / 1e12;
+    const double count = backward ? (double)g.f * g.nvol() : (double)g.fo * g.ovol();
+    return c.cost / 2.1e9 + (c.splits > 1 ? 4e-6 + 4.0 * count * (c.splits + 1) / 3e12 : 0.0);
 }
 
 size_t mfma_conv_workspace(const Geom& g, bool backward)

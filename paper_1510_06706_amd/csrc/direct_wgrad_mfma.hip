@@ -18,6 +18,7 @@
 // order through LDS); with many columns every wave owns columns of its own, so
 // that a staged tile feeds four times the MFMAs.  One partial matrix per workgroup.  A second kernel adds the partial matrices in
 // ascending split order, so the result is bit-reproducible (no atomics).
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -307,6 +308,17 @@ WgradChoice choose_wgrad(const Geom& g)
 }  // namespace
 
 bool mfma_wgrad_supported(const Geom& g) { return choose_wgrad(g).ok; }
+
+// Expected seconds of the pass: issued MFMAs (padding included) per compute unit that has a workgroup, and the tiles.
+double mfma_wgrad_seconds(const Geom& g)
+{
+    const WgradChoice c = choose_wgrad(g);
+    if (!c.ok) return 2.0 * g.f * g.fo * (double)g.ovol() * g.kvol() / 1e12;
+    const double groups = (double)c.ksplit * g.kz * g.ky * c.G * c.JG;
+    const double rounds = std::ceil(groups / 256.0);
+    const double mfma = (double)c.NJ * c.NT * c.NG * (c.R * c.TX / 4.0) * 32.0 / 4.0;       // clocks per tile, four SIMDs
+    return rounds * (c.tps * (mfma * 1.3 + 1200.0) + 8000.0) / 2.1e9 + 5e-6;
+}
 
 size_t mfma_wgrad_workspace(const Geom& g)
 {

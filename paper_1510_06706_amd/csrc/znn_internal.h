@@ -102,6 +102,9 @@ int direct_fwd(const Geom& g, const float* in, const float* w, float* out, void*
 int direct_bwd(const Geom& g, const float* gout, const float* w, float* gin, void* ws, hipStream_t s);
 int direct_wgrad(const Geom& g, const float* in, const float* gout, float* gw, void* ws, hipStream_t s);
 size_t direct_workspace_bytes(const Geom& g, int pass);
+// expected seconds of a pass (choice between the methods where nothing has been measured)
+double mfma_conv_seconds(const Geom& g, bool backward);
+double mfma_wgrad_seconds(const Geom& g);
 
 // ---------------------------------------------------------------- FFT method
 // Layout of a layer's kernel spectra, fixed when its plan is created (or by
