@@ -327,6 +327,58 @@ int  znn_autotune_round(const znn_conv_desc* desc, uint64_t memory_budget, void*
                         void* stream, znn_round_report* report);
 
 /*
+ * Programs: a training round or a forward pass of a whole net as one call (Algorithms 1 to 3).
+ *
+ * znn_program_create takes the operations of the round in an order that respects their dependencies, every operation
+ * with the stream it is to run on and the numbers of the buffers it works on.  znn_program_run launches them
+ * on the buffers and streams given then: streams[0] is the calling stream, on which everything before the
+ * call is over when the first operation starts and which has waited for the last one when work that follows on it starts;
+ * operations on other streams wait for each other exactly where one uses what the other writes (events that the
+ * program owns).  Nothing synchronises with the host, nothing is allocated, and a run may be captured
+ * into a HIP graph.  The operations give what the single entry points give, except that
+ *   - an operation may also apply what follows its result (`fn` with the buffers for it, see below),
+ *   - the kernel transforms and, within a bound on memory, the node spectra of a layer on the FFT method are computed
+ *     once per run and shared by its passes (Section 4),
+ *   - gradients that an UPDATE consumes may be completed by it: they are valid after the run, not between its operations.
+ * A program describes the plans as they are when it is created; a plan stands for one layer (one set of kernels, inputs and
+ * gradients) and one program is run by one thread at a time.  `scratch` is shared by the runs of a program.
+ *
+ * Buffers by position (-1 = absent, only where marked ?):
+ *   CONV_FWD       in, w, out, ?bias, ?y      y = fn(out + bias)
+ *   CONV_BWD       gout, w, gin, ?y           gin times fn'(y)
+ *   CONV_WGRAD     in, gout, gw
+ *   TRANSFER_FWD   x, bias, y                 TRANSFER_BWD   gy, y, gx                BIAS_GRAD  g, gb
+ *   FILTER_FWD     in, out, idx               FILTER_BWD     gout, idx, gin, ?y       (window, sparsity; n = extents of in)
+ *   POOL_FWD       in, out, idx               POOL_BWD       gout, idx, gin, ?y       (window; n = extents of in)
+ *   LOSS_GRAD      y, target, g, ?gx          gx = g times fn'(y)
+ *   NODE_SUM       out, part, ?part x 5, ?y   the parts in that order (positions 1 to 6), times fn'(y) (position 7)
+ *   UPDATE         g, p                       p = p - eta g, maps x n elements; p is written by nothing else
+ */
+typedef enum znn_op_kind {
+    ZNN_OP_CONV_FWD = 0, ZNN_OP_CONV_BWD = 1, ZNN_OP_CONV_WGRAD = 2, ZNN_OP_TRANSFER_FWD = 3, ZNN_OP_TRANSFER_BWD = 4,
+    ZNN_OP_BIAS_GRAD = 5, ZNN_OP_FILTER_FWD = 6, ZNN_OP_FILTER_BWD = 7, ZNN_OP_POOL_FWD = 8, ZNN_OP_POOL_BWD = 9,
+    ZNN_OP_LOSS_GRAD = 10, ZNN_OP_NODE_SUM = 11, ZNN_OP_UPDATE = 12
+} znn_op_kind;
+
+typedef enum znn_loss { ZNN_LOSS_SQUARE = 0, ZNN_LOSS_CROSS_ENTROPY = 1 } znn_loss;
+
+typedef struct znn_op {
+    int32_t kind, stream;
+    int32_t fn, loss;               /* znn_transfer_fn, znn_loss; 0 where they have no meaning */
+    int32_t maps;                   /* all but the convolutions: maps and extents of the operand */
+    znn_vec3 n, window, sparsity;
+    int32_t buf[8];
+    const znn_plan* plan;           /* convolutions */
+} znn_op;
+
+typedef struct znn_program znn_program;
+int  znn_program_create(const znn_op* ops, int32_t count, int32_t buffers, int32_t streams, znn_program** program);
+void znn_program_destroy(znn_program* program);
+int  znn_program_scratch_bytes(const znn_program* program, size_t* bytes);
+int  znn_program_run(znn_program* program, void* const* buffers, void* scratch, size_t scratch_bytes, float eta,
+                     void* const* streams);
+
+/*
  * Kernel-level timing for benchmarks and roofline reports.  While enabled, every
  * kernel the library launches is bracketed by two HIP events on its stream.
  * znn_trace_collect waits for the recorded launches, returns them in launch

@@ -30,6 +30,7 @@ EXPORTS = [
     "znn_transfer_fn_fwd", "znn_transfer_fn_bwd", "znn_cross_entropy_loss_grad",
     "znn_autotune_round_workspace_bytes", "znn_autotune_round", "znn_accumulate",
     "znn_plan_set_spectra_layout", "znn_plan_spectra_layout", "znn_plan_tiles", "znn_conv3d_fwd_static",
+    "znn_program_create", "znn_program_destroy", "znn_program_scratch_bytes", "znn_program_run",
 ]
 STATIC_SCRATCH_BYTES = 32 * 1024 * 1024
 SPECTRA_LAYOUTS = {"auto": 0, "full": 1, "folded": 2}
@@ -44,6 +45,12 @@ class Vec3(ctypes.Structure):
 class ConvDesc(ctypes.Structure):
     _fields_ = [("fan_in", ctypes.c_int32), ("fan_out", ctypes.c_int32), ("image", Vec3),
                 ("kernel", Vec3), ("sparsity", Vec3), ("mode", ctypes.c_int32)]
+
+
+class Op(ctypes.Structure):
+    _fields_ = [("kind", ctypes.c_int32), ("stream", ctypes.c_int32), ("fn", ctypes.c_int32), ("loss", ctypes.c_int32),
+                ("maps", ctypes.c_int32), ("n", Vec3), ("window", Vec3), ("sparsity", Vec3),
+                ("buf", ctypes.c_int32 * 8), ("plan", ctypes.c_void_p)]
 
 
 class TraceRecord(ctypes.Structure):
@@ -117,8 +124,13 @@ def lib():
         L.znn_conv3d_wgrad_memo.argtypes = [vp, vp, vp, sz, vp]
         L.znn_trace_enable.argtypes = [i32]
         L.znn_trace_collect.argtypes = [ctypes.POINTER(TraceRecord), i32, ctypes.POINTER(i32)]
+        L.znn_program_create.argtypes = [ctypes.POINTER(Op), i32, i32, i32, ctypes.POINTER(vp)]
+        L.znn_program_destroy.argtypes = [vp]
+        L.znn_program_destroy.restype = None
+        L.znn_program_scratch_bytes.argtypes = [vp, ctypes.POINTER(sz)]
+        L.znn_program_run.argtypes = [vp, ctypes.POINTER(vp), vp, sz, ctypes.c_float, ctypes.POINTER(vp)]
         for name in EXPORTS:
-            if name not in ("znn_last_error", "znn_plan_destroy"):
+            if name not in ("znn_last_error", "znn_plan_destroy", "znn_program_destroy"):
                 getattr(L, name).restype = ctypes.c_int
         _lib = L
     return _lib

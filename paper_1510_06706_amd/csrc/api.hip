@@ -255,6 +255,36 @@ static int run_fft_wgrad_from_spectra(const Geom& g, const FftWay& y, const floa
 
 static FftWay way_of(const znn_plan* p) { return FftWay{p->fold, p->tile}; }
 
+size_t plan_pass_bytes(const znn_plan* p, int pass, bool resident)
+{
+    return p->mode == ZNN_DIRECT ? direct_workspace_bytes(p->g, pass) : fft_pass_bytes(p->g, way_of(p), pass, resident);
+}
+
+size_t plan_kernel_bytes(const znn_plan* p) { return fft_spectra_bytes(p->g, p->fold); }
+size_t plan_memo_bytes(const znn_plan* p) { return fft_memo_bytes(p->g, way_of(p)); }
+
+int plan_kernel_spectra(const znn_plan* p, const float* w, float2* What, hipStream_t s)
+{
+    return run_kernel_spectra(p->g, way_of(p), w, What, s);
+}
+
+int plan_pass(const znn_plan* p, int pass, const float* a, const float* b, float* result, const float2* resident, void* ws,
+              float2* memo, hipStream_t s)
+{
+    const Geom& g = p->g;
+    if (p->mode == ZNN_DIRECT)
+        return pass == ZNN_PASS_FWD ? direct_fwd(g, a, b, result, ws, s)
+             : pass == ZNN_PASS_BWD ? direct_bwd(g, a, b, result, ws, s) : direct_wgrad(g, a, b, result, ws, s);
+    if (pass == ZNN_PASS_FWD) return run_fft_fwd(g, way_of(p), a, b, resident, result, ws, memo, s);
+    if (pass == ZNN_PASS_WGRAD) return run_fft_wgrad(g, way_of(p), a, b, result, ws, s);
+    return run_fft_bwd(g, way_of(p), a, b, resident, result, ws, memo ? memo_gradients(g, way_of(p), memo) : nullptr, s);
+}
+
+int plan_wgrad_memo(const znn_plan* p, float2* memo, float* gw, void* ws, hipStream_t s)
+{
+    return run_fft_wgrad_from_spectra(p->g, way_of(p), memo, memo_gradients(p->g, way_of(p), memo), gw, ws, s);
+}
+
 static bool aligned256(const void* p) { return ((uintptr_t)p & 255) == 0; }
 
 static int check_ws(const znn_plan* p, int pass, void* ws, size_t ws_bytes)
@@ -358,8 +388,7 @@ int znn_plan_workspace_bytes(const znn_plan* plan, int32_t pass, size_t* bytes)
 {
     if (!plan || !bytes) return fail(ZNN_EINVAL, "NULL argument");
     if (pass < ZNN_PASS_FWD || pass > ZNN_PASS_WGRAD) return fail(ZNN_EINVAL, "unknown pass %d", pass);
-    if (plan->mode == ZNN_DIRECT) *bytes = direct_workspace_bytes(plan->g, pass);
-    else *bytes = fft_pass_bytes(plan->g, way_of(plan), pass, plan->resident != nullptr);
+    *bytes = plan_pass_bytes(plan, pass, plan->resident != nullptr);
     return ZNN_OK;
 }
 
@@ -458,9 +487,7 @@ int znn_conv3d_wgrad_memo(znn_plan* plan, float* gw, void* ws, size_t ws_bytes, 
         return fail(ZNN_EINVAL, "the forward and the backward pass must run on this plan first");
     int rc = check_ws(plan, ZNN_PASS_WGRAD, ws, ws_bytes);
     if (rc != ZNN_OK) return rc;
-    const float2* Ihat = plan->memo;
-    const float2* Ghat = memo_gradients(plan->g, way_of(plan), plan->memo);
-    return run_fft_wgrad_from_spectra(plan->g, way_of(plan), Ihat, Ghat, gw, ws, (hipStream_t)stream);
+    return plan_wgrad_memo(plan, plan->memo, gw, ws, (hipStream_t)stream);
 }
 
 int znn_conv_release_kernels(znn_plan* plan)
@@ -477,8 +504,7 @@ int znn_conv3d_fwd(znn_plan* plan, const float* in, const float* w, float* out,
     if (!w && !(plan->mode == ZNN_FFT && plan->resident)) return fail(ZNN_EINVAL, "kernel pointer is NULL");
     int rc = check_ws(plan, ZNN_PASS_FWD, ws, ws_bytes);
     if (rc != ZNN_OK) return rc;
-    if (plan->mode == ZNN_DIRECT) return direct_fwd(plan->g, in, w, out, ws, (hipStream_t)stream);
-    rc = run_fft_fwd(plan->g, way_of(plan), in, w, plan->resident, out, ws, plan->memo, (hipStream_t)stream);
+    rc = plan_pass(plan, ZNN_PASS_FWD, in, w, out, plan->resident, ws, plan->memo, (hipStream_t)stream);
     if (plan->memo) plan->memo_has_in = rc == ZNN_OK;
     return rc;
 }
@@ -490,9 +516,7 @@ int znn_conv3d_bwd(znn_plan* plan, const float* gout, const float* w, float* gin
     if (!w && !(plan->mode == ZNN_FFT && plan->resident)) return fail(ZNN_EINVAL, "kernel pointer is NULL");
     int rc = check_ws(plan, ZNN_PASS_BWD, ws, ws_bytes);
     if (rc != ZNN_OK) return rc;
-    if (plan->mode == ZNN_DIRECT) return direct_bwd(plan->g, gout, w, gin, ws, (hipStream_t)stream);
-    rc = run_fft_bwd(plan->g, way_of(plan), gout, w, plan->resident, gin, ws,
-                     plan->memo ? memo_gradients(plan->g, way_of(plan), plan->memo) : nullptr, (hipStream_t)stream);
+    rc = plan_pass(plan, ZNN_PASS_BWD, gout, w, gin, plan->resident, ws, plan->memo, (hipStream_t)stream);
     if (plan->memo) plan->memo_has_gout = rc == ZNN_OK;
     return rc;
 }
@@ -503,8 +527,7 @@ int znn_conv3d_wgrad(znn_plan* plan, const float* in, const float* gout, float* 
     if (!plan || !in || !gout || !gw) return fail(ZNN_EINVAL, "NULL argument");
     int rc = check_ws(plan, ZNN_PASS_WGRAD, ws, ws_bytes);
     if (rc != ZNN_OK) return rc;
-    if (plan->mode == ZNN_DIRECT) return direct_wgrad(plan->g, in, gout, gw, ws, (hipStream_t)stream);
-    return run_fft_wgrad(plan->g, way_of(plan), in, gout, gw, ws, (hipStream_t)stream);
+    return plan_pass(plan, ZNN_PASS_WGRAD, in, gout, gw, nullptr, ws, nullptr, (hipStream_t)stream);
 }
 
 // ---------------------------------------------------------------- autotuner

@@ -7,13 +7,10 @@ int direct_fwd_generic(const Geom& g, const float* in, const float* w, float* ou
 int direct_bwd_generic(const Geom& g, const float* gout, const float* w, float* gin, hipStream_t s);
 int direct_wgrad_generic(const Geom& g, const float* in, const float* gout, float* gw, hipStream_t s);
 
-bool   mfma_conv_supported(const Geom& g, bool backward);
 size_t mfma_conv_workspace(const Geom& g, bool backward);
 int    mfma_conv(const Geom& g, bool backward, const float* src, const float* w, float* dst, void* ws,
                  hipStream_t s);
 
-bool   mfma_wgrad_supported(const Geom& g);
-size_t mfma_wgrad_workspace(const Geom& g);
 int    mfma_wgrad(const Geom& g, const float* in, const float* gout, float* gw, void* ws, hipStream_t s);
 
 size_t direct_workspace_bytes(const Geom& g, int pass)

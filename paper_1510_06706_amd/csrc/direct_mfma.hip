@@ -28,40 +28,44 @@ constexpr int kMaxTaps = 4096;
 // the full tiles (lane l of tile jt: output-side map jt*16 + l%16, input-side map chunk*4 + l/16), then, with
 // `tail`, [8 maps][4 input maps] for the 8-map block.  For the backward pass the two map indices trade places
 // and the tap is reflected.
-__global__ void __launch_bounds__(256)
-k_pack_weights_tail(const float* __restrict__ w, float* __restrict__ wp, int f, int fo, int kz, int ky, int kx,
-                    int backward, int NJ, int jgroups, int nchunk, int tail)
+// Several layers and passes at a time (PackArgs): the weights of a round take one launch instead of one per convolution.
+constexpr int kPackItems = 24;
+struct PackArgs { PackItem item[kPackItems]; unsigned first[kPackItems]; int n; };
+
+__global__ void __launch_bounds__(256) k_pack_weights(PackArgs A)
 {
-    const int taps = kz * ky * kx;
-    const int WT = NJ * 64 + (tail ? conv::kTailPacked : 0);
-    const long total = (long)jgroups * nchunk * taps * WT;
-    const long t = (long)blockIdx.x * 256 + threadIdx.x;
-    if (t >= total) return;
+    int q = 0;
+    while (q + 1 < A.n && blockIdx.x >= A.first[q + 1]) ++q;        // uniform
+    const PackItem& P = A.item[q];
+    const int taps = P.kz * P.ky * P.kx;
+    const int WT = P.NJ * 64 + (P.tail ? conv::kTailPacked : 0);
+    const long t = (long)(blockIdx.x - A.first[q]) * 256 + threadIdx.x;
+    if (t >= P.total) return;
     const int e = (int)(t % WT);
     long r = t / WT;
     const int tap = (int)(r % taps); r /= taps;
-    const int ic = (int)(r % nchunk);
-    const int jg = (int)(r / nchunk);
+    const int ic = (int)(r % P.nchunk);
+    const int jg = (int)(r / P.nchunk);
     int m, k;
-    if (e < NJ * 64) {
-        m = (jg * NJ + e / 64) * 16 + (e & 15);
+    if (e < P.NJ * 64) {
+        m = (jg * P.NJ + e / 64) * 16 + (e & 15);
         k = ic * 4 + ((e & 63) >> 4);
     } else {
-        m = NJ * 16 + (e - NJ * 64) / 4;
+        m = P.NJ * 16 + (e - P.NJ * 64) / 4;
         k = ic * 4 + (e & 3);
     }
-    const int fM = backward ? f : fo, fK = backward ? fo : f;
+    const int fM = P.backward ? P.f : P.fo, fK = P.backward ? P.fo : P.f;
     float v = 0.f;
     if (m < fM && k < fK) {
-        if (!backward) {
-            v = w[((long)m * f + k) * taps + tap];
+        if (!P.backward) {
+            v = P.w[((long)m * P.f + k) * taps + tap];
         } else {
-            const int c = tap % kx, b = (tap / kx) % ky, a = tap / (kx * ky);
-            const int rt = ((kz - 1 - a) * ky + (ky - 1 - b)) * kx + (kx - 1 - c);
-            v = w[((long)k * f + m) * taps + rt];
+            const int c = tap % P.kx, b = (tap / P.kx) % P.ky, a = tap / (P.kx * P.ky);
+            const int rt = ((P.kz - 1 - a) * P.ky + (P.ky - 1 - b)) * P.kx + (P.kx - 1 - c);
+            v = P.w[((long)k * P.f + m) * taps + rt];
         }
     }
-    wp[t] = v;
+    P.wp[t] = v;
 }
 
 __global__ void __launch_bounds__(256)
@@ -306,8 +310,10 @@ size_t mfma_conv_workspace(const Geom& g, bool backward)
            partial_bytes(c, backward ? g.f : g.fo, backward ? g.nvol() : g.ovol());
 }
 
-int mfma_conv(const Geom& g, bool backward, const float* src, const float* w, float* dst, void* ws,
-              hipStream_t s)
+// The pass on packed weights.  With more than one share of the input maps (mfma_conv_splits) the sums go to `partial`, one
+// array of result maps per share, and the caller adds them in ascending order.
+int mfma_conv_packed(const Geom& g, bool backward, const float* src, const float* wp, float* dst, float* partial,
+                     const Finish& finish, hipStream_t s)
 {
     ConvTile P = {};
     P.src = src; P.dst = dst;
@@ -337,17 +343,9 @@ int mfma_conv(const Geom& g, bool backward, const float* src, const float* w, fl
         fprintf(stderr, "[znn] conv mfma (%s): NJ=%d%s jgroups=%d NV=%d U=%d tile=%dx%dx%d halo=%dx%dx%d blocks=%d splits=%d lds=%zu buffers=%d\n",
                 backward ? "bwd" : "fwd", c.NJ, c.tail ? "+8" : "", c.jgroups, c.NV, group_width(g.kx, g.spx), c.Tz, c.Ty, c.Tx, c.HZ, c.HY, c.HX,
                 c.cz * c.cy * c.cx, c.splits, c.lds, c.dbuf ? 2 : 1);
-    const int taps = (int)g.kvol();
-    float* wp = (float*)ws;
     P.wp = wp;
-    P.partial = (float*)((char*)ws + packed_bytes(c, P.fK, taps));
-    {
-        const long total = (long)c.jgroups * P.nchunk * taps * (c.NJ * 64 + (c.tail ? conv::kTailPacked : 0));
-        ZNN_LAUNCH("weight packing", s, k_pack_weights_tail, dim3((unsigned)((total + 255) / 256)), dim3(256), 0,
-                   w, wp, g.f, g.fo, g.kz, g.ky, g.kx, backward ? 1 : 0, c.NJ, c.jgroups, P.nchunk, c.tail ? 1 : 0);
-    }
-    int rc = check_launch("weight packing");
-    if (rc != ZNN_OK) return rc;
+    P.partial = partial;
+    P.y = finish.y; P.bias = finish.bias; P.deriv = finish.deriv;
     const int U = group_width(g.kx, g.spx);
     ConvFn fn = c.tail ? pick_tail_kernel(U, c.NJ, c.NV, c.wl) : pick_plain_kernel(U, c.NJ, c.NV, c.wl);
     if (!fn) return fail(ZNN_EUNSUPPORTED, "no kernel instance for tile %dx%d", c.NJ, c.NV);
@@ -355,11 +353,62 @@ int mfma_conv(const Geom& g, bool backward, const float* src, const float* w, fl
     if (blocks >= 2147483647L) return fail(ZNN_EUNSUPPORTED, "too many tiles for one launch");
     ZNN_LAUNCH(backward ? "direct backward (MFMA)" : "direct forward (MFMA)", s, fn,
                dim3((unsigned)blocks, (unsigned)c.jgroups, (unsigned)c.splits), dim3(256), c.lds, P);
-    rc = check_launch(backward ? "direct backward (MFMA)" : "direct forward (MFMA)");
-    if (rc != ZNN_OK || c.splits == 1) return rc;
-    const long count = (long)P.fM * P.dz * P.dy * P.dx;
+    return check_launch(backward ? "direct backward (MFMA)" : "direct forward (MFMA)");
+}
+
+PackItem mfma_conv_pack_item(const Geom& g, bool backward, const float* w, float* wp)
+{
+    const TileChoice c = choose_for(g, backward);
+    PackItem p = {};
+    p.w = w; p.wp = wp;
+    p.f = g.f; p.fo = g.fo;
+    p.kz = g.kz; p.ky = g.ky; p.kx = g.kx;
+    p.backward = backward ? 1 : 0;
+    p.NJ = c.NJ; p.nchunk = ((backward ? g.fo : g.f) + 3) / 4;
+    p.tail = c.tail ? 1 : 0;
+    p.total = (long)c.jgroups * p.nchunk * g.kvol() * (c.NJ * 64 + (c.tail ? conv::kTailPacked : 0));
+    return p;
+}
+
+int mfma_pack_weights(const PackItem* items, int n, hipStream_t s)
+{
+    for (int i0 = 0; i0 < n; i0 += kPackItems) {
+        PackArgs A = {};
+        unsigned blocks = 0;
+        for (A.n = 0; A.n < kPackItems && i0 + A.n < n; ++A.n) {
+            A.item[A.n] = items[i0 + A.n];
+            A.first[A.n] = blocks;
+            blocks += (unsigned)((items[i0 + A.n].total + 255) / 256);
+        }
+        ZNN_LAUNCH("weight packing", s, k_pack_weights, dim3(blocks), dim3(256), 0, A);
+    }
+    return check_launch("weight packing");
+}
+
+size_t mfma_conv_packed_bytes(const Geom& g, bool backward)
+{
+    const TileChoice c = choose_for(g, backward);
+    return c.ok ? packed_bytes(c, backward ? g.fo : g.f, (int)g.kvol()) : 0;
+}
+
+int mfma_conv_splits(const Geom& g, bool backward) { return choose_for(g, backward).splits; }
+
+int mfma_conv(const Geom& g, bool backward, const float* src, const float* w, float* dst, void* ws,
+              hipStream_t s)
+{
+    const PackItem p = mfma_conv_pack_item(g, backward, w, (float*)ws);
+    float* partial = (float*)((char*)ws + mfma_conv_packed_bytes(g, backward));
+    int rc = mfma_pack_weights(&p, 1, s);
+    if (rc == ZNN_OK) rc = mfma_conv_packed(g, backward, src, p.wp, dst, partial, Finish{}, s);
+    if (rc != ZNN_OK || mfma_conv_splits(g, backward) == 1) return rc;
+    return mfma_conv_sum(g, backward, partial, dst, s);
+}
+
+int mfma_conv_sum(const Geom& g, bool backward, const float* partial, float* dst, hipStream_t s)
+{
+    const long count = backward ? (long)g.f * g.nvol() : (long)g.fo * g.ovol();
     ZNN_LAUNCH("sum over input-map shares", s, k_conv_reduce, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,
-               (const float*)P.partial, dst, count, c.splits);
+               partial, dst, count, mfma_conv_splits(g, backward));
     return check_launch("sum over input-map shares");
 }
 

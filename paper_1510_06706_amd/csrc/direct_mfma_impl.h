@@ -56,6 +56,9 @@ struct ConvTile {
     int cps;            // chunks per workgroup along gridDim.z (all of them unless the input maps are split)
     int dbuf;           // 1: two halo buffers take turns (next chunk in flight during the taps), 0: one buffer
     float* partial;     // [splits][fM][dz][dy][dx] partial sums when the input maps are split, else unused
+    float* y;           // where not NULL: y = max(result + bias[map], 0) beside the result (sums complete in this launch)
+    const float* bias;
+    const float* deriv; // where not NULL: the result is zero where this forward result of a rectifier is zero
     FastDiv dHX, dHY, dHZ;  // the halo loader takes its flat index apart without integer division
 };
 

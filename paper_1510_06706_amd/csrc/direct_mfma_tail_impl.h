@@ -290,6 +290,14 @@ __global__ void __launch_bounds__(256, 2) k_conv_mfma_tail(ConvTile P)
         if (z >= P.dz || y >= P.dy || x >= P.dx) return -1;
         return z * dplane + (long)y * P.dx + x;
     };
+    auto finish = [&](long at, int j, float v) {
+        if (P.deriv) v = P.deriv[at] > 0.f ? v : 0.f;       // uniform
+        out[at] = v;
+        if (P.y) {                                          // uniform
+            v += P.bias[j];
+            P.y[at] = v > 0.f ? v : 0.f;
+        }
+    };
     // 16x16x4: lane holds rows m = 4*(lane/16) + r, column n = lane%16
 #pragma unroll
     for (int nv = 0; nv < NV; ++nv) {
@@ -300,7 +308,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_mfma_tail(ConvTile P)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int j = (jg * NJ + jt) * 16 + grp * 4 + r;
-                if (TAIL || j < P.fM) out[(long)j * dvol + vox] = acc[jt][nv][r];
+                if (TAIL || j < P.fM) finish((long)j * dvol + vox, j, acc[jt][nv][r]);
             }
     }
     // 4x4x1: lane (block (mt, nt), v) holds maps mt*4 + r of voxel nt*4 + v
@@ -311,7 +319,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_mfma_tail(ConvTile P)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int j = NJ * 16 + (lane >> 5) * 4 + r;
-            if (j < P.fM) out[(long)j * dvol + vox] = accT[pr][r];
+            if (j < P.fM) finish((long)j * dvol + vox, j, accT[pr][r]);
         }
     }
 }

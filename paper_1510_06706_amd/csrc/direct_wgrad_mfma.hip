@@ -327,12 +327,12 @@ size_t mfma_wgrad_workspace(const Geom& g)
     return align256((size_t)c.ksplit * g.kz * g.ky * c.Mpad * c.Npad * sizeof(float));
 }
 
-int mfma_wgrad(const Geom& g, const float* in, const float* gout, float* gw, void* ws, hipStream_t s)
+int mfma_wgrad_partial(const Geom& g, const float* in, const float* gout, float* partial, WgradSum* sum, hipStream_t s)
 {
     const WgradChoice c = choose_wgrad(g);
     if (!c.ok) return fail(ZNN_EUNSUPPORTED, "no tile configuration fits this shape");
     WgradTile P = {};
-    P.in = in; P.gout = gout; P.partial = (float*)ws;
+    P.in = in; P.gout = gout; P.partial = partial;
     P.f = g.f; P.fo = g.fo;
     P.nz = g.nz; P.ny = g.ny; P.nx = g.nx;
     P.oz = g.oz; P.oy = g.oy; P.ox = g.ox;
@@ -355,15 +355,23 @@ int mfma_wgrad(const Geom& g, const float* in, const float* gout, float* gw, voi
     WgradFn fn = pick_wgrad(c.NJ, c.NT, c.NG, c.KW);
     if (!fn) return fail(ZNN_EUNSUPPORTED, "no kernel instance for tile %dx%d", c.NJ, c.NT);
     ZNN_LAUNCH("direct kernel gradient (MFMA)", s, fn, dim3((unsigned)c.ksplit, (unsigned)P.AB, (unsigned)(c.G * c.JG)), dim3(64 * c.NG * c.KW), 0, P);
-    int rc = check_launch("direct kernel gradient (MFMA)");
+    const long total = (long)g.fo * g.f * g.kvol();
+    *sum = WgradSum{c.ksplit, c.Mpad, c.Npad, c.mapmajor, total < 65536 && c.ksplit >= 16 ? 1 : 0};
+    return check_launch("direct kernel gradient (MFMA)");
+}
+
+int mfma_wgrad(const Geom& g, const float* in, const float* gout, float* gw, void* ws, hipStream_t s)
+{
+    WgradSum c;
+    int rc = mfma_wgrad_partial(g, in, gout, (float*)ws, &c, s);
     if (rc != ZNN_OK) return rc;
     const long total = (long)g.fo * g.f * g.kvol();
-    if (total < 65536 && c.ksplit >= 16)
+    if (c.four)
         ZNN_LAUNCH("kernel gradient reduction", s, k_wgrad_reduce4, dim3((unsigned)((total + 63) / 64)), dim3(256), 0,
-                           (const float*)ws, gw, g.f, g.fo, g.kz, g.ky, g.kx, c.ksplit, c.Mpad, c.Npad, c.mapmajor);
+                   (const float*)ws, gw, g.f, g.fo, g.kz, g.ky, g.kx, c.ksplit, c.Mpad, c.Npad, c.mapmajor);
     else
         ZNN_LAUNCH("kernel gradient reduction", s, k_wgrad_reduce, dim3((unsigned)((total + 255) / 256)), dim3(256), 0,
-                           (const float*)ws, gw, g.f, g.fo, g.kz, g.ky, g.kx, c.ksplit, c.Mpad, c.Npad, c.mapmajor);
+                   (const float*)ws, gw, g.f, g.fo, g.kz, g.ky, g.kx, c.ksplit, c.Mpad, c.Npad, c.mapmajor);
     return check_launch("kernel gradient reduction");
 }
 

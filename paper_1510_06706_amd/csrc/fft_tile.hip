@@ -904,6 +904,8 @@ Tiling tile_search(const Geom& g, size_t spectra_bytes)
                 }
                 const long omega = (long)M[0] * M[1] * (M[2] / 2 + 1);
                 if (omega * (long)sizeof(float2) > (long)kTileLds) continue;
+                // BlockOffsets counts on planes of a multiple of 4 frequencies: volumes of one row per plane stay whole
+                if (M[0] > 1 && M[1] * (M[2] / 2 + 1) % 4 != 0) continue;
                 L.tiles = (int)T;
                 L.blocks = (int)((omega + 15) / 16);
                 // entries are counted in 32 bits and an operand of a frequency block is addressed with 32-bit byte offsets

@@ -1,0 +1,678 @@
+// A round of a net as one native call: the passes of all layers are put in order once (znn_program_create) and then
+// launched back to back from here (znn_program_run).
+//
+// What bounds the rounds of small and ordinary nets is the number of launches: 78 of them for the six-layer 3D net, most of
+// them a few microseconds of work, issued at 8 us each where every one is a call from the host language.  A program
+//   * issues its launches natively (about 2 us each) on the given streams, with the events between streams derived
+//     from the buffers that its steps read and write;
+//   * packs the weights of all direct convolutions in one launch (k_pack_weights);
+//   * lets the kernel that completes an image also apply the transfer function of the next edge, and the kernel that
+//     completes a backward image the derivative of the edge below (conv::Finish, k_finish_fwd, k_finish_bwd, max-filter);
+//   * sums the biases' gradients of all layers in one launch that fills the chip (k_bias_parts: one workgroup per
+//     map and 8192 voxels; one workgroup per map took 76 us on the sparse net), and in the last launch completes
+//     the sums of all kernel and bias gradients and updates all parameters (k_update);
+//   * keeps the spectra of a layer on the FFT method from the forward to the backward pass and the gradient.
+// Six-layer 3D net on a 12^3 patch: 78 -> 35 launches.
+#include <algorithm>
+#include <cstring>
+#include <new>
+#include <vector>
+
+#include "znn_internal.h"
+
+namespace znn {
+
+namespace {
+
+__device__ __forceinline__ float derivative_times(int fn, float g, float y)
+{
+    if (fn == ZNN_RECTIFY) return y > 0.f ? g : 0.f;
+    return g * (fn == ZNN_LOGISTIC ? y * (1.0f - y) : 1.0f - y * y);
+}
+
+__device__ __forceinline__ float transfer(int fn, float v)
+{
+    if (fn == ZNN_RECTIFY) return v > 0.f ? v : 0.f;
+    return fn == ZNN_LOGISTIC ? 1.0f / (1.0f + expf(-v)) : tanhf(v);
+}
+
+// x = sum of the shares in ascending order (k_conv_reduce), y = fn(x + bias).  blockIdx.y: map.
+__global__ void __launch_bounds__(256)
+k_finish_fwd(const float* __restrict__ partial, float* __restrict__ x, const float* __restrict__ bias, float* __restrict__ y,
+             int voxels, long count, int splits, int fn)
+{
+    const int v = blockIdx.x * 256 + threadIdx.x;
+    if (v >= voxels) return;
+    const long t = (long)blockIdx.y * voxels + v;
+    float acc = partial[t];
+#pragma unroll 4
+    for (int s = 1; s < splits; ++s) acc += partial[(long)s * count + t];
+    x[t] = acc;
+    y[t] = transfer(fn, acc + bias[blockIdx.y]);
+}
+
+// g = (sum of the shares) times the derivative of the transfer function that gave y
+__global__ void __launch_bounds__(256)
+k_finish_bwd(const float* __restrict__ partial, const float* __restrict__ y, float* __restrict__ g, long count, int splits, int fn)
+{
+    const long t = (long)blockIdx.x * 256 + threadIdx.x;
+    if (t >= count) return;
+    float acc = partial[t];
+#pragma unroll 4
+    for (int s = 1; s < splits; ++s) acc += partial[(long)s * count + t];
+    g[t] = derivative_times(fn, acc, y[t]);
+}
+
+__global__ void __launch_bounds__(256) k_derivative_in_place(float* g, const float* __restrict__ y, long count, int fn)
+{
+    const long t = (long)blockIdx.x * 256 + threadIdx.x;
+    if (t < count) g[t] = derivative_times(fn, g[t], y[t]);
+}
+
+// Loss gradient and, for the output edge below it, the gradient before the transfer function (gx may be NULL).
+__global__ void __launch_bounds__(256)
+k_loss_finish(long count, const float* __restrict__ y, const float* __restrict__ target, float* __restrict__ g,
+              float* __restrict__ gx, int loss, int fn)
+{
+    const long t = (long)blockIdx.x * 256 + threadIdx.x;
+    if (t >= count) return;
+    const float v = y[t];
+    const float e = loss == ZNN_LOSS_SQUARE ? v - target[t] : (v - target[t]) / (v * (1.0f - v));
+    g[t] = e;
+    if (gx) gx[t] = derivative_times(fn, e, v);
+}
+
+// Node sums: the parts in ascending order, times the derivative of the edge below if y is given.
+struct SumArgs { const float* part[6]; const float* y; float* out; long count; int parts, fn; };
+__global__ void __launch_bounds__(256) k_node_sum(SumArgs A)
+{
+    const long t = (long)blockIdx.x * 256 + threadIdx.x;
+    if (t >= A.count) return;
+    float acc = A.part[0][t];
+    for (int i = 1; i < A.parts; ++i) acc = acc + A.part[i][t];
+    A.out[t] = A.y ? derivative_times(A.fn, acc, A.y[t]) : acc;
+}
+
+// Sums of the gradients over the voxels of every map, one workgroup per map and kBiasSpan voxels of any of the layers.
+constexpr int kBiasSpan = 8192, kBiasItems = 64;
+struct BiasItem { const float* g; float* parts; long voxels; int spans; unsigned first; };
+struct BiasArgs { BiasItem item[kBiasItems]; int n; };
+__global__ void __launch_bounds__(256) k_bias_parts(BiasArgs A)
+{
+    __shared__ float red[4];
+    int q = 0;
+    while (q + 1 < A.n && blockIdx.x >= A.item[q + 1].first) ++q;       // uniform
+    const BiasItem& B = A.item[q];
+    const unsigned r = blockIdx.x - B.first;
+    const unsigned m = r / B.spans, span = r % B.spans;
+    const float* p = B.g + (long)m * B.voxels + (long)span * kBiasSpan;
+    const int n = (int)min((long)kBiasSpan, B.voxels - (long)span * kBiasSpan);
+    float a[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a[i] = 0.f;
+    for (int t = threadIdx.x; t < n; t += 2048)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) a[i] += t + i * 256 < n ? p[t + i * 256] : 0.f;
+    float v = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+    for (int s = 32; s > 0; s >>= 1) v += __shfl_down(v, s);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) B.parts[r] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// Completes the gradients of a round and updates the parameters.  An item is the kernels or the biases of a layer:
+//   kind 0: the gradient is there;  kind 1: shares of the direct kernel gradient, in the order of k_wgrad_reduce;
+//   kind 2: the same in the order of k_wgrad_reduce4 (four waves per 64 elements);  kind 3: `spans` parts per bias.
+// p may be NULL (gradient only).
+constexpr int kUpdateItems = 32;
+struct UpdateItem {
+    const float* src; float* grad; float* p;
+    long total; unsigned first;
+    int kind, f, taps, kx, AB, ksplit, Mpad, Npad, mapmajor;
+};
+struct UpdateArgs { UpdateItem item[kUpdateItems]; int n; float eta; };
+__global__ void __launch_bounds__(256) k_update(UpdateArgs A)
+{
+    __shared__ float part[4][64];
+    int q = 0;
+    while (q + 1 < A.n && blockIdx.x >= A.item[q + 1].first) ++q;       // uniform
+    const UpdateItem& U = A.item[q];
+    const unsigned r = blockIdx.x - U.first;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const long t = U.kind == 2 ? (long)r * 64 + lane : (long)r * 256 + threadIdx.x;
+    float acc = 0.f;
+    if (t < U.total) {
+        if (U.kind == 0) acc = U.grad[t];
+        else if (U.kind == 3) for (int s = 0; s < U.ksplit; ++s) acc += U.src[t * U.ksplit + s];
+        else {
+            const int tap = (int)(t % U.taps);
+            const long e = t / U.taps;
+            const int i = (int)(e % U.f), j = (int)(e / U.f);
+            const int c = tap % U.kx, ab = tap / U.kx;
+            const int n = U.mapmajor ? i * U.kx + c : c * U.f + i;
+            const float* p = U.src + ((long)ab * U.Mpad + j) * U.Npad + n;
+            const long step = (long)U.AB * U.Mpad * U.Npad;
+            if (U.kind == 1) {
+#pragma unroll 4
+                for (int s = 0; s < U.ksplit; ++s) acc += p[s * step];
+            } else {
+#pragma unroll 4
+                for (int s = wave; s < U.ksplit; s += 4) acc += p[s * step];
+            }
+        }
+    }
+    if (U.kind == 2) {      // uniform
+        part[wave][lane] = acc;
+        __syncthreads();
+        if (wave != 0) return;
+        acc = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
+    }
+    if (t >= U.total) return;
+    if (U.kind != 0) U.grad[t] = acc;
+    if (U.p) U.p[t] = U.p[t] - A.eta * acc;
+}
+
+// A step of the program: an operation of the caller, or one of three that the program adds.
+enum { STEP_PACK = -1, STEP_BIAS = -2, STEP_UPDATE = -3 };
+constexpr size_t kNone = (size_t)-1;
+
+struct Step {
+    int kind;
+    znn_op op;
+    int stream;
+    bool skip;                          // no launch of its own: part of STEP_BIAS or STEP_UPDATE
+    int layer;                          // convolutions: index into znn_program::layers
+    size_t own;                         // place of the partial sums that STEP_UPDATE completes (kNone: it writes the gradient)
+    size_t pass_bytes;                  // scratch it needs while it runs
+    WgradSum sum;
+    std::vector<int> reads, writes;     // resources
+    std::vector<int> waits;             // steps of other streams that must be over
+    hipEvent_t event;                   // recorded behind the step if another stream waits for it
+};
+
+// What the program keeps of a plan (the plan as it was when the program was made).
+struct Layer {
+    const znn_plan* of;
+    znn_plan plan;
+    int w, in, gout;        // its buffers
+    bool has[3];            // passes of the layer in this program
+    size_t packed[2];       // direct method: weights of the forward / backward pass from the round's packing launch
+    size_t spectra;         // FFT method: kernels, transformed once for both passes
+    size_t memo;            // and the spectra of images and gradients, kept for the kernel gradient
+};
+
+long elements(const znn_op& o) { return (long)o.maps * o.n.z * o.n.y * o.n.x; }
+long voxels(const znn_op& o) { return (long)o.n.z * o.n.y * o.n.x; }
+int bias_spans(const znn_op& o) { return (int)((voxels(o) + kBiasSpan - 1) / kBiasSpan); }
+
+}  // namespace
+
+}  // namespace znn
+
+using namespace znn;
+
+struct znn_program {
+    int buffers, streams;
+    std::vector<Layer> layers;
+    std::vector<Step> steps;
+    std::vector<int> last_waits;        // steps that stream 0 waits for at the end
+    std::vector<char> used;             // streams with work on them
+    hipEvent_t start;
+    size_t scratch;
+    std::vector<size_t> area;           // per stream: place of the scratch of its passes
+    std::vector<int> bias_steps;        // deferred bias gradients
+    std::vector<int> update_steps;
+    std::vector<int> completes;         // per update: the step whose sums it completes, or -1
+};
+
+namespace znn {
+
+namespace {
+
+// spectra that a program keeps on the device between the passes of a round, at most
+constexpr size_t kKeptSpectra = (size_t)16 << 30;
+
+int check_op(const znn_op& o, int i, int buffers, int streams)
+{
+    if (o.kind < ZNN_OP_CONV_FWD || o.kind > ZNN_OP_UPDATE) return fail(ZNN_EINVAL, "operation %d: unknown kind %d", i, o.kind);
+    if (o.stream < 0 || o.stream >= streams) return fail(ZNN_EINVAL, "operation %d: no stream %d", i, o.stream);
+    // positions whose buffer must be given (mask), number of positions
+    static const struct { unsigned need; int n; } form[] = {
+        {7u, 5}, {7u, 4}, {7u, 3}, {7u, 3}, {7u, 3}, {3u, 2}, {7u, 3}, {7u, 4}, {7u, 3}, {7u, 4}, {7u, 4}, {3u, 8}, {3u, 2}};
+    for (int b = 0; b < 8; ++b) {
+        if (o.buf[b] >= buffers) return fail(ZNN_EINVAL, "operation %d: no buffer %d", i, o.buf[b]);
+        if (o.buf[b] < 0 && (form[o.kind].need >> b & 1)) return fail(ZNN_EINVAL, "operation %d: buffer %d is missing", i, b);
+        if (o.buf[b] >= 0 && b >= form[o.kind].n) return fail(ZNN_EINVAL, "operation %d: buffer %d has no meaning", i, b);
+    }
+    if (o.fn < ZNN_RECTIFY || o.fn > ZNN_TANH) return fail(ZNN_EINVAL, "operation %d: unknown transfer function %d", i, o.fn);
+    if (o.kind <= ZNN_OP_CONV_WGRAD) {
+        if (!o.plan) return fail(ZNN_EINVAL, "operation %d: plan is NULL", i);
+        if (o.kind == ZNN_OP_CONV_FWD && (o.buf[3] < 0) != (o.buf[4] < 0))
+            return fail(ZNN_EINVAL, "operation %d: a transfer function needs biases and a result", i);
+        return ZNN_OK;
+    }
+    if (o.kind == ZNN_OP_LOSS_GRAD && o.loss != ZNN_LOSS_SQUARE && o.loss != ZNN_LOSS_CROSS_ENTROPY)
+        return fail(ZNN_EINVAL, "operation %d: unknown loss %d", i, o.loss);
+    if (o.maps < 1 || o.n.z < 1 || o.n.y < 1 || o.n.x < 1) return fail(ZNN_EINVAL, "operation %d: maps and extents must be >= 1", i);
+    if ((double)o.maps * o.n.z * o.n.y * o.n.x / 256 >= 2147483647.0)
+        return fail(ZNN_EUNSUPPORTED, "operation %d: too many elements for one launch", i);
+    if (o.kind == ZNN_OP_FILTER_FWD || o.kind == ZNN_OP_FILTER_BWD || o.kind == ZNN_OP_POOL_FWD || o.kind == ZNN_OP_POOL_BWD)
+        return check_filter(o.maps, o.n, o.window, o.sparsity, o.kind == ZNN_OP_POOL_FWD || o.kind == ZNN_OP_POOL_BWD);
+    return ZNN_OK;
+}
+
+int layer_of(znn_program& P, const znn_op& o, int i)
+{
+    size_t l = 0;
+    while (l < P.layers.size() && P.layers[l].of != o.plan) ++l;
+    if (l == P.layers.size()) {
+        Layer L = {};
+        L.of = o.plan;
+        L.plan = *o.plan;
+        L.plan.resident = nullptr; L.plan.memo = nullptr;
+        L.w = L.in = L.gout = -1;
+        L.packed[0] = L.packed[1] = L.spectra = L.memo = kNone;
+        P.layers.push_back(L);
+    }
+    Layer& L = P.layers[l];
+    bool same = !L.has[o.kind];
+    auto is = [&](int& have, int b) { same = same && (have < 0 || have == b); have = b; };
+    if (o.kind != ZNN_OP_CONV_WGRAD) is(L.w, o.buf[1]);
+    if (o.kind != ZNN_OP_CONV_BWD) is(L.in, o.buf[0]);
+    if (o.kind != ZNN_OP_CONV_FWD) is(L.gout, o.buf[o.kind == ZNN_OP_CONV_BWD ? 0 : 1]);
+    L.has[o.kind] = true;
+    if (!same) { fail(ZNN_EINVAL, "operation %d: a plan stands for one layer of the program", i); return -1; }
+    return (int)l;
+}
+
+// Steps, places in the scratch memory and what is completed by the update.
+int place_steps(znn_program& P, const znn_op* ops, int count)
+{
+    auto add = [&](int kind) -> Step& {
+        Step s = {};
+        s.kind = kind; s.layer = -1; s.own = kNone;
+        P.steps.push_back(s);
+        return P.steps.back();
+    };
+    add(STEP_PACK).skip = true;
+    for (int i = 0; i < count; ++i) {
+        int rc = check_op(ops[i], i, P.buffers, P.streams);
+        if (rc != ZNN_OK) return rc;
+        Step& s = add(ops[i].kind);
+        s.op = ops[i];
+        s.stream = ops[i].stream;
+        if (s.kind <= ZNN_OP_CONV_WGRAD && (s.layer = layer_of(P, ops[i], i)) < 0) return ZNN_EINVAL;
+        if (s.kind == ZNN_OP_UPDATE) { s.skip = true; P.update_steps.push_back((int)P.steps.size() - 1); }
+    }
+    size_t at = 0, kept = 0;
+    auto take = [&](size_t bytes) { const size_t o = at; at += align256(bytes); return o; };
+    for (Layer& L : P.layers) {
+        if (L.plan.mode == ZNN_DIRECT) {
+            for (int b = 0; b < 2; ++b)
+                if (L.has[b] && mfma_conv_supported(L.plan.g, b == 1)) {
+                    L.packed[b] = take(mfma_conv_packed_bytes(L.plan.g, b == 1));
+                    P.steps[0].skip = false;
+                }
+        } else if (L.has[0] && L.has[1]) {
+            const size_t kernels = plan_kernel_bytes(&L.plan), nodes = plan_memo_bytes(&L.plan);
+            if (kept + kernels <= kKeptSpectra) { kept += kernels; L.spectra = take(kernels); }
+            if (L.has[2] && kept + nodes <= kKeptSpectra) { kept += nodes; L.memo = take(nodes); }
+        }
+    }
+    P.completes.assign(P.update_steps.size(), -1);
+    for (size_t u = 0; u < P.update_steps.size(); ++u) {
+        const int g = P.steps[P.update_steps[u]].op.buf[0];
+        for (size_t i = 0; i < P.steps.size(); ++i) {
+            Step& s = P.steps[i];
+            if (s.kind == ZNN_OP_BIAS_GRAD && s.op.buf[1] == g && s.own == kNone) {
+                s.own = take(sizeof(float) * s.op.maps * bias_spans(s.op));
+                s.skip = true;
+                P.bias_steps.push_back((int)i);
+                P.completes[u] = (int)i;
+            } else if (s.kind == ZNN_OP_CONV_WGRAD && s.op.buf[2] == g && s.own == kNone) {
+                const Layer& L = P.layers[s.layer];
+                if (L.plan.mode != ZNN_DIRECT || !mfma_wgrad_supported(L.plan.g)) continue;
+                s.own = take(mfma_wgrad_workspace(L.plan.g));
+                P.completes[u] = (int)i;
+            }
+        }
+    }
+    add(STEP_BIAS).skip = P.bias_steps.empty();
+    add(STEP_UPDATE).skip = P.update_steps.empty();
+    // scratch of the passes: one area per stream
+    std::vector<size_t> need(P.streams, 0);
+    for (Step& s : P.steps) {
+        if (s.layer < 0) continue;
+        const Layer& L = P.layers[s.layer];
+        const Geom& g = L.plan.g;
+        if (s.kind == ZNN_OP_CONV_WGRAD) s.pass_bytes = s.own != kNone ? 0 : plan_pass_bytes(&L.plan, s.kind, false);
+        else if (L.packed[s.kind] != kNone) {
+            const int splits = mfma_conv_splits(g, s.kind == ZNN_OP_CONV_BWD);
+            s.pass_bytes = splits > 1 ? sizeof(float) * splits * (s.kind ? (size_t)g.f * g.nvol() : (size_t)g.fo * g.ovol()) : 0;
+        } else s.pass_bytes = plan_pass_bytes(&L.plan, s.kind, L.spectra != kNone);
+        need[s.stream] = std::max(need[s.stream], align256(s.pass_bytes));
+    }
+    P.area.resize(P.streams);
+    for (int t = 0; t < P.streams; ++t) P.area[t] = take(need[t]);
+    P.scratch = at;
+    return ZNN_OK;
+}
+
+// What every step reads and writes: buffers, the sums that steps leave for the update, what the passes of a layer share.
+void name_resources(znn_program& P, int& resources)
+{
+    const int own = P.buffers, shared = own + (int)P.steps.size();      // shared: two per layer
+    resources = shared + 2 * (int)P.layers.size();
+    for (size_t i = 0; i < P.steps.size(); ++i) {
+        Step& s = P.steps[i];
+        const int* b = s.op.buf;
+        auto rd = [&](int x) { if (x >= 0) s.reads.push_back(x); };
+        auto wr = [&](int x) { if (x >= 0) s.writes.push_back(x); };
+        if (s.kind == STEP_PACK) {
+            for (size_t l = 0; l < P.layers.size(); ++l) {
+                const Layer& L = P.layers[l];
+                if (L.packed[0] != kNone || L.packed[1] != kNone) { rd(L.w); wr(shared + 2 * (int)l); }
+            }
+        } else if (s.kind == STEP_BIAS) {
+            for (int q : P.bias_steps) { rd(P.steps[q].op.buf[0]); wr(own + q); }
+        } else if (s.kind == STEP_UPDATE) {
+            for (size_t u = 0; u < P.update_steps.size(); ++u) {
+                const znn_op& o = P.steps[P.update_steps[u]].op;
+                if (P.completes[u] >= 0) { rd(own + P.completes[u]); wr(o.buf[0]); }
+                else rd(o.buf[0]);
+                wr(o.buf[1]);
+            }
+        } else if (s.skip) continue;
+        else switch (s.kind) {
+            case ZNN_OP_CONV_FWD: case ZNN_OP_CONV_BWD: {
+                const Layer& L = P.layers[s.layer];
+                const int kernels = shared + 2 * s.layer, nodes = kernels + 1;
+                rd(b[0]);
+                if (L.packed[s.kind] != kNone || (L.spectra != kNone && s.kind == ZNN_OP_CONV_BWD)) rd(kernels);
+                else { rd(b[1]); if (L.spectra != kNone) wr(kernels); }
+                if (L.memo != kNone) wr(nodes);
+                wr(b[2]);
+                rd(b[3]);
+                wr(b[4]);
+                break;
+            }
+            case ZNN_OP_CONV_WGRAD:
+                rd(b[0]); rd(b[1]);
+                if (P.layers[s.layer].memo != kNone) rd(shared + 2 * s.layer + 1);
+                wr(s.own != kNone ? own + (int)i : b[2]);
+                break;
+            case ZNN_OP_BIAS_GRAD: rd(b[0]); wr(b[1]); break;
+            case ZNN_OP_FILTER_FWD: case ZNN_OP_POOL_FWD: rd(b[0]); wr(b[1]); wr(b[2]); break;
+            case ZNN_OP_NODE_SUM: wr(b[0]); for (int q = 1; q < 8; ++q) rd(b[q]); break;
+            case ZNN_OP_LOSS_GRAD: rd(b[0]); rd(b[1]); wr(b[2]); wr(b[3]); break;
+            default: rd(b[0]); rd(b[1]); wr(b[2]); rd(b[3]); break;
+        }
+    }
+}
+
+// Waits between streams, without those that follow from earlier ones.
+int place_waits(znn_program& P)
+{
+    int resources = 0;
+    name_resources(P, resources);
+    const int n = (int)P.steps.size(), S = P.streams;
+    std::vector<int> writer(resources, -1), last(S, -1);
+    std::vector<std::vector<int>> readers(resources), after(n);
+    std::vector<std::vector<int>> over(S, std::vector<int>(S, -1));     // over[s][t]: last step of stream t over before stream s goes on
+    std::vector<char> record(n, 0);
+    P.used.assign(S, 0);
+    for (int i = 0; i < n; ++i) {
+        Step& s = P.steps[i];
+        if (s.skip) continue;
+        P.used[s.stream] = 1;
+        std::vector<int> deps;
+        for (int r : s.reads) if (writer[r] >= 0) deps.push_back(writer[r]);
+        for (int w : s.writes) {
+            if (writer[w] >= 0) deps.push_back(writer[w]);
+            deps.insert(deps.end(), readers[w].begin(), readers[w].end());
+        }
+        std::sort(deps.begin(), deps.end());
+        for (size_t k = deps.size(); k-- > 0;) {
+            const int d = deps[k], t = P.steps[d].stream;
+            if (t == s.stream || over[s.stream][t] >= d) continue;
+            s.waits.push_back(d);
+            record[d] = 1;
+            for (int q = 0; q < S; ++q) over[s.stream][q] = std::max(over[s.stream][q], after[d][q]);
+        }
+        for (int r : s.reads) readers[r].push_back(i);
+        for (int w : s.writes) { writer[w] = i; readers[w].clear(); }
+        over[s.stream][s.stream] = i;
+        after[i] = over[s.stream];
+        last[s.stream] = i;
+    }
+    for (int t = 1; t < S; ++t)
+        if (last[t] >= 0 && over[0][t] < last[t]) { record[last[t]] = 1; P.last_waits.push_back(last[t]); }
+    for (int i = 0; i < n; ++i)
+        if (record[i] && hipEventCreateWithFlags(&P.steps[i].event, hipEventDisableTiming) != hipSuccess)
+            return fail(ZNN_EHIP, "cannot create an event");
+    bool side = false;
+    for (int t = 1; t < S; ++t) side = side || P.used[t];
+    if (side && hipEventCreateWithFlags(&P.start, hipEventDisableTiming) != hipSuccess)
+        return fail(ZNN_EHIP, "cannot create an event");
+    return ZNN_OK;
+}
+
+// ---------------------------------------------------------------- launches
+unsigned blocks_of(long count) { return (unsigned)((count + 255) / 256); }
+
+int run_pack(const znn_program& P, float* const* buf, char* scratch, hipStream_t s)
+{
+    std::vector<PackItem> items;
+    for (const Layer& L : P.layers)
+        for (int b = 0; b < 2; ++b)
+            if (L.packed[b] != kNone)
+                items.push_back(mfma_conv_pack_item(L.plan.g, b == 1, buf[L.w], (float*)(scratch + L.packed[b])));
+    return mfma_pack_weights(items.data(), (int)items.size(), s);
+}
+
+int run_bias(const znn_program& P, float* const* buf, char* scratch, hipStream_t s)
+{
+    for (size_t i0 = 0; i0 < P.bias_steps.size(); i0 += kBiasItems) {
+        BiasArgs A = {};
+        unsigned blocks = 0;
+        for (; A.n < kBiasItems && i0 + A.n < P.bias_steps.size(); ++A.n) {
+            const Step& b = P.steps[P.bias_steps[i0 + A.n]];
+            A.item[A.n] = BiasItem{buf[b.op.buf[0]], (float*)(scratch + b.own), voxels(b.op), bias_spans(b.op), blocks};
+            blocks += (unsigned)bias_spans(b.op) * b.op.maps;
+        }
+        ZNN_LAUNCH("bias gradients", s, k_bias_parts, dim3(blocks), dim3(256), 0, A);
+    }
+    return check_launch("bias gradients");
+}
+
+int run_update(const znn_program& P, float* const* buf, char* scratch, float eta, hipStream_t s)
+{
+    for (size_t i0 = 0; i0 < P.update_steps.size(); i0 += kUpdateItems) {
+        UpdateArgs A = {};
+        A.eta = eta;
+        unsigned blocks = 0;
+        for (; A.n < kUpdateItems && i0 + A.n < P.update_steps.size(); ++A.n) {
+            const Step& u = P.steps[P.update_steps[i0 + A.n]];
+            const int done_by = P.completes[i0 + A.n];
+            UpdateItem& I = A.item[A.n];
+            I.grad = buf[u.op.buf[0]]; I.p = buf[u.op.buf[1]];
+            I.first = blocks;
+            I.total = elements(u.op);
+            if (done_by >= 0) {
+                const Step& d = P.steps[done_by];
+                I.src = (const float*)(scratch + d.own);
+                if (d.kind == ZNN_OP_BIAS_GRAD) { I.kind = 3; I.ksplit = bias_spans(d.op); }
+                else {
+                    const Geom& g = P.layers[d.layer].plan.g;
+                    I.kind = d.sum.four ? 2 : 1;
+                    I.f = g.f; I.taps = (int)g.kvol(); I.kx = g.kx; I.AB = g.kz * g.ky;
+                    I.ksplit = d.sum.ksplit; I.Mpad = d.sum.Mpad; I.Npad = d.sum.Npad; I.mapmajor = d.sum.mapmajor;
+                }
+            }
+            blocks += (unsigned)(I.kind == 2 ? (I.total + 63) / 64 : blocks_of(I.total));
+        }
+        ZNN_LAUNCH("gradient sums and update", s, k_update, dim3(blocks), dim3(256), 0, A);
+    }
+    return check_launch("gradient sums and update");
+}
+
+int run_conv(znn_program& P, Step& t, float* const* buf, char* scratch, hipStream_t s)
+{
+    Layer& L = P.layers[t.layer];
+    const Geom& g = L.plan.g;
+    const znn_op& o = t.op;
+    const bool bwd = t.kind == ZNN_OP_CONV_BWD;
+    char* const area = scratch + P.area[t.stream];
+    auto at = [&](int q) -> float* { return o.buf[q] < 0 ? nullptr : buf[o.buf[q]]; };
+    if (t.kind == ZNN_OP_CONV_WGRAD) {
+        if (t.own != kNone) return mfma_wgrad_partial(g, at(0), at(1), (float*)(scratch + t.own), &t.sum, s);
+        if (L.memo != kNone) return plan_wgrad_memo(&L.plan, (float2*)(scratch + L.memo), at(2), area, s);
+        return plan_pass(&L.plan, ZNN_PASS_WGRAD, at(0), at(1), at(2), nullptr, area, nullptr, s);
+    }
+    const long count = bwd ? (long)g.f * g.nvol() : (long)g.fo * g.ovol();
+    // what follows the sums: the next edge's transfer function, or the derivative of the one below
+    Finish F = {};
+    if (bwd) F.deriv = at(3); else { F.bias = at(3); F.y = at(4); }
+    F.fn = o.fn;
+    bool finished = !F.y && !F.deriv;
+    int rc;
+    if (L.packed[bwd] != kNone) {
+        const int splits = mfma_conv_splits(g, bwd);
+        const bool inside = !finished && splits == 1 && o.fn == ZNN_RECTIFY;
+        rc = mfma_conv_packed(g, bwd, at(0), (const float*)(scratch + L.packed[bwd]), at(2), (float*)area, inside ? F : Finish{}, s);
+        if (rc != ZNN_OK) return rc;
+        if (splits > 1) {
+            if (F.deriv) {
+                ZNN_LAUNCH("sum of shares, derivative", s, k_finish_bwd, dim3(blocks_of(count)), dim3(256), 0, (const float*)area, F.deriv, at(2),
+                           count, splits, o.fn);
+                finished = true;
+            } else if (F.y && g.fo <= 65535) {
+                ZNN_LAUNCH("sum of shares, transfer", s, k_finish_fwd, dim3(blocks_of(g.ovol()), (unsigned)g.fo), dim3(256), 0,
+                           (const float*)area, at(2), F.bias, F.y, (int)g.ovol(), count, splits, o.fn);
+                finished = true;
+            } else rc = mfma_conv_sum(g, bwd, (const float*)area, at(2), s);
+            if (rc != ZNN_OK) return rc;
+        } else finished = finished || inside;
+    } else if (L.spectra != kNone) {
+        float2* What = (float2*)(scratch + L.spectra);
+        if (!bwd) {
+            rc = plan_kernel_spectra(&L.plan, at(1), What, s);
+            if (rc != ZNN_OK) return rc;
+        }
+        float2* memo = L.memo != kNone ? (float2*)(scratch + L.memo) : nullptr;
+        rc = plan_pass(&L.plan, t.kind, at(0), nullptr, at(2), What, area, memo, s);
+        if (rc != ZNN_OK) return rc;
+    } else {
+        rc = plan_pass(&L.plan, t.kind, at(0), at(1), at(2), nullptr, area, nullptr, s);
+        if (rc != ZNN_OK) return rc;
+    }
+    if (!finished) {
+        if (F.y) return znn_transfer_fn_fwd(o.fn, g.fo, g.ovol(), at(2), F.bias, F.y, s);
+        ZNN_LAUNCH("transfer derivative", s, k_derivative_in_place, dim3(blocks_of(count)), dim3(256), 0, at(2), F.deriv, count, o.fn);
+    }
+    return check_launch("convolution of a program");
+}
+
+int run_step(znn_program& P, Step& t, float* const* buf, char* scratch, float eta, hipStream_t s)
+{
+    const znn_op& o = t.op;
+    auto at = [&](int q) -> float* { return o.buf[q] < 0 ? nullptr : buf[o.buf[q]]; };
+    const long count = t.kind > ZNN_OP_CONV_WGRAD ? elements(o) : 0;
+    switch (t.kind) {
+        case STEP_PACK: return run_pack(P, buf, scratch, s);
+        case STEP_BIAS: return run_bias(P, buf, scratch, s);
+        case STEP_UPDATE: return run_update(P, buf, scratch, eta, s);
+        case ZNN_OP_TRANSFER_FWD: return znn_transfer_fn_fwd(o.fn, o.maps, voxels(o), at(0), at(1), at(2), s);
+        case ZNN_OP_TRANSFER_BWD: return znn_transfer_fn_bwd(o.fn, o.maps, voxels(o), at(0), at(1), at(2), s);
+        case ZNN_OP_BIAS_GRAD: return znn_bias_grad(o.maps, voxels(o), at(0), at(1), s);
+        case ZNN_OP_FILTER_FWD:
+            return znn_maxfilter3d_sparse_fwd(o.maps, o.n, o.window, o.sparsity, at(0), at(1), (int32_t*)at(2), s);
+        case ZNN_OP_FILTER_BWD:
+            return maxfilter_bwd(o.maps, o.n, o.window, o.sparsity, at(0), (const int32_t*)at(1), at(2), at(3), o.fn, s);
+        case ZNN_OP_POOL_FWD: return znn_maxpool3d_fwd(o.maps, o.n, o.window, at(0), at(1), (int32_t*)at(2), s);
+        case ZNN_OP_POOL_BWD: {
+            int rc = znn_maxpool3d_bwd(o.maps, o.n, o.window, at(0), (const int32_t*)at(1), at(2), s);
+            if (rc != ZNN_OK || o.buf[3] < 0) return rc;
+            ZNN_LAUNCH("transfer derivative", s, k_derivative_in_place, dim3(blocks_of(count)), dim3(256), 0, at(2), at(3), count, o.fn);
+            return check_launch("transfer derivative");
+        }
+        case ZNN_OP_LOSS_GRAD:
+            ZNN_LAUNCH("loss gradient", s, k_loss_finish, dim3(blocks_of(count)), dim3(256), 0, count, at(0), at(1), at(2), at(3), o.loss, o.fn);
+            return check_launch("loss gradient");
+        case ZNN_OP_NODE_SUM: {
+            SumArgs A = {};
+            for (int q = 1; q < 7 && o.buf[q] >= 0; ++q) A.part[A.parts++] = at(q);
+            A.y = at(7); A.out = at(0); A.count = count; A.fn = o.fn;
+            ZNN_LAUNCH("node sum", s, k_node_sum, dim3(blocks_of(count)), dim3(256), 0, A);
+            return check_launch("node sum");
+        }
+    }
+    return run_conv(P, t, buf, scratch, s);
+}
+
+}  // namespace
+
+}  // namespace znn
+
+extern "C" {
+
+int znn_program_create(const znn_op* ops, int32_t count, int32_t buffers, int32_t streams, znn_program** program)
+{
+    if (!ops || !program) return fail(ZNN_EINVAL, "NULL argument");
+    if (count < 1 || buffers < 1 || streams < 1) return fail(ZNN_EINVAL, "a program needs operations, buffers and a stream");
+    znn_program* P = new (std::nothrow) znn_program;
+    if (!P) return fail(ZNN_EINVAL, "out of host memory");
+    P->buffers = buffers; P->streams = streams; P->start = nullptr; P->scratch = 0;
+    int rc = place_steps(*P, ops, count);
+    if (rc == ZNN_OK) rc = place_waits(*P);
+    if (rc != ZNN_OK) { znn_program_destroy(P); return rc; }
+    *program = P;
+    return ZNN_OK;
+}
+
+void znn_program_destroy(znn_program* program)
+{
+    if (!program) return;
+    for (Step& s : program->steps) if (s.event) (void)hipEventDestroy(s.event);
+    if (program->start) (void)hipEventDestroy(program->start);
+    delete program;
+}
+
+int znn_program_scratch_bytes(const znn_program* program, size_t* bytes)
+{
+    if (!program || !bytes) return fail(ZNN_EINVAL, "NULL argument");
+    *bytes = program->scratch;
+    return ZNN_OK;
+}
+
+int znn_program_run(znn_program* program, void* const* buffers, void* scratch, size_t scratch_bytes, float eta,
+                    void* const* streams)
+{
+    if (!program || !buffers || !streams) return fail(ZNN_EINVAL, "NULL argument");
+    znn_program& P = *program;
+    for (int b = 0; b < P.buffers; ++b) if (!buffers[b]) return fail(ZNN_EINVAL, "buffer %d is NULL", b);
+    if (P.scratch) {
+        if (!scratch) return fail(ZNN_EWORKSPACE, "scratch is NULL but %zu bytes are needed", P.scratch);
+        if ((uintptr_t)scratch & 255) return fail(ZNN_EWORKSPACE, "scratch is not 256-byte aligned");
+        if (scratch_bytes < P.scratch) return fail(ZNN_EWORKSPACE, "scratch has %zu bytes, %zu needed", scratch_bytes, P.scratch);
+    }
+    hipStream_t const* st = (hipStream_t const*)streams;
+    bool ok = true;
+    if (P.start) {
+        ok = hipEventRecord(P.start, st[0]) == hipSuccess;
+        for (int t = 1; t < P.streams; ++t) if (P.used[t]) ok = ok && hipStreamWaitEvent(st[t], P.start, 0) == hipSuccess;
+    }
+    // a failed launch still leaves the side streams joined below
+    int rc = ZNN_OK;
+    for (Step& s : P.steps) {
+        if (s.skip) continue;
+        for (int d : s.waits) ok = ok && hipStreamWaitEvent(st[s.stream], P.steps[d].event, 0) == hipSuccess;
+        if (rc == ZNN_OK) rc = run_step(P, s, (float* const*)buffers, (char*)scratch, eta, st[s.stream]);
+        if (s.event) ok = ok && hipEventRecord(s.event, st[s.stream]) == hipSuccess;
+    }
+    for (int d : P.last_waits) ok = ok && hipStreamWaitEvent(st[0], P.steps[d].event, 0) == hipSuccess;
+    if (rc != ZNN_OK) return rc;
+    return ok ? ZNN_OK : fail(ZNN_EHIP, "cannot order the streams of the program");
+}
+
+}  // extern "C"

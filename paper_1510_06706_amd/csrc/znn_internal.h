@@ -102,6 +102,24 @@ int direct_fwd(const Geom& g, const float* in, const float* w, float* out, void*
 int direct_bwd(const Geom& g, const float* gout, const float* w, float* gin, void* ws, hipStream_t s);
 int direct_wgrad(const Geom& g, const float* in, const float* gout, float* gw, void* ws, hipStream_t s);
 size_t direct_workspace_bytes(const Geom& g, int pass);
+// The tiled kernels in pieces, for rounds that pack the weights of all layers at once and finish several sums in one launch
+struct PackItem { const float* w; float* wp; int f, fo, kz, ky, kx, backward, NJ, nchunk, tail; long total; };
+bool mfma_conv_supported(const Geom& g, bool backward);
+PackItem mfma_conv_pack_item(const Geom& g, bool backward, const float* w, float* wp);
+int mfma_pack_weights(const PackItem* items, int n, hipStream_t s);
+size_t mfma_conv_packed_bytes(const Geom& g, bool backward);
+int mfma_conv_splits(const Geom& g, bool backward);
+// what a pass does with its finished sums v: y = fn(v + bias[map]) beside v (forward), or v times fn's derivative at the
+// forward result `deriv` (backward); the kernel itself takes the rectifier only
+struct Finish { float* y; const float* bias; const float* deriv; int fn; };
+int mfma_conv_packed(const Geom& g, bool backward, const float* src, const float* wp, float* dst, float* partial,
+                     const Finish& finish, hipStream_t s);
+int mfma_conv_sum(const Geom& g, bool backward, const float* partial, float* dst, hipStream_t s);
+bool mfma_wgrad_supported(const Geom& g);
+size_t mfma_wgrad_workspace(const Geom& g);
+// partial sums only; `sum` says how to add them: gw[e] = sum over splits in the order of k_wgrad_reduce / k_wgrad_reduce4
+struct WgradSum { int ksplit, Mpad, Npad, mapmajor, four; };
+int mfma_wgrad_partial(const Geom& g, const float* in, const float* gout, float* partial, WgradSum* sum, hipStream_t s);
 // expected seconds of a pass (choice between the methods where nothing has been measured)
 double mfma_conv_seconds(const Geom& g, bool backward);
 double mfma_wgrad_seconds(const Geom& g);
@@ -240,6 +258,21 @@ int  fft_x_c2r_reg(const XRegC2R& P, int N, hipStream_t s);
 
 // ---------------------------------------------------------------- fill (autotuner)
 int fill_pattern(float* p, long count, float scale, hipStream_t s);
+
+// max-filter backward, times the derivative of the transfer function that gave y (y may be NULL)
+int maxfilter_bwd(int32_t maps, znn_vec3 n, znn_vec3 win, znn_vec3 sp, const float* gout, const int32_t* idx, float* gin,
+                  const float* y, int fn, hipStream_t s);
+int check_filter(int32_t maps, znn_vec3 n, znn_vec3 win, znn_vec3 sp, bool pool);
+
+// ---------------------------------------------------------------- passes of a plan with buffers given by the caller
+size_t plan_pass_bytes(const znn_plan* p, int pass, bool resident);
+size_t plan_kernel_bytes(const znn_plan* p);        // spectra of the kernels
+size_t plan_memo_bytes(const znn_plan* p);          // spectra of images and gradients
+int plan_kernel_spectra(const znn_plan* p, const float* w, float2* What, hipStream_t s);
+// forward: a = in, b = w, result = out; backward: gout, w, gin; kernel gradient: in, gout, gw
+int plan_pass(const znn_plan* p, int pass, const float* a, const float* b, float* result, const float2* resident, void* ws,
+              float2* memo, hipStream_t s);
+int plan_wgrad_memo(const znn_plan* p, float2* memo, float* gw, void* ws, hipStream_t s);
 
 }  // namespace znn
 

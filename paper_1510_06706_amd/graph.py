@@ -22,9 +22,12 @@ The graph format is the one of ``synth.graph_shapes``.
 """
 from __future__ import annotations
 
+import math
+
 import numpy as np
 
 from . import binding as znn
+from . import program as zp
 from .synth import ONES, _opt, graph_shapes
 
 
@@ -75,6 +78,7 @@ class GraphNet:
         self.params = {n: {k: torch.from_numpy(np.ascontiguousarray(v)).to(device) for k, v in p.items()}
                        for n, p in params.items()}
         self.streams = [torch.cuda.Stream(device=device) for _ in range(max(1, int(streams)))]
+        self._programs = {}
         self._events, self._next_event = [], 0      # events are reused from round to round
         self.incoming, self.outgoing = {}, {}
         for e in self.edges:
@@ -210,13 +214,134 @@ class GraphNet:
             main.wait_event(ev)
         return grads, back
 
+    # ------------------------------------------------------------ rounds as one native call
+    def _build(self, loss):
+        """A training round as a program: edge i runs on stream 1 + i mod (number of streams), kernel gradients half
+        the streams further on, sums at a node on the stream of the last edge into it; the loss gradients and
+        the update run on the calling stream.  Where an edge alone fills a node, what follows the node is
+        applied by that edge's operation."""
+        g, shape, E = self.graph, self.shapes, self.edges
+        P = zp.Program(self.device, 1 + len(self.streams))
+        stream = lambda i: 1 + i % len(self.streams)  # noqa: E731
+        given = {("x", n): P.buffer("given", shape[n]) for n in g["inputs"]}
+        for n, p in self.params.items():
+            for k in p:
+                given[n, k] = P.buffer("given", p[k].shape)
+        by_name = {e[1]: e for e in E}
+
+        def parts_sum(out, parts, at, dims):
+            """Operation(s) that add `parts` in order into buffer `out`; the last one."""
+            while True:
+                op = P.add(zp.NODE_SUM, [out] + parts[:6], stream=at, maps=dims[0], n=dims[1:])
+                if len(parts) <= 6:
+                    return op
+                parts = [out] + parts[6:]
+
+        # forward: img[n] is node n's image, aux[e] what the backward edge reads
+        img, aux, part = {n: given["x", n] for n in g["inputs"]}, {}, {}
+        alone = lambda n: len(self.incoming[n]) == 1  # noqa: E731
+        for i, e in enumerate(E):
+            kind, name, src, dst = e[:4]
+            how = dict(stream=stream(i), maps=shape[src][0], n=shape[src][1:])
+            if name not in part:                # a transfer edge may have been taken over by the convolution before it
+                y = part[name] = P.buffer("fresh" if alone(dst) or kind == "transfer" else "kept", shape[dst])
+                if kind == "conv":
+                    op = P.add(zp.CONV_FWD, (img[src], given[name, "w"], y), stream=stream(i), plan=self.plans[name])
+                    then = next((by_name[n] for n in self.outgoing.get(dst, ()) if by_name[n][0] == "transfer"), None)
+                    if alone(dst) and then is not None:
+                        aux[then[1]] = part[then[1]] = P.buffer("fresh", shape[then[3]])
+                        P.attach(op, _opt(then, 4, "rectify"), part[then[1]], given[then[1], "b"])
+                elif kind == "transfer":
+                    aux[name] = y
+                    P.add(zp.TRANSFER_FWD, (img[src], given[name, "b"], y), fn=_opt(e, 4, "rectify"), **how)
+                else:
+                    aux[name] = P.buffer("fresh", shape[dst], True)
+                    P.add(zp.FILTER_FWD if kind == "maxfilter" else zp.POOL_FWD, (img[src], y, aux[name]), window=e[4],
+                          sparsity=_opt(e, 5, ONES) if kind == "maxfilter" else ONES, **how)
+            if all(n in part for n in self.incoming[dst]) and dst not in img:
+                if alone(dst):
+                    img[dst] = part[name]
+                else:
+                    img[dst] = P.buffer("fresh", shape[dst])
+                    parts_sum(img[dst], [part[n] for n in self.incoming[dst]], stream(i), shape[dst])
+
+        # backward: back[n] is node n's backward image, `below` the transfer edge whose derivative it already holds
+        gout, targets, back, below, gpart, grads = {}, {}, {}, {}, {}, {}
+        outgoing = lambda n: list(reversed(self.outgoing.get(n, [])))  # noqa: E731
+
+        def finish(node, at):
+            order = ["loss"] * (node in gout) + outgoing(node)
+            buf, op = gpart[node][order[0]]
+            if len(order) > 1:
+                buf = P.buffer("kept", shape[node])
+                op = parts_sum(buf, [gpart[node][k][0] for k in order], at, shape[node])
+            # the only edge into the node is a transfer function: its derivative with the sum
+            e = by_name[self.incoming[node][0]] if alone(node) else None
+            if e is not None and e[0] == "transfer":
+                if op["kind"] == zp.LOSS_GRAD:
+                    gx = P.buffer("kept", shape[node])
+                    P.attach(op, _opt(e, 4, "rectify"), gx=gx)
+                    buf, below[node] = gx, e[1]
+                elif P.attach(op, _opt(e, 4, "rectify"), aux[e[1]]):
+                    below[node] = e[1]
+            back[node] = (buf, op)
+
+        for n in g["outputs"]:
+            gout[n], targets[n] = P.buffer("fresh", shape[n]), P.buffer("given", shape[n])
+            op = P.add(zp.LOSS_GRAD, (img[n], targets[n], gout[n]), loss=loss, maps=shape[n][0], n=shape[n][1:])
+            gpart.setdefault(n, {})["loss"] = (gout[n], op)
+            if n not in self.outgoing:
+                finish(n, 0)
+        for i, e in enumerate(reversed(E)):
+            kind, name, src, dst = e[:4]
+            s, (b, op) = stream(i), back[dst]
+            how = dict(stream=s, maps=shape[src][0], n=shape[src][1:])
+            needed = src not in g["inputs"]
+            gs = None
+            if kind == "conv":
+                grads[name] = {"w": P.buffer("gradient", self.params[name]["w"].shape)}
+                if needed:
+                    gs = P.buffer("kept", shape[src])
+                    gop = P.add(zp.CONV_BWD, (b, given[name, "w"], gs), stream=s, plan=self.plans[name])
+                P.add(zp.CONV_WGRAD, (img[src], b, grads[name]["w"]), stream=stream(i + 1 + len(self.streams) // 2),
+                      plan=self.plans[name])
+            elif kind == "transfer":
+                if below.get(dst) == name:
+                    gs, gop = b, dict(op, kind=None)
+                else:
+                    gs = P.buffer("kept", shape[src])
+                    gop = P.add(zp.TRANSFER_BWD, (b, aux[name], gs), fn=_opt(e, 4, "rectify"), **how)
+                grads[name] = {"b": P.buffer("gradient", (shape[src][0],))}
+                P.add(zp.BIAS_GRAD, (gs, grads[name]["b"]), **how)
+            elif needed:
+                gs = P.buffer("kept", shape[src])
+                gop = P.add(zp.FILTER_BWD if kind == "maxfilter" else zp.POOL_BWD, (b, aux[name], gs), window=e[4],
+                            sparsity=_opt(e, 5, ONES) if kind == "maxfilter" else ONES, **how)
+            if gs is None or not needed:
+                continue
+            gpart.setdefault(src, {})[name] = (gs, gop)
+            if len(gpart[src]) == len(self.outgoing[src]) + (src in gout):
+                finish(src, s)
+        for n, d in grads.items():
+            for k in d:
+                P.add(zp.UPDATE, (d[k], given[n, k]), n=(1, 1, self.params[n][k].numel()))
+        return P.build(), given, targets, img, aux, gout, grads
+
     def train_round(self, inputs, targets, eta, loss="square"):
         """Forward, loss gradient at every output node, backward, update (Algorithm 3).  The
         update runs after every stream has joined: kernels are read by the backward edges."""
-        img, aux, _ = self.forward(inputs)
-        gout = {n: znn.loss_grad(img[n], targets[n], loss) for n in self.graph["outputs"]}
-        grads, back = self.backward(img, aux, gout)
-        for name, p in self.params.items():
+        if loss not in zp.LOSSES:
+            raise ValueError(loss)
+        if loss not in self._programs:
+            self._programs[loss] = self._build(loss)
+        P, given, target, img, aux, gout, grads = self._programs[loss]
+        tensors = {given["x", n]: zp.check_input(inputs[n], self.shapes[n]) for n in self.graph["inputs"]}
+        for n, p in self.params.items():
             for k in p:
-                znn.sgd_update(p[k], grads[name][k], eta)
-        return img, aux, gout, grads
+                tensors[given[n, k]] = zp.check_input(p[k], P.shapes[given[n, k]])
+        for n, b in target.items():
+            tensors[b] = zp.check_input(targets[n], count=math.prod(self.shapes[n]))
+        out = P.run(tensors, float(eta), self.streams)
+        out.update({given["x", n]: inputs[n] for n in self.graph["inputs"]})
+        return ({n: out[b] for n, b in img.items()}, {n: out[b] for n, b in aux.items()}, {n: out[b] for n, b in gout.items()},
+                {n: {k: out[b] for k, b in d.items()} for n, d in grads.items()})

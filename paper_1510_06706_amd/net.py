@@ -7,9 +7,12 @@ synthetic tensors live in ``synth``.
 """
 from __future__ import annotations
 
+import math
+
 import numpy as np
 
 from . import binding as znn
+from . import program as zp
 from .synth import ONES, _opt, shapes
 
 
@@ -47,11 +50,97 @@ class Net:
                 self.plans.append(plan)
             else:
                 self.plans.append(None)
+        self._memo = "fft_memo" in self.strategy
+        self._programs = {}
 
     def modes(self):
         return [None if p is None else p.mode for p in self.plans]
 
+    # ------------------------------------------------------------ rounds as one native call
+    def _program(self, loss):
+        """The forward pass (loss None) or a whole training round as a program on the calling stream (kernel gradients
+        on a second stream gained nothing: 410 against 422 us a round of the six-layer 3D net, 40 us slower replayed)."""
+        if loss in self._programs:
+            return self._programs[loss]
+        P = zp.Program(self.device)
+        L, shape = self.layers, self.shapes
+        given = {("x", 0): P.buffer("given", shape[0])}
+        for l, p in enumerate(self.params):
+            for k in p or ():
+                given[l, k] = P.buffer("given", p[k].shape)
+        act, aux, conv = [given["x", 0]], [None] * len(L), None
+        for l, spec in enumerate(L):
+            kind, y = spec[0], P.buffer("fresh", shape[l + 1])
+            if kind == "conv":
+                conv = P.add(zp.CONV_FWD, (act[-1], given[l, "w"], y), plan=self.plans[l])
+            elif kind == "transfer":
+                fn = _opt(spec, 1, "rectify")
+                if conv is None or not P.attach(conv, fn, y, given[l, "b"]):
+                    P.add(zp.TRANSFER_FWD, (act[-1], given[l, "b"], y), fn=fn, maps=shape[l][0], n=shape[l][1:])
+            else:
+                aux[l] = P.buffer("fresh", shape[l + 1], True)
+                P.add(zp.FILTER_FWD if kind == "maxfilter" else zp.POOL_FWD, (act[-1], y, aux[l]), maps=shape[l][0],
+                      n=shape[l][1:], window=spec[1], sparsity=_opt(spec, 2, ONES) if kind == "maxfilter" else ONES)
+            if kind != "conv":
+                conv = None
+            act.append(y)
+        grads, gout, target = [None] * len(L), None, None
+        if loss is not None:
+            target, gout = P.buffer("given", shape[-1]), P.buffer("fresh", shape[-1])
+            g, op = gout, P.add(zp.LOSS_GRAD, (act[-1], target, gout), loss=loss, maps=shape[-1][0], n=shape[-1][1:])
+            for l in range(len(L) - 1, -1, -1):
+                spec, kind = L[l], L[l][0]
+                below = lambda: P.buffer("kept", shape[l])  # noqa: B023,E731
+                how = dict(maps=shape[l][0], n=shape[l][1:])
+                if kind == "transfer":
+                    # the operation that completed g applies the derivative itself where it can
+                    fn = _opt(spec, 1, "rectify")
+                    if op is None or op["kind"] == zp.LOSS_GRAD or not P.attach(op, fn, act[l + 1]):
+                        h = below()
+                        if op is None or not P.attach(op, fn, gx=h):
+                            P.add(zp.TRANSFER_BWD, (g, act[l + 1], h), fn=fn, **how)
+                        g = h
+                    grads[l] = {"b": P.buffer("gradient", (shape[l][0],))}
+                    P.add(zp.BIAS_GRAD, (g, grads[l]["b"]), **how)
+                    op = None
+                elif kind == "conv":
+                    grads[l] = {"w": P.buffer("gradient", self.params[l]["w"].shape)}
+                    ready = g
+                    if l > 0:
+                        g = below()
+                        op = P.add(zp.CONV_BWD, (ready, given[l, "w"], g), plan=self.plans[l])
+                    P.add(zp.CONV_WGRAD, (act[l], ready, grads[l]["w"]), plan=self.plans[l])
+                elif l > 0:
+                    h = below()
+                    op = P.add(zp.FILTER_BWD if kind == "maxfilter" else zp.POOL_BWD, (g, aux[l], h), window=spec[1],
+                               sparsity=_opt(spec, 2, ONES) if kind == "maxfilter" else ONES, **how)
+                    g = h
+            for l, d in enumerate(grads):
+                for k in d or ():
+                    P.add(zp.UPDATE, (d[k], given[l, k]), n=(1, 1, self.params[l][k].numel()))
+        self._programs[loss] = P.build(), given, act, aux, target, gout, grads
+        return self._programs[loss]
+
+    def _run(self, loss, x, target=None, eta=0.0):
+        P, given, act, aux, t, gout, grads = self._program(loss)
+        tensors = {given["x", 0]: zp.check_input(x, self.shapes[0])}
+        for l, p in enumerate(self.params):
+            for k in p or ():
+                tensors[given[l, k]] = zp.check_input(p[k], P.shapes[given[l, k]])
+        if loss is not None:
+            tensors[t] = zp.check_input(target, count=math.prod(self.shapes[-1]))
+        out = P.run(tensors, float(eta))
+        return ([x] + [out[b] for b in act[1:]], [None if b is None else out[b] for b in aux],
+                None if gout is None else out[gout],
+                [None if d is None else {k: out[b] for k, b in d.items()} for d in grads])
+
     def forward(self, x):
+        if not self._memo:
+            return self._run(None, x)[:2]
+        return self._forward_by_layer(x)
+
+    def _forward_by_layer(self, x):
+        """One library call per layer: what plans with memoized spectra of their own need before ``backward``."""
         acts, aux = [x], [None] * len(self.layers)
         for l, spec in enumerate(self.layers):
             a = acts[-1]
@@ -94,7 +183,11 @@ class Net:
         return grads
 
     def train_round(self, x, target, eta, record=None, loss="square"):
-        acts, aux = self.forward(x)
+        if loss not in zp.LOSSES:
+            raise ValueError(loss)
+        if record is None:
+            return self._run(loss, x, target, eta)
+        acts, aux = self._forward_by_layer(x)
         gout = znn.loss_grad(acts[-1], target, loss)
         grads = self.backward(acts, aux, gout, record)
         for p, g in zip(self.params, grads):

@@ -1,0 +1,139 @@
+"""A round of a net as one native call (``znn_program_*``): the operations and their buffers.
+
+``net`` and ``graph`` list the operations of a round once, with the buffers they work on; a run then
+makes the tensors that the round returns, hands all pointers to the library in one call and launches
+nothing itself.  Every arithmetic step runs in libznn's kernels.
+"""
+from __future__ import annotations
+
+import ctypes
+import math
+
+from . import binding as znn
+from .binding import TRANSFER_FNS
+
+(CONV_FWD, CONV_BWD, CONV_WGRAD, TRANSFER_FWD, TRANSFER_BWD, BIAS_GRAD, FILTER_FWD, FILTER_BWD, POOL_FWD, POOL_BWD,
+ LOSS_GRAD, NODE_SUM, UPDATE) = range(13)
+LOSSES = {"square": 0, "cross_entropy": 1}
+
+
+class Program:
+    """Buffers are numbers.  ``given`` ones are tensors of the caller, ``fresh`` ones are allocated by every
+    run and returned, ``gradient`` ones likewise (all from one allocation), ``kept`` ones never leave the program."""
+
+    def __init__(self, device, streams=1):
+        self.device, self.streams = device, streams
+        self.ops, self.plans = [], []
+        self.shapes, self.kinds = [], []
+        self._h = None
+
+    # ------------------------------------------------------------ description
+    def buffer(self, kind, shape, integer=False):
+        self.shapes.append(tuple(shape))
+        self.kinds.append((kind, integer))
+        return len(self.kinds) - 1
+
+    def add(self, kind, buf, stream=0, plan=None, fn="rectify", loss="square", maps=1, n=(1, 1, 1),
+            window=(1, 1, 1), sparsity=(1, 1, 1)):
+        """Adds an operation and returns it; what follows its result may still be attached to it."""
+        op = dict(kind=kind, buf=list(buf) + [-1] * (8 - len(buf)), stream=stream, plan=plan, fn=TRANSFER_FNS[fn],
+                  loss=LOSSES[loss], maps=maps, n=n, window=window, sparsity=sparsity)
+        self.ops.append(op)
+        return op
+
+    @staticmethod
+    def attach(op, fn, y=-1, bias=-1, gx=-1):
+        """Lets `op` apply what follows it: a forward convolution the transfer function (bias, y), a loss gradient
+        (gx) or a backward operation (y) the derivative of the edge below.  False if the operation cannot."""
+        at = {CONV_FWD: ((3, bias), (4, y)), CONV_BWD: ((3, y),), FILTER_BWD: ((3, y),), POOL_BWD: ((3, y),),
+              LOSS_GRAD: ((3, gx),), NODE_SUM: ((7, y),)}.get(op["kind"])
+        if at is None or any(op["buf"][i] >= 0 for i, _ in at):
+            return False
+        for i, b in at:
+            op["buf"][i] = b
+        op["fn"] = TRANSFER_FNS[fn]
+        return True
+
+    def build(self):
+        n = len(self.kinds)
+        ops = (znn.Op * len(self.ops))()
+        for o, d in zip(ops, self.ops):
+            o.kind, o.stream, o.fn, o.loss, o.maps = d["kind"], d["stream"], d["fn"], d["loss"], d["maps"]
+            o.n, o.window, o.sparsity = (znn._v3(d[k]) for k in ("n", "window", "sparsity"))
+            o.buf[:] = d["buf"]
+            if d["plan"] is not None:
+                self.plans.append(d["plan"])
+                o.plan = d["plan"]._h.value
+        h = ctypes.c_void_p(0)
+        znn._check(znn.lib().znn_program_create(ops, len(self.ops), n, self.streams, ctypes.byref(h)))
+        self._h = h
+        need = ctypes.c_size_t(0)
+        znn._check(znn.lib().znn_program_scratch_bytes(h, ctypes.byref(need)))
+        self.scratch_bytes = need.value
+        up = lambda b: (b + 255) & ~255  # noqa: E731
+        kept, slab = up(need.value), 0
+        self._kept, self._grads, self._fresh = [], [], []
+        for b, (kind, integer) in enumerate(self.kinds):
+            size = 4 * math.prod(self.shapes[b])
+            if kind == "kept":
+                self._kept.append((b, kept))
+                kept += up(size)
+            elif kind == "gradient":
+                self._grads.append((b, slab))
+                slab += up(size)
+            elif kind == "fresh":
+                self._fresh.append((b, self.shapes[b], integer))
+        self._kept_bytes, self._slab = kept, slab // 4
+        self._scratch, self._buf, self._st = None, (ctypes.c_void_p * n)(), (ctypes.c_void_p * self.streams)()
+        return self
+
+    def __del__(self):
+        try:
+            if self._h:
+                znn.lib().znn_program_destroy(self._h)
+                self._h = None
+        except Exception:
+            pass
+
+    # ------------------------------------------------------------ runs
+    def run(self, given, eta=0.0, streams=()):
+        """given: {buffer: tensor}, checked by the caller.  Runs on the current stream (and `streams`, which
+        it joins); returns {buffer: tensor} of the fresh and the gradient buffers."""
+        import torch
+        buf, device = self._buf, self.device
+        if self._scratch is None and self._kept_bytes:
+            self._scratch = torch.empty(self._kept_bytes + 256, dtype=torch.uint8, device=device)
+            self._base = (self._scratch.data_ptr() + 255) & ~255
+            for b, at in self._kept:
+                buf[b] = self._base + at
+        for b, t in given.items():
+            buf[b] = t.data_ptr()
+        out = {}
+        for b, shape, integer in self._fresh:
+            t = out[b] = torch.empty(shape, dtype=torch.int32 if integer else torch.float32, device=device)
+            buf[b] = t.data_ptr()
+        if self._slab:
+            slab = torch.empty(self._slab, dtype=torch.float32, device=device)
+            base = slab.data_ptr()
+            for b, at in self._grads:
+                buf[b] = base + at
+        st = self._st
+        st[0] = torch.cuda.current_stream().cuda_stream
+        for i, s in enumerate(streams):
+            st[i + 1] = s.cuda_stream
+        znn._check(znn.lib().znn_program_run(self._h, buf, self._base if self._kept_bytes else None, self.scratch_bytes, eta, st))
+        for b, at in self._grads:
+            shape = self.shapes[b]
+            out[b] = slab[at // 4:at // 4 + math.prod(shape)].view(shape)
+        return out
+
+
+def check_input(t, shape=None, count=None):
+    """A tensor handed to a round: float32 values on the GPU, contiguous, of the shape (or number of values) expected."""
+    import torch
+    if shape is not None:
+        assert tuple(t.shape) == tuple(shape), t.shape
+    znn._ptr(t, torch.float32)
+    if count is not None and t.numel() != count:
+        raise ValueError("expected %d values, got %d" % (count, t.numel()))
+    return t

@@ -139,3 +139,37 @@ def test_captured_training_round_replays_bit_for_bit():
             # unrelated eager work between replays
             scratch = znn.transfer_fwd(d_x, dev(np.zeros(in_shape[0], dtype=np.float32)))
             del scratch
+
+
+NET_FORMS = {
+    # shares of the input maps and single launches, every transfer function behind and before them
+    "functions": ((1, 14, 15, 13), [("conv", 1, 20, (3, 3, 3)), ("transfer", "tanh"), ("conv", 20, 24, (2, 3, 3)),
+                                    ("transfer",), ("conv", 24, 3, (3, 3, 3)), ("transfer", "logistic")]),
+    # filters of unequal windows and spacings, pooling, transfer edges that nothing can take over
+    "filters": ((3, 12, 13, 16), [("conv", 3, 5, (2, 2, 2)), ("maxfilter", (2, 2, 1), (1, 2, 1)), ("transfer",),
+                                  ("transfer", "tanh"), ("maxfilter", (2, 2, 2), (2, 1, 3)), ("transfer",),
+                                  ("maxpool", (2, 1, 3)), ("maxfilter", (1, 2, 2)), ("transfer", "logistic")]),
+    # many output voxels: the kernel itself applies the rectifier and its derivative
+    "large": ((2, 40, 66, 70), [("conv", 2, 17, (3, 3, 3)), ("transfer",), ("conv", 17, 20, (2, 2, 2)), ("transfer",),
+                                ("conv", 20, 2, (1, 2, 3)), ("transfer", "tanh")]),
+}
+
+
+@pytest.mark.parametrize("form", sorted(NET_FORMS))
+@pytest.mark.parametrize("mode", ["direct", "fft"])
+def test_round_as_one_program_matches_the_calls_per_layer(form, mode):
+    """`record` makes the round go layer by layer through the single entry points."""
+    in_shape, layers = NET_FORMS[form]
+    x, target, params = synth.net_tensors(layers, in_shape, 61)
+    one, by_layer = znet.Net(layers, in_shape, params, mode), znet.Net(layers, in_shape, params, mode)
+    for round_ in range(2):
+        got = one.train_round(dev(x), dev(target), 0.01 / target.size)
+        ref = by_layer.train_round(dev(x), dev(target), 0.01 / target.size, record=[])
+        for l in range(len(layers)):
+            assert rel_err(host(got[0][l + 1]), host(ref[0][l + 1])) <= 1e-6, ("image", l)
+            if got[1][l] is not None:
+                assert np.array_equal(host(got[1][l]), host(ref[1][l])), ("choice", l)
+            for k in ref[3][l] or ():
+                assert rel_err(host(got[3][l][k]), host(ref[3][l][k])) <= 2e-5, ("gradient", l, k)
+                assert rel_err(host(one.params[l][k]), host(by_layer.params[l][k])) <= 2e-6, ("update", l, k)
+        assert rel_err(host(got[2]), host(ref[2])) <= 1e-6
