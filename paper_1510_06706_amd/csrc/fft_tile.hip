@@ -874,6 +874,7 @@ static double round_seconds(const Geom& g, const Tiling& L)
 Tiling tile_search(const Geom& g, size_t spectra_bytes)
 {
     Tiling best = {};
+    if (g.f > 65535) return best;       // maps are an extent of the grid that sums tiles
     const int n[3] = {g.nz, g.ny, g.nx}, o[3] = {g.oz, g.oy, g.ox};
     const int S[3] = {g.spz * (g.kz - 1) + 1, g.spy * (g.ky - 1) + 1, g.spx * (g.kx - 1) + 1};
     double best_t = 0;

@@ -623,8 +623,13 @@ int znn_program_create(const znn_op* ops, int32_t count, int32_t buffers, int32_
     znn_program* P = new (std::nothrow) znn_program;
     if (!P) return fail(ZNN_EINVAL, "out of host memory");
     P->buffers = buffers; P->streams = streams; P->start = nullptr; P->scratch = 0;
-    int rc = place_steps(*P, ops, count);
-    if (rc == ZNN_OK) rc = place_waits(*P);
+    int rc;
+    try {
+        rc = place_steps(*P, ops, count);
+        if (rc == ZNN_OK) rc = place_waits(*P);
+    } catch (const std::bad_alloc&) {       // callers are in other languages: no exception leaves the library
+        rc = fail(ZNN_EINVAL, "out of host memory");
+    }
     if (rc != ZNN_OK) { znn_program_destroy(P); return rc; }
     *program = P;
     return ZNN_OK;
@@ -667,7 +672,11 @@ int znn_program_run(znn_program* program, void* const* buffers, void* scratch, s
     for (Step& s : P.steps) {
         if (s.skip) continue;
         for (int d : s.waits) ok = ok && hipStreamWaitEvent(st[s.stream], P.steps[d].event, 0) == hipSuccess;
-        if (rc == ZNN_OK) rc = run_step(P, s, (float* const*)buffers, (char*)scratch, eta, st[s.stream]);
+        try {
+            if (rc == ZNN_OK) rc = run_step(P, s, (float* const*)buffers, (char*)scratch, eta, st[s.stream]);
+        } catch (const std::bad_alloc&) {
+            rc = fail(ZNN_EINVAL, "out of host memory");
+        }
         if (s.event) ok = ok && hipEventRecord(s.event, st[s.stream]) == hipSuccess;
     }
     for (int d : P.last_waits) ok = ok && hipStreamWaitEvent(st[0], P.steps[d].event, 0) == hipSuccess;

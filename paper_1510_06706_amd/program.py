@@ -84,7 +84,7 @@ class Program:
             elif kind == "fresh":
                 self._fresh.append((b, self.shapes[b], integer))
         self._kept_bytes, self._slab = kept, slab // 4
-        self._scratch, self._buf, self._st = None, (ctypes.c_void_p * n)(), (ctypes.c_void_p * self.streams)()
+        self._scratch = None
         return self
 
     def __del__(self):
@@ -100,12 +100,13 @@ class Program:
         """given: {buffer: tensor}, checked by the caller.  Runs on the current stream (and `streams`, which
         it joins); returns {buffer: tensor} of the fresh and the gradient buffers."""
         import torch
-        buf, device = self._buf, self.device
+        device = self.device
+        buf, st = (ctypes.c_void_p * len(self.kinds))(), (ctypes.c_void_p * self.streams)()     # of this run alone
         if self._scratch is None and self._kept_bytes:
             self._scratch = torch.empty(self._kept_bytes + 256, dtype=torch.uint8, device=device)
             self._base = (self._scratch.data_ptr() + 255) & ~255
-            for b, at in self._kept:
-                buf[b] = self._base + at
+        for b, at in self._kept:
+            buf[b] = self._base + at
         for b, t in given.items():
             buf[b] = t.data_ptr()
         out = {}
@@ -117,7 +118,6 @@ class Program:
             base = slab.data_ptr()
             for b, at in self._grads:
                 buf[b] = base + at
-        st = self._st
         st[0] = torch.cuda.current_stream().cuda_stream
         for i, s in enumerate(streams):
             st[i + 1] = s.cuda_stream
