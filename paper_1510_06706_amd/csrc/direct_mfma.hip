@@ -29,23 +29,30 @@ constexpr int kMaxTaps = 4096;
 // `tail`, [8 maps][4 input maps] for the 8-map block.  For the backward pass the two map indices trade places
 // and the tap is reflected.
 // Several layers and passes at a time (PackArgs): the weights of a round take one launch instead of one per convolution.
+// N = 1 serves the calls of a single layer, whose launch then carries 80 bytes of arguments instead of 2 KB.  Bound by the
+// integer divisions of the element's number; they are 64 bits wide only where the number is.
 constexpr int kPackItems = 24;
-struct PackArgs { PackItem item[kPackItems]; unsigned first[kPackItems]; int n; };
+template <int N> struct PackArgs { PackItem item[N]; unsigned first[N]; int n; };
 
-__global__ void __launch_bounds__(256) k_pack_weights(PackArgs A)
+template <int N>
+__global__ void __launch_bounds__(256) k_pack_weights(PackArgs<N> A)
 {
     int q = 0;
-    while (q + 1 < A.n && blockIdx.x >= A.first[q + 1]) ++q;        // uniform
+    if (N > 1) while (q + 1 < A.n && blockIdx.x >= A.first[q + 1]) ++q;        // uniform
     const PackItem& P = A.item[q];
     const int taps = P.kz * P.ky * P.kx;
     const int WT = P.NJ * 64 + (P.tail ? conv::kTailPacked : 0);
     const long t = (long)(blockIdx.x - A.first[q]) * 256 + threadIdx.x;
     if (t >= P.total) return;
-    const int e = (int)(t % WT);
-    long r = t / WT;
-    const int tap = (int)(r % taps); r /= taps;
-    const int ic = (int)(r % P.nchunk);
-    const int jg = (int)(r / P.nchunk);
+    int e, tap, ic, jg;
+    auto place = [&](auto n) {
+        e = (int)(n % (unsigned)WT); n /= (unsigned)WT;
+        tap = (int)(n % (unsigned)taps); n /= (unsigned)taps;
+        ic = (int)(n % (unsigned)P.nchunk);
+        jg = (int)(n / (unsigned)P.nchunk);
+    };
+    if (P.total <= 4294967295L) place((unsigned)t);         // uniform
+    else place((unsigned long)t);
     int m, k;
     if (e < P.NJ * 64) {
         m = (jg * P.NJ + e / 64) * 16 + (e & 15);
@@ -370,18 +377,24 @@ PackItem mfma_conv_pack_item(const Geom& g, bool backward, const float* w, float
     return p;
 }
 
+template <int N>
+static void pack_launch(const PackItem* items, int n, hipStream_t s)
+{
+    PackArgs<N> A = {};
+    unsigned blocks = 0;
+    for (; A.n < n; ++A.n) {
+        A.item[A.n] = items[A.n];
+        A.first[A.n] = blocks;
+        blocks += (unsigned)((items[A.n].total + 255) / 256);
+    }
+    ZNN_LAUNCH("weight packing", s, k_pack_weights<N>, dim3(blocks), dim3(256), 0, A);
+}
+
 int mfma_pack_weights(const PackItem* items, int n, hipStream_t s)
 {
-    for (int i0 = 0; i0 < n; i0 += kPackItems) {
-        PackArgs A = {};
-        unsigned blocks = 0;
-        for (A.n = 0; A.n < kPackItems && i0 + A.n < n; ++A.n) {
-            A.item[A.n] = items[i0 + A.n];
-            A.first[A.n] = blocks;
-            blocks += (unsigned)((items[i0 + A.n].total + 255) / 256);
-        }
-        ZNN_LAUNCH("weight packing", s, k_pack_weights, dim3(blocks), dim3(256), 0, A);
-    }
+    if (n == 1) pack_launch<1>(items, 1, s);
+    else
+        for (int i0 = 0; i0 < n; i0 += kPackItems) pack_launch<kPackItems>(items + i0, std::min(kPackItems, n - i0), s);
     return check_launch("weight packing");
 }
 

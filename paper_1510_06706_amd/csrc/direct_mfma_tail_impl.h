@@ -290,38 +290,45 @@ __global__ void __launch_bounds__(256, 2) k_conv_mfma_tail(ConvTile P)
         if (z >= P.dz || y >= P.dy || x >= P.dx) return -1;
         return z * dplane + (long)y * P.dx + x;
     };
-    auto finish = [&](long at, int j, float v) {
-        if (P.deriv) v = P.deriv[at] > 0.f ? v : 0.f;       // uniform
-        out[at] = v;
-        if (P.y) {                                          // uniform
-            v += P.bias[j];
-            P.y[at] = v > 0.f ? v : 0.f;
+    auto store_all = [&](auto&& store) {
+        // 16x16x4: lane holds rows m = 4*(lane/16) + r, column n = lane%16
+#pragma unroll
+        for (int nv = 0; nv < NV; ++nv) {
+            const long vox = voxel_of((wave * NV + nv) * 16 + col);
+            if (vox < 0) continue;
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int j = (jg * NJ + jt) * 16 + grp * 4 + r;
+                    if (TAIL || j < P.fM) store((long)j * dvol + vox, j, acc[jt][nv][r]);
+                }
         }
-    };
-    // 16x16x4: lane holds rows m = 4*(lane/16) + r, column n = lane%16
+        // 4x4x1: lane (block (mt, nt), v) holds maps mt*4 + r of voxel nt*4 + v
 #pragma unroll
-    for (int nv = 0; nv < NV; ++nv) {
-        const long vox = voxel_of((wave * NV + nv) * 16 + col);
-        if (vox < 0) continue;
-#pragma unroll
-        for (int jt = 0; jt < NJ; ++jt)
+        for (int pr = 0; pr < NP; ++pr) {
+            const long vox = pair_live(pr) ? voxel_of((wave * NV + 2 * pr) * 16 + tv32) : -1;
+            if (vox < 0) continue;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int j = (jg * NJ + jt) * 16 + grp * 4 + r;
-                if (TAIL || j < P.fM) finish((long)j * dvol + vox, j, acc[jt][nv][r]);
+                const int j = NJ * 16 + (lane >> 5) * 4 + r;
+                if (j < P.fM) store((long)j * dvol + vox, j, accT[pr][r]);
             }
-    }
-    // 4x4x1: lane (block (mt, nt), v) holds maps mt*4 + r of voxel nt*4 + v
-#pragma unroll
-    for (int pr = 0; pr < NP; ++pr) {
-        const long vox = pair_live(pr) ? voxel_of((wave * NV + 2 * pr) * 16 + tv32) : -1;
-        if (vox < 0) continue;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = NJ * 16 + (lane >> 5) * 4 + r;
-            if (j < P.fM) finish((long)j * dvol + vox, j, accT[pr][r]);
         }
-    }
+    };
+    // What follows the sums is decided once, outside the stores: a branch at each of them cost layers without it
+    // 3 % (24 -> 36 maps of 23 x 75 x 61, 3 x 5 x 5 kernels: 544 -> 560 us a round, 547 so).
+    if (P.deriv || P.y)
+        store_all([&](long at, int j, float v) {
+            if (P.deriv) v = P.deriv[at] > 0.f ? v : 0.f;       // uniform
+            out[at] = v;
+            if (P.y) {                                          // uniform
+                v += P.bias[j];
+                P.y[at] = v > 0.f ? v : 0.f;
+            }
+        });
+    else
+        store_all([&](long at, int, float v) { out[at] = v; });
 }
 
 // Instances.  With the block: 1..7 full tiles, 4 to 8 voxel tiles per wave, at most 28 accumulator tiles (more
