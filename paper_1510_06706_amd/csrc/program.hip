@@ -195,10 +195,10 @@ struct Layer {
     const znn_plan* of;
     znn_plan plan;
     int w, in, gout;        // its buffers
-    bool has[3];            // passes of the layer in this program
+    int step[3];            // its passes: steps of this program, -1 where there is none
     size_t packed[2];       // direct method: weights of the forward / backward pass from the round's packing launch
-    size_t spectra;         // FFT method: kernels, transformed once for both passes
-    size_t memo;            // and the spectra of images and gradients, kept for the kernel gradient
+    size_t spectra;         // FFT method: kernels, transformed once, by the first of the two passes that use them
+    size_t memo;            // and the spectra of images and gradients, kept for a kernel gradient that comes after both
 };
 
 long elements(const znn_op& o) { return (long)o.maps * o.n.z * o.n.y * o.n.x; }
@@ -232,17 +232,50 @@ namespace {
 // spectra that a program keeps on the device between the passes of a round, at most
 constexpr size_t kKeptSpectra = (size_t)16 << 30;
 
+// Per kind, as masks over the positions of znn_op::buf: which must be given, and what the operation reads and writes.
+struct Form { unsigned need; int n; unsigned reads, writes; };
+constexpr Form kForm[] = {
+    {7u, 5, 0x0bu, 0x14u},      // CONV_FWD
+    {7u, 4, 0x0bu, 0x04u},      // CONV_BWD
+    {7u, 3, 0x03u, 0x04u},      // CONV_WGRAD
+    {7u, 3, 0x03u, 0x04u},      // TRANSFER_FWD
+    {7u, 3, 0x03u, 0x04u},      // TRANSFER_BWD
+    {3u, 2, 0x01u, 0x02u},      // BIAS_GRAD
+    {7u, 3, 0x01u, 0x06u},      // FILTER_FWD
+    {7u, 4, 0x0bu, 0x04u},      // FILTER_BWD
+    {7u, 3, 0x01u, 0x06u},      // POOL_FWD
+    {7u, 4, 0x0bu, 0x04u},      // POOL_BWD
+    {7u, 4, 0x03u, 0x0cu},      // LOSS_GRAD
+    {3u, 8, 0xfeu, 0x01u},      // NODE_SUM
+    {3u, 2, 0x03u, 0x02u},      // UPDATE
+};
+
+bool uses(const Step& s, unsigned positions, int buffer)
+{
+    for (int q = 0; q < 8; ++q)
+        if ((positions >> q & 1) && s.op.buf[q] == buffer) return true;
+    return false;
+}
+
+bool writes(const Step& s, int buffer) { return s.kind >= 0 && uses(s, kForm[s.kind].writes, buffer); }
+
+// whether a step after `first` and before `last` writes the buffer
+bool written_between(const znn_program& P, int buffer, int first, int last)
+{
+    for (int i = first + 1; i < last; ++i)
+        if (writes(P.steps[i], buffer)) return true;
+    return false;
+}
+
 int check_op(const znn_op& o, int i, int buffers, int streams)
 {
     if (o.kind < ZNN_OP_CONV_FWD || o.kind > ZNN_OP_UPDATE) return fail(ZNN_EINVAL, "operation %d: unknown kind %d", i, o.kind);
     if (o.stream < 0 || o.stream >= streams) return fail(ZNN_EINVAL, "operation %d: no stream %d", i, o.stream);
-    // positions whose buffer must be given (mask), number of positions
-    static const struct { unsigned need; int n; } form[] = {
-        {7u, 5}, {7u, 4}, {7u, 3}, {7u, 3}, {7u, 3}, {3u, 2}, {7u, 3}, {7u, 4}, {7u, 3}, {7u, 4}, {7u, 4}, {3u, 8}, {3u, 2}};
+    const Form& form = kForm[o.kind];
     for (int b = 0; b < 8; ++b) {
         if (o.buf[b] >= buffers) return fail(ZNN_EINVAL, "operation %d: no buffer %d", i, o.buf[b]);
-        if (o.buf[b] < 0 && (form[o.kind].need >> b & 1)) return fail(ZNN_EINVAL, "operation %d: buffer %d is missing", i, b);
-        if (o.buf[b] >= 0 && b >= form[o.kind].n) return fail(ZNN_EINVAL, "operation %d: buffer %d has no meaning", i, b);
+        if (o.buf[b] < 0 && (form.need >> b & 1)) return fail(ZNN_EINVAL, "operation %d: buffer %d is missing", i, b);
+        if (o.buf[b] >= 0 && b >= form.n) return fail(ZNN_EINVAL, "operation %d: buffer %d has no meaning", i, b);
     }
     if (o.fn < ZNN_RECTIFY || o.fn > ZNN_TANH) return fail(ZNN_EINVAL, "operation %d: unknown transfer function %d", i, o.fn);
     if (o.kind <= ZNN_OP_CONV_WGRAD) {
@@ -261,7 +294,7 @@ int check_op(const znn_op& o, int i, int buffers, int streams)
     return ZNN_OK;
 }
 
-int layer_of(znn_program& P, const znn_op& o, int i)
+int layer_of(znn_program& P, const znn_op& o, int i, int step)
 {
     size_t l = 0;
     while (l < P.layers.size() && P.layers[l].of != o.plan) ++l;
@@ -271,16 +304,17 @@ int layer_of(znn_program& P, const znn_op& o, int i)
         L.plan = *o.plan;
         L.plan.resident = nullptr; L.plan.memo = nullptr;
         L.w = L.in = L.gout = -1;
+        L.step[0] = L.step[1] = L.step[2] = -1;
         L.packed[0] = L.packed[1] = L.spectra = L.memo = kNone;
         P.layers.push_back(L);
     }
     Layer& L = P.layers[l];
-    bool same = !L.has[o.kind];
+    bool same = L.step[o.kind] < 0;
     auto is = [&](int& have, int b) { same = same && (have < 0 || have == b); have = b; };
     if (o.kind != ZNN_OP_CONV_WGRAD) is(L.w, o.buf[1]);
     if (o.kind != ZNN_OP_CONV_BWD) is(L.in, o.buf[0]);
     if (o.kind != ZNN_OP_CONV_FWD) is(L.gout, o.buf[o.kind == ZNN_OP_CONV_BWD ? 0 : 1]);
-    L.has[o.kind] = true;
+    L.step[o.kind] = step;
     if (!same) { fail(ZNN_EINVAL, "operation %d: a plan stands for one layer of the program", i); return -1; }
     return (int)l;
 }
@@ -301,7 +335,7 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
         Step& s = add(ops[i].kind);
         s.op = ops[i];
         s.stream = ops[i].stream;
-        if (s.kind <= ZNN_OP_CONV_WGRAD && (s.layer = layer_of(P, ops[i], i)) < 0) return ZNN_EINVAL;
+        if (s.kind <= ZNN_OP_CONV_WGRAD && (s.layer = layer_of(P, ops[i], i, (int)P.steps.size() - 1)) < 0) return ZNN_EINVAL;
         if (s.kind == ZNN_OP_UPDATE) { s.skip = true; P.update_steps.push_back((int)P.steps.size() - 1); }
     }
     size_t at = 0, kept = 0;
@@ -309,14 +343,23 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
     for (Layer& L : P.layers) {
         if (L.plan.mode == ZNN_DIRECT) {
             for (int b = 0; b < 2; ++b)
-                if (L.has[b] && mfma_conv_supported(L.plan.g, b == 1)) {
+                if (L.step[b] >= 0 && mfma_conv_supported(L.plan.g, b == 1)) {
                     L.packed[b] = take(mfma_conv_packed_bytes(L.plan.g, b == 1));
                     P.steps[0].skip = false;
                 }
-        } else if (L.has[0] && L.has[1]) {
+        } else if (L.step[0] >= 0 && L.step[1] >= 0) {
+            const int fwd = L.step[0], bwd = L.step[1], grad = L.step[2];
             const size_t kernels = plan_kernel_bytes(&L.plan), nodes = plan_memo_bytes(&L.plan);
-            if (kept + kernels <= kKeptSpectra) { kept += kernels; L.spectra = take(kernels); }
-            if (L.has[2] && kept + nodes <= kKeptSpectra) { kept += nodes; L.memo = take(nodes); }
+            // spectra are shared where they are those of the same values: nothing writes the buffer in between
+            if (kept + kernels <= kKeptSpectra && !written_between(P, L.w, std::min(fwd, bwd), std::max(fwd, bwd))) {
+                kept += kernels;
+                L.spectra = take(kernels);
+            }
+            if (grad > fwd && grad > bwd && kept + nodes <= kKeptSpectra && !written_between(P, L.in, fwd, grad) &&
+                !written_between(P, L.gout, bwd, grad)) {
+                kept += nodes;
+                L.memo = take(nodes);
+            }
         }
     }
     P.completes.assign(P.update_steps.size(), -1);
@@ -358,6 +401,9 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
     return ZNN_OK;
 }
 
+// whether a pass of a layer with shared kernel spectra is the one that makes them
+bool transforms_kernels(const Layer& L, int kind) { return L.step[kind] < L.step[1 - kind]; }
+
 // What every step reads and writes: buffers, the sums that steps leave for the update, what the passes of a layer share.
 void name_resources(znn_program& P, int& resources)
 {
@@ -388,7 +434,7 @@ void name_resources(znn_program& P, int& resources)
                 const Layer& L = P.layers[s.layer];
                 const int kernels = shared + 2 * s.layer, nodes = kernels + 1;
                 rd(b[0]);
-                if (L.packed[s.kind] != kNone || (L.spectra != kNone && s.kind == ZNN_OP_CONV_BWD)) rd(kernels);
+                if (L.packed[s.kind] != kNone || (L.spectra != kNone && !transforms_kernels(L, s.kind))) rd(kernels);
                 else { rd(b[1]); if (L.spectra != kNone) wr(kernels); }
                 if (L.memo != kNone) wr(nodes);
                 wr(b[2]);
@@ -553,17 +599,14 @@ int run_conv(znn_program& P, Step& t, float* const* buf, char* scratch, hipStrea
             } else rc = mfma_conv_sum(g, bwd, (const float*)area, at(2), s);
             if (rc != ZNN_OK) return rc;
         } else finished = finished || inside;
-    } else if (L.spectra != kNone) {
-        float2* What = (float2*)(scratch + L.spectra);
-        if (!bwd) {
+    } else {
+        float2* What = L.spectra != kNone ? (float2*)(scratch + L.spectra) : nullptr;
+        if (What && transforms_kernels(L, t.kind)) {
             rc = plan_kernel_spectra(&L.plan, at(1), What, s);
             if (rc != ZNN_OK) return rc;
         }
         float2* memo = L.memo != kNone ? (float2*)(scratch + L.memo) : nullptr;
-        rc = plan_pass(&L.plan, t.kind, at(0), nullptr, at(2), What, area, memo, s);
-        if (rc != ZNN_OK) return rc;
-    } else {
-        rc = plan_pass(&L.plan, t.kind, at(0), at(1), at(2), nullptr, area, nullptr, s);
+        rc = plan_pass(&L.plan, t.kind, at(0), What ? nullptr : at(1), at(2), What, area, memo, s);
         if (rc != ZNN_OK) return rc;
     }
     if (!finished) {
