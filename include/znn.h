@@ -339,7 +339,8 @@ int  znn_autotune_round(const znn_conv_desc* desc, uint64_t memory_budget, void*
  *   - an operation may also apply what follows its result (`fn` with the buffers for it, see below),
  *   - the kernel transforms and, within a bound on memory, the node spectra of a layer on the FFT method are computed
  *     once per run and shared by its passes (Section 4),
- *   - gradients that an UPDATE consumes may be completed by it: they are valid after the run, not between its operations.
+ *   - work is moved (weights packed at the start; sums of gradients and updates in one launch at the end) only where no
+ *     operation of the list could tell: the result is that of the operations one after another.
  * A program describes the plans as they are when it is created; a plan stands for one layer (one set of kernels, inputs and
  * gradients) and one program is run by one thread at a time.  `scratch` is shared by the runs of a program.
  *
@@ -352,7 +353,7 @@ int  znn_autotune_round(const znn_conv_desc* desc, uint64_t memory_budget, void*
  *   POOL_FWD       in, out, idx               POOL_BWD       gout, idx, gin, ?y       (window; n = extents of in)
  *   LOSS_GRAD      y, target, g, ?gx          gx = g times fn'(y)
  *   NODE_SUM       out, part, ?part x 5, ?y   the parts in that order (positions 1 to 6), times fn'(y) (position 7)
- *   UPDATE         g, p                       p = p - eta g, maps x n elements; p is written by nothing else
+ *   UPDATE         g, p                       p = p - eta g, maps x n elements
  */
 typedef enum znn_op_kind {
     ZNN_OP_CONV_FWD = 0, ZNN_OP_CONV_BWD = 1, ZNN_OP_CONV_WGRAD = 2, ZNN_OP_TRANSFER_FWD = 3, ZNN_OP_TRANSFER_BWD = 4,

@@ -257,13 +257,21 @@ bool uses(const Step& s, unsigned positions, int buffer)
     return false;
 }
 
-bool writes(const Step& s, int buffer) { return s.kind >= 0 && uses(s, kForm[s.kind].writes, buffer); }
+unsigned writes(const Step& s) { return s.kind < 0 ? 0u : kForm[s.kind].writes; }
+unsigned touches(const Step& s) { return s.kind < 0 ? 0u : kForm[s.kind].reads | kForm[s.kind].writes; }
 
-// whether a step after `first` and before `last` writes the buffer
+// whether a step after `first` and before `last` writes / reads or writes the buffer
 bool written_between(const znn_program& P, int buffer, int first, int last)
 {
     for (int i = first + 1; i < last; ++i)
-        if (writes(P.steps[i], buffer)) return true;
+        if (uses(P.steps[i], writes(P.steps[i]), buffer)) return true;
+    return false;
+}
+
+bool touched_between(const znn_program& P, int buffer, int first, int last)
+{
+    for (int i = first + 1; i < last; ++i)
+        if (uses(P.steps[i], touches(P.steps[i]), buffer)) return true;
     return false;
 }
 
@@ -336,14 +344,29 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
         s.op = ops[i];
         s.stream = ops[i].stream;
         if (s.kind <= ZNN_OP_CONV_WGRAD && (s.layer = layer_of(P, ops[i], i, (int)P.steps.size() - 1)) < 0) return ZNN_EINVAL;
-        if (s.kind == ZNN_OP_UPDATE) { s.skip = true; P.update_steps.push_back((int)P.steps.size() - 1); }
+    }
+    const int n = (int)P.steps.size();
+    std::vector<int> last_touch(P.buffers, -1), last_write(P.buffers, -1);
+    for (int i = 0; i < n; ++i)
+        for (int q = 0; q < 8; ++q) {
+            const Step& s = P.steps[i];
+            const int b = s.op.buf[q];
+            if (touches(s) >> q & 1 && b >= 0) last_touch[b] = i;
+            if (writes(s) >> q & 1 && b >= 0) last_write[b] = i;
+        }
+    // An update joins the one launch at the end where no operation behind it could tell
+    for (int i = 0; i < n; ++i) {
+        Step& s = P.steps[i];
+        if (s.kind != ZNN_OP_UPDATE || last_touch[s.op.buf[0]] > i || last_touch[s.op.buf[1]] > i) continue;
+        s.skip = true;
+        P.update_steps.push_back(i);
     }
     size_t at = 0, kept = 0;
     auto take = [&](size_t bytes) { const size_t o = at; at += align256(bytes); return o; };
     for (Layer& L : P.layers) {
         if (L.plan.mode == ZNN_DIRECT) {
             for (int b = 0; b < 2; ++b)
-                if (L.step[b] >= 0 && mfma_conv_supported(L.plan.g, b == 1)) {
+                if (L.step[b] >= 0 && mfma_conv_supported(L.plan.g, b == 1) && !written_between(P, L.w, 0, L.step[b])) {
                     L.packed[b] = take(mfma_conv_packed_bytes(L.plan.g, b == 1));
                     P.steps[0].skip = false;
                 }
@@ -362,21 +385,24 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
             }
         }
     }
+    // It completes a gradient that nothing touches between the operation that makes it and the update; the sums of a bias
+    // move to the end where nothing writes their operand later
     P.completes.assign(P.update_steps.size(), -1);
     for (size_t u = 0; u < P.update_steps.size(); ++u) {
-        const int g = P.steps[P.update_steps[u]].op.buf[0];
-        for (size_t i = 0; i < P.steps.size(); ++i) {
+        const int at_update = P.update_steps[u], g = P.steps[at_update].op.buf[0];
+        for (int i = 0; i < at_update; ++i) {
             Step& s = P.steps[i];
-            if (s.kind == ZNN_OP_BIAS_GRAD && s.op.buf[1] == g && s.own == kNone) {
+            if (s.kind == ZNN_OP_BIAS_GRAD && s.op.buf[1] == g) {
+                if (touched_between(P, g, i, at_update) || last_write[s.op.buf[0]] > i) continue;
                 s.own = take(sizeof(float) * s.op.maps * bias_spans(s.op));
                 s.skip = true;
-                P.bias_steps.push_back((int)i);
-                P.completes[u] = (int)i;
-            } else if (s.kind == ZNN_OP_CONV_WGRAD && s.op.buf[2] == g && s.own == kNone) {
+                P.bias_steps.push_back(i);
+                P.completes[u] = i;
+            } else if (s.kind == ZNN_OP_CONV_WGRAD && s.op.buf[2] == g) {
                 const Layer& L = P.layers[s.layer];
-                if (L.plan.mode != ZNN_DIRECT || !mfma_wgrad_supported(L.plan.g)) continue;
+                if (L.plan.mode != ZNN_DIRECT || !mfma_wgrad_supported(L.plan.g) || touched_between(P, g, i, at_update)) continue;
                 s.own = take(mfma_wgrad_workspace(L.plan.g));
-                P.completes[u] = (int)i;
+                P.completes[u] = i;
             }
         }
     }
@@ -447,11 +473,11 @@ void name_resources(znn_program& P, int& resources)
                 if (P.layers[s.layer].memo != kNone) rd(shared + 2 * s.layer + 1);
                 wr(s.own != kNone ? own + (int)i : b[2]);
                 break;
-            case ZNN_OP_BIAS_GRAD: rd(b[0]); wr(b[1]); break;
-            case ZNN_OP_FILTER_FWD: case ZNN_OP_POOL_FWD: rd(b[0]); wr(b[1]); wr(b[2]); break;
-            case ZNN_OP_NODE_SUM: wr(b[0]); for (int q = 1; q < 8; ++q) rd(b[q]); break;
-            case ZNN_OP_LOSS_GRAD: rd(b[0]); rd(b[1]); wr(b[2]); wr(b[3]); break;
-            default: rd(b[0]); rd(b[1]); wr(b[2]); rd(b[3]); break;
+            default:
+                for (int q = 0; q < 8; ++q) {
+                    if (kForm[s.kind].reads >> q & 1) rd(b[q]);
+                    if (kForm[s.kind].writes >> q & 1) wr(b[q]);
+                }
         }
     }
 }
@@ -642,6 +668,7 @@ int run_step(znn_program& P, Step& t, float* const* buf, char* scratch, float et
         case ZNN_OP_LOSS_GRAD:
             ZNN_LAUNCH("loss gradient", s, k_loss_finish, dim3(blocks_of(count)), dim3(256), 0, count, at(0), at(1), at(2), at(3), o.loss, o.fn);
             return check_launch("loss gradient");
+        case ZNN_OP_UPDATE: return znn_sgd_update(count, eta, at(0), at(1), s);
         case ZNN_OP_NODE_SUM: {
             SumArgs A = {};
             for (int q = 1; q < 7 && o.buf[q] >= 0; ++q) A.part[A.parts++] = at(q);
