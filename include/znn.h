@@ -343,6 +343,8 @@ int  znn_autotune_round(const znn_conv_desc* desc, uint64_t memory_budget, void*
  *     operation of the list could tell: the result is that of the operations one after another.
  * A program describes the plans as they are when it is created; a plan stands for one layer (one set of kernels, inputs and
  * gradients) and one program is run by one thread at a time.  `scratch` is shared by the runs of a program.
+ * Buffers with different numbers must not overlap where an operation writes one of them -- except that the parameters of
+ * several layers may be the same memory if their UPDATEs stand behind everything that reads it: they take effect in order.
  *
  * Buffers by position (-1 = absent, only where marked ?):
  *   CONV_FWD       in, w, out, ?bias, ?y      y = fn(out + bias)

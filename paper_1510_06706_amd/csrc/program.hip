@@ -559,17 +559,21 @@ int run_bias(const znn_program& P, float* const* buf, char* scratch, hipStream_t
 
 int run_update(const znn_program& P, float* const* buf, char* scratch, float eta, hipStream_t s)
 {
-    for (size_t i0 = 0; i0 < P.update_steps.size(); i0 += kUpdateItems) {
+    for (size_t u = 0; u < P.update_steps.size();) {
         UpdateArgs A = {};
         A.eta = eta;
         unsigned blocks = 0;
-        for (; A.n < kUpdateItems && i0 + A.n < P.update_steps.size(); ++A.n) {
-            const Step& u = P.steps[P.update_steps[i0 + A.n]];
-            const int done_by = P.completes[i0 + A.n];
+        for (; A.n < kUpdateItems && u < P.update_steps.size(); ++A.n, ++u) {
+            const Step& t = P.steps[P.update_steps[u]];
+            const int done_by = P.completes[u];
             UpdateItem& I = A.item[A.n];
-            I.grad = buf[u.op.buf[0]]; I.p = buf[u.op.buf[1]];
+            I.grad = buf[t.op.buf[0]]; I.p = buf[t.op.buf[1]];
             I.first = blocks;
-            I.total = elements(u.op);
+            I.total = elements(t.op);
+            // layers that share parameters take their steps one after another
+            bool shared = false;
+            for (int q = 0; q < A.n && !shared; ++q) shared = I.p < A.item[q].p + A.item[q].total && A.item[q].p < I.p + I.total;
+            if (shared) break;
             if (done_by >= 0) {
                 const Step& d = P.steps[done_by];
                 I.src = (const float*)(scratch + d.own);

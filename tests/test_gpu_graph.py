@@ -173,3 +173,21 @@ def test_round_as_one_program_matches_the_calls_per_layer(form, mode):
                 assert rel_err(host(got[3][l][k]), host(ref[3][l][k])) <= 2e-5, ("gradient", l, k)
                 assert rel_err(host(one.params[l][k]), host(by_layer.params[l][k])) <= 2e-6, ("update", l, k)
         assert rel_err(host(got[2]), host(ref[2])) <= 1e-6
+
+
+def test_layers_of_a_net_may_share_their_kernels():
+    """Two layers holding one tensor: the round gives what the calls per layer give, where the updates follow each other."""
+    layers = [("conv", 2, 6, (3, 3, 3)), ("transfer",), ("conv", 6, 6, (3, 3, 3)), ("transfer", "tanh"),
+              ("conv", 6, 6, (3, 3, 3)), ("transfer", "logistic")]
+    in_shape = (2, 13, 14, 15)
+    x, target, params = synth.net_tensors(layers, in_shape, 67)
+    nets = [znet.Net(layers, in_shape, params, "direct") for _ in range(2)]
+    for net in nets:
+        net.params[4]["w"] = net.params[2]["w"]
+        net.params[5]["b"] = net.params[3]["b"]
+    for _ in range(4):
+        nets[0].train_round(dev(x), dev(target), 0.05)
+        nets[1].train_round(dev(x), dev(target), 0.05, record=[])
+    for l in (2, 3):
+        for k, v in nets[1].params[l].items():
+            assert rel_err(host(nets[0].params[l][k]), host(v)) <= 2e-6, (l, k)

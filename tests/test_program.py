@@ -111,8 +111,8 @@ def step_by_step(ops, t):
 ETA = 0.125
 
 
-def check(ops, shapes, seed, runs=2, tol=2e-5, streams=1):
-    """Every buffer after every run, with new values before each."""
+def check(ops, shapes, seed, runs=2, tol=2e-5, streams=1, same=()):
+    """Every buffer after every run, with new values before each; `same`: pairs of buffers that are one tensor."""
     import torch
     P = program(ops, shapes, streams)
     side = [torch.cuda.Stream() for _ in range(streams - 1)]
@@ -120,6 +120,8 @@ def check(ops, shapes, seed, runs=2, tol=2e-5, streams=1):
     for r in range(runs):
         got = [torch.rand(s, generator=gen, device="cuda:0") * 2 - 1 for s in shapes]
         ref = [t.clone() for t in got]
+        for a, b in same:
+            got[b], ref[b] = got[a], ref[a]
         P.run(dict(enumerate(got)), ETA, side)
         step_by_step(ops, ref)
         torch.cuda.synchronize()
@@ -222,3 +224,11 @@ def test_random_lists_of_operations_on_few_buffers(mode, streams):
             ops = [(k, b, dict(how, stream=int(rng.integers(streams)))) for k, b, how in ops]
         print("case", it, [(k, b) for k, b, _ in ops], flush=True)
         check(ops, shapes, it, tol=2e-4, streams=streams)      # a dozen operations pass a difference on
+
+
+@pytest.mark.gpu
+def test_layers_that_share_parameters_take_their_steps_in_order():
+    """One tensor as the parameters of several updates: buffers 0 to 4 are gradients, 5 to 9 parameters."""
+    n = 3000
+    ops = [(zp.UPDATE, (i, 5 + i), dict(n=(1, 1, n))) for i in range(5)]
+    check(ops, [(n,)] * 10, 9, runs=20, same=((5, 7), (5, 8), (6, 9)))
