@@ -355,7 +355,7 @@ int  znn_autotune_round(const znn_conv_desc* desc, uint64_t memory_budget, void*
  *   POOL_FWD       in, out, idx               POOL_BWD       gout, idx, gin, ?y       (window; n = extents of in)
  *   LOSS_GRAD      y, target, g, ?gx          gx = g times fn'(y)
  *   NODE_SUM       out, part, ?part x 5, ?y   the parts in that order (positions 1 to 6), times fn'(y) (position 7)
- *   UPDATE         g, p                       p = p - eta g, maps x n elements
+ *   UPDATE         g, p                       p = p - eta g, maps x n elements: those of the gradient
  */
 typedef enum znn_op_kind {
     ZNN_OP_CONV_FWD = 0, ZNN_OP_CONV_BWD = 1, ZNN_OP_CONV_WGRAD = 2, ZNN_OP_TRANSFER_FWD = 3, ZNN_OP_TRANSFER_BWD = 4,

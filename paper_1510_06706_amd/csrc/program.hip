@@ -346,6 +346,17 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
         if (s.kind <= ZNN_OP_CONV_WGRAD && (s.layer = layer_of(P, ops[i], i, (int)P.steps.size() - 1)) < 0) return ZNN_EINVAL;
     }
     const int n = (int)P.steps.size();
+    for (int u = 0; u < n; ++u) {
+        if (P.steps[u].kind != ZNN_OP_UPDATE) continue;
+        const znn_op& o = P.steps[u].op;
+        int i = u - 1;
+        while (i >= 0 && !uses(P.steps[i], writes(P.steps[i]), o.buf[0])) --i;
+        const Step* made = i < 0 ? nullptr : &P.steps[i];
+        const long have = !made ? -1 : made->kind == ZNN_OP_BIAS_GRAD ? made->op.maps
+                        : made->kind == ZNN_OP_CONV_WGRAD ? (long)made->op.plan->g.f * made->op.plan->g.fo * made->op.plan->g.kvol() : -1;
+        if (have >= 0 && have != elements(o))
+            return fail(ZNN_EINVAL, "operation %d: an update of %ld elements from a gradient of %ld", u - 1, elements(o), have);
+    }
     std::vector<int> last_touch(P.buffers, -1), last_write(P.buffers, -1);
     for (int i = 0; i < n; ++i)
         for (int q = 0; q < 8; ++q) {

@@ -74,6 +74,26 @@ def test_sums_move_to_the_update_only_where_no_operation_could_tell():
     assert need(G, U, U) == 0                        # the first update needs the gradient
 
 
+def refused(ops, shapes):
+    with pytest.raises(znn.ZnnError) as e:
+        program(ops, shapes)
+    return e.value.code == znn.ZNN_EINVAL
+
+
+@pytest.mark.parametrize("mode", ["direct", "fft"])
+def test_updates_of_another_size_than_their_gradient_are_refused(mode):
+    plan = znn.Plan(2, 3, (6, 7, 8), (2, 2, 2), mode)
+    shapes = conv_shapes(plan) + [(3,), (3,)]
+    W, G = (zp.CONV_WGRAD, (0, 3, 5), dict(plan=plan)), (zp.BIAS_GRAD, (3, 6), dict(maps=3, n=plan.o))
+    update = lambda g, p, count: (zp.UPDATE, (g, p), dict(n=(1, 1, count)))  # noqa: E731
+    program([W, G, update(5, 1, 48), update(6, 7, 3)], shapes)
+    program([update(5, 1, 48), (zp.UPDATE, (6, 7), dict(maps=3, n=(1, 1, 1)))], shapes)
+    for count in (47, 49, 480):
+        assert refused([W, update(5, 1, count)], shapes)
+    for count in (2, 4):
+        assert refused([G, update(6, 7, count)], shapes)
+
+
 # ------------------------------------------------------------------------------------------------------- on the GPU
 def step_by_step(ops, t):
     """The list through the single entry points, on tensors t."""
