@@ -285,6 +285,9 @@ int check_op(const znn_op& o, int i, int buffers, int streams)
         if (o.buf[b] < 0 && (form.need >> b & 1)) return fail(ZNN_EINVAL, "operation %d: buffer %d is missing", i, b);
         if (o.buf[b] >= 0 && b >= form.n) return fail(ZNN_EINVAL, "operation %d: buffer %d has no meaning", i, b);
     }
+    if (o.kind == ZNN_OP_NODE_SUM)
+        for (int b = 2; b < 7; ++b)
+            if (o.buf[b] >= 0 && o.buf[b - 1] < 0) return fail(ZNN_EINVAL, "operation %d: part %d of the sum is missing", i, b - 1);
     if (o.fn < ZNN_RECTIFY || o.fn > ZNN_TANH) return fail(ZNN_EINVAL, "operation %d: unknown transfer function %d", i, o.fn);
     if (o.kind <= ZNN_OP_CONV_WGRAD) {
         if (!o.plan) return fail(ZNN_EINVAL, "operation %d: plan is NULL", i);

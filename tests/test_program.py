@@ -94,6 +94,15 @@ def test_updates_of_another_size_than_their_gradient_are_refused(mode):
         assert refused([G, update(6, 7, count)], shapes)
 
 
+def test_sums_with_an_absent_part_before_a_given_one_are_refused():
+    shapes = [SHAPE] * 8
+    add = lambda *b: [(zp.NODE_SUM, b, dict(maps=3, n=SHAPE[1:]))]  # noqa: E731
+    for b in ((0, 1), (0, 1, 2), (0, 1, 2, 3, 4, 5, 6), (0, 1, -1, -1, -1, -1, -1, 7), (0, 1, 2, 3, -1, -1, -1, 7)):
+        program(add(*b), shapes)
+    for b in ((0, -1, 2), (0, 1, -1, 3), (0, 1, 2, 3, -1, 5), (0, 1, -1, -1, -1, -1, 6, 7)):
+        assert refused(add(*b), shapes)
+
+
 # ------------------------------------------------------------------------------------------------------- on the GPU
 def step_by_step(ops, t):
     """The list through the single entry points, on tensors t."""
