@@ -31,6 +31,7 @@ EXPORTS = [
     "znn_autotune_round_workspace_bytes", "znn_autotune_round", "znn_accumulate",
     "znn_plan_set_spectra_layout", "znn_plan_spectra_layout", "znn_plan_tiles", "znn_conv3d_fwd_static",
     "znn_program_create", "znn_program_destroy", "znn_program_scratch_bytes", "znn_program_run",
+    "znn_plan_set_round_memory",
 ]
 STATIC_SCRATCH_BYTES = 32 * 1024 * 1024
 SPECTRA_LAYOUTS = {"auto": 0, "full": 1, "folded": 2}
@@ -124,6 +125,7 @@ def lib():
         L.znn_conv3d_wgrad_memo.argtypes = [vp, vp, vp, sz, vp]
         L.znn_trace_enable.argtypes = [i32]
         L.znn_trace_collect.argtypes = [ctypes.POINTER(TraceRecord), i32, ctypes.POINTER(i32)]
+        L.znn_plan_set_round_memory.argtypes = [vp, sz]
         L.znn_program_create.argtypes = [ctypes.POINTER(Op), i32, i32, i32, ctypes.POINTER(vp)]
         L.znn_program_destroy.argtypes = [vp]
         L.znn_program_destroy.restype = None
@@ -224,6 +226,10 @@ class Plan:
     def set_spectra_layout(self, layout: str):
         """'auto', 'full' (the kernel transforms themselves) or 'folded' (half spectra)."""
         _check(lib().znn_plan_set_spectra_layout(self._h, SPECTRA_LAYOUTS[layout]))
+
+    def set_round_memory(self, nbytes: int):
+        """Bounds what rounds as one program hold of this layer beside the workspace of its passes."""
+        _check(lib().znn_plan_set_round_memory(self._h, int(nbytes)))
 
     @property
     def spectra_layout(self) -> str:

@@ -364,6 +364,7 @@ int znn_plan_create(const znn_conv_desc* desc, znn_plan** plan)
     p->memo = nullptr;
     p->memo_bytes = 0;
     p->memo_has_in = p->memo_has_gout = false;
+    p->round_memory = SIZE_MAX;
     *plan = p;
     return ZNN_OK;
 }
@@ -389,6 +390,13 @@ int znn_plan_workspace_bytes(const znn_plan* plan, int32_t pass, size_t* bytes)
     if (!plan || !bytes) return fail(ZNN_EINVAL, "NULL argument");
     if (pass < ZNN_PASS_FWD || pass > ZNN_PASS_WGRAD) return fail(ZNN_EINVAL, "unknown pass %d", pass);
     *bytes = plan_pass_bytes(plan, pass, plan->resident != nullptr);
+    return ZNN_OK;
+}
+
+int znn_plan_set_round_memory(znn_plan* plan, size_t bytes)
+{
+    if (!plan) return fail(ZNN_EINVAL, "plan is NULL");
+    plan->round_memory = bytes;
     return ZNN_OK;
 }
 

@@ -375,28 +375,31 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
         s.skip = true;
         P.update_steps.push_back(i);
     }
-    size_t at = 0, kept = 0;
+    size_t at = 0, spectra = 0;
     auto take = [&](size_t bytes) { const size_t o = at; at += align256(bytes); return o; };
-    for (Layer& L : P.layers) {
+    // what a layer may hold besides: its plan's bound, and one on all spectra
+    std::vector<size_t> room;
+    auto hold = [&](size_t layer, size_t bytes) { return bytes > room[layer] ? kNone : (room[layer] -= bytes, take(bytes)); };
+    auto hold_spectra = [&](size_t layer, size_t bytes) {
+        if (bytes > kKeptSpectra - spectra || bytes > room[layer]) return kNone;
+        spectra += bytes;
+        return hold(layer, bytes);
+    };
+    for (size_t l = 0; l < P.layers.size(); ++l) {
+        Layer& L = P.layers[l];
+        room.push_back(L.plan.round_memory);
         if (L.plan.mode == ZNN_DIRECT) {
             for (int b = 0; b < 2; ++b)
                 if (L.step[b] >= 0 && mfma_conv_supported(L.plan.g, b == 1) && !written_between(P, L.w, 0, L.step[b])) {
-                    L.packed[b] = take(mfma_conv_packed_bytes(L.plan.g, b == 1));
-                    P.steps[0].skip = false;
+                    L.packed[b] = hold(l, mfma_conv_packed_bytes(L.plan.g, b == 1));
+                    if (L.packed[b] != kNone) P.steps[0].skip = false;
                 }
         } else if (L.step[0] >= 0 && L.step[1] >= 0) {
             const int fwd = L.step[0], bwd = L.step[1], grad = L.step[2];
-            const size_t kernels = plan_kernel_bytes(&L.plan), nodes = plan_memo_bytes(&L.plan);
             // spectra are shared where they are those of the same values: nothing writes the buffer in between
-            if (kept + kernels <= kKeptSpectra && !written_between(P, L.w, std::min(fwd, bwd), std::max(fwd, bwd))) {
-                kept += kernels;
-                L.spectra = take(kernels);
-            }
-            if (grad > fwd && grad > bwd && kept + nodes <= kKeptSpectra && !written_between(P, L.in, fwd, grad) &&
-                !written_between(P, L.gout, bwd, grad)) {
-                kept += nodes;
-                L.memo = take(nodes);
-            }
+            if (!written_between(P, L.w, std::min(fwd, bwd), std::max(fwd, bwd))) L.spectra = hold_spectra(l, plan_kernel_bytes(&L.plan));
+            if (grad > fwd && grad > bwd && !written_between(P, L.in, fwd, grad) && !written_between(P, L.gout, bwd, grad))
+                L.memo = hold_spectra(l, plan_memo_bytes(&L.plan));
         }
     }
     // It completes a gradient that nothing touches between the operation that makes it and the update; the sums of a bias
@@ -415,8 +418,8 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
             } else if (s.kind == ZNN_OP_CONV_WGRAD && s.op.buf[2] == g) {
                 const Layer& L = P.layers[s.layer];
                 if (L.plan.mode != ZNN_DIRECT || !mfma_wgrad_supported(L.plan.g) || touched_between(P, g, i, at_update)) continue;
-                s.own = take(mfma_wgrad_workspace(L.plan.g));
-                P.completes[u] = i;
+                s.own = hold(s.layer, mfma_wgrad_workspace(L.plan.g));
+                if (s.own != kNone) P.completes[u] = i;
             }
         }
     }

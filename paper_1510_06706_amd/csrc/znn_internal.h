@@ -286,4 +286,5 @@ struct znn_plan {
     float2* memo;                // caller's buffer for memoized node spectra, or nullptr
     size_t memo_bytes;           // and its size
     bool memo_has_in, memo_has_gout;
+    size_t round_memory;         // what a program may hold of this layer beside the workspace of its passes
 };

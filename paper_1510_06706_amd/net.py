@@ -43,9 +43,14 @@ class Net:
                     m, ms, nbytes = znn.autotune_round(spec[1], spec[2], self.shapes[l][1:], spec[3],
                                                        memory_budget, sp, device)
                     self.tuning[l] = (m, ms, nbytes)
+                    spare = None if memory_budget is None else max(0, memory_budget - nbytes[m])
+                else:
+                    spare = None
                 plan = znn.Plan(spec[1], spec[2], self.shapes[l][1:], spec[3], "fft" if m == "fft_memo" else m, sp)
                 if m == "fft_memo":
                     plan.enable_memo(device)
+                elif spare is not None:         # the budget holds for rounds as one program as well
+                    plan.set_round_memory(spare)
                 self.strategy[l] = m
                 self.plans.append(plan)
             else:
@@ -185,7 +190,7 @@ class Net:
     def train_round(self, x, target, eta, record=None, loss="square"):
         if loss not in zp.LOSSES:
             raise ValueError(loss)
-        if record is None:
+        if record is None and not self._memo:
             return self._run(loss, x, target, eta)
         acts, aux = self._forward_by_layer(x)
         gout = znn.loss_grad(acts[-1], target, loss)

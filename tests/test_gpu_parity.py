@@ -631,3 +631,34 @@ def test_fft_layers_on_overlapping_tiles_match_the_oracle(f, fo, n, k, s):
     assert np.array_equal(out, host(p.fwd(d_in, None))) and np.array_equal(gin, host(p.bwd(d_g, None)))
     assert np.array_equal(gw, host(p.wgrad_memo()))
     p.close()
+
+
+def test_rounds_of_a_tuned_net_keep_to_the_memory_budget():
+    """A budget that memoization exceeds holds for the rounds too, and they match the calls per layer; layers with
+    memoized spectra leave them in their plans."""
+    from paper_1510_06706_amd import net as znet
+    layers = [("conv", 12, 12, (1, 5, 5)), ("transfer",), ("conv", 12, 12, (1, 5, 5)), ("transfer", "logistic")]
+    in_shape = (12, 1, 119, 120)
+    x, target, params = synth.net_tensors(layers, in_shape, 43)
+    probe = znet.Net(layers, in_shape, params, "tuned")
+    sizes = [probe.tuning[l][2] for l in (0, 2)]
+    budget = max(max(b["direct"], b["fft"]) for b in sizes)
+    assert all(b["fft_memo"] > budget for b in sizes), sizes
+    # what the tuner picks within the budget, and either method for all layers
+    for mode in (None, "direct", "fft"):
+        net = znet.Net(layers, in_shape, params, "tuned", memory_budget=budget)
+        if mode is not None:
+            net = znet.Net(layers, in_shape, params, mode)
+            for l, b in zip((0, 2), sizes):
+                net.plans[l].set_round_memory(budget - b[mode])
+        ref = znet.Net(layers, in_shape, params, [None if m is None else {0: "direct", 1: "fft"}[m] for m in net.modes()])
+        assert "fft_memo" not in net.strategy
+        acts, _, _, grads = net.train_round(dev(x), dev(target), 0.05)
+        r_acts, _, _, r_grads = ref.train_round(dev(x), dev(target), 0.05, record=[])
+        assert net._program("square")[0].scratch_bytes <= 2 * budget + 4096     # and the sums of the biases
+        assert rel_err(host(acts[-1]), host(r_acts[-1])) <= 1e-6
+        for l in (0, 2):
+            assert rel_err(host(grads[l]["w"]), host(r_grads[l]["w"])) <= 2e-5
+    memo = znet.Net(layers, in_shape, params, "fft_memo")
+    grads = memo.train_round(dev(x), dev(target), 0.05)[3]
+    assert np.array_equal(host(memo.plans[2].wgrad_memo()), host(grads[2]["w"]))

@@ -47,7 +47,7 @@ def test_spectra_are_shared_only_by_passes_that_follow_the_ones_that_make_them()
         assert need(conv_ops(plan, o)) == both - (memo if o[-1] != "W" else 0), o
     # nor are they once something has written the values they were made of
     F, B, W = conv_ops(plan, "FBW")
-    alone = max(plan.workspace_bytes(w) for w in (znn.ZNN_PASS_FWD, znn.ZNN_PASS_BWD, znn.ZNN_PASS_WGRAD))
+    alone = max(plan.workspace_bytes(w) for w in PASSES)
     for buffer, ops, want in ((0, lambda t: [F, t, B, W], both - memo), (3, lambda t: [F, B, t, W], both - memo),
                               (1, lambda t: [F, t, B, W], memo + alone), (1, lambda t: [t, F, B, W], both),
                               (0, lambda t: [t, B, F, W], both), (3, lambda t: [F, t, B, W], both)):
@@ -72,6 +72,30 @@ def test_sums_move_to_the_update_only_where_no_operation_could_tell():
     assert need(U, G) == 0
     assert need(G, G, U) == moved                    # the second one counts
     assert need(G, U, U) == 0                        # the first update needs the gradient
+
+
+PASSES = (znn.ZNN_PASS_FWD, znn.ZNN_PASS_BWD, znn.ZNN_PASS_WGRAD)
+
+
+def bounds(plan):
+    """Bounds on what a round holds of a layer, around the sizes of its parts."""
+    if plan.mode == znn.ZNN_FFT:
+        sizes = [plan.spectra_bytes(), plan.memo_bytes()]
+        return [0] + [v for s in sizes + [sum(sizes)] for v in (s - 1, s)]
+    return [0, 50000, 200000, 1 << 62]
+
+
+@pytest.mark.parametrize("mode", ["direct", "fft"])
+def test_a_round_holds_no_more_of_a_layer_than_its_plan_allows(mode):
+    plan = znn.Plan(8, 6, (14, 12, 15), (3, 2, 3), mode)
+    passes = max(plan.workspace_bytes(w) for w in PASSES)
+    round_ = conv_ops(plan, "FBW") + [(zp.UPDATE, (5, 1), dict(n=(1, 1, 6 * 8 * 18)))]
+    need = lambda: program(round_, conv_shapes(plan)).scratch_bytes  # noqa: E731
+    most = need()
+    for bound in bounds(plan):
+        plan.set_round_memory(bound)
+        assert need() <= min(most, passes + bound), bound
+    assert need() == most and most > passes
 
 
 def refused(ops, shapes):
@@ -261,3 +285,14 @@ def test_layers_that_share_parameters_take_their_steps_in_order():
     n = 3000
     ops = [(zp.UPDATE, (i, 5 + i), dict(n=(1, 1, n))) for i in range(5)]
     check(ops, [(n,)] * 10, 9, runs=20, same=((5, 7), (5, 8), (6, 9)))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode", ["direct", "fft"])
+def test_rounds_within_bounds_on_their_memory(mode):
+    """Whichever of packed weights, partial sums, kernel and node spectra fit."""
+    plan = znn.Plan(8, 6, (14, 12, 15), (3, 2, 3), mode)
+    for bound in bounds(plan):
+        print("case", mode, bound, flush=True)
+        plan.set_round_memory(bound)
+        check(conv_ops(plan, "FBW") + [(zp.UPDATE, (5, 1), dict(n=(1, 1, 6 * 8 * 18)))], conv_shapes(plan), 3)
