@@ -402,19 +402,20 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
                 L.memo = hold_spectra(l, plan_memo_bytes(&L.plan));
         }
     }
-    // It completes a gradient that nothing touches between the operation that makes it and the update; the sums of a bias
-    // move to the end where nothing writes their operand later
+    // It completes a gradient that nothing touches between the operation that makes it and the update; those of biases
+    // are summed in one launch before it where nothing writes their operands later, each in its place otherwise
     P.completes.assign(P.update_steps.size(), -1);
     for (size_t u = 0; u < P.update_steps.size(); ++u) {
         const int at_update = P.update_steps[u], g = P.steps[at_update].op.buf[0];
         for (int i = 0; i < at_update; ++i) {
             Step& s = P.steps[i];
             if (s.kind == ZNN_OP_BIAS_GRAD && s.op.buf[1] == g) {
-                if (touched_between(P, g, i, at_update) || last_write[s.op.buf[0]] > i) continue;
+                if (touched_between(P, g, i, at_update)) continue;
                 s.own = take(sizeof(float) * s.op.maps * bias_spans(s.op));
+                P.completes[u] = i;
+                if (last_write[s.op.buf[0]] > i) continue;
                 s.skip = true;
                 P.bias_steps.push_back(i);
-                P.completes[u] = i;
             } else if (s.kind == ZNN_OP_CONV_WGRAD && s.op.buf[2] == g) {
                 const Layer& L = P.layers[s.layer];
                 if (L.plan.mode != ZNN_DIRECT || !mfma_wgrad_supported(L.plan.g) || touched_between(P, g, i, at_update)) continue;
@@ -493,7 +494,7 @@ void name_resources(znn_program& P, int& resources)
             default:
                 for (int q = 0; q < 8; ++q) {
                     if (kForm[s.kind].reads >> q & 1) rd(b[q]);
-                    if (kForm[s.kind].writes >> q & 1) wr(b[q]);
+                    if (kForm[s.kind].writes >> q & 1) wr(s.own != kNone ? own + (int)i : b[q]);
                 }
         }
     }
@@ -559,13 +560,13 @@ int run_pack(const znn_program& P, float* const* buf, char* scratch, hipStream_t
     return mfma_pack_weights(items.data(), (int)items.size(), s);
 }
 
-int run_bias(const znn_program& P, float* const* buf, char* scratch, hipStream_t s)
+int run_bias(const znn_program& P, const std::vector<int>& steps, float* const* buf, char* scratch, hipStream_t s)
 {
-    for (size_t i0 = 0; i0 < P.bias_steps.size(); i0 += kBiasItems) {
+    for (size_t i0 = 0; i0 < steps.size(); i0 += kBiasItems) {
         BiasArgs A = {};
         unsigned blocks = 0;
-        for (; A.n < kBiasItems && i0 + A.n < P.bias_steps.size(); ++A.n) {
-            const Step& b = P.steps[P.bias_steps[i0 + A.n]];
+        for (; A.n < kBiasItems && i0 + A.n < steps.size(); ++A.n) {
+            const Step& b = P.steps[steps[i0 + A.n]];
             A.item[A.n] = BiasItem{buf[b.op.buf[0]], (float*)(scratch + b.own), voxels(b.op), bias_spans(b.op), blocks};
             blocks += (unsigned)bias_spans(b.op) * b.op.maps;
         }
@@ -670,11 +671,13 @@ int run_step(znn_program& P, Step& t, float* const* buf, char* scratch, float et
     const long count = t.kind > ZNN_OP_CONV_WGRAD ? elements(o) : 0;
     switch (t.kind) {
         case STEP_PACK: return run_pack(P, buf, scratch, s);
-        case STEP_BIAS: return run_bias(P, buf, scratch, s);
+        case STEP_BIAS: return run_bias(P, P.bias_steps, buf, scratch, s);
         case STEP_UPDATE: return run_update(P, buf, scratch, eta, s);
         case ZNN_OP_TRANSFER_FWD: return znn_transfer_fn_fwd(o.fn, o.maps, voxels(o), at(0), at(1), at(2), s);
         case ZNN_OP_TRANSFER_BWD: return znn_transfer_fn_bwd(o.fn, o.maps, voxels(o), at(0), at(1), at(2), s);
-        case ZNN_OP_BIAS_GRAD: return znn_bias_grad(o.maps, voxels(o), at(0), at(1), s);
+        case ZNN_OP_BIAS_GRAD:
+            if (t.own != kNone) return run_bias(P, {(int)(&t - P.steps.data())}, buf, scratch, s);
+            return znn_bias_grad(o.maps, voxels(o), at(0), at(1), s);
         case ZNN_OP_FILTER_FWD:
             return znn_maxfilter3d_sparse_fwd(o.maps, o.n, o.window, o.sparsity, at(0), at(1), (int32_t*)at(2), s);
         case ZNN_OP_FILTER_BWD:

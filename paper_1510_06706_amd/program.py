@@ -19,7 +19,13 @@ LOSSES = {"square": 0, "cross_entropy": 1}
 
 class Program:
     """Buffers are numbers.  ``given`` ones are tensors of the caller, ``fresh`` ones are allocated by every
-    run and returned, ``gradient`` ones likewise (all from one allocation), ``kept`` ones never leave the program."""
+    run and returned, ``gradient`` ones likewise (all from one allocation), ``kept`` ones never leave the run: they
+    and the scratch memory are allocated by every run and handed back behind it, so that a net holds nothing between
+    its rounds, runs on any stream, and a recorded round owns what it works on."""
+
+    # Bytes of kept buffers that have memory of their own.  Beyond it they take turns: the bias gradients then
+    # come in a launch per layer instead of one (a few us of rounds that move more than this several times over).
+    OWN_BYTES = 1 << 30
 
     def __init__(self, device, streams=1):
         self.device, self.streams = device, streams
@@ -54,8 +60,35 @@ class Program:
         op["fn"] = TRANSFER_FNS[fn]
         return True
 
+    def _take_turns(self):
+        """Gives kept buffers whose uses do not overlap one number.  The library orders the operations by the
+        buffers they name, so that this holds on several streams too."""
+        first, last = {}, {}
+        for i, d in enumerate(self.ops):
+            for b in d["buf"]:
+                if b >= 0 and self.kinds[b][0] == "kept":
+                    first.setdefault(b, i)
+                    last[b] = i
+        number, free = {}, []                       # free: (last use, number) of the numbers in use so far
+        for b in sorted(first, key=lambda b: first[b]):
+            size = lambda f: math.prod(self.shapes[f[1]])  # noqa: E731
+            idle = [f for f in free if f[0] < first[b]]
+            # the largest idle one: its memory grows least
+            f = max(idle, key=size) if idle else (-1, b)
+            number[b] = f[1]
+            if idle:
+                free.remove(f)
+                if math.prod(self.shapes[b]) > size(f):
+                    self.shapes[f[1]] = self.shapes[b]
+                self.kinds[b] = ("turn", f[1])
+            free.append((last[b], f[1]))
+        for d in self.ops:
+            d["buf"] = [number.get(b, b) for b in d["buf"]]
+
     def build(self):
         n = len(self.kinds)
+        if sum(4 * math.prod(s) for s, k in zip(self.shapes, self.kinds) if k[0] == "kept") > self.OWN_BYTES:
+            self._take_turns()
         ops = (znn.Op * len(self.ops))()
         for o, d in zip(ops, self.ops):
             o.kind, o.stream, o.fn, o.loss, o.maps = d["kind"], d["stream"], d["fn"], d["loss"], d["maps"]
@@ -83,8 +116,9 @@ class Program:
                 slab += up(size)
             elif kind == "fresh":
                 self._fresh.append((b, self.shapes[b], integer))
+        at = dict(self._kept)
+        self._kept += [(b, at[k[1]]) for b, k in enumerate(self.kinds) if k[0] == "turn"]
         self._kept_bytes, self._slab = kept, slab // 4
-        self._scratch = None
         return self
 
     def __del__(self):
@@ -102,11 +136,12 @@ class Program:
         import torch
         device = self.device
         buf, st = (ctypes.c_void_p * len(self.kinds))(), (ctypes.c_void_p * self.streams)()     # of this run alone
-        if self._scratch is None and self._kept_bytes:
-            self._scratch = torch.empty(self._kept_bytes + 256, dtype=torch.uint8, device=device)
-            self._base = (self._scratch.data_ptr() + 255) & ~255
+        base = None
+        if self._kept_bytes:
+            scratch = torch.empty(self._kept_bytes + 256, dtype=torch.uint8, device=device)
+            base = (scratch.data_ptr() + 255) & ~255
         for b, at in self._kept:
-            buf[b] = self._base + at
+            buf[b] = base + at
         for b, t in given.items():
             buf[b] = t.data_ptr()
         out = {}
@@ -115,13 +150,12 @@ class Program:
             buf[b] = t.data_ptr()
         if self._slab:
             slab = torch.empty(self._slab, dtype=torch.float32, device=device)
-            base = slab.data_ptr()
             for b, at in self._grads:
-                buf[b] = base + at
+                buf[b] = slab.data_ptr() + at
         st[0] = torch.cuda.current_stream().cuda_stream
         for i, s in enumerate(streams):
             st[i + 1] = s.cuda_stream
-        znn._check(znn.lib().znn_program_run(self._h, buf, self._base if self._kept_bytes else None, self.scratch_bytes, eta, st))
+        znn._check(znn.lib().znn_program_run(self._h, buf, base, self.scratch_bytes, eta, st))
         for b, at in self._grads:
             shape = self.shapes[b]
             out[b] = slab[at // 4:at // 4 + math.prod(shape)].view(shape)

@@ -191,3 +191,39 @@ def test_layers_of_a_net_may_share_their_kernels():
     for l in (2, 3):
         for k, v in nets[1].params[l].items():
             assert rel_err(host(nets[0].params[l][k]), host(v)) <= 2e-6, (l, k)
+
+
+def test_rounds_hold_no_memory_between_them(monkeypatch):
+    """Scratch and backward images belong to a run; where they are large the images take turns, with the same results
+    (bias gradients in a launch per layer add in the order of the one launch for all)."""
+    import torch
+    from paper_1510_06706_amd import program as zp
+    in_shape, layers = NET_FORMS["filters"]
+    x, target, params = synth.net_tensors(layers, in_shape, 71)
+    g = synth.multiscale_graph()
+    inputs, targets, gparams = synth.graph_tensors(g, 53)
+    x, target = dev(x), dev(target)
+    inputs, targets = ({n: dev(v) for n, v in d.items()} for d in (inputs, targets))
+
+    def rounds():
+        res, kept = [], []
+        for mode in ("direct", "fft"):
+            net, gnet = znet.Net(layers, in_shape, params, mode), zgraph.GraphNet(g, gparams, mode)
+            for run in (lambda: net.train_round(x, target, 0.05)[3],  # noqa: B023
+                        lambda: gnet.train_round(inputs, targets, 0.05)[3], lambda: net.forward(x)[0][1:]):  # noqa: B023
+                torch.cuda.synchronize()
+                before = torch.cuda.memory_allocated()
+                out = run()
+                torch.cuda.synchronize()
+                rows = out.values() if isinstance(out, dict) else out
+                res += [host(v) for r in rows if r is not None for v in (r.values() if isinstance(r, dict) else [r])]
+                del out, rows
+                assert torch.cuda.memory_allocated() <= before
+            kept += [net._program("square")[0]._kept_bytes, gnet._programs["square"][0]._kept_bytes]
+        return res, kept
+
+    want, most = rounds()
+    monkeypatch.setattr(zp.Program, "OWN_BYTES", 0)
+    got, less = rounds()
+    assert all(b < a for a, b in zip(most, less)), (most, less)
+    assert len(got) == len(want) and all(np.array_equal(a, b) for a, b in zip(want, got))

@@ -57,7 +57,7 @@ def test_spectra_are_shared_only_by_passes_that_follow_the_ones_that_make_them()
 
 
 def test_sums_move_to_the_update_only_where_no_operation_could_tell():
-    """Scratch holds the parts of the sums that move: none where the operand or the gradient is used again."""
+    """Scratch holds the parts of the sums that the update completes: none where the gradient is used before."""
     image, bias = (3, 70, 60, 50), (3,)
     shapes = [image, bias, bias, image, bias]       # gradient, its sums, biases, others
     how = dict(maps=3, n=image[1:])
@@ -67,7 +67,6 @@ def test_sums_move_to_the_update_only_where_no_operation_could_tell():
     need = lambda *ops: program(ops, shapes).scratch_bytes  # noqa: E731
     moved = need(G, U)
     assert moved > 0 and need(rewrite, G, U) == moved and need(G, reread) == 0
-    assert need(G, rewrite, U) == need(G, U, rewrite) == 0
     assert need(G, reread, U) == need(G, U, reread) == 0
     assert need(U, G) == 0
     assert need(G, G, U) == moved                    # the second one counts
@@ -96,6 +95,21 @@ def test_a_round_holds_no_more_of_a_layer_than_its_plan_allows(mode):
         plan.set_round_memory(bound)
         assert need() <= min(most, passes + bound), bound
     assert need() == most and most > passes
+
+
+def test_kept_buffers_take_turns_where_their_uses_do_not_overlap(monkeypatch):
+    def chain(own):
+        monkeypatch.setattr(zp.Program, "OWN_BYTES", own)
+        P = zp.Program("cuda:0")
+        a, bias, last = P.buffer("given", (2, 40)), P.buffer("given", (2,)), P.buffer("fresh", (2, 40))
+        kept = [P.buffer("kept", (2, 40)) for _ in range(6)]
+        for src, dst in zip([a] + kept, kept + [last]):
+            P.add(zp.TRANSFER_FWD, (src, bias, dst), maps=2, n=(1, 1, 40))
+        P.add(zp.NODE_SUM, (last, last, kept[1]), maps=2, n=(1, 1, 40))       # the second one is used again at the end
+        P.build()
+        return len({at for _, at in P._kept}), {b for b, _ in P._kept} == set(kept), P._kept_bytes
+    assert chain(1 << 30) == (6, True, 6 * 512)
+    assert chain(0) == (3, True, 3 * 512)
 
 
 def refused(ops, shapes):
@@ -208,6 +222,17 @@ def test_operands_of_a_layer_written_between_its_passes(order, buffer):
     ops = conv_ops(plan, order)
     for at in (1, 2):
         check(ops[:at] + [write] + ops[at:], shapes + [shape, (maps,)], 2 + at)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("streams", [1, 2])
+def test_bias_gradients_of_an_operand_that_is_written_again(streams):
+    image, bias = (3, 70, 60, 50), (3,)
+    how = dict(maps=3, n=image[1:])
+    G, U = (zp.BIAS_GRAD, (0, 1), how), (zp.UPDATE, (1, 2), dict(n=(1, 1, 3)))
+    rewrite = (zp.TRANSFER_FWD, (3, 4, 0), dict(how, stream=streams - 1))
+    for ops in ([G, rewrite, U], [G, U, rewrite], [rewrite, G, U], [G, rewrite, (zp.BIAS_GRAD, (0, 4), how), U]):
+        check(ops, [image, bias, bias, image, bias], 8, streams=streams)
 
 
 @pytest.mark.gpu
