@@ -223,10 +223,12 @@ class GraphNet:
         g, shape, E = self.graph, self.shapes, self.edges
         P = zp.Program(self.device, 1 + len(self.streams))
         stream = lambda i: 1 + i % len(self.streams)  # noqa: E731
-        given = {("x", n): P.buffer("given", shape[n]) for n in g["inputs"]}
-        for n, p in self.params.items():
-            for k in p:
-                given[n, k] = P.buffer("given", p[k].shape)
+        given = {(n, "x"): P.buffer("given", shape[n]) for n in g["inputs"]}
+        for e in E:
+            if e[0] == "conv":
+                given[e[1], "w"] = P.buffer("given", (e[4], shape[e[2]][0]) + tuple(e[5]))
+            elif e[0] == "transfer":
+                given[e[1], "b"] = P.buffer("given", shape[e[2]][:1])
         by_name = {e[1]: e for e in E}
 
         def parts_sum(out, parts, at, dims):
@@ -238,7 +240,7 @@ class GraphNet:
                 parts = [out] + parts[6:]
 
         # forward: img[n] is node n's image, aux[e] what the backward edge reads
-        img, aux, part = {n: given["x", n] for n in g["inputs"]}, {}, {}
+        img, aux, part = {n: given[n, "x"] for n in g["inputs"]}, {}, {}
         alone = lambda n: len(self.incoming[n]) == 1  # noqa: E731
         for i, e in enumerate(E):
             kind, name, src, dst = e[:4]
@@ -299,7 +301,7 @@ class GraphNet:
             needed = src not in g["inputs"]
             gs = None
             if kind == "conv":
-                grads[name] = {"w": P.buffer("gradient", self.params[name]["w"].shape)}
+                grads[name] = {"w": P.buffer("gradient", P.shapes[given[name, "w"]])}
                 if needed:
                     gs = P.buffer("kept", shape[src])
                     gop = P.add(zp.CONV_BWD, (b, given[name, "w"], gs), stream=s, plan=self.plans[name])
@@ -324,7 +326,7 @@ class GraphNet:
                 finish(src, s)
         for n, d in grads.items():
             for k in d:
-                P.add(zp.UPDATE, (d[k], given[n, k]), n=(1, 1, self.params[n][k].numel()))
+                P.add(zp.UPDATE, (d[k], given[n, k]), n=(1, 1, math.prod(P.shapes[d[k]])))
         return P.build(), given, targets, img, aux, gout, grads
 
     def train_round(self, inputs, targets, eta, loss="square"):
@@ -335,13 +337,13 @@ class GraphNet:
         if loss not in self._programs:
             self._programs[loss] = self._build(loss)
         P, given, target, img, aux, gout, grads = self._programs[loss]
-        tensors = {given["x", n]: zp.check_input(inputs[n], self.shapes[n]) for n in self.graph["inputs"]}
-        for n, p in self.params.items():
-            for k in p:
-                tensors[given[n, k]] = zp.check_input(p[k], P.shapes[given[n, k]])
+        tensors = {given[n, "x"]: zp.check_input(inputs[n], self.shapes[n]) for n in self.graph["inputs"]}
+        for (n, k), b in given.items():
+            if k != "x":
+                tensors[b] = zp.check_parameter(self.params[n][k], k, P.shapes[b])
         for n, b in target.items():
             tensors[b] = zp.check_input(targets[n], count=math.prod(self.shapes[n]))
         out = P.run(tensors, float(eta), self.streams)
-        out.update({given["x", n]: inputs[n] for n in self.graph["inputs"]})
+        out.update({given[n, "x"]: inputs[n] for n in self.graph["inputs"]})
         return ({n: out[b] for n, b in img.items()}, {n: out[b] for n, b in aux.items()}, {n: out[b] for n, b in gout.items()},
                 {n: {k: out[b] for k, b in d.items()} for n, d in grads.items()})

@@ -69,11 +69,13 @@ class Net:
             return self._programs[loss]
         P = zp.Program(self.device)
         L, shape = self.layers, self.shapes
-        given = {("x", 0): P.buffer("given", shape[0])}
-        for l, p in enumerate(self.params):
-            for k in p or ():
-                given[l, k] = P.buffer("given", p[k].shape)
-        act, aux, conv = [given["x", 0]], [None] * len(L), None
+        given = {(0, "x"): P.buffer("given", shape[0])}
+        for l, spec in enumerate(L):
+            if spec[0] == "conv":
+                given[l, "w"] = P.buffer("given", (spec[2], spec[1]) + tuple(spec[3]))
+            elif spec[0] == "transfer":
+                given[l, "b"] = P.buffer("given", shape[l][:1])
+        act, aux, conv = [given[0, "x"]], [None] * len(L), None
         for l, spec in enumerate(L):
             kind, y = spec[0], P.buffer("fresh", shape[l + 1])
             if kind == "conv":
@@ -109,7 +111,7 @@ class Net:
                     P.add(zp.BIAS_GRAD, (g, grads[l]["b"]), **how)
                     op = None
                 elif kind == "conv":
-                    grads[l] = {"w": P.buffer("gradient", self.params[l]["w"].shape)}
+                    grads[l] = {"w": P.buffer("gradient", P.shapes[given[l, "w"]])}
                     ready = g
                     if l > 0:
                         g = below()
@@ -122,16 +124,16 @@ class Net:
                     g = h
             for l, d in enumerate(grads):
                 for k in d or ():
-                    P.add(zp.UPDATE, (d[k], given[l, k]), n=(1, 1, self.params[l][k].numel()))
+                    P.add(zp.UPDATE, (d[k], given[l, k]), n=(1, 1, math.prod(P.shapes[d[k]])))
         self._programs[loss] = P.build(), given, act, aux, target, gout, grads
         return self._programs[loss]
 
     def _run(self, loss, x, target=None, eta=0.0):
         P, given, act, aux, t, gout, grads = self._program(loss)
-        tensors = {given["x", 0]: zp.check_input(x, self.shapes[0])}
-        for l, p in enumerate(self.params):
-            for k in p or ():
-                tensors[given[l, k]] = zp.check_input(p[k], P.shapes[given[l, k]])
+        tensors = {given[0, "x"]: zp.check_input(x, self.shapes[0])}
+        for (l, k), b in given.items():
+            if k != "x":
+                tensors[b] = zp.check_parameter(self.params[l][k], k, P.shapes[b])
         if loss is not None:
             tensors[t] = zp.check_input(target, count=math.prod(self.shapes[-1]))
         out = P.run(tensors, float(eta))

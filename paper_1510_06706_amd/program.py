@@ -163,11 +163,16 @@ class Program:
 
 
 def check_input(t, shape=None, count=None):
-    """A tensor handed to a round: float32 values on the GPU, contiguous, of the shape (or number of values) expected."""
+    """A tensor handed to a round: float32 values on the GPU, contiguous, of the shape (or at least the number of values) expected."""
     import torch
     if shape is not None:
         assert tuple(t.shape) == tuple(shape), t.shape
-    znn._ptr(t, torch.float32)
-    if count is not None and t.numel() != count:
+    if count is not None and t.numel() < count:
         raise ValueError("expected %d values, got %d" % (count, t.numel()))
+    znn._ptr(t, torch.float32)
     return t
+
+
+def check_parameter(t, key, shape):
+    """The kernels ("w") of a layer, which the calls per layer take in their shape only, or its biases ("b")."""
+    return check_input(t, shape) if key == "w" else check_input(t, count=math.prod(shape))

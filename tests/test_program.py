@@ -7,7 +7,9 @@ import numpy as np
 import pytest
 
 from paper_1510_06706_amd import binding as znn
+from paper_1510_06706_amd import net as znet
 from paper_1510_06706_amd import program as zp
+from paper_1510_06706_amd import synth
 
 SHAPE = (3, 10, 12, 9)          # of every image; kernels of one voxel keep it
 
@@ -139,6 +141,30 @@ def test_sums_with_an_absent_part_before_a_given_one_are_refused():
         program(add(*b), shapes)
     for b in ((0, -1, 2), (0, 1, -1, 3), (0, 1, 2, 3, -1, 5), (0, 1, -1, -1, -1, -1, 6, 7)):
         assert refused(add(*b), shapes)
+
+
+NET = [("conv", 2, 3, (2, 1, 2)), ("transfer",), ("conv", 3, 2, (1, 2, 2)), ("transfer", "logistic")]
+
+
+def test_rounds_refuse_kernels_of_another_shape(monkeypatch):
+    """Also where the number of values is the same, and where they were replaced before the first round."""
+    import torch
+    in_shape = (2, 5, 6, 7)
+    x, target, params = synth.net_tensors(NET, in_shape, 3)
+    x, target = torch.from_numpy(x), torch.from_numpy(target)
+    monkeypatch.setattr(znn, "_ptr", lambda t, dtype=None: None)       # what is refused here is refused before any launch
+    for l, shape in ((0, (3, 2, 1, 2, 2)), (2, (2, 3, 1, 2, 1)), (2, (3, 2, 1, 2, 2))):
+        net = znet.Net(NET, in_shape, params, "direct", device="cpu")
+        net.params[l]["w"] = torch.zeros(shape)
+        for run in (lambda: net.forward(x), lambda: net.train_round(x, target, 0.1)):  # noqa: B023
+            with pytest.raises(AssertionError):
+                run()
+    net = znet.Net(NET, in_shape, params, "direct", device="cpu")
+    net.params[1]["b"] = torch.zeros(2)
+    with pytest.raises(ValueError):
+        net.forward(x)
+    with pytest.raises(AssertionError):
+        net.train_round(torch.zeros((2, 5, 6, 8)), target, 0.1)
 
 
 # ------------------------------------------------------------------------------------------------------- on the GPU
