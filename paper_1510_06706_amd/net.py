@@ -142,9 +142,10 @@ class Net:
                 [None if d is None else {k: out[b] for k, b in d.items()} for d in grads])
 
     def forward(self, x):
-        if not self._memo:
-            return self._run(None, x)[:2]
-        return self._forward_by_layer(x)
+        # without convolutions, inputs of any extent pass
+        if self._memo or tuple(x.shape) != tuple(self.shapes[0]):
+            return self._forward_by_layer(x)
+        return self._run(None, x)[:2]
 
     def _forward_by_layer(self, x):
         """One library call per layer: what plans with memoized spectra of their own need before ``backward``."""

@@ -227,3 +227,17 @@ def test_rounds_hold_no_memory_between_them(monkeypatch):
     got, less = rounds()
     assert all(b < a for a, b in zip(most, less)), (most, less)
     assert len(got) == len(want) and all(np.array_equal(a, b) for a, b in zip(want, got))
+
+
+def test_nets_without_convolutions_take_images_of_any_extent():
+    """Their forward pass is not bound to the extents the net was made for."""
+    layers = [("maxfilter", (2, 2, 2)), ("transfer", "tanh"), ("maxpool", (1, 2, 2))]
+    in_shape = (3, 6, 7, 9)
+    _, _, params = synth.net_tensors(layers, in_shape, 73)
+    net = znet.Net(layers, in_shape, params)
+    for n in (in_shape, (3, 9, 5, 7)):
+        x = synth.uniform_pm1(74, 0, n)
+        want, aux = onet.forward(layers, params, x)
+        got = net.forward(dev(x))
+        assert rel_err(host(got[0][-1]), want[-1]) <= 1e-6
+        assert all(a is None or np.array_equal(host(b), a) for a, b in zip(aux, got[1]))
