@@ -188,6 +188,8 @@ class Plan:
         self._h = ctypes.c_void_p(0)
         self._ws = None
         self._spectra = None
+        self._memo = None
+        self.revision = 0           # counts the changes that a program made of the plan does not see
         _check(lib().znn_plan_create(ctypes.byref(self.desc), ctypes.byref(self._h)))
 
     def close(self):
@@ -226,10 +228,12 @@ class Plan:
     def set_spectra_layout(self, layout: str):
         """'auto', 'full' (the kernel transforms themselves) or 'folded' (half spectra)."""
         _check(lib().znn_plan_set_spectra_layout(self._h, SPECTRA_LAYOUTS[layout]))
+        self.revision += 1
 
     def set_round_memory(self, nbytes: int):
         """Bounds what rounds as one program hold of this layer beside the workspace of its passes."""
         _check(lib().znn_plan_set_round_memory(self._h, int(nbytes)))
+        self.revision += 1
 
     @property
     def spectra_layout(self) -> str:
@@ -279,9 +283,10 @@ class Plan:
         """Attaches a buffer (owned by this object) in which fwd / bwd leave their node spectra."""
         import torch
         need = self.memo_bytes()
-        self._memo = torch.empty(need + 256, dtype=torch.uint8, device=device)
-        aligned = (self._memo.data_ptr() + 255) & ~255
+        buf = torch.empty(need + 256, dtype=torch.uint8, device=device)
+        aligned = (buf.data_ptr() + 255) & ~255
         _check(lib().znn_conv_set_memo(self._h, ctypes.c_void_p(aligned), need))
+        self._memo = buf
 
     def disable_memo(self):
         _check(lib().znn_conv_set_memo(self._h, ctypes.c_void_p(0), 0))

@@ -334,7 +334,7 @@ class GraphNet:
         update runs after every stream has joined: kernels are read by the backward edges."""
         if loss not in zp.LOSSES:
             raise ValueError(loss)
-        if loss not in self._programs:
+        if loss not in self._programs or not self._programs[loss][0].current(list(self.plans.values())):
             self._programs[loss] = self._build(loss)
         P, given, target, img, aux, gout, grads = self._programs[loss]
         tensors = {given[n, "x"]: zp.check_input(inputs[n], self.shapes[n]) for n in self.graph["inputs"]}

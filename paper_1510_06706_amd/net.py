@@ -55,8 +55,11 @@ class Net:
                 self.plans.append(plan)
             else:
                 self.plans.append(None)
-        self._memo = "fft_memo" in self.strategy
         self._programs = {}
+
+    @property
+    def _memo(self):
+        return any(p is not None and p._memo is not None for p in self.plans)
 
     def modes(self):
         return [None if p is None else p.mode for p in self.plans]
@@ -65,7 +68,7 @@ class Net:
     def _program(self, loss):
         """The forward pass (loss None) or a whole training round as a program on the calling stream (kernel gradients
         on a second stream gained nothing: 410 against 422 us a round of the six-layer 3D net, 40 us slower replayed)."""
-        if loss in self._programs:
+        if loss in self._programs and self._programs[loss][0].current([p for p in self.plans if p is not None]):
             return self._programs[loss]
         P = zp.Program(self.device)
         L, shape = self.layers, self.shapes

@@ -95,7 +95,8 @@ class Program:
             o.n, o.window, o.sparsity = (znn._v3(d[k]) for k in ("n", "window", "sparsity"))
             o.buf[:] = d["buf"]
             if d["plan"] is not None:
-                self.plans.append(d["plan"])
+                if all(d["plan"] is not p for p, _ in self.plans):
+                    self.plans.append((d["plan"], d["plan"].revision))
                 o.plan = d["plan"]._h.value
         h = ctypes.c_void_p(0)
         znn._check(znn.lib().znn_program_create(ops, len(self.ops), n, self.streams, ctypes.byref(h)))
@@ -128,6 +129,10 @@ class Program:
                 self._h = None
         except Exception:
             pass
+
+    def current(self, plans):
+        """Whether `plans`, in the order of their first operations, are those the program describes, as they were then."""
+        return len(plans) == len(self.plans) and all(p is q and p.revision == r for p, (q, r) in zip(plans, self.plans))
 
     # ------------------------------------------------------------ runs
     def run(self, given, eta=0.0, streams=()):

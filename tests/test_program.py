@@ -167,6 +167,24 @@ def test_rounds_refuse_kernels_of_another_shape(monkeypatch):
         net.train_round(torch.zeros((2, 5, 6, 8)), target, 0.1)
 
 
+def test_rounds_follow_changes_of_their_plans():
+    layers = [("conv", 8, 8, (3, 3, 3)), ("transfer",), ("conv", 8, 6, (2, 3, 3)), ("transfer", "logistic")]
+    in_shape = (8, 24, 23, 22)
+    params = synth.net_tensors(layers, in_shape, 5)[2]
+    net = znet.Net(layers, in_shape, params, "fft", device="cpu")
+    need = lambda n: [n._program(loss)[0].scratch_bytes for loss in (None, "square")]  # noqa: E731
+    before = need(net)
+    assert net._program("square") is net._program("square")
+    for layout in ("full", "auto"):
+        made = net._program("square")[0]
+        net.plans[2].set_spectra_layout(layout)
+        assert net._program("square")[0] is not made
+    net.plans[2].set_round_memory(0)
+    assert need(net)[1] < before[1]
+    net.plans = znet.Net(layers, in_shape, params, ["direct"] * 4, device="cpu").plans
+    assert need(net) == need(znet.Net(layers, in_shape, params, "direct", device="cpu"))
+
+
 # ------------------------------------------------------------------------------------------------------- on the GPU
 def step_by_step(ops, t):
     """The list through the single entry points, on tensors t."""
@@ -347,3 +365,15 @@ def test_rounds_within_bounds_on_their_memory(mode):
         print("case", mode, bound, flush=True)
         plan.set_round_memory(bound)
         check(conv_ops(plan, "FBW") + [(zp.UPDATE, (5, 1), dict(n=(1, 1, 6 * 8 * 18)))], conv_shapes(plan), 3)
+
+
+@pytest.mark.gpu
+def test_rounds_of_nets_whose_plans_were_given_memo_buffers_fill_them():
+    import torch
+    in_shape = (2, 9, 10, 11)
+    x, target, params = (v if isinstance(v, list) else torch.from_numpy(v).to("cuda:0") for v in synth.net_tensors(NET, in_shape, 7))
+    net = znet.Net(NET, in_shape, params, "fft")
+    net.train_round(x, target, 0.1)
+    net.plans[2].enable_memo()
+    grads = net.train_round(x, target, 0.1)[3]
+    assert torch.equal(net.plans[2].wgrad_memo(), grads[2]["w"])
