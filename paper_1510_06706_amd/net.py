@@ -58,8 +58,11 @@ class Net:
         self._programs = {}
 
     @property
-    def _memo(self):
-        return any(p is not None and p._memo is not None for p in self.plans)
+    def _by_layer(self):
+        """Whether rounds go layer by layer: plans that were given memo buffers leave their spectra there, and in a
+        program a plan stands for one layer, where the caller may have set one for several of a shape."""
+        plans = [p for p in self.plans if p is not None]
+        return any(p._memo is not None for p in plans) or len({id(p) for p in plans}) < len(plans)
 
     def modes(self):
         return [None if p is None else p.mode for p in self.plans]
@@ -146,7 +149,7 @@ class Net:
 
     def forward(self, x):
         # without convolutions, inputs of any extent pass
-        if self._memo or tuple(x.shape) != tuple(self.shapes[0]):
+        if self._by_layer or tuple(x.shape) != tuple(self.shapes[0]):
             return self._forward_by_layer(x)
         return self._run(None, x)[:2]
 
@@ -196,7 +199,7 @@ class Net:
     def train_round(self, x, target, eta, record=None, loss="square"):
         if loss not in zp.LOSSES:
             raise ValueError(loss)
-        if record is None and not self._memo:
+        if record is None and not self._by_layer:
             return self._run(loss, x, target, eta)
         acts, aux = self._forward_by_layer(x)
         gout = znn.loss_grad(acts[-1], target, loss)

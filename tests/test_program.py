@@ -377,3 +377,18 @@ def test_rounds_of_nets_whose_plans_were_given_memo_buffers_fill_them():
     net.plans[2].enable_memo()
     grads = net.train_round(x, target, 0.1)[3]
     assert torch.equal(net.plans[2].wgrad_memo(), grads[2]["w"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode", ["direct", "fft"])
+def test_layers_of_one_shape_may_share_a_plan(mode):
+    import torch
+    layers = [("conv", 3, 3, (1, 1, 1)), ("transfer", "tanh"), ("conv", 3, 3, (1, 1, 1)), ("transfer", "logistic")]
+    in_shape = (3, 7, 8, 9)
+    x, target, params = (v if isinstance(v, list) else torch.from_numpy(v).to("cuda:0") for v in synth.net_tensors(layers, in_shape, 11))
+    own, shared = (znet.Net(layers, in_shape, params, mode) for _ in range(2))
+    shared.plans[2] = shared.plans[0]
+    for _ in range(2):
+        got, want = shared.train_round(x, target, 0.01), own.train_round(x, target, 0.01, record=[])
+        assert torch.equal(got[0][-1], want[0][-1]) and torch.equal(shared.forward(x)[0][-1], own._forward_by_layer(x)[0][-1])
+        assert all(torch.equal(g[k], w[k]) for g, w in zip(got[3], want[3]) for k in w)
