@@ -233,7 +233,7 @@ def test_nets_without_convolutions_take_images_of_any_extent():
     """Their forward pass is not bound to the extents the net was made for."""
     layers = [("maxfilter", (2, 2, 2)), ("transfer", "tanh"), ("maxpool", (1, 2, 2))]
     in_shape = (3, 6, 7, 9)
-    _, _, params = synth.net_tensors(layers, in_shape, 73)
+    params = [None, {"b": synth.uniform_pm1(73, 4, (3,), 0.1)}, None]
     net = znet.Net(layers, in_shape, params)
     for n in (in_shape, (3, 9, 5, 7)):
         x = synth.uniform_pm1(74, 0, n)
