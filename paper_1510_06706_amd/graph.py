@@ -8,14 +8,15 @@ reversed, a node's backward image being the sum over its outgoing edges.
 
 The paper's CPU design runs the edges as tasks on worker threads.  On the GPU the same
 dependency structure becomes streams and events: every edge is launched on one of a few
-HIP streams after waiting for the event of its source node, so independent branches
-overlap on the device, and the kernel-gradient of an edge runs on another stream than
-its backward image (they only share inputs).  Sums at nodes are taken in the fixed order
-of the edge list (every converging edge writes its own buffer, then the buffers are added
-one by one), so results do not depend on which stream finished first.  Every tensor of a
-round stays referenced until the round has joined the calling stream, and the next round
-starts from events recorded after that join, so memory handed back to the allocator is never
-reused while another stream still reads it.
+HIP streams, so independent branches overlap on the device, and the kernel-gradient of an edge
+runs on another stream than its backward image (they only share inputs).  Sums at nodes are
+taken in the fixed order of the edge list (every converging edge writes its own buffer), so
+results do not depend on which stream finished first.
+
+A round (``GraphNet.train_round``) is one native program: the library orders its operations by
+the buffers they use, with events of its own, forks every stream from the calling one and joins
+it again.  ``GraphNet.forward`` and ``backward`` run the passes edge by edge, one library call
+each, for callers that want node images or gradients without a round.
 
 This module only sequences library calls; every arithmetic step runs in libznn's kernels.
 The graph format is the one of ``synth.graph_shapes``.
@@ -59,15 +60,11 @@ class GraphNet:
     """Device-side state of a computation graph: plans per convolution edge, parameters as
     CUDA tensors, a pool of HIP streams (all at the default priority).
 
-    Rounds run eagerly only.  Recording a round into a HIP graph is deliberately not offered:
-    this executor waits on pooled events that were created and first recorded outside any
-    capture, and joins its side streams (among them the kernel-gradient stream) to the
-    calling stream only through the events of later edges, so a capture would contain waits on
-    uncaptured work and forked streams that are never joined back before the capture ends;
-    recording it that way crashed inside the runtime's end-of-capture call.  A capturable
-    executor needs events created inside the capture, every side stream forked from the
-    capturing stream, and a join of every side stream before the capture ends.  Layered nets
-    (``net.Net.capture_round``) run on one stream and can be recorded."""
+    Edge by edge, ``forward`` and ``backward`` wait on pooled events that were first recorded by an
+    earlier pass, and join their side streams only through the events of later edges: they run eagerly
+    only.  Every tensor of a pass stays referenced until the pass has joined the calling stream, and the
+    next pass starts from events recorded after that join, so memory handed back to the allocator is never
+    reused while another stream still reads it."""
 
     def __init__(self, graph, params, mode="auto", device="cuda:0", streams=4):
         import torch
@@ -87,8 +84,8 @@ class GraphNet:
         for n in self.shapes:
             if n not in graph["outputs"] and n not in self.outgoing:
                 raise ValueError("node %r reaches no output" % (n,))
-        # two plans per convolution edge: forward/backward image on one stream, kernel gradient
-        # on another, each with its own workspace
+        # two plans per convolution edge: edge by edge, forward and backward image run on one stream and the
+        # kernel gradient on another, each with its own workspace (programs need one)
         self.plans, self.plans_w = {}, {}
         for e in self.edges:
             if e[0] == "conv":

@@ -175,6 +175,58 @@ def test_round_as_one_program_matches_the_calls_per_layer(form, mode):
         assert rel_err(host(got[2]), host(ref[2])) <= 1e-6
 
 
+def wide_graph():
+    """Nodes where more parts converge than one launch adds (six), in both directions; pooling and max-filter edges that fan
+    out of a node and converge again, a transfer edge into a sum and one behind a sum."""
+    k = (2, 3, 2)
+    edges = [("conv", "c0", "x", "a", 5, k), ("transfer", "t0", "a", "a1"), ("conv", "e0", "x2", "a2", 5, (1, 1, 1)),
+             ("transfer", "u0", "a2", "a3", "tanh")]
+    edges += [("conv", "c%d" % i, "a1", "b", 3, k) for i in range(1, 9)]                # eight parts forward and backward
+    edges += [("transfer", "t1", "b", "b1", "tanh"),
+              ("maxpool", "p0", "b1", "p", (2, 1, 2)), ("maxfilter", "m0", "b1", "m", (2, 1, 2)),
+              ("maxpool", "p1", "b1", "p", (2, 1, 2)),                                     # two poolings into one node
+              ("conv", "c9", "a3", "q", 3, (1, 1, 1)), ("transfer", "t2", "p", "q", "logistic"),
+              ("conv", "d0", "m", "y0", 2, k), ("transfer", "t3", "y0", "y", "logistic"),
+              ("conv", "d1", "q", "z", 2, k)]
+    return {"inputs": {"x": (2, 10, 12, 12), "x2": (2, 4, 8, 5)}, "edges": edges, "outputs": ["y", "z"]}
+
+
+@pytest.mark.parametrize("mode", ["direct", "fft"])
+@pytest.mark.parametrize("form", ["multiscale", "wide"])
+def test_round_of_a_graph_as_one_program_matches_the_calls_per_edge(form, mode):
+    """`forward` and `backward` run the same edges one library call each."""
+    import torch
+    g = synth.multiscale_graph() if form == "multiscale" else wide_graph()
+    inputs, targets, params = synth.graph_tensors(g, 81)
+    one, by_edge = zgraph.GraphNet(g, params, mode), zgraph.GraphNet(g, params, mode)
+    # the second round's images inherit the first's gradients, which agree to 2e-5, through a step of at most about a
+    # hundredth of the weights: 2e-7 of them
+    eta = 0.01 / max(v.size for v in targets.values())
+    d_in, d_t = ({n: dev(v) for n, v in d.items()} for d in (inputs, targets))
+    for round_ in range(2):
+        got = one.train_round(d_in, d_t, eta)
+        img, aux, _ = by_edge.forward(d_in)
+        gout = {n: znn.loss_grad(img[n], d_t[n], "square") for n in g["outputs"]}
+        grads, _ = by_edge.backward(img, aux, gout)
+        for n, d in grads.items():
+            for k, v in d.items():
+                znn.sgd_update(by_edge.params[n][k], v, eta)
+        torch.cuda.synchronize()
+        assert set(got[0]) == set(img) and set(got[3]) == set(grads)
+        near = lambda a, b, tol: rel_err(host(a), host(b)) <= tol  # noqa: E731
+        for n in img:
+            assert near(got[0][n], img[n], 1e-6), ("image", n)
+        for e in g["edges"]:
+            if e[0] in ("maxfilter", "maxpool"):
+                assert np.array_equal(host(got[1][e[1]]), host(aux[e[1]])), ("choice", e[1])
+        for n in gout:
+            assert near(got[2][n], gout[n], 2e-6), ("loss", n)
+        for n, d in grads.items():
+            for k, v in d.items():
+                assert near(got[3][n][k], v, 2e-5), ("gradient", n, k)
+                assert near(one.params[n][k], by_edge.params[n][k], 2e-6), ("update", n, k)
+
+
 def test_layers_of_a_net_may_share_their_kernels():
     """Two layers holding one tensor: the round gives what the calls per layer give, where the updates follow each other."""
     layers = [("conv", 2, 6, (3, 3, 3)), ("transfer",), ("conv", 6, 6, (3, 3, 3)), ("transfer", "tanh"),
