@@ -12,7 +12,17 @@ from paper_1510_06706_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-TOL = {"direct": 1e-4, "fft": 1e-3}
+TOL = {"direct": 1e-4, "fft": 1e-3, "volumes": 1e-3}
+
+
+def plan(f, fo, n, k, mode, s=(1, 1, 1)):
+    """A plan of the direct method, of the FFT method as the library runs it ("fft": on overlapping tiles where that is
+    expected to be faster), or of the FFT method on whole volumes ("volumes": in the layout the library takes for those)."""
+    p = znn.Plan(f, fo, n, k, "fft" if mode == "volumes" else mode, s)
+    if mode == "volumes":
+        p.set_spectra_layout(p.spectra_layout)
+        assert p.tiles is None
+    return p
 
 
 def dev(a):
@@ -53,13 +63,13 @@ SMALL = [
 ]
 
 
-@pytest.mark.parametrize("mode", ["direct", "fft"])
+@pytest.mark.parametrize("mode", ["direct", "fft", "volumes"])
 @pytest.mark.parametrize("f,fo,n,k", SMALL)
 def test_three_passes_match_the_oracle(f, fo, n, k, mode):
     print("case", f, fo, n, k, mode, flush=True)
     cfg = synth.LayerShape("t", f, fo, n, k, 1.0, 77 + f + fo)
     inp, w, gout = synth.layer_tensors(cfg)
-    p = znn.Plan(f, fo, n, k, mode)
+    p = plan(f, fo, n, k, mode)
     d_in, d_w, d_g = dev(inp), dev(w), dev(gout)
     out = host(p.fwd(d_in, d_w))
     gin = host(p.bwd(d_g, d_w))
@@ -145,13 +155,13 @@ SPARSE = [
 ]
 
 
-@pytest.mark.parametrize("mode", ["direct", "fft"])
+@pytest.mark.parametrize("mode", ["direct", "fft", "volumes"])
 @pytest.mark.parametrize("f,fo,n,k,s", SPARSE)
 def test_sparse_convolution_matches_the_oracle(f, fo, n, k, s, mode):
     print("case", f, fo, n, k, s, mode, flush=True)
     cfg = synth.LayerShape("t", f, fo, n, k, 1.0, 55 + f, s)
     inp, w, gout = synth.layer_tensors(cfg)
-    p = znn.Plan(f, fo, n, k, mode, s)
+    p = plan(f, fo, n, k, mode, s)
     assert p.o == oracle.out_extents(n, k, s)
     d_in, d_w, d_g = dev(inp), dev(w), dev(gout)
     tol = TOL[mode]
@@ -175,7 +185,7 @@ def test_fft_layers_with_folded_kernel_transform_match_the_oracle(f, fo, n, k, s
     print("case", f, fo, n, k, s, flush=True)
     cfg = synth.LayerShape("t", f, fo, n, k, 1.0 / np.sqrt(f * np.prod(k)), 91 + f, s)
     inp, w, gout = synth.layer_tensors(cfg)
-    p = znn.Plan(f, fo, n, k, "fft", s)
+    p = plan(f, fo, n, k, "volumes", s)
     N = p.fft_extents
     full = f * fo * N[0] * N[1] * (N[2] // 2 + 1) * 8
     assert p.spectra_bytes() < full          # half spectra: the folded path is the one that runs
@@ -235,7 +245,7 @@ def test_fft_passes_with_register_resident_pencils_for_every_extent(N):
     for n, k in (((N, 6, 7), (3, 2, 2)), ((4, N, 7), (2, 3, 2))):
         cfg = synth.LayerShape("t", 2, 3, n, k, 1.0, 200 + N)
         inp, w, gout = synth.layer_tensors(cfg)
-        p = znn.Plan(2, 3, n, k, "fft")
+        p = plan(2, 3, n, k, "volumes")
         assert p.fft_extents[0 if n[0] == N else 1] == N
         d_in, d_w, d_g = dev(inp), dev(w), dev(gout)
         assert rel_err(host(p.fwd(d_in, d_w)), oracle.conv3d_fwd(inp, w)) <= TOL["fft"], (n, "fwd")
@@ -265,7 +275,7 @@ def test_fft_x_passes_with_register_resident_rows_for_every_extent(N):
         n, k = (5, 17, nx), (2, 3, 4)
         cfg = synth.LayerShape("t", 2, 3, n, k, 1.0, 500 + N)
         inp, w, gout = synth.layer_tensors(cfg)
-        p = znn.Plan(2, 3, n, k, "fft")
+        p = plan(2, 3, n, k, "volumes")
         assert p.fft_extents[2] == N
         d_in, d_w, d_g = dev(inp), dev(w), dev(gout)
         assert rel_err(host(p.fwd(d_in, d_w)), oracle.conv3d_fwd(inp, w)) <= TOL["fft"], (n, "fwd")
@@ -301,7 +311,7 @@ def test_fft_x_and_y_passes_in_one_launch_for_every_extent(N):
             n = (8, ny, nx)
             cfg = synth.LayerShape("t", 3, 2, n, k, 1.0, 600 + N)
             inp, w, gout = synth.layer_tensors(cfg)
-            p = znn.Plan(3, 2, n, k, "fft")
+            p = plan(3, 2, n, k, "volumes")
             assert p.fft_extents[1:] == (N, N)
             d_in, d_w, d_g = dev(inp), dev(w), dev(gout)
             assert rel_err(host(p.fwd(d_in, d_w)), oracle.conv3d_fwd(inp, w)) <= TOL["fft"], (n, k, "fwd")
@@ -322,7 +332,7 @@ def test_fft_strided_passes_in_two_levels_for_every_extent(N):
     for f, fo, n, k in ((2, 1, (1, N, 10), (1, 4, 3)), (1, 2, (N - 1, 4, 6), (5, 2, 2))):
         cfg = synth.LayerShape("t", f, fo, n, k, 1.0, 800 + N)
         inp, w, gout = synth.layer_tensors(cfg)
-        p = znn.Plan(f, fo, n, k, "fft")
+        p = plan(f, fo, n, k, "volumes")
         assert N in p.fft_extents
         d_in, d_w, d_g = dev(inp), dev(w), dev(gout)
         assert rel_err(host(p.fwd(d_in, d_w)), oracle.conv3d_fwd(inp, w)) <= TOL["fft"], (n, "fwd")
@@ -366,11 +376,12 @@ def test_fft_multiply_accumulate_finishes_the_inverse_transform_along_z(f, fo, n
     p.close()
 
 
-def test_resident_kernel_spectra_give_the_same_result():
+@pytest.mark.parametrize("mode", ["fft", "volumes"])
+def test_resident_kernel_spectra_give_the_same_result(mode):
     f, fo, n, k = 6, 5, (10, 12, 9), (3, 4, 2)
     cfg = synth.LayerShape("t", f, fo, n, k, 1.0, 91)
     inp, w, gout = synth.layer_tensors(cfg)
-    p = znn.Plan(f, fo, n, k, "fft")
+    p = plan(f, fo, n, k, mode)
     d_in, d_w, d_g = dev(inp), dev(w), dev(gout)
     out0, gin0 = host(p.fwd(d_in, d_w)), host(p.bwd(d_g, d_w))
     big = p.workspace_bytes(znn.ZNN_PASS_FWD)
@@ -384,11 +395,12 @@ def test_resident_kernel_spectra_give_the_same_result():
     p.close()
 
 
-def test_memoized_node_spectra_give_the_same_kernel_gradient():
+@pytest.mark.parametrize("mode", ["fft", "volumes"])
+def test_memoized_node_spectra_give_the_same_kernel_gradient(mode):
     f, fo, n, k = 5, 7, (11, 9, 12), (3, 2, 4)
     cfg = synth.LayerShape("t", f, fo, n, k, 1.0, 93)
     inp, w, gout = synth.layer_tensors(cfg)
-    p = znn.Plan(f, fo, n, k, "fft")
+    p = plan(f, fo, n, k, mode)
     d_in, d_w, d_g = dev(inp), dev(w), dev(gout)
     gw0 = host(p.wgrad(d_in, d_g))
     p.enable_memo()

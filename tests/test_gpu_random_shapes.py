@@ -1,4 +1,5 @@
-"""Parity of the three passes with the oracle on a seeded sweep of random layer shapes, both methods.
+"""Parity of the three passes with the oracle on a seeded sweep of random layer shapes: the direct method, the FFT method
+as the library runs it (on overlapping tiles where that is expected to be faster) and on whole volumes.
 
 The hand-picked shapes of test_gpu_parity.py aim at known code paths; this sweep is for the ones nobody
 thought of: map counts around the tile sizes (16 q + r), anisotropic and sparse kernels, 2D layers, long
@@ -13,7 +14,7 @@ from paper_1510_06706_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-TOL = {"direct": 1e-4, "fft": 1e-3}
+TOL = {"direct": 1e-4, "fft": 1e-3, "volumes": 1e-3}
 WIDTHS = [1, 3, 8, 17, 24, 33, 40, 56, 72, 88, 104, 120, 136]
 
 
@@ -57,9 +58,14 @@ def test_random_layer_shapes_match_the_oracle(long_rows):
         inp, w, gout = synth.layer_tensors(cfg)
         refs = (oracle.conv3d_fwd(inp, w, s), oracle.conv3d_bwd(gout, w, n, s), oracle.conv3d_wgrad(inp, gout, s))
         d_in, d_w, d_g = (torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0") for a in (inp, w, gout))
-        for mode in ("direct", "fft"):
+        for mode in ("direct", "fft", "volumes"):
             print("case", it, mode, f, fo, n, k, s, flush=True)
-            p = znn.Plan(f, fo, n, k, mode, s)
+            p = znn.Plan(f, fo, n, k, "direct" if mode == "direct" else "fft", s)
+            if mode == "volumes":
+                if p.tiles is None:
+                    p.close()
+                    continue            # that is what "fft" has just run
+                p.set_spectra_layout(p.spectra_layout)
             got = (p.fwd(d_in, d_w), p.bwd(d_g, d_w), p.wgrad(d_in, d_g))
             torch.cuda.synchronize()
             for name, g, r in zip(("fwd", "bwd", "wgrad"), got, refs):
