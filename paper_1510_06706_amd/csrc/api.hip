@@ -203,8 +203,7 @@ static size_t fft_pass_bytes(const Geom& g, const FftWay& w, int pass, bool resi
 {
     if (!w.tile.on) return fft_workspace(g, w.fold, pass, resident).total;
     const size_t need = tile_workspace_bytes(g, w.tile, pass, resident);
-    // forward and backward report no less than the whole-volume passes would take, so that the tiles of a layer
-    // with much overlap come in fewer chunks
+    // forward and backward: the same workspace serves the plan once it is set to the default layout of whole volumes
     return pass == ZNN_PASS_WGRAD ? std::max(need, align256(sizeof(float2) * (size_t)g.svol()) * (g.f + g.fo))
                                   : std::max(need, fft_workspace(g, w.fold, pass, resident).total);
 }
@@ -231,14 +230,14 @@ static int run_fft_fwd(const Geom& g, const FftWay& y, const float* in, const fl
                        void* ws, float2* memo_in, hipStream_t s)
 {
     if (!y.tile.on) return fft_fwd(g, y.fold, in, w, resident, out, ws, memo_in, s);
-    return tile_fwd(g, y.tile, in, w, resident, out, ws, fft_pass_bytes(g, y, ZNN_PASS_FWD, resident != nullptr), memo_in, s);
+    return tile_fwd(g, y.tile, in, w, resident, out, ws, memo_in, s);
 }
 
 static int run_fft_bwd(const Geom& g, const FftWay& y, const float* gout, const float* w, const float2* resident, float* gin,
                        void* ws, float2* memo_gout, hipStream_t s)
 {
     if (!y.tile.on) return fft_bwd(g, y.fold, gout, w, resident, gin, ws, memo_gout, s);
-    return tile_bwd(g, y.tile, gout, w, resident, gin, ws, fft_pass_bytes(g, y, ZNN_PASS_BWD, resident != nullptr), memo_gout, s);
+    return tile_bwd(g, y.tile, gout, w, resident, gin, ws, memo_gout, s);
 }
 
 static int run_fft_wgrad(const Geom& g, const FftWay& y, const float* in, const float* gout, float* gw, void* ws, hipStream_t s)

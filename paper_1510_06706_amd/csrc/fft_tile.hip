@@ -938,22 +938,6 @@ static size_t add_bytes(const Tiling& L, int maps)
     return align256(sizeof(float) * (size_t)L.M[0] * L.M[1] * L.M[2] * L.tiles * maps);
 }
 
-static size_t result_bytes(const Geom& g, const Tiling& L, int pass, int maps)
-{
-    return tile_node_bytes(g, L, maps) + (pass == ZNN_PASS_BWD ? add_bytes(L, maps) : 0);
-}
-
-// result maps per chunk: as few equal chunks as `bytes` of scratch allow (0: not even one map fits)
-static int chunk_of(const Geom& g, const Tiling& L, int pass, size_t bytes)
-{
-    const int outs = pass == ZNN_PASS_FWD ? g.fo : g.f;
-    for (int n = 1; n <= outs; ++n) {
-        const int c = (outs + n - 1) / n;
-        if (result_bytes(g, L, pass, c) <= bytes) return c;
-    }
-    return 0;
-}
-
 size_t tile_workspace_bytes(const Geom& g, const Tiling& L, int pass, bool resident)
 {
     if (pass == ZNN_PASS_WGRAD)
@@ -993,10 +977,9 @@ static int tile_gradients(const Geom& g, const Tiling& L, const float* gout, flo
 static float inv_volume(const Tiling& L) { return (float)(1.0 / ((double)L.M[0] * L.M[1] * L.M[2])); }
 
 int tile_fwd(const Geom& g, const Tiling& L, const float* in, const float* w, const float2* resident, float* out,
-             void* ws, size_t ws_bytes, float2* memo_in, hipStream_t s)
+             void* ws, float2* memo_in, hipStream_t s)
 {
     char* p = (char*)ws;
-    char* const end = p + ws_bytes;
     float2* U = memo_in;
     if (!U) { U = (float2*)p; p += tile_node_bytes(g, L, g.f); }
     const float2* What = resident;
@@ -1008,34 +991,25 @@ int tile_fwd(const Geom& g, const Tiling& L, const float* in, const float* w, co
         if (rc != ZNN_OK) return rc;
         p += tile_kernel_bytes(g, L);
     }
-    const int chunk = chunk_of(g, L, ZNN_PASS_FWD, (size_t)(end - p));
-    if (chunk < 1) return fail(ZNN_EWORKSPACE, "workspace too small for one result map");
-    for (int j0 = 0; j0 < g.fo; j0 += chunk) {
-        const int nj = std::min(chunk, g.fo - j0);
-        TileProduct P = {};
-        P.A = What + (long)j0 * g.f * 16; P.am = g.f * 16; P.ak = 16; P.blkA = (long)g.f * g.fo * 16;
-        P.B = U; P.bk = L.tiles * 16; P.bn = 16; P.blkB = (long)g.f * L.tiles * 16;
-        P.C = (float2*)p; P.cm = L.tiles * 16; P.cn = 16; P.blkC = (long)nj * L.tiles * 16;
-        P.M = nj; P.N = L.tiles; P.K = g.f; P.blocks = L.blocks; P.splits = 1;
-        rc = product("spectral products forward (tiles)", false, P, s);
-        if (rc != ZNN_OK) return rc;
-        TileGeom G = base_geom(L);
-        const int o[3] = {g.oz, g.oy, g.ox};
-        for (int d = 0; d < 3; ++d) {
-            G.T[d] = L.T[d]; G.hop[d] = L.B[d]; G.n[d] = o[d]; G.w[d] = L.B[d]; G.o[d] = L.M[d] - L.B[d]; G.sp[d] = 1;
-        }
-        rc = inverse_tiles("inverse fft of image tiles", G, (long)nj * L.tiles, (const float2*)p,
-                           out + (long)j0 * g.ovol(), inv_volume(L), 1, 0, s);
-        if (rc != ZNN_OK) return rc;
+    TileProduct P = {};
+    P.A = What; P.am = g.f * 16; P.ak = 16; P.blkA = (long)g.f * g.fo * 16;
+    P.B = U; P.bk = L.tiles * 16; P.bn = 16; P.blkB = (long)g.f * L.tiles * 16;
+    P.C = (float2*)p; P.cm = L.tiles * 16; P.cn = 16; P.blkC = (long)g.fo * L.tiles * 16;
+    P.M = g.fo; P.N = L.tiles; P.K = g.f; P.blocks = L.blocks; P.splits = 1;
+    rc = product("spectral products forward (tiles)", false, P, s);
+    if (rc != ZNN_OK) return rc;
+    TileGeom G = base_geom(L);
+    const int o[3] = {g.oz, g.oy, g.ox};
+    for (int d = 0; d < 3; ++d) {
+        G.T[d] = L.T[d]; G.hop[d] = L.B[d]; G.n[d] = o[d]; G.w[d] = L.B[d]; G.o[d] = L.M[d] - L.B[d]; G.sp[d] = 1;
     }
-    return ZNN_OK;
+    return inverse_tiles("inverse fft of image tiles", G, (long)g.fo * L.tiles, (const float2*)p, out, inv_volume(L), 1, 0, s);
 }
 
 int tile_bwd(const Geom& g, const Tiling& L, const float* gout, const float* w, const float2* resident, float* gin,
-             void* ws, size_t ws_bytes, float2* memo_gout, hipStream_t s)
+             void* ws, float2* memo_gout, hipStream_t s)
 {
     char* p = (char*)ws;
-    char* const end = p + ws_bytes;
     float2* V = memo_gout;
     if (!V) { V = (float2*)p; p += tile_node_bytes(g, L, g.fo); }
     const float2* What = resident;
@@ -1048,56 +1022,41 @@ int tile_bwd(const Geom& g, const Tiling& L, const float* gout, const float* w, 
         p += tile_kernel_bytes(g, L);
     }
     const bool one = L.tiles == 1;
-    // The real tiles of the whole result take the start of the workspace, over the operands that lie there and have been
-    // used by then; where that leaves no room for the spectra of the whole result, it comes in chunks of maps with spectra
-    // and tiles behind the operands.
-    int chunk = g.f;
-    char* result = std::max(p, (char*)ws + add_bytes(L, g.f));
-    float* tiles = (float*)ws;
-    if (tile_node_bytes(g, L, g.f) > (size_t)(end - (char*)ws) || result > end - tile_node_bytes(g, L, g.f)) {
-        chunk = chunk_of(g, L, ZNN_PASS_BWD, (size_t)(end - p));
-        if (chunk < 1) return fail(ZNN_EWORKSPACE, "workspace too small for one result map");
-        result = p;
-        tiles = (float*)(p + tile_node_bytes(g, L, chunk));
-    }
+    // The real tiles of the result take the start of the workspace, over the operands that lie there and have been
+    // used by then; its spectra lie behind both.
+    float* const tiles = (float*)ws;
+    float2* const result = (float2*)std::max(p, (char*)ws + add_bytes(L, g.f));
     const int n[3] = {g.nz, g.ny, g.nx};
-    for (int i0 = 0; i0 < g.f; i0 += chunk) {
-        const int ni = std::min(chunk, g.f - i0);
-        TileProduct P = {};
-        P.A = What + (long)i0 * 16; P.am = 16; P.ak = g.f * 16; P.blkA = (long)g.f * g.fo * 16;
-        P.B = V; P.bk = L.tiles * 16; P.bn = 16; P.blkB = (long)g.fo * L.tiles * 16;
-        P.C = (float2*)result; P.cm = L.tiles * 16; P.cn = 16; P.blkC = (long)ni * L.tiles * 16;
-        P.M = ni; P.N = L.tiles; P.K = g.fo; P.blocks = L.blocks; P.splits = 1;
-        rc = product("spectral products backward (tiles)", true, P, s);
-        if (rc != ZNN_OK) return rc;
-        TileGeom G = base_geom(L);
-        for (int d = 0; d < 3; ++d) {
-            G.T[d] = 1; G.hop[d] = 0; G.o[d] = 0; G.sp[d] = 1;
-            G.n[d] = G.w[d] = one ? n[d] : L.M[d];
-        }
-        rc = inverse_tiles("inverse fft of gradient tiles", G, (long)ni * L.tiles, (const float2*)result,
-                           one ? gin + (long)i0 * g.nvol() : tiles, inv_volume(L), 1, 0, s);
-        if (rc != ZNN_OK) return rc;
-        if (one) continue;
-        TileAdd A = {};
-        A.src = tiles; A.dst = gin + (long)i0 * g.nvol();
-        for (int d = 0; d < 3; ++d) {
-            A.M[d] = L.M[d]; A.T[d] = L.T[d]; A.hop[d] = L.B[d]; A.n[d] = n[d];
-            A.fhop[d] = make_fastdiv((unsigned)L.B[d]);
-        }
-        A.xy = g.ny * g.nx;
-        A.fnx = make_fastdiv((unsigned)g.nx);
-        bool two = true;
-        for (int d = 0; d < 3; ++d) two = two && L.M[d] <= 2 * L.B[d];
-        // z values per workgroup: few enough for four workgroups per compute unit
-        A.zs = two ? (int)std::max(1L, std::min(16L, (long)((A.xy + 255) / 256) * ni * g.nz / 1024)) : 1;
-        const dim3 grid((unsigned)((A.xy + 255) / 256), (unsigned)((g.nz + A.zs - 1) / A.zs), (unsigned)ni);
-        if (two) ZNN_LAUNCH("sum of overlapping tiles", s, k_tile_add2, grid, dim3(256), 0, A);
-        else     ZNN_LAUNCH("sum of overlapping tiles", s, k_tile_add, grid, dim3(256), 0, A);
-        rc = check_launch("sum of overlapping tiles");
-        if (rc != ZNN_OK) return rc;
+    TileProduct P = {};
+    P.A = What; P.am = 16; P.ak = g.f * 16; P.blkA = (long)g.f * g.fo * 16;
+    P.B = V; P.bk = L.tiles * 16; P.bn = 16; P.blkB = (long)g.fo * L.tiles * 16;
+    P.C = result; P.cm = L.tiles * 16; P.cn = 16; P.blkC = (long)g.f * L.tiles * 16;
+    P.M = g.f; P.N = L.tiles; P.K = g.fo; P.blocks = L.blocks; P.splits = 1;
+    rc = product("spectral products backward (tiles)", true, P, s);
+    if (rc != ZNN_OK) return rc;
+    TileGeom G = base_geom(L);
+    for (int d = 0; d < 3; ++d) {
+        G.T[d] = 1; G.hop[d] = 0; G.o[d] = 0; G.sp[d] = 1;
+        G.n[d] = G.w[d] = one ? n[d] : L.M[d];
     }
-    return ZNN_OK;
+    rc = inverse_tiles("inverse fft of gradient tiles", G, (long)g.f * L.tiles, result, one ? gin : tiles, inv_volume(L), 1, 0, s);
+    if (rc != ZNN_OK || one) return rc;
+    TileAdd A = {};
+    A.src = tiles; A.dst = gin;
+    for (int d = 0; d < 3; ++d) {
+        A.M[d] = L.M[d]; A.T[d] = L.T[d]; A.hop[d] = L.B[d]; A.n[d] = n[d];
+        A.fhop[d] = make_fastdiv((unsigned)L.B[d]);
+    }
+    A.xy = g.ny * g.nx;
+    A.fnx = make_fastdiv((unsigned)g.nx);
+    bool two = true;
+    for (int d = 0; d < 3; ++d) two = two && L.M[d] <= 2 * L.B[d];
+    // z values per workgroup: few enough for four workgroups per compute unit
+    A.zs = two ? (int)std::max(1L, std::min(16L, (long)((A.xy + 255) / 256) * g.f * g.nz / 1024)) : 1;
+    const dim3 grid((unsigned)((A.xy + 255) / 256), (unsigned)((g.nz + A.zs - 1) / A.zs), (unsigned)g.f);
+    if (two) ZNN_LAUNCH("sum of overlapping tiles", s, k_tile_add2, grid, dim3(256), 0, A);
+    else     ZNN_LAUNCH("sum of overlapping tiles", s, k_tile_add, grid, dim3(256), 0, A);
+    return check_launch("sum of overlapping tiles");
 }
 
 int tile_wgrad_from_spectra(const Geom& g, const Tiling& L, const float2* U, const float2* V, float* gw, void* scratch,
