@@ -22,7 +22,9 @@ class Net:
     ``mode`` is "direct", "fft", "auto" (cached autotuner choice or cost model), a list with
     one entry per layer, or "tuned": every convolutional layer is timed as a whole round in
     the three strategies direct / FFT / FFT with memoized spectra (Section 4) and takes the
-    fastest one whose buffers fit ``memory_budget`` bytes (per layer; None = no limit).
+    fastest one whose buffers fit ``memory_budget`` bytes (per layer; None = no limit).  "fft_memo"
+    (in a list) attaches memo buffers to the layer's plan, and rounds go layer by layer to leave the
+    spectra there; rounds of tuned nets are programs, which memoize in their own memory.
     """
 
     def __init__(self, layers, in_shape, params, mode="auto", device="cuda:0", memory_budget=None):
@@ -47,10 +49,11 @@ class Net:
                 else:
                     spare = None
                 plan = znn.Plan(spec[1], spec[2], self.shapes[l][1:], spec[3], "fft" if m == "fft_memo" else m, sp)
-                if m == "fft_memo":
+                if m == "fft_memo" and l not in self.tuning:
                     plan.enable_memo(device)
                 elif spare is not None:         # the budget holds for rounds as one program as well
-                    plan.set_round_memory(spare)
+                    # which do the memoizing of a tuned net: its plans get no buffers beside theirs
+                    plan.set_round_memory(spare + (plan.spectra_bytes() + plan.memo_bytes() if m == "fft_memo" else 0))
                 self.strategy[l] = m
                 self.plans.append(plan)
             else:
@@ -63,6 +66,10 @@ class Net:
         program a plan stands for one layer, where the caller may have set one for several of a shape."""
         plans = [p for p in self.plans if p is not None]
         return any(p._memo is not None for p in plans) or len({id(p) for p in plans}) < len(plans)
+
+    def _memoized(self, l):
+        """Whether the calls of layer l, one by one, leave their spectra in its plan."""
+        return self.strategy[l] == "fft_memo" and self.plans[l]._memo is not None
 
     def modes(self):
         return [None if p is None else p.mode for p in self.plans]
@@ -158,7 +165,7 @@ class Net:
         acts, aux = [x], [None] * len(self.layers)
         for l, spec in enumerate(self.layers):
             a = acts[-1]
-            if spec[0] == "conv" and self.strategy[l] == "fft_memo":
+            if spec[0] == "conv" and self._memoized(l):
                 self.plans[l].prepare_kernels(self.params[l]["w"])      # once per round: w changes every update
                 y = self.plans[l].fwd(a, None)
             elif spec[0] == "conv":
@@ -180,7 +187,7 @@ class Net:
             spec = self.layers[l]
             if record is not None:
                 record.append((l, g))
-            if spec[0] == "conv" and self.strategy[l] == "fft_memo" and l > 0:
+            if spec[0] == "conv" and self._memoized(l) and l > 0:
                 # backward first: it leaves the spectra of g next to those of the forward input
                 g = self.plans[l].bwd(g, None)
                 grads[l] = {"w": self.plans[l].wgrad_memo(device=self.device)}

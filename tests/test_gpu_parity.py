@@ -645,7 +645,7 @@ def test_fft_layers_on_overlapping_tiles_match_the_oracle(f, fo, n, k, s):
     p.close()
 
 
-def test_rounds_of_a_tuned_net_keep_to_the_memory_budget():
+def test_rounds_of_a_tuned_net_keep_to_the_memory_budget(monkeypatch):
     """A budget that memoization exceeds holds for the rounds too, and they match the calls per layer; layers with
     memoized spectra leave them in their plans."""
     from paper_1510_06706_amd import net as znet
@@ -671,6 +671,21 @@ def test_rounds_of_a_tuned_net_keep_to_the_memory_budget():
         assert rel_err(host(acts[-1]), host(r_acts[-1])) <= 1e-6
         for l in (0, 2):
             assert rel_err(host(grads[l]["w"]), host(r_grads[l]["w"])) <= 2e-5
+    # where the tuner picks memoization the rounds memoize within the budget, in memory of their own
+    monkeypatch.setattr(znn, "autotune_round", lambda f, fo, n, *a: ("fft_memo", {}, sizes[0 if n[1] == in_shape[2] else 1]))
+    budget = max(b["fft_memo"] for b in sizes)
+    net, ref = znet.Net(layers, in_shape, params, "tuned", memory_budget=budget), znet.Net(layers, in_shape, params, "fft")
+    p = net.plans[2]
+    assert net.strategy[2] == "fft_memo" and p._memo is None
+    acts, _, _, grads = net.train_round(dev(x), dev(target), 0.0)
+    r_acts, _, _, r_grads = ref.train_round(dev(x), dev(target), 0.0, record=[])
+    assert p.spectra_bytes() + p.memo_bytes() <= net._program("square")[0].scratch_bytes <= 2 * budget + 4096
+    acts2, aux2 = net.forward(dev(x))                   # and pass by pass
+    grads2 = net.backward(acts2, aux2, znn.loss_grad(acts2[-1], dev(target)))
+    for a, g in ((acts, grads), (acts2, grads2)):
+        assert rel_err(host(a[-1]), host(r_acts[-1])) <= 1e-6
+        for l in (0, 2):
+            assert rel_err(host(g[l]["w"]), host(r_grads[l]["w"])) <= 2e-5
     memo = znet.Net(layers, in_shape, params, "fft_memo")
     grads = memo.train_round(dev(x), dev(target), 0.05)[3]
     assert np.array_equal(host(memo.plans[2].wgrad_memo()), host(grads[2]["w"]))
