@@ -7,10 +7,11 @@ with the method the per-layer autotuner picks for it (Section 4): for the FFT me
 kernel transforms (once per step: the update changes the kernels), the forward and the backward
 pass streaming the resident kernel spectra, and the kernel gradient from the node spectra the two
 passes memoized; for the direct method the three passes.  `value` = f' n'^3 / t_step output voxels
-per second.  The same JSON line carries, under `configs`, every pass of every configuration in both
-methods with the roofline of each of its steps (configs 1, 2, 4, 5; config 5 also with the kernel
-spectra kept in full, 52 GB; config 3 as whole training rounds; the max-filter pair), the roofline
-of the kernel that dominates the headline step, and the CPU oracle timed on a sample of config 5.
+per second.  The JSON line also carries the roofline of the kernel that dominates the headline step
+and the CPU oracle timed on a sample of config 5.  Every pass of every configuration in both methods
+(configs 1, 2, 4, 5; config 5 also with the kernel spectra kept in full, 52 GB; config 3 as whole
+training rounds; the max-filter pair) goes to stderr, a line each, and with `--rows FILE` to a JSON
+file, with the roofline of each of its steps (all of it on the one line would make that longer than 12 KB).
 """
 import argparse
 import json
@@ -219,6 +220,7 @@ def main():
     ap.add_argument("--warmup", type=int, default=5)
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--headline-only", action="store_true", help="skip the per-configuration table")
+    ap.add_argument("--rows", metavar="FILE", default=None, help="write the per-configuration table to this JSON file")
     ap.add_argument("--probe", choices=["c5-fft", "c5-fft-full", "c2", "c4", "c2-direct"], default=None,
                     help="for rocprofv3 counter runs: run the named passes a few times, then a plain 1 GiB "
                          "device copy whose known size calibrates the byte counters, and exit")
@@ -339,7 +341,6 @@ def main():
         "effective_tflops": 3 * 2.0 * cfg.macs / (ms_per_step * 1e-3) / 1e12,
         "per_mode": per_mode,
         "roofline": roof,
-        "kernels": kernels,
     }
     plan.close()
     if not args.no_cpu_baseline:
@@ -357,13 +358,15 @@ def main():
         rows += config3_rows(timer)
         rows += layer_rows(timer, synth.CONFIG4, "C4", variants + [("fft", "full", True, True)])[0]
         rows += c5_rows
-        result["configs"] = rows
-        result["configs_note"] = ("per pass: ms = mean of timed_reps launches after warm-up (HIP events on the launch stream; "
-                                  "slow passes are capped at about 1.5 s of timed work), effective_tflops = 2 f f' n'^3 k^3 / t "
-                                  "in either method; bound/achieved/frac are those of dominant_step, `steps` prices every step of "
-                                  "the pass from the library's per-launch events; fft rows: kernel_spectra = the transforms of all "
-                                  "kernels (once per round), wgrad_memo = kernel gradient from the node spectra forward and "
-                                  "backward left behind, wgrad = the same with its own node transforms")
+        if args.rows:
+            with open(args.rows, "w") as fh:
+                json.dump({"note": "per pass: ms = mean of timed_reps launches after warm-up (HIP events on the launch stream; "
+                                   "slow passes are capped at about 1.5 s of timed work), effective_tflops = 2 f f' n'^3 k^3 / t "
+                                   "in either method; bound/achieved/frac are those of dominant_step, `steps` prices every step of "
+                                   "the pass from the library's per-launch events; fft rows: kernel_spectra = the transforms of all "
+                                   "kernels (once per round), wgrad_memo = kernel gradient from the node spectra forward and "
+                                   "backward left behind, wgrad = the same with its own node transforms",
+                           "kernels": kernels, "configs": rows}, fh, indent=1)
     print(json.dumps(result))
 
 
