@@ -25,7 +25,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-TRAFFIC_PROFILE = "profiles/config5_hbm_traffic_pmc.txt"
+# of the headline layer on tiles and on whole volumes
+TRAFFIC_PROFILES = {True: "profiles/config5_tiles_hbm_traffic_pmc.txt", False: "profiles/config5_hbm_traffic_pmc.txt"}
 
 
 def log(msg):
@@ -221,7 +222,8 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--headline-only", action="store_true", help="skip the per-configuration table")
     ap.add_argument("--rows", metavar="FILE", default=None, help="write the per-configuration table to this JSON file")
-    ap.add_argument("--probe", choices=["c5-fft", "c5-fft-full", "c2", "c4", "c2-direct"], default=None,
+    ap.add_argument("--probe", default=None,
+                    choices=["c5-fft", "c5-fft-folded", "c5-fft-full", "c2", "c2-folded", "c2-direct", "c4", "c4-folded"],
                     help="for rocprofv3 counter runs: run the named passes a few times, then a plain 1 GiB "
                          "device copy whose known size calibrates the byte counters, and exit")
     args = ap.parse_args()
@@ -307,9 +309,10 @@ def main():
     roof = {"kernel": top["kernel"], "ms": top["ms_per_launch"], "launches_per_step": top["launches_per_step"]}
     roof.update(rl.price(bound, work, top["ms_per_launch"]))
     roof["algorithmic_work_per_launch"] = work
-    traffic = rl.measured_traffic(TRAFFIC_PROFILE)
+    profile = TRAFFIC_PROFILES[tiles is not None]
+    traffic = rl.measured_traffic(profile)
     roof["traffic"] = traffic.get(top["kernel"])
-    roof["traffic_source"] = (TRAFFIC_PROFILE + " (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of an earlier run, "
+    roof["traffic_source"] = (profile + " (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of an earlier run, "
                               "scaled by a plain copy; not measured by this run)") if roof["traffic"] else None
 
     per_mode = {}
@@ -376,16 +379,16 @@ def probe(which):
     from paper_1510_06706_amd import binding as znn
     from paper_1510_06706_amd import synth
     dev = torch.device("cuda:0")
-    cfg = {"c5-fft": synth.CONFIG5, "c5-fft-full": synth.CONFIG5, "c2": synth.CONFIG2, "c2-direct": synth.CONFIG2,
-           "c4": synth.CONFIG4}[which]
+    cfg = {"c2": synth.CONFIG2, "c4": synth.CONFIG4, "c5": synth.CONFIG5}[which[:2]]
+    layout = which.rsplit("-", 1)[-1]
     inp, w, gout = synth.layer_tensors(cfg)
     d_in, d_w, d_g = (torch.from_numpy(a).to(dev) for a in (inp, w, gout))
     modes = ["fft"] if which.startswith("c5") else ["direct"] if which == "c2-direct" else ["direct", "fft"]
     for mode in modes:
         p = znn.Plan(cfg.fan_in, cfg.fan_out, cfg.image, cfg.kernel, mode)
         if mode == "fft":
-            if which == "c5-fft-full":
-                p.set_spectra_layout("full")
+            if layout in ("folded", "full"):
+                p.set_spectra_layout(layout)
             p.enable_memo(dev)
         for _ in range(2):
             if mode == "fft":

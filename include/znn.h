@@ -334,8 +334,8 @@ int  znn_autotune_round(const znn_conv_desc* desc, uint64_t memory_budget, void*
  * on the buffers and streams given then: streams[0] is the calling stream, on which everything before the
  * call is over when the first operation starts and which has waited for the last one when work that follows on it starts;
  * operations on other streams wait for each other exactly where one uses what the other writes (events that the
- * program owns).  Nothing synchronises with the host, nothing is allocated, and a run may be captured
- * into a HIP graph.  The operations give what the single entry points give, except that
+ * program owns).  Nothing synchronises with the host and nothing is allocated; a run on one stream may be captured
+ * into a HIP graph (on several streams this is not tested).  The operations give what the single entry points give, except that
  *   - an operation may also apply what follows its result (`fn` with the buffers for it, see below),
  *   - the kernel transforms and, within a bound on memory, the node spectra of a layer on the FFT method are computed
  *     once per run and shared by its passes (Section 4),

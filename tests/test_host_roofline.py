@@ -62,3 +62,6 @@ def test_committed_traffic_profile_parses():
     assert t and all(v > 0 for v in t.values())
     assert any(k.startswith("spectral mac forward") for k in t)
     assert rl.measured_traffic("profiles/no_such_file.txt") == {}
+    tiles = rl.measured_traffic("profiles/config5_tiles_hbm_traffic_pmc.txt")
+    assert len(tiles) == 10 and all(v > 0 for v in tiles.values())
+    assert "spectral products of the kernel gradient (tiles)" in tiles
