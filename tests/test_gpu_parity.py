@@ -645,6 +645,29 @@ def test_fft_layers_on_overlapping_tiles_match_the_oracle(f, fo, n, k, s):
     p.close()
 
 
+@pytest.mark.parametrize("f,fo,n,k,tiled", [
+    (2, 3, (40, 1, 30), (3, 1, 3), False),      # several planes of one row: no tile length fits, whole volumes
+    (16, 16, (40, 1, 40), (3, 1, 3), False),
+    (5, 4, (33, 1, 1), (3, 1, 1), False),
+    (6, 7, (1, 1, 90), (1, 1, 5), True),        # one row
+    (4, 5, (1, 60, 1), (1, 7, 1), True),        # one column
+    (3, 3, (25, 40, 1), (2, 3, 1), True),       # rows of one voxel
+    (9, 4, (20, 2, 31), (3, 2, 4), True),       # results of one row per plane
+    (5, 6, (17, 3, 29), (2, 1, 4), True),
+])
+def test_fft_layers_of_thin_volumes_match_the_oracle(f, fo, n, k, tiled):
+    print("case", f, fo, n, k, flush=True)
+    cfg = synth.LayerShape("t", f, fo, n, k, 1.0 / np.sqrt(f * np.prod(k)), 950 + f)
+    inp, w, gout = synth.layer_tensors(cfg)
+    p = znn.Plan(f, fo, n, k, "fft")
+    assert (p.tiles is not None) == tiled
+    d_in, d_w, d_g = dev(inp), dev(w), dev(gout)
+    assert rel_err(host(p.fwd(d_in, d_w)), oracle.conv3d_fwd(inp, w)) <= 1e-5
+    assert rel_err(host(p.bwd(d_g, d_w)), oracle.conv3d_bwd(gout, w, n)) <= 1e-5
+    assert rel_err(host(p.wgrad(d_in, d_g)), oracle.conv3d_wgrad(inp, gout)) <= 1e-5
+    p.close()
+
+
 def test_rounds_of_a_tuned_net_keep_to_the_memory_budget(monkeypatch):
     """A budget that memoization exceeds holds for the rounds too, and they match the calls per layer; layers with
     memoized spectra leave them in their plans."""
