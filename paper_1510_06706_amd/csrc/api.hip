@@ -230,7 +230,7 @@ static int run_fft_fwd(const Geom& g, const FftWay& y, const float* in, const fl
                        void* ws, float2* memo_in, hipStream_t s)
 {
     if (!y.tile.on) return fft_fwd(g, y.fold, in, w, resident, out, ws, memo_in, s);
-    return tile_fwd(g, y.tile, in, w, resident, out, ws, memo_in, s);
+    return tile_fwd(g, y.tile, in, w, resident, out, ws, tile_workspace_bytes(g, y.tile, ZNN_PASS_FWD, resident != nullptr), memo_in, s);
 }
 
 static int run_fft_bwd(const Geom& g, const FftWay& y, const float* gout, const float* w, const float2* resident, float* gin,
@@ -277,6 +277,21 @@ int plan_pass(const znn_plan* p, int pass, const float* a, const float* b, float
     if (pass == ZNN_PASS_FWD) return run_fft_fwd(g, way_of(p), a, b, resident, result, ws, memo, s);
     if (pass == ZNN_PASS_WGRAD) return run_fft_wgrad(g, way_of(p), a, b, result, ws, s);
     return run_fft_bwd(g, way_of(p), a, b, resident, result, ws, memo ? memo_gradients(g, way_of(p), memo) : nullptr, s);
+}
+
+size_t plan_forward_least(const znn_plan* p)
+{
+    return p->tile.on ? fft_workspace(p->g, p->fold, ZNN_PASS_FWD, p->resident != nullptr).total
+                      : plan_pass_bytes(p, ZNN_PASS_FWD, p->resident != nullptr);
+}
+
+int plan_forward_within(znn_plan* p, const float* in, const float* w, float* out, void* ws, size_t bytes, hipStream_t s)
+{
+    if (!p->tile.on) return znn_conv3d_fwd(p, in, w, out, ws, bytes, s);
+    if (!w && !p->resident) return fail(ZNN_EINVAL, "kernel pointer is NULL");
+    const int rc = tile_fwd(p->g, p->tile, in, w, p->resident, out, ws, bytes, p->memo, s);
+    if (p->memo) p->memo_has_in = rc == ZNN_OK;
+    return rc;
 }
 
 int plan_wgrad_memo(const znn_plan* p, float2* memo, float* gw, void* ws, hipStream_t s)

@@ -43,6 +43,7 @@ struct TileGeom {
     int vw, clip;               // samples per memory access along x: 4, 2 or 1; tiles reach beyond the map
     int rows_per_step, step[3]; // rows a workgroup's threads cover at a time, and that as (entries, z, y)
     FastDiv fw[3], fwx, fMxh, fcol;     // divisions by w, w[2] / vw, Mxh, My * Mxh
+    int first, count;           // tiles of a map in this launch: numbers first .. first + count - 1 (finish_geom: 0 = all)
 };
 struct TileFwd { const float* src; float2* dst; TileGeom G; };
 struct TileInv { const float2* src; float* dst; TileGeom G; float scale; int splits; long split_stride; };
@@ -55,9 +56,8 @@ __device__ __forceinline__ EntryInfo entry_info(const TileGeom& G, int e)
     EntryInfo I;
     I.ok = e < G.entries;
     if (!I.ok) { I.base = 0; I.v[0] = I.v[1] = I.v[2] = 0; return I; }
-    const int T = G.T[0] * G.T[1] * G.T[2];
-    const int map = e / T;
-    int t = e - map * T;
+    const int map = e / G.count;
+    int t = G.first + e - map * G.count;
     const int tz = t / (G.T[1] * G.T[2]);
     t -= tz * G.T[1] * G.T[2];
     const int ty = t / G.T[2], tx = t - ty * G.T[2];
@@ -748,6 +748,7 @@ unsigned mask_of(int o, int w, int sp)
 void finish_geom(TileGeom& G, long entries, int* threads, size_t* lds)
 {
     G.entries = (int)entries;
+    if (!G.count) G.count = G.T[0] * G.T[1] * G.T[2];
     const size_t one = sizeof(float2) * (size_t)G.w[0] * G.M[1] * G.Mxh;     // the planes along z that hold samples
     const int cols = G.M[0] > 1 ? G.M[1] * G.Mxh : G.Mxh;
     int nb = 1;
@@ -956,12 +957,13 @@ int tile_kernel_spectra(const Geom& g, const Tiling& L, const float* w, float2* 
     return forward_tiles("fft of kernels (tiles)", G, (long)g.f * g.fo, w, What, s);
 }
 
-static int tile_images(const Geom& g, const Tiling& L, const float* in, float2* U, hipStream_t s)
+static int tile_images(const Geom& g, const Tiling& L, const float* in, float2* U, int first, int count, hipStream_t s)
 {
     TileGeom G = base_geom(L);
+    G.first = first; G.count = count;
     const int n[3] = {g.nz, g.ny, g.nx};
     for (int d = 0; d < 3; ++d) { G.T[d] = L.T[d]; G.hop[d] = L.B[d]; G.n[d] = n[d]; G.w[d] = L.M[d]; G.o[d] = 0; G.sp[d] = 1; }
-    return forward_tiles("fft of image tiles", G, (long)g.f * L.tiles, in, U, s);
+    return forward_tiles("fft of image tiles", G, (long)g.f * count, in, U, s);
 }
 
 static int tile_gradients(const Geom& g, const Tiling& L, const float* gout, float2* V, hipStream_t s)
@@ -976,34 +978,50 @@ static int tile_gradients(const Geom& g, const Tiling& L, const float* gout, flo
 
 static float inv_volume(const Tiling& L) { return (float)(1.0 / ((double)L.M[0] * L.M[1] * L.M[2])); }
 
+// The tiles come in as few equal groups as the workspace allows: one in tile_workspace_bytes, more in the built-in array of
+// znn_conv3d_fwd_static.  Tiles of the forward pass do not meet, and a product adds in the same order whatever the group,
+// so the results are the same bits.
 int tile_fwd(const Geom& g, const Tiling& L, const float* in, const float* w, const float2* resident, float* out,
-             void* ws, float2* memo_in, hipStream_t s)
+             void* ws, size_t ws_bytes, float2* memo_in, hipStream_t s)
 {
-    char* p = (char*)ws;
-    float2* U = memo_in;
-    if (!U) { U = (float2*)p; p += tile_node_bytes(g, L, g.f); }
-    const float2* What = resident;
-    int rc = tile_images(g, L, in, U, s);
-    if (rc != ZNN_OK) return rc;
-    if (!What) {
-        What = (const float2*)p;
-        rc = tile_kernel_spectra(g, L, w, (float2*)p, s);
-        if (rc != ZNN_OK) return rc;
-        p += tile_kernel_bytes(g, L);
+    const size_t kernels = resident ? 0 : tile_kernel_bytes(g, L);
+    auto images = [&](int c) { return memo_in ? 0 : spectra_of(L, (long)g.f * c); };
+    int count = 0;
+    for (int n = 1; n <= L.tiles && !count; ++n) {
+        const int c = (L.tiles + n - 1) / n;
+        if (images(c) + kernels + spectra_of(L, (long)g.fo * c) <= ws_bytes) count = c;
     }
-    TileProduct P = {};
-    P.A = What; P.am = g.f * 16; P.ak = 16; P.blkA = (long)g.f * g.fo * 16;
-    P.B = U; P.bk = L.tiles * 16; P.bn = 16; P.blkB = (long)g.f * L.tiles * 16;
-    P.C = (float2*)p; P.cm = L.tiles * 16; P.cn = 16; P.blkC = (long)g.fo * L.tiles * 16;
-    P.M = g.fo; P.N = L.tiles; P.K = g.f; P.blocks = L.blocks; P.splits = 1;
-    rc = product("spectral products forward (tiles)", false, P, s);
-    if (rc != ZNN_OK) return rc;
+    if (!count) return fail(ZNN_EWORKSPACE, "workspace too small for the spectra of the kernels and of one tile");
+    float2* const U = memo_in ? memo_in : (float2*)ws;
+    float2* const own = (float2*)((char*)ws + images(count));
+    float2* const result = (float2*)((char*)own + kernels);
+    const float2* const What = resident ? resident : own;
     TileGeom G = base_geom(L);
     const int o[3] = {g.oz, g.oy, g.ox};
     for (int d = 0; d < 3; ++d) {
         G.T[d] = L.T[d]; G.hop[d] = L.B[d]; G.n[d] = o[d]; G.w[d] = L.B[d]; G.o[d] = L.M[d] - L.B[d]; G.sp[d] = 1;
     }
-    return inverse_tiles("inverse fft of image tiles", G, (long)g.fo * L.tiles, (const float2*)p, out, inv_volume(L), 1, 0, s);
+    for (int first = 0; first < L.tiles; first += count) {
+        const int c = std::min(count, L.tiles - first);
+        int rc = ZNN_OK;
+        // a memo buffer takes the spectra of all tiles
+        if (!memo_in) rc = tile_images(g, L, in, U, first, c, s);
+        else if (first == 0) rc = tile_images(g, L, in, U, 0, L.tiles, s);
+        if (rc == ZNN_OK && !resident && first == 0) rc = tile_kernel_spectra(g, L, w, own, s);
+        if (rc != ZNN_OK) return rc;
+        const int tiles = memo_in ? L.tiles : c;                // of a map of U
+        TileProduct P = {};
+        P.A = What; P.am = g.f * 16; P.ak = 16; P.blkA = (long)g.f * g.fo * 16;
+        P.B = U + (memo_in ? (long)first * 16 : 0); P.bk = tiles * 16; P.bn = 16; P.blkB = (long)g.f * tiles * 16;
+        P.C = result; P.cm = c * 16; P.cn = 16; P.blkC = (long)g.fo * c * 16;
+        P.M = g.fo; P.N = c; P.K = g.f; P.blocks = L.blocks; P.splits = 1;
+        rc = product("spectral products forward (tiles)", false, P, s);
+        G.first = first; G.count = c;
+        if (rc == ZNN_OK)
+            rc = inverse_tiles("inverse fft of image tiles", G, (long)g.fo * c, result, out, inv_volume(L), 1, 0, s);
+        if (rc != ZNN_OK) return rc;
+    }
+    return ZNN_OK;
 }
 
 int tile_bwd(const Geom& g, const Tiling& L, const float* gout, const float* w, const float2* resident, float* gin,
@@ -1083,7 +1101,7 @@ int tile_wgrad(const Geom& g, const Tiling& L, const float* in, const float* gou
     char* p = (char*)ws;
     float2* U = (float2*)p; p += tile_node_bytes(g, L, g.f);
     float2* V = (float2*)p; p += tile_node_bytes(g, L, g.fo);
-    int rc = tile_images(g, L, in, U, s);
+    int rc = tile_images(g, L, in, U, 0, L.tiles, s);
     if (rc == ZNN_OK) rc = tile_gradients(g, L, gout, V, s);
     if (rc != ZNN_OK) return rc;
     return tile_wgrad_from_spectra(g, L, U, V, gw, p, s);

@@ -46,13 +46,11 @@ int scratch_of_current_device(void** out)
 extern "C" int znn_conv3d_fwd_static(znn_plan* plan, const float* in, const float* w, float* out, void* stream)
 {
     if (!plan || !in || !out) return znn::fail(ZNN_EINVAL, "NULL argument");
-    size_t need = 0;
-    int rc = znn_plan_workspace_bytes(plan, ZNN_PASS_FWD, &need);
-    if (rc != ZNN_OK) return rc;
+    const size_t need = znn::plan_forward_least(plan);
     if (need > kScratchBytes)
         return znn::fail(ZNN_EWORKSPACE, "this layer's forward pass needs %zu bytes of scratch, the built-in array holds %zu; "
                                          "use znn_conv3d_fwd with a workspace", need, kScratchBytes);
     void* ptr = nullptr;
-    if ((rc = scratch_of_current_device(&ptr)) != ZNN_OK) return rc;
-    return znn_conv3d_fwd(plan, in, w, out, ptr, kScratchBytes, stream);
+    const int rc = scratch_of_current_device(&ptr);
+    return rc != ZNN_OK ? rc : znn::plan_forward_within(plan, in, w, out, ptr, kScratchBytes, (hipStream_t)stream);
 }

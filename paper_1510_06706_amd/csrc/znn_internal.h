@@ -273,6 +273,9 @@ int plan_kernel_spectra(const znn_plan* p, const float* w, float2* What, hipStre
 int plan_pass(const znn_plan* p, int pass, const float* a, const float* b, float* result, const float2* resident, void* ws,
               float2* memo, hipStream_t s);
 int plan_wgrad_memo(const znn_plan* p, float2* memo, float* gw, void* ws, hipStream_t s);
+// the forward pass in less than its workspace: on tiles in as little as it would take on whole volumes
+size_t plan_forward_least(const znn_plan* p);
+int plan_forward_within(znn_plan* p, const float* in, const float* w, float* out, void* ws, size_t bytes, hipStream_t s);
 
 }  // namespace znn
 

@@ -229,3 +229,21 @@ def test_spectra_layout_is_a_property_of_the_plan():
     d.close()
     assert znn.lib().znn_plan_set_spectra_layout(None, 1) == znn.ZNN_EINVAL
     assert znn.lib().znn_plan_spectra_layout(None, None) == znn.ZNN_EINVAL
+
+
+def test_static_forward_takes_layers_by_what_they_need_on_whole_volumes():
+    """Tiles may need more scratch than the built-in array for a layer that fits it on whole volumes; what did not fit is refused.
+    Without a GPU a call that is not refused fails when it looks for the array."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the call would run")
+    fake = ctypes.c_void_p(0x1000)
+    for f, fo, n, k, fits in ((1, 15, (77, 47, 81), (3, 3, 3), True), (15, 42, (69, 22, 58), (1, 5, 5), True),
+                              (10, 1, (80, 80, 80), (3, 3, 3), True), (40, 40, (64, 64, 64), (5, 5, 5), False)):
+        p = znn.Plan(f, fo, n, k, "fft")
+        assert p.tiles is not None and p.workspace_bytes(znn.ZNN_PASS_FWD) > znn.STATIC_SCRATCH_BYTES
+        rc = znn.lib().znn_conv3d_fwd_static(p._h, fake, fake, fake, ctypes.c_void_p(0))
+        assert rc == (znn.ZNN_EHIP if fits else znn.ZNN_EWORKSPACE), znn.last_error()
+        p.set_spectra_layout(p.spectra_layout)
+        assert (p.workspace_bytes(znn.ZNN_PASS_FWD) <= znn.STATIC_SCRATCH_BYTES) == fits
+        p.close()

@@ -46,6 +46,38 @@ def test_forward_without_allocation_matches_forward_with_workspace(mode):
         p.close()
 
 
+# layers whose tiles take more than the array where whole volumes would not: kernels transformed by the call, and resident
+TILES = [(1, 15, (77, 47, 81), (3, 3, 3), False), (15, 42, (69, 22, 58), (1, 5, 5), False), (10, 1, (80, 80, 80), (3, 3, 3), False),
+         (75, 4, (39, 39, 39), (6, 6, 6), True), (105, 9, (1, 286, 240), (1, 3, 3), True), (24, 25, (54, 54, 54), (5, 5, 5), True)]
+
+
+@pytest.mark.parametrize("f,fo,n,k,resident", TILES)
+def test_forward_without_allocation_takes_the_tiles_of_a_layer_in_groups(f, fo, n, k, resident):
+    import torch
+    print("case", f, fo, n, k, resident, flush=True)
+    dev = torch.device("cuda:0")
+    inp, w, gout = synth.layer_tensors(synth.LayerShape("noalloc", f, fo, n, k, 1.0 / np.sqrt(f * np.prod(k)), 710 + f))
+    d_in, d_w, d_g = (torch.from_numpy(a).to(dev) for a in (inp, w, gout))
+    p = znn.Plan(f, fo, n, k, "fft")
+    assert p.tiles is not None
+    if resident:
+        p.prepare_kernels(d_w)
+    w_ = None if resident else d_w
+    assert p.workspace_bytes(znn.ZNN_PASS_FWD) > znn.STATIC_SCRATCH_BYTES
+    want = p.fwd(d_in, w_)
+    got = torch.full_like(want, float("nan"))
+    p.fwd_static(d_in, w_, got)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    # node spectra for a memoized kernel gradient are left whole
+    gw = p.wgrad(d_in, d_g)
+    p.enable_memo()
+    p.bwd(d_g, w_)
+    p.fwd_static(d_in, w_, got.fill_(float("nan")))
+    assert torch.equal(got, want) and torch.equal(p.wgrad_memo(), gw)
+    p.close()
+
+
 def test_forward_without_allocation_refuses_layers_beyond_the_array():
     import torch
     cfg = synth.CONFIG2
