@@ -79,6 +79,7 @@ const Tuning& tuning()
         v.conv_no_wl = flag("ZNN_CONV_NO_WL");
         v.conv_no_split = flag("ZNN_CONV_NO_SPLIT");
         v.conv_no_tail = flag("ZNN_CONV_NO_TAIL");
+        v.conv_no_parts = flag("ZNN_CONV_NO_PARTS");
         if (const char* e = getenv("ZNN_CONV_TILE"))
             if (sscanf(e, "%d,%d,%d,%d", &v.conv_tile[0], &v.conv_tile[1], &v.conv_tile[2], &v.conv_tile[3]) != 4)
                 v.conv_tile[0] = v.conv_tile[1] = v.conv_tile[2] = v.conv_tile[3] = 0;

@@ -7,6 +7,7 @@
 // reflected and the output gradient zero-extended by k-1 on every side
 // (Section 3.1), which the halo loader and the weight packer provide; no
 // separate kernel is needed.
+// Layers with more than four input-side maps take the kernel on split operands instead (direct_split.hip).
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -14,6 +15,8 @@
 #include <vector>
 
 #include "direct_mfma_tail_impl.h"
+#include "direct_split.h"
+#include "direct_split_impl.h"
 
 namespace znn {
 
@@ -34,6 +37,51 @@ constexpr int kMaxTaps = 4096;
 constexpr int kPackItems = 24;
 template <int N> struct PackArgs { PackItem item[N]; unsigned first[N]; int n; };
 
+// Weights for the split kernel: a thread makes the three parts of eight input maps' weights at one tap, [group][chunk][step]
+// [16-map tile][part][lane].  The leading part of a number that would round to infinity is cut instead, and an infinity or
+// NaN has no other parts, so that the parts always add up to the weight.
+__device__ __forceinline__ void pack_split(const PackItem& P, long t)
+{
+    const int taps = P.kz * P.ky * P.kx, steps = (taps + split::kTaps - 1) / split::kTaps;
+    const int lane = (int)(t & 63);
+    long r = t >> 6;
+    const int jt = (int)(r % P.NJ); r /= P.NJ;
+    const int s = (int)(r % steps); r /= steps;
+    const int ic = (int)(r % P.nchunk), jg = (int)(r / P.nchunk);
+    const int m = (jg * P.NJ + jt) * 16 + (lane & 15), tap = s * split::kTaps + (lane >> 4);
+    const int fM = P.backward ? P.f : P.fo, fK = P.backward ? P.fo : P.f;
+    float v[8];
+    split::uintx4 part[3];
+    bool odd = false;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int k = ic * split::kMaps + e;
+        v[e] = 0.f;
+        if (m < fM && k < fK && tap < taps)
+            v[e] = P.backward ? P.w[((long)k * P.f + m) * taps + (taps - 1 - tap)] : P.w[((long)m * P.f + k) * taps + tap];
+        odd = odd || !(fabsf(v[e]) < 3.38e38f);
+    }
+    if (!odd) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) part[p] = split::take_part8(v);
+    } else {
+        part[0] = part[1] = part[2] = split::uintx4{0u, 0u, 0u, 0u};
+        for (int e = 0; e < 8; ++e) {
+            float x = v[e];
+            for (int p = 0; p < 3; ++p) {
+                unsigned u = __builtin_bit_cast(unsigned, x);
+                if (x != x) u |= 0x400000u;                                                 // stays a NaN
+                u &= 0xffff0000u;
+                part[p][e >> 1] |= e & 1 ? u : u >> 16;
+                x = fabsf(x) <= 3.4028234e38f ? x - __builtin_bit_cast(float, u) : 0.f;
+            }
+        }
+    }
+    split::uintx4* out = reinterpret_cast<split::uintx4*>(P.wp) + (t >> 6) * 3 * 64 + lane;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) out[p * 64] = part[p];
+}
+
 template <int N>
 __global__ void __launch_bounds__(256) k_pack_weights(PackArgs<N> A)
 {
@@ -44,6 +92,7 @@ __global__ void __launch_bounds__(256) k_pack_weights(PackArgs<N> A)
     const int WT = P.NJ * 64 + (P.tail ? conv::kTailPacked : 0);
     const long t = (long)(blockIdx.x - A.first[q]) * 256 + threadIdx.x;
     if (t >= P.total) return;
+    if (P.split) { pack_split(P, t); return; }      // uniform
     int e, tap, ic, jg;
     auto place = [&](auto n) {
         e = (int)(n % (unsigned)WT); n /= (unsigned)WT;
@@ -294,8 +343,9 @@ TileChoice choose_for(const Geom& g, bool backward)
 // The tiled path takes every shape whose halo box fits LDS; otherwise the caller falls back.
 bool mfma_conv_supported(const Geom& g, bool backward)
 {
-    const TileChoice c = choose_for(g, backward);
     const long svol = backward ? g.ovol() : g.nvol();
+    if (svol < (1L << 28) && choose_split(g, backward).ok) return true;
+    const TileChoice c = choose_for(g, backward);
     // the halo loader addresses the chunk's four source maps with one 32-bit byte offset
     return c.ok && svol < (1L << 28);
 }
@@ -303,6 +353,7 @@ bool mfma_conv_supported(const Geom& g, bool backward)
 // Expected seconds of the pass: the search's clocks, the sum of the shares, weight packing.
 double mfma_conv_seconds(const Geom& g, bool backward)
 {
+    if (const SplitChoice p = choose_split(g, backward); p.ok) return p.cost / 1.9e9 + 2e-6;
     const TileChoice c = choose_for(g, backward);
     if (!c.ok) return 2.0 * g.f * g.fo * (double)g.ovol() * g.kvol() / 1e12;
     const double count = backward ? (double)g.f * g.nvol() : (double)g.fo * g.ovol();
@@ -311,6 +362,9 @@ double mfma_conv_seconds(const Geom& g, bool backward)
 
 size_t mfma_conv_workspace(const Geom& g, bool backward)
 {
+    if (const SplitChoice p = choose_split(g, backward); p.ok)
+        return split_packed_bytes(p) +
+               (p.splits > 1 ? align256((size_t)p.splits * (backward ? g.f * g.nvol() : g.fo * g.ovol()) * sizeof(float)) : 0);
     const TileChoice c = choose_for(g, backward);
     if (!c.ok) return 0;
     return packed_bytes(c, backward ? g.fo : g.f, (int)g.kvol()) +
@@ -322,6 +376,7 @@ size_t mfma_conv_workspace(const Geom& g, bool backward)
 int mfma_conv_packed(const Geom& g, bool backward, const float* src, const float* wp, float* dst, float* partial,
                      const Finish& finish, hipStream_t s)
 {
+    if (choose_split(g, backward).ok) return split_conv(g, backward, src, wp, dst, partial, finish, s);
     ConvTile P = {};
     P.src = src; P.dst = dst;
     P.kz = g.kz; P.ky = g.ky; P.kx = g.kx;
@@ -365,12 +420,18 @@ int mfma_conv_packed(const Geom& g, bool backward, const float* src, const float
 
 PackItem mfma_conv_pack_item(const Geom& g, bool backward, const float* w, float* wp)
 {
-    const TileChoice c = choose_for(g, backward);
     PackItem p = {};
     p.w = w; p.wp = wp;
     p.f = g.f; p.fo = g.fo;
     p.kz = g.kz; p.ky = g.ky; p.kx = g.kx;
     p.backward = backward ? 1 : 0;
+    if (const SplitChoice c = choose_split(g, backward); c.ok) {
+        p.split = 1;
+        p.NJ = c.NJ; p.nchunk = c.nchunk;
+        p.total = (long)c.jgroups * c.nchunk * c.steps * c.NJ * 64;
+        return p;
+    }
+    const TileChoice c = choose_for(g, backward);
     p.NJ = c.NJ; p.nchunk = ((backward ? g.fo : g.f) + 3) / 4;
     p.tail = c.tail ? 1 : 0;
     p.total = (long)c.jgroups * p.nchunk * g.kvol() * (c.NJ * 64 + (c.tail ? conv::kTailPacked : 0));
@@ -400,11 +461,16 @@ int mfma_pack_weights(const PackItem* items, int n, hipStream_t s)
 
 size_t mfma_conv_packed_bytes(const Geom& g, bool backward)
 {
+    if (const SplitChoice p = choose_split(g, backward); p.ok) return split_packed_bytes(p);
     const TileChoice c = choose_for(g, backward);
     return c.ok ? packed_bytes(c, backward ? g.fo : g.f, (int)g.kvol()) : 0;
 }
 
-int mfma_conv_splits(const Geom& g, bool backward) { return choose_for(g, backward).splits; }
+int mfma_conv_splits(const Geom& g, bool backward)
+{
+    const SplitChoice p = choose_split(g, backward);
+    return p.ok ? p.splits : choose_for(g, backward).splits;
+}
 
 int mfma_conv(const Geom& g, bool backward, const float* src, const float* w, float* dst, void* ws,
               hipStream_t s)

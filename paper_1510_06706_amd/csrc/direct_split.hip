@@ -1,0 +1,218 @@
+// Host side of the split direct kernel (direct_split_impl.h): search for the workgroup's box and launch.  Weights are packed
+// by k_pack_weights (direct_mfma.hip) together with those of other layers.
+#include <algorithm>
+#include <cstdio>
+#include <cstring>
+#include <mutex>
+#include <vector>
+
+#include "direct_split.h"
+#include "direct_split_impl.h"
+
+namespace znn {
+
+namespace {
+
+using split::SplitFn;
+using split::SplitTile;
+
+constexpr int kCUs = 256;
+constexpr size_t kLds = 160 * 1024;
+constexpr int kMaxTaps = 4096;
+
+// Instances: accumulators (NJ NV tiles) and two sets of weights (24 NJ registers) fit the 256 registers of two waves per SIMD.
+constexpr bool instance(int nj, int nv) { return nj >= 1 && nj <= 5 && nj * nv <= (nj <= 2 ? 16 : nj == 3 ? 18 : nj == 4 ? 12 : 10); }
+
+template <int NJ, int NV, int NW> SplitFn instance_of()
+{
+    if constexpr (instance(NJ, NV)) return split::k_conv_split<NJ, NV, NW>;
+    else return nullptr;
+}
+
+template <int NJ, int NW> SplitFn pick_nv(int nv)
+{
+    switch (nv) {
+        case 1: return instance_of<NJ, 1, NW>();
+        case 2: return instance_of<NJ, 2, NW>();
+        case 3: return instance_of<NJ, 3, NW>();
+        case 4: return instance_of<NJ, 4, NW>();
+        case 6: return instance_of<NJ, 6, NW>();
+        case 8: return instance_of<NJ, 8, NW>();
+    }
+    return nullptr;
+}
+
+template <int NW> SplitFn pick_nj(int nj, int nv)
+{
+    switch (nj) {
+        case 1: return pick_nv<1, NW>(nv);
+        case 2: return pick_nv<2, NW>(nv);
+        case 3: return pick_nv<3, NW>(nv);
+        case 4: return pick_nv<4, NW>(nv);
+        case 5: return pick_nv<5, NW>(nv);
+    }
+    return nullptr;
+}
+
+SplitFn pick(int nj, int nv, int nw) { return nw == 8 ? pick_nj<8>(nj, nv) : pick_nj<4>(nj, nv); }
+
+// One axis of a pass: source and result extents, taps, their spacing and the taps of zeros in front.
+struct Axis { int s, d, k, sp, p, phases, e; };     // e: longest sublattice of the result
+struct Pass { Axis a[3]; int fM, fK; };
+
+Pass pass_of(const Geom& g, bool backward)
+{
+    Pass P;
+    const int n[3] = {g.nz, g.ny, g.nx}, o[3] = {g.oz, g.oy, g.ox}, k[3] = {g.kz, g.ky, g.kx}, sp[3] = {g.spz, g.spy, g.spx};
+    for (int d = 0; d < 3; ++d) {
+        Axis& a = P.a[d];
+        a.s = backward ? o[d] : n[d];
+        a.d = backward ? n[d] : o[d];
+        a.k = k[d];
+        a.sp = k[d] > 1 ? sp[d] : 1;
+        a.p = backward ? k[d] - 1 : 0;
+        a.phases = std::min(a.sp, a.d);
+        a.e = (a.d + a.sp - 1) / a.sp;
+    }
+    P.fM = backward ? g.f : g.fo;
+    P.fK = backward ? g.fo : g.f;
+    return P;
+}
+
+// Expected clocks of the launch (and of the sum of its shares) for every box that fits, the least taken.
+SplitChoice search(const Pass& P)
+{
+    SplitChoice best = {};
+    const Axis &az = P.a[0], &ay = P.a[1], &ax = P.a[2];
+    const int taps = az.k * ay.k * ax.k;
+    if (taps > kMaxTaps) return best;
+    const int steps = (taps + split::kTaps - 1) / split::kTaps;
+    const int tiles = (P.fM + 15) / 16, nchunk = (P.fK + split::kMaps - 1) / split::kMaps;
+    const int jgroups = (tiles + 4) / 5, NJ = (tiles + jgroups - 1) / jgroups;
+    const int phases = az.phases * ay.phases * ax.phases;
+    const double count = (double)P.fM * az.d * ay.d * ax.d;
+    const int nvs[6] = {1, 2, 3, 4, 6, 8}, nws[2] = {4, 8};
+    const int (&pin)[4] = tuning().conv_tile;
+    for (int NW : nws)
+        for (int NV : nvs) {
+            if (!instance(NJ, NV) || (pin[0] && NV * NW != pin[0])) continue;
+            const int cap = 16 * NV * NW;
+            // clocks of a step of the workgroup: matrix cores, LDS reads (128 bytes a clock), weights from the vector cache (64)
+            const double step = 0.92 * std::max({NW / 4 * NJ * NV * 96.0, NW * NV * 24.0, NW * NJ * 48.0}) + 82.0 * NW / 4;
+            const int most = (NJ <= 2 && NJ * NV <= 8 ? 12 : 8) / NW;       // workgroups whose registers fit a compute unit
+            for (int Tx = 1; Tx <= ax.e && Tx <= cap; ++Tx)
+                for (int Ty = 1; Ty <= ay.e && Tx * Ty <= cap; ++Ty) {
+                    int Tz = std::min(cap / (Tx * Ty), az.e);
+                    if (pin[0]) {
+                        if (Tx != pin[3] || Ty != pin[2] || pin[1] * Ty * Tx > cap) continue;
+                        Tz = pin[1];
+                    }
+                    const int HZ = Tz + az.k - 1, HY = Ty + ay.k - 1, HX = Tx + ax.k - 1;
+                    const long hvol = (long)HZ * HY * HX;
+                    const size_t lds = (size_t)hvol * (split::kVoxelBytes + 4) + (size_t)(steps + 2) * split::kTaps * 4;
+                    if (lds > kLds) continue;
+                    const int fit = std::max(1, std::min(most, (int)(kLds / lds)));
+                    const int cz = (az.e + Tz - 1) / Tz, cy = (ay.e + Ty - 1) / Ty, cx = (ax.e + Tx - 1) / Tx;
+                    const long blocks = (long)cz * cy * cx * phases;
+                    // constants fitted to the times of 900 boxes on 22 layers (standard deviation 15 %)
+                    const double stage = 4.0 * hvol * (1.0 + 0.06 * (ax.sp - 1));
+                    const double fixed = 5200.0 + 11.5 * cap * NJ;
+                    for (int splits = 1, cps = nchunk; ; ) {
+                        const long groups = blocks * jgroups * splits;
+                        const long per_cu = (groups + kCUs - 1) / kCUs;
+                        // a unit with one wave per SIMD has nothing to overlap its waits with, one workgroup nothing for its stages
+                        const long both = std::min((long)fit, per_cu);
+                        const double alone = both * NW < 8 ? 1.38 : 1.0;
+                        double cost = per_cu * (fixed + cps * (steps * step * alone + stage * (both > 1 ? 0.46 : 1.0)));
+                        if (splits > 1) cost += 7000.0 + count * (splits + 1) * 4.0 / 3.0e12 * 2.1e9;
+                        cost -= 0.01 * Tx;
+                        if (!best.ok || cost < best.cost) {
+                            best.ok = true;
+                            best.NJ = NJ; best.jgroups = jgroups; best.NV = NV; best.NW = NW;
+                            best.T[0] = Tz; best.T[1] = Ty; best.T[2] = Tx;
+                            best.H[0] = HZ; best.H[1] = HY; best.H[2] = HX;
+                            best.c[0] = cz; best.c[1] = cy; best.c[2] = cx;
+                            best.phases = phases; best.steps = steps; best.nchunk = nchunk;
+                            best.cps = cps; best.splits = splits;
+                            best.lds = lds; best.cost = cost;
+                        }
+                        // the next smaller share of the chunks, while the chip is not full
+                        if (cps == 1 || groups >= 3 * kCUs || tuning().conv_no_split) break;
+                        do ++splits; while ((nchunk + splits - 1) / splits == cps);
+                        cps = (nchunk + splits - 1) / splits;
+                        splits = (nchunk + cps - 1) / cps;
+                    }
+                }
+        }
+    return best;
+}
+
+}  // namespace
+
+// The search walks thousands of boxes, and every call of a pass asks several times: remembered per shape.
+SplitChoice choose_split(const Geom& g, bool backward)
+{
+    struct Entry { int key[13]; SplitChoice choice; };
+    static std::mutex lock;
+    static std::vector<Entry> memo;
+    Entry e;
+    const int key[13] = {g.f, g.fo, g.nz, g.ny, g.nx, g.kz, g.ky, g.kx, g.spz, g.spy, g.spx, backward ? 1 : 0, 0};
+    memcpy(e.key, key, sizeof(key));
+    {
+        std::lock_guard<std::mutex> hold(lock);
+        for (const Entry& m : memo)
+            if (memcmp(m.key, key, sizeof(key)) == 0) return m.choice;
+    }
+    const Pass P = pass_of(g, backward);
+    e.choice = SplitChoice{};
+    // Chunks hold eight input maps: with four and less, half of the products and more would be padding, and the fp32 kernel
+    // (chunks of four) is the better one.
+    if (P.fK > 4 && !tuning().conv_no_parts) e.choice = search(P);
+    std::lock_guard<std::mutex> hold(lock);
+    if (memo.size() >= 256) memo.erase(memo.begin());
+    memo.push_back(e);
+    return e.choice;
+}
+
+// Packed weights; one step of padding behind them, which the kernel fetches ahead.
+size_t split_packed_bytes(const SplitChoice& c)
+{
+    return align256(((size_t)c.jgroups * c.nchunk * c.steps + 1) * c.NJ * 3 * 64 * 16);
+}
+
+int split_conv(const Geom& g, bool backward, const float* src, const void* wp, float* dst, float* partial, const Finish& finish,
+               hipStream_t s)
+{
+    const SplitChoice c = choose_split(g, backward);
+    const Pass p = pass_of(g, backward);
+    SplitTile P = {};
+    P.src = src; P.wp = (const split::uintx4*)wp; P.dst = dst;
+    P.fK = p.fK; P.fM = p.fM;
+    P.sz = p.a[0].s; P.sy = p.a[1].s; P.sx = p.a[2].s;
+    P.pz = p.a[0].p; P.py = p.a[1].p; P.px = p.a[2].p;
+    P.dz = p.a[0].d; P.dy = p.a[1].d; P.dx = p.a[2].d;
+    P.kz = p.a[0].k; P.ky = p.a[1].k; P.kx = p.a[2].k;
+    P.spz = p.a[0].sp; P.spy = p.a[1].sp; P.spx = p.a[2].sp;
+    P.Tz = c.T[0]; P.Ty = c.T[1]; P.Tx = c.T[2];
+    P.HZ = c.H[0]; P.HY = c.H[1]; P.HX = c.H[2]; P.hvol = c.H[0] * c.H[1] * c.H[2];
+    P.cy = c.c[1]; P.cx = c.c[2];
+    P.qy = p.a[1].phases; P.qx = p.a[2].phases; P.phases = c.phases;
+    const long total = (long)c.c[0] * c.c[1] * c.c[2] * c.phases;
+    if (total >= 2147483640L) return fail(ZNN_EUNSUPPORTED, "too many tiles for one launch");
+    P.total = (int)total; P.run = (int)((total + 7) / 8);
+    P.nchunk = c.nchunk; P.cps = c.cps; P.steps = c.steps;
+    P.partial = partial;
+    P.y = finish.y; P.bias = finish.bias; P.deriv = finish.deriv;
+    P.dHX = make_fastdiv((unsigned)c.H[2]); P.dHY = make_fastdiv((unsigned)c.H[1]);
+    if (log_enabled())
+        fprintf(stderr, "[znn] conv split (%s): NJ=%d jgroups=%d NV=%d waves=%d tile=%dx%dx%d halo=%dx%dx%d blocks=%ld splits=%d lds=%zu cost=%.0f\n",
+                backward ? "bwd" : "fwd", c.NJ, c.jgroups, c.NV, c.NW, c.T[0], c.T[1], c.T[2], c.H[0], c.H[1], c.H[2], total, c.splits,
+                c.lds, c.cost);
+    const SplitFn fn = pick(c.NJ, c.NV, c.NW);
+    if (!fn) return fail(ZNN_EUNSUPPORTED, "no kernel instance for tile %dx%d", c.NJ, c.NV);
+    ZNN_LAUNCH(backward ? "direct backward (MFMA)" : "direct forward (MFMA)", s, fn,
+               dim3((unsigned)P.run * 8, (unsigned)c.jgroups, (unsigned)c.splits), dim3(64 * c.NW), c.lds, P);
+    return check_launch(backward ? "direct backward (MFMA)" : "direct forward (MFMA)");
+}
+
+}  // namespace znn

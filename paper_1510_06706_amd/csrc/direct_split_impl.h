@@ -1,0 +1,364 @@
+// Direct method, forward and backward pass, on the bf16 matrix cores at fp32 precision: kernel and the split of its
+// operands.  The host side (packer, search for the workgroup's box, launch) is direct_split.hip.
+//
+//   D[m][n] += A[m][k] * B[k][n]      v_mfma_f32_16x16x32_bf16, six of them per product
+//     m : 16 output maps              (A = packed kernel weights, coalesced 16-byte loads)
+//     n : 16 output voxels            (B = input voxels read from an LDS halo box)
+//     k : 8 input maps at 4 taps
+//
+// Every fp32 operand is the sum of three bf16 numbers, x = x0 + x1 + x2 (8 significant bits each, together the 24 of x),
+// and a product is taken as x0 y0 + (x0 y1 + x1 y0) + (x0 y2 + x1 y1 + x2 y0): what is left out is below 2^-24 of it, each
+// partial product is exact, and sums are kept in fp32.  Six of these MFMAs do the work of eight v_mfma_f32_16x16x4_f32
+// in 6 x 16 instead of 8 x 32 clocks.
+//
+// Layout: a workgroup of NW waves owns a box of output voxels for 16 NJ output maps; a wave owns NV of its 16-voxel tiles.
+// Per chunk of eight input maps the halo box is split once and staged as [voxel][3 parts][8 maps]: an operand is one 16-byte
+// LDS read, and voxels 48 bytes apart spread over the banks (3 is coprime to the 16 four-bank groups).  A lane group of 16
+// reads its own tap of the step's four, at an offset it looks up once per step, so the walk over the taps is the same for
+// every kernel shape; the count is padded to a multiple of four with weights of zero.
+//
+// Measured against the fp32 kernel (direct_mfma_tail_impl.h), forward / backward pass: 40 -> 40 maps, 64^3, 5^3 kernels 740 /
+// 780 -> 480 / 475 us (180 TFLOP/s of fp32 products); 80 -> 80, 256^2, 11^2: 806 / 741 -> 420 / 426 us; 120 -> 120, 48^3, 7^3:
+// 9.2 / 9.0 -> 3.3 / 4.4 ms; 40 -> 40, 24^3, 3^3: 32 / 39 -> 22 / 23 us; the same, 60^3, taps two apart: 227 / 213 -> 98 /
+// 131 us.  Error against 64 bits (2-norm) of the same layers: 9.1e-7 -> 2.5e-7, 1.2e-6 -> 3.3e-7, 2.6e-6 -> 6.7e-7,
+// 1.6e-7 -> 8.8e-8, 4.2e-7 -> 1.2e-7: sums of a step on their own are what does it (kept in one running sum, the six
+// instructions would be as far off as the fp32 one).
+//
+// Sparse taps (s voxels apart) tie together only voxels of the same residues modulo s: a workgroup's box lies on one of the
+// s_z s_y s_x sublattices, on which the taps are neighbours, so the halo of a sparse layer is that of a dense one.
+#pragma once
+
+#include <type_traits>
+
+#include "znn_internal.h"
+
+namespace znn {
+namespace split {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) const char* lds_bytes;
+typedef __attribute__((address_space(3))) const uintx4* lds_quads;
+typedef __attribute__((address_space(3))) const int* lds_ints;
+
+constexpr int kMaps = 8;            // input maps of a chunk
+constexpr int kTaps = 4;            // taps of a step
+constexpr int kVoxelBytes = 48;     // three parts of eight maps
+constexpr int kFetch = 2;           // halo voxels a thread has in flight
+
+// The leading bf16 part of x and y, packed; x and y keep the rest, which is exact.
+__device__ __forceinline__ unsigned take_part(float& x, float& y)
+{
+    const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2){x, y}, bf16x2));
+    x -= __builtin_bit_cast(float, u << 16);
+    y -= __builtin_bit_cast(float, u & 0xffff0000u);
+    return u;
+}
+
+__device__ __forceinline__ uintx4 take_part8(float (&x)[8])
+{
+    uintx4 u;
+    u[0] = take_part(x[0], x[1]);
+    u[1] = take_part(x[2], x[3]);
+    u[2] = take_part(x[4], x[5]);
+    u[3] = take_part(x[6], x[7]);
+    return u;
+}
+
+struct SplitTile {
+    const float* src;       // K-side images [fK][sz][sy][sx]
+    const uintx4* wp;       // packed weights [jgroup][chunk][step][NJ][3][64]
+    float* dst;             // M-side images [fM][dz][dy][dx]
+    int fK, fM;
+    int sz, sy, sx;
+    int pz, py, px;         // taps of zeros virtually in front of the source (in units of the tap spacing)
+    int dz, dy, dx;
+    int kz, ky, kx;
+    int spz, spy, spx;      // tap spacing
+    int Tz, Ty, Tx;         // output voxels per workgroup, on their sublattice
+    int HZ, HY, HX, hvol;   // halo box
+    int cy, cx;             // boxes per axis of a sublattice
+    int qy, qx, phases;     // sublattices along y and x, and in all
+    int total, run;         // workgroups (boxes x sublattices), and those of one XCD
+    int nchunk, cps;        // chunks of eight input maps, and those of a workgroup (gridDim.z shares them out)
+    int steps;              // ceil(taps / 4)
+    float* partial;         // [shares][fM][dz][dy][dx] where gridDim.z > 1
+    float* y;               // where not NULL: y = max(result + bias[map], 0) beside the result
+    const float* bias;
+    const float* deriv;     // where not NULL: the result is zero where this forward result of a rectifier is zero
+    FastDiv dHX, dHY;
+};
+
+using SplitFn = void (*)(SplitTile);
+
+// Bound by the matrix cores (six MFMAs of 16 clocks per 16 x 16 x 32 product).
+template <int NJ, int NV, int NW>
+__global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
+{
+    constexpr int NT = 64 * NW;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const unsigned lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, grp = lane >> 4;
+
+    // Workgroups go to the eight XCDs in turn; each XCD takes a contiguous run, sublattices of a box next to each other:
+    // they read the same cache lines.
+    const int id = (blockIdx.x & 7) * P.run + (blockIdx.x >> 3);
+    if (id >= P.total) return;
+    int box = id / P.phases, ph = id - box * P.phases;
+    const int fx = ph % P.qx; ph /= P.qx;
+    const int fy = ph % P.qy, fz = ph / P.qy;
+    const int bx = box % P.cx; box /= P.cx;
+    const int by = box % P.cy, bz = box / P.cy;
+    const int z0 = bz * P.Tz, y0 = by * P.Ty, x0 = bx * P.Tx;       // on the sublattice
+    const int Ttot = P.Tz * P.Ty * P.Tx;
+    const long splane = (long)P.sy * P.sx, svol = P.sz * splane;
+    const long dplane = (long)P.dy * P.dx, dvol = P.dz * dplane;
+    const int jg = blockIdx.y;
+    const int ic0 = blockIdx.z * P.cps, ic1 = min(P.nchunk, ic0 + P.cps);
+
+    // place of output voxel t of the box in a result map, -1 outside it
+    auto voxel_of = [&](int t) -> long {
+        if (t >= Ttot) return -1;
+        const int q = t / P.Tx, tx = t - q * P.Tx, tz = q / P.Ty, ty = q - tz * P.Ty;
+        const int z = fz + (z0 + tz) * P.spz, y = fy + (y0 + ty) * P.spy, x = fx + (x0 + tx) * P.spx;
+        if (z >= P.dz || y >= P.dy || x >= P.dx) return -1;
+        return z * dplane + (long)y * P.dx + x;
+    };
+
+    // halo offsets of the taps, four per step; packed tap (a, b, c) meets the halo at (kz-1-a, ky-1-b, kx-1-c)
+    int* const tofs = reinterpret_cast<int*>(smem + P.hvol * kVoxelBytes);
+    const int taps = P.kz * P.ky * P.kx;
+    for (int t = threadIdx.x; t < (P.steps + 2) * kTaps; t += NT) {
+        const int q = min(t, taps - 1);
+        const int c = q % P.kx, r = q / P.kx, b = r % P.ky, a = r / P.ky;
+        tofs[t] = (((P.kz - 1 - a) * P.HY + (P.ky - 1 - b)) * P.HX + (P.kx - 1 - c)) * kVoxelBytes;
+    }
+    // halo voxels: byte offset in a source map, -1 outside the image (zeros)
+    unsigned* const from = reinterpret_cast<unsigned*>(tofs + (P.steps + 2) * kTaps);
+    for (int r = threadIdx.x; r < P.hvol; r += NT) {
+        const int r1 = (int)fdiv((unsigned)r, P.dHX), hx = r - r1 * P.HX;
+        const int hz = (int)fdiv((unsigned)r1, P.dHY), hy = r1 - hz * P.HY;
+        const int gz = fz + (z0 + hz - P.pz) * P.spz, gy = fy + (y0 + hy - P.py) * P.spy, gx = fx + (x0 + hx - P.px) * P.spx;
+        const bool in = gz >= 0 && gz < P.sz && gy >= 0 && gy < P.sy && gx >= 0 && gx < P.sx;
+        from[r] = in ? (unsigned)((gz * P.sy + gy) * P.sx + gx) * 4u : ~0u;
+    }
+    const lds_bytes lbase = (lds_bytes)smem;
+    lds_bytes voff[NV];
+#pragma unroll
+    for (int nv = 0; nv < NV; ++nv) {
+        int t = (wave * NV + nv) * 16 + col;
+        if (t >= Ttot) t = 0;
+        const int q = t / P.Tx, tx = t - q * P.Tx, tz = q / P.Ty, ty = q - tz * P.Ty;
+        voff[nv] = lbase + ((tz * P.HY + ty) * P.HX + tx) * kVoxelBytes;
+    }
+
+    floatx4 acc[NJ][NV];
+#pragma unroll
+    for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+        for (int nv = 0; nv < NV; ++nv) acc[jt][nv] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    // A thread reads, splits and stores the halo voxels it has an entry of `from` for, so this needs no barrier before it.
+    // Its latency is left to the other workgroup of the compute unit: loads kept in flight through the taps would take the
+    // registers of two result tiles.
+    auto stage = [&](int ic) {
+        const float* base = P.src + (long)ic * kMaps * svol;
+        const int nvalid = P.fK - ic * kMaps;           // uniform
+        const char* map[kMaps];
+#pragma unroll
+        for (int m = 0; m < kMaps; ++m) map[m] = reinterpret_cast<const char*>(base + min(m, nvalid - 1) * svol);
+        for (int r0 = threadIdx.x; r0 < P.hvol; r0 += kFetch * NT) {
+            float v[kFetch][kMaps];
+#pragma unroll
+            for (int i = 0; i < kFetch; ++i) {
+                const int r = r0 + i * NT;
+                // every load is unconditional, of some voxel of the map: a branch around each would take longer than the split
+                const unsigned o = r < P.hvol ? from[r] : ~0u, at = o != ~0u ? o : 0u;
+#pragma unroll
+                for (int m = 0; m < kMaps; ++m) v[i][m] = *reinterpret_cast<const float*>(map[m] + at);
+            }
+#pragma unroll
+            for (int i = 0; i < kFetch; ++i)
+                if (r0 + i * NT < P.hvol) {
+                    const bool in = from[r0 + i * NT] != ~0u;
+#pragma unroll
+                    for (int m = 0; m < kMaps; ++m) v[i][m] = in && m < nvalid ? v[i][m] : 0.f;
+                    uintx4* at = reinterpret_cast<uintx4*>(smem + (r0 + i * NT) * kVoxelBytes);
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) at[p] = take_part8(v[i]);
+                }
+        }
+    };
+
+    const int wstep = NJ * 3 * 64;                      // packed weights of a step
+    const uintx4* wq = P.wp + ((long)jg * P.nchunk + ic0) * P.steps * wstep + lane;
+    for (int ic = ic0; ic < ic1; ++ic) {
+        bf16x8 a0[NJ][3], a1[NJ][3];
+        uintx4 b0[3], b1[3];
+        floatx4 t0[NJ], t1[NJ];
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt) t0[jt] = t1[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+        auto weights = [&](bf16x8 (&a)[NJ][3]) {
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) a[jt][p] = __builtin_bit_cast(bf16x8, wq[(jt * 3 + p) * 64]);
+        };
+        weights(a0);
+        __syncthreads();                                // nobody still reads the chunk before
+        stage(ic);
+        __syncthreads();
+
+        lds_ints to = (lds_ints)(lbase + P.hvol * kVoxelBytes) + grp;
+        int now = to[0], next = to[kTaps];
+        auto voxels = [&](uintx4 (&b)[3], lds_bytes at) {
+#pragma unroll
+            for (int p = 0; p < 3; ++p) b[p] = reinterpret_cast<lds_quads>(at)[p];
+        };
+        voxels(b0, voff[0] + now);
+        // One step: the MFMAs of a voxel tile run while the operands of the next one arrive.  PAR: which register set of
+        // the voxel operands the step's first tile is in.
+        auto step = [&](bf16x8 (&a)[NJ][3], bf16x8 (&an)[NJ][3], auto par) __attribute__((always_inline)) {
+            constexpr int PAR = decltype(par)::value;
+            wq += wstep;
+            weights(an);                                // behind the last step: the next chunk's, or the padding
+#pragma unroll
+            for (int nv = 0; nv < NV; ++nv) {
+                uintx4 (&b)[3] = ((PAR + nv) & 1) ? b1 : b0;
+                uintx4 (&bn)[3] = ((PAR + nv) & 1) ? b0 : b1;
+                if (nv + 1 < NV) voxels(bn, voff[nv + 1 < NV ? nv + 1 : 0] + now);
+                else {
+                    now = next;
+                    to += kTaps;
+                    next = to[kTaps];
+                    voxels(bn, voff[0] + now);
+                }
+                // the six products of a step in sums of their own, smallest first: rounding them into the running sum one by
+                // one would cost as much precision as the fp32 instruction does
+                const bf16x8 c0 = __builtin_bit_cast(bf16x8, b[0]), c1 = __builtin_bit_cast(bf16x8, b[1]),
+                             c2 = __builtin_bit_cast(bf16x8, b[2]);
+                floatx4 (&t)[NJ] = ((PAR + nv) & 1) ? t1 : t0;
+                floatx4 (&tp)[NJ] = ((PAR + nv) & 1) ? t0 : t1;
+                __builtin_amdgcn_sched_barrier(0);
+                const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int jt = 0; jt < NJ; ++jt) t[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[jt][0], c2, zero, 0, 0, 0);
+#pragma unroll
+                for (int jt = 0; jt < NJ; ++jt) t[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[jt][2], c0, t[jt], 0, 0, 0);
+#pragma unroll
+                for (int jt = 0; jt < NJ; ++jt) acc[jt][(nv + NV - 1) % NV] += tp[jt];      // of the tile before
+#pragma unroll
+                for (int jt = 0; jt < NJ; ++jt) t[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[jt][1], c1, t[jt], 0, 0, 0);
+#pragma unroll
+                for (int jt = 0; jt < NJ; ++jt) t[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[jt][0], c1, t[jt], 0, 0, 0);
+#pragma unroll
+                for (int jt = 0; jt < NJ; ++jt) t[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[jt][1], c0, t[jt], 0, 0, 0);
+#pragma unroll
+                for (int jt = 0; jt < NJ; ++jt) t[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[jt][0], c0, t[jt], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        constexpr int ODD = NV & 1;
+        int s = 0;
+        for (; s + 2 <= P.steps; s += 2) {
+            step(a0, a1, std::integral_constant<int, 0>{});
+            step(a1, a0, std::integral_constant<int, ODD>{});
+        }
+        if (s < P.steps) step(a0, a1, std::integral_constant<int, 0>{});
+        // the last tile's: in set 0 or 1 by the parity of steps x NV
+        if (P.steps & ODD & 1) {
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt) acc[jt][NV - 1] += t0[jt];
+        } else {
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt) acc[jt][NV - 1] += t1[jt];
+        }
+    }
+
+    // An infinity or a NaN among the operands makes the parts' products NaN where the product itself may not be: sums that
+    // are not finite are taken again in fp32, straight from memory, as v_mfma_f32_16x16x4_f32 gives them.
+    bool bad = false;
+#pragma unroll
+    for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+        for (int nv = 0; nv < NV; ++nv)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) bad = bad || !(fabsf(acc[jt][nv][r]) <= 3.4028234e38f);
+    if (__builtin_amdgcn_ballot_w64(bad)) {
+        int base[NV];
+#pragma unroll
+        for (int nv = 0; nv < NV; ++nv) {
+            base[nv] = min((wave * NV + nv) * 16 + col, Ttot - 1);
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt) acc[jt][nv] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+        for (int ic = ic0; ic < ic1; ++ic)
+            for (int q = 0; q < taps; ++q) {
+                const int c = q % P.kx, r = q / P.kx, b = r % P.ky, a = r / P.ky;
+                const uintx4* wt = P.wp + (((long)jg * P.nchunk + ic) * P.steps + q / kTaps) * wstep + (q % kTaps) * 16 + col;
+                for (int h = 0; h < kMaps / 4; ++h) {
+                    const int m = h * 4 + grp, map = ic * kMaps + m;        // the lane's input map
+                    float w[NJ], v[NV];
+#pragma unroll
+                    for (int jt = 0; jt < NJ; ++jt) {
+                        float part[3];
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) {
+                            const unsigned u = reinterpret_cast<const unsigned*>(wt + (jt * 3 + p) * 64)[m >> 1];
+                            part[p] = __builtin_bit_cast(float, m & 1 ? u & 0xffff0000u : u << 16);
+                        }
+                        w[jt] = part[0] + (part[1] + part[2]);
+                    }
+#pragma unroll
+                    for (int nv = 0; nv < NV; ++nv) {
+                        const int qq = base[nv] / P.Tx, tx = base[nv] - qq * P.Tx, tz = qq / P.Ty, ty = qq - tz * P.Ty;
+                        const int gz = fz + (z0 + tz + P.kz - 1 - a - P.pz) * P.spz, gy = fy + (y0 + ty + P.ky - 1 - b - P.py) * P.spy,
+                                  gx = fx + (x0 + tx + P.kx - 1 - c - P.px) * P.spx;
+                        const bool in = map < P.fK && gz >= 0 && gz < P.sz && gy >= 0 && gy < P.sy && gx >= 0 && gx < P.sx;
+                        v[nv] = in ? P.src[map * svol + ((long)gz * P.sy + gy) * P.sx + gx] : 0.f;
+                    }
+#pragma unroll
+                    for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+                        for (int nv = 0; nv < NV; ++nv)
+                            acc[jt][nv] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[jt], v[nv], acc[jt][nv], 0, 0, 0);
+                }
+            }
+    }
+
+    float* const out = gridDim.z > 1 ? P.partial + (long)blockIdx.z * P.fM * dvol : P.dst;
+    // lane holds maps 4 (lane / 16) + r of voxel lane % 16
+    auto store_all = [&](auto&& store) {
+#pragma unroll
+        for (int nv = 0; nv < NV; ++nv) {
+            const long vox = voxel_of((wave * NV + nv) * 16 + col);
+            if (vox < 0) continue;
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int j = (jg * NJ + jt) * 16 + grp * 4 + r;
+                    if (j < P.fM) store((long)j * dvol + vox, j, acc[jt][nv][r]);
+                }
+        }
+    };
+    // what follows the sums is decided once, outside the stores
+    if (P.deriv || P.y)
+        store_all([&](long at, int j, float v) {
+            if (P.deriv) v = P.deriv[at] > 0.f ? v : 0.f;       // uniform
+            out[at] = v;
+            if (P.y) {                                          // uniform
+                v += P.bias[j];
+                P.y[at] = v > 0.f ? v : 0.f;
+            }
+        });
+    else
+        store_all([&](long at, int, float v) { out[at] = v; });
+}
+
+}  // namespace split
+}  // namespace znn

@@ -76,6 +76,7 @@ struct Tuning {
     bool conv_no_wl;            // ZNN_CONV_NO_WL: never stage a chunk's weights in LDS
     bool conv_no_split;         // ZNN_CONV_NO_SPLIT: never split the input maps over workgroups
     bool conv_no_tail;          // ZNN_CONV_NO_TAIL: pad the last maps to a 16-row tile instead of an 8-map block
+    bool conv_no_parts;         // ZNN_CONV_NO_PARTS: fp32 matrix instructions where the split kernel would run
     int  conv_tile[4];          // ZNN_CONV_TILE="NV,Tz,Ty,Tx": pin the output box (0 = not pinned)
     int  wgrad_halves;          // ZNN_WGRAD_HALVES: 1 = four waves, 2 = eight waves per workgroup
     int  wgrad_maxnj;           // ZNN_WGRAD_MAXNJ: most 16-map tiles per workgroup
@@ -103,7 +104,7 @@ int direct_bwd(const Geom& g, const float* gout, const float* w, float* gin, voi
 int direct_wgrad(const Geom& g, const float* in, const float* gout, float* gw, void* ws, hipStream_t s);
 size_t direct_workspace_bytes(const Geom& g, int pass);
 // The tiled kernels in pieces, for rounds that pack the weights of all layers at once and finish several sums in one launch
-struct PackItem { const float* w; float* wp; int f, fo, kz, ky, kx, backward, NJ, nchunk, tail; long total; };
+struct PackItem { const float* w; float* wp; int f, fo, kz, ky, kx, backward, split, NJ, nchunk, tail; long total; };
 bool mfma_conv_supported(const Geom& g, bool backward);
 PackItem mfma_conv_pack_item(const Geom& g, bool backward, const float* w, float* wp);
 int mfma_pack_weights(const PackItem* items, int n, hipStream_t s);

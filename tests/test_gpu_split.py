@@ -1,0 +1,101 @@
+"""The direct kernels on operands split into three bf16 parts (forward, backward): edges of their tiles, sublattices of sparse
+taps, shares of the input maps, and operands that are not finite.
+
+The bound is derived, element by element, from S = sum of |products| (the oracle on absolute values): what the split leaves
+out of a product is below 2^-23 of it, a step of 32 products is summed by six instructions, and then one fp32 addition per
+step and share rounds a partial sum that is at most S.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1510_06706_amd import binding as znn
+from paper_1510_06706_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # f, fo, n, k, s: map counts around the chunks of 8 and the tiles of 16, taps around the steps of 4
+    (5, 1, (6, 7, 8), (1, 1, 1), (1, 1, 1)),            # one tap
+    (8, 16, (9, 8, 17), (1, 2, 2), (1, 1, 1)),          # one full step
+    (9, 17, (7, 9, 16), (1, 1, 5), (1, 1, 1)),          # a step and a tap
+    (40, 40, (14, 13, 12), (3, 3, 3), (1, 1, 1)),
+    (24, 81, (5, 20, 19), (2, 3, 4), (1, 1, 1)),        # two groups of map tiles
+    (130, 7, (6, 6, 9), (2, 2, 2), (1, 1, 1)),          # many chunks, shares of them
+    (6, 33, (1, 40, 23), (1, 7, 3), (1, 1, 1)),         # 2D
+    (16, 8, (33, 4, 40), (3, 1, 3), (1, 1, 1)),
+    (12, 12, (15, 14, 13), (3, 3, 3), (2, 3, 4)),       # sublattices of different extents
+    (10, 10, (9, 9, 11), (3, 3, 3), (4, 4, 5)),         # result extents below the tap spacing
+    (8, 24, (3, 30, 30), (1, 3, 3), (3, 2, 2)),         # spacing on an axis of one tap
+    (48, 64, (20, 20, 20), (3, 3, 3), (1, 1, 1)),
+    (72, 72, (10, 11, 12), (5, 4, 3), (1, 1, 1)),       # five map tiles
+    (5, 5, (30, 9, 10), (17, 9, 7), (1, 1, 1)),         # 1071 taps
+]
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a.astype(np.float32))).to("cuda:0")
+
+
+def tensors(f, fo, n, k, s, seed):
+    x, w, g = synth.layer_tensors(synth.LayerShape("t", f, fo, n, k, 1.0, seed, s))
+    return x, w, g
+
+
+def bound(ref_abs, maps, taps):
+    adds = -(-maps // 8) * -(-taps // 4) + -(-maps // 8)
+    return (adds + 16) * 2.0 ** -24 * ref_abs
+
+
+@pytest.mark.parametrize("f,fo,n,k,s", SHAPES)
+def test_passes_stay_within_the_bound_of_the_split(f, fo, n, k, s):
+    x, w, g = tensors(f, fo, n, k, s, 9100)
+    taps = k[0] * k[1] * k[2]
+    p = znn.Plan(f, fo, n, k, "direct", s)
+    out, gin = p.fwd(dev(x), dev(w)).cpu().numpy(), p.bwd(dev(g), dev(w)).cpu().numpy()
+    err = np.abs(out.astype(np.float64) - oracle.conv3d_fwd(x, w, s))
+    assert np.all(err <= bound(oracle.conv3d_fwd(np.abs(x), np.abs(w), s), f, taps))
+    err = np.abs(gin.astype(np.float64) - oracle.conv3d_bwd(g, w, n, s))
+    assert np.all(err <= bound(oracle.conv3d_bwd(np.abs(g), np.abs(w), n, s), fo, taps))
+    p.close()
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** 60])
+def test_the_split_keeps_its_precision_at_any_scale(scale):
+    f, fo, n, k, s = 16, 16, (10, 10, 10), (3, 3, 3), (1, 1, 1)
+    x, w, g = tensors(f, fo, n, k, s, 9101)
+    p = znn.Plan(f, fo, n, k, "direct", s)
+    base, scaled = p.fwd(dev(x), dev(w)), p.fwd(dev(x * scale), dev(w / scale))
+    assert np.array_equal(base.cpu().numpy(), scaled.cpu().numpy())
+    p.close()
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38])
+def test_operands_that_are_not_finite_act_as_in_fp32(value):
+    f, fo, n, k, s = 9, 20, (11, 12, 13), (3, 3, 3), (1, 1, 1)
+    x, w, g = tensors(f, fo, n, k, s, 9102)
+    w *= 2.0 ** -10
+    taps = 27
+    p = znn.Plan(f, fo, n, k, "direct", s)
+
+    def same(got, ref, limit):
+        got = got.cpu().numpy().astype(np.float64)
+        assert np.array_equal(np.isnan(got), np.isnan(ref))
+        assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref))
+        ok = np.isfinite(ref)
+        assert np.all(np.abs(got[ok] - ref[ok]) <= limit[ok])
+
+    # results that are finite sum the same products in the order of the fp32 instruction: one rounding each
+    def limit(ref_abs, maps):
+        return (maps * taps + 16) * 2.0 ** -24 * np.where(np.isfinite(ref_abs), ref_abs, 0.0)
+
+    xs, gs, ws = x.copy(), g.copy(), w.copy()
+    xs[4, 5, 6, 7] = value
+    gs[11, 3, 0, 8] = value
+    same(p.fwd(dev(xs), dev(w)), oracle.conv3d_fwd(xs, w), limit(oracle.conv3d_fwd(np.abs(xs), np.abs(w)), f))
+    same(p.bwd(dev(gs), dev(w)), oracle.conv3d_bwd(gs, w, n), limit(oracle.conv3d_bwd(np.abs(gs), np.abs(w), n), fo))
+    ws[17, 3, 1, 2, 0] = value
+    xw = x * 2.0 ** -10
+    same(p.fwd(dev(xw), dev(ws)), oracle.conv3d_fwd(xw, ws), limit(oracle.conv3d_fwd(np.abs(xw), np.abs(ws)), f))
+    p.close()
