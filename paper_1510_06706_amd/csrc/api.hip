@@ -83,14 +83,6 @@ const Tuning& tuning()
         if (const char* e = getenv("ZNN_CONV_TILE"))
             if (sscanf(e, "%d,%d,%d,%d", &v.conv_tile[0], &v.conv_tile[1], &v.conv_tile[2], &v.conv_tile[3]) != 4)
                 v.conv_tile[0] = v.conv_tile[1] = v.conv_tile[2] = v.conv_tile[3] = 0;
-        v.wgrad_halves = num("ZNN_WGRAD_HALVES", 2);
-        v.wgrad_maxnj = num("ZNN_WGRAD_MAXNJ", 6);
-        if (v.wgrad_maxnj < 1 || v.wgrad_maxnj > 8) v.wgrad_maxnj = 6;
-        v.wgrad_own_columns_from = num("ZNN_WGRAD_OWN_COLUMNS_FROM", 16);
-        v.wgrad_own_waves = num("ZNN_WGRAD_OWN_WAVES", 4) == 8 ? 8 : 4;
-        v.wgrad_stride_mod = num("ZNN_WGRAD_STRIDE_MOD", 4);
-        if (v.wgrad_stride_mod < 0 || v.wgrad_stride_mod > 28 || v.wgrad_stride_mod % 4) v.wgrad_stride_mod = 4;
-        v.wgrad_slow_loader = flag("ZNN_WGRAD_SLOW_LOADER");
         v.fft_mac_z0 = num("ZNN_FFT_MAC_Z0", 0);
         v.fft_mac_valu = flag("ZNN_FFT_MAC_VALU");
         v.fft_wgrad_plain = flag("ZNN_FFT_WGRAD_PLAIN");

@@ -6,11 +6,6 @@
 //     n : 16 output voxels            (B = input voxels read from an LDS halo box)
 //     k : 8 input maps at 4 taps
 //
-// Every fp32 operand is the sum of three bf16 numbers, x = x0 + x1 + x2 (8 significant bits each, together the 24 of x),
-// and a product is taken as x0 y0 + (x0 y1 + x1 y0) + (x0 y2 + x1 y1 + x2 y0): what is left out is below 2^-24 of it, each
-// partial product is exact, and sums are kept in fp32.  Six of these MFMAs do the work of eight v_mfma_f32_16x16x4_f32
-// in 6 x 16 instead of 8 x 32 clocks.
-//
 // Layout: a workgroup of NW waves owns a box of output voxels for 16 NJ output maps; a wave owns NV of its 16-voxel tiles.
 // Per chunk of eight input maps the halo box is split once and staged as [voxel][3 parts][8 maps]: an operand is one 16-byte
 // LDS read, and voxels 48 bytes apart spread over the banks (3 is coprime to the 16 four-bank groups).  A lane group of 16
@@ -30,43 +25,15 @@
 
 #include <type_traits>
 
-#include "znn_internal.h"
+#include "split_parts.h"
 
 namespace znn {
 namespace split {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) const char* lds_bytes;
-typedef __attribute__((address_space(3))) const uintx4* lds_quads;
-typedef __attribute__((address_space(3))) const int* lds_ints;
-
 constexpr int kMaps = 8;            // input maps of a chunk
 constexpr int kTaps = 4;            // taps of a step
-constexpr int kVoxelBytes = 48;     // three parts of eight maps
+constexpr int kVoxelBytes = kVectorBytes;     // three parts of eight maps
 constexpr int kFetch = 2;           // halo voxels a thread has in flight
-
-// The leading bf16 part of x and y, packed; x and y keep the rest, which is exact.
-__device__ __forceinline__ unsigned take_part(float& x, float& y)
-{
-    const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2){x, y}, bf16x2));
-    x -= __builtin_bit_cast(float, u << 16);
-    y -= __builtin_bit_cast(float, u & 0xffff0000u);
-    return u;
-}
-
-__device__ __forceinline__ uintx4 take_part8(float (&x)[8])
-{
-    uintx4 u;
-    u[0] = take_part(x[0], x[1]);
-    u[1] = take_part(x[2], x[3]);
-    u[2] = take_part(x[4], x[5]);
-    u[3] = take_part(x[6], x[7]);
-    return u;
-}
 
 struct SplitTile {
     const float* src;       // K-side images [fK][sz][sy][sx]
@@ -237,29 +204,10 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
                     next = to[kTaps];
                     voxels(bn, voff[0] + now);
                 }
-                // the six products of a step in sums of their own, smallest first: rounding them into the running sum one by
-                // one would cost as much precision as the fp32 instruction does
-                const bf16x8 c0 = __builtin_bit_cast(bf16x8, b[0]), c1 = __builtin_bit_cast(bf16x8, b[1]),
-                             c2 = __builtin_bit_cast(bf16x8, b[2]);
-                floatx4 (&t)[NJ] = ((PAR + nv) & 1) ? t1 : t0;
-                floatx4 (&tp)[NJ] = ((PAR + nv) & 1) ? t0 : t1;
-                __builtin_amdgcn_sched_barrier(0);
-                const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+                floatx4* into[NJ];
 #pragma unroll
-                for (int jt = 0; jt < NJ; ++jt) t[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[jt][0], c2, zero, 0, 0, 0);
-#pragma unroll
-                for (int jt = 0; jt < NJ; ++jt) t[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[jt][2], c0, t[jt], 0, 0, 0);
-#pragma unroll
-                for (int jt = 0; jt < NJ; ++jt) acc[jt][(nv + NV - 1) % NV] += tp[jt];      // of the tile before
-#pragma unroll
-                for (int jt = 0; jt < NJ; ++jt) t[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[jt][1], c1, t[jt], 0, 0, 0);
-#pragma unroll
-                for (int jt = 0; jt < NJ; ++jt) t[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[jt][0], c1, t[jt], 0, 0, 0);
-#pragma unroll
-                for (int jt = 0; jt < NJ; ++jt) t[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[jt][1], c0, t[jt], 0, 0, 0);
-#pragma unroll
-                for (int jt = 0; jt < NJ; ++jt) t[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[jt][0], c0, t[jt], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int jt = 0; jt < NJ; ++jt) into[jt] = &acc[jt][(nv + NV - 1) % NV];
+                products<NJ>((PAR + nv) & 1 ? t1 : t0, a, b, (PAR + nv) & 1 ? t0 : t1, into);
             }
         };
         constexpr int ODD = NV & 1;
@@ -287,7 +235,7 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
 #pragma unroll
         for (int nv = 0; nv < NV; ++nv)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) bad = bad || !(fabsf(acc[jt][nv][r]) <= 3.4028234e38f);
+            for (int r = 0; r < 4; ++r) bad = bad || !(fabsf(acc[jt][nv][r]) <= kLargest);
     if (__builtin_amdgcn_ballot_w64(bad)) {
         int base[NV];
 #pragma unroll

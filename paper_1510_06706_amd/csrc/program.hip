@@ -122,14 +122,15 @@ __global__ void __launch_bounds__(256) k_bias_parts(BiasArgs A)
 }
 
 // Completes the gradients of a round and updates the parameters.  An item is the kernels or the biases of a layer:
-//   kind 0: the gradient is there;  kind 1: shares of the direct kernel gradient, in the order of k_wgrad_reduce;
-//   kind 2: the same in the order of k_wgrad_reduce4 (four waves per 64 elements);  kind 3: `spans` parts per bias.
+//   kind 0: the gradient is there;  kind 1: shares of the direct kernel gradient, in the order of k_wgrad_sum;
+//   kind 2: the same in the order of k_wgrad_sum4 (four waves per 64 elements);  kind 3: `spans` parts per bias.
 // p may be NULL (gradient only).
 constexpr int kUpdateItems = 32;
 struct UpdateItem {
     const float* src; float* grad; float* p;
     long total; unsigned first;
-    int kind, f, taps, kx, AB, ksplit, Mpad, Npad, mapmajor;
+    int kind;
+    WgradSum sum;           // kind 3: sum.ksplit parts
 };
 struct UpdateArgs { UpdateItem item[kUpdateItems]; int n; float eta; };
 __global__ void __launch_bounds__(256) k_update(UpdateArgs A)
@@ -140,25 +141,24 @@ __global__ void __launch_bounds__(256) k_update(UpdateArgs A)
     const UpdateItem& U = A.item[q];
     const unsigned r = blockIdx.x - U.first;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const long t = U.kind == 2 ? (long)r * 64 + lane : (long)r * 256 + threadIdx.x;
+    const bool shares = U.kind == 1 || U.kind == 2;         // threads run along the partial sums
+    const long e = U.kind == 2 ? (long)r * 64 + lane : (long)r * 256 + threadIdx.x;
+    long t = e, from = 0;
+    const bool live = shares ? e < U.sum.slots && wgrad_slot(U.sum, e, from, t) : e < U.total;
     float acc = 0.f;
-    if (t < U.total) {
+    if (live) {
+        const int n = U.sum.ksplit;
         if (U.kind == 0) acc = U.grad[t];
-        else if (U.kind == 3) for (int s = 0; s < U.ksplit; ++s) acc += U.src[t * U.ksplit + s];
+        else if (U.kind == 3) for (int s = 0; s < n; ++s) acc += U.src[t * n + s];
         else {
-            const int tap = (int)(t % U.taps);
-            const long e = t / U.taps;
-            const int i = (int)(e % U.f), j = (int)(e / U.f);
-            const int c = tap % U.kx, ab = tap / U.kx;
-            const int n = U.mapmajor ? i * U.kx + c : c * U.f + i;
-            const float* p = U.src + ((long)ab * U.Mpad + j) * U.Npad + n;
-            const long step = (long)U.AB * U.Mpad * U.Npad;
+            const float* p = U.src + from;
+            const long step = (long)U.sum.planes * U.sum.Mpad * U.sum.Npad;
             if (U.kind == 1) {
 #pragma unroll 4
-                for (int s = 0; s < U.ksplit; ++s) acc += p[s * step];
+                for (int s = 0; s < n; ++s) acc += p[s * step];
             } else {
 #pragma unroll 4
-                for (int s = wave; s < U.ksplit; s += 4) acc += p[s * step];
+                for (int s = wave; s < n; s += 4) acc += p[s * step];
             }
         }
     }
@@ -168,7 +168,7 @@ __global__ void __launch_bounds__(256) k_update(UpdateArgs A)
         if (wave != 0) return;
         acc = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
     }
-    if (t >= U.total) return;
+    if (!live) return;
     if (U.kind != 0) U.grad[t] = acc;
     if (U.p) U.p[t] = U.p[t] - A.eta * acc;
 }
@@ -420,7 +420,7 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
             } else if (s.kind == ZNN_OP_CONV_WGRAD && s.op.buf[2] == g) {
                 const Layer& L = P.layers[s.layer];
                 if (L.plan.mode != ZNN_DIRECT || !mfma_wgrad_supported(L.plan.g) || touched_between(P, g, i, at_update)) continue;
-                s.own = hold(s.layer, mfma_wgrad_workspace(L.plan.g));
+                s.own = hold(s.layer, mfma_wgrad_sums_bytes(L.plan.g));
                 if (s.own != kNone) P.completes[u] = i;
             }
         }
@@ -433,7 +433,7 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
         if (s.layer < 0) continue;
         const Layer& L = P.layers[s.layer];
         const Geom& g = L.plan.g;
-        if (s.kind == ZNN_OP_CONV_WGRAD) s.pass_bytes = s.own != kNone ? 0 : plan_pass_bytes(&L.plan, s.kind, false);
+        if (s.kind == ZNN_OP_CONV_WGRAD) s.pass_bytes = s.own != kNone ? mfma_wgrad_copies_bytes(g) : plan_pass_bytes(&L.plan, s.kind, false);
         else if (L.packed[s.kind] != kNone) {
             const int splits = mfma_conv_splits(g, s.kind == ZNN_OP_CONV_BWD);
             s.pass_bytes = splits > 1 ? sizeof(float) * splits * (s.kind ? (size_t)g.f * g.nvol() : (size_t)g.fo * g.ovol()) : 0;
@@ -596,15 +596,13 @@ int run_update(const znn_program& P, float* const* buf, char* scratch, float eta
             if (done_by >= 0) {
                 const Step& d = P.steps[done_by];
                 I.src = (const float*)(scratch + d.own);
-                if (d.kind == ZNN_OP_BIAS_GRAD) { I.kind = 3; I.ksplit = bias_spans(d.op); }
+                if (d.kind == ZNN_OP_BIAS_GRAD) { I.kind = 3; I.sum.ksplit = bias_spans(d.op); }
                 else {
-                    const Geom& g = P.layers[d.layer].plan.g;
                     I.kind = d.sum.four ? 2 : 1;
-                    I.f = g.f; I.taps = (int)g.kvol(); I.kx = g.kx; I.AB = g.kz * g.ky;
-                    I.ksplit = d.sum.ksplit; I.Mpad = d.sum.Mpad; I.Npad = d.sum.Npad; I.mapmajor = d.sum.mapmajor;
+                    I.sum = d.sum;
                 }
             }
-            blocks += (unsigned)(I.kind == 2 ? (I.total + 63) / 64 : blocks_of(I.total));
+            blocks += I.kind == 2 ? (unsigned)((I.sum.slots + 63) / 64) : blocks_of(I.kind == 1 ? I.sum.slots : I.total);
         }
         ZNN_LAUNCH("gradient sums and update", s, k_update, dim3(blocks), dim3(256), 0, A);
     }
@@ -620,7 +618,7 @@ int run_conv(znn_program& P, Step& t, float* const* buf, char* scratch, hipStrea
     char* const area = scratch + P.area[t.stream];
     auto at = [&](int q) -> float* { return o.buf[q] < 0 ? nullptr : buf[o.buf[q]]; };
     if (t.kind == ZNN_OP_CONV_WGRAD) {
-        if (t.own != kNone) return mfma_wgrad_partial(g, at(0), at(1), (float*)(scratch + t.own), &t.sum, s);
+        if (t.own != kNone) return mfma_wgrad_partial(g, at(0), at(1), (float*)(scratch + t.own), area, &t.sum, s);
         if (L.memo != kNone) return plan_wgrad_memo(&L.plan, (float2*)(scratch + L.memo), at(2), area, s);
         return plan_pass(&L.plan, ZNN_PASS_WGRAD, at(0), at(1), at(2), nullptr, area, nullptr, s);
     }

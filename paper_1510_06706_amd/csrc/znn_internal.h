@@ -78,12 +78,6 @@ struct Tuning {
     bool conv_no_tail;          // ZNN_CONV_NO_TAIL: pad the last maps to a 16-row tile instead of an 8-map block
     bool conv_no_parts;         // ZNN_CONV_NO_PARTS: fp32 matrix instructions where the split kernel would run
     int  conv_tile[4];          // ZNN_CONV_TILE="NV,Tz,Ty,Tx": pin the output box (0 = not pinned)
-    int  wgrad_halves;          // ZNN_WGRAD_HALVES: 1 = four waves, 2 = eight waves per workgroup
-    int  wgrad_maxnj;           // ZNN_WGRAD_MAXNJ: most 16-map tiles per workgroup
-    int  wgrad_own_waves;       // ZNN_WGRAD_OWN_WAVES: 4 or 8 waves per workgroup in that layout
-    int  wgrad_own_columns_from; // ZNN_WGRAD_OWN_COLUMNS_FROM: column tiles from which every wave owns columns
-    int  wgrad_stride_mod;      // ZNN_WGRAD_STRIDE_MOD: residue modulo 32 of the LDS map stride
-    bool wgrad_slow_loader;     // ZNN_WGRAD_SLOW_LOADER: general tile loader everywhere
     int  fft_mac_z0;            // ZNN_FFT_MAC_Z0: frequencies per thread of the folded multiply-accumulate / 4
     bool fft_mac_valu;          // ZNN_FFT_MAC_VALU: folded multiply-accumulate on the vector ALUs only
     bool fft_wgrad_plain;       // ZNN_FFT_WGRAD_PLAIN: per-z pruned DFT instead of the radix-4 grouped one
@@ -117,10 +111,31 @@ int mfma_conv_packed(const Geom& g, bool backward, const float* src, const float
                      const Finish& finish, hipStream_t s);
 int mfma_conv_sum(const Geom& g, bool backward, const float* partial, float* dst, hipStream_t s);
 bool mfma_wgrad_supported(const Geom& g);
-size_t mfma_wgrad_workspace(const Geom& g);
-// partial sums only; `sum` says how to add them: gw[e] = sum over splits in the order of k_wgrad_reduce / k_wgrad_reduce4
-struct WgradSum { int ksplit, Mpad, Npad, mapmajor, four; };
-int mfma_wgrad_partial(const Geom& g, const float* in, const float* gout, float* partial, WgradSum* sum, hipStream_t s);
+size_t mfma_wgrad_workspace(const Geom& g);     // the two together:
+size_t mfma_wgrad_sums_bytes(const Geom& g);    // the shares' partial sums
+size_t mfma_wgrad_copies_bytes(const Geom& g);  // what the pass itself needs
+// Partial sums of a kernel gradient, [share][tap group][Mpad][Npad], and how to add them: in ascending order of the shares
+// (k_wgrad_sum), or four interleaved sums per element (k_wgrad_sum4).  Columns of a group are (input map, tap of the group).
+struct WgradSum { int ksplit, planes, planes_b, Mpad, Npad, f, GA, GB, k[3], columns, four; long slots; };
+int mfma_wgrad_partial(const Geom& g, const float* in, const float* gout, float* partial, void* copies, WgradSum* sum, hipStream_t s);
+// Element number t of (output map, tap group, column): where a share has it and where the gradient does.  false: a tap
+// behind the last one.
+__device__ __forceinline__ bool wgrad_slot(const WgradSum& S, long t, long& from, long& to)
+{
+    unsigned n, plane, j;
+    auto place = [&](auto r) {
+        n = (unsigned)(r % (unsigned)S.columns); r /= (unsigned)S.columns;
+        plane = (unsigned)(r % (unsigned)S.planes);
+        j = (unsigned)(r / (unsigned)S.planes);
+    };
+    if (S.slots <= 4294967295L) place((unsigned)t);         // uniform
+    else place((unsigned long)t);
+    const unsigned tg = S.GA * S.GB * S.k[2], i = n / tg, q = n - i * tg, c = q % S.k[2], r = q / S.k[2];
+    const int b = plane % S.planes_b * S.GB + r % S.GB, a = plane / S.planes_b * S.GA + r / S.GB;
+    from = ((long)plane * S.Mpad + j) * S.Npad + n;
+    to = ((((long)j * S.f + i) * S.k[0] + a) * S.k[1] + b) * S.k[2] + c;
+    return a < S.k[0] && b < S.k[1];
+}
 // expected seconds of a pass (choice between the methods where nothing has been measured)
 double mfma_conv_seconds(const Geom& g, bool backward);
 double mfma_wgrad_seconds(const Geom& g);

@@ -1,4 +1,4 @@
-"""The direct kernels on operands split into three bf16 parts (forward, backward): edges of their tiles, sublattices of sparse
+"""The direct kernels on operands split into three bf16 parts: edges of their tiles, sublattices of sparse
 taps, shares of the input maps, and operands that are not finite.
 
 The bound is derived, element by element, from S = sum of |products| (the oracle on absolute values): what the split leaves
@@ -98,4 +98,68 @@ def test_operands_that_are_not_finite_act_as_in_fp32(value):
     ws[17, 3, 1, 2, 0] = value
     xw = x * 2.0 ** -10
     same(p.fwd(dev(xw), dev(ws)), oracle.conv3d_fwd(xw, ws), limit(oracle.conv3d_fwd(np.abs(xw), np.abs(ws)), f))
+    p.close()
+
+
+GRADIENTS = [
+    # f, fo, n, k, s: pieces of the axes with and without a remainder, tap groups, column groups, shares
+    (1, 1, (1, 1, 5), (1, 1, 1), (1, 1, 1)),            # fewer voxels than pieces
+    (1, 40, (9, 10, 11), (3, 3, 3), (1, 1, 1)),         # all taps in one group
+    (3, 5, (2, 3, 50), (2, 2, 7), (1, 1, 1)),
+    (16, 16, (8, 16, 32), (1, 1, 1), (1, 1, 1)),        # nothing left over anywhere
+    (17, 33, (11, 13, 15), (2, 3, 4), (1, 1, 1)),
+    (40, 40, (14, 13, 12), (3, 3, 3), (1, 1, 1)),
+    (24, 81, (5, 20, 19), (2, 3, 4), (1, 1, 1)),        # two groups of map tiles
+    (130, 7, (6, 6, 9), (2, 2, 2), (1, 1, 1)),          # column groups
+    (6, 33, (1, 60, 47), (1, 11, 11), (1, 1, 1)),       # 2D
+    (12, 12, (15, 14, 13), (3, 3, 3), (2, 3, 4)),       # residues of different extents
+    (10, 10, (9, 9, 11), (3, 3, 3), (4, 4, 5)),         # result extents below the tap spacing
+    (8, 24, (3, 30, 30), (1, 3, 3), (3, 2, 2)),         # spacing on an axis of one tap
+    (5, 5, (30, 9, 10), (17, 9, 7), (1, 1, 1)),
+    (4, 6, (40, 41, 42), (3, 3, 3), (1, 1, 1)),         # many shares, four sums per element
+]
+
+
+@pytest.mark.parametrize("f,fo,n,k,s", GRADIENTS)
+def test_kernel_gradient_stays_within_the_bound_of_the_split(f, fo, n, k, s):
+    x, w, g = tensors(f, fo, n, k, s, 9103)
+    p = znn.Plan(f, fo, n, k, "direct", s)
+    gw = p.wgrad(dev(x), dev(g)).cpu().numpy()
+    voxels = g[0].size
+    # a step per 32 voxels, remainders of pieces and tiles at most double them; waves and shares
+    limit = (2 * (voxels // 32) + 600) * 2.0 ** -24 * oracle.conv3d_wgrad(np.abs(x), np.abs(g), s)
+    assert np.all(np.abs(gw.astype(np.float64) - oracle.conv3d_wgrad(x, g, s)) <= limit)
+    p.close()
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan, 3.4e38])
+@pytest.mark.parametrize("s", [(1, 1, 1), (2, 1, 2)])
+def test_kernel_gradient_of_images_that_are_not_finite_acts_as_in_fp32(value, s):
+    f, fo, n, k = 9, 20, (11, 12, 13), (3, 3, 3)
+    x, w, g = tensors(f, fo, n, k, s, 9104)
+    x[4, 5, 6, 7] = value
+    g *= 2.0 ** -10
+    p = znn.Plan(f, fo, n, k, "direct", s)
+    got, ref = p.wgrad(dev(x), dev(g)).cpu().numpy().astype(np.float64), oracle.conv3d_wgrad(x, g, s)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref))
+    ok = np.isfinite(ref)
+    ref_abs = oracle.conv3d_wgrad(np.abs(x), np.abs(g), s)
+    assert np.all(np.abs(got[ok] - ref[ok]) <= (2 * g[0].size + 600) * 2.0 ** -24 * ref_abs[ok])
+    p.close()
+
+
+@pytest.mark.parametrize("f,fo,n,k,s", [
+    (8, 8, (131, 120, 121), (3, 3, 3), (1, 1, 1)),      # slabs of planes
+    (8, 9, (1, 1300, 1201), (1, 3, 2), (1, 1, 1)),      # slabs of rows
+    (6, 8, (140, 121, 120), (3, 2, 2), (3, 2, 2)),      # slabs of one residue
+])
+def test_kernel_gradient_of_large_layers_in_slabs(f, fo, n, k, s):
+    x, w, g = tensors(f, fo, n, k, s, 9105)
+    p = znn.Plan(f, fo, n, k, "direct", s)
+    assert (f * x[0].size + fo * g[0].size) * 6 * 1.2 > 96 << 20 and p.workspace_bytes(2) < 192 << 20
+    gw = p.wgrad(dev(x), dev(g)).cpu().numpy()
+    ref, ref_abs = oracle.conv3d_wgrad(x, g, s), oracle.conv3d_wgrad(np.abs(x), np.abs(g), s)
+    # sums this long are far inside the worst case: a tenth of it still leaves a lost or doubled slab no room
+    assert np.all(np.abs(gw.astype(np.float64) - ref) <= 0.1 * (2 * (g[0].size // 32) + 600) * 2.0 ** -24 * ref_abs)
     p.close()
