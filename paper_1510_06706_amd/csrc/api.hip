@@ -75,11 +75,7 @@ const Tuning& tuning()
         auto num = [](const char* name, int dflt) { const char* e = getenv(name); return e && *e ? atoi(e) : dflt; };
         Tuning v = {};
         v.log = flag("ZNN_LOG");
-        v.conv_u1 = flag("ZNN_CONV_U1");
-        v.conv_no_wl = flag("ZNN_CONV_NO_WL");
         v.conv_no_split = flag("ZNN_CONV_NO_SPLIT");
-        v.conv_no_tail = flag("ZNN_CONV_NO_TAIL");
-        v.conv_no_parts = flag("ZNN_CONV_NO_PARTS");
         if (const char* e = getenv("ZNN_CONV_TILE"))
             if (sscanf(e, "%d,%d,%d,%d", &v.conv_tile[0], &v.conv_tile[1], &v.conv_tile[2], &v.conv_tile[3]) != 4)
                 v.conv_tile[0] = v.conv_tile[1] = v.conv_tile[2] = v.conv_tile[3] = 0;
@@ -188,7 +184,7 @@ static int model_choice(const Geom& g)
     if (g.Nz > kMaxFftExtent || g.Ny > kMaxFftExtent || g.Nx > kMaxFftExtent) return ZNN_DIRECT;
     const FftWay w = fft_way(g);
     const double fft = w.tile.on ? w.tile.seconds : whole_volume_seconds(g, w.fold);
-    const double direct = mfma_conv_seconds(g, false) + mfma_conv_seconds(g, true) + mfma_wgrad_seconds(g);
+    const double direct = conv_seconds(g, false) + conv_seconds(g, true) + grad_seconds(g);
     return 1.2 * fft + 80e-6 < 1.1 * direct + 16e-6 ? ZNN_FFT : ZNN_DIRECT;
 }
 

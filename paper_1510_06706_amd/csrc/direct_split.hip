@@ -1,12 +1,11 @@
-// Host side of the split direct kernel (direct_split_impl.h): search for the workgroup's box and launch.  Weights are packed
-// by k_pack_weights (direct_mfma.hip) together with those of other layers.
+// Host side of the split direct kernel (direct_split_impl.h): packing of the weights, search for the workgroup's box, launch.
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
 #include <vector>
 
-#include "direct_split.h"
+#include "direct.h"
 #include "direct_split_impl.h"
 
 namespace znn {
@@ -15,6 +14,65 @@ namespace {
 
 using split::SplitFn;
 using split::SplitTile;
+
+// Weights for the split kernel: a thread makes the three parts of eight input maps' weights at one tap, [group][chunk][step]
+// [16-map tile][part][lane].  The leading part of a number that would round to infinity is cut instead, and an infinity or
+// NaN has no other parts, so that the parts always add up to the weight.
+__device__ __forceinline__ void pack_split(const PackItem& P, long t)
+{
+    const int taps = P.taps, steps = (taps + split::kTaps - 1) / split::kTaps;
+    const int lane = (int)(t & 63);
+    long r = t >> 6;
+    const int jt = (int)(r % P.NJ); r /= P.NJ;
+    const int s = (int)(r % steps); r /= steps;
+    const int ic = (int)(r % P.nchunk), jg = (int)(r / P.nchunk);
+    const int m = (jg * P.NJ + jt) * 16 + (lane & 15), tap = s * split::kTaps + (lane >> 4);
+    const int fM = P.backward ? P.f : P.fo, fK = P.backward ? P.fo : P.f;
+    float v[8];
+    split::uintx4 part[3];
+    bool odd = false;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int k = ic * split::kMaps + e;
+        v[e] = 0.f;
+        if (m < fM && k < fK && tap < taps)
+            v[e] = P.backward ? P.w[((long)k * P.f + m) * taps + (taps - 1 - tap)] : P.w[((long)m * P.f + k) * taps + tap];
+        odd = odd || !(fabsf(v[e]) < 3.38e38f);
+    }
+    if (!odd) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) part[p] = split::take_part8(v);
+    } else {
+        part[0] = part[1] = part[2] = split::uintx4{0u, 0u, 0u, 0u};
+        for (int e = 0; e < 8; ++e) {
+            float x = v[e];
+            for (int p = 0; p < 3; ++p) {
+                unsigned u = __builtin_bit_cast(unsigned, x);
+                if (x != x) u |= 0x400000u;                                                 // stays a NaN
+                u &= 0xffff0000u;
+                part[p][e >> 1] |= e & 1 ? u : u >> 16;
+                x = fabsf(x) <= 3.4028234e38f ? x - __builtin_bit_cast(float, u) : 0.f;
+            }
+        }
+    }
+    split::uintx4* out = reinterpret_cast<split::uintx4*>(P.wp) + (t >> 6) * 3 * 64 + lane;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) out[p * 64] = part[p];
+}
+
+// Several layers and passes at a time: the weights of a round take one launch instead of one per convolution.  N = 1 serves the
+// calls of a single layer, whose launch then carries 80 bytes of arguments instead of 2 KB.
+constexpr int kPackItems = 24;
+template <int N> struct PackArgs { PackItem item[N]; unsigned first[N]; int n; };
+
+template <int N>
+__global__ void __launch_bounds__(256) k_pack_weights(PackArgs<N> A)
+{
+    int q = 0;
+    if (N > 1) while (q + 1 < A.n && blockIdx.x >= A.first[q + 1]) ++q;        // uniform
+    const long t = (long)(blockIdx.x - A.first[q]) * 256 + threadIdx.x;
+    if (t < A.item[q].total) pack_split(A.item[q], t);
+}
 
 constexpr int kCUs = 256;
 constexpr size_t kLds = 160 * 1024;
@@ -165,14 +223,15 @@ SplitChoice choose_split(const Geom& g, bool backward)
     }
     const Pass P = pass_of(g, backward);
     e.choice = SplitChoice{};
-    // Chunks hold eight input maps: with four and less, half of the products and more would be padding, and the fp32 kernel
-    // (chunks of four) is the better one.
-    if (P.fK > 4 && !tuning().conv_no_parts) e.choice = search(P);
+    // a lane's byte offset in a source map has 32 bits
+    if ((backward ? g.ovol() : g.nvol()) < (1L << 28)) e.choice = search(P);
     std::lock_guard<std::mutex> hold(lock);
     if (memo.size() >= 256) memo.erase(memo.begin());
     memo.push_back(e);
     return e.choice;
 }
+
+double split_seconds(const SplitChoice& c) { return c.cost / 1.9e9 + 2e-6; }
 
 // Packed weights; one step of padding behind them, which the kernel fetches ahead.
 size_t split_packed_bytes(const SplitChoice& c)
@@ -180,10 +239,42 @@ size_t split_packed_bytes(const SplitChoice& c)
     return align256(((size_t)c.jgroups * c.nchunk * c.steps + 1) * c.NJ * 3 * 64 * 16);
 }
 
-int split_conv(const Geom& g, bool backward, const float* src, const void* wp, float* dst, float* partial, const Finish& finish,
-               hipStream_t s)
+PackItem split_pack_item(const Geom& g, const SplitChoice& c, bool backward, const float* w, void* wp)
 {
-    const SplitChoice c = choose_split(g, backward);
+    PackItem p = {};
+    p.w = w; p.wp = wp;
+    p.f = g.f; p.fo = g.fo;
+    p.taps = (int)g.kvol();
+    p.backward = backward ? 1 : 0;
+    p.NJ = c.NJ; p.nchunk = c.nchunk;
+    p.total = (long)c.jgroups * c.nchunk * c.steps * c.NJ * 64;
+    return p;
+}
+
+template <int N>
+static void pack_launch(const PackItem* items, int n, hipStream_t s)
+{
+    PackArgs<N> A = {};
+    unsigned blocks = 0;
+    for (; A.n < n; ++A.n) {
+        A.item[A.n] = items[A.n];
+        A.first[A.n] = blocks;
+        blocks += (unsigned)((items[A.n].total + 255) / 256);
+    }
+    ZNN_LAUNCH("weight packing", s, k_pack_weights<N>, dim3(blocks), dim3(256), 0, A);
+}
+
+int split_pack_weights(const PackItem* items, int n, hipStream_t s)
+{
+    if (n == 1) pack_launch<1>(items, 1, s);
+    else
+        for (int i0 = 0; i0 < n; i0 += kPackItems) pack_launch<kPackItems>(items + i0, std::min(kPackItems, n - i0), s);
+    return check_launch("weight packing");
+}
+
+int split_conv(const Geom& g, const SplitChoice& c, bool backward, const float* src, const void* wp, float* dst, float* partial,
+               const Finish& finish, hipStream_t s)
+{
     const Pass p = pass_of(g, backward);
     SplitTile P = {};
     P.src = src; P.wp = (const split::uintx4*)wp; P.dst = dst;

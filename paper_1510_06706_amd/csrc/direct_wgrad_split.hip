@@ -7,6 +7,7 @@
 #include <mutex>
 #include <vector>
 
+#include "direct.h"
 #include "direct_wgrad_split_impl.h"
 
 namespace znn {
@@ -58,7 +59,7 @@ __global__ void __launch_bounds__(256) k_split_images(SplitArgs A)
 
 // The sums over the shares in ascending order.  Threads run along the columns of the partial sums, which are read once per share;
 // gw[j][i][tap] of a column is written wherever it lies.
-struct GradSumArgs { const float* partial; float* gw; WgradSum S; long slots; int fo; };
+struct GradSumArgs { const float* partial; float* gw; WgradSum S; long slots; };
 __global__ void __launch_bounds__(256) k_wgrad_sum(GradSumArgs A)
 {
     const long t = (long)blockIdx.x * 256 + threadIdx.x;
@@ -299,9 +300,9 @@ Slabs slabs_of(const Geom& g, const GradChoice& c)
 
 }  // namespace
 
-bool mfma_wgrad_supported(const Geom& g) { return choose(g).ok; }
+bool split_grad_supported(const Geom& g) { return choose(g).ok; }
 
-double mfma_wgrad_seconds(const Geom& g)
+double split_grad_seconds(const Geom& g)
 {
     const GradChoice c = choose(g);
     if (!c.ok) return 2.0 * g.f * g.fo * (double)g.ovol() * g.kvol() / 1e12;
@@ -312,22 +313,20 @@ double mfma_wgrad_seconds(const Geom& g)
 static size_t columns_of(const Geom& g, const GradChoice& c) { return ((size_t)g.f * c.GA * c.GB * g.kx + 15) / 16 * 16; }
 
 // the partial sums, and the copies of the images that only the pass itself needs
-size_t mfma_wgrad_sums_bytes(const Geom& g)
+size_t split_grad_sums_bytes(const Geom& g)
 {
     const GradChoice c = choose(g);
     if (!c.ok) return 0;
     return align256((size_t)c.shares * c.planes_a * c.planes_b * g.fo * columns_of(g, c) * sizeof(float));
 }
 
-size_t mfma_wgrad_copies_bytes(const Geom& g)
+size_t split_grad_copies_bytes(const Geom& g)
 {
     const GradChoice c = choose(g);
     return c.ok ? slabs_of(g, c).bytes : 0;
 }
 
-size_t mfma_wgrad_workspace(const Geom& g) { return mfma_wgrad_sums_bytes(g) + mfma_wgrad_copies_bytes(g); }
-
-int mfma_wgrad_partial(const Geom& g, const float* in, const float* gout, float* partial, void* copies, WgradSum* sum, hipStream_t s)
+int split_grad(const Geom& g, const float* in, const float* gout, float* partial, void* copies, WgradSum* sum, hipStream_t s)
 {
     const GradChoice c = choose(g);
     if (!c.ok) return fail(ZNN_EUNSUPPORTED, "no tile configuration fits this shape");
@@ -408,16 +407,12 @@ int mfma_wgrad_partial(const Geom& g, const float* in, const float* gout, float*
     return check_launch("direct kernel gradient (MFMA)");
 }
 
-int mfma_wgrad(const Geom& g, const float* in, const float* gout, float* gw, void* ws, hipStream_t s)
+int sum_shares(const WgradSum& S, const float* partial, float* gw, hipStream_t s)
 {
     GradSumArgs A = {};
-    const int rc = mfma_wgrad_partial(g, in, gout, (float*)ws, (char*)ws + mfma_wgrad_sums_bytes(g), &A.S, s);
-    if (rc != ZNN_OK) return rc;
-    A.partial = (const float*)ws; A.gw = gw; A.slots = A.S.slots; A.fo = g.fo;
-    if (A.S.four)
-        ZNN_LAUNCH("kernel gradient reduction", s, k_wgrad_sum4, dim3((unsigned)((A.slots + 63) / 64)), dim3(256), 0, A);
-    else
-        ZNN_LAUNCH("kernel gradient reduction", s, k_wgrad_sum, dim3((unsigned)((A.slots + 255) / 256)), dim3(256), 0, A);
+    A.S = S; A.partial = partial; A.gw = gw; A.slots = S.slots;
+    if (S.four) ZNN_LAUNCH("kernel gradient reduction", s, k_wgrad_sum4, dim3((unsigned)((S.slots + 63) / 64)), dim3(256), 0, A);
+    else        ZNN_LAUNCH("kernel gradient reduction", s, k_wgrad_sum, dim3((unsigned)((S.slots + 255) / 256)), dim3(256), 0, A);
     return check_launch("kernel gradient reduction");
 }
 

@@ -391,8 +391,8 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
         room.push_back(L.plan.round_memory);
         if (L.plan.mode == ZNN_DIRECT) {
             for (int b = 0; b < 2; ++b)
-                if (L.step[b] >= 0 && mfma_conv_supported(L.plan.g, b == 1) && !written_between(P, L.w, 0, L.step[b])) {
-                    L.packed[b] = hold(l, mfma_conv_packed_bytes(L.plan.g, b == 1));
+                if (L.step[b] >= 0 && conv_takes_packed(L.plan.g, b == 1) && !written_between(P, L.w, 0, L.step[b])) {
+                    L.packed[b] = hold(l, conv_packed_bytes(L.plan.g, b == 1));
                     if (L.packed[b] != kNone) P.steps[0].skip = false;
                 }
         } else if (L.step[0] >= 0 && L.step[1] >= 0) {
@@ -419,8 +419,8 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
                 P.bias_steps.push_back(i);
             } else if (s.kind == ZNN_OP_CONV_WGRAD && s.op.buf[2] == g) {
                 const Layer& L = P.layers[s.layer];
-                if (L.plan.mode != ZNN_DIRECT || !mfma_wgrad_supported(L.plan.g) || touched_between(P, g, i, at_update)) continue;
-                s.own = hold(s.layer, mfma_wgrad_sums_bytes(L.plan.g));
+                if (L.plan.mode != ZNN_DIRECT || touched_between(P, g, i, at_update)) continue;
+                s.own = hold(s.layer, grad_sums_bytes(L.plan.g));
                 if (s.own != kNone) P.completes[u] = i;
             }
         }
@@ -433,9 +433,9 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
         if (s.layer < 0) continue;
         const Layer& L = P.layers[s.layer];
         const Geom& g = L.plan.g;
-        if (s.kind == ZNN_OP_CONV_WGRAD) s.pass_bytes = s.own != kNone ? mfma_wgrad_copies_bytes(g) : plan_pass_bytes(&L.plan, s.kind, false);
+        if (s.kind == ZNN_OP_CONV_WGRAD) s.pass_bytes = s.own != kNone ? grad_copies_bytes(g) : plan_pass_bytes(&L.plan, s.kind, false);
         else if (L.packed[s.kind] != kNone) {
-            const int splits = mfma_conv_splits(g, s.kind == ZNN_OP_CONV_BWD);
+            const int splits = conv_splits(g, s.kind == ZNN_OP_CONV_BWD);
             s.pass_bytes = splits > 1 ? sizeof(float) * splits * (s.kind ? (size_t)g.f * g.nvol() : (size_t)g.fo * g.ovol()) : 0;
         } else s.pass_bytes = plan_pass_bytes(&L.plan, s.kind, L.spectra != kNone);
         need[s.stream] = std::max(need[s.stream], align256(s.pass_bytes));
@@ -557,8 +557,8 @@ int run_pack(const znn_program& P, float* const* buf, char* scratch, hipStream_t
     for (const Layer& L : P.layers)
         for (int b = 0; b < 2; ++b)
             if (L.packed[b] != kNone)
-                items.push_back(mfma_conv_pack_item(L.plan.g, b == 1, buf[L.w], (float*)(scratch + L.packed[b])));
-    return mfma_pack_weights(items.data(), (int)items.size(), s);
+                items.push_back(conv_pack_item(L.plan.g, b == 1, buf[L.w], scratch + L.packed[b]));
+    return conv_pack_weights(items.data(), (int)items.size(), s);
 }
 
 int run_bias(const znn_program& P, const std::vector<int>& steps, float* const* buf, char* scratch, hipStream_t s)
@@ -618,7 +618,7 @@ int run_conv(znn_program& P, Step& t, float* const* buf, char* scratch, hipStrea
     char* const area = scratch + P.area[t.stream];
     auto at = [&](int q) -> float* { return o.buf[q] < 0 ? nullptr : buf[o.buf[q]]; };
     if (t.kind == ZNN_OP_CONV_WGRAD) {
-        if (t.own != kNone) return mfma_wgrad_partial(g, at(0), at(1), (float*)(scratch + t.own), area, &t.sum, s);
+        if (t.own != kNone) return grad_partial(g, at(0), at(1), (float*)(scratch + t.own), area, &t.sum, s);
         if (L.memo != kNone) return plan_wgrad_memo(&L.plan, (float2*)(scratch + L.memo), at(2), area, s);
         return plan_pass(&L.plan, ZNN_PASS_WGRAD, at(0), at(1), at(2), nullptr, area, nullptr, s);
     }
@@ -629,10 +629,11 @@ int run_conv(znn_program& P, Step& t, float* const* buf, char* scratch, hipStrea
     F.fn = o.fn;
     bool finished = !F.y && !F.deriv;
     int rc;
-    if (L.packed[bwd] != kNone) {
-        const int splits = mfma_conv_splits(g, bwd);
+    const bool few = L.plan.mode == ZNN_DIRECT && !conv_takes_packed(g, bwd);
+    if (few || L.packed[bwd] != kNone) {
+        const int splits = conv_splits(g, bwd);
         const bool inside = !finished && splits == 1 && o.fn == ZNN_RECTIFY;
-        rc = mfma_conv_packed(g, bwd, at(0), (const float*)(scratch + L.packed[bwd]), at(2), (float*)area, inside ? F : Finish{}, s);
+        rc = conv_pass(g, bwd, at(0), at(1), few ? nullptr : scratch + L.packed[bwd], at(2), (float*)area, inside ? F : Finish{}, s);
         if (rc != ZNN_OK) return rc;
         if (splits > 1) {
             if (F.deriv) {
@@ -643,7 +644,7 @@ int run_conv(znn_program& P, Step& t, float* const* buf, char* scratch, hipStrea
                 ZNN_LAUNCH("sum of shares, transfer", s, k_finish_fwd, dim3(blocks_of(g.ovol()), (unsigned)g.fo), dim3(256), 0,
                            (const float*)area, at(2), F.bias, F.y, (int)g.ovol(), count, splits, o.fn);
                 finished = true;
-            } else rc = mfma_conv_sum(g, bwd, (const float*)area, at(2), s);
+            } else rc = conv_sum(g, bwd, (const float*)area, at(2), s);
             if (rc != ZNN_OK) return rc;
         } else finished = finished || inside;
     } else {

@@ -72,12 +72,8 @@ __device__ __forceinline__ unsigned fdiv(unsigned n, FastDiv f)
 // creation at the latest), and never on a launch path; none of them changes a data layout.
 struct Tuning {
     bool log;                   // ZNN_LOG: print launch configurations to stderr
-    bool conv_u1;               // ZNN_CONV_U1: walk the taps of the direct convolution one at a time
-    bool conv_no_wl;            // ZNN_CONV_NO_WL: never stage a chunk's weights in LDS
     bool conv_no_split;         // ZNN_CONV_NO_SPLIT: never split the input maps over workgroups
-    bool conv_no_tail;          // ZNN_CONV_NO_TAIL: pad the last maps to a 16-row tile instead of an 8-map block
-    bool conv_no_parts;         // ZNN_CONV_NO_PARTS: fp32 matrix instructions where the split kernel would run
-    int  conv_tile[4];          // ZNN_CONV_TILE="NV,Tz,Ty,Tx": pin the output box (0 = not pinned)
+    int  conv_tile[4];          // ZNN_CONV_TILE="NV,Tz,Ty,Tx": pin the output box, NV 16-voxel tiles (0 = not pinned)
     int  fft_mac_z0;            // ZNN_FFT_MAC_Z0: frequencies per thread of the folded multiply-accumulate / 4
     bool fft_mac_valu;          // ZNN_FFT_MAC_VALU: folded multiply-accumulate on the vector ALUs only
     bool fft_wgrad_plain;       // ZNN_FFT_WGRAD_PLAIN: per-z pruned DFT instead of the radix-4 grouped one
@@ -97,27 +93,25 @@ int direct_fwd(const Geom& g, const float* in, const float* w, float* out, void*
 int direct_bwd(const Geom& g, const float* gout, const float* w, float* gin, void* ws, hipStream_t s);
 int direct_wgrad(const Geom& g, const float* in, const float* gout, float* gw, void* ws, hipStream_t s);
 size_t direct_workspace_bytes(const Geom& g, int pass);
-// The tiled kernels in pieces, for rounds that pack the weights of all layers at once and finish several sums in one launch
-struct PackItem { const float* w; float* wp; int f, fo, kz, ky, kx, backward, split, NJ, nchunk, tail; long total; };
-bool mfma_conv_supported(const Geom& g, bool backward);
-PackItem mfma_conv_pack_item(const Geom& g, bool backward, const float* w, float* wp);
-int mfma_pack_weights(const PackItem* items, int n, hipStream_t s);
-size_t mfma_conv_packed_bytes(const Geom& g, bool backward);
-int mfma_conv_splits(const Geom& g, bool backward);
+// The passes in pieces, for rounds that pack the weights of all layers at once and finish several sums in one launch
+struct PackItem { const float* w; void* wp; int f, fo, taps, backward, NJ, nchunk; long total; };
+bool conv_takes_packed(const Geom& g, bool backward);       // else it takes the weights as they are
+PackItem conv_pack_item(const Geom& g, bool backward, const float* w, void* wp);
+int conv_pack_weights(const PackItem* items, int n, hipStream_t s);
+size_t conv_packed_bytes(const Geom& g, bool backward);
+int conv_splits(const Geom& g, bool backward);
 // what a pass does with its finished sums v: y = fn(v + bias[map]) beside v (forward), or v times fn's derivative at the
-// forward result `deriv` (backward); the kernel itself takes the rectifier only
+// forward result `deriv` (backward); the kernels themselves take the rectifier only
 struct Finish { float* y; const float* bias; const float* deriv; int fn; };
-int mfma_conv_packed(const Geom& g, bool backward, const float* src, const float* wp, float* dst, float* partial,
-                     const Finish& finish, hipStream_t s);
-int mfma_conv_sum(const Geom& g, bool backward, const float* partial, float* dst, hipStream_t s);
-bool mfma_wgrad_supported(const Geom& g);
-size_t mfma_wgrad_workspace(const Geom& g);     // the two together:
-size_t mfma_wgrad_sums_bytes(const Geom& g);    // the shares' partial sums
-size_t mfma_wgrad_copies_bytes(const Geom& g);  // what the pass itself needs
+int conv_pass(const Geom& g, bool backward, const float* src, const float* w, const void* wp, float* dst, float* partial,
+              const Finish& finish, hipStream_t s);
+int conv_sum(const Geom& g, bool backward, const float* partial, float* dst, hipStream_t s);
+size_t grad_sums_bytes(const Geom& g);          // the shares' partial sums
+size_t grad_copies_bytes(const Geom& g);        // what the pass itself needs
 // Partial sums of a kernel gradient, [share][tap group][Mpad][Npad], and how to add them: in ascending order of the shares
 // (k_wgrad_sum), or four interleaved sums per element (k_wgrad_sum4).  Columns of a group are (input map, tap of the group).
 struct WgradSum { int ksplit, planes, planes_b, Mpad, Npad, f, GA, GB, k[3], columns, four; long slots; };
-int mfma_wgrad_partial(const Geom& g, const float* in, const float* gout, float* partial, void* copies, WgradSum* sum, hipStream_t s);
+int grad_partial(const Geom& g, const float* in, const float* gout, float* partial, void* copies, WgradSum* sum, hipStream_t s);
 // Element number t of (output map, tap group, column): where a share has it and where the gradient does.  false: a tap
 // behind the last one.
 __device__ __forceinline__ bool wgrad_slot(const WgradSum& S, long t, long& from, long& to)
@@ -137,8 +131,8 @@ __device__ __forceinline__ bool wgrad_slot(const WgradSum& S, long t, long& from
     return a < S.k[0] && b < S.k[1];
 }
 // expected seconds of a pass (choice between the methods where nothing has been measured)
-double mfma_conv_seconds(const Geom& g, bool backward);
-double mfma_wgrad_seconds(const Geom& g);
+double conv_seconds(const Geom& g, bool backward);
+double grad_seconds(const Geom& g);
 
 // ---------------------------------------------------------------- FFT method
 // Layout of a layer's kernel spectra, fixed when its plan is created (or by

@@ -1,0 +1,66 @@
+"""The direct kernels on the vector ALUs (one or two input-side maps, small layers, shapes the matrix kernels do not take):
+widths of their tap groups, blocks of maps, shares of the voxels.
+
+Bounds are derived from S = sum of |products|: one rounding per product and sum, in chains of fp32 multiply-adds.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1510_06706_amd import binding as znn
+from paper_1510_06706_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # f, fo, n, k, s: groups of 1, 2, 3, 4, 5, 7 and 11 taps along x, maps around the blocks of 4 and 8
+    (1, 1, (4, 5, 6), (1, 1, 1), (1, 1, 1)),
+    (1, 4, (16, 16, 16), (3, 3, 3), (1, 1, 1)),
+    (1, 5, (6, 7, 40), (2, 1, 13), (1, 1, 1)),
+    (2, 9, (5, 9, 30), (1, 3, 22), (1, 1, 1)),
+    (1, 17, (3, 12, 31), (2, 4, 10), (1, 1, 1)),
+    (1, 8, (9, 8, 33), (3, 2, 8), (1, 1, 1)),
+    (7, 1, (9, 8, 33), (1, 2, 7), (1, 1, 1)),           # backward: one map on the input side
+    (1, 3, (21, 23, 25), (3, 2, 3), (2, 5, 4)),         # sparse taps
+    (1, 6, (1, 90, 91), (1, 11, 11), (1, 1, 1)),        # 2D, several shares
+    (2, 2, (40, 41, 43), (3, 3, 3), (1, 1, 1)),         # several shares
+    (1, 1, (18, 18, 17), (17, 17, 15), (1, 1, 1)),      # 4335 taps
+]
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a.astype(np.float32))).to("cuda:0")
+
+
+@pytest.mark.parametrize("f,fo,n,k,s", SHAPES)
+def test_passes_stay_within_the_bound_of_fp32_chains(f, fo, n, k, s):
+    x, w, g = synth.layer_tensors(synth.LayerShape("t", f, fo, n, k, 1.0, 9200, s))
+    taps, eps = k[0] * k[1] * k[2], 2.0 ** -24
+    p = znn.Plan(f, fo, n, k, "direct", s)
+
+    def close(got, ref, ref_abs, terms):
+        assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= (terms + 16) * eps * ref_abs)
+
+    a, b, c = np.abs(x), np.abs(w), np.abs(g)
+    close(p.fwd(dev(x), dev(w)), oracle.conv3d_fwd(x, w, s), oracle.conv3d_fwd(a, b, s), f * taps)
+    close(p.bwd(dev(g), dev(w)), oracle.conv3d_bwd(g, w, n, s), oracle.conv3d_bwd(c, b, n, s), fo * taps)
+    # chains of a thread, then its workgroup's tree and the shares
+    close(p.wgrad(dev(x), dev(g)), oracle.conv3d_wgrad(x, g, s), oracle.conv3d_wgrad(a, c, s), g[0].size // 64 + 32)
+    p.close()
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_values_that_are_not_finite_reach_the_results_they_belong_to(value):
+    f, fo, n, k = 1, 4, (9, 10, 11), (3, 3, 3)
+    x, w, g = synth.layer_tensors(synth.LayerShape("t", f, fo, n, k, 1.0, 9201))
+    x[0, 4, 5, 6] = value
+    g[2, 3, 3, 3] = value
+    p = znn.Plan(f, fo, n, k, "direct")
+    got = (p.fwd(dev(x), dev(w)), p.bwd(dev(g), dev(w)), p.wgrad(dev(x), dev(np.ones_like(g))))
+    ref = (oracle.conv3d_fwd(x, w), oracle.conv3d_bwd(g, w, n), oracle.conv3d_wgrad(x, np.ones_like(g)))
+    for a, b in zip(got, ref):
+        a = a.cpu().numpy()
+        assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(np.isposinf(a), np.isposinf(b))
+        assert np.array_equal(np.isneginf(a), np.isneginf(b))
+    p.close()
