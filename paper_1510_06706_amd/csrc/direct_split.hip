@@ -22,10 +22,10 @@ __device__ __forceinline__ void pack_split(const PackItem& P, long t)
 {
     const int taps = P.taps, steps = (taps + split::kTaps - 1) / split::kTaps;
     const int lane = (int)(t & 63);
-    long r = t >> 6;
-    const int jt = (int)(r % P.NJ); r /= P.NJ;
-    const int s = (int)(r % steps); r /= steps;
-    const int ic = (int)(r % P.nchunk), jg = (int)(r / P.nchunk);
+    unsigned r = (unsigned)(t >> 6);        // a wave's 3 KiB: 2^32 of them are more than any memory
+    const int jt = (int)(r % (unsigned)P.NJ); r /= (unsigned)P.NJ;
+    const int s = (int)(r % (unsigned)steps); r /= (unsigned)steps;
+    const int ic = (int)(r % (unsigned)P.nchunk), jg = (int)(r / (unsigned)P.nchunk);
     const int m = (jg * P.NJ + jt) * 16 + (lane & 15), tap = s * split::kTaps + (lane >> 4);
     const int fM = P.backward ? P.f : P.fo, fK = P.backward ? P.fo : P.f;
     float v[8];
@@ -34,9 +34,10 @@ __device__ __forceinline__ void pack_split(const PackItem& P, long t)
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const int k = ic * split::kMaps + e;
-        v[e] = 0.f;
-        if (m < fM && k < fK && tap < taps)
-            v[e] = P.backward ? P.w[((long)k * P.f + m) * taps + (taps - 1 - tap)] : P.w[((long)m * P.f + k) * taps + tap];
+        const bool in = m < fM && k < fK && tap < taps;
+        const long at = P.backward ? ((long)k * P.f + m) * taps + (taps - 1 - tap) : ((long)m * P.f + k) * taps + tap;
+        const float x = P.w[in ? at : 0];       // all eight loads are in flight together
+        v[e] = in ? x : 0.f;
         odd = odd || !(fabsf(v[e]) < 3.38e38f);
     }
     if (!odd) {
@@ -172,6 +173,7 @@ SplitChoice search(const Pass& P)
                     const int fit = std::max(1, std::min(most, (int)(kLds / lds)));
                     const int cz = (az.e + Tz - 1) / Tz, cy = (ay.e + Ty - 1) / Ty, cx = (ax.e + Tx - 1) / Tx;
                     const long blocks = (long)cz * cy * cx * phases;
+                    if ((double)blocks * std::max({phases, cx, cy}) >= 4294967296.0) continue;      // fdiv of workgroup numbers
                     // constants fitted to the times of 900 boxes on 22 layers (standard deviation 15 %)
                     const double stage = 4.0 * hvol * (1.0 + 0.06 * (ax.sp - 1));
                     const double fixed = 5200.0 + 11.5 * cap * NJ;
@@ -295,6 +297,10 @@ int split_conv(const Geom& g, const SplitChoice& c, bool backward, const float* 
     P.partial = partial;
     P.y = finish.y; P.bias = finish.bias; P.deriv = finish.deriv;
     P.dHX = make_fastdiv((unsigned)c.H[2]); P.dHY = make_fastdiv((unsigned)c.H[1]);
+    P.dTX = make_fastdiv((unsigned)c.T[2]); P.dTY = make_fastdiv((unsigned)c.T[1]);
+    P.dKX = make_fastdiv((unsigned)P.kx); P.dKY = make_fastdiv((unsigned)P.ky);
+    P.dPH = make_fastdiv((unsigned)P.phases); P.dQX = make_fastdiv((unsigned)P.qx); P.dQY = make_fastdiv((unsigned)P.qy);
+    P.dCX = make_fastdiv((unsigned)P.cx); P.dCY = make_fastdiv((unsigned)P.cy);
     if (log_enabled())
         fprintf(stderr, "[znn] conv split (%s): NJ=%d jgroups=%d NV=%d waves=%d tile=%dx%dx%d halo=%dx%dx%d blocks=%ld splits=%d lds=%zu cost=%.0f\n",
                 backward ? "bwd" : "fwd", c.NJ, c.jgroups, c.NV, c.NW, c.T[0], c.T[1], c.T[2], c.H[0], c.H[1], c.H[2], total, c.splits,

@@ -56,7 +56,7 @@ struct SplitTile {
     float* y;               // where not NULL: y = max(result + bias[map], 0) beside the result
     const float* bias;
     const float* deriv;     // where not NULL: the result is zero where this forward result of a rectifier is zero
-    FastDiv dHX, dHY;
+    FastDiv dHX, dHY, dTX, dTY, dKX, dKY, dPH, dQX, dQY, dCX, dCY;      // H, T, k, phases, q, c (the search sees to it that they are exact)
 };
 
 using SplitFn = void (*)(SplitTile);
@@ -75,11 +75,9 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
     // they read the same cache lines.
     const int id = (blockIdx.x & 7) * P.run + (blockIdx.x >> 3);
     if (id >= P.total) return;
-    int box = id / P.phases, ph = id - box * P.phases;
-    const int fx = ph % P.qx; ph /= P.qx;
-    const int fy = ph % P.qy, fz = ph / P.qy;
-    const int bx = box % P.cx; box /= P.cx;
-    const int by = box % P.cy, bz = box / P.cy;
+    const int box = (int)fdiv((unsigned)id, P.dPH), ph = id - box * P.phases;
+    const int pr = (int)fdiv((unsigned)ph, P.dQX), fx = ph - pr * P.qx, fz = (int)fdiv((unsigned)pr, P.dQY), fy = pr - fz * P.qy;
+    const int br = (int)fdiv((unsigned)box, P.dCX), bx = box - br * P.cx, bz = (int)fdiv((unsigned)br, P.dCY), by = br - bz * P.cy;
     const int z0 = bz * P.Tz, y0 = by * P.Ty, x0 = bx * P.Tx;       // on the sublattice
     const int Ttot = P.Tz * P.Ty * P.Tx;
     const long splane = (long)P.sy * P.sx, svol = P.sz * splane;
@@ -87,10 +85,17 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
     const int jg = blockIdx.y;
     const int ic0 = blockIdx.z * P.cps, ic1 = min(P.nchunk, ic0 + P.cps);
 
+    auto place = [&](int t, int& tz, int& ty, int& tx) {
+        const int q = (int)fdiv((unsigned)t, P.dTX);
+        tx = t - q * P.Tx;
+        tz = (int)fdiv((unsigned)q, P.dTY);
+        ty = q - tz * P.Ty;
+    };
     // place of output voxel t of the box in a result map, -1 outside it
     auto voxel_of = [&](int t) -> long {
         if (t >= Ttot) return -1;
-        const int q = t / P.Tx, tx = t - q * P.Tx, tz = q / P.Ty, ty = q - tz * P.Ty;
+        int tz, ty, tx;
+        place(t, tz, ty, tx);
         const int z = fz + (z0 + tz) * P.spz, y = fy + (y0 + ty) * P.spy, x = fx + (x0 + tx) * P.spx;
         if (z >= P.dz || y >= P.dy || x >= P.dx) return -1;
         return z * dplane + (long)y * P.dx + x;
@@ -101,7 +106,7 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
     const int taps = P.kz * P.ky * P.kx;
     for (int t = threadIdx.x; t < (P.steps + 2) * kTaps; t += NT) {
         const int q = min(t, taps - 1);
-        const int c = q % P.kx, r = q / P.kx, b = r % P.ky, a = r / P.ky;
+        const int r = (int)fdiv((unsigned)q, P.dKX), c = q - r * P.kx, a = (int)fdiv((unsigned)r, P.dKY), b = r - a * P.ky;
         tofs[t] = (((P.kz - 1 - a) * P.HY + (P.ky - 1 - b)) * P.HX + (P.kx - 1 - c)) * kVoxelBytes;
     }
     // halo voxels: byte offset in a source map, -1 outside the image (zeros)
@@ -119,7 +124,8 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
     for (int nv = 0; nv < NV; ++nv) {
         int t = (wave * NV + nv) * 16 + col;
         if (t >= Ttot) t = 0;
-        const int q = t / P.Tx, tx = t - q * P.Tx, tz = q / P.Ty, ty = q - tz * P.Ty;
+        int tz, ty, tx;
+        place(t, tz, ty, tx);
         voff[nv] = lbase + ((tz * P.HY + ty) * P.HX + tx) * kVoxelBytes;
     }
 
@@ -263,7 +269,8 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
                     }
 #pragma unroll
                     for (int nv = 0; nv < NV; ++nv) {
-                        const int qq = base[nv] / P.Tx, tx = base[nv] - qq * P.Tx, tz = qq / P.Ty, ty = qq - tz * P.Ty;
+                        int tz, ty, tx;
+                        place(base[nv], tz, ty, tx);
                         const int gz = fz + (z0 + tz + P.kz - 1 - a - P.pz) * P.spz, gy = fy + (y0 + ty + P.ky - 1 - b - P.py) * P.spy,
                                   gx = fx + (x0 + tx + P.kx - 1 - c - P.px) * P.spx;
                         const bool in = map < P.fK && gz >= 0 && gz < P.sz && gy >= 0 && gy < P.sy && gx >= 0 && gx < P.sx;
