@@ -564,7 +564,7 @@ __global__ void __launch_bounds__(256) k_tile_add(TileAdd A)
 // ---------------------------------------------------------------- matrix products per frequency
 // C[m][n] = sum_k A[m][k] B[k][n] (CONJ: conj(A)) for every frequency, on v_mfma_f32_16x16x4_f32.  A workgroup owns
 // 16 MT x 16 NT results of a block of 16 frequencies, each of its four waves four of the frequencies (real and imaginary
-// part in accumulators of their own).  A chunk of four k -- the depth of one MFMA -- of both operands is copied to LDS as
+// part in accumulators of their own).  A chunk of four or eight k -- one or two MFMAs deep -- of both operands is copied to LDS as
 // it lies in memory (runs of 16 frequencies = 128 bytes; 16 bytes per lane, no registers) while the chunk before it is
 // used.  A lane reads the two frequencies of its row and k with one 16-byte access; the eight 16-byte pieces of a run are
 // stored in an order that depends on the row (piece ^ (row / 2) % 8), so that sixteen rows cover all banks, and the results
@@ -584,12 +584,15 @@ struct TileProduct {
 };
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr int kChunk = 4;
+
+// k of a chunk: two MFMAs deep where the products of one would not cover the way to memory
+constexpr int chunk_of(int mt, int nt) { return mt * nt == 1 ? 8 : 4; }
 
 template <int MT, int NT, bool CONJ>
 __global__ void __launch_bounds__(256, 2) k_tile_product(TileProduct P)
 {
     constexpr int RA = 16 * MT, RB = 16 * NT;               // rows of A and B in LDS
+    constexpr int kChunk = chunk_of(MT, NT);
     constexpr int LA = RA * kChunk / 8 / 4, LB = RB * kChunk / 8 / 4;       // copies of 1 KiB (8 rows) per wave and chunk
     __shared__ float4 buf0[(RA + RB) * kChunk * 8];
     __shared__ float4 buf1[(RA + RB) * kChunk * 8];
@@ -645,15 +648,17 @@ __global__ void __launch_bounds__(256, 2) k_tile_product(TileProduct P)
     const int row = lane & 15, kl = lane >> 4;
     const int at0 = row * 8 + ((2 * wave) ^ (row >> 1)), at1 = row * 8 + ((2 * wave + 1) ^ (row >> 1));
     auto chunk = [&](const float4* buf, int k) {
-        const float4* pa = buf + kl * RA * 8;
-        const float4* pb = buf + (RA * kChunk + kl * RB) * 8;
+#pragma unroll
+        for (int s = 0; s < kChunk / 4; ++s, k += 4)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {                       // frequencies 2 h, 2 h + 1 of the wave
+            const float4* pa = buf + (4 * s + kl) * RA * 8;
+            const float4* pb = buf + (RA * kChunk + (4 * s + kl) * RB) * 8;
             const int at = h ? at1 : at0;
             float4 a[MT], b[NT];
 #pragma unroll
             for (int i = 0; i < MT; ++i) a[i] = pa[i * 128 + at];
-            if (k + kChunk > k1 && k + kl >= k1) {          // behind the last k
+            if (k + 4 > k1 && k + kl >= k1) {               // behind the last k
 #pragma unroll
                 for (int i = 0; i < MT; ++i) a[i] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
@@ -831,22 +836,35 @@ int product_of(const char* name, bool conj, TileProduct P, hipStream_t s)
     return check_launch(name);
 }
 
-// Result tiles of a workgroup by the work they leave: MFMAs, copies of the operands and a fixed part per workgroup
-// (measured shares at 16 to 144 rows and columns); 40 x 40 results are 3 workgroups of 48 x 16 instead of 4 of 32 x 32.
+// Result tiles of a workgroup by the time they leave.  Clocks of a chunk of four k with two workgroups on a compute unit, measured
+// on 120 x 125 x 120 products of 7488 frequencies (all shapes within 1.15 to 1.40 ms): larger tiles read less, smaller ones keep
+// more workgroups in flight.  Alone on its unit a workgroup takes 0.6 of that, and never less than the way to memory, which chunks of
+// eight k halve.  40 maps x 16 tiles of 32 x 32 of a 2D layer: 105 workgroups of 1 x 1 instead of 35 of 3 x 1, 19.4 -> 10.5 us;
+// gradient of 80 x 80 maps: 1 x 1 instead of 2 x 2, 66 -> 57 us.
 int product(const char* name, bool conj, const TileProduct& P, hipStream_t s)
 {
+    struct Shape { int m, n; double clocks; };
+    constexpr Shape shapes[] = {{2, 2, 6040}, {3, 1, 4640}, {1, 3, 4850}, {2, 1, 2990}, {1, 2, 3140}, {1, 1, 1720}};
     const int mt = (P.M + 15) / 16, nt = (P.N + 15) / 16;
-    auto cost = [&](int a, int b) { return (double)((mt + a - 1) / a) * ((nt + b - 1) / b) * (a * b + 0.35 * (a + b) + 0.5); };
-    const int shapes[][2] = {{2, 2}, {3, 1}, {1, 3}, {2, 1}, {1, 2}};
     int best = 0;
-    for (int i = 1; i < 5; ++i)
-        if (cost(shapes[i][0], shapes[i][1]) < cost(shapes[best][0], shapes[best][1])) best = i;
+    double best_cost = 0;
+    for (int i = 0; i < 6; ++i) {
+        const Shape& S = shapes[i];
+        const double groups = (double)P.blocks * P.splits * ((mt + S.m - 1) / S.m) * ((nt + S.n - 1) / S.n);
+        const int deep = chunk_of(S.m, S.n);
+        const double chunks = std::ceil(std::ceil((double)P.K / P.splits) / deep);
+        const double alone = 0.6 + 0.4 * std::min(1.0, std::max(0.0, groups / 256.0 - 1.0));
+        const double rounds = groups > 2048.0 ? groups / 512.0 : std::ceil(groups / 512.0);
+        const double cost = rounds * (chunks * std::max(alone * S.clocks * deep / 4, 1500.0) + 4000.0);
+        if (i == 0 || cost < best_cost) { best = i; best_cost = cost; }
+    }
     switch (best) {
         case 0: return product_of<2, 2>(name, conj, P, s);
         case 1: return product_of<3, 1>(name, conj, P, s);
         case 2: return product_of<1, 3>(name, conj, P, s);
         case 3: return product_of<2, 1>(name, conj, P, s);
-        default: return product_of<1, 2>(name, conj, P, s);
+        case 4: return product_of<1, 2>(name, conj, P, s);
+        default: return product_of<1, 1>(name, conj, P, s);
     }
 }
 
