@@ -151,6 +151,14 @@ __device__ __forceinline__ void rows_c2r(float2* lds, const TileGeom& G)
     }
 }
 
+// The mask of an axis as the loops test it, bit by bit: without this the compiler keeps every bit's test in scalar registers
+// from one column to the next, three times as many as there are.
+__device__ __forceinline__ unsigned bits(unsigned mask)
+{
+    asm volatile("" : "+s"(mask));
+    return mask;
+}
+
 // transforms along y, in place, of the planes z that hold samples; forward reads, inverse writes only the
 // rows of mask[1]
 template <int M, int DIR, bool FULL>
@@ -161,14 +169,18 @@ __device__ __forceinline__ void columns_y(float2* lds, const TileGeom& G)
         const int q = (int)fdiv((unsigned)u, G.fMxh), k = u - q * G.Mxh;
         const int b = (int)fdiv((unsigned)q, G.fw[0]), z = q - b * G.w[0];
         float2* c = lds + (b * G.w[0] + z) * G.M[1] * G.Mxh + k;
+        const unsigned mask = bits(G.mask[1]);
         float2 v[M];
 #pragma unroll
         for (int m = 0; m < M; ++m)
-            v[m] = FULL || ((G.mask[1] >> m) & 1u) ? c[m * G.Mxh] : make_float2(0.f, 0.f);
+            v[m] = FULL || ((mask >> m) & 1u) ? c[m * G.Mxh] : make_float2(0.f, 0.f);
         fft_inplace<M, DIR>(v);
+        // stepped anew: the places of all elements would take the registers of a workgroup's share of the unit
+        int at = (int)(c - lds);
+        asm volatile("" : "+v"(at));
 #pragma unroll
-        for (int m = 0; m < M; ++m)
-            if (DIR < 0 || ((G.mask[1] >> m) & 1u)) c[m * G.Mxh] = v[m];
+        for (int m = 0; m < M; ++m, at += G.Mxh)
+            if (DIR < 0 || ((mask >> m) & 1u)) lds[at] = v[m];
     }
 }
 
@@ -197,11 +209,12 @@ __device__ __forceinline__ void columns_z_store(const float2* lds, float2* dst, 
         const int b = (int)fdiv((unsigned)u, G.fcol), p = u - b * P;
         if (e0 + b >= G.entries) break;
         const float2* c = lds + b * G.w[0] * P + p;
+        const unsigned mask = bits(G.mask[0]);
         float2 v[M];
 #pragma unroll
         for (int m = 0; m < M; ++m) {
             v[m] = make_float2(0.f, 0.f);
-            if (FULL || ((G.mask[0] >> m) & 1u)) { v[m] = *c; c += P; }
+            if (FULL || ((mask >> m) & 1u)) { v[m] = *c; c += P; }
         }
         fft_inplace<M, -1>(v);
         char* d = reinterpret_cast<char*>(dst + (long)e0 * 16);
@@ -237,9 +250,10 @@ __device__ __forceinline__ void load_columns_z(float2* lds, const TileInv& I, in
         }
         fft_inplace<M, +1>(v);
         float2* c = lds + b * G.w[0] * P + p;
+        const unsigned mask = bits(G.mask[0]);
 #pragma unroll
         for (int m = 0; m < M; ++m)
-            if ((G.mask[0] >> m) & 1u) { *c = v[m]; c += P; }
+            if ((mask >> m) & 1u) { *c = v[m]; c += P; }
     }
 }
 
@@ -256,7 +270,7 @@ __device__ __forceinline__ void store_plane(const float2* lds, float2* dst, cons
 
 __device__ __forceinline__ void load_plane(float2* lds, const TileInv& I, int e0)
 {
-    constexpr int kLoads = 16;
+    constexpr int kLoads = 8;
     const TileGeom& G = I.G;
     const int P = G.M[1] * G.Mxh, total = min(G.per_wg, G.entries - e0) * P;
     for (int u0 = threadIdx.x; u0 < total; u0 += kLoads * blockDim.x) {
@@ -423,9 +437,13 @@ typedef __attribute__((address_space(3))) void* lds_ptr;
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // Bound by the store of the spectra (8 bytes per frequency) and the transforms; the tile's samples come in as rows of
-// neighbouring lanes, one row, then one column per thread is transformed in registers.
+// neighbouring lanes, one row, then one column per thread is transformed in registers.  The phases of a workgroup wait for memory and
+// for each other, so what counts is how many workgroups a compute unit holds: five waves per SIMD (96 registers; the inverse keeps
+// 13 words in scratch for it, and three waves where columns of 32 make it 147).  Tests of mask bits and addresses that the
+// compiler kept across columns cost 20 to 30 registers and most of the scalar ones.  40 maps of 64^3 in tiles of 16 x 24 x 24:
+// forward 48 -> 42 us, inverse 46 -> 39 and 53 -> 44 us; inverse of tiles of 32: 43 -> 34 us.
 template <bool LONG, bool FULL>
-__global__ void __launch_bounds__(kTileThreads, LONG ? 2 : 4) k_tile_fwd(TileFwd A)
+__global__ void __launch_bounds__(kTileThreads, 5) k_tile_fwd(TileFwd A)
 {
     extern __shared__ float2 lds[];
     __shared__ EntryInfo info[kTileEntries];
@@ -460,7 +478,7 @@ __global__ void __launch_bounds__(kTileThreads, LONG ? 2 : 4) k_tile_fwd(TileFwd
 }
 
 template <bool LONG, bool SPLIT>
-__global__ void __launch_bounds__(kTileThreads, LONG ? 2 : 4) k_tile_inv(TileInv A)
+__global__ void __launch_bounds__(kTileThreads, LONG ? 3 : 5) k_tile_inv(TileInv A)
 {
     extern __shared__ float2 lds[];
     __shared__ EntryInfo info[kTileEntries];
