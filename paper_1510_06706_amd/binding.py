@@ -10,6 +10,10 @@ import ctypes
 import os
 from typing import Optional, Sequence, Tuple
 
+# torch ships its own HIP runtime: loaded before the library, which then binds to the same runtime instance (one process, one
+# runtime) instead of a second copy.
+import torch
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libznn.so")
 
@@ -78,9 +82,6 @@ def lib():
         if not os.path.exists(LIB_PATH):
             raise RuntimeError("libznn.so is not built: run `python -m paper_1510_06706_amd.build` "
                                "(or __graft_entry__.build()) first")
-        # torch ships its own HIP runtime; load it first so that this library binds to
-        # the same runtime instance (one process, one runtime) instead of a second copy.
-        import torch  # noqa: F401
         L = ctypes.CDLL(LIB_PATH)
         vp, sz, i32, i64 = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int32, ctypes.c_int64
         L.znn_last_error.restype = ctypes.c_char_p
@@ -157,23 +158,20 @@ def make_desc(fan_in, fan_out, image, kernel, mode="direct", sparsity=(1, 1, 1))
 
 
 def _stream_ptr(stream=None):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _ptr(t, dtype=None):
-    """Device pointer of a contiguous CUDA tensor (None -> NULL)."""
+    """Device pointer of a contiguous CUDA tensor (None -> NULL), as the integer that ctypes takes for a pointer."""
     if t is None:
-        return ctypes.c_void_p(0)
-    import torch
+        return None
     if not t.is_cuda:
         raise ValueError("tensor must live on the GPU")
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise ValueError("tensor must be %s, got %s" % (dtype, t.dtype))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 class Plan:
@@ -185,6 +183,7 @@ class Plan:
         self.n, self.k = tuple(int(v) for v in image), tuple(int(v) for v in kernel)
         self.s = tuple(int(v) for v in sparsity)
         self.o = tuple(n - s * (k - 1) for n, k, s in zip(self.n, self.k, self.s))
+        self._in, self._out, self._ker = (self.f,) + self.n, (self.fo,) + self.o, (self.fo, self.f) + self.k
         self._h = ctypes.c_void_p(0)
         self._ws = None
         self._spectra = None
@@ -250,20 +249,18 @@ class Plan:
 
     def _workspace(self, which: int, device):
         """Grows (never shrinks) a torch byte buffer used as the caller workspace."""
-        import torch
         need = self.workspace_bytes(which)
         if need == 0:
-            return ctypes.c_void_p(0), 0
+            return None, 0
         if self._ws is None or self._ws.numel() < need + 256:
             self._ws = None
             self._ws = torch.empty(need + 256, dtype=torch.uint8, device=device)
         base = self._ws.data_ptr()
         aligned = (base + 255) & ~255
-        return ctypes.c_void_p(aligned), need
+        return aligned, need
 
     def prepare_kernels(self, w, stream=None):
         """Transforms all kernels once; the spectra stay resident in a buffer this object owns."""
-        import torch
         need = self.spectra_bytes()
         buf = getattr(self, "_spectra", None)
         if buf is None or buf.numel() != need + 256 or buf.device != w.device:
@@ -281,7 +278,6 @@ class Plan:
 
     def enable_memo(self, device="cuda:0"):
         """Attaches a buffer (owned by this object) in which fwd / bwd leave their node spectra."""
-        import torch
         need = self.memo_bytes()
         buf = torch.empty(need + 256, dtype=torch.uint8, device=device)
         aligned = (buf.data_ptr() + 255) & ~255
@@ -294,7 +290,6 @@ class Plan:
 
     def wgrad_memo(self, gw=None, device="cuda:0", stream=None):
         """Kernel gradient of the tensors given to the last fwd and bwd, from their memoized spectra."""
-        import torch
         if gw is None:
             gw = torch.empty((self.fo, self.f) + self.k, dtype=torch.float32, device=device)
         assert tuple(gw.shape) == (self.fo, self.f) + self.k
@@ -307,13 +302,12 @@ class Plan:
         self._spectra = None
 
     def fwd(self, inp, w, out=None, stream=None):
-        import torch
-        assert tuple(inp.shape) == (self.f,) + self.n, inp.shape
+        assert inp.shape == self._in, inp.shape
         if w is not None:
-            assert tuple(w.shape) == (self.fo, self.f) + self.k, w.shape
+            assert w.shape == self._ker, w.shape
         if out is None:
-            out = torch.empty((self.fo,) + self.o, dtype=torch.float32, device=inp.device)
-        assert tuple(out.shape) == (self.fo,) + self.o
+            out = torch.empty(self._out, dtype=torch.float32, device=inp.device)
+        assert out.shape == self._out
         ws, wsb = self._workspace(ZNN_PASS_FWD, inp.device)
         _check(lib().znn_conv3d_fwd(self._h, _ptr(inp, torch.float32), _ptr(w, torch.float32),
                                     _ptr(out, torch.float32), ws, wsb, _stream_ptr(stream)))
@@ -322,33 +316,30 @@ class Plan:
     def fwd_static(self, inp, w, out, stream=None):
         """znn_conv3d_fwd_static: the forward pass with the library's built-in scratch array; this
         wrapper allocates nothing either (the caller passes `out`)."""
-        import torch
-        assert tuple(inp.shape) == (self.f,) + self.n, inp.shape
-        assert tuple(out.shape) == (self.fo,) + self.o
+        assert inp.shape == self._in, inp.shape
+        assert out.shape == self._out
         _check(lib().znn_conv3d_fwd_static(self._h, _ptr(inp, torch.float32), _ptr(w, torch.float32),
                                            _ptr(out, torch.float32), _stream_ptr(stream)))
         return out
 
     def bwd(self, gout, w, gin=None, stream=None):
-        import torch
-        assert tuple(gout.shape) == (self.fo,) + self.o, gout.shape
+        assert gout.shape == self._out, gout.shape
         if w is not None:
-            assert tuple(w.shape) == (self.fo, self.f) + self.k, w.shape
+            assert w.shape == self._ker, w.shape
         if gin is None:
-            gin = torch.empty((self.f,) + self.n, dtype=torch.float32, device=gout.device)
-        assert tuple(gin.shape) == (self.f,) + self.n
+            gin = torch.empty(self._in, dtype=torch.float32, device=gout.device)
+        assert gin.shape == self._in
         ws, wsb = self._workspace(ZNN_PASS_BWD, gout.device)
         _check(lib().znn_conv3d_bwd(self._h, _ptr(gout, torch.float32), _ptr(w, torch.float32),
                                     _ptr(gin, torch.float32), ws, wsb, _stream_ptr(stream)))
         return gin
 
     def wgrad(self, inp, gout, gw=None, stream=None):
-        import torch
-        assert tuple(inp.shape) == (self.f,) + self.n, inp.shape
-        assert tuple(gout.shape) == (self.fo,) + self.o, gout.shape
+        assert inp.shape == self._in, inp.shape
+        assert gout.shape == self._out, gout.shape
         if gw is None:
-            gw = torch.empty((self.fo, self.f) + self.k, dtype=torch.float32, device=inp.device)
-        assert tuple(gw.shape) == (self.fo, self.f) + self.k
+            gw = torch.empty(self._ker, dtype=torch.float32, device=inp.device)
+        assert gw.shape == self._ker
         ws, wsb = self._workspace(ZNN_PASS_WGRAD, inp.device)
         _check(lib().znn_conv3d_wgrad(self._h, _ptr(inp, torch.float32), _ptr(gout, torch.float32),
                                       _ptr(gw, torch.float32), ws, wsb, _stream_ptr(stream)))
@@ -356,7 +347,6 @@ class Plan:
 
 
 def maxfilter3d_fwd(inp, win, sparsity=(1, 1, 1), stream=None):
-    import torch
     maps, n = inp.shape[0], tuple(inp.shape[1:])
     o = tuple(a - s * (b - 1) for a, b, s in zip(n, win, sparsity))
     if min(o) < 1:
@@ -373,7 +363,6 @@ def maxfilter3d_fwd(inp, win, sparsity=(1, 1, 1), stream=None):
 
 
 def maxfilter3d_bwd(gout, idx, n, win, sparsity=(1, 1, 1), stream=None):
-    import torch
     maps = gout.shape[0]
     gin = torch.empty((maps,) + tuple(n), dtype=torch.float32, device=gout.device)
     if tuple(sparsity) == (1, 1, 1):
@@ -386,7 +375,6 @@ def maxfilter3d_bwd(gout, idx, n, win, sparsity=(1, 1, 1), stream=None):
 
 
 def maxpool3d_fwd(inp, p, stream=None):
-    import torch
     maps, n = inp.shape[0], tuple(inp.shape[1:])
     o = tuple(a // b if b > 0 else 0 for a, b in zip(n, p))
     out = torch.empty((maps,) + o, dtype=torch.float32, device=inp.device)
@@ -397,7 +385,6 @@ def maxpool3d_fwd(inp, p, stream=None):
 
 
 def maxpool3d_bwd(gout, idx, n, p, stream=None):
-    import torch
     maps = gout.shape[0]
     gin = torch.empty((maps,) + tuple(n), dtype=torch.float32, device=gout.device)
     _check(lib().znn_maxpool3d_bwd(maps, _v3(n), _v3(p), _ptr(gout, torch.float32), _ptr(idx, torch.int32),
@@ -406,7 +393,6 @@ def maxpool3d_bwd(gout, idx, n, p, stream=None):
 
 
 def transfer_fwd(x, bias, fn="rectify", stream=None):
-    import torch
     y = torch.empty_like(x)
     maps = x.shape[0]
     if fn == "rectify":
@@ -419,7 +405,6 @@ def transfer_fwd(x, bias, fn="rectify", stream=None):
 
 
 def transfer_bwd(gy, y, fn="rectify", stream=None):
-    import torch
     gx = torch.empty_like(gy)
     maps = gy.shape[0]
     if fn == "rectify":
@@ -432,7 +417,6 @@ def transfer_bwd(gy, y, fn="rectify", stream=None):
 
 
 def bias_grad(g, stream=None):
-    import torch
     maps = g.shape[0]
     gb = torch.empty((maps,), dtype=torch.float32, device=g.device)
     _check(lib().znn_bias_grad(maps, g.numel() // maps, _ptr(g, torch.float32), _ptr(gb), _stream_ptr(stream)))
@@ -440,7 +424,6 @@ def bias_grad(g, stream=None):
 
 
 def square_loss_grad(out, target, stream=None):
-    import torch
     g = torch.empty_like(out)
     _check(lib().znn_square_loss_grad(out.numel(), _ptr(out, torch.float32), _ptr(target, torch.float32),
                                       _ptr(g), _stream_ptr(stream)))
@@ -448,7 +431,6 @@ def square_loss_grad(out, target, stream=None):
 
 
 def cross_entropy_loss_grad(out, target, stream=None):
-    import torch
     g = torch.empty_like(out)
     _check(lib().znn_cross_entropy_loss_grad(out.numel(), _ptr(out, torch.float32), _ptr(target, torch.float32),
                                              _ptr(g), _stream_ptr(stream)))
@@ -465,14 +447,12 @@ def loss_grad(out, target, loss="square", stream=None):
 
 def accumulate(y, x, stream=None):
     """y += x (node sum of a computation graph)."""
-    import torch
     assert y.shape == x.shape
     _check(lib().znn_accumulate(y.numel(), _ptr(x, torch.float32), _ptr(y, torch.float32), _stream_ptr(stream)))
     return y
 
 
 def sgd_update(p, g, eta, stream=None):
-    import torch
     _check(lib().znn_sgd_update(p.numel(), float(eta), _ptr(g, torch.float32), _ptr(p, torch.float32),
                                 _stream_ptr(stream)))
     return p
@@ -486,7 +466,6 @@ def autotune_workspace_bytes(desc: ConvDesc) -> int:
 
 def autotune(fan_in, fan_out, image, kernel, device="cuda:0", stream=None, sparsity=(1, 1, 1)):
     """Returns (chosen mode, ms[method][pass]) and caches the choice for mode='auto' plans."""
-    import torch
     desc = make_desc(fan_in, fan_out, image, kernel, "auto", sparsity)
     need = autotune_workspace_bytes(desc)
     buf = torch.empty(need + 256, dtype=torch.uint8, device=device)
@@ -503,7 +482,6 @@ def autotune_round(fan_in, fan_out, image, kernel, memory_budget=None, sparsity=
     """Times a whole training round of the layer as direct / FFT / FFT with memoized spectra,
     leaving out what exceeds ``memory_budget`` bytes (None = no limit).  Returns
     (chosen strategy name, {name: ms}, {name: bytes})."""
-    import torch
     desc = make_desc(fan_in, fan_out, image, kernel, "auto", sparsity)
     b = ctypes.c_size_t(0)
     _check(lib().znn_autotune_round_workspace_bytes(ctypes.byref(desc), ctypes.byref(b)))
