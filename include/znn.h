@@ -345,9 +345,10 @@ int  znn_autotune_round(const znn_conv_desc* desc, uint64_t memory_budget, void*
  *     operation of the list could tell: the result is that of the operations one after another.
  * A program describes the plans as they are when it is created; a plan stands for one layer (one set of kernels, inputs and
  * gradients) and one program is run by one thread at a time.  `scratch` is shared by the runs of a program.
- * Beside the workspace of its passes a program holds packed weights and partial sums of the layers on the direct method and
- * spectra of those on the FFT method (16 GiB of spectra at most); znn_plan_set_round_memory bounds that per layer (a plan
- * sets no bound), for programs created afterwards: what does not fit is computed in every pass instead.
+ * Beside the workspace of its passes a program holds packed weights and partial sums of the layers on the direct method, on
+ * one stream also the image copies of their kernel gradients that one launch makes (at most 8 MiB of a layer), and spectra
+ * of those on the FFT method (16 GiB of spectra at most); znn_plan_set_round_memory bounds that per layer (a plan sets no
+ * bound), for programs created afterwards: what does not fit is computed in every pass instead.
  * Buffers with different numbers must not overlap where an operation writes one of them -- except that the parameters of
  * several layers may be the same memory if their UPDATEs stand behind everything that reads it: they take effect in order.
  *

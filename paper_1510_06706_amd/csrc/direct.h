@@ -30,7 +30,9 @@ bool split_grad_supported(const Geom& g);
 double split_grad_seconds(const Geom& g);
 size_t split_grad_sums_bytes(const Geom& g);
 size_t split_grad_copies_bytes(const Geom& g);
-int split_grad(const Geom& g, const float* in, const float* gout, float* partial, void* copies, WgradSum* sum, hipStream_t s);
+int split_grad(const Geom& g, const GradItem& item, hipStream_t s);
+bool split_grad_joins(const Geom& g);
+int split_grads(const GradItem* items, int count, hipStream_t s);
 int sum_shares(const WgradSum& S, const float* partial, float* gw, hipStream_t s);
 
 // ---- all passes on the vector ALUs (direct_few.hip)

@@ -88,8 +88,12 @@ size_t grad_copies_bytes(const Geom& g) { return few_gradient(g) ? 0 : split_gra
 
 int grad_partial(const Geom& g, const float* in, const float* gout, float* partial, void* copies, WgradSum* sum, hipStream_t s)
 {
-    return few_gradient(g) ? few_grad(g, in, gout, partial, nullptr, sum, s) : split_grad(g, in, gout, partial, copies, sum, s);
+    return few_gradient(g) ? few_grad(g, in, gout, partial, nullptr, sum, s)
+                           : split_grad(g, GradItem{&g, in, gout, partial, copies, sum}, s);
 }
+
+bool grad_joins(const Geom& g) { return !few_gradient(g) && split_grad_joins(g); }
+int grads_partial(const GradItem* items, int count, hipStream_t s) { return split_grads(items, count, s); }
 
 static size_t conv_workspace(const Geom& g, bool backward)
 {

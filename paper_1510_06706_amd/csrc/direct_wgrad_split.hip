@@ -25,12 +25,15 @@ struct SplitImage {
     unsigned first;         // workgroup it starts at
     FastDiv dVX, dVY, dVZ;  // V
 };
-struct SplitArgs { SplitImage image[2]; };
+constexpr int kGradJobs = 8;        // layers that share a launch of k_split_images
+struct SplitArgs { SplitImage image[2 * kGradJobs]; int n; };
 
 // A thread makes one vector: eight loads (neighbouring lanes along x), the split, three 16-byte stores.  Bound by memory.
 __global__ void __launch_bounds__(256) k_split_images(SplitArgs A)
 {
-    const SplitImage& S = A.image[blockIdx.x >= A.image[1].first ? 1 : 0];      // uniform
+    int q = 0;
+    while (q + 1 < A.n && blockIdx.x >= A.image[q + 1].first) ++q;      // uniform
+    const SplitImage& S = A.image[q];
     const long t = (long)(blockIdx.x - S.first) * 256 + threadIdx.x;
     if (t >= S.vectors) return;
     const unsigned vol = (unsigned)S.all[0] * S.all[1] * S.all[2];
@@ -326,23 +329,33 @@ size_t split_grad_copies_bytes(const Geom& g)
     return c.ok ? slabs_of(g, c).bytes : 0;
 }
 
-int split_grad(const Geom& g, const float* in, const float* gout, float* partial, void* copies, WgradSum* sum, hipStream_t s)
+namespace {
+
+// One slab of a layer's gradient, as its launches take it.
+struct GradJob {
+    GradTile P;
+    SplitImage image[2];
+    unsigned copy_blocks[2];
+    GradFn fn;
+};
+
+int log_grad(const GradChoice& c, const Slabs& slabs)
 {
-    const GradChoice c = choose(g);
-    if (!c.ok) return fail(ZNN_EUNSUPPORTED, "no tile configuration fits this shape");
+    return fprintf(stderr, "[znn] wgrad split: NJ=%d JG=%d NT=%d G=%d KW=%d pieces=%dx%dx%d tile=%dx%dx%d halo=%dx%dx%d taps=%dx%d planes=%d tiles=%d tps=%d shares=%d slab=%dx%d cost=%.0f\n",
+                   c.NJ, c.JG, c.NT, c.G, c.KW, c.E[0], c.E[1], c.E[2], c.R[0], c.R[1], c.R[2], c.H[0], c.H[1], c.H[2], c.GA, c.GB,
+                   c.planes_a * c.planes_b, c.tiles, c.tps, c.shares, slabs.residues, slabs.rows, c.cost);
+}
+
+// The slab of `residues` residues from r0 and `rows` tile rows from row0 on; tps: tiles of a share (0: set here, by the first slab).
+int make_job(const Geom& g, const GradChoice& c, int d0, int r0, int residues, int row0, int rows, const GradItem& item, int& tps, GradJob& job)
+{
     const int n[3] = {g.nz, g.ny, g.nx}, o[3] = {g.oz, g.oy, g.ox}, k[3] = {g.kz, g.ky, g.kx}, sp[3] = {g.spz, g.spy, g.spx};
-    const Slabs slabs = slabs_of(g, c);
-    const int d0 = slabs.axis, planes = c.planes_a * c.planes_b;
-    const long other = (long)planes * c.G * c.JG;
-    const GradFn fn = pick(c.NJ, c.NT);
-    if (!fn) return fail(ZNN_EUNSUPPORTED, "no kernel instance for tile %dx%d", c.NJ, c.NT);
-    if (log_enabled())
-        fprintf(stderr, "[znn] wgrad split: NJ=%d JG=%d NT=%d G=%d KW=%d pieces=%dx%dx%d tile=%dx%dx%d halo=%dx%dx%d taps=%dx%d planes=%d tiles=%d tps=%d shares=%d slab=%dx%d cost=%.0f\n",
-                c.NJ, c.JG, c.NT, c.G, c.KW, c.E[0], c.E[1], c.E[2], c.R[0], c.R[1], c.R[2], c.H[0], c.H[1], c.H[2], c.GA, c.GB, planes, c.tiles, c.tps,
-                c.shares, slabs.residues, slabs.rows, c.cost);
-    GradTile P = {};
-    SplitArgs A = {};
-    P.in = in; P.gout = gout; P.partial = partial;
+    const int planes = c.planes_a * c.planes_b;
+    job.fn = pick(c.NJ, c.NT);
+    if (!job.fn) return fail(ZNN_EUNSUPPORTED, "no kernel instance for tile %dx%d", c.NJ, c.NT);
+    GradTile& P = job.P;
+    P = GradTile{};
+    P.in = item.in; P.gout = item.gout; P.partial = item.partial;
     P.f = g.f; P.fo = g.fo;
     P.GA = c.GA; P.GB = c.GB; P.planes_b = c.planes_b; P.planes = planes;
     P.GS = c.GS; P.IS = c.IS;
@@ -353,57 +366,127 @@ int split_grad(const Geom& g, const float* in, const float* gout, float* partial
     P.dHX = make_fastdiv((unsigned)c.H[2]); P.dHY = make_fastdiv((unsigned)c.H[1]);
     P.dGU = make_fastdiv((unsigned)c.GS / 16); P.dIU = make_fastdiv((unsigned)c.IS / 16);
     P.dTG = make_fastdiv((unsigned)(c.GA * c.GB * k[2])); P.dKX = make_fastdiv((unsigned)k[2]); P.dGB = make_fastdiv((unsigned)c.GB);
-    A.image[0].src = gout; A.image[1].src = in;
-    int tps = 0, shares = 0;
-    for (int r = 0; r < c.ph[d0]; r += slabs.residues)
-        for (int row = 0; row < c.T[d0]; row += slabs.rows) {
-            const int rows = std::min(slabs.rows, c.T[d0] - row);
-            int ph[3];
-            for (int d = 0; d < 3; ++d) {
-                const bool cut = d == d0;
-                ph[d] = cut ? slabs.residues : c.ph[d];
-                P.T[d] = cut ? rows : c.T[d];
-                P.r0[d] = cut ? r : 0; P.q0[d] = cut ? row * c.R[d] : 0;
-                P.n[d] = n[d]; P.o[d] = o[d]; P.k[d] = k[d]; P.sp[d] = k[d] > 1 ? sp[d] : 1;
-                P.E[d] = c.E[d]; P.Q[d] = c.Q[d]; P.R[d] = c.R[d]; P.H[d] = c.H[d];
-                P.P[d] = ph[d] * P.T[d] * c.R[d];
-                P.I[d] = P.P[d] + ph[d] * (k[d] - 1);
-                for (SplitImage& S : A.image) { S.E[d] = c.E[d]; S.Q[d] = c.Q[d]; S.sp[d] = P.sp[d]; S.r0[d] = P.r0[d]; S.q0[d] = P.q0[d]; }
-                A.image[0].n[d] = o[d]; A.image[0].all[d] = P.P[d]; A.image[0].V[d] = P.P[d] / ph[d]; A.image[0].real[d] = c.Q[d];
-                A.image[1].n[d] = n[d]; A.image[1].all[d] = P.I[d]; A.image[1].V[d] = P.I[d] / ph[d]; A.image[1].real[d] = c.Q[d] + k[d] - 1;
-            }
-            uintx4* const gs = (uintx4*)copies;
-            uintx4* const is = (uintx4*)((char*)copies + align256(vectors(P.P, g.fo) * kVectorBytes));
-            A.image[0].dst = gs; A.image[0].vectors = (long)vectors(P.P, g.fo);
-            A.image[1].dst = is; A.image[1].vectors = (long)vectors(P.I, g.f);
-            for (SplitImage& S : A.image) {
-                S.dVZ = make_fastdiv((unsigned)S.V[0]); S.dVY = make_fastdiv((unsigned)S.V[1]); S.dVX = make_fastdiv((unsigned)S.V[2]);
-            }
-            const long blocks0 = (A.image[0].vectors + 255) / 256, blocks1 = (A.image[1].vectors + 255) / 256;
-            A.image[1].first = (unsigned)blocks0;
-            P.gs = gs; P.is = is;
-            P.tiles_y = ph[1] * P.T[1]; P.tiles_x = ph[2] * P.T[2];
-            P.tiles = ph[0] * P.T[0] * P.tiles_y * P.tiles_x;
-            if (!shares) {      // the first slab is the largest: the others have no more shares than it
-                tps = (P.tiles + c.shares - 1) / c.shares;
-                shares = (P.tiles + tps - 1) / tps;
-            }
-            P.tps = tps;
-            const long total = (P.tiles + tps - 1) / tps * other;
-            if (blocks0 + blocks1 >= 2147483647L || total >= 2147483640L) return fail(ZNN_EUNSUPPORTED, "too many tiles for one launch");
-            P.total = (int)total; P.run = (int)((total + 7) / 8);
-            ZNN_LAUNCH("split of images", s, k_split_images, dim3((unsigned)(blocks0 + blocks1)), dim3(256), 0, A);
-            ZNN_LAUNCH("direct kernel gradient (MFMA)", s, fn, dim3((unsigned)P.run * 8), dim3(64 * kGradWaves), 0, P);
-            P.more = 1;
+    SplitImage &sg = job.image[0], &si = job.image[1];
+    sg = si = SplitImage{};
+    sg.src = item.gout; si.src = item.in;
+    int ph[3];
+    for (int d = 0; d < 3; ++d) {
+        const bool cut = d == d0;
+        ph[d] = cut ? residues : c.ph[d];
+        P.T[d] = cut ? rows : c.T[d];
+        P.r0[d] = cut ? r0 : 0; P.q0[d] = cut ? row0 * c.R[d] : 0;
+        P.n[d] = n[d]; P.o[d] = o[d]; P.k[d] = k[d]; P.sp[d] = k[d] > 1 ? sp[d] : 1;
+        P.E[d] = c.E[d]; P.Q[d] = c.Q[d]; P.R[d] = c.R[d]; P.H[d] = c.H[d];
+        P.P[d] = ph[d] * P.T[d] * c.R[d];
+        P.I[d] = P.P[d] + ph[d] * (k[d] - 1);
+        for (SplitImage& S : job.image) { S.E[d] = c.E[d]; S.Q[d] = c.Q[d]; S.sp[d] = P.sp[d]; S.r0[d] = P.r0[d]; S.q0[d] = P.q0[d]; }
+        sg.n[d] = o[d]; sg.all[d] = P.P[d]; sg.V[d] = P.P[d] / ph[d]; sg.real[d] = c.Q[d];
+        si.n[d] = n[d]; si.all[d] = P.I[d]; si.V[d] = P.I[d] / ph[d]; si.real[d] = c.Q[d] + k[d] - 1;
+    }
+    sg.vectors = (long)vectors(P.P, g.fo);
+    si.vectors = (long)vectors(P.I, g.f);
+    sg.dst = (uintx4*)item.copies;
+    si.dst = (uintx4*)((char*)item.copies + align256(vectors(P.P, g.fo) * kVectorBytes));
+    P.gs = sg.dst; P.is = si.dst;
+    for (SplitImage& S : job.image) {
+        S.dVZ = make_fastdiv((unsigned)S.V[0]); S.dVY = make_fastdiv((unsigned)S.V[1]); S.dVX = make_fastdiv((unsigned)S.V[2]);
+    }
+    const long blocks0 = (sg.vectors + 255) / 256, blocks1 = (si.vectors + 255) / 256;
+    P.tiles_y = ph[1] * P.T[1]; P.tiles_x = ph[2] * P.T[2];
+    P.tiles = ph[0] * P.T[0] * P.tiles_y * P.tiles_x;
+    if (!tps) tps = (P.tiles + c.shares - 1) / c.shares;
+    P.tps = tps;
+    const long total = (long)((P.tiles + tps - 1) / tps) * planes * c.G * c.JG;
+    if (blocks0 + blocks1 >= 2147483647L || total >= 2147483640L) return fail(ZNN_EUNSUPPORTED, "too many tiles for one launch");
+    job.copy_blocks[0] = (unsigned)blocks0; job.copy_blocks[1] = (unsigned)blocks1;
+    P.total = (int)total; P.run = (int)((total + 7) / 8);
+    return ZNN_OK;
+}
+
+// Copies of all jobs (at most kGradJobs of them) in one launch, then the gradients.
+void launch_jobs(const GradJob* jobs, int count, hipStream_t s)
+{
+    SplitArgs A = {};
+    unsigned blocks = 0;
+    for (int q = 0; q < count; ++q)
+        for (int i = 0; i < 2; ++i) {
+            A.image[A.n] = jobs[q].image[i];
+            A.image[A.n++].first = blocks;
+            blocks += jobs[q].copy_blocks[i];
         }
+    ZNN_LAUNCH("split of images", s, k_split_images, dim3(blocks), dim3(256), 0, A);
+    for (int q = 0; q < count; ++q)
+        ZNN_LAUNCH("direct kernel gradient (MFMA)", s, jobs[q].fn, dim3((unsigned)jobs[q].P.run * 8), dim3(64 * kGradWaves), 0, jobs[q].P);
+}
+
+WgradSum shares_of(const Geom& g, const GradChoice& c, const GradJob& first)
+{
     WgradSum S = {};
-    S.ksplit = shares; S.planes = planes; S.planes_b = c.planes_b; S.Mpad = P.Mpad; S.Npad = P.Npad;
+    const int k[3] = {g.kz, g.ky, g.kx};
+    S.ksplit = (first.P.tiles + first.P.tps - 1) / first.P.tps; S.planes = first.P.planes; S.planes_b = c.planes_b;
+    S.Mpad = first.P.Mpad; S.Npad = first.P.Npad;
     S.f = g.f; S.GA = c.GA; S.GB = c.GB;
     for (int d = 0; d < 3; ++d) S.k[d] = k[d];
     S.columns = g.f * c.GA * c.GB * k[2];
-    S.slots = (long)g.fo * planes * S.columns;
-    S.four = S.slots < 65536 && shares >= 16 ? 1 : 0;
-    *sum = S;
+    S.slots = (long)g.fo * S.planes * S.columns;
+    S.four = S.slots < 65536 && S.ksplit >= 16 ? 1 : 0;
+    return S;
+}
+
+}  // namespace
+
+int split_grad(const Geom& g, const GradItem& item, hipStream_t s)
+{
+    const GradChoice c = choose(g);
+    if (!c.ok) return fail(ZNN_EUNSUPPORTED, "no tile configuration fits this shape");
+    const Slabs slabs = slabs_of(g, c);
+    const int d0 = slabs.axis;
+    if (log_enabled()) log_grad(c, slabs);
+    GradJob job;
+    int tps = 0;            // the first slab is the largest: the others have no more shares than it
+    bool more = false;
+    for (int r = 0; r < c.ph[d0]; r += slabs.residues)
+        for (int row = 0; row < c.T[d0]; row += slabs.rows) {
+            const int rc = make_job(g, c, d0, r, slabs.residues, row, std::min(slabs.rows, c.T[d0] - row), item, tps, job);
+            if (rc != ZNN_OK) return rc;
+            job.P.more = more;
+            if (!more) *item.sum = shares_of(g, c, job);
+            launch_jobs(&job, 1, s);
+            more = true;
+        }
+    return check_launch("direct kernel gradient (MFMA)");
+}
+
+// Copies of at most 8 MiB, three workgroups per compute unit, leave a launch of their own mostly waiting: three layers of the six-layer 3D
+// net on a 12^3 patch (40 maps of 24^3, 21^3 and 19^3) took 22 us in three launches; together 305 -> 291 us a round.  Two layers
+// of 40 maps of 34^3 and 28^3 with sparse taps, 16 MiB and 8 MiB, gained nothing by it: 640 -> 643 us, copies no longer in the cache.
+bool split_grad_joins(const Geom& g)
+{
+    const GradChoice c = choose(g);
+    if (!c.ok) return false;
+    const Slabs slabs = slabs_of(g, c);
+    return slabs.residues == c.ph[slabs.axis] && slabs.rows == c.T[slabs.axis] && slabs.bytes <= (size_t)8 << 20;
+}
+
+// Gradients of layers that split_grad_joins takes
+int split_grads(const GradItem* items, int count, hipStream_t s)
+{
+    for (int q0 = 0; q0 < count; q0 += kGradJobs) {
+        const int n = std::min(kGradJobs, count - q0);
+        GradJob jobs[kGradJobs];
+        for (int q = 0; q < n; ++q) {
+            const GradItem& item = items[q0 + q];
+            const Geom& g = *item.g;
+            const GradChoice c = choose(g);
+            const Slabs slabs = slabs_of(g, c);
+            if (log_enabled()) log_grad(c, slabs);
+            int tps = 0;
+            const int rc = make_job(g, c, slabs.axis, 0, slabs.residues, 0, slabs.rows, item, tps, jobs[q]);
+            if (rc != ZNN_OK) return rc;
+            *item.sum = shares_of(g, c, jobs[q]);
+        }
+        launch_jobs(jobs, n, s);
+    }
     return check_launch("direct kernel gradient (MFMA)");
 }
 

@@ -12,8 +12,9 @@
 //     map and 8192 voxels; one workgroup per map took 76 us on the sparse net), and in the last launch completes
 //     the sums of all kernel and bias gradients and updates all parameters (k_update);
 //   * keeps the spectra of a layer on the FFT method from the forward to the backward pass and the gradient.
-// Six-layer 3D net on a 12^3 patch: 78 -> 34 launches, 617 -> 413 us; the kernels themselves take 428 us of a traced round (32 us
-// short launches of 2 to 7 us, 23 us k_update, 372 us convolutions of 7 to 23 us with the sums of their shares).
+//   * on one stream, copies the images of the kernel gradients of small layers by one launch at the end.
+// Six-layer 3D net on a 12^3 patch: 78 -> 34 launches, 617 -> 413 us on the fp32 direct kernels, 291 us on those on split operands: chains
+// of kernels of 4 to 17 us (direct passes 144 us, gradients with their copies and sums 100 us, the rest 2 to 9 us each).
 #include <algorithm>
 #include <cstring>
 #include <new>
@@ -173,17 +174,18 @@ __global__ void __launch_bounds__(256) k_update(UpdateArgs A)
     if (U.p) U.p[t] = U.p[t] - A.eta * acc;
 }
 
-// A step of the program: an operation of the caller, or one of three that the program adds.
-enum { STEP_PACK = -1, STEP_BIAS = -2, STEP_UPDATE = -3 };
+// A step of the program: an operation of the caller, or one of four that the program adds.
+enum { STEP_PACK = -1, STEP_BIAS = -2, STEP_UPDATE = -3, STEP_GRADS = -4 };
 constexpr size_t kNone = (size_t)-1;
 
 struct Step {
     int kind;
     znn_op op;
     int stream;
-    bool skip;                          // no launch of its own: part of STEP_BIAS or STEP_UPDATE
+    bool skip;                          // no launch of its own: part of STEP_GRADS, STEP_BIAS or STEP_UPDATE
     int layer;                          // convolutions: index into znn_program::layers
     size_t own;                         // place of the partial sums that STEP_UPDATE completes (kNone: it writes the gradient)
+    size_t copies;                      // kernel gradients of STEP_GRADS: place of their copies
     size_t pass_bytes;                  // scratch it needs while it runs
     WgradSum sum;
     std::vector<int> reads, writes;     // resources
@@ -222,6 +224,7 @@ struct znn_program {
     size_t scratch;
     std::vector<size_t> area;           // per stream: place of the scratch of its passes
     std::vector<int> bias_steps;        // deferred bias gradients
+    std::vector<int> grad_steps;        // kernel gradients whose images are copied by one launch
     std::vector<int> update_steps;
     std::vector<int> completes;         // per update: the step whose sums it completes, or -1
 };
@@ -336,7 +339,7 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
 {
     auto add = [&](int kind) -> Step& {
         Step s = {};
-        s.kind = kind; s.layer = -1; s.own = kNone;
+        s.kind = kind; s.layer = -1; s.own = s.copies = kNone;
         P.steps.push_back(s);
         return P.steps.back();
     };
@@ -425,12 +428,29 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
             }
         }
     }
+    // On one stream the kernel gradients of small layers, which nothing waits for, go to the end, where one launch copies the
+    // images of all, if nothing writes their operands later; on several they run beside the passes.
+    std::vector<int> joins;
+    for (int i = 0; i < n && P.streams == 1; ++i) {
+        const Step& s = P.steps[i];
+        if (s.kind == ZNN_OP_CONV_WGRAD && s.own != kNone && last_write[s.op.buf[0]] < i && last_write[s.op.buf[1]] < i &&
+            grad_joins(P.layers[s.layer].plan.g))
+            joins.push_back(i);
+    }
+    for (int i : joins) {
+        Step& s = P.steps[i];
+        if (joins.size() > 1) s.copies = hold(s.layer, grad_copies_bytes(P.layers[s.layer].plan.g));
+        if (s.copies == kNone) continue;
+        s.skip = true;
+        P.grad_steps.push_back(i);
+    }
+    add(STEP_GRADS).skip = P.grad_steps.empty();
     add(STEP_BIAS).skip = P.bias_steps.empty();
     add(STEP_UPDATE).skip = P.update_steps.empty();
     // scratch of the passes: one area per stream
     std::vector<size_t> need(P.streams, 0);
     for (Step& s : P.steps) {
-        if (s.layer < 0) continue;
+        if (s.layer < 0 || s.copies != kNone) continue;
         const Layer& L = P.layers[s.layer];
         const Geom& g = L.plan.g;
         if (s.kind == ZNN_OP_CONV_WGRAD) s.pass_bytes = s.own != kNone ? grad_copies_bytes(g) : plan_pass_bytes(&L.plan, s.kind, false);
@@ -464,6 +484,8 @@ void name_resources(znn_program& P, int& resources)
                 const Layer& L = P.layers[l];
                 if (L.packed[0] != kNone || L.packed[1] != kNone) { rd(L.w); wr(shared + 2 * (int)l); }
             }
+        } else if (s.kind == STEP_GRADS) {
+            for (int q : P.grad_steps) { rd(P.steps[q].op.buf[0]); rd(P.steps[q].op.buf[1]); wr(own + q); }
         } else if (s.kind == STEP_BIAS) {
             for (int q : P.bias_steps) { rd(P.steps[q].op.buf[0]); wr(own + q); }
         } else if (s.kind == STEP_UPDATE) {
@@ -576,6 +598,17 @@ int run_bias(const znn_program& P, const std::vector<int>& steps, float* const* 
     return check_launch("bias gradients");
 }
 
+int run_grads(znn_program& P, float* const* buf, char* scratch, hipStream_t s)
+{
+    std::vector<GradItem> items;
+    for (int q : P.grad_steps) {
+        Step& t = P.steps[q];
+        items.push_back(GradItem{&P.layers[t.layer].plan.g, buf[t.op.buf[0]], buf[t.op.buf[1]], (float*)(scratch + t.own),
+                                 scratch + t.copies, &t.sum});
+    }
+    return grads_partial(items.data(), (int)items.size(), s);
+}
+
 int run_update(const znn_program& P, float* const* buf, char* scratch, float eta, hipStream_t s)
 {
     for (size_t u = 0; u < P.update_steps.size();) {
@@ -671,6 +704,7 @@ int run_step(znn_program& P, Step& t, float* const* buf, char* scratch, float et
     const long count = t.kind > ZNN_OP_CONV_WGRAD ? elements(o) : 0;
     switch (t.kind) {
         case STEP_PACK: return run_pack(P, buf, scratch, s);
+        case STEP_GRADS: return run_grads(P, buf, scratch, s);
         case STEP_BIAS: return run_bias(P, P.bias_steps, buf, scratch, s);
         case STEP_UPDATE: return run_update(P, buf, scratch, eta, s);
         case ZNN_OP_TRANSFER_FWD: return znn_transfer_fn_fwd(o.fn, o.maps, voxels(o), at(0), at(1), at(2), s);

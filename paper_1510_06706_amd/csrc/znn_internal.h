@@ -73,7 +73,7 @@ __device__ __forceinline__ unsigned fdiv(unsigned n, FastDiv f)
 struct Tuning {
     bool log;                   // ZNN_LOG: print launch configurations to stderr
     bool conv_no_split;         // ZNN_CONV_NO_SPLIT: never split the input maps over workgroups
-    int  conv_tile[4];          // ZNN_CONV_TILE="NV,Tz,Ty,Tx": pin the output box, NV 16-voxel tiles (0 = not pinned)
+    int  conv_tile[4];          // ZNN_CONV_TILE="T,Tz,Ty,Tx": pin the output box, T 16-voxel tiles (0 = not pinned)
     int  fft_mac_z0;            // ZNN_FFT_MAC_Z0: frequencies per thread of the folded multiply-accumulate / 4
     bool fft_mac_valu;          // ZNN_FFT_MAC_VALU: folded multiply-accumulate on the vector ALUs only
     bool fft_wgrad_plain;       // ZNN_FFT_WGRAD_PLAIN: per-z pruned DFT instead of the radix-4 grouped one
@@ -112,6 +112,10 @@ size_t grad_copies_bytes(const Geom& g);        // what the pass itself needs
 // (k_wgrad_sum), or four interleaved sums per element (k_wgrad_sum4).  Columns of a group are (input map, tap of the group).
 struct WgradSum { int ksplit, planes, planes_b, Mpad, Npad, f, GA, GB, k[3], columns, four; long slots; };
 int grad_partial(const Geom& g, const float* in, const float* gout, float* partial, void* copies, WgradSum* sum, hipStream_t s);
+// The same for several layers that grad_joins takes, whose images are copied by one launch; no two have the same memory for sums or copies.
+struct GradItem { const Geom* g; const float* in; const float* gout; float* partial; void* copies; WgradSum* sum; };
+bool grad_joins(const Geom& g);
+int grads_partial(const GradItem* items, int count, hipStream_t s);
 // Element number t of (output map, tap group, column): where a share has it and where the gradient does.  false: a tap
 // behind the last one.
 __device__ __forceinline__ bool wgrad_slot(const WgradSum& S, long t, long& from, long& to)

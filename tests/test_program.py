@@ -392,3 +392,39 @@ def test_layers_of_one_shape_may_share_a_plan(mode):
         got, want = shared.train_round(x, target, 0.01), own.train_round(x, target, 0.01, record=[])
         assert torch.equal(got[0][-1], want[0][-1]) and torch.equal(shared.forward(x)[0][-1], own._forward_by_layer(x)[0][-1])
         assert all(torch.equal(g[k], w[k]) for g, w in zip(got[3], want[3]) for k in w)
+
+
+def gradients(plans, rewrite, bound=None):
+    """Kernel gradients of layers that share nothing, and their updates; `rewrite`: layers with an operand written after them."""
+    ops, shapes = [], []
+    for l, p in enumerate(plans):
+        p.set_round_memory((1 << 62) if bound is None else bound)
+        at, fn = len(shapes), dict(maps=p.f, n=p.n, fn="tanh")
+        shapes += [(p.f,) + p.n, (p.fo,) + p.o, (p.fo, p.f) + p.k, (p.fo, p.f) + p.k, (p.f,) + p.n, (p.f,)]
+        ops += [(zp.CONV_WGRAD, (at, at + 1, at + 2), dict(plan=p))]
+        ops += [(zp.TRANSFER_FWD, (at + 4, at + 5, at), fn)] if l in rewrite else []
+        ops += [(zp.UPDATE, (at + 2, at + 3), dict(n=(1, 1, int(np.prod(shapes[at + 2])))))]
+    return ops, shapes
+
+
+def small_layers(count):
+    """Layers whose gradients run on split copies of their images (of at most 8 MiB), of different extents, taps and tap spacings."""
+    forms = [((22, 23, 24), (3, 3, 3), (1, 1, 1)), ((19, 25, 24), (2, 3, 3), (1, 2, 1)), ((1, 90, 92), (1, 5, 7), (1, 1, 1))]
+    return [znn.Plan(36 + l, 40, *forms[l % 3][:2], "direct", forms[l % 3][2]) for l in range(count)]
+
+
+def test_copies_are_held_where_several_gradients_share_their_launch():
+    a, b = small_layers(2)
+    need = lambda plans, rewrite=(), bound=None: program(*gradients(plans, rewrite, bound)).scratch_bytes  # noqa: E731
+    one, other, both = need([a]), need([b]), need([a, b])
+    assert both == one + other                           # both copies at once
+    assert need([a, b], (0,)) == need([a, b], (1,)) < both   # one left to share with: an area that the two use in turn
+    assert need([a, b], (), 0) == max(one, other)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("count,rewrite,bound", [(2, (), None), (3, (1,), None), (9, (), None), (9, (0, 8), None), (3, (), 1 << 20)])
+def test_gradients_that_share_the_copies_of_their_images(count, rewrite, bound):
+    """One group of layers, a layer more than a group takes, layers that stay behind, and a bound that keeps the copies out."""
+    print("case", count, rewrite, bound, flush=True)
+    check(*gradients(small_layers(count), rewrite, bound), 11)
