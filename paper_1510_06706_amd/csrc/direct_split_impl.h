@@ -13,7 +13,7 @@
 // every kernel shape; the count is padded to a multiple of four with weights of zero.
 //
 // Measured against v_mfma_f32_16x16x4_f32 on 4-map chunks of the same halo boxes, forward / backward pass: 40 -> 40 maps, 64^3, 5^3 kernels 740 /
-// 780 -> 480 / 475 us (180 TFLOP/s of fp32 products); 80 -> 80, 256^2, 11^2: 806 / 741 -> 420 / 426 us; 120 -> 120, 48^3, 7^3:
+// 780 -> 500 / 475 us (173, 182 TFLOP/s of fp32 products); 80 -> 80, 256^2, 11^2: 806 / 741 -> 435 / 432 us; 120 -> 120, 48^3, 7^3:
 // 9.2 / 9.0 -> 3.3 / 4.4 ms; 40 -> 40, 24^3, 3^3: 32 / 39 -> 22 / 23 us; the same, 60^3, taps two apart: 227 / 213 -> 98 /
 // 131 us.  Error against 64 bits (2-norm) of the same layers: 9.1e-7 -> 2.5e-7, 1.2e-6 -> 3.3e-7, 2.6e-6 -> 6.7e-7,
 // 1.6e-7 -> 8.8e-8, 4.2e-7 -> 1.2e-7: sums of a step on their own are what does it (kept in one running sum, the six

@@ -3,8 +3,9 @@ and the published MI355X peaks it is priced against.  No compute happens here.
 
 Steps (rows of the hot path) and what bounds them:
 
-  D-fwd / D-bwd / D-wgrad   fp32 matrix cores; 2 FLOP per multiply-add, f f' n'^3 k^3 of them per pass
-                            (Table 2, "Direct", which counts a multiply-add once).
+  D-fwd / D-bwd / D-wgrad   bf16 matrix cores; 2 FLOP per multiply-add, f f' n'^3 k^3 of them per pass (Table 2,
+                            "Direct", which counts a multiply-add once), each executed as six of bf16 (operands as
+                            sums of three bf16 parts).  Layers of few maps: fp32 vector ALU, the same count.
   F-img / F-inv             HBM; per node volume one read of the image (4 n^3 bytes; 4 n'^3 for an output
                             gradient) and one write of its spectrum (8 N_w bytes), resp. the reverse.
   F-ker                     HBM; the kernel spectra are written once in the plan's layout.
@@ -37,7 +38,8 @@ Steps (rows of the hot path) and what bounds them:
   MF-fwd / MF-bwd           HBM; 4 bytes read + 8 written per output voxel, resp. 8 read + 4 written per
                             input voxel.
 
-Peaks: fp32 MFMA 157.3 TFLOP/s; HBM 8 TB/s; fp32 vector 157.3 TFLOP/s = 256 CUs x 4 SIMDs x 16 lanes x
+Peaks: fp32 MFMA 157.3 TFLOP/s; bf16 MFMA 2516.6 TFLOP/s, a sixth of which (419.4) is the peak of fp32 products taken
+from bf16 parts; HBM 8 TB/s; fp32 vector 157.3 TFLOP/s = 256 CUs x 4 SIMDs x 16 lanes x
 2 (packed) x 2 FLOP x 2.4 GHz.  This build issues no packed fp32 instructions (compiler flag required on
 this pool), which caps the vector ALUs at 78.6 TFLOP/s; rows bound by them carry both fractions.
 """
@@ -47,6 +49,7 @@ import os
 from collections import OrderedDict
 
 PEAK_FP32_MFMA_TFLOPS = 157.3
+PEAK_SPLIT_MFMA_TFLOPS = 2516.6 / 6
 PEAK_FP32_VECTOR_TFLOPS = 157.3
 PEAK_FP32_VECTOR_UNPACKED_TFLOPS = 78.6
 PEAK_HBM_GBS = 8000.0
@@ -91,8 +94,8 @@ def step_of(name: str, what: str) -> str:
         return "D-bwd"
     if name.startswith("direct kernel gradient"):
         return "D-wgrad"
-    if name in ("weight packing", "sum over input-map shares", "kernel gradient reduction"):
-        return "direct: packing and fixed-order sums"
+    if name in ("weight packing", "split of images", "sum over input-map shares", "kernel gradient reduction"):
+        return "direct: packing, split of images and fixed-order sums"
     if name.startswith("spectral mac"):
         return "F-mac"
     if name == "pruned DFT of spectral products" or name.endswith("of product"):
@@ -208,6 +211,9 @@ def price(bound: str, work: float, ms: float):
     if bound == "mfma":
         return {"bound": "mfma", "achieved": a, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
                 "frac": a / PEAK_FP32_MFMA_TFLOPS}
+    if bound == "mfma_split":
+        return {"bound": "mfma", "achieved": a, "peak": PEAK_SPLIT_MFMA_TFLOPS, "unit": "TFLOP/s",
+                "frac": a / PEAK_SPLIT_MFMA_TFLOPS, "work": "fp32 multiply-adds, each executed as six of bf16"}
     return {"bound": "alu", "achieved": a, "peak": PEAK_FP32_VECTOR_TFLOPS, "unit": "TFLOP/s",
             "frac": a / PEAK_FP32_VECTOR_TFLOPS, "frac_of_unpacked_peak": a / PEAK_FP32_VECTOR_UNPACKED_TFLOPS,
             "work": "FLOPs the kernel executes"}
@@ -233,7 +239,10 @@ def steps_of_pass(records, reps, cfg, N, layout, what, extra_work=None, tiles=No
         e["ms"] = e["ms"] / reps
         key = st + "/mfma" if st == "F-mac" and any("MFMA" in k for k in e["kernels"]) else st
         if key in model:
-            e.update(price(model[key][0], model[key][1], e["ms"]))
+            bound = model[key][0]
+            if st in ("D-fwd", "D-bwd", "D-wgrad"):
+                bound = "mfma_split" if any("MFMA" in k for k in e["kernels"]) else "alu"
+            e.update(price(bound, model[key][1], e["ms"]))
             if key.endswith("/mfma"):
                 e["work"] = "FLOPs the kernel executes: vector ALU (butterfly, product) + matrix cores (class sums)"
         rows.append(e)
