@@ -160,7 +160,8 @@ int  znn_conv3d_fwd(znn_plan* plan, const float* in, const float* w, float* out,
  * The call allocates and frees nothing.  A layer whose forward pass needs more scratch than
  * that (znn_plan_workspace_bytes) is refused with ZNN_EWORKSPACE before anything is launched --
  * on tiles (znn_plan_tiles) only one that would need more on whole volumes; the tiles of others
- * come in groups that fit.
+ * come in groups that fit, as do the output maps of layers on the direct method (of which those whose weights of sixteen
+ * output maps do not fit, some 340000 taps in all, take kernels without scratch and may differ in rounding).
  * All calls on one GPU share the one array: calls that may overlap in time on the same GPU (two
  * streams, two threads) race and must be serialised by the caller; calls on one stream are safe.
  * The array's device address is looked up on the first call per device, with that device current.

@@ -270,12 +270,14 @@ int plan_pass(const znn_plan* p, int pass, const float* a, const float* b, float
 
 size_t plan_forward_least(const znn_plan* p)
 {
+    if (p->mode == ZNN_DIRECT) return direct_fwd_least(p->g);
     return p->tile.on ? fft_workspace(p->g, p->fold, ZNN_PASS_FWD, p->resident != nullptr).total
                       : plan_pass_bytes(p, ZNN_PASS_FWD, p->resident != nullptr);
 }
 
 int plan_forward_within(znn_plan* p, const float* in, const float* w, float* out, void* ws, size_t bytes, hipStream_t s)
 {
+    if (p->mode == ZNN_DIRECT && w && direct_workspace_bytes(p->g, ZNN_PASS_FWD) > bytes) return direct_fwd_groups(p->g, in, w, out, ws, s);
     if (!p->tile.on) return znn_conv3d_fwd(p, in, w, out, ws, bytes, s);
     if (!w && !p->resident) return fail(ZNN_EINVAL, "kernel pointer is NULL");
     const int rc = tile_fwd(p->g, p->tile, in, w, p->resident, out, ws, bytes, p->memo, s);

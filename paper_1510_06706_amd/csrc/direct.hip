@@ -125,6 +125,51 @@ int direct_fwd(const Geom& g, const float* in, const float* w, float* out, void*
     return direct_conv(g, false, in, w, out, ws, s);
 }
 
+// The forward pass one group of output maps after another (the maps that a workgroup takes): weights and sums of one at a time, the
+// same launches otherwise.  For callers whose scratch does not hold those of all.
+static Geom group_of(const Geom& g, const SplitChoice& c, int first)
+{
+    Geom q = g;
+    q.fo = std::min(16 * c.NJ, g.fo - first);
+    return q;
+}
+
+static size_t group_bytes(const Geom& g, const SplitChoice& c)
+{
+    const size_t sums = c.splits > 1 ? align256(sizeof(float) * c.splits * result_count(group_of(g, c, 0), false)) : 0;
+    return split_packed_bytes(c) + sums;
+}
+
+size_t direct_fwd_least(const Geom& g)
+{
+    SplitChoice c = way(g, false);
+    if (!c.ok) return 0;
+    c.jgroups = 1;
+    const size_t bytes = group_bytes(g, c);
+    return bytes > ZNN_STATIC_SCRATCH_BYTES ? 0 : std::min(conv_workspace(g, false), bytes);
+}
+
+int direct_fwd_groups(const Geom& g, const float* in, const float* w, float* out, void* ws, hipStream_t s)
+{
+    SplitChoice c = way(g, false);
+    c.jgroups = 1;
+    if (!c.ok || group_bytes(g, c) > ZNN_STATIC_SCRATCH_BYTES) return few_conv(g, false, in, w, out, Finish{}, s);
+    float* partial = (float*)((char*)ws + split_packed_bytes(c));
+    for (int first = 0; first < g.fo; first += 16 * c.NJ) {
+        const Geom q = group_of(g, c, first);
+        float* dst = out + (long)first * g.ovol();
+        const PackItem p = split_pack_item(q, c, false, w + (long)first * g.f * g.kvol(), ws);
+        int rc = split_pack_weights(&p, 1, s);
+        if (rc == ZNN_OK) rc = split_conv(q, c, false, in, ws, dst, partial, Finish{}, s);
+        if (rc != ZNN_OK) return rc;
+        if (c.splits == 1) continue;
+        const long count = result_count(q, false);
+        ZNN_LAUNCH("sum over input-map shares", s, k_conv_reduce, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, partial, dst, count,
+                   c.splits);
+    }
+    return check_launch("direct forward in groups of maps");
+}
+
 int direct_bwd(const Geom& g, const float* gout, const float* w, float* gin, void* ws, hipStream_t s)
 {
     return direct_conv(g, true, gout, w, gin, ws, s);

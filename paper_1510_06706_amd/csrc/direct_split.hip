@@ -138,8 +138,12 @@ Pass pass_of(const Geom& g, bool backward)
     return P;
 }
 
-// Expected clocks of the launch (and of the sum of its shares) for every box that fits, the least taken.
-SplitChoice search(const Pass& P)
+// packed weights of one group of NJ map tiles, with the step behind them that the kernel fetches ahead
+size_t packed_group(int nchunk, int steps, int NJ) { return ((size_t)nchunk * steps + 1) * NJ * 3 * 64 * 16; }
+
+// Expected clocks of the launch (and of the sum of its shares) for every box that fits, the least taken.  What one group of output maps
+// needs, weights and sums, is kept within `room` where it can be.
+SplitChoice search(const Pass& P, size_t room)
 {
     SplitChoice best = {};
     const Axis &az = P.a[0], &ay = P.a[1], &ax = P.a[2];
@@ -147,7 +151,14 @@ SplitChoice search(const Pass& P)
     if (taps > kMaxTaps) return best;
     const int steps = (taps + split::kTaps - 1) / split::kTaps;
     const int tiles = (P.fM + 15) / 16, nchunk = (P.fK + split::kMaps - 1) / split::kMaps;
-    const int jgroups = (tiles + 4) / 5, NJ = (tiles + jgroups - 1) / jgroups;
+    int jgroups = (tiles + 4) / 5, NJ = (tiles + jgroups - 1) / jgroups;
+    if (packed_group(nchunk, steps, 1) > room) room = SIZE_MAX;     // not even a tile of maps
+    while (NJ > 1 && packed_group(nchunk, steps, NJ) > room) {
+        ++jgroups;
+        NJ = (tiles + jgroups - 1) / jgroups;
+    }
+    const size_t packed = align256(packed_group(nchunk, steps, NJ));
+    const size_t sums = sizeof(float) * std::min(P.fM, 16 * NJ) * (size_t)az.d * ay.d * ax.d;     // of a share
     const int phases = az.phases * ay.phases * ax.phases;
     const double count = (double)P.fM * az.d * ay.d * ax.d;
     const int nvs[6] = {1, 2, 3, 4, 6, 8}, nws[2] = {4, 8};
@@ -178,6 +189,7 @@ SplitChoice search(const Pass& P)
                     const double stage = 4.0 * hvol * (1.0 + 0.06 * (ax.sp - 1));
                     const double fixed = 5200.0 + 11.5 * cap * NJ;
                     for (int splits = 1, cps = nchunk; ; ) {
+                        if (splits > 1 && sums > (room - packed) / splits) break;
                         const long groups = blocks * jgroups * splits;
                         const long per_cu = (groups + kCUs - 1) / kCUs;
                         // a unit with one wave per SIMD has nothing to overlap its waits with, one workgroup nothing for its stages
@@ -226,7 +238,7 @@ SplitChoice choose_split(const Geom& g, bool backward)
     const Pass P = pass_of(g, backward);
     e.choice = SplitChoice{};
     // a lane's byte offset in a source map has 32 bits
-    if ((backward ? g.ovol() : g.nvol()) < (1L << 28)) e.choice = search(P);
+    if ((backward ? g.ovol() : g.nvol()) < (1L << 28)) e.choice = search(P, backward ? SIZE_MAX : ZNN_STATIC_SCRATCH_BYTES);     // the forward pass has to do with that
     std::lock_guard<std::mutex> hold(lock);
     if (memo.size() >= 256) memo.erase(memo.begin());
     memo.push_back(e);

@@ -90,6 +90,8 @@ inline bool log_enabled() { return tuning().log; }
 
 // ---------------------------------------------------------------- direct method
 int direct_fwd(const Geom& g, const float* in, const float* w, float* out, void* ws, hipStream_t s);
+size_t direct_fwd_least(const Geom& g);         // bytes that direct_fwd_groups needs
+int direct_fwd_groups(const Geom& g, const float* in, const float* w, float* out, void* ws, hipStream_t s);
 int direct_bwd(const Geom& g, const float* gout, const float* w, float* gin, void* ws, hipStream_t s);
 int direct_wgrad(const Geom& g, const float* in, const float* gout, float* gw, void* ws, hipStream_t s);
 size_t direct_workspace_bytes(const Geom& g, int pass);

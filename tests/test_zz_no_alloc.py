@@ -90,3 +90,27 @@ def test_forward_without_allocation_refuses_layers_beyond_the_array():
                                          ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(0))
     assert rc == znn.ZNN_EWORKSPACE and "built-in array" in znn.last_error()
     p.close()
+
+
+# layers of the direct method whose weights, or sums of the shares of their input maps, take more than the array: three groups of maps
+# (the last one smaller), shares of the input maps as well, and a layer whose weights of sixteen output maps do not fit
+WIDE = [(200, 213, (6, 9, 20), (5, 5, 5), True), (160, 120, (8, 9, 12), (7, 7, 7), True), (512, 3, (9, 9, 10), (9, 9, 9), False)]
+
+
+@pytest.mark.parametrize("f,fo,n,k,same", WIDE)
+def test_forward_without_allocation_takes_the_output_maps_of_a_layer_in_groups(f, fo, n, k, same):
+    import torch
+    print("case", f, fo, n, k, flush=True)
+    x = torch.rand((f,) + n, device="cuda:0") * 2 - 1
+    w = torch.rand((fo, f) + k, device="cuda:0") * 2 - 1
+    p = znn.Plan(f, fo, n, k, "direct")
+    assert not same or p.workspace_bytes(znn.ZNN_PASS_FWD) > znn.STATIC_SCRATCH_BYTES
+    want = p.fwd(x, w)
+    got = torch.full_like(want, float("nan"))
+    p.fwd_static(x, w, got)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want) or not same
+    # sums of f k^3 rounded products in two orders
+    size = p.fwd(x.abs(), w.abs())
+    assert bool(((got - want).abs() <= 2.0 ** -23 * (f * k[0] * k[1] * k[2]) ** 0.5 * 4 * size).all())
+    p.close()
