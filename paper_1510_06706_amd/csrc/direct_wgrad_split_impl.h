@@ -261,17 +261,7 @@ __global__ void __launch_bounds__(64 * kGradWaves) k_wgrad_split(GradTile P)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) acc[jt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
         const long ovol = (long)C.o[0] * C.o[1] * C.o[2], nvol = (long)C.n[0] * C.n[1] * C.n[2];
-        for (int tile = first; tile < last; ++tile) {
-            bool open = tile == first;
-#pragma unroll
-            for (int jt = 0; jt < NJ; ++jt)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        open = open || (acc[jt][nt][r] == acc[jt][nt][r] && (jg * NJ + jt) * 16 + grp * 4 + r < C.fo &&
-                                        n0 + (set * NT + nt) * 16 + col < ncols);
-            if (!__builtin_amdgcn_ballot_w64(open)) break;      // a NaN stays one
+        for (int tile = first; tile < last; ++tile)
             for (int ks = kw; ks < C.steps; ks += C.KW)
                 for (int e = 0; e < 8; ++e) {
                     const int tx = tile % C.tiles_x, tr = tile / C.tiles_x, ty = tr % C.tiles_y, tz = tr / C.tiles_y;
@@ -301,7 +291,6 @@ __global__ void __launch_bounds__(64 * kGradWaves) k_wgrad_split(GradTile P)
                         for (int nt = 0; nt < NT; ++nt)
                             acc[jt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[jt], bv[nt], acc[jt][nt], 0, 0, 0);
                 }
-        }
     }
 
     // add the sums of the KW waves of each set, pairs first
