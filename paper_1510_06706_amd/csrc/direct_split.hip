@@ -16,7 +16,7 @@ using split::SplitFn;
 using split::SplitTile;
 
 // Weights for the split kernel: a thread makes the three parts of eight input maps' weights at one tap, [group][chunk][step]
-// [16-map tile][part][lane].  The leading part of a number that would round to infinity is cut instead, and an infinity or
+// [16-map tile][part][lane], negative in every second step.  The leading part of a number that would round to infinity is cut instead, and an infinity or
 // NaN has no other parts, so that the parts always add up to the weight.
 __device__ __forceinline__ void pack_split(const PackItem& P, long t)
 {
@@ -31,13 +31,14 @@ __device__ __forceinline__ void pack_split(const PackItem& P, long t)
     float v[8];
     split::uintx4 part[3];
     bool odd = false;
+    const float sign = split::step_negative(s, steps, ic) ? -1.f : 1.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const int k = ic * split::kMaps + e;
         const bool in = m < fM && k < fK && tap < taps;
         const long at = P.backward ? ((long)k * P.f + m) * taps + (taps - 1 - tap) : ((long)m * P.f + k) * taps + tap;
         const float x = P.w[in ? at : 0];       // all eight loads are in flight together
-        v[e] = in ? x : 0.f;
+        v[e] = in ? x * sign : 0.f;
         odd = odd || !(fabsf(v[e]) < 3.38e38f);
     }
     if (!odd) {

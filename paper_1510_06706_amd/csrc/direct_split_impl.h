@@ -35,9 +35,15 @@ constexpr int kTaps = 4;            // taps of a step
 constexpr int kVoxelBytes = kVectorBytes;     // three parts of eight maps
 constexpr int kFetch = 2;           // halo voxels a thread has in flight
 
+// Sign of a step: every second one of a chunk, and a last one without a partner in every second chunk.
+__device__ __forceinline__ bool step_negative(int step, int steps, int chunk)
+{
+    return step & 1 || ((steps & 1) && step == steps - 1 && (chunk & 1));
+}
+
 struct SplitTile {
     const float* src;       // K-side images [fK][sz][sy][sx]
-    const uintx4* wp;       // packed weights [jgroup][chunk][step][NJ][3][64]
+    const uintx4* wp;       // packed weights [jgroup][chunk][step][NJ][3][64], negative where step_negative
     float* dst;             // M-side images [fM][dz][dy][dx]
     int fK, fM;
     int sz, sy, sx;
@@ -182,6 +188,7 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
                 for (int p = 0; p < 3; ++p) a[jt][p] = __builtin_bit_cast(bf16x8, wq[(jt * 3 + p) * 64]);
         };
         weights(a0);
+        const float lone = ic & 1 ? -1.f : 1.f;         // sign of a last step without a partner
         __syncthreads();                                // nobody still reads the chunk before
         stage(ic);
         __syncthreads();
@@ -194,8 +201,8 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
         };
         voxels(b0, voff[0] + now);
         // One step: the MFMAs of a voxel tile run while the operands of the next one arrive.  PAR: which register set of
-        // the voxel operands the step's first tile is in.
-        auto step = [&](bf16x8 (&a)[NJ][3], bf16x8 (&an)[NJ][3], auto par) __attribute__((always_inline)) {
+        // the voxel operands the step's first tile is in; sign, before: how add_signed takes its tiles, and those before.
+        auto step = [&](bf16x8 (&a)[NJ][3], bf16x8 (&an)[NJ][3], auto sign, auto before, auto par) __attribute__((always_inline)) {
             constexpr int PAR = decltype(par)::value;
             wq += wstep;
             weights(an);                                // behind the last step: the next chunk's, or the padding
@@ -213,23 +220,30 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
                 floatx4* into[NJ];
 #pragma unroll
                 for (int jt = 0; jt < NJ; ++jt) into[jt] = &acc[jt][(nv + NV - 1) % NV];
-                products<NJ>((PAR + nv) & 1 ? t1 : t0, a, b, (PAR + nv) & 1 ? t0 : t1, into);
+                floatx4 (&t)[NJ] = (PAR + nv) & 1 ? t1 : t0;
+                floatx4 (&tb)[NJ] = (PAR + nv) & 1 ? t0 : t1;       // the tile before; for the first one, of the step before
+                if (nv == 0) products<NJ, decltype(before)::value>(t, a, b, tb, lone, into);
+                else products<NJ, decltype(sign)::value>(t, a, b, tb, lone, into);
             }
         };
         constexpr int ODD = NV & 1;
+        const std::integral_constant<int, 1> plus;
+        const std::integral_constant<int, -1> minus;
+        const std::integral_constant<int, 0> either;
         int s = 0;
         for (; s + 2 <= P.steps; s += 2) {
-            step(a0, a1, std::integral_constant<int, 0>{});
-            step(a1, a0, std::integral_constant<int, ODD>{});
+            step(a0, a1, plus, minus, std::integral_constant<int, 0>{});
+            step(a1, a0, minus, plus, std::integral_constant<int, ODD>{});
         }
-        if (s < P.steps) step(a0, a1, std::integral_constant<int, 0>{});
+        if (s < P.steps) step(a0, a1, either, minus, std::integral_constant<int, 0>{});
         // the last tile's: in set 0 or 1 by the parity of steps x NV
+        const float last = P.steps & 1 ? lone : -1.f;
         if (P.steps & ODD & 1) {
 #pragma unroll
-            for (int jt = 0; jt < NJ; ++jt) acc[jt][NV - 1] += t0[jt];
+            for (int jt = 0; jt < NJ; ++jt) add_signed<0>(acc[jt][NV - 1], t0[jt], last);
         } else {
 #pragma unroll
-            for (int jt = 0; jt < NJ; ++jt) acc[jt][NV - 1] += t1[jt];
+            for (int jt = 0; jt < NJ; ++jt) add_signed<0>(acc[jt][NV - 1], t1[jt], last);
         }
     }
 
@@ -266,6 +280,7 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
                             part[p] = __builtin_bit_cast(float, m & 1 ? u & 0xffff0000u : u << 16);
                         }
                         w[jt] = part[0] + (part[1] + part[2]);
+                        if (step_negative(q / kTaps, P.steps, ic)) w[jt] = -w[jt];
                     }
 #pragma unroll
                     for (int nv = 0; nv < NV; ++nv) {

@@ -20,8 +20,10 @@ using namespace split;
 // the tap spacing sp); vectors q from `real` on, and voxels outside the image, are zero.
 struct SplitImage {
     const float* src; uintx4* dst;
-    int n[3], E[3], Q[3], sp[3], real[3], V[3], all[3], r0[3], q0[3];      // all: vectors of all residues
+    int n[3], sp[3], real[3], V[3], all[3], r0[3], q0[3];      // all: vectors of all residues
+    int step[3], log2E[3];  // Q sp, E
     long vectors;
+    int signs;              // 1: steps (four vectors along x) change their sign along every axis
     unsigned first;         // workgroup it starts at
     FastDiv dVX, dVY, dVZ;  // V
 };
@@ -45,16 +47,20 @@ __global__ void __launch_bounds__(256) k_split_images(SplitArgs A)
     const int rx = S.r0[2] + hx, ry = S.r0[1] + hy, rz = S.r0[0] + hz;
     const int x = S.q0[2] + (int)vx - hx * S.V[2], y = S.q0[1] + (int)vy - hy * S.V[1], z = S.q0[0] + (int)vz - hz * S.V[0];
     const float* src = S.src + map * ((long)S.n[0] * S.n[1] * S.n[2]);
-    const bool real = z < S.real[0] && y < S.real[1] && x < S.real[2];
+    const bool real = (z < S.real[0]) & (y < S.real[1]) & (x < S.real[2]);
+    const float sign = S.signs && ((vx / 4 + vy + vz) & 1) ? -1.f : 1.f;
+    const int z0 = rz + z * S.sp[0], y0 = ry + y * S.sp[1], x0 = rx + x * S.sp[2];
     float v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        // e as (e_z, e_y, e_x): E are powers of two
-        const int ex = e & (S.E[2] - 1), ey = (e / S.E[2]) & (S.E[1] - 1), ez = e / (S.E[2] * S.E[1]);
-        const int gz = rz + (ez * S.Q[0] + z) * S.sp[0], gy = ry + (ey * S.Q[1] + y) * S.sp[1], gx = rx + (ex * S.Q[2] + x) * S.sp[2];
-        const bool in = real && gz < S.n[0] && gy < S.n[1] && gx < S.n[2];
-        const float w = src[in ? ((long)gz * S.n[1] + gy) * S.n[2] + gx : 0];
-        v[e] = in ? w : 0.f;
+        // e as (e_z, e_y, e_x)
+        const int ex = e & ((1 << S.log2E[2]) - 1), ey = e >> S.log2E[2] & ((1 << S.log2E[1]) - 1), ez = e >> (S.log2E[2] + S.log2E[1]);
+        const int gz = z0 + ez * S.step[0], gy = y0 + ey * S.step[1], gx = x0 + ex * S.step[2];
+        const bool in = real & (gz < S.n[0]) & (gy < S.n[1]) & (gx < S.n[2]);
+        long at = ((long)gz * S.n[1] + gy) * S.n[2] + gx;
+        asm volatile("" : "+v"(at));        // not a branch around it, which would wait for the load before
+        const float w = src[in ? at : 0];
+        v[e] = in ? w * sign : 0.f;
     }
 #pragma unroll
     for (int p = 0; p < 3; ++p) S.dst[t * 3 + p] = take_part8(v);
@@ -379,10 +385,14 @@ int make_job(const Geom& g, const GradChoice& c, int d0, int r0, int residues, i
         P.E[d] = c.E[d]; P.Q[d] = c.Q[d]; P.R[d] = c.R[d]; P.H[d] = c.H[d];
         P.P[d] = ph[d] * P.T[d] * c.R[d];
         P.I[d] = P.P[d] + ph[d] * (k[d] - 1);
-        for (SplitImage& S : job.image) { S.E[d] = c.E[d]; S.Q[d] = c.Q[d]; S.sp[d] = P.sp[d]; S.r0[d] = P.r0[d]; S.q0[d] = P.q0[d]; }
+        for (SplitImage& S : job.image) {
+            S.step[d] = c.Q[d] * P.sp[d]; S.log2E[d] = c.E[d] / 2 - c.E[d] / 8;     // 0 to 3 of 1, 2, 4, 8
+            S.sp[d] = P.sp[d]; S.r0[d] = P.r0[d]; S.q0[d] = P.q0[d];
+        }
         sg.n[d] = o[d]; sg.all[d] = P.P[d]; sg.V[d] = P.P[d] / ph[d]; sg.real[d] = c.Q[d];
         si.n[d] = n[d]; si.all[d] = P.I[d]; si.V[d] = P.I[d] / ph[d]; si.real[d] = c.Q[d] + k[d] - 1;
     }
+    sg.signs = 1;
     sg.vectors = (long)vectors(P.P, g.fo);
     si.vectors = (long)vectors(P.I, g.f);
     sg.dst = (uintx4*)item.copies;

@@ -40,7 +40,7 @@ constexpr int kGradBuffer = 78 * 1024;      // bytes of a tile buffer
 constexpr int kGradSpans = 10;              // copies of 1 KiB of a tile per wave
 
 struct GradTile {
-    const uintx4* gs;       // gout, split: [fo][PZ][PY][PX][3]
+    const uintx4* gs;       // gout, split: [fo][PZ][PY][PX][3], negative in every second step
     const uintx4* is;       // in, split: [f][IZ][IY][IX][3]
     const float* in; const float* gout; float* partial;
     int f, fo;
@@ -149,7 +149,8 @@ __global__ void __launch_bounds__(64 * kGradWaves) k_wgrad_split(GradTile P)
         gx = tx * P.R[2]; gy = ty * P.R[1]; gz = tz * P.R[0];
         ix = gx + hx * (P.k[2] - 1); iy = gy + hy * (P.k[1] - 1); iz = gz + hz * (P.k[0] - 1);
     }
-    auto copy_tile = [&](char* buf) __attribute__((always_inline)) {
+    auto copy_tile = [&](char* buf, int& odd) __attribute__((always_inline)) {
+        odd = gx / 4 + gy + gz;         // sign of its first step
         const uintx4* g = gsrc + (((long)gz * P.P[1] + gy) * P.P[2] + gx) * 3;
         const uintx4* in = isrc + (((long)iz * P.I[1] + iy) * P.I[2] + ix) * 3;
 #pragma unroll
@@ -187,19 +188,20 @@ __global__ void __launch_bounds__(64 * kGradWaves) k_wgrad_split(GradTile P)
     __syncthreads();
 
     // The wave's steps of a staged tile.  The copies of the next tile are queued behind the requests for the first operands.
-    auto use_tile = [&](lds_bytes buf, bool more, char* other) __attribute__((always_inline)) {
+    auto use_tile = [&](lds_bytes buf, int odd, bool more, char* other, int& other_odd) __attribute__((always_inline)) {
         auto load = [&](uintx4 (&v)[3], lds_bytes at) {
 #pragma unroll
             for (int p = 0; p < 3; ++p) v[p] = reinterpret_cast<lds_quads>(at)[p];
         };
         int ks = kw;
         if (live == 0 || ks >= P.steps) {       // uniform
-            if (more) copy_tile(other);
+            if (more) copy_tile(other, other_odd);
             return;
         }
         for (; ks < P.steps; ks += P.KW) {
             const int r = (int)fdiv((unsigned)ks, P.dX4), x = (ks - r * X4) * 4, z = (int)fdiv((unsigned)r, P.dRY), y = r - z * P.R[1];
             const int ao = (r * P.R[2] + x) * kVectorBytes, bo = ((z * P.H[1] + y) * P.H[2] + x) * kVectorBytes;
+            const float sign = (odd + x / 4 + y + z) & 1 ? -1.f : 1.f;
             bf16x8 a[NJ][3];
             uintx4 b0[3], b1[3];
             floatx4 t0[NJ], t1[NJ];
@@ -212,7 +214,7 @@ __global__ void __launch_bounds__(64 * kGradWaves) k_wgrad_split(GradTile P)
                     a[jt][p] = __builtin_bit_cast(bf16x8, reinterpret_cast<lds_quads>(buf + aoff[jt] + ao)[p]);
                 }
             __builtin_amdgcn_sched_barrier(0);
-            if (more && ks == kw) copy_tile(other);
+            if (more && ks == kw) copy_tile(other, other_odd);
 #pragma unroll
             for (int jt = 0; jt < NJ; ++jt) t1[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -223,22 +225,23 @@ __global__ void __launch_bounds__(64 * kGradWaves) k_wgrad_split(GradTile P)
                 floatx4 *into[NJ];
 #pragma unroll
                 for (int jt = 0; jt < NJ; ++jt) into[jt] = &acc[jt][nt ? nt - 1 : 0];
-                products<NJ>(nt & 1 ? t1 : t0, a, b, nt & 1 ? t0 : t1, into);
+                products<NJ, 0>(nt & 1 ? t1 : t0, a, b, nt & 1 ? t0 : t1, sign, into);
             }
 #pragma unroll
-            for (int jt = 0; jt < NJ; ++jt) acc[jt][NT - 1] += (NT - 1) & 1 ? t1[jt] : t0[jt];
+            for (int jt = 0; jt < NJ; ++jt) add_signed<0>(acc[jt][NT - 1], (NT - 1) & 1 ? t1[jt] : t0[jt], sign);
         }
     };
 
-    if (first < last) copy_tile(bufA);
+    int oddA = 0, oddB = 0;
+    if (first < last) copy_tile(bufA, oddA);
     for (int tile = first; tile < last; tile += 2) {
         __builtin_amdgcn_s_waitcnt(0);      // this wave's copies have landed
         __syncthreads();                    // everyone's have, and nobody still reads the other buffer
-        use_tile(lA, tile + 1 < last, bufB);
+        use_tile(lA, oddA, tile + 1 < last, bufB, oddB);
         if (tile + 1 >= last) break;
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        use_tile(lB, tile + 2 < last, bufA);
+        use_tile(lB, oddB, tile + 2 < last, bufA, oddA);
     }
 
     // Sums that are not finite: the parts of an infinity or a NaN do not multiply as it does.  The wave's share again in fp32,

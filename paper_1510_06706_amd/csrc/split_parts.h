@@ -7,6 +7,11 @@
 // How far such sums are from 64 bits (2-norm, dot products of 5000 / 40 000 terms; fp32 instruction: 1.2e-6 / 3.6e-6): added
 // into one running sum 1.1e-6 / 3.5e-6 -- and 1.16 times the fp32 error where half of one operand is zero --, each step of six
 // summed from zero and then added 2.3e-7 / 6.3e-7.  The kernels do the latter.
+//
+// The instruction rounds its sums downwards (fp32 MFMAs round to nearest): results were low by 2e-8 to 1.3e-7 of their root mean
+// square, all by the same, and the gradients of a net of six layers, which add that up, 2e-6 off where rounding to nearest leaves
+// 3e-7.  So one operand changes its sign from step to step, and every second step is subtracted: what rounds down in one
+// rounds up in the next.
 #pragma once
 
 #include "znn_internal.h"
@@ -51,11 +56,23 @@ __device__ __forceinline__ floatx4 mfma(const bf16x8& a, const bf16x8& b, const 
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Six products of a step, from zero, smallest first, for NJ row tiles and one column tile.  acc += before is the column tile
-// before, whose products are done by now: between the instructions of this one they cost nothing.
-template <int NJ>
+// acc += sign t; SIGN: 1 or -1, or 0 where only `sign` (uniform) says it
+template <int SIGN>
+__device__ __forceinline__ void add_signed(floatx4& acc, const floatx4& t, float sign)
+{
+    if (SIGN > 0) acc += t;
+    else if (SIGN < 0) acc -= t;
+    else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = fmaf(t[r], sign, acc[r]);
+    }
+}
+
+// Six products of a step, from zero, smallest first, for NJ row tiles and one column tile.  acc += sign before (add_signed) is the
+// column tile before, whose products are done by now: between the instructions of this one they cost nothing.
+template <int NJ, int SIGN>
 __device__ __forceinline__ void products(floatx4 (&t)[NJ], const bf16x8 (&a)[NJ][3], const uintx4 (&b)[3], const floatx4 (&before)[NJ],
-                                         floatx4* const (&acc)[NJ])
+                                         float sign, floatx4* const (&acc)[NJ])
 {
     const bf16x8 c0 = __builtin_bit_cast(bf16x8, b[0]), c1 = __builtin_bit_cast(bf16x8, b[1]), c2 = __builtin_bit_cast(bf16x8, b[2]);
     const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -65,7 +82,7 @@ __device__ __forceinline__ void products(floatx4 (&t)[NJ], const bf16x8 (&a)[NJ]
 #pragma unroll
     for (int j = 0; j < NJ; ++j) t[j] = mfma(a[j][2], c0, t[j]);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) *acc[j] += before[j];
+    for (int j = 0; j < NJ; ++j) add_signed<SIGN>(*acc[j], before[j], sign);
 #pragma unroll
     for (int j = 0; j < NJ; ++j) t[j] = mfma(a[j][1], c1, t[j]);
 #pragma unroll

@@ -61,6 +61,29 @@ def test_passes_stay_within_the_bound_of_the_split(f, fo, n, k, s):
     p.close()
 
 
+@pytest.mark.parametrize("n,s", [((26, 26, 26), (1, 1, 1)), ((34, 34, 34), (4, 4, 4))])
+@pytest.mark.parametrize("half", [False, True])
+def test_errors_of_the_split_have_no_common_sign(n, s, half):
+    """The bf16 matrix instruction rounds sums downwards, by some 2^-28 of a step's sum; steps of alternating signs cancel it."""
+    f, fo, k = 40, 40, (3, 3, 3)
+    x, w, g = tensors(f, fo, n, k, s, 9106)
+    if half:                                            # what a rectifier leaves
+        x, g = np.maximum(x, 0), np.where(g > 0, g, 0).astype(np.float32)
+    p = znn.Plan(f, fo, n, k, "direct", s)
+    assert p.workspace_bytes(0) > 0 and p.workspace_bytes(1) > 0        # packed weights
+    assert p.workspace_bytes(2) > 4 * (x.size + g.size)                 # copies of the images
+
+    def unbiased(got, ref, steps):
+        e, rms = got.cpu().numpy().astype(np.float64) - ref, np.sqrt(np.mean(ref ** 2))
+        # four times the share of a step without a partner, and six standard deviations of the mean
+        assert abs(np.mean(e)) <= rms * 2.0 ** -26 / np.sqrt(steps) + 6 * np.sqrt(np.mean(e ** 2) / e.size)
+
+    unbiased(p.fwd(dev(x), dev(w)), oracle.conv3d_fwd(x, w, s), 35)
+    unbiased(p.bwd(dev(g), dev(w)), oracle.conv3d_bwd(g, w, n, s), 35)
+    unbiased(p.wgrad(dev(x), dev(g)), oracle.conv3d_wgrad(x, g, s), g[0].size // 32)
+    p.close()
+
+
 @pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** 60])
 def test_the_split_keeps_its_precision_at_any_scale(scale):
     f, fo, n, k, s = 16, 16, (10, 10, 10), (3, 3, 3), (1, 1, 1)
