@@ -25,7 +25,7 @@ struct SplitImage {
     long vectors;
     int signs;              // 1: steps (four vectors along x) change their sign along every axis
     unsigned first;         // workgroup it starts at
-    FastDiv dVX, dVY, dVZ;  // V
+    FastDiv dvol, dall[3], dV[3];   // product of all, all, V
 };
 constexpr int kGradJobs = 8;        // layers that share a launch of k_split_images
 struct SplitArgs { SplitImage image[2 * kGradJobs]; int n; };
@@ -38,12 +38,12 @@ __global__ void __launch_bounds__(256) k_split_images(SplitArgs A)
     const SplitImage& S = A.image[q];
     const long t = (long)(blockIdx.x - S.first) * 256 + threadIdx.x;
     if (t >= S.vectors) return;
-    const unsigned vol = (unsigned)S.all[0] * S.all[1] * S.all[2];
-    const unsigned map = S.vectors <= 4294967295L ? (unsigned)t / vol : (unsigned)(t / vol);
+    const unsigned vol = S.dvol.d;
+    const unsigned map = S.vectors < 2147483648L ? fdiv_any((unsigned)t, S.dvol) : (unsigned)(t / vol);
     const unsigned r = (unsigned)(t - (long)map * vol);
-    // quotients by FastDiv are exact where the dividend is small: rows and planes, after one division of the whole
-    const unsigned row = r / (unsigned)S.all[2], vx = r - row * S.all[2], vz = row / (unsigned)S.all[1], vy = row - vz * S.all[1];
-    const int hx = (int)fdiv(vx, S.dVX), hy = (int)fdiv(vy, S.dVY), hz = (int)fdiv(vz, S.dVZ);
+    // an axis may be long: quotients have to be exact for any dividend
+    const unsigned row = fdiv_any(r, S.dall[2]), vx = r - row * S.all[2], vz = fdiv_any(row, S.dall[1]), vy = row - vz * S.all[1];
+    const int hx = (int)fdiv_any(vx, S.dV[2]), hy = (int)fdiv_any(vy, S.dV[1]), hz = (int)fdiv_any(vz, S.dV[0]);
     const int rx = S.r0[2] + hx, ry = S.r0[1] + hy, rz = S.r0[0] + hz;
     const int x = S.q0[2] + (int)vx - hx * S.V[2], y = S.q0[1] + (int)vy - hy * S.V[1], z = S.q0[0] + (int)vz - hz * S.V[0];
     const float* src = S.src + map * ((long)S.n[0] * S.n[1] * S.n[2]);
@@ -57,9 +57,9 @@ __global__ void __launch_bounds__(256) k_split_images(SplitArgs A)
         const int ex = e & ((1 << S.log2E[2]) - 1), ey = e >> S.log2E[2] & ((1 << S.log2E[1]) - 1), ez = e >> (S.log2E[2] + S.log2E[1]);
         const int gz = z0 + ez * S.step[0], gy = y0 + ey * S.step[1], gx = x0 + ex * S.step[2];
         const bool in = real & (gz < S.n[0]) & (gy < S.n[1]) & (gx < S.n[2]);
-        long at = ((long)gz * S.n[1] + gy) * S.n[2] + gx;
+        unsigned at = (gz * S.n[1] + gy) * S.n[2] + gx;     // a map has less than 2^30 voxels
         asm volatile("" : "+v"(at));        // not a branch around it, which would wait for the load before
-        const float w = src[in ? at : 0];
+        const float w = src[in ? at : 0u];
         v[e] = in ? w * sign : 0.f;
     }
 #pragma unroll
@@ -255,26 +255,6 @@ GradChoice search(const Geom& g)
     return best;
 }
 
-GradChoice choose(const Geom& g)
-{
-    struct Entry { int key[14]; GradChoice choice; };
-    static std::mutex lock;
-    static std::vector<Entry> memo;
-    Entry e;
-    const int key[14] = {g.f, g.fo, g.nz, g.ny, g.nx, g.kz, g.ky, g.kx, g.spz, g.spy, g.spx, g.oz, g.oy, g.ox};
-    memcpy(e.key, key, sizeof(key));
-    {
-        std::lock_guard<std::mutex> hold(lock);
-        for (const Entry& m : memo)
-            if (memcmp(m.key, key, sizeof(key)) == 0) return m.choice;
-    }
-    e.choice = search(g);
-    std::lock_guard<std::mutex> hold(lock);
-    if (memo.size() >= 256) memo.erase(memo.begin());
-    memo.push_back(e);
-    return e.choice;
-}
-
 size_t vectors(const int (&v)[3], int maps) { return (size_t)maps * v[0] * v[1] * v[2]; }
 
 // The images are copied, and the gradient summed, in slabs along the first axis that has tiles to share out, so that the copies of
@@ -305,6 +285,33 @@ Slabs slabs_of(const Geom& g, const GradChoice& c)
     }
     S.bytes = bytes(S.residues, S.rows);
     return S;
+}
+
+// The kernels index voxels of a map and 16-byte units of a slab's copies with 32 bits.
+bool indexes_fit(const Geom& g, const GradChoice& c)
+{
+    return g.nvol() < (1L << 30) && slabs_of(g, c).bytes / kPartBytes < (1L << 31);
+}
+
+GradChoice choose(const Geom& g)
+{
+    struct Entry { int key[14]; GradChoice choice; };
+    static std::mutex lock;
+    static std::vector<Entry> memo;
+    Entry e;
+    const int key[14] = {g.f, g.fo, g.nz, g.ny, g.nx, g.kz, g.ky, g.kx, g.spz, g.spy, g.spx, g.oz, g.oy, g.ox};
+    memcpy(e.key, key, sizeof(key));
+    {
+        std::lock_guard<std::mutex> hold(lock);
+        for (const Entry& m : memo)
+            if (memcmp(m.key, key, sizeof(key)) == 0) return m.choice;
+    }
+    e.choice = search(g);
+    if (e.choice.ok && !indexes_fit(g, e.choice)) e.choice.ok = false;
+    std::lock_guard<std::mutex> hold(lock);
+    if (memo.size() >= 256) memo.erase(memo.begin());
+    memo.push_back(e);
+    return e.choice;
 }
 
 }  // namespace
@@ -399,7 +406,8 @@ int make_job(const Geom& g, const GradChoice& c, int d0, int r0, int residues, i
     si.dst = (uintx4*)((char*)item.copies + align256(vectors(P.P, g.fo) * kVectorBytes));
     P.gs = sg.dst; P.is = si.dst;
     for (SplitImage& S : job.image) {
-        S.dVZ = make_fastdiv((unsigned)S.V[0]); S.dVY = make_fastdiv((unsigned)S.V[1]); S.dVX = make_fastdiv((unsigned)S.V[2]);
+        for (int d = 0; d < 3; ++d) { S.dall[d] = make_fastdiv((unsigned)S.all[d]); S.dV[d] = make_fastdiv((unsigned)S.V[d]); }
+        S.dvol = make_fastdiv((unsigned)S.all[0] * S.all[1] * S.all[2]);
     }
     const long blocks0 = (sg.vectors + 255) / 256, blocks1 = (si.vectors + 255) / 256;
     P.tiles_y = ph[1] * P.T[1]; P.tiles_x = ph[2] * P.T[2];

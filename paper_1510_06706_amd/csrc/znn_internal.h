@@ -67,6 +67,13 @@ __device__ __forceinline__ unsigned fdiv(unsigned n, FastDiv f)
 {
     return f.d <= 1 ? n : __umulhi(n, f.M);
 }
+// The same for any n with n + d < 2^32: n M / 2^32 lies less than one above n / d.
+__host__ __device__ __forceinline__ unsigned fdiv_any(unsigned n, FastDiv f)
+{
+    if (f.d <= 1) return n;
+    const unsigned q = (unsigned)((unsigned long)n * f.M >> 32);
+    return q * f.d > n ? q - 1 : q;
+}
 
 // Tuning aids.  The environment is read exactly once, the first time anything asks (plan
 // creation at the latest), and never on a launch path; none of them changes a data layout.

@@ -186,3 +186,19 @@ def test_kernel_gradient_of_large_layers_in_slabs(f, fo, n, k, s):
     # sums this long are far inside the worst case: a tenth of it still leaves a lost or doubled slab no room
     assert np.all(np.abs(gw.astype(np.float64) - ref) <= 0.1 * (2 * (g[0].size // 32) + 600) * 2.0 ** -24 * ref_abs)
     p.close()
+
+
+@pytest.mark.parametrize("f,fo,n,k,s", [
+    (16, 16, (1, 1, 1200000), (1, 1, 5), (1, 1, 1)),    # pieces of 150 000 vectors
+    (16, 16, (1, 1, 1300001), (1, 1, 5), (1, 1, 2)),    # two residues of pieces of 81 000
+])
+def test_kernel_gradient_of_long_rows(f, fo, n, k, s):
+    x, w, g = tensors(f, fo, n, k, s, 9107)
+    p = znn.Plan(f, fo, n, k, "direct", s)
+    assert p.workspace_bytes(2) > 4 * (x.size + g.size)                 # copies of the images
+    gw = p.wgrad(dev(x), dev(g)).cpu().numpy()
+    ref, ref_abs = oracle.conv3d_wgrad(x, g, s), oracle.conv3d_wgrad(np.abs(x), np.abs(g), s)
+    # The sums walk randomly, some 1e-3 of ref_abs far, and so do their roundings: 2^-24 1e-3 sqrt(voxels / 32) is 1e-8 of it.  32 wrong
+    # voxels of a million (four vectors) are off by sqrt(32) / 3 products of size 1, 6e-6 of it.
+    assert np.all(np.abs(gw.astype(np.float64) - ref) <= 5e-7 * ref_abs)
+    p.close()
