@@ -22,7 +22,7 @@ double split_seconds(const SplitChoice& c);
 size_t split_packed_bytes(const SplitChoice& c);
 PackItem split_pack_item(const Geom& g, const SplitChoice& c, bool backward, const float* w, void* wp);
 int split_pack_weights(const PackItem* items, int n, hipStream_t s);
-int split_conv(const Geom& g, const SplitChoice& c, bool backward, const float* src, const void* wp, float* dst, float* partial,
+int split_conv(const Geom& g, const SplitChoice& c, bool backward, const float* src, const float* w, const void* wp, float* dst, float* partial,
                const Finish& finish, hipStream_t s);
 
 // ---- kernel gradient on split operands (direct_wgrad_split.hip)

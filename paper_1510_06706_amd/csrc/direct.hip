@@ -71,7 +71,7 @@ int conv_pass(const Geom& g, bool backward, const float* src, const float* w, co
               const Finish& finish, hipStream_t s)
 {
     const SplitChoice c = way(g, backward);
-    return c.ok ? split_conv(g, c, backward, src, wp, dst, partial, finish, s) : few_conv(g, backward, src, w, dst, finish, s);
+    return c.ok ? split_conv(g, c, backward, src, w, wp, dst, partial, finish, s) : few_conv(g, backward, src, w, dst, finish, s);
 }
 
 int conv_sum(const Geom& g, bool backward, const float* partial, float* dst, hipStream_t s)
@@ -158,9 +158,10 @@ int direct_fwd_groups(const Geom& g, const float* in, const float* w, float* out
     for (int first = 0; first < g.fo; first += 16 * c.NJ) {
         const Geom q = group_of(g, c, first);
         float* dst = out + (long)first * g.ovol();
-        const PackItem p = split_pack_item(q, c, false, w + (long)first * g.f * g.kvol(), ws);
+        const float* wq = w + (long)first * g.f * g.kvol();
+        const PackItem p = split_pack_item(q, c, false, wq, ws);
         int rc = split_pack_weights(&p, 1, s);
-        if (rc == ZNN_OK) rc = split_conv(q, c, false, in, ws, dst, partial, Finish{}, s);
+        if (rc == ZNN_OK) rc = split_conv(q, c, false, in, wq, ws, dst, partial, Finish{}, s);
         if (rc != ZNN_OK) return rc;
         if (c.splits == 1) continue;
         const long count = result_count(q, false);

@@ -16,8 +16,7 @@ using split::SplitFn;
 using split::SplitTile;
 
 // Weights for the split kernel: a thread makes the three parts of eight input maps' weights at one tap, [group][chunk][step]
-// [16-map tile][part][lane], negative in every second step.  The leading part of a number that would round to infinity is cut instead, and an infinity or
-// NaN has no other parts, so that the parts always add up to the weight.
+// [16-map tile][part][lane], negative in every second step.
 __device__ __forceinline__ void pack_split(const PackItem& P, long t)
 {
     const int taps = P.taps, steps = (taps + split::kTaps - 1) / split::kTaps;
@@ -29,37 +28,18 @@ __device__ __forceinline__ void pack_split(const PackItem& P, long t)
     const int m = (jg * P.NJ + jt) * 16 + (lane & 15), tap = s * split::kTaps + (lane >> 4);
     const int fM = P.backward ? P.f : P.fo, fK = P.backward ? P.fo : P.f;
     float v[8];
-    split::uintx4 part[3];
-    bool odd = false;
-    const float sign = split::step_negative(s, steps, ic) ? -1.f : 1.f;
+    const float scale = split::step_negative(s, steps, ic) ? -split::kScale : split::kScale;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const int k = ic * split::kMaps + e;
         const bool in = m < fM && k < fK && tap < taps;
         const long at = P.backward ? ((long)k * P.f + m) * taps + (taps - 1 - tap) : ((long)m * P.f + k) * taps + tap;
         const float x = P.w[in ? at : 0];       // all eight loads are in flight together
-        v[e] = in ? x * sign : 0.f;
-        odd = odd || !(fabsf(v[e]) < 3.38e38f);
-    }
-    if (!odd) {
-#pragma unroll
-        for (int p = 0; p < 3; ++p) part[p] = split::take_part8(v);
-    } else {
-        part[0] = part[1] = part[2] = split::uintx4{0u, 0u, 0u, 0u};
-        for (int e = 0; e < 8; ++e) {
-            float x = v[e];
-            for (int p = 0; p < 3; ++p) {
-                unsigned u = __builtin_bit_cast(unsigned, x);
-                if (x != x) u |= 0x400000u;                                                 // stays a NaN
-                u &= 0xffff0000u;
-                part[p][e >> 1] |= e & 1 ? u : u >> 16;
-                x = fabsf(x) <= 3.4028234e38f ? x - __builtin_bit_cast(float, u) : 0.f;
-            }
-        }
+        v[e] = in ? x * scale : 0.f;
     }
     split::uintx4* out = reinterpret_cast<split::uintx4*>(P.wp) + (t >> 6) * 3 * 64 + lane;
 #pragma unroll
-    for (int p = 0; p < 3; ++p) out[p * 64] = part[p];
+    for (int p = 0; p < 3; ++p) out[p * 64] = split::take_part8(v);
 }
 
 // Several layers and passes at a time: the weights of a round take one launch instead of one per convolution.  N = 1 serves the
@@ -287,12 +267,13 @@ int split_pack_weights(const PackItem* items, int n, hipStream_t s)
     return check_launch("weight packing");
 }
 
-int split_conv(const Geom& g, const SplitChoice& c, bool backward, const float* src, const void* wp, float* dst, float* partial,
+int split_conv(const Geom& g, const SplitChoice& c, bool backward, const float* src, const float* w, const void* wp, float* dst, float* partial,
                const Finish& finish, hipStream_t s)
 {
     const Pass p = pass_of(g, backward);
     SplitTile P = {};
     P.src = src; P.wp = (const split::uintx4*)wp; P.dst = dst;
+    P.w = w; P.wm = backward ? g.kvol() : g.f * g.kvol(); P.wk = backward ? g.f * g.kvol() : g.kvol(); P.reflected = backward ? 1 : 0;
     P.fK = p.fK; P.fM = p.fM;
     P.sz = p.a[0].s; P.sy = p.a[1].s; P.sx = p.a[2].s;
     P.pz = p.a[0].p; P.py = p.a[1].p; P.px = p.a[2].p;

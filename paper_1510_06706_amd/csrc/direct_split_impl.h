@@ -45,6 +45,9 @@ struct SplitTile {
     const float* src;       // K-side images [fK][sz][sy][sx]
     const uintx4* wp;       // packed weights [jgroup][chunk][step][NJ][3][64], negative where step_negative
     float* dst;             // M-side images [fM][dz][dy][dx]
+    const float* w;         // weights: tap t of result map m and source map k at m wm + k wk + t, t from the end where `reflected`
+    long wm, wk;
+    int reflected;
     int fK, fM;
     int sz, sy, sx;
     int pz, py, px;         // taps of zeros virtually in front of the source (in units of the tap spacing)
@@ -163,9 +166,10 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
 #pragma unroll
             for (int i = 0; i < kFetch; ++i)
                 if (r0 + i * NT < P.hvol) {
-                    const bool in = from[r0 + i * NT] != ~0u;
+                    // maps that do not exist have weights of zero
+                    const float scale = from[r0 + i * NT] != ~0u ? kScale : 0.f;
 #pragma unroll
-                    for (int m = 0; m < kMaps; ++m) v[i][m] = in && m < nvalid ? v[i][m] : 0.f;
+                    for (int m = 0; m < kMaps; ++m) v[i][m] *= scale;
                     uintx4* at = reinterpret_cast<uintx4*>(smem + (r0 + i * NT) * kVoxelBytes);
 #pragma unroll
                     for (int p = 0; p < 3; ++p) at[p] = take_part8(v[i]);
@@ -247,8 +251,14 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
         }
     }
 
-    // An infinity or a NaN among the operands makes the parts' products NaN where the product itself may not be: sums that
-    // are not finite are taken again in fp32, straight from memory, as v_mfma_f32_16x16x4_f32 gives them.
+#pragma unroll
+    for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+        for (int nv = 0; nv < NV; ++nv) acc[jt][nv] *= kUnscale;
+
+    // An infinity or a NaN among the operands (or the voxel read in place of a zero) makes the parts' products NaN where the
+    // product itself may not be: sums that are not finite are taken again in fp32, straight from memory, as
+    // v_mfma_f32_16x16x4_f32 gives them.
     bool bad = false;
 #pragma unroll
     for (int jt = 0; jt < NJ; ++jt)
@@ -267,20 +277,13 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
         for (int ic = ic0; ic < ic1; ++ic)
             for (int q = 0; q < taps; ++q) {
                 const int c = q % P.kx, r = q / P.kx, b = r % P.ky, a = r / P.ky;
-                const uintx4* wt = P.wp + (((long)jg * P.nchunk + ic) * P.steps + q / kTaps) * wstep + (q % kTaps) * 16 + col;
                 for (int h = 0; h < kMaps / 4; ++h) {
                     const int m = h * 4 + grp, map = ic * kMaps + m;        // the lane's input map
                     float w[NJ], v[NV];
 #pragma unroll
                     for (int jt = 0; jt < NJ; ++jt) {
-                        float part[3];
-#pragma unroll
-                        for (int p = 0; p < 3; ++p) {
-                            const unsigned u = reinterpret_cast<const unsigned*>(wt + (jt * 3 + p) * 64)[m >> 1];
-                            part[p] = __builtin_bit_cast(float, m & 1 ? u & 0xffff0000u : u << 16);
-                        }
-                        w[jt] = part[0] + (part[1] + part[2]);
-                        if (step_negative(q / kTaps, P.steps, ic)) w[jt] = -w[jt];
+                        const int to = (jg * NJ + jt) * 16 + col;
+                        w[jt] = map < P.fK && to < P.fM ? P.w[to * P.wm + map * P.wk + (P.reflected ? taps - 1 - q : q)] : 0.f;
                     }
 #pragma unroll
                     for (int nv = 0; nv < NV; ++nv) {

@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(256) k_split_images(SplitArgs A)
     const int x = S.q0[2] + (int)vx - hx * S.V[2], y = S.q0[1] + (int)vy - hy * S.V[1], z = S.q0[0] + (int)vz - hz * S.V[0];
     const float* src = S.src + map * ((long)S.n[0] * S.n[1] * S.n[2]);
     const bool real = (z < S.real[0]) & (y < S.real[1]) & (x < S.real[2]);
-    const float sign = S.signs && ((vx / 4 + vy + vz) & 1) ? -1.f : 1.f;
+    const float scale = S.signs && ((vx / 4 + vy + vz) & 1) ? -kScale : kScale;
     const int z0 = rz + z * S.sp[0], y0 = ry + y * S.sp[1], x0 = rx + x * S.sp[2];
     float v[8];
 #pragma unroll
@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(256) k_split_images(SplitArgs A)
         unsigned at = (gz * S.n[1] + gy) * S.n[2] + gx;     // a map has less than 2^30 voxels
         asm volatile("" : "+v"(at));        // not a branch around it, which would wait for the load before
         const float w = src[in ? at : 0u];
-        v[e] = in ? w * sign : 0.f;
+        v[e] = in ? w * scale : 0.f;
     }
 #pragma unroll
     for (int p = 0; p < 3; ++p) S.dst[t * 3 + p] = take_part8(v);

@@ -201,7 +201,7 @@ __global__ void __launch_bounds__(64 * kGradWaves) k_wgrad_split(GradTile P)
         for (; ks < P.steps; ks += P.KW) {
             const int r = (int)fdiv((unsigned)ks, P.dX4), x = (ks - r * X4) * 4, z = (int)fdiv((unsigned)r, P.dRY), y = r - z * P.R[1];
             const int ao = (r * P.R[2] + x) * kVectorBytes, bo = ((z * P.H[1] + y) * P.H[2] + x) * kVectorBytes;
-            const float sign = (odd + x / 4 + y + z) & 1 ? -1.f : 1.f;
+            const float sign = (odd + x / 4 + y + z) & 1 ? -kUnscale : kUnscale;
             bf16x8 a[NJ][3];
             uintx4 b0[3], b1[3];
             floatx4 t0[NJ], t1[NJ];

@@ -1,7 +1,10 @@
 // fp32 numbers as sums of three bf16 numbers, for the direct kernels that multiply them on the bf16 matrix cores.
 //
-// x = x0 + x1 + x2 with 8 significant bits each holds the 24 bits of x.  A product is taken as x0 y0 + (x0 y1 + x1 y0) +
-// (x0 y2 + x1 y1 + x2 y0): what is left out is below 2^-23 of it, every partial product is exact, and sums are kept in fp32.
+// 2^16 x = x0 + x1 + x2 with 8 significant bits each holds the 24 bits of x, or all that a subnormal x has: bf16 reaches down to 2^-133,
+// so without the factor operands below 2^-110 would lose bits (all but eight at 2^-126).  A product is taken as x0 y0 + (x0 y1 + x1 y0) +
+// (x0 y2 + x1 y1 + x2 y0): what is left out is below 2^-24 of it, every partial product is exact, and sums are kept in fp32, 2^32
+// too large until they are done.  Sums from 2^96 on may so be infinite, as parts of operands from 2^112 on are: results that are not
+// finite are taken again by the kernels, in fp32 from memory.
 // Six v_mfma_f32_16x16x32_bf16 (16 clocks each) do the work of eight v_mfma_f32_16x16x4_f32 (32 clocks each).
 //
 // How far such sums are from 64 bits (2-norm, dot products of 5000 / 40 000 terms; fp32 instruction: 1.2e-6 / 3.6e-6): added
@@ -31,6 +34,8 @@ typedef __attribute__((address_space(3))) const int* lds_ints;
 constexpr int kPartBytes = 16;      // one part of eight numbers
 constexpr int kVectorBytes = 48;    // three parts of eight numbers
 constexpr float kLargest = 3.4028234e38f;
+constexpr float kScale = 65536.f;                       // of an operand
+constexpr float kUnscale = 1.f / (kScale * kScale);     // of a sum
 
 // The leading bf16 part of x and y, packed; x and y keep the rest, which is exact.
 __device__ __forceinline__ unsigned take_part(float& x, float& y)

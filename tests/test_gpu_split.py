@@ -94,6 +94,31 @@ def test_the_split_keeps_its_precision_at_any_scale(scale):
     p.close()
 
 
+@pytest.mark.parametrize("ex,ew", [(-112, 0), (-120, 0), (-126, 0), (-138, 0), (0, -126), (-62, -62), (-66, -66), (45, 44)])
+def test_the_split_keeps_its_precision_to_the_ends_of_the_range(ex, ew):
+    """Operands near and below the smallest normal number, products near it, and sums that are finite only without the split's scale."""
+    f, fo, n, k = 40, 40, (26, 26, 26), (3, 3, 3)
+    x, w, g = tensors(f, fo, n, k, (1, 1, 1), 9108)
+    p = znn.Plan(f, fo, n, k, "direct")
+    assert p.workspace_bytes(0) > 0 and p.workspace_bytes(1) > 0        # packed weights
+    assert p.workspace_bytes(2) > 4 * (x.size + g.size)                 # copies of the images
+    x, g, v, w = (np.ldexp(a, e).astype(np.float32) for a, e in ((x, ex), (g, ex), (g, ew), (w, ew)))
+
+    def close(got, ref, limit):
+        # a share's sum and their sum may be subnormal: rounded to 2^-149
+        assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= limit + 16 * 2.0 ** -149)
+
+    def fp32(maps, ref_abs):        # sums taken again in fp32 round once per product
+        return (27 * maps + 16) * 2.0 ** -24 * ref_abs if ex + ew > 80 else bound(ref_abs, maps, 27)
+
+    close(p.fwd(dev(x), dev(w)), oracle.conv3d_fwd(x, w), fp32(f, oracle.conv3d_fwd(np.abs(x), np.abs(w))))
+    close(p.bwd(dev(g), dev(w)), oracle.conv3d_bwd(g, w, n), fp32(fo, oracle.conv3d_bwd(np.abs(g), np.abs(w), n)))
+    voxels = g[0].size
+    close(p.wgrad(dev(x), dev(v)), oracle.conv3d_wgrad(x, v),
+          (2 * (voxels // (1 if ex + ew > 80 else 32)) + 600) * 2.0 ** -24 * oracle.conv3d_wgrad(np.abs(x), np.abs(v)))
+    p.close()
+
+
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38])
 def test_operands_that_are_not_finite_act_as_in_fp32(value):
     f, fo, n, k, s = 9, 20, (11, 12, 13), (3, 3, 3), (1, 1, 1)
