@@ -160,8 +160,9 @@ int  znn_conv3d_fwd(znn_plan* plan, const float* in, const float* w, float* out,
  * The call allocates and frees nothing.  A layer whose forward pass needs more scratch than
  * that (znn_plan_workspace_bytes) is refused with ZNN_EWORKSPACE before anything is launched --
  * on tiles (znn_plan_tiles) only one that would need more on whole volumes; the tiles of others
- * come in groups that fit, as do the output maps of layers on the direct method (of which those whose weights of sixteen
- * output maps do not fit, some 340000 taps in all, take kernels without scratch and may differ in rounding).
+ * come in groups that fit, as do the output maps of layers on the direct method and the shares of their input maps (of which those
+ * whose weights of sixteen output maps do not fit, some 340000 taps in all, take kernels without scratch, those whose partial sums of
+ * one share do not fit beside these take no shares, and both may differ in rounding).
  * All calls on one GPU share the one array: calls that may overlap in time on the same GPU (two
  * streams, two threads) race and must be serialised by the caller; calls on one stream are safe.
  * The array's device address is looked up on the first call per device, with that device current.

@@ -22,8 +22,9 @@ double split_seconds(const SplitChoice& c);
 size_t split_packed_bytes(const SplitChoice& c);
 PackItem split_pack_item(const Geom& g, const SplitChoice& c, bool backward, const float* w, void* wp);
 int split_pack_weights(const PackItem* items, int n, hipStream_t s);
+// `shares` shares of the input maps from share0 on, 0: all of them.  More than one: a result array of `partial` each; one: into dst.
 int split_conv(const Geom& g, const SplitChoice& c, bool backward, const float* src, const float* w, const void* wp, float* dst, float* partial,
-               const Finish& finish, hipStream_t s);
+               const Finish& finish, hipStream_t s, int share0 = 0, int shares = 0);
 
 // ---- kernel gradient on split operands (direct_wgrad_split.hip)
 bool split_grad_supported(const Geom& g);

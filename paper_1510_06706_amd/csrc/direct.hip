@@ -13,15 +13,22 @@ namespace znn {
 
 namespace {
 
-// x = sum of the shares in ascending order
+// x = sum of the shares in ascending order, behind what x holds where `more`
 __global__ void __launch_bounds__(256)
-k_conv_reduce(const float* __restrict__ partial, float* __restrict__ dst, long count, int splits)
+k_conv_reduce(const float* __restrict__ partial, float* __restrict__ dst, long count, int splits, int more)
 {
     const long t = (long)blockIdx.x * 256 + threadIdx.x;
     if (t >= count) return;
     float acc = partial[t];
+    if (more) acc = dst[t] + acc;       // uniform
     for (int s = 1; s < splits; ++s) acc += partial[(long)s * count + t];
     dst[t] = acc;
+}
+
+void reduce(const float* partial, float* dst, long count, int splits, bool more, hipStream_t s)
+{
+    ZNN_LAUNCH("sum over input-map shares", s, k_conv_reduce, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, partial, dst, count, splits,
+               more ? 1 : 0);
 }
 
 long result_count(const Geom& g, bool backward) { return backward ? (long)g.f * g.nvol() : (long)g.fo * g.ovol(); }
@@ -76,9 +83,7 @@ int conv_pass(const Geom& g, bool backward, const float* src, const float* w, co
 
 int conv_sum(const Geom& g, bool backward, const float* partial, float* dst, hipStream_t s)
 {
-    const long count = result_count(g, backward);
-    ZNN_LAUNCH("sum over input-map shares", s, k_conv_reduce, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, partial, dst, count,
-               conv_splits(g, backward));
+    reduce(partial, dst, result_count(g, backward), conv_splits(g, backward), false, s);
     return check_launch("sum over input-map shares");
 }
 
@@ -125,8 +130,9 @@ int direct_fwd(const Geom& g, const float* in, const float* w, float* out, void*
     return direct_conv(g, false, in, w, out, ws, s);
 }
 
-// The forward pass one group of output maps after another (the maps that a workgroup takes): weights and sums of one at a time, the
-// same launches otherwise.  For callers whose scratch does not hold those of all.
+// The forward pass in the built-in scratch array: one group of output maps after another, and where the sums of all shares do not
+// fit, a few shares after another.  Chunks, shares and the order of every sum are those of the ordinary call, so results are too, but
+// where the sums of one share do not fit.
 static Geom group_of(const Geom& g, const SplitChoice& c, int first)
 {
     Geom q = g;
@@ -134,26 +140,44 @@ static Geom group_of(const Geom& g, const SplitChoice& c, int first)
     return q;
 }
 
-static size_t group_bytes(const Geom& g, const SplitChoice& c)
-{
-    const size_t sums = c.splits > 1 ? align256(sizeof(float) * c.splits * result_count(group_of(g, c, 0), false)) : 0;
-    return split_packed_bytes(c) + sums;
-}
+static size_t share_bytes(const Geom& g, const SplitChoice& c) { return sizeof(float) * result_count(group_of(g, c, 0), false); }
 
-size_t direct_fwd_least(const Geom& g)
+// c.jgroups = 1 and the largest groups whose weights and sums fit, or else the smallest; shares: those of a launch.  Not ok: the weights
+// of sixteen output maps do not fit, and the vector ALUs take the pass.
+static SplitChoice choose_groups(const Geom& g, int& shares)
 {
     SplitChoice c = way(g, false);
-    if (!c.ok) return 0;
+    if (!c.ok) return c;
+    const int tiles = (g.fo + 15) / 16;
+    int groups = (tiles + c.NJ - 1) / c.NJ;
     c.jgroups = 1;
-    const size_t bytes = group_bytes(g, c);
-    return bytes > ZNN_STATIC_SCRATCH_BYTES ? 0 : std::min(conv_workspace(g, false), bytes);
+    for (; ; c.NJ = (tiles + ++groups - 1) / groups) {
+        const size_t packed = split_packed_bytes(c);
+        c.ok = packed <= ZNN_STATIC_SCRATCH_BYTES;
+        shares = c.ok && c.splits > 1 ? (int)std::min<size_t>(c.splits, (ZNN_STATIC_SCRATCH_BYTES - packed) / share_bytes(g, c)) : 1;
+        if (c.NJ == 1 || (c.ok && shares == c.splits)) break;
+    }
+    if (shares > 0) return c;
+    // not even the sums of one share: one after another in the accumulators
+    shares = c.splits = 1;
+    c.cps = c.nchunk;
+    return c;
+}
+
+// never more than the array holds
+size_t direct_fwd_least(const Geom& g)
+{
+    int shares;
+    const SplitChoice c = choose_groups(g, shares);
+    if (!c.ok) return 0;
+    return std::min(conv_workspace(g, false), split_packed_bytes(c) + (c.splits > 1 ? shares * share_bytes(g, c) : 0));
 }
 
 int direct_fwd_groups(const Geom& g, const float* in, const float* w, float* out, void* ws, hipStream_t s)
 {
-    SplitChoice c = way(g, false);
-    c.jgroups = 1;
-    if (!c.ok || group_bytes(g, c) > ZNN_STATIC_SCRATCH_BYTES) return few_conv(g, false, in, w, out, Finish{}, s);
+    int shares;
+    const SplitChoice c = choose_groups(g, shares);
+    if (!c.ok) return few_conv(g, false, in, w, out, Finish{}, s);
     float* partial = (float*)((char*)ws + split_packed_bytes(c));
     for (int first = 0; first < g.fo; first += 16 * c.NJ) {
         const Geom q = group_of(g, c, first);
@@ -161,12 +185,13 @@ int direct_fwd_groups(const Geom& g, const float* in, const float* w, float* out
         const float* wq = w + (long)first * g.f * g.kvol();
         const PackItem p = split_pack_item(q, c, false, wq, ws);
         int rc = split_pack_weights(&p, 1, s);
-        if (rc == ZNN_OK) rc = split_conv(q, c, false, in, wq, ws, dst, partial, Finish{}, s);
+        for (int share = 0; share < c.splits && rc == ZNN_OK; share += shares) {
+            const int n = std::min(shares, c.splits - share);
+            // a share on its own goes where it belongs if it is the first, the others behind it
+            rc = split_conv(q, c, false, in, wq, ws, n > 1 || share == 0 ? dst : partial, partial, Finish{}, s, share, n);
+            if (rc == ZNN_OK && (n > 1 || share > 0)) reduce(partial, dst, result_count(q, false), n, share > 0, s);
+        }
         if (rc != ZNN_OK) return rc;
-        if (c.splits == 1) continue;
-        const long count = result_count(q, false);
-        ZNN_LAUNCH("sum over input-map shares", s, k_conv_reduce, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, partial, dst, count,
-                   c.splits);
     }
     return check_launch("direct forward in groups of maps");
 }

@@ -119,12 +119,8 @@ Pass pass_of(const Geom& g, bool backward)
     return P;
 }
 
-// packed weights of one group of NJ map tiles, with the step behind them that the kernel fetches ahead
-size_t packed_group(int nchunk, int steps, int NJ) { return ((size_t)nchunk * steps + 1) * NJ * 3 * 64 * 16; }
-
-// Expected clocks of the launch (and of the sum of its shares) for every box that fits, the least taken.  What one group of output maps
-// needs, weights and sums, is kept within `room` where it can be.
-SplitChoice search(const Pass& P, size_t room)
+// Expected clocks of the launch (and of the sum of its shares) for every box that fits, the least taken.
+SplitChoice search(const Pass& P)
 {
     SplitChoice best = {};
     const Axis &az = P.a[0], &ay = P.a[1], &ax = P.a[2];
@@ -132,14 +128,7 @@ SplitChoice search(const Pass& P, size_t room)
     if (taps > kMaxTaps) return best;
     const int steps = (taps + split::kTaps - 1) / split::kTaps;
     const int tiles = (P.fM + 15) / 16, nchunk = (P.fK + split::kMaps - 1) / split::kMaps;
-    int jgroups = (tiles + 4) / 5, NJ = (tiles + jgroups - 1) / jgroups;
-    if (packed_group(nchunk, steps, 1) > room) room = SIZE_MAX;     // not even a tile of maps
-    while (NJ > 1 && packed_group(nchunk, steps, NJ) > room) {
-        ++jgroups;
-        NJ = (tiles + jgroups - 1) / jgroups;
-    }
-    const size_t packed = align256(packed_group(nchunk, steps, NJ));
-    const size_t sums = sizeof(float) * std::min(P.fM, 16 * NJ) * (size_t)az.d * ay.d * ax.d;     // of a share
+    const int jgroups = (tiles + 4) / 5, NJ = (tiles + jgroups - 1) / jgroups;
     const int phases = az.phases * ay.phases * ax.phases;
     const double count = (double)P.fM * az.d * ay.d * ax.d;
     const int nvs[6] = {1, 2, 3, 4, 6, 8}, nws[2] = {4, 8};
@@ -170,7 +159,6 @@ SplitChoice search(const Pass& P, size_t room)
                     const double stage = 4.0 * hvol * (1.0 + 0.06 * (ax.sp - 1));
                     const double fixed = 5200.0 + 11.5 * cap * NJ;
                     for (int splits = 1, cps = nchunk; ; ) {
-                        if (splits > 1 && sums > (room - packed) / splits) break;
                         const long groups = blocks * jgroups * splits;
                         const long per_cu = (groups + kCUs - 1) / kCUs;
                         // a unit with one wave per SIMD has nothing to overlap its waits with, one workgroup nothing for its stages
@@ -205,11 +193,11 @@ SplitChoice search(const Pass& P, size_t room)
 // The search walks thousands of boxes, and every call of a pass asks several times: remembered per shape.
 SplitChoice choose_split(const Geom& g, bool backward)
 {
-    struct Entry { int key[13]; SplitChoice choice; };
+    struct Entry { int key[12]; SplitChoice choice; };
     static std::mutex lock;
     static std::vector<Entry> memo;
     Entry e;
-    const int key[13] = {g.f, g.fo, g.nz, g.ny, g.nx, g.kz, g.ky, g.kx, g.spz, g.spy, g.spx, backward ? 1 : 0, 0};
+    const int key[12] = {g.f, g.fo, g.nz, g.ny, g.nx, g.kz, g.ky, g.kx, g.spz, g.spy, g.spx, backward ? 1 : 0};
     memcpy(e.key, key, sizeof(key));
     {
         std::lock_guard<std::mutex> hold(lock);
@@ -219,7 +207,7 @@ SplitChoice choose_split(const Geom& g, bool backward)
     const Pass P = pass_of(g, backward);
     e.choice = SplitChoice{};
     // a lane's byte offset in a source map has 32 bits
-    if ((backward ? g.ovol() : g.nvol()) < (1L << 28)) e.choice = search(P, backward ? SIZE_MAX : ZNN_STATIC_SCRATCH_BYTES);     // the forward pass has to do with that
+    if ((backward ? g.ovol() : g.nvol()) < (1L << 28)) e.choice = search(P);
     std::lock_guard<std::mutex> hold(lock);
     if (memo.size() >= 256) memo.erase(memo.begin());
     memo.push_back(e);
@@ -268,7 +256,7 @@ int split_pack_weights(const PackItem* items, int n, hipStream_t s)
 }
 
 int split_conv(const Geom& g, const SplitChoice& c, bool backward, const float* src, const float* w, const void* wp, float* dst, float* partial,
-               const Finish& finish, hipStream_t s)
+               const Finish& finish, hipStream_t s, int share0, int shares)
 {
     const Pass p = pass_of(g, backward);
     SplitTile P = {};
@@ -287,7 +275,9 @@ int split_conv(const Geom& g, const SplitChoice& c, bool backward, const float* 
     const long total = (long)c.c[0] * c.c[1] * c.c[2] * c.phases;
     if (total >= 2147483640L) return fail(ZNN_EUNSUPPORTED, "too many tiles for one launch");
     P.total = (int)total; P.run = (int)((total + 7) / 8);
+    if (!shares) shares = c.splits;
     P.nchunk = c.nchunk; P.cps = c.cps; P.steps = c.steps;
+    P.share0 = share0;
     P.partial = partial;
     P.y = finish.y; P.bias = finish.bias; P.deriv = finish.deriv;
     P.dHX = make_fastdiv((unsigned)c.H[2]); P.dHY = make_fastdiv((unsigned)c.H[1]);
@@ -296,13 +286,13 @@ int split_conv(const Geom& g, const SplitChoice& c, bool backward, const float* 
     P.dPH = make_fastdiv((unsigned)P.phases); P.dQX = make_fastdiv((unsigned)P.qx); P.dQY = make_fastdiv((unsigned)P.qy);
     P.dCX = make_fastdiv((unsigned)P.cx); P.dCY = make_fastdiv((unsigned)P.cy);
     if (log_enabled())
-        fprintf(stderr, "[znn] conv split (%s): NJ=%d jgroups=%d NV=%d waves=%d tile=%dx%dx%d halo=%dx%dx%d blocks=%ld splits=%d lds=%zu cost=%.0f\n",
-                backward ? "bwd" : "fwd", c.NJ, c.jgroups, c.NV, c.NW, c.T[0], c.T[1], c.T[2], c.H[0], c.H[1], c.H[2], total, c.splits,
-                c.lds, c.cost);
+        fprintf(stderr, "[znn] conv split (%s): NJ=%d jgroups=%d NV=%d waves=%d tile=%dx%dx%d halo=%dx%dx%d blocks=%ld splits=%d-%d/%d lds=%zu cost=%.0f\n",
+                backward ? "bwd" : "fwd", c.NJ, c.jgroups, c.NV, c.NW, c.T[0], c.T[1], c.T[2], c.H[0], c.H[1], c.H[2], total, share0,
+                share0 + shares, c.splits, c.lds, c.cost);
     const SplitFn fn = pick(c.NJ, c.NV, c.NW);
     if (!fn) return fail(ZNN_EUNSUPPORTED, "no kernel instance for tile %dx%d", c.NJ, c.NV);
     ZNN_LAUNCH(backward ? "direct backward (MFMA)" : "direct forward (MFMA)", s, fn,
-               dim3((unsigned)P.run * 8, (unsigned)c.jgroups, (unsigned)c.splits), dim3(64 * c.NW), c.lds, P);
+               dim3((unsigned)P.run * 8, (unsigned)c.jgroups, (unsigned)shares), dim3(64 * c.NW), c.lds, P);
     return check_launch(backward ? "direct backward (MFMA)" : "direct forward (MFMA)");
 }
 

@@ -59,7 +59,8 @@ struct SplitTile {
     int cy, cx;             // boxes per axis of a sublattice
     int qy, qx, phases;     // sublattices along y and x, and in all
     int total, run;         // workgroups (boxes x sublattices), and those of one XCD
-    int nchunk, cps;        // chunks of eight input maps, and those of a workgroup (gridDim.z shares them out)
+    int nchunk, cps;        // chunks of eight input maps, and those of a share (gridDim.z shares in a launch)
+    int share0;             // first share of the launch
     int steps;              // ceil(taps / 4)
     float* partial;         // [shares][fM][dz][dy][dx] where gridDim.z > 1
     float* y;               // where not NULL: y = max(result + bias[map], 0) beside the result
@@ -92,7 +93,7 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
     const long splane = (long)P.sy * P.sx, svol = P.sz * splane;
     const long dplane = (long)P.dy * P.dx, dvol = P.dz * dplane;
     const int jg = blockIdx.y;
-    const int ic0 = blockIdx.z * P.cps, ic1 = min(P.nchunk, ic0 + P.cps);
+    const int ic0 = (P.share0 + blockIdx.z) * P.cps, ic1 = min(P.nchunk, ic0 + P.cps);
 
     auto place = [&](int t, int& tz, int& ty, int& tx) {
         const int q = (int)fdiv((unsigned)t, P.dTX);

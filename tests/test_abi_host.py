@@ -247,3 +247,15 @@ def test_static_forward_takes_layers_by_what_they_need_on_whole_volumes():
         p.set_spectra_layout(p.spectra_layout)
         assert (p.workspace_bytes(znn.ZNN_PASS_FWD) <= znn.STATIC_SCRATCH_BYTES) == fits
         p.close()
+
+
+@pytest.mark.parametrize("f,n", [(200, 20), (200, 18), (160, 24)])
+def test_forward_pass_with_a_workspace_is_not_held_to_the_built_in_array(f, n):
+    """Small images of wide layers with many taps fill the chip by shares of the input maps, whose weights and sums are more than the
+    built-in array holds: 200 -> 200 maps, 20^3, 7^3 in one share is expected to take 1564 us, in seven 388."""
+    p = znn.Plan(f, f, (n,) * 3, (7,) * 3, "direct")
+    maps, chunks, steps = -(-f // 80) * 80, -(-f // 8), -(-343 // 4)
+    weights = maps * chunks * steps * 4 * 8 * 6
+    shares = (p.workspace_bytes(znn.ZNN_PASS_FWD) - weights) // (f * (n - 6) ** 3 * 4)
+    assert shares >= 5
+    p.close()

@@ -93,8 +93,10 @@ def test_forward_without_allocation_refuses_layers_beyond_the_array():
 
 
 # layers of the direct method whose weights, or sums of the shares of their input maps, take more than the array: three groups of maps
-# (the last one smaller), shares of the input maps as well, and a layer whose weights of sixteen output maps do not fit
-WIDE = [(200, 213, (6, 9, 20), (5, 5, 5), True), (160, 120, (8, 9, 12), (7, 7, 7), True), (512, 3, (9, 9, 10), (9, 9, 9), False)]
+# (the last one smaller), shares of the input maps as well, and a layer whose weights of sixteen output maps do not fit; shares of the
+# input maps a few at a time, one at a time, and none, as the sums of one do not fit
+WIDE = [(200, 213, (6, 9, 20), (5, 5, 5), True), (160, 120, (8, 9, 12), (7, 7, 7), True), (512, 3, (9, 9, 10), (9, 9, 9), False),
+        (400, 16, (36, 36, 36), (9, 9, 9), True), (440, 16, (36, 36, 36), (9, 9, 9), True), (470, 16, (36, 36, 36), (9, 9, 9), False)]
 
 
 @pytest.mark.parametrize("f,fo,n,k,same", WIDE)
