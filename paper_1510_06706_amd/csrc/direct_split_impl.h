@@ -257,9 +257,6 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
 #pragma unroll
         for (int nv = 0; nv < NV; ++nv) acc[jt][nv] *= kUnscale;
 
-    // An infinity or a NaN among the operands (or the voxel read in place of a zero) makes the parts' products NaN where the
-    // product itself may not be: sums that are not finite are taken again in fp32, straight from memory, as
-    // v_mfma_f32_16x16x4_f32 gives them.
     bool bad = false;
 #pragma unroll
     for (int jt = 0; jt < NJ; ++jt)
@@ -267,53 +264,6 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
         for (int nv = 0; nv < NV; ++nv)
 #pragma unroll
             for (int r = 0; r < 4; ++r) bad = bad || !(fabsf(acc[jt][nv][r]) <= kLargest);
-    if (__builtin_amdgcn_ballot_w64(bad)) {
-        int base[NV];
-#pragma unroll
-        for (int nv = 0; nv < NV; ++nv) {
-            base[nv] = min((wave * NV + nv) * 16 + col, Ttot - 1);
-#pragma unroll
-            for (int jt = 0; jt < NJ; ++jt) acc[jt][nv] = floatx4{0.f, 0.f, 0.f, 0.f};
-        }
-        for (int ic = ic0; ic < ic1; ++ic)
-            for (int q = 0; q < taps; ++q) {
-                const int c = q % P.kx, r = q / P.kx, b = r % P.ky, a = r / P.ky;
-                for (int h = 0; h < kMaps / 4; ++h) {
-                    const int m = h * 4 + grp, map = ic * kMaps + m;        // the lane's input map
-                    float w[NJ], v[NV];
-#pragma unroll
-                    for (int jt = 0; jt < NJ; ++jt) {
-                        const int to = (jg * NJ + jt) * 16 + col;
-                        w[jt] = map < P.fK && to < P.fM ? P.w[to * P.wm + map * P.wk + (P.reflected ? taps - 1 - q : q)] : 0.f;
-                    }
-#pragma unroll
-                    for (int nv = 0; nv < NV; ++nv) {
-                        int tz, ty, tx;
-                        place(base[nv], tz, ty, tx);
-                        const int gz = fz + (z0 + tz + P.kz - 1 - a - P.pz) * P.spz, gy = fy + (y0 + ty + P.ky - 1 - b - P.py) * P.spy,
-                                  gx = fx + (x0 + tx + P.kx - 1 - c - P.px) * P.spx;
-                        const bool in = map < P.fK && gz >= 0 && gz < P.sz && gy >= 0 && gy < P.sy && gx >= 0 && gx < P.sx;
-                        v[nv] = in ? P.src[map * svol + ((long)gz * P.sy + gy) * P.sx + gx] : 0.f;
-                    }
-#pragma unroll
-                    for (int jt = 0; jt < NJ; ++jt)
-#pragma unroll
-                        for (int nv = 0; nv < NV; ++nv)
-                            acc[jt][nv] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[jt], v[nv], acc[jt][nv], 0, 0, 0);
-                }
-                if (q > 0) continue;
-                // a NaN stays one: waves whose results all are need not go to the end (a round of the six-layer 3D net after it has
-                // diverged: 1070 -> 670 us)
-                bool open = false;
-#pragma unroll
-                for (int jt = 0; jt < NJ; ++jt)
-#pragma unroll
-                    for (int nv = 0; nv < NV; ++nv)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) open = open || (acc[jt][nv][r] == acc[jt][nv][r] && (jg * NJ + jt) * 16 + grp * 4 + r < P.fM);
-                if (!__builtin_amdgcn_ballot_w64(open)) { ic = ic1; break; }
-            }
-    }
 
     float* const out = gridDim.z > 1 ? P.partial + (long)blockIdx.z * P.fM * dvol : P.dst;
     // lane holds maps 4 (lane / 16) + r of voxel lane % 16
@@ -343,6 +293,107 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
         });
     else
         store_all([&](long at, int, float v) { out[at] = v; });
+
+    // An infinity or a NaN among the operands (or the voxel read in place of a zero) makes the parts' products NaN where the
+    // product itself may not be: results that are not finite are read back and taken again in fp32, straight from memory, on
+    // v_mfma_f32_16x16x4_f32, a voxel tile at a time.  A NaN stays one, so a tile is done when all of these are; the finite ones stand.
+    // 40 -> 40 maps, 64^3, 5^3 kernels, forward 560 us on finite values: weights of half the maps NaN 480 us (6.0 ms where a wave took all
+    // of its tiles again), all voxels NaN 510, one voxel infinite 800; 80 -> 80, 256^2, 11^2, 430 us: 400, 400 and 2900 us.
+    if (!__builtin_amdgcn_ballot_w64(bad)) return;
+    // the launch's parameters from memory again: they need not stay in scalar registers for this
+    auto args = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const SplitTile& C = *(const SplitTile*)args;
+    const int maps = min(ic1 * kMaps, C.fK);
+#pragma unroll 1
+    for (int nv = 0; nv < NV; ++nv) {
+        const int t = (wave * NV + nv) * 16 + col;
+        const long vox = voxel_of(t);
+        int tz, ty, tx;
+        place(t < Ttot ? t : 0, tz, ty, tx);
+        const unsigned* const at = from + (tz * C.HY + ty) * C.HX + tx;
+        unsigned wrong = 0;                                     // the lane's results that are
+        floatx4 again[NJ];
+        global_floats row[NJ];                                  // weights of the lane's result map (or the last one, for no result)
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt) {
+            again[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+            row[jt] = (global_floats)C.w + min((jg * NJ + jt) * 16 + (int)col, C.fM - 1) * C.wm;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int j = (jg * NJ + jt) * 16 + grp * 4 + r;
+                if (vox >= 0 && j < C.fM && !(fabsf(out[(long)j * dvol + vox]) <= kLargest)) wrong |= 1u << (jt * 4 + r);
+            }
+        }
+        // whether some of them are not NaN again yet
+        auto open = [&] {
+            unsigned left = wrong;
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (again[jt][r] != again[jt][r]) left &= ~(1u << (jt * 4 + r));
+            return __builtin_amdgcn_ballot_w64(left != 0) != 0;
+        };
+        // Products of `N` input maps at taps t0 to t0 + 15, N of its four by a lane: a result map's weights of these are 64 contiguous bytes.
+        auto add_products = [&](int map, int t0, auto many) {
+            constexpr int N = decltype(many)::value;
+            float v[N][N], w[N][N][NJ];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int q = t0 + 4 * grp + i, tap = min(q, taps - 1);
+                const unsigned o = q < taps ? at[tofs[tap] / kVoxelBytes] : ~0u;
+#pragma unroll
+                for (int h = 0; h < N; ++h) {
+                    const long of = min(map + h, maps - 1);         // uniform
+                    const bool has = q < taps && map + h < maps;
+                    const float x = ((global_floats)C.src + of * svol)[o != ~0u ? o / 4 : 0];
+                    v[i][h] = has && o != ~0u ? x : 0.f;
+#pragma unroll
+                    for (int jt = 0; jt < NJ; ++jt) {
+                        const float y = row[jt][of * C.wk + (C.reflected ? taps - 1 - tap : tap)];
+                        w[i][h][jt] = has ? y : 0.f;
+                    }
+                }
+            }
+#pragma unroll
+            for (int h = 0; h < N; ++h)
+#pragma unroll
+                for (int i = 0; i < N; ++i)
+#pragma unroll
+                    for (int jt = 0; jt < NJ; ++jt) again[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][h][jt], v[i][h], again[jt], 0, 0, 0);
+        };
+        // Where a few products make NaN of them already, no more are needed: whole maps of a net that has diverged.  The walk is bound by
+        // the way to memory, so a step of it requests much.
+        bool more = open();
+        if (more) {
+            add_products(ic0 * kMaps, 0, std::integral_constant<int, 1>{});
+            more = open();
+        }
+        if (more) {
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt) again[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int map = ic0 * kMaps; map < maps && more; map += 4)
+                for (int t0 = 0; t0 < taps && more; t0 += 16) {
+                    add_products(map, t0, std::integral_constant<int, 4>{});
+                    more = open();
+                }
+        }
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (wrong >> (jt * 4 + r) & 1) {
+                    const int j = (jg * NJ + jt) * 16 + grp * 4 + r;
+                    const long to = (long)j * dvol + vox;
+                    float s = again[jt][r];
+                    out[to] = s;
+                    if (C.y) {                                          // uniform
+                        s += C.bias[j];
+                        C.y[to] = s > 0.f ? s : 0.f;
+                    }
+                }
+    }
 }
 
 }  // namespace split

@@ -30,6 +30,7 @@ typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) const char* lds_bytes;
 typedef __attribute__((address_space(3))) const uintx4* lds_quads;
 typedef __attribute__((address_space(3))) const int* lds_ints;
+typedef __attribute__((address_space(1))) const float* global_floats;
 
 constexpr int kPartBytes = 16;      // one part of eight numbers
 constexpr int kVectorBytes = 48;    // three parts of eight numbers

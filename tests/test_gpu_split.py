@@ -149,6 +149,44 @@ def test_operands_that_are_not_finite_act_as_in_fp32(value):
     p.close()
 
 
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("s", [(1, 1, 1), (2, 3, 2)])
+def test_finite_results_stand_beside_those_that_are_not(value, s):
+    """Maps whose weights are not finite, as in a net that has diverged, are none of the others' business; nor are single voxels."""
+    f, fo, n, k = 40, 40, (21, 24, 30), (3, 3, 3)
+    x, w, g = tensors(f, fo, n, k, s, 9109)
+    p = znn.Plan(f, fo, n, k, "direct", s)
+    assert p.workspace_bytes(0) > 0 and p.workspace_bytes(1) > 0        # packed weights
+    out, gin = p.fwd(dev(x), dev(w)).cpu().numpy(), p.bwd(dev(g), dev(w)).cpu().numpy()
+
+    def stands(got, base, ref, there, inner=slice(None)):
+        got = got.cpu().numpy()
+        assert np.array_equal(got[~there], base[~there])
+        got, ref = got[inner], ref[inner]
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+        assert np.array_equal(np.isneginf(got), np.isneginf(ref))
+
+    for maps in ((3, 17, 39), range(8, 40)):
+        for wx, at in ((w.copy(), (list(maps),)), (w.copy(), (slice(None), list(maps)))):
+            wx[at] = value
+            if len(at) == 1:
+                there = np.zeros(out.shape, bool)
+                there[list(maps)] = True
+                stands(p.fwd(dev(x), dev(wx)), out, oracle.conv3d_fwd(x, wx, s), there)
+            else:
+                there = np.zeros(gin.shape, bool)
+                there[list(maps)] = True
+                # at the border the kernels multiply weights by zeros that the oracle leaves out
+                stands(p.bwd(dev(g), dev(wx)), gin, oracle.conv3d_bwd(g, wx, n, s), there,
+                       (slice(None),) + tuple(slice(2 * b, a - 2 * b) for a, b in zip(n, s)))
+    x[9, 7, 8, 9] = g[21, 5, 5, 5] = value
+    ref = oracle.conv3d_fwd(x, w, s)
+    stands(p.fwd(dev(x), dev(w)), out, ref, ~np.isfinite(ref))
+    ref = oracle.conv3d_bwd(g, w, n, s)
+    stands(p.bwd(dev(g), dev(w)), gin, ref, ~np.isfinite(ref))
+    p.close()
+
+
 GRADIENTS = [
     # f, fo, n, k, s: pieces of the axes with and without a remainder, tap groups, column groups, shares
     (1, 1, (1, 1, 5), (1, 1, 1), (1, 1, 1)),            # fewer voxels than pieces
