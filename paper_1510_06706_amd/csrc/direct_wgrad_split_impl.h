@@ -244,8 +244,10 @@ __global__ void __launch_bounds__(64 * kGradWaves) k_wgrad_split(GradTile P)
         use_tile(lB, oddB, tile + 2 < last, bufA, oddA);
     }
 
-    // Sums that are not finite: the parts of an infinity or a NaN do not multiply as it does.  The wave's share again in fp32,
-    // straight from memory.
+    // Sums that are not finite: the parts of an infinity or a NaN do not multiply as it does.  Where the first products of the wave's
+    // share, in fp32, make NaN of all of them already -- whole maps of a net that has diverged -- NaN they are, and the finite ones
+    // stand; else its share again in fp32, straight from memory.  40 -> 40 maps, 64^3, 5^3, 585 us on finite values: all NaN 600 us,
+    // one voxel or all of them infinite 2400 us.
     bool bad = false;
 #pragma unroll
     for (int jt = 0; jt < NJ; ++jt)
@@ -259,41 +261,100 @@ __global__ void __launch_bounds__(64 * kGradWaves) k_wgrad_split(GradTile P)
         asm volatile("" : "+s"(args));
         const GradTile& C = *(const GradTile*)args;
         const int tg = C.GA * C.GB * C.k[2], ncols = C.f * tg, X4 = C.R[2] / 4;
-#pragma unroll
-        for (int jt = 0; jt < NJ; ++jt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[jt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
         const long ovol = (long)C.o[0] * C.o[1] * C.o[2], nvol = (long)C.n[0] * C.n[1] * C.n[2];
-        for (int tile = first; tile < last; ++tile)
-            for (int ks = kw; ks < C.steps; ks += C.KW)
-                for (int e = 0; e < 8; ++e) {
-                    const int tx = tile % C.tiles_x, tr = tile / C.tiles_x, ty = tr % C.tiles_y, tz = tr / C.tiles_y;
-                    const int r = ks / X4, qx = tx % C.T[2] * C.R[2] + (ks - r * X4) * 4 + grp;
-                    const int qy = C.q0[1] + ty % C.T[1] * C.R[1] + r % C.R[1], qz = C.q0[0] + tz % C.T[0] * C.R[0] + r / C.R[1];
-                    const int ex = e % C.E[2], ey = e / C.E[2] % C.E[1], ez = e / C.E[2] / C.E[1];
-                    const int z = C.r0[0] + tz / C.T[0] + (ez * C.Q[0] + qz) * C.sp[0], y = C.r0[1] + ty / C.T[1] + (ey * C.Q[1] + qy) * C.sp[1],
-                              x = tx / C.T[2] + (ex * C.Q[2] + qx) * C.sp[2];
-                    const bool ok = qz < C.Q[0] && qy < C.Q[1] && qx < C.Q[2] && z < C.o[0] && y < C.o[1] && x < C.o[2];
-                    float av[NJ], bv[NT];
+        // voxel of the lane in step ks of a tile, piece e; false: none
+        auto voxel = [&](int tile, int ks, int e, int& z, int& y, int& x) {
+            const int tx = tile % C.tiles_x, tr = tile / C.tiles_x, ty = tr % C.tiles_y, tz = tr / C.tiles_y;
+            const int r = ks / X4, qx = tx % C.T[2] * C.R[2] + (ks - r * X4) * 4 + grp;
+            const int qy = C.q0[1] + ty % C.T[1] * C.R[1] + r % C.R[1], qz = C.q0[0] + tz % C.T[0] * C.R[0] + r / C.R[1];
+            const int ex = e % C.E[2], ey = e / C.E[2] % C.E[1], ez = e / C.E[2] / C.E[1];
+            z = C.r0[0] + tz / C.T[0] + (ez * C.Q[0] + qz) * C.sp[0];
+            y = C.r0[1] + ty / C.T[1] + (ey * C.Q[1] + qy) * C.sp[1];
+            x = tx / C.T[2] + (ex * C.Q[2] + qx) * C.sp[2];
+            return qz < C.Q[0] && qy < C.Q[1] && qx < C.Q[2] && z < C.o[0] && y < C.o[1] && x < C.o[2];
+        };
+        auto of_gout = [&](int jt, bool ok, int z, int y, int x) {
+            const int j = (jg * NJ + jt) * 16 + col;
+            return ok && j < C.fo ? ((global_floats)C.gout)[j * ovol + ((long)z * C.o[1] + y) * C.o[2] + x] : 0.f;
+        };
+        // where the lane's column of a tile begins in `in`, -1: none
+        auto column = [&](int nt) {
+            const int n = n0 + (set * NT + nt) * 16 + col;
+            const int i = n / tg, q = n - i * tg, c = q % C.k[2], b = b0 + q / C.k[2] % C.GB, a = a0 + q / C.k[2] / C.GB;
+            const int cz = C.sp[0] * (C.k[0] - 1 - a), cy = C.sp[1] * (C.k[1] - 1 - b), cx = C.sp[2] * (C.k[2] - 1 - c);
+            return n < ncols && a < C.k[0] && b < C.k[1] ? i * nvol + ((long)cz * C.n[1] + cy) * C.n[2] + cx : -1l;
+        };
+        auto of_in = [&](long begin, bool ok, int z, int y, int x) {
+            return ok && begin >= 0 ? ((global_floats)C.in)[begin + ((long)z * C.n[1] + y) * C.n[2] + x] : 0.f;
+        };
+        auto is_wrong = [](float v) {
+            asm volatile("" : "+v"(v));     // compared anew: outcomes that are kept would take all scalar registers
+            return !(fabsf(v) <= kLargest);
+        };
+        bool open = false;          // whether some sums are not NaN after these products (uniform)
+#pragma unroll 1
+        for (int p = 0; p < NT && !open; ++p) {
+            unsigned wrong = 0;     // the lane's sums in column tile p that are, where they are wanted
 #pragma unroll
-                    for (int jt = 0; jt < NJ; ++jt) {
-                        const int j = (jg * NJ + jt) * 16 + col;
-                        av[jt] = ok && j < C.fo ? C.gout[j * ovol + ((long)z * C.o[1] + y) * C.o[2] + x] : 0.f;
-                    }
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
-                        const int n = n0 + (set * NT + nt) * 16 + col;
-                        const int i = n / tg, q = n - i * tg, c = q % C.k[2], b = b0 + q / C.k[2] % C.GB, a = a0 + q / C.k[2] / C.GB;
-                        const long at = ((long)(z + C.sp[0] * (C.k[0] - 1 - a)) * C.n[1] + y + C.sp[1] * (C.k[1] - 1 - b)) * C.n[2] + x +
-                                        C.sp[2] * (C.k[2] - 1 - c);
-                        bv[nt] = ok && n < ncols && a < C.k[0] && b < C.k[1] ? C.in[i * nvol + at] : 0.f;
-                    }
+            for (int nt = 0; nt < NT; ++nt)
+                if (p == nt) {      // uniform
 #pragma unroll
                     for (int jt = 0; jt < NJ; ++jt)
 #pragma unroll
-                        for (int nt = 0; nt < NT; ++nt)
-                            acc[jt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[jt], bv[nt], acc[jt][nt], 0, 0, 0);
+                        for (int r = 0; r < 4; ++r)
+                            if (is_wrong(acc[jt][nt][r])) wrong |= 1u << (jt * 4 + r);
                 }
+            const long begin = column(p);
+            if (begin < 0) wrong = 0;
+            floatx4 t[NJ];
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt) t[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int e = 0; e < 8; ++e) {
+                int z, y, x;
+                const bool ok = voxel(first, kw, e, z, y, x) && kw < C.steps;
+                const float bv = of_in(begin, ok, z, y, x);
+#pragma unroll
+                for (int jt = 0; jt < NJ; ++jt) t[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(of_gout(jt, ok, z, y, x), bv, t[jt], 0, 0, 0);
+            }
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (t[jt][r] != t[jt][r]) wrong &= ~(1u << (jt * 4 + r));
+            open = __builtin_amdgcn_ballot_w64(wrong != 0) != 0;
+        }
+        if (!open) {
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[jt][nt][r] = is_wrong(acc[jt][nt][r]) ? __builtin_nanf("") : acc[jt][nt][r];
+        } else {
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[jt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+            long begin[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) begin[nt] = column(nt);
+            for (int tile = first; tile < last; ++tile)
+                for (int ks = kw; ks < C.steps; ks += C.KW)
+                    for (int e = 0; e < 8; ++e) {
+                        int z, y, x;
+                        const bool ok = voxel(tile, ks, e, z, y, x);
+                        float av[NJ], bv[NT];
+#pragma unroll
+                        for (int jt = 0; jt < NJ; ++jt) av[jt] = of_gout(jt, ok, z, y, x);
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) bv[nt] = of_in(begin[nt], ok, z, y, x);
+#pragma unroll
+                        for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+                            for (int nt = 0; nt < NT; ++nt)
+                                acc[jt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[jt], bv[nt], acc[jt][nt], 0, 0, 0);
+                    }
+        }
     }
 
     // add the sums of the KW waves of each set, pairs first

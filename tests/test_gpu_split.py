@@ -43,6 +43,20 @@ def tensors(f, fo, n, k, s, seed):
     return x, w, g
 
 
+def kernels_of(call, *names):
+    """The call's result; `names` are among the kernels that it launches."""
+    import torch
+    znn.trace_enable(True)
+    try:
+        result = call()
+        torch.cuda.synchronize()
+        launched = {name for name, _ in znn.trace_collect(64)}
+    finally:
+        znn.trace_enable(False)
+    assert set(names) <= launched, (names, launched)
+    return result
+
+
 def bound(ref_abs, maps, taps):
     adds = -(-maps // 8) * -(-taps // 4) + -(-maps // 8)
     return (adds + 16) * 2.0 ** -24 * ref_abs
@@ -232,6 +246,40 @@ def test_kernel_gradient_of_images_that_are_not_finite_acts_as_in_fp32(value, s)
     ok = np.isfinite(ref)
     ref_abs = oracle.conv3d_wgrad(np.abs(x), np.abs(g), s)
     assert np.all(np.abs(got[ok] - ref[ok]) <= (2 * g[0].size + 600) * 2.0 ** -24 * ref_abs[ok])
+    p.close()
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("f,fo,n,k,s", [
+    (40, 40, (26, 24, 30), (3, 3, 3), (1, 1, 1)),
+    (40, 37, (28, 30, 27), (3, 3, 3), (2, 3, 2)),
+    (80, 80, (1, 60, 71), (1, 11, 11), (1, 1, 1)),      # five row tiles
+    (24, 81, (15, 20, 29), (2, 3, 4), (1, 1, 1)),       # two groups of them, columns that end within a tile
+])
+def test_finite_kernel_gradients_stand_beside_those_that_are_not(f, fo, n, k, s, value):
+    x, w, g = tensors(f, fo, n, k, s, 9110)
+    p = znn.Plan(f, fo, n, k, "direct", s)
+    base = kernels_of(lambda: p.wgrad(dev(x), dev(g)), "direct kernel gradient (MFMA)").cpu().numpy()
+
+    def stands(x, g, maps, limit):
+        got, ref = p.wgrad(dev(x), dev(g)).cpu().numpy(), oracle.conv3d_wgrad(x, g, s)
+        there = np.zeros(base.shape, bool)
+        there[maps] = True
+        assert np.all(np.abs(got[~there] - base[~there]) <= limit[~there])
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+        assert np.array_equal(np.isneginf(got), np.isneginf(ref))
+
+    # whole maps of either image: no products of theirs are taken again where they are NaN.  Else those of their waves, in fp32.
+    limit = (2 * g[0].size + 600) * 2.0 ** -24 * oracle.conv3d_wgrad(np.abs(x), np.abs(g), s) * 2
+    whole = 0 * limit if np.isnan(value) else limit
+    xs, gs = x.copy(), g.copy()
+    xs[5] = gs[17] = value
+    stands(xs, g, np.s_[:, 5], whole)
+    stands(x, gs, np.s_[17], whole)
+    xs, gs = x.copy(), g.copy()
+    xs[3, :, -3, 9] = gs[2, 0, 0, -1] = value           # some voxels
+    stands(xs, g, np.s_[:, 3], limit)
+    stands(x, gs, np.s_[2], limit)
     p.close()
 
 
