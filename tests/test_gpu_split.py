@@ -2,7 +2,7 @@
 taps, shares of the input maps, and operands that are not finite.
 
 The bound is derived, element by element, from S = sum of |products| (the oracle on absolute values): what the split leaves
-out of a product is below 2^-23 of it, a step of 32 products is summed by six instructions, and then one fp32 addition per
+out of a product is below 2^-24 of it, a step of 32 products is summed by six instructions, and then one fp32 addition per
 step and share rounds a partial sum that is at most S.
 """
 import numpy as np
@@ -30,6 +30,18 @@ SHAPES = [
     (48, 64, (20, 20, 20), (3, 3, 3), (1, 1, 1)),
     (72, 72, (10, 11, 12), (5, 4, 3), (1, 1, 1)),       # five map tiles
     (5, 5, (30, 9, 10), (17, 9, 7), (1, 1, 1)),         # 1071 taps
+]
+
+
+# Layers as small as some of those above take the kernels on the vector ALUs; these are the same edges on layers that do not, which
+# the tests assert.
+WIDE_SHAPES = [
+    (64, 64, (32, 48, 48), (1, 1, 1), (1, 1, 1)),       # one tap
+    (24, 40, (33, 34, 66), (1, 2, 2), (1, 1, 1)),       # one full step
+    (17, 33, (44, 45, 46), (1, 1, 5), (1, 1, 1)),       # a step and a tap
+    (130, 7, (26, 26, 29), (2, 2, 2), (1, 1, 1)),       # many chunks
+    (40, 40, (25, 24, 23), (3, 3, 3), (2, 3, 4)),       # sublattices of different extents
+    (64, 64, (25, 24, 31), (3, 3, 3), (8, 8, 9)),       # result extents around the tap spacing
 ]
 
 
@@ -62,17 +74,27 @@ def bound(ref_abs, maps, taps):
     return (adds + 16) * 2.0 ** -24 * ref_abs
 
 
-@pytest.mark.parametrize("f,fo,n,k,s", SHAPES)
-def test_passes_stay_within_the_bound_of_the_split(f, fo, n, k, s):
+def passes_within_bound(f, fo, n, k, s, forward=(), backward=()):
     x, w, g = tensors(f, fo, n, k, s, 9100)
     taps = k[0] * k[1] * k[2]
     p = znn.Plan(f, fo, n, k, "direct", s)
-    out, gin = p.fwd(dev(x), dev(w)).cpu().numpy(), p.bwd(dev(g), dev(w)).cpu().numpy()
+    out = kernels_of(lambda: p.fwd(dev(x), dev(w)), *forward).cpu().numpy()
+    gin = kernels_of(lambda: p.bwd(dev(g), dev(w)), *backward).cpu().numpy()
     err = np.abs(out.astype(np.float64) - oracle.conv3d_fwd(x, w, s))
     assert np.all(err <= bound(oracle.conv3d_fwd(np.abs(x), np.abs(w), s), f, taps))
     err = np.abs(gin.astype(np.float64) - oracle.conv3d_bwd(g, w, n, s))
     assert np.all(err <= bound(oracle.conv3d_bwd(np.abs(g), np.abs(w), n, s), fo, taps))
     p.close()
+
+
+@pytest.mark.parametrize("f,fo,n,k,s", SHAPES)
+def test_passes_stay_within_the_bound_of_the_split(f, fo, n, k, s):
+    passes_within_bound(f, fo, n, k, s)
+
+
+@pytest.mark.parametrize("f,fo,n,k,s", WIDE_SHAPES)
+def test_passes_of_wide_layers_run_on_the_split_and_stay_within_its_bound(f, fo, n, k, s):
+    passes_within_bound(f, fo, n, k, s, ["direct forward (MFMA)"], ["direct backward (MFMA)"])
 
 
 @pytest.mark.parametrize("n,s", [((26, 26, 26), (1, 1, 1)), ((34, 34, 34), (4, 4, 4))])
@@ -220,11 +242,26 @@ GRADIENTS = [
 ]
 
 
-@pytest.mark.parametrize("f,fo,n,k,s", GRADIENTS)
-def test_kernel_gradient_stays_within_the_bound_of_the_split(f, fo, n, k, s):
+# As WIDE_SHAPES
+WIDE_GRADIENTS = [
+    (2, 40, (60, 61, 62), (3, 3, 3), (1, 1, 1)),        # all taps in one group
+    (128, 128, (8, 32, 128), (1, 1, 1), (1, 1, 1)),     # nothing left over anywhere
+    (17, 33, (31, 33, 35), (2, 3, 4), (1, 1, 1)),
+    (24, 81, (15, 20, 29), (2, 3, 4), (1, 1, 1)),       # two groups of map tiles
+    (260, 16, (26, 26, 29), (2, 2, 2), (1, 1, 1)),      # column groups
+    (6, 33, (1, 160, 147), (1, 11, 11), (1, 1, 1)),     # 2D
+    (40, 40, (25, 24, 23), (3, 3, 3), (2, 3, 4)),       # residues of different extents
+    (64, 64, (20, 44, 45), (3, 3, 3), (9, 4, 4)),       # a result extent below the tap spacing
+    (40, 48, (6, 61, 60), (1, 3, 3), (3, 2, 2)),        # spacing on an axis of one tap
+    (5, 5, (40, 29, 30), (17, 9, 7), (1, 1, 1)),        # 1071 taps
+    (6, 40, (40, 41, 42), (3, 3, 3), (1, 1, 1)),        # many shares
+]
+
+
+def gradient_within_bound(f, fo, n, k, s, *names):
     x, w, g = tensors(f, fo, n, k, s, 9103)
     p = znn.Plan(f, fo, n, k, "direct", s)
-    gw = p.wgrad(dev(x), dev(g)).cpu().numpy()
+    gw = kernels_of(lambda: p.wgrad(dev(x), dev(g)), *names).cpu().numpy()
     voxels = g[0].size
     # a step per 32 voxels, remainders of pieces and tiles at most double them; waves and shares
     limit = (2 * (voxels // 32) + 600) * 2.0 ** -24 * oracle.conv3d_wgrad(np.abs(x), np.abs(g), s)
@@ -232,21 +269,41 @@ def test_kernel_gradient_stays_within_the_bound_of_the_split(f, fo, n, k, s):
     p.close()
 
 
-@pytest.mark.parametrize("value", [np.inf, np.nan, 3.4e38])
-@pytest.mark.parametrize("s", [(1, 1, 1), (2, 1, 2)])
-def test_kernel_gradient_of_images_that_are_not_finite_acts_as_in_fp32(value, s):
-    f, fo, n, k = 9, 20, (11, 12, 13), (3, 3, 3)
+@pytest.mark.parametrize("f,fo,n,k,s", GRADIENTS)
+def test_kernel_gradient_stays_within_the_bound_of_the_split(f, fo, n, k, s):
+    gradient_within_bound(f, fo, n, k, s)
+
+
+@pytest.mark.parametrize("f,fo,n,k,s", WIDE_GRADIENTS)
+def test_kernel_gradient_of_wide_layers_runs_on_the_split_and_stays_within_its_bound(f, fo, n, k, s):
+    gradient_within_bound(f, fo, n, k, s, "split of images", "direct kernel gradient (MFMA)")
+
+
+def gradient_as_in_fp32(f, fo, n, k, s, value, *names):
     x, w, g = tensors(f, fo, n, k, s, 9104)
     x[4, 5, 6, 7] = value
     g *= 2.0 ** -10
     p = znn.Plan(f, fo, n, k, "direct", s)
-    got, ref = p.wgrad(dev(x), dev(g)).cpu().numpy().astype(np.float64), oracle.conv3d_wgrad(x, g, s)
+    got = kernels_of(lambda: p.wgrad(dev(x), dev(g)), *names).cpu().numpy().astype(np.float64)
+    ref = oracle.conv3d_wgrad(x, g, s)
     assert np.array_equal(np.isnan(got), np.isnan(ref))
     assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref))
     ok = np.isfinite(ref)
     ref_abs = oracle.conv3d_wgrad(np.abs(x), np.abs(g), s)
     assert np.all(np.abs(got[ok] - ref[ok]) <= (2 * g[0].size + 600) * 2.0 ** -24 * ref_abs[ok])
     p.close()
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan, 3.4e38])
+@pytest.mark.parametrize("s", [(1, 1, 1), (2, 1, 2)])
+def test_kernel_gradient_of_images_that_are_not_finite_acts_as_in_fp32(value, s):
+    gradient_as_in_fp32(9, 20, (11, 12, 13), (3, 3, 3), s, value)
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan, 3.4e38])
+@pytest.mark.parametrize("n,s", [((24, 22, 27), (1, 1, 1)), ((26, 24, 29), (2, 1, 2))])
+def test_kernel_gradient_of_wide_layers_that_are_not_finite_acts_as_in_fp32(value, n, s):
+    gradient_as_in_fp32(40, 36, n, (3, 3, 3), s, value, "direct kernel gradient (MFMA)")
 
 
 @pytest.mark.parametrize("value", [np.nan, np.inf])
@@ -285,14 +342,16 @@ def test_finite_kernel_gradients_stand_beside_those_that_are_not(f, fo, n, k, s,
 
 @pytest.mark.parametrize("f,fo,n,k,s", [
     (8, 8, (131, 120, 121), (3, 3, 3), (1, 1, 1)),      # slabs of planes
-    (8, 9, (1, 1300, 1201), (1, 3, 2), (1, 1, 1)),      # slabs of rows
-    (6, 8, (140, 121, 120), (3, 2, 2), (3, 2, 2)),      # slabs of one residue
+    (16, 16, (1, 1100, 1001), (1, 3, 3), (1, 1, 1)),    # slabs of rows
+    (16, 16, (80, 121, 120), (3, 2, 2), (3, 2, 2)),     # slabs of one residue
+    (8, 9, (1, 1300, 1201), (1, 3, 2), (1, 1, 1)),      # on the vector ALUs
+    (6, 8, (140, 121, 120), (3, 2, 2), (3, 2, 2)),
 ])
 def test_kernel_gradient_of_large_layers_in_slabs(f, fo, n, k, s):
     x, w, g = tensors(f, fo, n, k, s, 9105)
     p = znn.Plan(f, fo, n, k, "direct", s)
     assert (f * x[0].size + fo * g[0].size) * 6 * 1.2 > 96 << 20 and p.workspace_bytes(2) < 192 << 20
-    gw = p.wgrad(dev(x), dev(g)).cpu().numpy()
+    gw = kernels_of(lambda: p.wgrad(dev(x), dev(g)), "direct kernel gradient (%s)" % ("few maps" if f * fo < 64 or fo == 9 else "MFMA")).cpu().numpy()
     ref, ref_abs = oracle.conv3d_wgrad(x, g, s), oracle.conv3d_wgrad(np.abs(x), np.abs(g), s)
     # sums this long are far inside the worst case: a tenth of it still leaves a lost or doubled slab no room
     assert np.all(np.abs(gw.astype(np.float64) - ref) <= 0.1 * (2 * (g[0].size // 32) + 600) * 2.0 ** -24 * ref_abs)
