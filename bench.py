@@ -181,20 +181,22 @@ def config3_rows(timer):
     x, target, params = synth.config3_tensors()
     d_x, d_t = torch.from_numpy(x).to("cuda:0"), torch.from_numpy(target).to("cuda:0")
     out_vox = 3 * 12 ** 3
+    eta = 0.01 / target.size        # the random net stays finite with it
     for mode in ("direct", "fft", "tuned"):
         net = znet.Net(synth.CONFIG3_LAYERS, synth.CONFIG3_INPUT, params, mode)
-        ms, reps = timer.run(lambda: net.train_round(d_x, d_t, synth.CONFIG3_ETA))
+        ms, reps = timer.run(lambda: net.train_round(d_x, d_t, eta))
         row = {"config": "C3", "layer": "training round: 6 conv layers 3^3 of width 40, 26^3 -> 12^3, rectifiers, two 2^3 max-filters",
                "mode": mode, "pass": "forward + backward + update", "ms": ms, "timed_reps": reps,
                "voxels_per_s": out_vox / (ms * 1e-3),
                "frac_note": "not meaningful: ~80 small launches, bound by launch latency; read the absolute time"}
         if mode == "tuned":
             row["strategies"] = [net.strategy[l] for l in sorted(net.tuning)]
-            replay, _ = net.capture_round(d_x, d_t, synth.CONFIG3_ETA)
+            replay, _ = net.capture_round(d_x, d_t, eta)
             gms, greps = timer.run(replay)
             rows.append(dict(row, mode="tuned, replayed from a HIP graph", ms=gms, timed_reps=greps,
                              voxels_per_s=out_vox / (gms * 1e-3)))
         rows.append(row)
+        assert all(bool(torch.isfinite(v).all()) for p in net.params if p for v in p.values())
         log("C3  %-6s round %.4f ms" % (mode, ms))
         del net
     for maps, n, win in ((40, (22, 22, 22), (2, 2, 2)), (40, (17, 17, 17), (2, 2, 2))):
