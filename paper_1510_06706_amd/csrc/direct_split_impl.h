@@ -8,7 +8,8 @@
 //
 // Layout: a workgroup of NW waves owns a box of output voxels for 16 NJ output maps; a wave owns NV of its 16-voxel tiles.
 // Per chunk of eight input maps the halo box is split once and staged as [voxel][3 parts][8 maps]: an operand is one 16-byte
-// LDS read, and voxels 48 bytes apart spread over the banks (3 is coprime to the 16 four-bank groups).  A lane group of 16
+// LDS read, and voxels 48 bytes apart spread over the banks (3 is coprime to the 16 four-bank groups; rows of the box and the taps of
+// the four lane groups still meet: 3.2 to 3.6 conflict clocks an LDS instruction, a tenth of the time).  A lane group of 16
 // reads its own tap of the step's four, at an offset it looks up once per step, so the walk over the taps is the same for
 // every kernel shape; the count is padded to a multiple of four with weights of zero.
 //

@@ -476,7 +476,8 @@ int split_grad(const Geom& g, const GradItem& item, hipStream_t s)
 }
 
 // Copies of at most 8 MiB, three workgroups per compute unit, leave a launch of their own mostly waiting: three layers of the six-layer 3D
-// net on a 12^3 patch (40 maps of 24^3, 21^3 and 19^3) took 22 us in three launches; together 305 -> 291 us a round.  Two layers
+// net on a 12^3 patch (40 maps of 24^3, 21^3 and 19^3) took 22 us in three launches; together 305 -> 291 us a round (the line lies
+// between two measured rounds).  Two layers
 // of 40 maps of 34^3 and 28^3 with sparse taps, 16 MiB and 8 MiB, gained nothing by it: 640 -> 643 us, copies no longer in the cache.
 bool split_grad_joins(const Geom& g)
 {

@@ -438,8 +438,9 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 
 // Bound by the store of the spectra (8 bytes per frequency) and the transforms; the tile's samples come in as rows of
 // neighbouring lanes, one row, then one column per thread is transformed in registers.  The phases of a workgroup wait for memory and
-// for each other, so what counts is how many workgroups a compute unit holds: five waves per SIMD (96 registers; the inverse keeps
-// 13 words in scratch for it, and three waves where columns of 32 make it 147).  Tests of mask bits and addresses that the
+// for each other, so what counts is how many workgroups a compute unit holds: five waves per SIMD (96 registers; the inverse spills
+// 13 of them for it, 21 where it writes split spectra, the forward kernels keep 12 to 44 bytes a lane in scratch; three waves where
+// columns of 32 make it 147).  Tiles of 24^3 take 60 KB of LDS, two workgroups a unit whatever the registers, and gain nothing by it.  Tests of mask bits and addresses that the
 // compiler kept across columns cost 20 to 30 registers and most of the scalar ones.  40 maps of 64^3 in tiles of 16 x 24 x 24:
 // forward 48 -> 42 us, inverse 46 -> 39 and 53 -> 44 us; inverse of tiles of 32: 43 -> 34 us.
 template <bool LONG, bool FULL>
