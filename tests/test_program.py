@@ -428,3 +428,28 @@ def test_gradients_that_share_the_copies_of_their_images(count, rewrite, bound):
     """One group of layers, a layer more than a group takes, layers that stay behind, and a bound that keeps the copies out."""
     print("case", count, rewrite, bound, flush=True)
     check(*gradients(small_layers(count), rewrite, bound), 11)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("extent", [14, 52])            # sums of shares, and transfer functions inside the passes
+def test_rounds_whose_values_are_not_finite_are_those_of_the_calls(extent, value):
+    import torch
+    layers = [("conv", 2, 40, (3, 3, 3)), ("transfer",), ("conv", 40, 40, (3, 3, 3)), ("transfer",), ("conv", 40, 24, (3, 3, 3)), ("transfer", "tanh")]
+    x, target, params = synth.net_tensors(layers, (2, extent, extent, extent + 1), 11)
+    params[2]["w"][[3, 17, 31]] = value                 # whole output maps, taken to zero or kept by the rectifier
+    params[4]["w"][5, 7, 1, 1, 1] = value
+    x, target = torch.from_numpy(x).to("cuda:0"), torch.from_numpy(target).to("cuda:0")
+    rounds = [znet.Net(layers, (2, extent, extent, extent + 1), params, "direct") for _ in range(2)]
+    program, calls = rounds[0].train_round(x, target, 1e-3), rounds[1].train_round(x, target, 1e-3, [])
+
+    def same(a, b):
+        return np.array_equal(a.cpu().numpy(), b.cpu().numpy(), equal_nan=True)
+
+    for l in (1, 3, 5):
+        assert same(program[0][l + 1], calls[0][l + 1]), l
+    for l in (0, 2, 4):
+        assert same(program[3][l]["w"], calls[3][l]["w"]), l
+        # sums of as many terms as the image has voxels, in another order
+        a, b = (r[3][l + 1]["b"].cpu().numpy() for r in (program, calls))
+        assert np.allclose(a, b, rtol=1e-4, atol=1e-4 * np.nanmax(np.abs(b[np.isfinite(b)]), initial=0), equal_nan=True), l
