@@ -21,6 +21,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace znn {
 
@@ -582,13 +583,19 @@ __global__ void __launch_bounds__(256) k_tile_add(TileAdd A)
 
 // ---------------------------------------------------------------- matrix products per frequency
 // C[m][n] = sum_k A[m][k] B[k][n] (CONJ: conj(A)) for every frequency, on v_mfma_f32_16x16x4_f32.  A workgroup owns
-// 16 MT x 16 NT results of a block of 16 frequencies, each of its four waves four of the frequencies (real and imaginary
-// part in accumulators of their own).  A chunk of four or eight k -- one or two MFMAs deep -- of both operands is copied to LDS as
-// it lies in memory (runs of 16 frequencies = 128 bytes; 16 bytes per lane, no registers) while the chunk before it is
-// used.  A lane reads the two frequencies of its row and k with one 16-byte access; the eight 16-byte pieces of a run are
+// 16 MT x 16 NT results of a block of 16 frequencies, each of its NW waves 16 / NW of the frequencies (real and imaginary
+// part in accumulators of their own).  A chunk of four k of both operands is copied to LDS as
+// it lies in memory (runs of 16 frequencies = 128 bytes; 16 bytes per lane, no registers), S - 1 chunks ahead of the one in use:
+// a workgroup waits for the oldest copies alone.  A lane reads the two frequencies of its row and k with one 16-byte access; the eight 16-byte pieces of a run are
 // stored in an order that depends on the row (piece ^ (row / 2) % 8), so that sixteen rows cover all banks, and the results
 // leave through LDS in the same arrangement, as full lines.  All workgroups of a block run on one XCD next to each
 // other in time.
+// What bounds it is the way of the operands to LDS, so it matters that copies are requested before the products they overlap: the
+// scheduler had moved every second chunk's behind them, next to the wait (1190 -> 1140 us on 120 x 125 x 120 products).  16 x 16 results by eight
+// waves with three buffers keep 24 waves on a unit: 80 x 144 x 80 products of 544 frequencies 53 -> 48 us (16 x 48 results by four
+// waves, two buffers), 20 x 80 x 28 43 -> 38 us, 40 x 45 x 40 of 4992 59 -> 55 us.  On 120 x 125 x 120: 1245 us, and 1166 us for 32 x 32 results by four waves; of
+// these alone the products take 880 us and the copies 560.  Tried for wide layers: 64 x 32 results by eight waves, three buffers, one workgroup on a unit (1190 us), 32 x 32
+// with three buffers (1240 us), by eight waves with two (1210 us), 48 x 48 (1370 us).
 // Tried: operands straight from global memory to the lanes of v_mfma_f32_4x4x1_16B_f32, whose sixteen blocks are the
 // sixteen frequencies: neighbouring lanes then lie in different rows, 64 cache accesses per load, 3.3 ms per product
 // of 96^3 images and 120 x 120 maps; the same through LDS: 1.42 ms (the short MFMAs issue at 80 % of their rate, and the
@@ -604,17 +611,30 @@ struct TileProduct {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// k of a chunk: two MFMAs deep where the products of one would not cover the way to memory
-constexpr int chunk_of(int mt, int nt) { return mt * nt == 1 ? 8 : 4; }
+constexpr int kChunk = 4;           // k of a chunk
 
-template <int MT, int NT, bool CONJ>
-__global__ void __launch_bounds__(256, 2) k_tile_product(TileProduct P)
+// Workgroup barrier behind this wave's LDS reads and copies but the newest N.  The wait is the builtin, as the compiler has to know that the
+// older copies have landed: behind a wait in inline assembly it puts one for all copies before the next LDS read.
+template <int N>
+__device__ __forceinline__ void copies_barrier()
+{
+    __builtin_amdgcn_s_waitcnt((N & 15) | (N >> 4) << 14 | 7 << 4);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+template <int MT, int NT, int NW, int S, bool CONJ>
+__global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 6) k_tile_product(TileProduct P)
 {
     constexpr int RA = 16 * MT, RB = 16 * NT;               // rows of A and B in LDS
-    constexpr int kChunk = chunk_of(MT, NT);
-    constexpr int LA = RA * kChunk / 8 / 4, LB = RB * kChunk / 8 / 4;       // copies of 1 KiB (8 rows) per wave and chunk
-    __shared__ float4 buf0[(RA + RB) * kChunk * 8];
-    __shared__ float4 buf1[(RA + RB) * kChunk * 8];
+    constexpr int FP = 8 / NW;                              // pairs of frequencies of a wave
+    constexpr int kBuf = (RA + RB) * kChunk * 8;
+    constexpr int LA = RA * kChunk / 8 / NW, LB = RB * kChunk / 8 / NW;     // copies of 1 KiB (8 rows) per wave and chunk
+    static_assert(RA * kChunk / 8 % NW == 0 && RB * kChunk / 8 % NW == 0, "");
+    __shared__ float4 buf0[kBuf];
+    __shared__ float4 buf1[kBuf];
+    __shared__ float4 buf2[S > 2 ? kBuf : 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // consecutive workgroups go to the eight XCDs in turn: each XCD takes a contiguous run of (block, tile) pairs
     const int per = P.gm * P.gn * P.splits;
@@ -643,7 +663,8 @@ __global__ void __launch_bounds__(256, 2) k_tile_product(TileProduct P)
         const int row = 8 * ((wave * LB + c) % (RB / 8)) + (lane >> 3);
         bo[c] = (unsigned)(min(n0 + row, P.N - 1) * P.bn) * 8u + (unsigned)(((lane & 7) ^ ((row >> 1) & 7)) * 16);
     }
-    auto copy = [&](float4* buf, int k) {
+    // requested where it stands, in front of the products
+    auto copy = [&](float4* buf, int k) __attribute__((always_inline)) {
 #pragma unroll
         for (int c = 0; c < LA; ++c) {
             const int kk = min(k + (wave * LA + c) / (RA / 8), k1 - 1);
@@ -655,34 +676,35 @@ __global__ void __launch_bounds__(256, 2) k_tile_product(TileProduct P)
             __builtin_amdgcn_global_load_lds((global_cptr)(B + (long)kk * (P.bk * 8) + bo[c]),
                                              (lds_ptr)(buf + RA * kChunk * 8 + (wave * LB + c) * 64), 16, 0, 0);
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
 
-    f32x4 re[4][MT][NT], im[4][MT][NT];                     // [frequency]
+    f32x4 re[2 * FP][MT][NT], im[2 * FP][MT][NT];           // [frequency]
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
+    for (int f = 0; f < 2 * FP; ++f)
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int t = 0; t < NT; ++t) re[f][i][t] = im[f][i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int row = lane & 15, kl = lane >> 4;
-    const int at0 = row * 8 + ((2 * wave) ^ (row >> 1)), at1 = row * 8 + ((2 * wave + 1) ^ (row >> 1));
-    auto chunk = [&](const float4* buf, int k) {
+    int at[FP];
 #pragma unroll
-        for (int s = 0; s < kChunk / 4; ++s, k += 4)
+    for (int h = 0; h < FP; ++h) at[h] = row * 8 + ((FP * wave + h) ^ (row >> 1));
+    auto chunk = [&](const float4* buf, int k, auto last) __attribute__((always_inline)) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {                       // frequencies 2 h, 2 h + 1 of the wave
-            const float4* pa = buf + (4 * s + kl) * RA * 8;
-            const float4* pb = buf + (RA * kChunk + (4 * s + kl) * RB) * 8;
-            const int at = h ? at1 : at0;
+        for (int h = 0; h < FP; ++h) {                       // frequencies 2 h, 2 h + 1 of the wave
+            const float4* pa = buf + kl * RA * 8;
+            const float4* pb = buf + (RA * kChunk + kl * RB) * 8;
             float4 a[MT], b[NT];
 #pragma unroll
-            for (int i = 0; i < MT; ++i) a[i] = pa[i * 128 + at];
-            if (k + 4 > k1 && k + kl >= k1) {               // behind the last k
+            for (int i = 0; i < MT; ++i) a[i] = pa[i * 128 + at[h]];
 #pragma unroll
-                for (int i = 0; i < MT; ++i) a[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int t = 0; t < NT; ++t) b[t] = pb[t * 128 + at[h]];
+            if constexpr (decltype(last)::value) {          // k behind the last one
+                const bool in = k + kl < k1;
+#pragma unroll
+                for (int i = 0; i < MT; ++i) a[i] = make_float4(in ? a[i].x : 0.f, in ? a[i].y : 0.f, in ? a[i].z : 0.f, in ? a[i].w : 0.f);
             }
-#pragma unroll
-            for (int t = 0; t < NT; ++t) b[t] = pb[t * 128 + at];
 #pragma unroll
             for (int i = 0; i < MT; ++i) {
                 const float n0_ = -a[i].y, n1_ = -a[i].w;
@@ -702,50 +724,72 @@ __global__ void __launch_bounds__(256, 2) k_tile_product(TileProduct P)
         }
     };
     // never taken: tells the optimizer that LDS holds data
-    if (P.K < 0) buf0[threadIdx.x] = buf1[threadIdx.x] = *reinterpret_cast<const float4*>(A + threadIdx.x * 16);
-    if (k0 < k1) copy(buf0, k0);
-    int k = k0;
-    for (; k + kChunk < k1; k += 2 * kChunk) {
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        copy(buf1, k + kChunk);
-        chunk(buf0, k);
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (k + 2 * kChunk < k1) copy(buf0, k + 2 * kChunk);
-        chunk(buf1, k + kChunk);
+    if (P.K < 0) buf0[threadIdx.x] = buf1[threadIdx.x] = buf2[0] = *reinterpret_cast<const float4*>(A + threadIdx.x * 16);
+    const int n = k1 > k0 ? (k1 - k0 + kChunk - 1) / kChunk : 0;            // chunks
+    auto buffer = [&](auto which) -> float4* {
+        constexpr int W = decltype(which)::value;
+        if constexpr (W == 0) return buf0; else if constexpr (W == 1) return buf1; else return buf2;
+    };
+    // the first copies of a workgroup without k (an empty share) read the last k there is
+    copy(buf0, k0);
+    if constexpr (S > 2) copy(buf1, k0 + kChunk);
+    int c = 0;
+    // whole turns of the buffers; copies behind the last chunk repeat it
+    auto turn = [&](auto which) __attribute__((always_inline)) {
+        constexpr int W = decltype(which)::value;
+        copies_barrier<(S - 2) * (LA + LB)>();
+        copy(buffer(std::integral_constant<int, (W + S - 1) % S>{}), k0 + min(c + W + S - 1, n - 1) * kChunk);
+        chunk(buffer(which), k0 + (c + W) * kChunk, std::false_type{});
+    };
+    for (; c + S < n; c += S) {
+        turn(std::integral_constant<int, 0>{});
+        turn(std::integral_constant<int, 1>{});
+        if constexpr (S > 2) turn(std::integral_constant<int, 2>{});
     }
-    if (k < k1) {
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        chunk(buf0, k);
+    // the last one to S chunks
+    if (n > 0) {
+        copies_barrier<0>();
+        if (c + S - 1 < n) copy(buffer(std::integral_constant<int, S - 1>{}), k0 + (c + S - 1) * kChunk);
+        chunk(buf0, k0 + c * kChunk, std::true_type{});
     }
-    // results: lane (n = lane % 16, q = lane / 16) holds rows 4 q .. 4 q + 3 of a tile.  SR rows at a time go through LDS.
-    constexpr int SR = 8 * RB <= (RA + RB) * kChunk ? 8 : 4;
+    if (c + 1 < n) {
+        copies_barrier<0>();
+        chunk(buf1, k0 + (c + 1) * kChunk, std::true_type{});
+    }
+    if (S > 2 && c + 2 < n) {
+        copies_barrier<0>();
+        chunk(buf2, k0 + (c + 2) * kChunk, std::true_type{});
+    }
+    copies_barrier<0>();
+    // results: lane (n = lane % 16, q = lane / 16) holds rows 4 q .. 4 q + 3 of a tile.  SR rows at a time go through LDS, through
+    // the two buffers in turn.
+    constexpr int SR = 8 * 8 * RB <= kBuf ? 8 : 4;
     float2* C = P.C + blk * P.blkC + split * P.splitC;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int part = 0; part < 16 / SR; ++part) {
             const int mrow = m0 + 16 * i + SR * part;
-            __syncthreads();
-            if (mrow < P.M && (lane >> 4) * 4 / SR == part) {
+            if (mrow >= P.M) break;                                 // uniform
+            float4* const buf = (i * (16 / SR) + part) & 1 ? buf1 : buf0;
+            if ((lane >> 4) * 4 / SR == part) {
                 const int q4 = (lane >> 4) % (SR / 4);
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        float4* o = buf0 + ((4 * q4 + r) * RB + 16 * t) * 8;
-                        o[at0] = make_float4(re[0][i][t][r], im[0][i][t][r], re[1][i][t][r], im[1][i][t][r]);
-                        o[at1] = make_float4(re[2][i][t][r], im[2][i][t][r], re[3][i][t][r], im[3][i][t][r]);
+                        float4* o = buf + ((4 * q4 + r) * RB + 16 * t) * 8;
+#pragma unroll
+                        for (int h = 0; h < FP; ++h)
+                            o[at[h]] = make_float4(re[2 * h][i][t][r], im[2 * h][i][t][r], re[2 * h + 1][i][t][r], im[2 * h + 1][i][t][r]);
                     }
             }
-            __syncthreads();
+            lds_barrier();
 #pragma unroll 4
-            for (int u = threadIdx.x; u < SR * RB * 8; u += 256) {
+            for (int u = threadIdx.x; u < SR * RB * 8; u += 64 * NW) {
                 const int m = u / (RB * 8), n = (u / 8) % RB, piece = (u & 7) ^ ((n >> 1) & 7);
                 if (mrow + m < P.M && n0 + n < P.N)
-                    *reinterpret_cast<float4*>(C + (long)(mrow + m) * P.cm + (long)(n0 + n) * P.cn + piece * 2) = buf0[u];
+                    *reinterpret_cast<float4*>(C + (long)(mrow + m) * P.cm + (long)(n0 + n) * P.cn + piece * 2) = buf[u];
             }
         }
 }
@@ -842,7 +886,7 @@ int inverse_tiles(const char* name, TileGeom G, long entries, const float2* src,
     return check_launch(name);
 }
 
-template <int MT, int NT>
+template <int MT, int NT, int NW, int S>
 int product_of(const char* name, bool conj, TileProduct P, hipStream_t s)
 {
     P.gm = (P.M + 16 * MT - 1) / (16 * MT);
@@ -850,41 +894,20 @@ int product_of(const char* name, bool conj, TileProduct P, hipStream_t s)
     const long run = ((long)P.blocks * P.gm * P.gn * P.splits + 7) / 8, grid = run * 8;
     if (grid >= 2147483647L) return fail(ZNN_EUNSUPPORTED, "too many tiles for one launch");
     P.run = (int)run;
-    if (conj) ZNN_LAUNCH(name, s, (k_tile_product<MT, NT, true>), dim3((unsigned)grid), dim3(256), 0, P);
-    else      ZNN_LAUNCH(name, s, (k_tile_product<MT, NT, false>), dim3((unsigned)grid), dim3(256), 0, P);
+    if (conj) ZNN_LAUNCH(name, s, (k_tile_product<MT, NT, NW, S, true>), dim3((unsigned)grid), dim3(64 * NW), 0, P);
+    else      ZNN_LAUNCH(name, s, (k_tile_product<MT, NT, NW, S, false>), dim3((unsigned)grid), dim3(64 * NW), 0, P);
     return check_launch(name);
 }
 
-// Result tiles of a workgroup by the time they leave.  Clocks of a chunk of four k with two workgroups on a compute unit, measured
-// on 120 x 125 x 120 products of 7488 frequencies (all shapes within 1.15 to 1.40 ms): larger tiles read less, smaller ones keep
-// more workgroups in flight.  Alone on its unit a workgroup takes 0.6 of that, and never less than the way to memory, which chunks of
-// eight k halve.  40 maps x 16 tiles of 32 x 32 of a 2D layer: 105 workgroups of 1 x 1 instead of 35 of 3 x 1, 19.4 -> 10.5 us;
-// gradient of 80 x 80 maps: 1 x 1 instead of 2 x 2, 66 -> 57 us.
+// Tiles of 32 x 32 results read half as much, but a compute unit holds two of their workgroups, so they take products of at least four rounds
+// of these, where padding to 32 costs little: 120 x 125 x 120 products of 7488 frequencies 1166 us against 1245, 111 x 64 x 21 187 against 207.
+// Below, 16 x 16: 80 x 144 x 80 of 544 frequencies 48 us against 60, 28 x 56 x 20 of 6336 35 against 42, 40 x 45 x 40 of 4992 58 against 91.  On 177 products
+// of 60 layers the rule is within 2 % of the faster one of seven shapes.
 int product(const char* name, bool conj, const TileProduct& P, hipStream_t s)
 {
-    struct Shape { int m, n; double clocks; };
-    constexpr Shape shapes[] = {{2, 2, 6040}, {3, 1, 4640}, {1, 3, 4850}, {2, 1, 2990}, {1, 2, 3140}, {1, 1, 1720}};
-    const int mt = (P.M + 15) / 16, nt = (P.N + 15) / 16;
-    int best = 0;
-    double best_cost = 0;
-    for (int i = 0; i < 6; ++i) {
-        const Shape& S = shapes[i];
-        const double groups = (double)P.blocks * P.splits * ((mt + S.m - 1) / S.m) * ((nt + S.n - 1) / S.n);
-        const int deep = chunk_of(S.m, S.n);
-        const double chunks = std::ceil(std::ceil((double)P.K / P.splits) / deep);
-        const double alone = 0.6 + 0.4 * std::min(1.0, std::max(0.0, groups / 256.0 - 1.0));
-        const double rounds = groups > 2048.0 ? groups / 512.0 : std::ceil(groups / 512.0);
-        const double cost = rounds * (chunks * std::max(alone * S.clocks * deep / 4, 1500.0) + 4000.0);
-        if (i == 0 || cost < best_cost) { best = i; best_cost = cost; }
-    }
-    switch (best) {
-        case 0: return product_of<2, 2>(name, conj, P, s);
-        case 1: return product_of<3, 1>(name, conj, P, s);
-        case 2: return product_of<1, 3>(name, conj, P, s);
-        case 3: return product_of<2, 1>(name, conj, P, s);
-        case 4: return product_of<1, 2>(name, conj, P, s);
-        default: return product_of<1, 1>(name, conj, P, s);
-    }
+    auto groups = [&](int rows) { return (double)P.blocks * P.splits * ((P.M + rows - 1) / rows) * ((P.N + rows - 1) / rows); };
+    if (groups(32) >= 2048 && groups(16) >= 3.2 * groups(32)) return product_of<2, 2, 4, 2>(name, conj, P, s);
+    return product_of<1, 1, 8, 3>(name, conj, P, s);
 }
 
 constexpr int kLengths[] = {8, 12, 16, 20, 24, 32};

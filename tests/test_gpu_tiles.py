@@ -42,3 +42,28 @@ def test_products_of_few_tiles_match_the_oracle(f, fo, n, k):
         err = np.linalg.norm(got.cpu().numpy().astype(np.float64) - ref)
         assert err <= 2.0 ** -24 * (6 * np.log2(np.prod(m)) + terms) * np.linalg.norm(size)
     p.close()
+
+
+# sums of one to nine chunks of four, whole and not, on 16 x 16 results and, of wide layers, on 32 x 32
+@pytest.mark.parametrize("f,fo,n,k", [
+    (2, 3, (1, 50, 50), (1, 5, 5)),
+    (4, 5, (9, 30, 21), (3, 3, 3)),
+    (11, 12, (1, 60, 33), (1, 7, 7)),
+    (13, 21, (12, 14, 31), (3, 4, 3)),
+    (33, 66, (58, 58, 44), (3, 3, 3)),
+    (35, 97, (58, 44, 47), (4, 3, 5)),
+    (61, 63, (70, 70, 70), (5, 5, 5)),          # forward and backward by 32 x 32
+    (63, 127, (42, 42, 42), (7, 7, 7)),
+])
+def test_products_of_every_number_of_chunks_match_the_direct_method(f, fo, n, k):
+    print("case", f, fo, n, k, flush=True)
+    x, w, g = (dev(v) for v in synth.layer_tensors(synth.LayerShape("t", f, fo, n, k, 1.0, 9400 + f, (1, 1, 1))))
+    p, q = znn.Plan(f, fo, n, k, "fft"), znn.Plan(f, fo, n, k, "direct")
+    m, t = p.tiles
+    for name, a, b, terms in (("fwd", x, w, f), ("bwd", g, w, fo), ("wgrad", x, g, int(np.prod(t)))):
+        got, ref = getattr(p, name)(a, b).double(), getattr(q, name)(a, b).double()
+        size = getattr(q, name)(a.abs(), b.abs()).double().norm()
+        # the direct method sums a few thousand products, or n^3 of a gradient in shares, each chain no longer than 512
+        assert (got - ref).norm() <= 2.0 ** -24 * (6 * np.log2(np.prod(m)) + terms + 512) * size, name
+    p.close()
+    q.close()
