@@ -30,6 +30,7 @@ namespace {
 constexpr int kTileThreads = 512;           // most threads of a transform workgroup
 constexpr int kTileEntries = 16;            // most tiles of a transform workgroup
 constexpr size_t kTileLds = 60 * 1024;   // LDS of a transform workgroup: two fit a compute unit
+constexpr size_t kUnitLds = 160 * 1024, kTileStatic = 512;      // LDS of a compute unit; of a workgroup beside its tiles
 
 // ---------------------------------------------------------------- transforms of tiles
 // An entry is one tile of one map (for kernels: one kernel).  Axis order z, y, x everywhere.
@@ -70,10 +71,33 @@ __device__ __forceinline__ EntryInfo entry_info(const TileGeom& G, int e)
     return I;
 }
 
+// Lengths 2^a q with q = 3 or 5 are taken apart by the prime factor algorithm: element q n1 + 2^a n2 (mod M) goes to place n1 of
+// transform n2, and coefficient (k1, k2) is that of the k with these residues, so nothing is multiplied by twiddles in between, and all
+// indices are of registers (24 points: 264 instead of 320 operations).
+constexpr int odd_part(int n) { return n % 2 ? n : odd_part(n / 2); }
+
 template <int M, int DIR>
 __device__ __forceinline__ void fft_inplace(float2 (&v)[M])
 {
-    if constexpr (M > 1) {
+    constexpr int Q = odd_part(M), P = M / Q;
+    if constexpr (Q > 1 && P > 1) {
+        float2 t[Q][P];
+#pragma unroll
+        for (int n2 = 0; n2 < Q; ++n2) {
+#pragma unroll
+            for (int n1 = 0; n1 < P; ++n1) t[n2][n1] = v[(Q * n1 + P * n2) % M];
+            fft_inplace<P, DIR>(t[n2]);
+        }
+#pragma unroll
+        for (int k1 = 0; k1 < P; ++k1) {
+            float2 c[Q];
+#pragma unroll
+            for (int n2 = 0; n2 < Q; ++n2) c[n2] = t[n2][k1];
+            fft_inplace<Q, DIR>(c);
+#pragma unroll
+            for (int j = 0; j < Q; ++j) v[k1 + P * j] = c[(k1 + P * j) % Q];
+        }
+    } else if constexpr (M > 1) {
         float2 w[M];
         passes<M, DIR, M, 1>(v, w);
         if constexpr (count_passes(M) % 2 == 1) {
@@ -83,11 +107,13 @@ __device__ __forceinline__ void fft_inplace(float2 (&v)[M])
     }
 }
 
-// real row of M samples at `row` (masked) -> M/2 + 1 coefficients in the same words, by one thread
+// real row of M samples at `row` (masked) -> M/2 + 1 coefficients in the same words, by one thread.  With a = Z[k], b = Z[H - k],
+// e = a + conj b and u = -i w^k (a - conj b): X[k] = (e + u) / 2 and X[H - k] = conj(e - u) / 2.
 template <int M, bool FULL>
 __device__ __forceinline__ void row_r2c(float2* row, unsigned mask)
 {
     constexpr int H = M / 2;
+    static_assert(H % 2 == 0, "");
     float2 Z[H];
 #pragma unroll
     for (int m = 0; m < H; ++m) {
@@ -98,32 +124,38 @@ __device__ __forceinline__ void row_r2c(float2* row, unsigned mask)
     fft_inplace<H, -1>(Z);
     row[0] = make_float2(Z[0].x + Z[0].y, 0.f);
     row[H] = make_float2(Z[0].x - Z[0].y, 0.f);
+    row[H / 2] = make_float2(Z[H / 2].x, -Z[H / 2].y);
 #pragma unroll
-    for (int k = 1; k < H; ++k) {
+    for (int k = 1; k < H / 2; ++k) {
         const float2 a = Z[k], b = Z[H - k];
-        const float2 e = make_float2(a.x + b.x, a.y - b.y);
-        const float2 d = make_float2(a.x - b.x, a.y + b.y);
-        const float wc = TwTable<M>::t.c[k], ws = -TwTable<M>::t.s[k];
-        row[k] = make_float2(0.5f * (e.x + wc * d.y + ws * d.x), 0.5f * (e.y + ws * d.y - wc * d.x));
+        const float ex = 0.5f * (a.x + b.x), ey = 0.5f * (a.y - b.y), dx = a.x - b.x, dy = a.y + b.y;
+        const float wc = 0.5f * TwTable<M>::t.c[k], ws = -0.5f * TwTable<M>::t.s[k];
+        const float ux = wc * dy + ws * dx, uy = ws * dy - wc * dx;
+        row[k] = make_float2(ex + ux, ey + uy);
+        row[H - k] = make_float2(ex - ux, uy - ey);
     }
 }
 
-// M/2 + 1 coefficients -> M real samples (times M) in the same words
+// M/2 + 1 coefficients -> M real samples (times M) in the same words.  Z[k] = e + u and Z[H - k] = conj(e - u) with a = X[k], b = X[H - k],
+// e = a + conj b and u = i w^-k (a - conj b).
 template <int M>
 __device__ __forceinline__ void row_c2r(float2* row)
 {
     constexpr int H = M / 2;
+    static_assert(H % 2 == 0, "");
     float2 X[H + 1], Z[H];
 #pragma unroll
     for (int k = 0; k <= H; ++k) X[k] = row[k];
     Z[0] = make_float2(X[0].x + X[H].x, X[0].x - X[H].x);
+    Z[H / 2] = make_float2(2.f * X[H / 2].x, -2.f * X[H / 2].y);
 #pragma unroll
-    for (int k = 1; k < H; ++k) {
+    for (int k = 1; k < H / 2; ++k) {
         const float2 a = X[k], b = X[H - k];
-        const float2 e = make_float2(a.x + b.x, a.y - b.y);            // X[k] + conj X[H-k]
-        const float2 d = make_float2(a.x - b.x, a.y + b.y);            // X[k] - conj X[H-k]
-        const float wc = TwTable<M>::t.c[k], ws = TwTable<M>::t.s[k];  // w^-k
-        Z[k] = make_float2(e.x - wc * d.y - ws * d.x, e.y + wc * d.x - ws * d.y);     // e + i w^-k d
+        const float ex = a.x + b.x, ey = a.y - b.y, dx = a.x - b.x, dy = a.y + b.y;
+        const float wc = TwTable<M>::t.c[k], ws = TwTable<M>::t.s[k];          // w^-k
+        const float ux = -wc * dy - ws * dx, uy = wc * dx - ws * dy;
+        Z[k] = make_float2(ex + ux, ey + uy);
+        Z[H - k] = make_float2(ex - ux, uy - ey);
     }
     fft_inplace<H, +1>(Z);
 #pragma unroll
@@ -381,7 +413,11 @@ __device__ __forceinline__ void load_samples(float* lf, const float* __restrict_
 #pragma unroll
                         for (int bit = 1; bit < VW; bit *= 2)
 #pragma unroll
-                            for (int c = 0; c + bit < VW; ++c) t[c] = d & bit ? t[c + bit] : t[c];      // ascending: reads what is not yet shifted
+                            for (int c = 0; c + bit < VW; ++c) {        // ascending: reads what is not yet shifted
+                                float here = t[c], next = t[c + bit];
+                                asm volatile("" : "+v"(here), "+v"(next));      // a choice between registers; else it becomes one of a place in scratch memory
+                                t[c] = d & bit ? next : here;
+                            }
                     }
 #pragma unroll
                     for (int c = 0; c < VW; ++c) t[c] = c < left ? t[c] : 0.f;
@@ -439,13 +475,13 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 
 // Bound by the store of the spectra (8 bytes per frequency) and the transforms; the tile's samples come in as rows of
 // neighbouring lanes, one row, then one column per thread is transformed in registers.  The phases of a workgroup wait for memory and
-// for each other, so what counts is how many workgroups a compute unit holds: five waves per SIMD (96 registers; the inverse spills
-// 13 of them for it, 21 where it writes split spectra, the forward kernels keep 12 to 44 bytes a lane in scratch; three waves where
-// columns of 32 make it 147).  Tiles of 24^3 take 60 KB of LDS, two workgroups a unit whatever the registers, and gain nothing by it.  Tests of mask bits and addresses that the
+// for each other, so what counts is how many workgroups a compute unit holds (finish_geom): four waves per SIMD (128 registers;
+// three where columns of 32 make it 147) and no scratch memory.  At five waves, 96 registers, the inverse spilled 13: kernel gradients of 120 x 120 maps,
+// 24^3, 240 -> 203 us.  Tests of mask bits and addresses that the
 // compiler kept across columns cost 20 to 30 registers and most of the scalar ones.  40 maps of 64^3 in tiles of 16 x 24 x 24:
-// forward 48 -> 42 us, inverse 46 -> 39 and 53 -> 44 us; inverse of tiles of 32: 43 -> 34 us.
+// forward 41 -> 37 us, inverse 41 -> 36 us; their kernels 27 -> 19 and 21 -> 16 us.
 template <bool LONG, bool FULL>
-__global__ void __launch_bounds__(kTileThreads, 5) k_tile_fwd(TileFwd A)
+__global__ void __launch_bounds__(kTileThreads, 4) k_tile_fwd(TileFwd A)
 {
     extern __shared__ float2 lds[];
     __shared__ EntryInfo info[kTileEntries];
@@ -480,7 +516,7 @@ __global__ void __launch_bounds__(kTileThreads, 5) k_tile_fwd(TileFwd A)
 }
 
 template <bool LONG, bool SPLIT>
-__global__ void __launch_bounds__(kTileThreads, LONG ? 3 : 5) k_tile_inv(TileInv A)
+__global__ void __launch_bounds__(kTileThreads, LONG ? 3 : 4) k_tile_inv(TileInv A)
 {
     extern __shared__ float2 lds[];
     __shared__ EntryInfo info[kTileEntries];
@@ -810,10 +846,12 @@ unsigned mask_of(int o, int w, int sp)
     return m;
 }
 
+bool has_long(const TileGeom& G) { return G.M[0] > 24 || G.M[1] > 24 || G.M[2] > 24; }
+
 // Fills what follows from the fields set by the caller; returns threads and LDS bytes of a workgroup.  Entries per
 // workgroup: as many as keep the threads of the column passes busiest within 40 KiB of LDS (four workgroups per compute
 // unit; a single larger tile still leaves two), while the launch has two workgroups per compute unit.
-void finish_geom(TileGeom& G, long entries, int* threads, size_t* lds)
+void finish_geom(TileGeom& G, long entries, bool inverse, int* threads, size_t* lds)
 {
     G.entries = (int)entries;
     if (!G.count) G.count = G.T[0] * G.T[1] * G.T[2];
@@ -839,7 +877,17 @@ void finish_geom(TileGeom& G, long entries, int* threads, size_t* lds)
     G.fwx = make_fastdiv((unsigned)(G.w[2] / G.vw));
     G.fMxh = make_fastdiv((unsigned)G.Mxh);
     G.fcol = make_fastdiv((unsigned)(G.M[1] * G.Mxh));
-    *threads = std::min(kTileThreads, std::max(128, (nb * cols + 63) / 64 * 64));
+    // Waves of a workgroup.  The unit places a workgroup of five waves two on one SIMD, so it holds two such workgroups where registers
+    // would do for four: workgroups of four waves, or of two where no phase but the last has more rows and columns, if a unit gets three of them.
+    // 40 maps of 64^3, 1800 tiles: 5 waves 40.9 / 41.4 / 39.7 us (inverse, images, gradients), 4 waves 37.5 / 39.0 / 34.6, 3 waves 40.0 / 41.5 / 35.3; kernels 5, 4, 2
+    // waves 26.8, 23.3, 19.5.  Fewer workgroups leave the unit to one or two of them, and these take all the waves the column passes fill (108
+    // workgroups 9.0 us, by two waves 14.8), as do tiles that fill half of its LDS (24^3: 349 us, by four waves 470).
+    const int rows = nb * G.w[0] * std::max(G.w[1], G.Mxh);         // or columns along y
+    const long fit = std::min((long)(kUnitLds / (nb * one + kTileStatic)), (entries + nb * 256 - 1) / (nb * 256));
+    if (fit >= 3)
+        *threads = rows <= 128 || (inverse && has_long(G)) ? 128 : 256;
+    else
+        *threads = std::min(kTileThreads, std::max(128, (nb * cols + 63) / 64 * 64));
     *lds = nb * one;
     G.rows_per_step = *threads / (G.w[2] / G.vw);
     G.step[2] = G.rows_per_step % G.w[1];
@@ -847,13 +895,11 @@ void finish_geom(TileGeom& G, long entries, int* threads, size_t* lds)
     G.step[0] = G.rows_per_step / G.w[1] / G.w[0];
 }
 
-bool has_long(const TileGeom& G) { return G.M[0] > 24 || G.M[1] > 24 || G.M[2] > 24; }
-
 int forward_tiles(const char* name, TileGeom G, long entries, const float* src, float2* dst, hipStream_t s)
 {
     TileFwd A;
     int threads; size_t lds;
-    finish_geom(G, entries, &threads, &lds);
+    finish_geom(G, entries, false, &threads, &lds);
     A.src = src; A.dst = dst; A.G = G;
     const dim3 grid((unsigned)((entries + G.per_wg - 1) / G.per_wg)), block(threads);
     bool full = true;
@@ -873,7 +919,7 @@ int inverse_tiles(const char* name, TileGeom G, long entries, const float2* src,
 {
     TileInv A;
     int threads; size_t lds;
-    finish_geom(G, entries, &threads, &lds);
+    finish_geom(G, entries, true, &threads, &lds);
     A.src = src; A.dst = dst; A.G = G; A.scale = scale; A.splits = splits; A.split_stride = split_stride;
     const dim3 grid((unsigned)((entries + G.per_wg - 1) / G.per_wg)), block(threads);
     if (has_long(G)) {
