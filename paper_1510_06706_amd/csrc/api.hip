@@ -215,18 +215,30 @@ static int run_kernel_spectra(const Geom& g, const FftWay& y, const float* w, fl
     return y.tile.on ? tile_kernel_spectra(g, y.tile, w, What, s) : fft_kernel_spectra(g, y.fold, w, What, s);
 }
 
-static int run_fft_fwd(const Geom& g, const FftWay& y, const float* in, const float* w, const float2* resident, float* out,
-                       void* ws, float2* memo_in, hipStream_t s)
+// Whole volumes: spectra that do not belong in the workspace are made first.
+static int whole_kernels(const Geom& g, const FftWay& y, const KernelSpectra& K, const float2** resident, hipStream_t s)
 {
-    if (!y.tile.on) return fft_fwd(g, y.fold, in, w, resident, out, ws, memo_in, s);
-    return tile_fwd(g, y.tile, in, w, resident, out, ws, tile_workspace_bytes(g, y.tile, ZNN_PASS_FWD, resident != nullptr), memo_in, s);
+    *resident = K.held ? K.held : K.made;
+    return !K.held && K.made ? fft_kernel_spectra(g, y.fold, K.w, K.made, s) : ZNN_OK;
 }
 
-static int run_fft_bwd(const Geom& g, const FftWay& y, const float* gout, const float* w, const float2* resident, float* gin,
+static int run_fft_fwd(const Geom& g, const FftWay& y, const float* in, const KernelSpectra& K, float* out,
+                       void* ws, float2* memo_in, hipStream_t s)
+{
+    if (y.tile.on)
+        return tile_fwd(g, y.tile, in, K, out, ws, tile_workspace_bytes(g, y.tile, ZNN_PASS_FWD, K.held || K.made), memo_in, s);
+    const float2* resident;
+    const int rc = whole_kernels(g, y, K, &resident, s);
+    return rc != ZNN_OK ? rc : fft_fwd(g, y.fold, in, K.w, resident, out, ws, memo_in, s);
+}
+
+static int run_fft_bwd(const Geom& g, const FftWay& y, const float* gout, const KernelSpectra& K, float* gin,
                        void* ws, float2* memo_gout, hipStream_t s)
 {
-    if (!y.tile.on) return fft_bwd(g, y.fold, gout, w, resident, gin, ws, memo_gout, s);
-    return tile_bwd(g, y.tile, gout, w, resident, gin, ws, memo_gout, s);
+    if (y.tile.on) return tile_bwd(g, y.tile, gout, K, gin, ws, memo_gout, s);
+    const float2* resident;
+    const int rc = whole_kernels(g, y, K, &resident, s);
+    return rc != ZNN_OK ? rc : fft_bwd(g, y.fold, gout, K.w, resident, gin, ws, memo_gout, s);
 }
 
 static int run_fft_wgrad(const Geom& g, const FftWay& y, const float* in, const float* gout, float* gw, void* ws, hipStream_t s)
@@ -251,21 +263,17 @@ size_t plan_pass_bytes(const znn_plan* p, int pass, bool resident)
 size_t plan_kernel_bytes(const znn_plan* p) { return fft_spectra_bytes(p->g, p->fold); }
 size_t plan_memo_bytes(const znn_plan* p) { return fft_memo_bytes(p->g, way_of(p)); }
 
-int plan_kernel_spectra(const znn_plan* p, const float* w, float2* What, hipStream_t s)
-{
-    return run_kernel_spectra(p->g, way_of(p), w, What, s);
-}
-
 int plan_pass(const znn_plan* p, int pass, const float* a, const float* b, float* result, const float2* resident, void* ws,
-              float2* memo, hipStream_t s)
+              float2* memo, hipStream_t s, float2* made)
 {
     const Geom& g = p->g;
+    const KernelSpectra K = {resident ? nullptr : b, resident, made};
     if (p->mode == ZNN_DIRECT)
         return pass == ZNN_PASS_FWD ? direct_fwd(g, a, b, result, ws, s)
              : pass == ZNN_PASS_BWD ? direct_bwd(g, a, b, result, ws, s) : direct_wgrad(g, a, b, result, ws, s);
-    if (pass == ZNN_PASS_FWD) return run_fft_fwd(g, way_of(p), a, b, resident, result, ws, memo, s);
+    if (pass == ZNN_PASS_FWD) return run_fft_fwd(g, way_of(p), a, K, result, ws, memo, s);
     if (pass == ZNN_PASS_WGRAD) return run_fft_wgrad(g, way_of(p), a, b, result, ws, s);
-    return run_fft_bwd(g, way_of(p), a, b, resident, result, ws, memo ? memo_gradients(g, way_of(p), memo) : nullptr, s);
+    return run_fft_bwd(g, way_of(p), a, K, result, ws, memo ? memo_gradients(g, way_of(p), memo) : nullptr, s);
 }
 
 size_t plan_forward_least(const znn_plan* p)
@@ -280,7 +288,7 @@ int plan_forward_within(znn_plan* p, const float* in, const float* w, float* out
     if (p->mode == ZNN_DIRECT && w && direct_workspace_bytes(p->g, ZNN_PASS_FWD) > bytes) return direct_fwd_groups(p->g, in, w, out, ws, s);
     if (!p->tile.on) return znn_conv3d_fwd(p, in, w, out, ws, bytes, s);
     if (!w && !p->resident) return fail(ZNN_EINVAL, "kernel pointer is NULL");
-    const int rc = tile_fwd(p->g, p->tile, in, w, p->resident, out, ws, bytes, p->memo, s);
+    const int rc = tile_fwd(p->g, p->tile, in, KernelSpectra{w, p->resident, nullptr}, out, ws, bytes, p->memo, s);
     if (p->memo) p->memo_has_in = rc == ZNN_OK;
     return rc;
 }
@@ -629,8 +637,8 @@ int znn_autotune(const znn_conv_desc* desc, void* ws, size_t ws_bytes, void* str
                     else if (pass == 1) rc = direct_bwd(g, gout, w, gin, scr, s);
                     else rc = direct_wgrad(g, in, gout, gw, scr, s);
                 } else {
-                    if (pass == 0) rc = run_fft_fwd(g, F, in, w, nullptr, out, scr, nullptr, s);
-                    else if (pass == 1) rc = run_fft_bwd(g, F, gout, w, nullptr, gin, scr, nullptr, s);
+                    if (pass == 0) rc = run_fft_fwd(g, F, in, KernelSpectra{w, nullptr, nullptr}, out, scr, nullptr, s);
+                    else if (pass == 1) rc = run_fft_bwd(g, F, gout, KernelSpectra{w, nullptr, nullptr}, gin, scr, nullptr, s);
                     else rc = run_fft_wgrad(g, F, in, gout, gw, scr, s);
                 }
             }
@@ -756,13 +764,13 @@ int znn_autotune_round(const znn_conv_desc* desc, uint64_t memory_budget, void* 
                 if (rc == ZNN_OK) rc = direct_bwd(g, gout, w, gin, scr, s);
                 if (rc == ZNN_OK) rc = direct_wgrad(g, in, gout, gw, scr, s);
             } else if (t == ZNN_STRATEGY_FFT) {
-                rc = run_fft_fwd(g, F, in, w, nullptr, out, scr, nullptr, s);
-                if (rc == ZNN_OK) rc = run_fft_bwd(g, F, gout, w, nullptr, gin, scr, nullptr, s);
+                rc = run_fft_fwd(g, F, in, KernelSpectra{w, nullptr, nullptr}, out, scr, nullptr, s);
+                if (rc == ZNN_OK) rc = run_fft_bwd(g, F, gout, KernelSpectra{w, nullptr, nullptr}, gin, scr, nullptr, s);
                 if (rc == ZNN_OK) rc = run_fft_wgrad(g, F, in, gout, gw, scr, s);
             } else {
                 rc = run_kernel_spectra(g, F, w, What, s);
-                if (rc == ZNN_OK) rc = run_fft_fwd(g, F, in, nullptr, What, out, scr, Ihat, s);
-                if (rc == ZNN_OK) rc = run_fft_bwd(g, F, gout, nullptr, What, gin, scr, Ghat, s);
+                if (rc == ZNN_OK) rc = run_fft_fwd(g, F, in, KernelSpectra{nullptr, What, nullptr}, out, scr, Ihat, s);
+                if (rc == ZNN_OK) rc = run_fft_bwd(g, F, gout, KernelSpectra{nullptr, What, nullptr}, gin, scr, Ghat, s);
                 if (rc == ZNN_OK) rc = run_fft_wgrad_from_spectra(g, F, Ihat, Ghat, gw, scr, s);
             }
         }

@@ -481,13 +481,11 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // compiler kept across columns cost 20 to 30 registers and most of the scalar ones.  40 maps of 64^3 in tiles of 16 x 24 x 24:
 // forward 41 -> 37 us, inverse 41 -> 36 us; their kernels 27 -> 19 and 21 -> 16 us.
 template <bool LONG, bool FULL>
-__global__ void __launch_bounds__(kTileThreads, 4) k_tile_fwd(TileFwd A)
+__device__ __forceinline__ void tile_forward(float2* lds, EntryInfo* info, const TileFwd& A, int group)
 {
-    extern __shared__ float2 lds[];
-    __shared__ EntryInfo info[kTileEntries];
     const TileGeom& G = A.G;
     float* lf = reinterpret_cast<float*>(lds);
-    const int e0 = blockIdx.x * G.per_wg;
+    const int e0 = group * G.per_wg;
     if ((int)threadIdx.x < G.per_wg) info[threadIdx.x] = entry_info(G, e0 + threadIdx.x);
     lds_barrier();
     if (G.clip) {
@@ -513,6 +511,25 @@ __global__ void __launch_bounds__(kTileThreads, 4) k_tile_fwd(TileFwd A)
 #define ZNN_CALL(L) columns_z_store<L, FULL>(lds, A.dst, G, e0)
     ZNN_TILE_SWITCH(LONG, G.M[0], store_plane(lds, A.dst, G, e0), ZNN_CALL)
 #undef ZNN_CALL
+}
+
+template <bool LONG, bool FULL>
+__global__ void __launch_bounds__(kTileThreads, 4) k_tile_fwd(TileFwd A)
+{
+    extern __shared__ float2 lds[];
+    __shared__ EntryInfo info[kTileEntries];
+    tile_forward<LONG, FULL>(lds, info, A, blockIdx.x);
+}
+
+// Transforms of both operands of a pass in one launch, the second one's workgroups from `second` on (its tiles are not FULL).
+struct TileFwdPair { TileFwd item[2]; unsigned second; };
+template <bool LONG, bool FULL>
+__global__ void __launch_bounds__(kTileThreads, 4) k_tile_fwd_pair(TileFwdPair P)
+{
+    extern __shared__ float2 lds[];
+    __shared__ EntryInfo info[kTileEntries];
+    if (blockIdx.x < P.second) tile_forward<LONG, FULL>(lds, info, P.item[0], blockIdx.x);
+    else tile_forward<LONG, false>(lds, info, P.item[1], blockIdx.x - P.second);
 }
 
 template <bool LONG, bool SPLIT>
@@ -851,7 +868,7 @@ bool has_long(const TileGeom& G) { return G.M[0] > 24 || G.M[1] > 24 || G.M[2] >
 // Fills what follows from the fields set by the caller; returns threads and LDS bytes of a workgroup.  Entries per
 // workgroup: as many as keep the threads of the column passes busiest within 40 KiB of LDS (four workgroups per compute
 // unit; a single larger tile still leaves two), while the launch has two workgroups per compute unit.
-void finish_geom(TileGeom& G, long entries, bool inverse, int* threads, size_t* lds)
+void finish_geom(TileGeom& G, long entries, bool inverse, int* threads, size_t* lds, int given = 0)
 {
     G.entries = (int)entries;
     if (!G.count) G.count = G.T[0] * G.T[1] * G.T[2];
@@ -865,6 +882,8 @@ void finish_geom(TileGeom& G, long entries, bool inverse, int* threads, size_t* 
         const double use = (double)(c * cols) / t;
         if (use > best + 0.02) { best = use; nb = c; }
     }
+    // a launch of twice the waves takes twice the entries, if that leaves enough workgroups
+    if (given && nb * 2 <= kTileEntries && nb * 2 * one <= 40 * 1024 && entries >= 1024L * nb) nb *= 2;
     G.per_wg = nb;
     for (int d = 0; d < 3; ++d) {
         G.fw[d] = make_fastdiv((unsigned)G.w[d]);
@@ -888,6 +907,7 @@ void finish_geom(TileGeom& G, long entries, bool inverse, int* threads, size_t* 
         *threads = rows <= 128 || (inverse && has_long(G)) ? 128 : 256;
     else
         *threads = std::min(kTileThreads, std::max(128, (nb * cols + 63) / 64 * 64));
+    if (given) *threads = given;
     *lds = nb * one;
     G.rows_per_step = *threads / (G.w[2] / G.vw);
     G.step[2] = G.rows_per_step % G.w[1];
@@ -895,21 +915,58 @@ void finish_geom(TileGeom& G, long entries, bool inverse, int* threads, size_t* 
     G.step[0] = G.rows_per_step / G.w[1] / G.w[0];
 }
 
-int forward_tiles(const char* name, TileGeom G, long entries, const float* src, float2* dst, hipStream_t s)
+bool is_full(const TileGeom& G) { return G.w[0] == G.M[0] && G.w[1] == G.M[1] && G.w[2] == G.M[2]; }
+
+// real tiles of one operand and where their spectra go
+struct TileOperand { const char* name; TileGeom G; long entries; const float* src; float2* dst; };
+
+int forward_tiles(const TileOperand& O, hipStream_t s)
 {
     TileFwd A;
     int threads; size_t lds;
-    finish_geom(G, entries, false, &threads, &lds);
-    A.src = src; A.dst = dst; A.G = G;
-    const dim3 grid((unsigned)((entries + G.per_wg - 1) / G.per_wg)), block(threads);
-    bool full = true;
-    for (int d = 0; d < 3; ++d) full = full && G.w[d] == G.M[d];
-    if (has_long(G)) {
-        if (full) ZNN_LAUNCH(name, s, (k_tile_fwd<true, true>), grid, block, lds, A);
-        else      ZNN_LAUNCH(name, s, (k_tile_fwd<true, false>), grid, block, lds, A);
+    A.src = O.src; A.dst = O.dst; A.G = O.G;
+    finish_geom(A.G, O.entries, false, &threads, &lds);
+    const dim3 grid((unsigned)((O.entries + A.G.per_wg - 1) / A.G.per_wg)), block(threads);
+    const bool full = is_full(A.G);
+    if (has_long(A.G)) {
+        if (full) ZNN_LAUNCH(O.name, s, (k_tile_fwd<true, true>), grid, block, lds, A);
+        else      ZNN_LAUNCH(O.name, s, (k_tile_fwd<true, false>), grid, block, lds, A);
     } else {
-        if (full) ZNN_LAUNCH(name, s, (k_tile_fwd<false, true>), grid, block, lds, A);
-        else      ZNN_LAUNCH(name, s, (k_tile_fwd<false, false>), grid, block, lds, A);
+        if (full) ZNN_LAUNCH(O.name, s, (k_tile_fwd<false, true>), grid, block, lds, A);
+        else      ZNN_LAUNCH(O.name, s, (k_tile_fwd<false, false>), grid, block, lds, A);
+    }
+    return check_launch(O.name);
+}
+
+// Both operands of a pass.  Neither waits for the other, and the launch of the smaller one would not fill the chip: 20 -> 28 maps, 23 x 131 x 115,
+// forward 38.8 + 14.6 us, gradient 38.7 + 46.6; the round's transforms of operands 198 -> 167 us, the six layers of the 2D net's round 110 -> 82 us.
+int forward_tiles(const char* name, const TileOperand& first, const TileOperand& second, hipStream_t s)
+{
+    const TileOperand* const O[2] = {&first, &second};
+    TileFwdPair P;
+    int threads[2]; size_t lds[2]; unsigned groups[2];
+    for (int q = 0; q < 2; ++q) {
+        P.item[q].src = O[q]->src; P.item[q].dst = O[q]->dst; P.item[q].G = O[q]->G;
+        finish_geom(P.item[q].G, O[q]->entries, false, &threads[q], &lds[q]);
+    }
+    const int most = std::max(threads[0], threads[1]);
+    for (int q = 0; q < 2; ++q) {
+        if (threads[q] < most) {
+            P.item[q].G = O[q]->G;
+            finish_geom(P.item[q].G, O[q]->entries, false, &threads[q], &lds[q], most);
+        }
+        groups[q] = (unsigned)((O[q]->entries + P.item[q].G.per_wg - 1) / P.item[q].G.per_wg);
+    }
+    P.second = groups[0];
+    const dim3 grid(groups[0] + groups[1]), block(most);
+    const size_t bytes = std::max(lds[0], lds[1]);
+    const bool full = is_full(first.G);
+    if (has_long(first.G)) {
+        if (full) ZNN_LAUNCH(name, s, (k_tile_fwd_pair<true, true>), grid, block, bytes, P);
+        else      ZNN_LAUNCH(name, s, (k_tile_fwd_pair<true, false>), grid, block, bytes, P);
+    } else {
+        if (full) ZNN_LAUNCH(name, s, (k_tile_fwd_pair<false, true>), grid, block, bytes, P);
+        else      ZNN_LAUNCH(name, s, (k_tile_fwd_pair<false, false>), grid, block, bytes, P);
     }
     return check_launch(name);
 }
@@ -1055,31 +1112,36 @@ size_t tile_workspace_bytes(const Geom& g, const Tiling& L, int pass, bool resid
     return tile_node_bytes(g, L, outs) + std::max(operands, pass == ZNN_PASS_BWD ? add_bytes(L, outs) : 0);
 }
 
-int tile_kernel_spectra(const Geom& g, const Tiling& L, const float* w, float2* What, hipStream_t s)
+static TileOperand tile_kernels(const Geom& g, const Tiling& L, const float* w, float2* What)
 {
     TileGeom G = base_geom(L);
     const int k[3] = {g.kz, g.ky, g.kx}, sp[3] = {g.spz, g.spy, g.spx};
     for (int d = 0; d < 3; ++d) { G.T[d] = 1; G.hop[d] = 0; G.n[d] = G.w[d] = k[d]; G.o[d] = 0; G.sp[d] = sp[d]; }
-    return forward_tiles("fft of kernels (tiles)", G, (long)g.f * g.fo, w, What, s);
+    return TileOperand{"fft of kernels (tiles)", G, (long)g.f * g.fo, w, What};
 }
 
-static int tile_images(const Geom& g, const Tiling& L, const float* in, float2* U, int first, int count, hipStream_t s)
+int tile_kernel_spectra(const Geom& g, const Tiling& L, const float* w, float2* What, hipStream_t s)
+{
+    return forward_tiles(tile_kernels(g, L, w, What), s);
+}
+
+static TileOperand tile_images(const Geom& g, const Tiling& L, const float* in, float2* U, int first, int count)
 {
     TileGeom G = base_geom(L);
     G.first = first; G.count = count;
     const int n[3] = {g.nz, g.ny, g.nx};
     for (int d = 0; d < 3; ++d) { G.T[d] = L.T[d]; G.hop[d] = L.B[d]; G.n[d] = n[d]; G.w[d] = L.M[d]; G.o[d] = 0; G.sp[d] = 1; }
-    return forward_tiles("fft of image tiles", G, (long)g.f * count, in, U, s);
+    return TileOperand{"fft of image tiles", G, (long)g.f * count, in, U};
 }
 
-static int tile_gradients(const Geom& g, const Tiling& L, const float* gout, float2* V, hipStream_t s)
+static TileOperand tile_gradients(const Geom& g, const Tiling& L, const float* gout, float2* V)
 {
     TileGeom G = base_geom(L);
     const int o[3] = {g.oz, g.oy, g.ox};
     for (int d = 0; d < 3; ++d) {
         G.T[d] = L.T[d]; G.hop[d] = L.B[d]; G.n[d] = o[d]; G.w[d] = L.B[d]; G.o[d] = L.M[d] - L.B[d]; G.sp[d] = 1;
     }
-    return forward_tiles("fft of gradient tiles", G, (long)g.fo * L.tiles, gout, V, s);
+    return TileOperand{"fft of gradient tiles", G, (long)g.fo * L.tiles, gout, V};
 }
 
 static float inv_volume(const Tiling& L) { return (float)(1.0 / ((double)L.M[0] * L.M[1] * L.M[2])); }
@@ -1087,21 +1149,22 @@ static float inv_volume(const Tiling& L) { return (float)(1.0 / ((double)L.M[0] 
 // The tiles come in as few equal groups as the workspace allows: one in tile_workspace_bytes, more in the built-in array of
 // znn_conv3d_fwd_static.  Tiles of the forward pass do not meet, and a product adds in the same order whatever the group,
 // so the results are the same bits.
-int tile_fwd(const Geom& g, const Tiling& L, const float* in, const float* w, const float2* resident, float* out,
+int tile_fwd(const Geom& g, const Tiling& L, const float* in, const KernelSpectra& K, float* out,
              void* ws, size_t ws_bytes, float2* memo_in, hipStream_t s)
 {
-    const size_t kernels = resident ? 0 : tile_kernel_bytes(g, L);
-    auto images = [&](int c) { return memo_in ? 0 : spectra_of(L, (long)g.f * c); };
+    const size_t kernels = K.held || K.made ? 0 : tile_kernel_bytes(g, L);
+    auto image_bytes = [&](int c) { return memo_in ? 0 : spectra_of(L, (long)g.f * c); };
     int count = 0;
     for (int n = 1; n <= L.tiles && !count; ++n) {
         const int c = (L.tiles + n - 1) / n;
-        if (images(c) + kernels + spectra_of(L, (long)g.fo * c) <= ws_bytes) count = c;
+        if (image_bytes(c) + kernels + spectra_of(L, (long)g.fo * c) <= ws_bytes) count = c;
     }
     if (!count) return fail(ZNN_EWORKSPACE, "workspace too small for the spectra of the kernels and of one tile");
     float2* const U = memo_in ? memo_in : (float2*)ws;
-    float2* const own = (float2*)((char*)ws + images(count));
+    float2* const own = (float2*)((char*)ws + image_bytes(count));
     float2* const result = (float2*)((char*)own + kernels);
-    const float2* const What = resident ? resident : own;
+    float2* const made = K.made ? K.made : own;
+    const float2* const What = K.held ? K.held : made;
     TileGeom G = base_geom(L);
     const int o[3] = {g.oz, g.oy, g.ox};
     for (int d = 0; d < 3; ++d) {
@@ -1111,9 +1174,10 @@ int tile_fwd(const Geom& g, const Tiling& L, const float* in, const float* w, co
         const int c = std::min(count, L.tiles - first);
         int rc = ZNN_OK;
         // a memo buffer takes the spectra of all tiles
-        if (!memo_in) rc = tile_images(g, L, in, U, first, c, s);
-        else if (first == 0) rc = tile_images(g, L, in, U, 0, L.tiles, s);
-        if (rc == ZNN_OK && !resident && first == 0) rc = tile_kernel_spectra(g, L, w, own, s);
+        const bool transform = !memo_in || first == 0;
+        const TileOperand images = memo_in ? tile_images(g, L, in, U, 0, L.tiles) : tile_images(g, L, in, U, first, c);
+        if (!K.held && first == 0) rc = forward_tiles("fft of image tiles and kernels", images, tile_kernels(g, L, K.w, made), s);
+        else if (transform) rc = forward_tiles(images, s);
         if (rc != ZNN_OK) return rc;
         const int tiles = memo_in ? L.tiles : c;                // of a map of U
         TileProduct P = {};
@@ -1130,21 +1194,18 @@ int tile_fwd(const Geom& g, const Tiling& L, const float* in, const float* w, co
     return ZNN_OK;
 }
 
-int tile_bwd(const Geom& g, const Tiling& L, const float* gout, const float* w, const float2* resident, float* gin,
+int tile_bwd(const Geom& g, const Tiling& L, const float* gout, const KernelSpectra& K, float* gin,
              void* ws, float2* memo_gout, hipStream_t s)
 {
     char* p = (char*)ws;
     float2* V = memo_gout;
     if (!V) { V = (float2*)p; p += tile_node_bytes(g, L, g.fo); }
-    const float2* What = resident;
-    int rc = tile_gradients(g, L, gout, V, s);
+    float2* made = K.made;
+    if (!K.held && !made) { made = (float2*)p; p += tile_kernel_bytes(g, L); }
+    const float2* const What = K.held ? K.held : made;
+    int rc = K.held ? forward_tiles(tile_gradients(g, L, gout, V), s)
+                    : forward_tiles("fft of gradient tiles and kernels", tile_gradients(g, L, gout, V), tile_kernels(g, L, K.w, made), s);
     if (rc != ZNN_OK) return rc;
-    if (!What) {
-        What = (const float2*)p;
-        rc = tile_kernel_spectra(g, L, w, (float2*)p, s);
-        if (rc != ZNN_OK) return rc;
-        p += tile_kernel_bytes(g, L);
-    }
     const bool one = L.tiles == 1;
     // The real tiles of the result take the start of the workspace, over the operands that lie there and have been
     // used by then; its spectra lie behind both.
@@ -1207,8 +1268,7 @@ int tile_wgrad(const Geom& g, const Tiling& L, const float* in, const float* gou
     char* p = (char*)ws;
     float2* U = (float2*)p; p += tile_node_bytes(g, L, g.f);
     float2* V = (float2*)p; p += tile_node_bytes(g, L, g.fo);
-    int rc = tile_images(g, L, in, U, 0, L.tiles, s);
-    if (rc == ZNN_OK) rc = tile_gradients(g, L, gout, V, s);
+    const int rc = forward_tiles("fft of image and gradient tiles", tile_images(g, L, in, U, 0, L.tiles), tile_gradients(g, L, gout, V), s);
     if (rc != ZNN_OK) return rc;
     return tile_wgrad_from_spectra(g, L, U, V, gw, p, s);
 }

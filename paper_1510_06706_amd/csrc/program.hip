@@ -682,12 +682,9 @@ int run_conv(znn_program& P, Step& t, float* const* buf, char* scratch, hipStrea
         } else finished = finished || inside;
     } else {
         float2* What = L.spectra != kNone ? (float2*)(scratch + L.spectra) : nullptr;
-        if (What && transforms_kernels(L, t.kind)) {
-            rc = plan_kernel_spectra(&L.plan, at(1), What, s);
-            if (rc != ZNN_OK) return rc;
-        }
         float2* memo = L.memo != kNone ? (float2*)(scratch + L.memo) : nullptr;
-        rc = plan_pass(&L.plan, t.kind, at(0), What ? nullptr : at(1), at(2), What, area, memo, s);
+        const bool held = What && !transforms_kernels(L, t.kind);
+        rc = plan_pass(&L.plan, t.kind, at(0), held ? nullptr : at(1), at(2), held ? What : nullptr, area, memo, s, What);
         if (rc != ZNN_OK) return rc;
     }
     if (!finished) {

@@ -291,10 +291,12 @@ int check_filter(int32_t maps, znn_vec3 n, znn_vec3 win, znn_vec3 sp, bool pool)
 size_t plan_pass_bytes(const znn_plan* p, int pass, bool resident);
 size_t plan_kernel_bytes(const znn_plan* p);        // spectra of the kernels
 size_t plan_memo_bytes(const znn_plan* p);          // spectra of images and gradients
-int plan_kernel_spectra(const znn_plan* p, const float* w, float2* What, hipStream_t s);
-// forward: a = in, b = w, result = out; backward: gout, w, gin; kernel gradient: in, gout, gw
+// Kernel spectra of a pass: held by the caller (w NULL), or made from w by the pass itself, at `made` or (NULL) in its workspace.
+struct KernelSpectra { const float* w; const float2* held; float2* made; };
+// forward: a = in, b = w, result = out; backward: gout, w, gin; kernel gradient: in, gout, gw.  The spectra that b stands for: `resident`, or,
+// where that is NULL, made at `made` or in the workspace.
 int plan_pass(const znn_plan* p, int pass, const float* a, const float* b, float* result, const float2* resident, void* ws,
-              float2* memo, hipStream_t s);
+              float2* memo, hipStream_t s, float2* made = nullptr);
 int plan_wgrad_memo(const znn_plan* p, float2* memo, float* gw, void* ws, hipStream_t s);
 // the forward pass in less than its workspace: on tiles in as little as it would take on whole volumes
 size_t plan_forward_least(const znn_plan* p);

@@ -77,6 +77,8 @@ def flops4_wgrad_dft(taps: int) -> float:
 # the FFT method on overlapping tiles
 TILE_STEPS = {
     "fft of kernels (tiles)": "F-ker", "fft of image tiles": "F-img", "fft of gradient tiles": "F-img",
+    "fft of image tiles and kernels": "F-img and F-ker", "fft of gradient tiles and kernels": "F-img and F-ker",
+    "fft of image and gradient tiles": "F-img",
     "spectral products forward (tiles)": "F-mac", "spectral products backward (tiles)": "F-mac",
     "spectral products of the kernel gradient (tiles)": "F-wgrad products",
     "inverse fft of image tiles": "F-inv", "inverse fft of gradient tiles": "F-inv",
@@ -130,6 +132,7 @@ def work_of_tiles(cfg, tiles, what: str):
     w["F-ker"] = w["F-wgrad inverse"] = ("hbm", pairs * (4.0 * k + 8.0 * omega))
     w["F-img"] = ("hbm", {"fwd": f * (4.0 * n + node), "bwd": fo * (4.0 * no + node)}.get(
         what, f * (4.0 * n + node) + fo * (4.0 * no + node)))
+    w["F-img and F-ker"] = ("hbm", w["F-img"][1] + w["F-ker"][1])
     w["F-inv"] = ("hbm", fo * (4.0 * no + node) if what == "fwd" else f * ((4.0 * tvol * nt if nt > 1 else 4.0 * n) + node))
     w["F-add"] = ("hbm", 4.0 * f * (tvol * nt + n))
     return w

@@ -67,3 +67,27 @@ def test_products_of_every_number_of_chunks_match_the_direct_method(f, fo, n, k)
         assert (got - ref).norm() <= 2.0 ** -24 * (6 * np.log2(np.prod(m)) + terms + 512) * size, name
     p.close()
     q.close()
+
+
+@pytest.mark.parametrize("f,fo,n,k,s", [
+    (7, 5, (9, 31, 33), (3, 4, 3), (1, 1, 1)),          # few entries: none are doubled up
+    (34, 40, (1, 90, 77), (1, 7, 9), (1, 1, 1)),        # 2D, clipped tiles, kernels by twice the waves and entries
+    (48, 40, (23, 40, 42), (3, 5, 5), (1, 1, 1)),
+    (24, 25, (26, 30, 44), (2, 3, 2), (2, 3, 4)),       # spaced taps
+    (40, 30, (30, 33, 62), (11, 9, 12), (1, 1, 1)),     # tiles of 32
+])
+def test_transforms_of_both_operands_in_one_launch(f, fo, n, k, s):
+    """Kernels transformed beside the images, and images beside the gradients, give the bits of launches of their own
+    (prepared kernels, kept node spectra)."""
+    import torch
+    print("case", f, fo, n, k, s, flush=True)
+    x, w, g = (dev(v) for v in synth.layer_tensors(synth.LayerShape("t", f, fo, n, k, 1.0, 9500 + f, s)))
+    p, q = znn.Plan(f, fo, n, k, "fft", s), znn.Plan(f, fo, n, k, "fft", s)
+    assert p.tiles is not None
+    q.enable_memo("cuda:0")
+    q.prepare_kernels(w)
+    assert torch.equal(p.fwd(x, w), q.fwd(x, None))
+    assert torch.equal(p.bwd(g, w), q.bwd(g, None))
+    assert torch.equal(p.wgrad(x, g), q.wgrad_memo())
+    p.close()
+    q.close()
