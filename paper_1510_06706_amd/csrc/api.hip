@@ -223,19 +223,19 @@ static int whole_kernels(const Geom& g, const FftWay& y, const KernelSpectra& K,
 }
 
 static int run_fft_fwd(const Geom& g, const FftWay& y, const float* in, const KernelSpectra& K, float* out,
-                       void* ws, float2* memo_in, hipStream_t s)
+                       void* ws, float2* memo_in, hipStream_t s, const Finish& finish = {})
 {
     if (y.tile.on)
-        return tile_fwd(g, y.tile, in, K, out, ws, tile_workspace_bytes(g, y.tile, ZNN_PASS_FWD, K.held || K.made), memo_in, s);
+        return tile_fwd(g, y.tile, in, K, out, ws, tile_workspace_bytes(g, y.tile, ZNN_PASS_FWD, K.held || K.made), memo_in, finish, s);
     const float2* resident;
     const int rc = whole_kernels(g, y, K, &resident, s);
     return rc != ZNN_OK ? rc : fft_fwd(g, y.fold, in, K.w, resident, out, ws, memo_in, s);
 }
 
 static int run_fft_bwd(const Geom& g, const FftWay& y, const float* gout, const KernelSpectra& K, float* gin,
-                       void* ws, float2* memo_gout, hipStream_t s)
+                       void* ws, float2* memo_gout, hipStream_t s, const Finish& finish = {})
 {
-    if (y.tile.on) return tile_bwd(g, y.tile, gout, K, gin, ws, memo_gout, s);
+    if (y.tile.on) return tile_bwd(g, y.tile, gout, K, gin, ws, memo_gout, finish, s);
     const float2* resident;
     const int rc = whole_kernels(g, y, K, &resident, s);
     return rc != ZNN_OK ? rc : fft_bwd(g, y.fold, gout, K.w, resident, gin, ws, memo_gout, s);
@@ -264,16 +264,21 @@ size_t plan_kernel_bytes(const znn_plan* p) { return fft_spectra_bytes(p->g, p->
 size_t plan_memo_bytes(const znn_plan* p) { return fft_memo_bytes(p->g, way_of(p)); }
 
 int plan_pass(const znn_plan* p, int pass, const float* a, const float* b, float* result, const float2* resident, void* ws,
-              float2* memo, hipStream_t s, float2* made)
+              float2* memo, hipStream_t s, PassMore* more)
 {
     const Geom& g = p->g;
-    const KernelSpectra K = {resident ? nullptr : b, resident, made};
+    const KernelSpectra K = {resident ? nullptr : b, resident, more ? more->made : nullptr};
+    Finish finish = {};
+    if (more && p->mode == ZNN_FFT && p->tile.on && more->finish.fn == ZNN_RECTIFY) {
+        finish = more->finish;
+        more->finished = true;
+    }
     if (p->mode == ZNN_DIRECT)
         return pass == ZNN_PASS_FWD ? direct_fwd(g, a, b, result, ws, s)
              : pass == ZNN_PASS_BWD ? direct_bwd(g, a, b, result, ws, s) : direct_wgrad(g, a, b, result, ws, s);
-    if (pass == ZNN_PASS_FWD) return run_fft_fwd(g, way_of(p), a, K, result, ws, memo, s);
+    if (pass == ZNN_PASS_FWD) return run_fft_fwd(g, way_of(p), a, K, result, ws, memo, s, finish);
     if (pass == ZNN_PASS_WGRAD) return run_fft_wgrad(g, way_of(p), a, b, result, ws, s);
-    return run_fft_bwd(g, way_of(p), a, K, result, ws, memo ? memo_gradients(g, way_of(p), memo) : nullptr, s);
+    return run_fft_bwd(g, way_of(p), a, K, result, ws, memo ? memo_gradients(g, way_of(p), memo) : nullptr, s, finish);
 }
 
 size_t plan_forward_least(const znn_plan* p)
@@ -288,7 +293,7 @@ int plan_forward_within(znn_plan* p, const float* in, const float* w, float* out
     if (p->mode == ZNN_DIRECT && w && direct_workspace_bytes(p->g, ZNN_PASS_FWD) > bytes) return direct_fwd_groups(p->g, in, w, out, ws, s);
     if (!p->tile.on) return znn_conv3d_fwd(p, in, w, out, ws, bytes, s);
     if (!w && !p->resident) return fail(ZNN_EINVAL, "kernel pointer is NULL");
-    const int rc = tile_fwd(p->g, p->tile, in, KernelSpectra{w, p->resident, nullptr}, out, ws, bytes, p->memo, s);
+    const int rc = tile_fwd(p->g, p->tile, in, KernelSpectra{w, p->resident, nullptr}, out, ws, bytes, p->memo, Finish{}, s);
     if (p->memo) p->memo_has_in = rc == ZNN_OK;
     return rc;
 }

@@ -48,17 +48,16 @@ struct TileGeom {
     int first, count;           // tiles of a map in this launch: numbers first .. first + count - 1 (finish_geom: 0 = all)
 };
 struct TileFwd { const float* src; float2* dst; TileGeom G; };
-struct TileInv { const float2* src; float* dst; TileGeom G; float scale; int splits; long split_stride; };
+struct TileInv { const float2* src; float* dst; TileGeom G; float scale; int splits; long split_stride; Finish finish; };
 
-struct EntryInfo { long base; int v[3]; int ok; };
+struct EntryInfo { long base; int v[3]; int map; };
 
 // where an entry's samples lie in the real maps, and how many of them per axis exist
 __device__ __forceinline__ EntryInfo entry_info(const TileGeom& G, int e)
 {
     EntryInfo I;
-    I.ok = e < G.entries;
-    if (!I.ok) { I.base = 0; I.v[0] = I.v[1] = I.v[2] = 0; return I; }
-    const int map = e / G.count;
+    if (e >= G.entries) { I.base = 0; I.v[0] = I.v[1] = I.v[2] = I.map = 0; return I; }
+    const int map = I.map = e / G.count;
     int t = G.first + e - map * G.count;
     const int tz = t / (G.T[1] * G.T[2]);
     t -= tz * G.T[1] * G.T[2];
@@ -428,9 +427,13 @@ __device__ __forceinline__ void load_samples(float* lf, const float* __restrict_
     }
 }
 
-template <int VW>
-__device__ __forceinline__ void store_samples(const float* lf, float* dst, float scale, const TileGeom& G, const EntryInfo* info)
+// What follows the sums of an image (Finish, the rectifier) is done as they are stored.  A pass of its own over the image took 17 us beside the 36
+// of the transform on 40 maps of 23 x 75 x 125, and 4 us where there is little of it.
+template <int VW, bool FINISH>
+__device__ __forceinline__ void store_samples(const float* lf, const TileInv& A, const EntryInfo* info, const float* bias)
 {
+    const TileGeom& G = A.G;
+    const Finish& F = A.finish;
     typedef typename VecOf<VW>::type vec;
     RowWalk R(G, VW);
     if (R.idle) return;
@@ -438,10 +441,31 @@ __device__ __forceinline__ void store_samples(const float* lf, float* dst, float
     while (R.b < G.per_wg) {
         const EntryInfo& E = info[R.b];
         const int at = R.lds_at(G), left = R.left(E);
-        float* p = dst + R.at(G, E);
+        const long place = R.at(G, E);
+        float* p = A.dst + place;
         float v[VW];
 #pragma unroll
-        for (int c = 0; c < VW; ++c) v[c] = scale * lf[at + c * G.sp[2]];
+        for (int c = 0; c < VW; ++c) v[c] = A.scale * lf[at + c * G.sp[2]];
+        if (FINISH && F.deriv) {                        // uniform, as F.y
+#pragma unroll
+            for (int c = 0; c < VW; ++c)
+                if (c < left) v[c] = F.deriv[place + c] > 0.f ? v[c] : 0.f;
+        }
+        if (FINISH && F.y) {
+#pragma clang fp contract(off)                          // of the sum that is stored
+            float u[VW];
+#pragma unroll
+            for (int c = 0; c < VW; ++c) { u[c] = v[c] + bias[R.b]; u[c] = u[c] > 0.f ? u[c] : 0.f; }
+            if (left >= VW) {
+                vec t;
+                __builtin_memcpy(&t, u, sizeof(vec));
+                *reinterpret_cast<vec*>(F.y + place) = t;
+            } else {
+#pragma unroll
+                for (int c = 0; c < VW; ++c)
+                    if (c < left) F.y[place + c] = u[c];
+            }
+        }
         if (left >= VW) {
             vec t;
             __builtin_memcpy(&t, v, sizeof(vec));
@@ -537,10 +561,14 @@ __global__ void __launch_bounds__(kTileThreads, LONG ? 3 : 4) k_tile_inv(TileInv
 {
     extern __shared__ float2 lds[];
     __shared__ EntryInfo info[kTileEntries];
+    __shared__ float bias[kTileEntries];
     const TileGeom& G = A.G;
     const float* lf = reinterpret_cast<const float*>(lds);
     const int e0 = blockIdx.x * G.per_wg;
-    if ((int)threadIdx.x < G.per_wg) info[threadIdx.x] = entry_info(G, e0 + threadIdx.x);
+    if ((int)threadIdx.x < G.per_wg) {
+        info[threadIdx.x] = entry_info(G, e0 + threadIdx.x);
+        if (A.finish.y) bias[threadIdx.x] = A.finish.bias[info[threadIdx.x].map];
+    }
 #define ZNN_CALL(L) (load_columns_z<L, SPLIT>)(lds, A, e0)
     ZNN_TILE_SWITCH(LONG, G.M[0], load_plane(lds, A, e0), ZNN_CALL)
 #undef ZNN_CALL
@@ -555,13 +583,19 @@ __global__ void __launch_bounds__(kTileThreads, LONG ? 3 : 4) k_tile_inv(TileInv
     ZNN_TILE_SWITCH(LONG, G.M[2], (void)0, ZNN_CALL)
 #undef ZNN_CALL
     lds_barrier();
-    if (G.vw == 4) store_samples<4>(lf, A.dst, A.scale, G, info);
-    else if (G.vw == 2) store_samples<2>(lf, A.dst, A.scale, G, info);
-    else store_samples<1>(lf, A.dst, A.scale, G, info);
+    if (A.finish.y || A.finish.deriv) {
+        if (G.vw == 4) store_samples<4, true>(lf, A, info, bias);
+        else if (G.vw == 2) store_samples<2, true>(lf, A, info, bias);
+        else store_samples<1, true>(lf, A, info, bias);
+    } else {
+        if (G.vw == 4) store_samples<4, false>(lf, A, info, bias);
+        else if (G.vw == 2) store_samples<2, false>(lf, A, info, bias);
+        else store_samples<1, false>(lf, A, info, bias);
+    }
 }
 
-// gin[x] = sum over the tiles that cover x, in ascending order (overlap-add).  Bound by the read of the tiles.
-struct TileAdd { const float* src; float* dst; int M[3], T[3], hop[3], n[3]; FastDiv fhop[3], fnx; int xy, zs; };
+// gin[x] = sum over the tiles that cover x, in ascending order (overlap-add), times the rectifier's derivative if there is one below.  Bound by the read of the tiles.
+struct TileAdd { const float* src; float* dst; const float* deriv; int M[3], T[3], hop[3], n[3]; FastDiv fhop[3], fnx; int xy, zs; };
 
 // tiles lo .. hi along axis d cover coordinate c
 __device__ __forceinline__ void tiles_over(const TileAdd& A, int d, int c, int& lo, int& hi)
@@ -608,7 +642,9 @@ __global__ void __launch_bounds__(256) k_tile_add2(TileAdd A)
 #pragma unroll
             for (int i = 0; i < 4; ++i) sum = fmaf(weight[i], p[at[i]], sum);
         }
-        A.dst[(map * A.n[0] + z) * (long)A.xy + u] = sum;
+        const long to = (map * A.n[0] + z) * (long)A.xy + u;
+        if (A.deriv) sum = A.deriv[to] > 0.f ? sum : 0.f;
+        A.dst[to] = sum;
     }
 }
 
@@ -631,7 +667,9 @@ __global__ void __launch_bounds__(256) k_tile_add(TileAdd A)
             for (int d = lo[2]; d <= hi[2]; ++d)
                 sum += base[(((long)a * A.T[1] + b) * A.T[2] + d) * vol +
                             ((z - a * A.hop[0]) * A.M[1] + (y - b * A.hop[1])) * A.M[2] + (x - d * A.hop[2])];
-    A.dst[(map * A.n[0] + z) * (long)A.xy + u] = sum;
+    const long to = (map * A.n[0] + z) * (long)A.xy + u;
+    if (A.deriv) sum = A.deriv[to] > 0.f ? sum : 0.f;
+    A.dst[to] = sum;
 }
 
 // ---------------------------------------------------------------- matrix products per frequency
@@ -939,7 +977,7 @@ int forward_tiles(const TileOperand& O, hipStream_t s)
 }
 
 // Both operands of a pass.  Neither waits for the other, and the launch of the smaller one would not fill the chip: 20 -> 28 maps, 23 x 131 x 115,
-// forward 38.8 + 14.6 us, gradient 38.7 + 46.6; the round's transforms of operands 198 -> 167 us, the six layers of the 2D net's round 110 -> 82 us.
+// forward 38.8 + 14.6 us and gradient 38.7 + 46.6 in launches of their own; a round 422 -> 391 us, one of the 2D net 422 -> 394.
 int forward_tiles(const char* name, const TileOperand& first, const TileOperand& second, hipStream_t s)
 {
     const TileOperand* const O[2] = {&first, &second};
@@ -972,9 +1010,10 @@ int forward_tiles(const char* name, const TileOperand& first, const TileOperand&
 }
 
 int inverse_tiles(const char* name, TileGeom G, long entries, const float2* src, float* dst, float scale, int splits,
-                  long split_stride, hipStream_t s)
+                  long split_stride, const Finish& finish, hipStream_t s)
 {
     TileInv A;
+    A.finish = finish;
     int threads; size_t lds;
     finish_geom(G, entries, true, &threads, &lds);
     A.src = src; A.dst = dst; A.G = G; A.scale = scale; A.splits = splits; A.split_stride = split_stride;
@@ -1150,7 +1189,7 @@ static float inv_volume(const Tiling& L) { return (float)(1.0 / ((double)L.M[0] 
 // znn_conv3d_fwd_static.  Tiles of the forward pass do not meet, and a product adds in the same order whatever the group,
 // so the results are the same bits.
 int tile_fwd(const Geom& g, const Tiling& L, const float* in, const KernelSpectra& K, float* out,
-             void* ws, size_t ws_bytes, float2* memo_in, hipStream_t s)
+             void* ws, size_t ws_bytes, float2* memo_in, const Finish& finish, hipStream_t s)
 {
     const size_t kernels = K.held || K.made ? 0 : tile_kernel_bytes(g, L);
     auto image_bytes = [&](int c) { return memo_in ? 0 : spectra_of(L, (long)g.f * c); };
@@ -1188,14 +1227,14 @@ int tile_fwd(const Geom& g, const Tiling& L, const float* in, const KernelSpectr
         rc = product("spectral products forward (tiles)", false, P, s);
         G.first = first; G.count = c;
         if (rc == ZNN_OK)
-            rc = inverse_tiles("inverse fft of image tiles", G, (long)g.fo * c, result, out, inv_volume(L), 1, 0, s);
+            rc = inverse_tiles("inverse fft of image tiles", G, (long)g.fo * c, result, out, inv_volume(L), 1, 0, finish, s);
         if (rc != ZNN_OK) return rc;
     }
     return ZNN_OK;
 }
 
 int tile_bwd(const Geom& g, const Tiling& L, const float* gout, const KernelSpectra& K, float* gin,
-             void* ws, float2* memo_gout, hipStream_t s)
+             void* ws, float2* memo_gout, const Finish& finish, hipStream_t s)
 {
     char* p = (char*)ws;
     float2* V = memo_gout;
@@ -1224,10 +1263,11 @@ int tile_bwd(const Geom& g, const Tiling& L, const float* gout, const KernelSpec
         G.T[d] = 1; G.hop[d] = 0; G.o[d] = 0; G.sp[d] = 1;
         G.n[d] = G.w[d] = one ? n[d] : L.M[d];
     }
-    rc = inverse_tiles("inverse fft of gradient tiles", G, (long)g.f * L.tiles, result, one ? gin : tiles, inv_volume(L), 1, 0, s);
+    rc = inverse_tiles("inverse fft of gradient tiles", G, (long)g.f * L.tiles, result, one ? gin : tiles, inv_volume(L), 1, 0,
+                       one ? finish : Finish{}, s);
     if (rc != ZNN_OK || one) return rc;
     TileAdd A = {};
-    A.src = tiles; A.dst = gin;
+    A.src = tiles; A.dst = gin; A.deriv = finish.deriv;
     for (int d = 0; d < 3; ++d) {
         A.M[d] = L.M[d]; A.T[d] = L.T[d]; A.hop[d] = L.B[d]; A.n[d] = n[d];
         A.fhop[d] = make_fastdiv((unsigned)L.B[d]);
@@ -1260,7 +1300,7 @@ int tile_wgrad_from_spectra(const Geom& g, const Tiling& L, const float2* U, con
     const int k[3] = {g.kz, g.ky, g.kx}, sp[3] = {g.spz, g.spy, g.spx};
     for (int d = 0; d < 3; ++d) { G.T[d] = 1; G.hop[d] = 0; G.n[d] = G.w[d] = k[d]; G.o[d] = 0; G.sp[d] = sp[d]; }
     return inverse_tiles("inverse fft of kernel gradients (tiles)", G, (long)g.f * g.fo, (const float2*)scratch, gw,
-                         inv_volume(L), P.splits, P.splitC, s);
+                         inv_volume(L), P.splits, P.splitC, Finish{}, s);
 }
 
 int tile_wgrad(const Geom& g, const Tiling& L, const float* in, const float* gout, float* gw, void* ws, hipStream_t s)

@@ -684,8 +684,10 @@ int run_conv(znn_program& P, Step& t, float* const* buf, char* scratch, hipStrea
         float2* What = L.spectra != kNone ? (float2*)(scratch + L.spectra) : nullptr;
         float2* memo = L.memo != kNone ? (float2*)(scratch + L.memo) : nullptr;
         const bool held = What && !transforms_kernels(L, t.kind);
-        rc = plan_pass(&L.plan, t.kind, at(0), held ? nullptr : at(1), at(2), held ? What : nullptr, area, memo, s, What);
+        PassMore more = {What, F, false};
+        rc = plan_pass(&L.plan, t.kind, at(0), held ? nullptr : at(1), at(2), held ? What : nullptr, area, memo, s, &more);
         if (rc != ZNN_OK) return rc;
+        finished = finished || more.finished;
     }
     if (!finished) {
         if (F.y) return znn_transfer_fn_fwd(o.fn, g.fo, g.ovol(), at(2), F.bias, F.y, s);

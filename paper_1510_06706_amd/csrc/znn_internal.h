@@ -294,9 +294,12 @@ size_t plan_memo_bytes(const znn_plan* p);          // spectra of images and gra
 // Kernel spectra of a pass: held by the caller (w NULL), or made from w by the pass itself, at `made` or (NULL) in its workspace.
 struct KernelSpectra { const float* w; const float2* held; float2* made; };
 // forward: a = in, b = w, result = out; backward: gout, w, gin; kernel gradient: in, gout, gw.  The spectra that b stands for: `resident`, or,
-// where that is NULL, made at `made` or in the workspace.
+// where that is NULL, made at more->made or in the workspace.
+// What a round asks of a pass of the FFT method beside its result: where the kernel spectra go, and what follows the sums, which the pass
+// does if it can (`finished`).
+struct PassMore { float2* made; Finish finish; bool finished; };
 int plan_pass(const znn_plan* p, int pass, const float* a, const float* b, float* result, const float2* resident, void* ws,
-              float2* memo, hipStream_t s, float2* made = nullptr);
+              float2* memo, hipStream_t s, PassMore* more = nullptr);
 int plan_wgrad_memo(const znn_plan* p, float2* memo, float* gw, void* ws, hipStream_t s);
 // the forward pass in less than its workspace: on tiles in as little as it would take on whole volumes
 size_t plan_forward_least(const znn_plan* p);

@@ -91,3 +91,28 @@ def test_transforms_of_both_operands_in_one_launch(f, fo, n, k, s):
     assert torch.equal(p.wgrad(x, g), q.wgrad_memo())
     p.close()
     q.close()
+
+
+# images of one tile (the inverse transform itself takes the derivative) and of many, windows that let samples travel by four, two and one
+@pytest.mark.parametrize("f,fo,n,k", [(5, 7, (1, 20, 22), (1, 5, 5)), (17, 6, (9, 40, 37), (2, 4, 4)), (8, 9, (1, 66, 71), (1, 6, 7)),
+                                      (33, 34, (11, 33, 60), (3, 5, 5)), (4, 3, (1, 40, 40), (1, 13, 13)), (8, 9, (8, 12, 12), (1, 9, 9))])
+def test_transfer_functions_inside_the_passes_give_the_bits_of_their_own(f, fo, n, k):
+    import torch
+    from paper_1510_06706_amd import program as zp
+    print("case", f, fo, n, k, flush=True)
+    x, w, g = (dev(v) for v in synth.layer_tensors(synth.LayerShape("t", f, fo, n, k, 1.0, 9600 + f, (1, 1, 1))))
+    p = znn.Plan(f, fo, n, k, "fft")
+    assert p.tiles is not None
+    bias = torch.linspace(-0.2, 0.3, fo, device="cuda:0")
+    below = torch.where(x > 0, x, torch.zeros_like(x))           # a rectifier's result
+    out, gin, y = torch.empty_like(g), torch.empty_like(x), torch.empty_like(g)
+    P = zp.Program("cuda:0", 1)
+    for t in (x, w, out, bias, y, g, gin, below):
+        P.buffer("given", t.shape)
+    P.add(zp.CONV_FWD, (0, 1, 2, 3, 4), plan=p)
+    P.add(zp.CONV_BWD, (5, 1, 6, 7), plan=p)
+    P.build().run(dict(enumerate([x, w, out, bias, y, g, gin, below])))
+    ref, back = p.fwd(x, w), p.bwd(g, w)
+    assert torch.equal(out, ref) and torch.equal(y, torch.relu(ref + bias.view(-1, 1, 1, 1)))
+    assert torch.equal(gin, torch.where(below > 0, back, torch.zeros_like(back)))
+    p.close()
