@@ -233,9 +233,9 @@ static int run_fft_fwd(const Geom& g, const FftWay& y, const float* in, const Ke
 }
 
 static int run_fft_bwd(const Geom& g, const FftWay& y, const float* gout, const KernelSpectra& K, float* gin,
-                       void* ws, float2* memo_gout, hipStream_t s, const Finish& finish = {})
+                       void* ws, float2* memo_gout, hipStream_t s, const Finish& finish = {}, const TileGrad& grad = {})
 {
-    if (y.tile.on) return tile_bwd(g, y.tile, gout, K, gin, ws, memo_gout, finish, s);
+    if (y.tile.on) return tile_bwd(g, y.tile, gout, K, gin, ws, memo_gout, finish, grad, s);
     const float2* resident;
     const int rc = whole_kernels(g, y, K, &resident, s);
     return rc != ZNN_OK ? rc : fft_bwd(g, y.fold, gout, K.w, resident, gin, ws, memo_gout, s);
@@ -278,7 +278,15 @@ int plan_pass(const znn_plan* p, int pass, const float* a, const float* b, float
              : pass == ZNN_PASS_BWD ? direct_bwd(g, a, b, result, ws, s) : direct_wgrad(g, a, b, result, ws, s);
     if (pass == ZNN_PASS_FWD) return run_fft_fwd(g, way_of(p), a, K, result, ws, memo, s, finish);
     if (pass == ZNN_PASS_WGRAD) return run_fft_wgrad(g, way_of(p), a, b, result, ws, s);
-    return run_fft_bwd(g, way_of(p), a, K, result, ws, memo ? memo_gradients(g, way_of(p), memo) : nullptr, s, finish);
+    return run_fft_bwd(g, way_of(p), a, K, result, ws, memo ? memo_gradients(g, way_of(p), memo) : nullptr, s, finish,
+                       TileGrad{memo, more ? more->gw : nullptr});
+}
+
+bool plan_joins_gradient(const znn_plan* p)
+{
+    if (p->mode != ZNN_FFT || !p->tile.on) return false;
+    const size_t bytes = tile_joined_bytes(p->g, p->tile);
+    return bytes && bytes <= plan_pass_bytes(p, ZNN_PASS_WGRAD, false);
 }
 
 size_t plan_forward_least(const znn_plan* p)

@@ -557,14 +557,11 @@ __global__ void __launch_bounds__(kTileThreads, 4) k_tile_fwd_pair(TileFwdPair P
 }
 
 template <bool LONG, bool SPLIT>
-__global__ void __launch_bounds__(kTileThreads, LONG ? 3 : 4) k_tile_inv(TileInv A)
+__device__ __forceinline__ void tile_inverse(float2* lds, EntryInfo* info, float* bias, const TileInv& A, int group)
 {
-    extern __shared__ float2 lds[];
-    __shared__ EntryInfo info[kTileEntries];
-    __shared__ float bias[kTileEntries];
     const TileGeom& G = A.G;
     const float* lf = reinterpret_cast<const float*>(lds);
-    const int e0 = blockIdx.x * G.per_wg;
+    const int e0 = group * G.per_wg;
     if ((int)threadIdx.x < G.per_wg) {
         info[threadIdx.x] = entry_info(G, e0 + threadIdx.x);
         if (A.finish.y) bias[threadIdx.x] = A.finish.bias[info[threadIdx.x].map];
@@ -592,6 +589,27 @@ __global__ void __launch_bounds__(kTileThreads, LONG ? 3 : 4) k_tile_inv(TileInv
         else if (G.vw == 2) store_samples<2, false>(lf, A, info, bias);
         else store_samples<1, false>(lf, A, info, bias);
     }
+}
+
+template <bool LONG, bool SPLIT>
+__global__ void __launch_bounds__(kTileThreads, LONG ? 3 : 4) k_tile_inv(TileInv A)
+{
+    extern __shared__ float2 lds[];
+    __shared__ EntryInfo info[kTileEntries];
+    __shared__ float bias[kTileEntries];
+    tile_inverse<LONG, SPLIT>(lds, info, bias, A, blockIdx.x);
+}
+
+// Images and kernel gradients of one layer in one launch, the gradients' workgroups from `second` on.
+struct TileInvPair { TileInv item[2]; unsigned second; };
+template <bool LONG>
+__global__ void __launch_bounds__(kTileThreads, LONG ? 3 : 4) k_tile_inv_pair(TileInvPair P)
+{
+    extern __shared__ float2 lds[];
+    __shared__ EntryInfo info[kTileEntries];
+    __shared__ float bias[kTileEntries];
+    if (blockIdx.x < P.second) tile_inverse<LONG, false>(lds, info, bias, P.item[0], blockIdx.x);
+    else tile_inverse<LONG, true>(lds, info, bias, P.item[1], blockIdx.x - P.second);
 }
 
 // gin[x] = sum over the tiles that cover x, in ascending order (overlap-add), times the rectifier's derivative if there is one below.  Bound by the read of the tiles.
@@ -716,7 +734,7 @@ __device__ __forceinline__ void copies_barrier()
 }
 
 template <int MT, int NT, int NW, int S, bool CONJ>
-__global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 6) k_tile_product(TileProduct P)
+__device__ __forceinline__ void tile_product(const TileProduct& P, unsigned group)
 {
     constexpr int RA = 16 * MT, RB = 16 * NT;               // rows of A and B in LDS
     constexpr int FP = 8 / NW;                              // pairs of frequencies of a wave
@@ -729,7 +747,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 6) k_tile_product(TileP
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // consecutive workgroups go to the eight XCDs in turn: each XCD takes a contiguous run of (block, tile) pairs
     const int per = P.gm * P.gn * P.splits;
-    const int id = (blockIdx.x & 7) * P.run + (blockIdx.x >> 3);
+    const int id = (group & 7) * P.run + (group >> 3);
     const int blk = id / per;
     if (blk >= P.blocks) return;
     int q = id - blk * per;
@@ -885,6 +903,21 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 6) k_tile_product(TileP
         }
 }
 
+template <int MT, int NT, int NW, int S, bool CONJ>
+__global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 6) k_tile_product(TileProduct P)
+{
+    tile_product<MT, NT, NW, S, CONJ>(P, blockIdx.x);
+}
+
+// The conjugated products of the backward pass and of the kernel gradient in one launch, the latter's workgroups from `second` (a
+// multiple of eight) on.
+struct TileProductPair { TileProduct item[2]; unsigned second; };
+__global__ void __launch_bounds__(512, 6) k_tile_product_pair(TileProductPair A)
+{
+    const int q = blockIdx.x >= A.second;
+    tile_product<1, 1, 8, 3, true>(A.item[q], blockIdx.x - (q ? A.second : 0));
+}
+
 // ---------------------------------------------------------------- launches
 TileGeom base_geom(const Tiling& L)
 {
@@ -1009,33 +1042,67 @@ int forward_tiles(const char* name, const TileOperand& first, const TileOperand&
     return check_launch(name);
 }
 
-int inverse_tiles(const char* name, TileGeom G, long entries, const float2* src, float* dst, float scale, int splits,
-                  long split_stride, const Finish& finish, hipStream_t s)
+// spectra (partial sums of them, to be added) and where the real tiles go
+struct TileResult { TileGeom G; long entries; const float2* src; float* dst; float scale; int splits; long split_stride; Finish finish; };
+
+TileInv inverse_of(const TileResult& R, int given, int* threads, size_t* lds, unsigned* groups)
 {
     TileInv A;
-    A.finish = finish;
-    int threads; size_t lds;
-    finish_geom(G, entries, true, &threads, &lds);
-    A.src = src; A.dst = dst; A.G = G; A.scale = scale; A.splits = splits; A.split_stride = split_stride;
-    const dim3 grid((unsigned)((entries + G.per_wg - 1) / G.per_wg)), block(threads);
-    if (has_long(G)) {
-        if (splits > 1) ZNN_LAUNCH(name, s, (k_tile_inv<true, true>), grid, block, lds, A);
-        else            ZNN_LAUNCH(name, s, (k_tile_inv<true, false>), grid, block, lds, A);
+    A.G = R.G;
+    finish_geom(A.G, R.entries, true, threads, lds, given);
+    A.src = R.src; A.dst = R.dst; A.scale = R.scale; A.splits = R.splits; A.split_stride = R.split_stride; A.finish = R.finish;
+    *groups = (unsigned)((R.entries + A.G.per_wg - 1) / A.G.per_wg);
+    return A;
+}
+
+int inverse_tiles(const char* name, const TileResult& R, hipStream_t s)
+{
+    int threads; size_t lds; unsigned groups;
+    const TileInv A = inverse_of(R, 0, &threads, &lds, &groups);
+    const dim3 grid(groups), block(threads);
+    if (has_long(A.G)) {
+        if (A.splits > 1) ZNN_LAUNCH(name, s, (k_tile_inv<true, true>), grid, block, lds, A);
+        else              ZNN_LAUNCH(name, s, (k_tile_inv<true, false>), grid, block, lds, A);
     } else {
-        if (splits > 1) ZNN_LAUNCH(name, s, (k_tile_inv<false, true>), grid, block, lds, A);
-        else            ZNN_LAUNCH(name, s, (k_tile_inv<false, false>), grid, block, lds, A);
+        if (A.splits > 1) ZNN_LAUNCH(name, s, (k_tile_inv<false, true>), grid, block, lds, A);
+        else              ZNN_LAUNCH(name, s, (k_tile_inv<false, false>), grid, block, lds, A);
     }
     return check_launch(name);
+}
+
+// Two results of one tiling, the first one not in shares.
+int inverse_tiles(const char* name, const TileResult& first, const TileResult& second, hipStream_t s)
+{
+    TileInvPair P;
+    const TileResult* const R[2] = {&first, &second};
+    int threads[2]; size_t lds[2]; unsigned groups[2];
+    for (int q = 0; q < 2; ++q) P.item[q] = inverse_of(*R[q], 0, &threads[q], &lds[q], &groups[q]);
+    const int most = std::max(threads[0], threads[1]);
+    for (int q = 0; q < 2; ++q)
+        if (threads[q] < most) P.item[q] = inverse_of(*R[q], most, &threads[q], &lds[q], &groups[q]);
+    P.second = groups[0];
+    const dim3 grid(groups[0] + groups[1]), block(most);
+    const size_t bytes = std::max(lds[0], lds[1]);
+    if (has_long(first.G)) ZNN_LAUNCH(name, s, k_tile_inv_pair<true>, grid, block, bytes, P);
+    else                   ZNN_LAUNCH(name, s, k_tile_inv_pair<false>, grid, block, bytes, P);
+    return check_launch(name);
+}
+
+// Workgroups of a product with MT x NT tiles of 16 x 16 results each, a multiple of eight.
+long place_groups(TileProduct& P, int MT, int NT)
+{
+    P.gm = (P.M + 16 * MT - 1) / (16 * MT);
+    P.gn = (P.N + 16 * NT - 1) / (16 * NT);
+    const long run = ((long)P.blocks * P.gm * P.gn * P.splits + 7) / 8;
+    P.run = (int)std::min(run, 2147483647L / 8);
+    return run * 8;
 }
 
 template <int MT, int NT, int NW, int S>
 int product_of(const char* name, bool conj, TileProduct P, hipStream_t s)
 {
-    P.gm = (P.M + 16 * MT - 1) / (16 * MT);
-    P.gn = (P.N + 16 * NT - 1) / (16 * NT);
-    const long run = ((long)P.blocks * P.gm * P.gn * P.splits + 7) / 8, grid = run * 8;
+    const long grid = place_groups(P, MT, NT);
     if (grid >= 2147483647L) return fail(ZNN_EUNSUPPORTED, "too many tiles for one launch");
-    P.run = (int)run;
     if (conj) ZNN_LAUNCH(name, s, (k_tile_product<MT, NT, NW, S, true>), dim3((unsigned)grid), dim3(64 * NW), 0, P);
     else      ZNN_LAUNCH(name, s, (k_tile_product<MT, NT, NW, S, false>), dim3((unsigned)grid), dim3(64 * NW), 0, P);
     return check_launch(name);
@@ -1045,11 +1112,27 @@ int product_of(const char* name, bool conj, TileProduct P, hipStream_t s)
 // of these, where padding to 32 costs little: 120 x 125 x 120 products of 7488 frequencies 1166 us against 1245, 111 x 64 x 21 187 against 207.
 // Below, 16 x 16: 80 x 144 x 80 of 544 frequencies 48 us against 60, 28 x 56 x 20 of 6336 35 against 42, 40 x 45 x 40 of 4992 58 against 91.  On 177 products
 // of 60 layers the rule is within 2 % of the faster one of seven shapes.
+double groups_of(const TileProduct& P, int rows)
+{
+    return (double)P.blocks * P.splits * ((P.M + rows - 1) / rows) * ((P.N + rows - 1) / rows);
+}
+
+bool is_wide(const TileProduct& P) { return groups_of(P, 32) >= 2048 && groups_of(P, 16) >= 3.2 * groups_of(P, 32); }
+
 int product(const char* name, bool conj, const TileProduct& P, hipStream_t s)
 {
-    auto groups = [&](int rows) { return (double)P.blocks * P.splits * ((P.M + rows - 1) / rows) * ((P.N + rows - 1) / rows); };
-    if (groups(32) >= 2048 && groups(16) >= 3.2 * groups(32)) return product_of<2, 2, 4, 2>(name, conj, P, s);
-    return product_of<1, 1, 8, 3>(name, conj, P, s);
+    return is_wide(P) ? product_of<2, 2, 4, 2>(name, conj, P, s) : product_of<1, 1, 8, 3>(name, conj, P, s);
+}
+
+int products(const char* name, const TileProduct& first, const TileProduct& second, hipStream_t s)
+{
+    TileProductPair A;
+    A.item[0] = first; A.item[1] = second;
+    const long grid[2] = {place_groups(A.item[0], 1, 1), place_groups(A.item[1], 1, 1)};
+    if (grid[0] + grid[1] >= 2147483647L) return fail(ZNN_EUNSUPPORTED, "too many tiles for one launch");
+    A.second = (unsigned)grid[0];
+    ZNN_LAUNCH(name, s, k_tile_product_pair, dim3((unsigned)(grid[0] + grid[1])), dim3(512), 0, A);
+    return check_launch(name);
 }
 
 constexpr int kLengths[] = {8, 12, 16, 20, 24, 32};
@@ -1227,14 +1310,54 @@ int tile_fwd(const Geom& g, const Tiling& L, const float* in, const KernelSpectr
         rc = product("spectral products forward (tiles)", false, P, s);
         G.first = first; G.count = c;
         if (rc == ZNN_OK)
-            rc = inverse_tiles("inverse fft of image tiles", G, (long)g.fo * c, result, out, inv_volume(L), 1, 0, finish, s);
+            rc = inverse_tiles("inverse fft of image tiles", TileResult{G, (long)g.fo * c, result, out, inv_volume(L), 1, 0, finish}, s);
         if (rc != ZNN_OK) return rc;
     }
     return ZNN_OK;
 }
 
+static TileProduct backward_product(const Geom& g, const Tiling& L, const float2* What, const float2* V, float2* result)
+{
+    TileProduct P = {};
+    P.A = What; P.am = 16; P.ak = g.f * 16; P.blkA = (long)g.f * g.fo * 16;
+    P.B = V; P.bk = L.tiles * 16; P.bn = 16; P.blkB = (long)g.fo * L.tiles * 16;
+    P.C = result; P.cm = L.tiles * 16; P.cn = 16; P.blkC = (long)g.f * L.tiles * 16;
+    P.M = g.f; P.N = L.tiles; P.K = g.fo; P.blocks = L.blocks; P.splits = 1;
+    return P;
+}
+
+static TileProduct gradient_product(const Geom& g, const Tiling& L, const float2* U, const float2* V, float2* sums)
+{
+    TileProduct P = {};
+    P.splits = gradient_splits(g, L);
+    P.A = U; P.am = L.tiles * 16; P.ak = 16; P.blkA = (long)g.f * L.tiles * 16;
+    P.B = V; P.bn = L.tiles * 16; P.bk = 16; P.blkB = (long)g.fo * L.tiles * 16;
+    P.C = sums; P.cm = 16; P.cn = g.f * 16; P.blkC = (long)g.f * g.fo * 16;
+    P.splitC = P.blkC * L.blocks;
+    P.M = g.f; P.N = g.fo; P.K = L.tiles; P.blocks = L.blocks;
+    return P;
+}
+
+static TileResult gradient_result(const Geom& g, const Tiling& L, const TileProduct& P, float* gw)
+{
+    TileGeom G = base_geom(L);
+    const int k[3] = {g.kz, g.ky, g.kx}, sp[3] = {g.spz, g.spy, g.spx};
+    for (int d = 0; d < 3; ++d) { G.T[d] = 1; G.hop[d] = 0; G.n[d] = G.w[d] = k[d]; G.o[d] = 0; G.sp[d] = sp[d]; }
+    return TileResult{G, (long)g.f * g.fo, P.C, gw, inv_volume(L), P.splits, P.splitC, Finish{}};
+}
+
+// Products of a small layer leave most of the chip idle and cost what a launch does (8 us on 40 maps x 12 tiles): joined while both together are
+// at most two fills of it (a unit holds three of their workgroups).  2D nets, a round with no layer joined, those of one fill, those of two: 48^2 patch, 40 maps
+// 387 us, -, 344; 64^2 430, 399, 386; 64 maps 529, 529, 476.  Layers that fill the chip by themselves keep the shape of workgroup that is best for each.
+size_t tile_joined_bytes(const Geom& g, const Tiling& L)
+{
+    const TileProduct P = backward_product(g, L, nullptr, nullptr, nullptr), Q = gradient_product(g, L, nullptr, nullptr, nullptr);
+    if (is_wide(P) || is_wide(Q) || groups_of(P, 16) + groups_of(Q, 16) > 2 * 768) return 0;
+    return add_bytes(L, g.f) + tile_node_bytes(g, L, g.f) + Q.splits * tile_kernel_bytes(g, L);
+}
+
 int tile_bwd(const Geom& g, const Tiling& L, const float* gout, const KernelSpectra& K, float* gin,
-             void* ws, float2* memo_gout, const Finish& finish, hipStream_t s)
+             void* ws, float2* memo_gout, const Finish& finish, const TileGrad& grad, hipStream_t s)
 {
     char* p = (char*)ws;
     float2* V = memo_gout;
@@ -1251,20 +1374,22 @@ int tile_bwd(const Geom& g, const Tiling& L, const float* gout, const KernelSpec
     float* const tiles = (float*)ws;
     float2* const result = (float2*)std::max(p, (char*)ws + add_bytes(L, g.f));
     const int n[3] = {g.nz, g.ny, g.nx};
-    TileProduct P = {};
-    P.A = What; P.am = 16; P.ak = g.f * 16; P.blkA = (long)g.f * g.fo * 16;
-    P.B = V; P.bk = L.tiles * 16; P.bn = 16; P.blkB = (long)g.fo * L.tiles * 16;
-    P.C = result; P.cm = L.tiles * 16; P.cn = 16; P.blkC = (long)g.f * L.tiles * 16;
-    P.M = g.f; P.N = L.tiles; P.K = g.fo; P.blocks = L.blocks; P.splits = 1;
-    rc = product("spectral products backward (tiles)", true, P, s);
-    if (rc != ZNN_OK) return rc;
+    const TileProduct P = backward_product(g, L, What, V, result);
     TileGeom G = base_geom(L);
     for (int d = 0; d < 3; ++d) {
         G.T[d] = 1; G.hop[d] = 0; G.o[d] = 0; G.sp[d] = 1;
         G.n[d] = G.w[d] = one ? n[d] : L.M[d];
     }
-    rc = inverse_tiles("inverse fft of gradient tiles", G, (long)g.f * L.tiles, result, one ? gin : tiles, inv_volume(L), 1, 0,
-                       one ? finish : Finish{}, s);
+    const TileResult R = {G, (long)g.f * L.tiles, result, one ? gin : tiles, inv_volume(L), 1, 0, one ? finish : Finish{}};
+    if (grad.gw) {
+        const TileProduct Q = gradient_product(g, L, grad.U, V, (float2*)((char*)result + tile_node_bytes(g, L, g.f)));
+        rc = products("spectral products backward and of the kernel gradient (tiles)", P, Q, s);
+        if (rc == ZNN_OK)
+            rc = inverse_tiles("inverse fft of gradient tiles and kernel gradients", R, gradient_result(g, L, Q, grad.gw), s);
+    } else {
+        rc = product("spectral products backward (tiles)", true, P, s);
+        if (rc == ZNN_OK) rc = inverse_tiles("inverse fft of gradient tiles", R, s);
+    }
     if (rc != ZNN_OK || one) return rc;
     TileAdd A = {};
     A.src = tiles; A.dst = gin; A.deriv = finish.deriv;
@@ -1287,20 +1412,10 @@ int tile_bwd(const Geom& g, const Tiling& L, const float* gout, const KernelSpec
 int tile_wgrad_from_spectra(const Geom& g, const Tiling& L, const float2* U, const float2* V, float* gw, void* scratch,
                             hipStream_t s)
 {
-    TileProduct P = {};
-    P.splits = gradient_splits(g, L);
-    P.A = U; P.am = L.tiles * 16; P.ak = 16; P.blkA = (long)g.f * L.tiles * 16;
-    P.B = V; P.bn = L.tiles * 16; P.bk = 16; P.blkB = (long)g.fo * L.tiles * 16;
-    P.C = (float2*)scratch; P.cm = 16; P.cn = g.f * 16; P.blkC = (long)g.f * g.fo * 16;
-    P.splitC = P.blkC * L.blocks;
-    P.M = g.f; P.N = g.fo; P.K = L.tiles; P.blocks = L.blocks;
-    int rc = product("spectral products of the kernel gradient (tiles)", true, P, s);
+    const TileProduct P = gradient_product(g, L, U, V, (float2*)scratch);
+    const int rc = product("spectral products of the kernel gradient (tiles)", true, P, s);
     if (rc != ZNN_OK) return rc;
-    TileGeom G = base_geom(L);
-    const int k[3] = {g.kz, g.ky, g.kx}, sp[3] = {g.spz, g.spy, g.spx};
-    for (int d = 0; d < 3; ++d) { G.T[d] = 1; G.hop[d] = 0; G.n[d] = G.w[d] = k[d]; G.o[d] = 0; G.sp[d] = sp[d]; }
-    return inverse_tiles("inverse fft of kernel gradients (tiles)", G, (long)g.f * g.fo, (const float2*)scratch, gw,
-                         inv_volume(L), P.splits, P.splitC, Finish{}, s);
+    return inverse_tiles("inverse fft of kernel gradients (tiles)", gradient_result(g, L, P, gw), s);
 }
 
 int tile_wgrad(const Geom& g, const Tiling& L, const float* in, const float* gout, float* gw, void* ws, hipStream_t s)

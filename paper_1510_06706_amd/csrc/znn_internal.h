@@ -295,9 +295,10 @@ size_t plan_memo_bytes(const znn_plan* p);          // spectra of images and gra
 struct KernelSpectra { const float* w; const float2* held; float2* made; };
 // forward: a = in, b = w, result = out; backward: gout, w, gin; kernel gradient: in, gout, gw.  The spectra that b stands for: `resident`, or,
 // where that is NULL, made at more->made or in the workspace.
-// What a round asks of a pass of the FFT method beside its result: where the kernel spectra go, and what follows the sums, which the pass
-// does if it can (`finished`).
-struct PassMore { float2* made; Finish finish; bool finished; };
+// What a round asks of a pass of the FFT method beside its result: where the kernel spectra go, the kernel gradient beside the backward pass
+// (from the node spectra in `memo`, where plan_joins_gradient), and what follows the sums, which the pass does if it can (`finished`).
+struct PassMore { float2* made; float* gw; Finish finish; bool finished; };
+bool plan_joins_gradient(const znn_plan* p);        // within the workspace that the kernel gradient takes on its own
 int plan_pass(const znn_plan* p, int pass, const float* a, const float* b, float* result, const float2* resident, void* ws,
               float2* memo, hipStream_t s, PassMore* more = nullptr);
 int plan_wgrad_memo(const znn_plan* p, float2* memo, float* gw, void* ws, hipStream_t s);

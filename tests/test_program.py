@@ -268,6 +268,35 @@ def test_operands_of_a_layer_written_between_its_passes(order, buffer):
         check(ops[:at] + [write] + ops[at:], shapes + [shape, (maps,)], 2 + at)
 
 
+def joined_lists(plan):
+    """A layer's round, whole and with its gradient's buffer used between the backward pass and the gradient, or by the pass itself."""
+    F, B, W = conv_ops(plan, "FBW")
+    B = (B[0], (3, 1, 4, 6), B[2])                                              # times a derivative
+    gw = dict(n=(1, 1, plan.fo * plan.f * int(np.prod(plan.k))))
+    read, write = (zp.NODE_SUM, (7, 5), gw), (zp.NODE_SUM, (5, 7), gw)
+    shapes = conv_shapes(plan) + [(plan.f,) + plan.n, (plan.fo, plan.f) + plan.k]
+    return shapes, [[F, B, W], [F, B, read, W], [F, B, write, W], [F, read, B, W, read], [B, F, W], [F, B, W, (zp.UPDATE, (5, 1), gw)]]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("f,fo,n,k,s", [
+    (40, 40, (1, 30, 44), (1, 7, 7), (1, 1, 1)),
+    (9, 9, (1, 41, 37), (1, 9, 5), (1, 1, 1)),              # sums of few tiles, results below a tile of 16
+    (17, 33, (1, 28, 28), (1, 11, 11), (1, 1, 1)),
+    (33, 17, (1, 28, 28), (1, 11, 11), (1, 1, 1)),          # real tiles that take more than the spectra of the gradients
+    (8, 9, (8, 12, 12), (1, 9, 9), (1, 1, 1)),              # one tile
+    (6, 7, (8, 60, 50), (3, 2, 3), (2, 1, 2)),              # many tiles: the gradient's sums are in shares
+    (12, 20, (1, 50, 90), (1, 13, 13), (1, 1, 1)),          # tiles of 32
+])
+def test_gradients_that_share_the_launches_of_the_backward_pass(f, fo, n, k, s):
+    plan = znn.Plan(f, fo, n, k, "fft", s)
+    assert plan.tiles is not None
+    shapes, lists = joined_lists(plan)
+    for i, ops in enumerate(lists):
+        print("list", i, flush=True)
+        check(ops, shapes, 70 + i)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("streams", [1, 2])
 def test_bias_gradients_of_an_operand_that_is_written_again(streams):
