@@ -66,6 +66,11 @@ class GraphNet:
     next pass starts from events recorded after that join, so memory handed back to the allocator is never
     reused while another stream still reads it."""
 
+    # Multiply-adds of a round's convolutions, times two, from which on several streams are the faster ones.  Multi-scale nets, us a round on several streams
+    # and on one: width 8, 20^3 432 and 185; 16, 40^3 (6e9) 459 and 327; 40, 32^3 (1.7e10) 517 and 517; 32, 40^3 (2.4e10) 538 and 535; 40, 36^3 (2.5e10) 541 and
+    # 577; 40, 40^3 (3.7e10) 690 and 712; 48, 48^3 (1e11) 1479 and 1572.
+    SEVERAL_STREAMS = 2e10
+
     def __init__(self, graph, params, mode="auto", device="cuda:0", streams=4):
         import torch
         self.graph = graph
@@ -212,14 +217,21 @@ class GraphNet:
         return grads, back
 
     # ------------------------------------------------------------ rounds as one native call
+    def _side_streams(self):
+        """The streams of a round.  Its waits between streams take 5 to 12 us each, which only long edges pay for."""
+        flops = sum(6.0 * self.shapes[e[2]][0] * e[4] * math.prod(self.shapes[e[3]][1:]) * math.prod(e[5])
+                    for e in self.edges if e[0] == "conv")
+        return self.streams if flops >= self.SEVERAL_STREAMS else []
+
     def _build(self, loss):
         """A training round as a program: edge i runs on stream 1 + i mod (number of streams), kernel gradients half
         the streams further on, sums at a node on the stream of the last edge into it; the loss gradients and
-        the update run on the calling stream.  Where an edge alone fills a node, what follows the node is
+        the update run on the calling stream, and all of a small round does.  Where an edge alone fills a node, what follows the node is
         applied by that edge's operation."""
         g, shape, E = self.graph, self.shapes, self.edges
-        P = zp.Program(self.device, 1 + len(self.streams))
-        stream = lambda i: 1 + i % len(self.streams)  # noqa: E731
+        side = self._side_streams()
+        P = zp.Program(self.device, 1 + len(side))
+        stream = lambda i: 1 + i % len(side) if side else 0  # noqa: E731
         given = {(n, "x"): P.buffer("given", shape[n]) for n in g["inputs"]}
         for e in E:
             if e[0] == "conv":
@@ -302,7 +314,7 @@ class GraphNet:
                 if needed:
                     gs = P.buffer("kept", shape[src])
                     gop = P.add(zp.CONV_BWD, (b, given[name, "w"], gs), stream=s, plan=self.plans[name])
-                P.add(zp.CONV_WGRAD, (img[src], b, grads[name]["w"]), stream=stream(i + 1 + len(self.streams) // 2),
+                P.add(zp.CONV_WGRAD, (img[src], b, grads[name]["w"]), stream=stream(i + 1 + len(side) // 2),
                       plan=self.plans[name])
             elif kind == "transfer":
                 if below.get(dst) == name:
@@ -340,7 +352,7 @@ class GraphNet:
                 tensors[b] = zp.check_parameter(self.params[n][k], k, P.shapes[b])
         for n, b in target.items():
             tensors[b] = zp.check_input(targets[n], count=math.prod(self.shapes[n]))
-        out = P.run(tensors, float(eta), self.streams)
+        out = P.run(tensors, float(eta), self.streams[:P.streams - 1])
         out.update({given[n, "x"]: inputs[n] for n in self.graph["inputs"]})
         return ({n: out[b] for n, b in img.items()}, {n: out[b] for n, b in aux.items()}, {n: out[b] for n, b in gout.items()},
                 {n: {k: out[b] for k, b in d.items()} for n, d in grads.items()})

@@ -56,6 +56,25 @@ def test_multiscale_graph_round_matches_the_reference(mode):
         assert np.array_equal(results[0][key], results[1][key]), key
 
 
+@pytest.mark.parametrize("mode", ["direct", "fft"])
+def test_rounds_on_one_and_on_several_streams_are_the_same_bits(mode, monkeypatch):
+    """On either side of the size that chooses between them."""
+    g = synth.multiscale_graph()
+    inputs, targets, params = synth.graph_tensors(g, 52)
+    results = []
+    for least, streams in ((0.0, 4), (0.0, 1), (1e30, 4)):
+        monkeypatch.setattr(zgraph.GraphNet, "SEVERAL_STREAMS", least)
+        net = zgraph.GraphNet(g, params, mode, streams=streams)
+        for _ in range(2):
+            img, _, _, grads = net.train_round({n: dev(v) for n, v in inputs.items()}, {n: dev(v) for n, v in targets.items()},
+                                               1e-5, "cross_entropy")
+        results.append({(n, k): host(v) for d in ({n: {"x": v} for n, v in img.items()}, grads, net.params)
+                        for n, gr in d.items() for k, v in gr.items()})
+    for r in results[1:]:
+        for key in r:
+            assert np.array_equal(r[key], results[0][key]), key
+
+
 def test_graph_rejects_a_node_that_reaches_no_output():
     g = synth.multiscale_graph()
     g["outputs"] = ["y"]
