@@ -97,6 +97,7 @@ int grad_partial(const Geom& g, const float* in, const float* gout, float* parti
                            : split_grad(g, GradItem{&g, in, gout, partial, copies, sum}, s);
 }
 
+bool grad_is_few(const Geom& g) { return few_gradient(g); }
 bool grad_joins(const Geom& g) { return !few_gradient(g) && split_grad_joins(g); }
 int grads_partial(const GradItem* items, int count, hipStream_t s) { return split_grads(items, count, s); }
 

@@ -5,7 +5,9 @@
 // 1 -> 4 maps of 16^3, 3^3 kernels, all three passes 39 -> 32 us; 1 -> 40 maps of 26^3, kernel gradient 23 -> 9 us.
 #include <algorithm>
 #include <cmath>
+#include <vector>
 
+#include "bias_parts.h"
 #include "direct.h"
 
 namespace znn {
@@ -150,11 +152,10 @@ __device__ __forceinline__ float wave_sum(float v)
 }
 
 template <int U, int JB>
-__global__ void __launch_bounds__(256) k_grad_few(FewGrad P)
+__device__ __forceinline__ void grad_few(const FewGrad& P, long id, float* lds)
 {
     constexpr int kAtOnce = 4;
-    __shared__ float red[4][JB * U];
-    long id = blockIdx.x;
+    float (*const red)[JB * U] = reinterpret_cast<float (*)[JB * U]>(lds);      // of the four waves
     const int share = (int)(id % P.shares); id /= P.shares;
     const int cg = (int)(id % P.groups); id /= P.groups;
     const int ab = (int)(id % P.rows); id /= P.rows;
@@ -214,9 +215,60 @@ __global__ void __launch_bounds__(256) k_grad_few(FewGrad P)
     else P.partial[(((long)share * P.rows + ab) * P.fo + j) * ((long)P.f * P.k[2]) + (long)i * P.k[2] + c] = t;
 }
 
-using FewGradFn = void (*)(FewGrad);
+template <int U, int JB>
+__global__ void __launch_bounds__(256) k_grad_few(FewGrad P)
+{
+    __shared__ float lds[4 * JB * U];
+    grad_few<U, JB>(P, blockIdx.x, lds);
+}
 
-template <int U> FewGradFn pick_grad(int jb) { return jb == 4 ? k_grad_few<U, 4> : k_grad_few<U, 8>; }
+// maps of a block where the rows of eight would have too many accumulators
+constexpr bool four_only(int u) { return u >= 7; }
+
+// Several layers with groups of U taps, and the sums of biases behind them.
+constexpr int kFewItems = 8;
+struct FewGrads { FewGrad item[kFewItems]; unsigned first[kFewItems]; int jb[kFewItems]; int n; unsigned bias_first; BiasItem bias[kFewBiases]; int biases; };
+
+template <int U>
+__global__ void __launch_bounds__(256) k_grads_few(FewGrads A)
+{
+    __shared__ float lds[4 * (four_only(U) ? 4 : 8) * U];
+    if (blockIdx.x >= A.bias_first) {
+        const unsigned r = blockIdx.x - A.bias_first;
+        int q = 0;
+        while (q + 1 < A.biases && r >= A.bias[q + 1].first) ++q;       // uniform, as below
+        bias_part(A.bias[q], r - A.bias[q].first, lds);
+        return;
+    }
+    int q = 0;
+    while (q + 1 < A.n && blockIdx.x >= A.first[q + 1]) ++q;
+    const long id = blockIdx.x - A.first[q];
+    if constexpr (four_only(U)) grad_few<U, 4>(A.item[q], id, lds);
+    else if (A.jb[q] == 4) grad_few<U, 4>(A.item[q], id, lds);
+    else grad_few<U, 8>(A.item[q], id, lds);
+}
+
+using FewGradFn = void (*)(FewGrad);
+using FewGradsFn = void (*)(FewGrads);
+
+FewGradsFn pick_grads(int u)
+{
+    switch (u) {
+        case 2: return k_grads_few<2>;
+        case 3: return k_grads_few<3>;
+        case 4: return k_grads_few<4>;
+        case 5: return k_grads_few<5>;
+        case 7: return k_grads_few<7>;
+        case 11: return k_grads_few<11>;
+        default: return k_grads_few<1>;
+    }
+}
+
+template <int U> FewGradFn pick_grad(int jb)
+{
+    if constexpr (four_only(U)) return k_grad_few<U, 4>;
+    else return jb == 4 ? k_grad_few<U, 4> : k_grad_few<U, 8>;
+}
 
 FewGradFn pick_grad(int u, int jb)
 {
@@ -232,7 +284,7 @@ FewGradFn pick_grad(int u, int jb)
 }
 
 // rows of four maps where eight would leave most of them empty, or the accumulators be many
-int grad_maps(const Geom& g) { return g.fo <= 4 || group_width(g.kx) >= 7 ? 4 : 8; }
+int grad_maps(const Geom& g) { return g.fo <= 4 || four_only(group_width(g.kx)) ? 4 : 8; }
 
 long few_grad_groups(const Geom& g) { return (long)g.f * ((g.fo + grad_maps(g) - 1) / grad_maps(g)) * g.kz * g.ky * (g.kx / group_width(g.kx)); }
 
@@ -288,10 +340,10 @@ int few_conv(const Geom& g, bool backward, const float* src, const float* w, flo
     return check_launch(name);
 }
 
-// One share: into gw (partial NULL).  Otherwise shares of partial sums in the layout of WgradSum.
-int few_grad(const Geom& g, const float* in, const float* gout, float* partial, float* gw, WgradSum* sum, hipStream_t s)
+// One share: into gw (partial NULL).  Otherwise shares of partial sums in the layout of WgradSum.  The workgroups of a launch, 0: too many.
+static unsigned few_grad_of(const Geom& g, const float* in, const float* gout, float* partial, float* gw, FewGrad& P, WgradSum& S)
 {
-    FewGrad P = {};
+    P = FewGrad{};
     const int n[3] = {g.nz, g.ny, g.nx}, o[3] = {g.oz, g.oy, g.ox}, k[3] = {g.kz, g.ky, g.kx}, sp[3] = {g.spz, g.spy, g.spx};
     P.in = in; P.gout = gout; P.partial = partial; P.gw = gw;
     P.f = g.f; P.fo = g.fo;
@@ -302,17 +354,55 @@ int few_grad(const Geom& g, const float* in, const float* gout, float* partial, 
     P.shares = few_grad_shares(g);
     P.span = ((g.ovol() + P.shares - 1) / P.shares + 1023) / 1024 * 1024;
     P.shares = (int)((g.ovol() + P.span - 1) / P.span);
-    const long blocks = few_grad_groups(g) * P.shares;
-    if (blocks >= 2147483647L) return fail(ZNN_EUNSUPPORTED, "too many kernel taps for one launch");
-    ZNN_LAUNCH("direct kernel gradient (few maps)", s, pick_grad(U, JB), dim3((unsigned)blocks), dim3(256), 0, P);
-    WgradSum S = {};
+    S = WgradSum{};
     S.ksplit = P.shares; S.planes = P.rows; S.planes_b = g.ky; S.Mpad = g.fo; S.Npad = S.columns = g.f * g.kx;
     S.f = g.f; S.GA = S.GB = 1;
     for (int d = 0; d < 3; ++d) S.k[d] = k[d];
     S.slots = (long)g.fo * S.planes * S.columns;
     S.four = S.slots < 65536 && P.shares >= 16 ? 1 : 0;
-    *sum = S;
-    return check_launch("direct kernel gradient (few maps)");
+    const long blocks = few_grad_groups(g) * P.shares;
+    return blocks < 2147483647L ? (unsigned)blocks : 0;
+}
+
+static const char* const kFewName = "direct kernel gradient (few maps)";
+
+int few_grad(const Geom& g, const float* in, const float* gout, float* partial, float* gw, WgradSum* sum, hipStream_t s)
+{
+    FewGrad P;
+    const unsigned blocks = few_grad_of(g, in, gout, partial, gw, P, *sum);
+    if (!blocks) return fail(ZNN_EUNSUPPORTED, "too many kernel taps for one launch");
+    ZNN_LAUNCH(kFewName, s, pick_grad(group_width(g.kx), grad_maps(g)), dim3(blocks), dim3(256), 0, P);
+    return check_launch(kFewName);
+}
+
+int few_grads(const GradItem* items, int count, const BiasItem* bias, int biases, unsigned bias_groups, hipStream_t s)
+{
+    std::vector<char> done(count, 0);
+    for (int q0 = 0; q0 < count; ++q0) {
+        if (done[q0]) continue;
+        const int U = group_width(items[q0].g->kx);
+        FewGrads A = {};
+        unsigned blocks = 0;
+        for (int q = q0; q < count && A.n < kFewItems; ++q) {
+            const Geom& g = *items[q].g;
+            if (done[q] || group_width(g.kx) != U) continue;
+            const unsigned own = few_grad_of(g, items[q].in, items[q].gout, items[q].partial, nullptr, A.item[A.n], *items[q].sum);
+            if (!own) return fail(ZNN_EUNSUPPORTED, "too many kernel taps for one launch");
+            if (A.n && own > 2147483647u - kFewBiasGroups - blocks) break;      // the next launch's
+            A.jb[A.n] = grad_maps(g);
+            A.first[A.n++] = blocks;
+            blocks += own;
+            done[q] = 1;
+        }
+        A.bias_first = blocks;
+        if (q0 == 0) {
+            std::copy(bias, bias + biases, A.bias);
+            A.biases = biases;
+            blocks += bias_groups;
+        }
+        ZNN_LAUNCH(kFewName, s, pick_grads(U), dim3(blocks), dim3(256), 0, A);
+    }
+    return check_launch(kFewName);
 }
 
 }  // namespace znn

@@ -20,6 +20,7 @@
 #include <new>
 #include <vector>
 
+#include "bias_parts.h"
 #include "znn_internal.h"
 
 namespace znn {
@@ -95,31 +96,15 @@ __global__ void __launch_bounds__(256) k_node_sum(SumArgs A)
     A.out[t] = A.y ? derivative_times(A.fn, acc, A.y[t]) : acc;
 }
 
-// Sums of the gradients over the voxels of every map, one workgroup per map and kBiasSpan voxels of any of the layers.
-constexpr int kBiasSpan = 8192, kBiasItems = 64;
-struct BiasItem { const float* g; float* parts; long voxels; int spans; unsigned first; };
+// Sums of the gradients over the voxels of every map.
+constexpr int kBiasItems = 64;
 struct BiasArgs { BiasItem item[kBiasItems]; int n; };
 __global__ void __launch_bounds__(256) k_bias_parts(BiasArgs A)
 {
     __shared__ float red[4];
     int q = 0;
     while (q + 1 < A.n && blockIdx.x >= A.item[q + 1].first) ++q;       // uniform
-    const BiasItem& B = A.item[q];
-    const unsigned r = blockIdx.x - B.first;
-    const unsigned m = r / B.spans, span = r % B.spans;
-    const float* p = B.g + (long)m * B.voxels + (long)span * kBiasSpan;
-    const int n = (int)min((long)kBiasSpan, B.voxels - (long)span * kBiasSpan);
-    float a[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) a[i] = 0.f;
-    for (int t = threadIdx.x; t < n; t += 2048)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) a[i] += t + i * 256 < n ? p[t + i * 256] : 0.f;
-    float v = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-    for (int s = 32; s > 0; s >>= 1) v += __shfl_down(v, s);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) B.parts[r] = (red[0] + red[1]) + (red[2] + red[3]);
+    bias_part(A.item[q], blockIdx.x - A.item[q].first, red);
 }
 
 // Completes the gradients of a round and updates the parameters.  An item is the kernels or the biases of a layer:
@@ -174,15 +159,15 @@ __global__ void __launch_bounds__(256) k_update(UpdateArgs A)
     if (U.p) U.p[t] = U.p[t] - A.eta * acc;
 }
 
-// A step of the program: an operation of the caller, or one of four that the program adds.
-enum { STEP_PACK = -1, STEP_BIAS = -2, STEP_UPDATE = -3, STEP_GRADS = -4 };
+// A step of the program: an operation of the caller, or one of five that the program adds.
+enum { STEP_PACK = -1, STEP_BIAS = -2, STEP_UPDATE = -3, STEP_GRADS = -4, STEP_FEW = -5 };
 constexpr size_t kNone = (size_t)-1;
 
 struct Step {
     int kind;
     znn_op op;
     int stream;
-    bool skip;                          // no launch of its own: part of STEP_GRADS, STEP_BIAS or STEP_UPDATE
+    bool skip;                          // no launch of its own: part of STEP_GRADS, STEP_FEW, STEP_BIAS or STEP_UPDATE, or of the backward pass
     int layer;                          // convolutions: index into znn_program::layers
     size_t own;                         // place of the partial sums that STEP_UPDATE completes (kNone: it writes the gradient)
     size_t copies;                      // kernel gradients of STEP_GRADS: place of their copies
@@ -226,6 +211,7 @@ struct znn_program {
     std::vector<size_t> area;           // per stream: place of the scratch of its passes
     std::vector<int> bias_steps;        // deferred bias gradients
     std::vector<int> grad_steps;        // kernel gradients whose images are copied by one launch
+    std::vector<int> few_steps;         // kernel gradients on the vector ALUs that share a launch, with the bias gradients
     std::vector<int> update_steps;
     std::vector<int> completes;         // per update: the step whose sums it completes, or -1
 };
@@ -440,10 +426,16 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
     // images of all, if nothing writes their operands later; on several they run beside the passes.
     std::vector<int> joins;
     for (int i = 0; i < n && P.streams == 1; ++i) {
-        const Step& s = P.steps[i];
-        if (s.kind == ZNN_OP_CONV_WGRAD && s.own != kNone && last_write[s.op.buf[0]] < i && last_write[s.op.buf[1]] < i &&
-            grad_joins(P.layers[s.layer].plan.g))
-            joins.push_back(i);
+        Step& s = P.steps[i];
+        if (s.kind != ZNN_OP_CONV_WGRAD || s.own == kNone || last_write[s.op.buf[0]] >= i || last_write[s.op.buf[1]] >= i) continue;
+        const Geom& g = P.layers[s.layer].plan.g;
+        if (grad_joins(g)) joins.push_back(i);
+        // As one launch with the sums of the biases: a gradient of few or small maps leaves most of the chip idle.  Six-layer 3D net, three of 7, 21 and 9 us
+        // and 5 of the biases: a round 284 -> 268 us; 2D net 344 -> 332; sparse net, two of 7 and 19 us, 630 -> 618.
+        else if (grad_is_few(g)) {
+            s.skip = true;
+            P.few_steps.push_back(i);
+        }
     }
     for (int i : joins) {
         Step& s = P.steps[i];
@@ -452,8 +444,9 @@ int place_steps(znn_program& P, const znn_op* ops, int count)
         s.skip = true;
         P.grad_steps.push_back(i);
     }
+    add(STEP_FEW).skip = P.few_steps.empty();
     add(STEP_GRADS).skip = P.grad_steps.empty();
-    add(STEP_BIAS).skip = P.bias_steps.empty();
+    add(STEP_BIAS).skip = P.bias_steps.empty() || !P.few_steps.empty();
     add(STEP_UPDATE).skip = P.update_steps.empty();
     // scratch of the passes: one area per stream
     std::vector<size_t> need(P.streams, 0);
@@ -494,6 +487,9 @@ void name_resources(znn_program& P, int& resources)
             }
         } else if (s.kind == STEP_GRADS) {
             for (int q : P.grad_steps) { rd(P.steps[q].op.buf[0]); rd(P.steps[q].op.buf[1]); wr(own + q); }
+        } else if (s.kind == STEP_FEW) {
+            for (int q : P.few_steps) { rd(P.steps[q].op.buf[0]); rd(P.steps[q].op.buf[1]); wr(own + q); }
+            for (int q : P.bias_steps) { rd(P.steps[q].op.buf[0]); wr(own + q); }
         } else if (s.kind == STEP_BIAS) {
             for (int q : P.bias_steps) { rd(P.steps[q].op.buf[0]); wr(own + q); }
         } else if (s.kind == STEP_UPDATE) {
@@ -592,6 +588,11 @@ int run_pack(const znn_program& P, float* const* buf, char* scratch, hipStream_t
     return conv_pack_weights(items.data(), (int)items.size(), s);
 }
 
+BiasItem bias_item(const Step& b, float* const* buf, char* scratch, unsigned first)
+{
+    return BiasItem{buf[b.op.buf[0]], (float*)(scratch + b.own), voxels(b.op), bias_spans(b.op), first};
+}
+
 int run_bias(const znn_program& P, const std::vector<int>& steps, float* const* buf, char* scratch, hipStream_t s)
 {
     for (size_t i0 = 0; i0 < steps.size(); i0 += kBiasItems) {
@@ -599,7 +600,7 @@ int run_bias(const znn_program& P, const std::vector<int>& steps, float* const* 
         unsigned blocks = 0;
         for (; A.n < kBiasItems && i0 + A.n < steps.size(); ++A.n) {
             const Step& b = P.steps[steps[i0 + A.n]];
-            A.item[A.n] = BiasItem{buf[b.op.buf[0]], (float*)(scratch + b.own), voxels(b.op), bias_spans(b.op), blocks};
+            A.item[A.n] = bias_item(b, buf, scratch, blocks);
             blocks += (unsigned)bias_spans(b.op) * b.op.maps;
         }
         ZNN_LAUNCH("bias gradients", s, k_bias_parts, dim3(blocks), dim3(256), 0, A);
@@ -616,6 +617,29 @@ int run_grads(znn_program& P, float* const* buf, char* scratch, hipStream_t s)
                                  scratch + t.copies, &t.sum});
     }
     return grads_partial(items.data(), (int)items.size(), s);
+}
+
+int run_few(znn_program& P, float* const* buf, char* scratch, hipStream_t s)
+{
+    std::vector<GradItem> items;
+    std::vector<BiasItem> bias;
+    for (int q : P.few_steps) {
+        Step& t = P.steps[q];
+        items.push_back(GradItem{&P.layers[t.layer].plan.g, buf[t.op.buf[0]], buf[t.op.buf[1]], (float*)(scratch + t.own), nullptr, &t.sum});
+    }
+    size_t blocks = 0;
+    for (int q : P.bias_steps) {
+        bias.push_back(bias_item(P.steps[q], buf, scratch, (unsigned)blocks));
+        blocks += (size_t)bias.back().spans * P.steps[q].op.maps;
+    }
+    // more biases than go with the gradients, in a launch of their own
+    if (bias.size() > kFewBiases || blocks > kFewBiasGroups) {
+        const int rc = run_bias(P, P.bias_steps, buf, scratch, s);
+        if (rc != ZNN_OK) return rc;
+        bias.clear();
+        blocks = 0;
+    }
+    return few_grads(items.data(), (int)items.size(), bias.data(), (int)bias.size(), (unsigned)blocks, s);
 }
 
 int run_update(const znn_program& P, float* const* buf, char* scratch, float eta, hipStream_t s)
@@ -713,6 +737,7 @@ int run_step(znn_program& P, Step& t, float* const* buf, char* scratch, float et
     switch (t.kind) {
         case STEP_PACK: return run_pack(P, buf, scratch, s);
         case STEP_GRADS: return run_grads(P, buf, scratch, s);
+        case STEP_FEW: return run_few(P, buf, scratch, s);
         case STEP_BIAS: return run_bias(P, P.bias_steps, buf, scratch, s);
         case STEP_UPDATE: return run_update(P, buf, scratch, eta, s);
         case ZNN_OP_TRANSFER_FWD: return znn_transfer_fn_fwd(o.fn, o.maps, voxels(o), at(0), at(1), at(2), s);

@@ -124,6 +124,7 @@ int grad_partial(const Geom& g, const float* in, const float* gout, float* parti
 // The same for several layers that grad_joins takes, whose images are copied by one launch; no two have the same memory for sums or copies.
 struct GradItem { const Geom* g; const float* in; const float* gout; float* partial; void* copies; WgradSum* sum; };
 bool grad_joins(const Geom& g);
+bool grad_is_few(const Geom& g);         // on the vector ALUs
 int grads_partial(const GradItem* items, int count, hipStream_t s);
 // Element number t of (output map, tap group, column): where a share has it and where the gradient does.  false: a tap
 // behind the last one.

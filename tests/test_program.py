@@ -482,3 +482,23 @@ def test_rounds_whose_values_are_not_finite_are_those_of_the_calls(extent, value
         # sums of as many terms as the image has voxels, in another order
         a, b = (r[3][l + 1]["b"].cpu().numpy() for r in (program, calls))
         assert np.allclose(a, b, rtol=1e-4, atol=1e-4 * np.nanmax(np.abs(b[np.isfinite(b)]), initial=0), equal_nan=True), l
+
+
+def few_layers(count):
+    """Layers whose gradients run on the vector ALUs: blocks of four maps and of eight, rows of one to eleven taps, several shares of voxels."""
+    forms = [(1, 5, (20, 21, 22), (3, 3, 3)), (5, 3, (9, 14, 13), (2, 3, 3)), (1, 9, (1, 70, 66), (1, 11, 11)), (2, 4, (8, 9, 10), (2, 2, 5)),
+             (1, 2, (12, 13, 14), (3, 3, 1)), (1, 3, (1, 40, 41), (1, 4, 4)), (3, 1, (1, 30, 31), (1, 7, 7)), (2, 2, (5, 6, 7), (1, 2, 2))]
+    return [znn.Plan(*forms[l % len(forms)], "direct") for l in range(count)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("count,biases,rewrite", [(1, 1, ()), (2, 0, (1,)), (8, 8, ()), (8, 24, (3,)), (70, 3, ()), (3, 25, ())])
+def test_gradients_on_the_vector_alus_that_share_a_launch(count, biases, rewrite):
+    """One width of taps and several, more layers than a launch takes, more biases, and layers that stay behind."""
+    print("case", count, biases, rewrite, flush=True)
+    ops, shapes = gradients(few_layers(count), rewrite)
+    for b in range(biases):
+        dims, at = (1 + b % 3, 3, 40 + 13 * b, 31), len(shapes)
+        shapes += [dims, dims[:1], dims[:1]]
+        ops += [(zp.BIAS_GRAD, (at, at + 1), dict(maps=dims[0], n=dims[1:])), (zp.UPDATE, (at + 1, at + 2), dict(n=(1, 1, dims[0])))]
+    check(ops, shapes, 12)
