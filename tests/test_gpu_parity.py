@@ -470,6 +470,19 @@ def test_sparse_maxfilter_is_exact_and_its_jacobian_matches(n, win, s, kind):
     assert rel_err(gin, oracle.maxfilter3d_bwd(g, ref_idx, n, win, s)) <= 1e-6
 
 
+@pytest.mark.parametrize("row", range(1, 11))
+@pytest.mark.parametrize("z,s", [(1, (1, 1, 1)), (2, (1, 1, 1)), (2, (2, 3, 4)), (1, (1, 2, 5))])
+def test_maxfilter_rows_of_every_length_around_groups_of_four(row, z, s):
+    """Windows of z x 2 x 2: the last group of a row overlaps the one before, rows below four go voxel by voxel; NaN and infinities as a scan finds them."""
+    n = (s[0] * (z - 1) + 3, s[1] + 4, s[2] + row)
+    x = np.maximum(np.round(synth.uniform_pm1(19, 0, (3,) + n) * 3), 0).astype(np.float32)
+    x[0].flat[::5], x[1].flat[::7], x[2].flat[::11] = -0.0, np.inf, np.nan
+    ref_out, ref_idx = oracle.maxfilter3d_fwd(x, (z, 2, 2), s)
+    out, idx = znn.maxfilter3d_fwd(dev(x), (z, 2, 2), s)
+    assert np.array_equal(host(out).astype(np.float64), ref_out, equal_nan=True)
+    assert np.array_equal(host(idx), ref_idx)
+
+
 POOLS = [((4, 6, 8), (2, 2, 2)), ((6, 3, 4), (3, 1, 2)), ((1, 32, 27), (1, 4, 3)), ((2, 2, 2), (2, 2, 2)),
          ((3, 4, 5), (1, 1, 1)), ((24, 26, 22), (2, 2, 2))]
 
