@@ -64,3 +64,34 @@ def test_values_that_are_not_finite_reach_the_results_they_belong_to(value):
         assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(np.isposinf(a), np.isposinf(b))
         assert np.array_equal(np.isneginf(a), np.isneginf(b))
     p.close()
+
+
+@pytest.mark.parametrize("f,fo,n,k,s", [
+    (1, 41, (42, 60, 12), (3, 3, 3), (1, 1, 1)),            # rows of 10: the last group repeats two voxels
+    (1, 40, (66, 130, 6), (3, 3, 3), (1, 1, 1)),            # of 4, one group
+    (2, 33, (66, 70, 9), (1, 2, 5), (1, 3, 1)),             # of 5, one voxel beyond it
+    (1, 39, (50, 50, 17), (2, 2, 2), (3, 2, 10)),           # of 7, taps ten apart
+    (1, 3, (101, 203, 8), (2, 1, 1), (1, 1, 1)),            # blocks of four maps
+    (1, 40, (1, 310, 215), (1, 1, 11), (1, 1, 1)),
+    (3, 4, (90, 90, 20), (1, 1, 14), (1, 1, 1)),            # two groups of seven taps
+    (1, 40, (90, 130, 5), (1, 1, 3), (1, 1, 1)),            # rows of 3 go voxel by voxel
+])
+def test_forward_passes_of_four_voxels_a_thread(f, fo, n, k, s):
+    """Large passes, and a transfer function inside them."""
+    import torch
+    from paper_1510_06706_amd import program as zp
+    print("case", f, fo, n, k, s, flush=True)
+    x, w, _ = synth.layer_tensors(synth.LayerShape("t", f, fo, n, k, 1.0, 9700 + f, s))
+    p = znn.Plan(f, fo, n, k, "direct", s)
+    got = p.fwd(dev(x), dev(w))
+    ref, size = oracle.conv3d_fwd(x, w, s), oracle.conv3d_fwd(np.abs(x), np.abs(w), s)
+    assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= 2.0 ** -24 * (f * np.prod(k) + 1) * size)
+    bias, out, y = torch.linspace(-0.3, 0.3, fo, device="cuda:0"), torch.empty_like(got), torch.empty_like(got)
+    P = zp.Program("cuda:0", 1)
+    t = [dev(x), dev(w), out, bias, y]
+    for v in t:
+        P.buffer("given", v.shape)
+    P.add(zp.CONV_FWD, (0, 1, 2, 3, 4), plan=p)
+    P.build().run(dict(enumerate(t)))
+    assert torch.equal(out, got) and torch.equal(y, torch.relu(got + bias.view(-1, 1, 1, 1)))
+    p.close()
