@@ -67,9 +67,9 @@ class GraphNet:
     reused while another stream still reads it."""
 
     # Multiply-adds of a round's convolutions, times two, from which on several streams are the faster ones.  Multi-scale nets, us a round on several streams
-    # and on one: width 8, 20^3 432 and 185; 16, 40^3 (6e9) 459 and 327; 40, 32^3 (1.7e10) 517 and 517; 32, 40^3 (2.4e10) 538 and 535; 40, 36^3 (2.5e10) 541 and
-    # 577; 40, 40^3 (3.7e10) 690 and 712; 48, 48^3 (1e11) 1479 and 1572.
-    SEVERAL_STREAMS = 2e10
+    # and on one: width 8, 20^3 443 and 164; 16, 40^3 (6e9) 483 and 311; 32, 40^3 (2.4e10) 543 and 510; 40, 36^3 (2.5e10) 551 and 555; 36, 40^3 (3e10) 651
+    # and 651; 44, 40^3 (4.4e10) 757 and 761; 48, 40^3 (5.2e10) 766 and 793; 48, 48^3 (1e11) 1465 and 1519.
+    SEVERAL_STREAMS = 3e10
 
     def __init__(self, graph, params, mode="auto", device="cuda:0", streams=4):
         import torch
