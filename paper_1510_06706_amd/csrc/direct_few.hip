@@ -156,25 +156,86 @@ __global__ void __launch_bounds__(256) k_conv_few4(FewTile P)
     }
 }
 
+// The same of the backward pass with neighbouring taps along x: the four voxels' rows of U taps are U + 3 loads together, of zeros outside the source.
+// 40 -> 1 maps, 3^3 kernels: 38^3 15.9 -> 12.5 us, 64^3 46.7 -> 24.8; 40 -> 2, 90^3 203 -> 92; 24 -> 1, 50^3, 5^3 45.7 -> 34.1.
+template <int U, int JB>
+__global__ void __launch_bounds__(256) k_conv_back4(FewTile P)
+{
+    typedef float floatu4 __attribute__((ext_vector_type(4), aligned(4)));
+    const unsigned groups = (unsigned)(P.d[2] + 3) / 4, v = blockIdx.x * 256 + threadIdx.x;
+    const int m0 = blockIdx.y * JB;
+    if (v >= groups * P.d[1] * P.d[0]) return;
+    const unsigned r = v / groups;
+    const int x = min((int)(v - r * groups) * 4, P.d[2] - 4), z = (int)(r / (unsigned)P.d[1]), y = (int)(r - (unsigned)z * P.d[1]);
+    floatu4 acc[JB];
+#pragma unroll
+    for (int q = 0; q < JB; ++q) acc[q] = floatu4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < P.fK; ++i) {
+        const float* src = P.src + i * P.svol;
+        const float* w = P.w + i * P.wk;
+        for (int a = 0; a < P.k[0]; ++a) {
+            const int gz = z + a * P.sp[0] - P.p[0];
+            for (int b = 0; b < P.k[1]; ++b) {
+                const int gy = y + b * P.sp[1] - P.p[1];
+                const bool ok = gz >= 0 && gz < P.s[0] && gy >= 0 && gy < P.s[1];
+                const float* row = src + (ok ? ((long)gz * P.s[1] + gy) * P.s[2] : 0);
+                for (int c0 = 0; c0 < P.k[2]; c0 += U) {
+                    float s[U + 3];
+#pragma unroll
+                    for (int e = 0; e < U + 3; ++e) {
+                        const int gx = x + c0 + e - P.p[2];
+                        const bool in = ok && gx >= 0 && gx < P.s[2];
+                        const float t = row[in ? gx : 0];
+                        s[e] = in ? t : 0.f;
+                    }
+#pragma unroll
+                    for (int q = 0; q < JB; ++q) {
+                        const float* wr = w + min(m0 + q, P.fM - 1) * P.wm + (a * P.k[1] + b) * P.k[2] + c0;      // uniform
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[q][e] = fmaf(wr[u], s[u + e], acc[q][e]);
+                    }
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < JB; ++q) {
+        if (m0 + q >= P.fM) return;
+        const long at = (m0 + q) * P.dvol + (long)r * P.d[2] + x;
+        if (P.deriv) {                                      // uniform
+            const floatu4 d = *reinterpret_cast<const floatu4*>(P.deriv + at);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[q][e] = d[e] > 0.f ? acc[q][e] : 0.f;
+        }
+        *reinterpret_cast<floatu4*>(P.dst + at) = acc[q];
+    }
+}
+
 using FewFn = void (*)(FewTile);
 
-template <int U> FewFn pick_few4(int jb) { return jb == 4 ? k_conv_few4<U, 4> : k_conv_few4<U, 8>; }
+template <int U> FewFn pick_few4(int jb, bool backward)
+{
+    if (backward) return jb == 4 ? k_conv_back4<U, 4> : k_conv_back4<U, 8>;
+    return jb == 4 ? k_conv_few4<U, 4> : k_conv_few4<U, 8>;
+}
 
-FewFn pick_few4(int u, int jb)
+FewFn pick_few4(int u, int jb, bool backward)
 {
     switch (u) {
-        case 2: return pick_few4<2>(jb);
-        case 3: return pick_few4<3>(jb);
-        case 4: return pick_few4<4>(jb);
-        case 5: return pick_few4<5>(jb);
-        case 7: return pick_few4<7>(jb);
-        case 11: return pick_few4<11>(jb);
-        default: return pick_few4<1>(jb);
+        case 2: return pick_few4<2>(jb, backward);
+        case 3: return pick_few4<3>(jb, backward);
+        case 4: return pick_few4<4>(jb, backward);
+        case 5: return pick_few4<5>(jb, backward);
+        case 7: return pick_few4<7>(jb, backward);
+        case 11: return pick_few4<11>(jb, backward);
+        default: return pick_few4<1>(jb, backward);
     }
 }
 
 // Workgroups from which that is the faster way, measured at 45 to 3330: 3^3 kernels 70 of them 7.7 -> 7.3 us, 160 9.7 -> 7.8; rows of eleven taps 115 14.8 -> 18.6, 180 18.7
-// -> 18.8.
+// -> 18.8.  Backward: 3^3 kernels 70 8.7 -> 9.2, 160 12.3 -> 12.2; rows of eleven taps 100 19.0 -> 19.3.
 constexpr long kFourGroups = 160;
 
 template <int U> FewFn pick_few(int jb, bool backward)
@@ -410,8 +471,10 @@ int few_conv(const Geom& g, bool backward, const float* src, const float* w, flo
     if (blocks >= 2147483647L || groups > 65535) return fail(ZNN_EUNSUPPORTED, "too many voxels or maps for one launch");
     const char* name = backward ? "direct backward (few maps)" : "direct forward (few maps)";
     const long blocks4 = ((long)P.d[0] * P.d[1] * ((P.d[2] + 3) / 4) + 255) / 256;
-    if (!backward && P.d[2] >= 4 && P.dvol < 2147483648L && blocks4 * groups >= kFourGroups)
-        ZNN_LAUNCH(name, s, pick_few4(group_width(g.kx), jb), dim3((unsigned)blocks4, (unsigned)groups), dim3(256), 0, P);
+    // voxels that two threads take: not where the derivative is read from what is written
+    const bool four = !backward || (P.sp[2] == 1 && P.deriv != P.dst);
+    if (four && P.d[2] >= 4 && P.dvol < 2147483648L && blocks4 * groups >= kFourGroups)
+        ZNN_LAUNCH(name, s, pick_few4(group_width(g.kx), jb, backward), dim3((unsigned)blocks4, (unsigned)groups), dim3(256), 0, P);
     else
         ZNN_LAUNCH(name, s, pick_few(group_width(g.kx), jb, backward), dim3((unsigned)blocks, (unsigned)groups), dim3(256), 0, P);
     return check_launch(name);

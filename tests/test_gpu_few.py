@@ -95,3 +95,36 @@ def test_forward_passes_of_four_voxels_a_thread(f, fo, n, k, s):
     P.build().run(dict(enumerate(t)))
     assert torch.equal(out, got) and torch.equal(y, torch.relu(got + bias.view(-1, 1, 1, 1)))
     p.close()
+
+
+@pytest.mark.parametrize("f,fo,n,k,s", [
+    (41, 1, (42, 60, 10), (3, 3, 3), (1, 1, 1)),            # rows of 10: the last group repeats two voxels
+    (40, 1, (66, 130, 4), (3, 3, 3), (1, 1, 1)),            # of 4, one group
+    (33, 2, (66, 70, 5), (1, 2, 5), (1, 3, 1)),             # of 5, kernels as wide
+    (39, 1, (50, 50, 17), (2, 2, 1), (3, 2, 1)),            # one tap a row
+    (3, 1, (101, 203, 8), (2, 1, 4), (1, 1, 1)),            # blocks of four maps
+    (40, 1, (1, 310, 215), (1, 1, 11), (1, 1, 1)),
+    (4, 3, (90, 90, 20), (1, 1, 14), (1, 1, 1)),            # two groups of seven taps
+    (40, 1, (50, 50, 17), (2, 2, 2), (1, 1, 3)),            # spaced taps go voxel by voxel
+])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_backward_passes_of_four_voxels_a_thread(f, fo, n, k, s, in_place):
+    """Large passes, alone and times the derivative of a rectifier whose result they may replace."""
+    import torch
+    from paper_1510_06706_amd import program as zp
+    print("case", f, fo, n, k, s, in_place, flush=True)
+    x, w, g = synth.layer_tensors(synth.LayerShape("t", f, fo, n, k, 1.0, 9800 + f, s))
+    p = znn.Plan(f, fo, n, k, "direct", s)
+    got = p.bwd(dev(g), dev(w))
+    ref, size = oracle.conv3d_bwd(g, w, n, s), oracle.conv3d_bwd(np.abs(g), np.abs(w), n, s)
+    assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= 2.0 ** -24 * (fo * np.prod(k) + 1) * size)
+    below = torch.relu(dev(x))
+    want = torch.where(below > 0, got, torch.zeros_like(got))
+    P = zp.Program("cuda:0", 1)
+    t = [dev(g), dev(w), below if in_place else torch.empty_like(got), below]
+    for v in t:
+        P.buffer("given", v.shape)
+    P.add(zp.CONV_BWD, (0, 1, 2, 3), plan=p)
+    P.build().run(dict(enumerate(t)))
+    assert torch.equal(t[2], want)
+    p.close()
