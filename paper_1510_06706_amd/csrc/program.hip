@@ -12,9 +12,10 @@
 //     map and 8192 voxels; one workgroup per map took 76 us on the sparse net), and in the last launch completes
 //     the sums of all kernel and bias gradients and updates all parameters (k_update);
 //   * keeps the spectra of a layer on the FFT method from the forward to the backward pass and the gradient;
-//   * on one stream, copies the images of the kernel gradients of small layers by one launch at the end.
-// Six-layer 3D net on a 12^3 patch: 78 -> 34 launches, 617 -> 413 us on the fp32 direct kernels, 291 us on those on split operands: chains
-// of kernels of 4 to 17 us (direct passes 144 us, gradients with their copies and sums 100 us, the rest 2 to 9 us each).
+//   * on one stream, copies the images of the kernel gradients of small layers by one launch at the end, takes the gradients on the vector
+//     ALUs and the biases' sums by another, and those of small FFT layers by the launches of their backward passes.
+// Six-layer 3D net on a 12^3 patch: 78 -> 31 launches, 617 -> 413 us on the fp32 direct kernels, 268 us on those on split operands: chains
+// of kernels of 4 to 26 us (direct passes 144 us, gradients with their copies and sums 85 us, the rest 2 to 9 us each).
 #include <algorithm>
 #include <cstring>
 #include <new>
