@@ -355,7 +355,7 @@ int  znn_autotune_round(const znn_conv_desc* desc, uint64_t memory_budget, void*
  * several layers may be the same memory if their UPDATEs stand behind everything that reads it: they take effect in order.
  *
  * Buffers by position (-1 = absent, only where marked ?):
- *   CONV_FWD       in, w, out, ?bias, ?y      y = fn(out + bias)
+ *   CONV_FWD       in, w, out, ?bias, ?y      y = fn(out + bias); one buffer for out and y ends as y
  *   CONV_BWD       gout, w, gin, ?y           gin times fn'(y)
  *   CONV_WGRAD     in, gout, gw
  *   TRANSFER_FWD   x, bias, y                 TRANSFER_BWD   gy, y, gx                BIAS_GRAD  g, gb

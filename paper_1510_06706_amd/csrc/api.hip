@@ -269,7 +269,7 @@ int plan_pass(const znn_plan* p, int pass, const float* a, const float* b, float
     const Geom& g = p->g;
     const KernelSpectra K = {resident ? nullptr : b, resident, more ? more->made : nullptr};
     Finish finish = {};
-    if (more && p->mode == ZNN_FFT && p->tile.on && more->finish.fn == ZNN_RECTIFY) {
+    if (more && (more->finish.y || more->finish.deriv) && p->mode == ZNN_FFT && p->tile.on && more->finish.fn == ZNN_RECTIFY) {
         finish = more->finish;
         more->finished = true;
     }

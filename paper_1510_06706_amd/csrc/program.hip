@@ -695,19 +695,21 @@ int run_conv(znn_program& P, Step& t, float* const* buf, char* scratch, hipStrea
     if (bwd) F.deriv = at(3); else { F.bias = at(3); F.y = at(4); }
     F.fn = o.fn;
     bool finished = !F.y && !F.deriv;
+    // One buffer for out and y: a pass may write them in any order and reads its sums again where they are not finite, so y follows behind it.
+    const Finish here = F.y == at(2) ? Finish{} : F;
     int rc;
     const bool few = L.plan.mode == ZNN_DIRECT && !conv_takes_packed(g, bwd);
     if (few || L.packed[bwd] != kNone) {
         const int splits = conv_splits(g, bwd);
-        const bool inside = !finished && splits == 1 && o.fn == ZNN_RECTIFY;
-        rc = conv_pass(g, bwd, at(0), at(1), few ? nullptr : scratch + L.packed[bwd], at(2), (float*)area, inside ? F : Finish{}, s);
+        const bool inside = (here.y || here.deriv) && splits == 1 && o.fn == ZNN_RECTIFY;
+        rc = conv_pass(g, bwd, at(0), at(1), few ? nullptr : scratch + L.packed[bwd], at(2), (float*)area, inside ? here : Finish{}, s);
         if (rc != ZNN_OK) return rc;
         if (splits > 1) {
             if (F.deriv) {
                 ZNN_LAUNCH("sum of shares, derivative", s, k_finish_bwd, dim3(blocks_of(count)), dim3(256), 0, (const float*)area, F.deriv, at(2),
                            count, splits, o.fn);
                 finished = true;
-            } else if (F.y && g.fo <= 65535) {
+            } else if (here.y && g.fo <= 65535) {
                 ZNN_LAUNCH("sum of shares, transfer", s, k_finish_fwd, dim3(blocks_of(g.ovol()), (unsigned)g.fo), dim3(256), 0,
                            (const float*)area, at(2), F.bias, F.y, (int)g.ovol(), count, splits, o.fn);
                 finished = true;
@@ -718,7 +720,7 @@ int run_conv(znn_program& P, Step& t, float* const* buf, char* scratch, hipStrea
         float2* What = L.spectra != kNone ? (float2*)(scratch + L.spectra) : nullptr;
         float2* memo = L.memo != kNone ? (float2*)(scratch + L.memo) : nullptr;
         const bool held = What && !transforms_kernels(L, t.kind);
-        PassMore more = {What, bwd && L.joined ? buf[P.steps[L.step[2]].op.buf[2]] : nullptr, F, false};
+        PassMore more = {What, bwd && L.joined ? buf[P.steps[L.step[2]].op.buf[2]] : nullptr, here, false};
         rc = plan_pass(&L.plan, t.kind, at(0), held ? nullptr : at(1), at(2), held ? What : nullptr, area, memo, s, &more);
         if (rc != ZNN_OK) return rc;
         finished = finished || more.finished;

@@ -268,6 +268,33 @@ def test_operands_of_a_layer_written_between_its_passes(order, buffer):
         check(ops[:at] + [write] + ops[at:], shapes + [shape, (maps,)], 2 + at)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode,f,fo,n,k", [
+    ("fft", 5, 7, (1, 20, 22), (1, 5, 5)), ("fft", 17, 6, (9, 40, 37), (2, 4, 4)),             # one tile and many
+    ("fft whole", 4, 5, (14, 12, 15), (3, 2, 3)),
+    ("direct", 1, 5, (9, 10, 11), (3, 3, 3)), ("direct", 1, 40, (42, 60, 12), (3, 3, 3)),      # vector ALUs, one and four voxels a thread
+    ("direct", 40, 20, (9, 10, 11), (3, 3, 3)), ("direct", 20, 40, (30, 31, 33), (2, 2, 2)),   # matrix cores, in shares and at once
+])
+@pytest.mark.parametrize("fn", ["rectify", "tanh"])
+def test_a_transfer_function_may_replace_the_sums_it_is_of(mode, f, fo, n, k, fn):
+    """`out` and `y` one buffer: it ends as y, also where sums are not finite."""
+    import torch
+    print("case", mode, f, fo, n, k, fn, flush=True)
+    plan = znn.Plan(f, fo, n, k, mode.split()[0])
+    if mode == "fft whole":
+        plan.set_spectra_layout("full")
+    assert (plan.tiles is not None) == (mode == "fft")
+    shapes = conv_shapes(plan)[:3] + [(fo,)]
+    ops = [(zp.CONV_FWD, (0, 1, 2, 3, 2), dict(plan=plan, fn=fn))]
+    check(ops, shapes, 23)
+    x, w, out, b = (torch.linspace(-1, 1, int(np.prod(s)), device="cuda:0").view(s) for s in shapes)
+    if mode == "direct":
+        x[0, 0, :2], w[0] = float("inf"), -w[0].abs() - 0.1
+    program(ops, shapes).run(dict(enumerate([x, w, out, b])), 0.0, [])
+    want = znn.transfer_fwd(plan.fwd(x, w), b, fn)
+    assert np.allclose(out.cpu().numpy(), want.cpu().numpy(), rtol=2e-5, atol=2e-5 * float(want[want.isfinite()].abs().max()), equal_nan=True)
+
+
 def joined_lists(plan):
     """A layer's round, whole and with its gradient's buffer used between the backward pass and the gradient, or by the pass itself."""
     F, B, W = conv_ops(plan, "FBW")
