@@ -996,13 +996,17 @@ void finish_geom(TileGeom& G, long entries, bool inverse, int* threads, size_t* 
     // would do for four: workgroups of four waves, or of two where no phase but the last has more rows and columns, if a unit gets three of them.
     // 40 maps of 64^3, 1800 tiles: 5 waves 40.9 / 41.4 / 39.7 us (inverse, images, gradients), 4 waves 37.5 / 39.0 / 34.6, 3 waves 40.0 / 41.5 / 35.3; kernels 5, 4, 2
     // waves 26.8, 23.3, 19.5.  Fewer workgroups leave the unit to one or two of them, and these take all the waves the column passes fill (108
-    // workgroups 9.0 us, by two waves 14.8), as do tiles that fill half of its LDS (24^3: 349 us, by four waves 470).
+    // workgroups 9.0 us, by two waves 14.8), as do tiles that fill half of its LDS (24^3: 349 us, by four waves 470).  Inverses with columns of 32 have registers for
+    // twelve waves on a unit: two waves where it gets more than three workgroups, four where LDS or their number leaves it three.  2, 4 waves: three of them, 102 maps in tiles
+    // of 32 x 20 x 20 115 / 91 us (14 maps 56 / 39), 102 of 16 x 32 15.4 / 12.2; four, 62 maps of 32^2 20.8 / 23.6; six and more, 90 maps of 12 x 32 x 16 84 / 104.
     const int rows = nb * G.w[0] * std::max(G.w[1], G.Mxh);         // or columns along y
     const long fit = std::min((long)(kUnitLds / (nb * one + kTileStatic)), (entries + nb * 256 - 1) / (nb * 256));
-    if (fit >= 3)
-        *threads = rows <= 128 || (inverse && has_long(G)) ? 128 : 256;
-    else
+    if (fit < 3)
         *threads = std::min(kTileThreads, std::max(128, (nb * cols + 63) / 64 * 64));
+    else if (rows <= 128)
+        *threads = 128;
+    else
+        *threads = inverse && has_long(G) && fit > 3 ? 128 : 256;
     if (given) *threads = given;
     *lds = nb * one;
     G.rows_per_step = *threads / (G.w[2] / G.vw);

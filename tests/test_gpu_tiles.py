@@ -116,3 +116,21 @@ def test_transfer_functions_inside_the_passes_give_the_bits_of_their_own(f, fo, 
     assert torch.equal(out, ref) and torch.equal(y, torch.relu(ref + bias.view(-1, 1, 1, 1)))
     assert torch.equal(gin, torch.where(below > 0, back, torch.zeros_like(back)))
     p.close()
+
+
+# inverse transforms with columns of 32 by workgroups of two and of four waves, of one tile and of seven
+@pytest.mark.parametrize("f,fo,n,k", [(1, 87, (41, 41, 29), (2, 3, 2)), (3, 87, (32, 23, 17), (4, 4, 4)), (6, 79, (1, 194, 179), (1, 11, 11)),
+                                      (1, 36, (47, 17, 31), (4, 4, 4)), (1, 82, (1, 172, 136), (1, 11, 11))])
+def test_inverse_transforms_of_long_columns_match_the_direct_method(f, fo, n, k):
+    print("case", f, fo, n, k, flush=True)
+    for f, fo in ((f, fo), (fo, f)):
+        x, w, g = (dev(v) for v in synth.layer_tensors(synth.LayerShape("t", f, fo, n, k, 1.0, 9900 + f, (1, 1, 1))))
+        p, q = znn.Plan(f, fo, n, k, "fft"), znn.Plan(f, fo, n, k, "direct")
+        assert 32 in p.tiles[0]
+        for name, a, b, terms in (("fwd", x, w, f), ("bwd", g, w, fo)):
+            got, ref = getattr(p, name)(a, b).double(), getattr(q, name)(a, b).double()
+            size = getattr(q, name)(a.abs(), b.abs()).double().norm()
+            # the direct method sums at most a few thousand products in chains no longer than 512
+            assert (got - ref).norm() <= 2.0 ** -24 * (6 * np.log2(np.prod(p.tiles[0])) + terms + 512) * size, name
+        p.close()
+        q.close()
