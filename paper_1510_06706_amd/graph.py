@@ -64,14 +64,19 @@ class GraphNet:
     earlier pass, and join their side streams only through the events of later edges: they run eagerly
     only.  Every tensor of a pass stays referenced until the pass has joined the calling stream, and the
     next pass starts from events recorded after that join, so memory handed back to the allocator is never
-    reused while another stream still reads it."""
+    reused while another stream still reads it.
 
-    # Multiply-adds of a round's convolutions, times two, from which on several streams are the faster ones.  Multi-scale nets, us a round on several streams
-    # and on one: width 8, 20^3 443 and 164; 16, 40^3 (6e9) 483 and 311; 32, 40^3 (2.4e10) 543 and 510; 40, 36^3 (2.5e10) 551 and 555; 36, 40^3 (3e10) 651
-    # and 651; 44, 40^3 (4.4e10) 757 and 761; 48, 40^3 (5.2e10) 766 and 793; 48, 48^3 (1e11) 1465 and 1519.
+    ``streams`` is the number of side streams.  None stands for four, of which a round uses all or, where it is
+    small, none; a number is kept to by every round."""
+
+    # Multiply-adds of a round's convolutions by the direct method, times two, from which on several streams may be the faster ones.  Multi-scale nets, us a round
+    # on several streams and on one: width 8, 20^3 443 and 164; 16, 40^3 (6e9) 483 and 311; 32, 40^3 (2.4e10) 543 and 510; 40, 36^3 (2.5e10) 551 and 555;
+    # 36, 40^3 (3e10) 651 and 651; 44, 40^3 (4.4e10) 757 and 761; 48, 40^3 (5.2e10) 766 and 793; 48, 48^3 (1e11) 1465 and 1519; all by the FFT method 24, 48^3
+    # (2.5e10) 810 and 786; 40, 40^3 (3.6e10) 818 and 861.  Independent branches that never meet gain less by streams, as each edge brings its waits:
+    # two to eight, two to four layers deep, 2D and 3D, either method (1e8 to 5.5e10), one took 0.35 to 0.98 of the time of several.
     SEVERAL_STREAMS = 3e10
 
-    def __init__(self, graph, params, mode="auto", device="cuda:0", streams=4):
+    def __init__(self, graph, params, mode="auto", device="cuda:0", streams=None):
         import torch
         self.graph = graph
         self.device = device
@@ -79,7 +84,8 @@ class GraphNet:
         self.edges = edge_order(graph)
         self.params = {n: {k: torch.from_numpy(np.ascontiguousarray(v)).to(device) for k, v in p.items()}
                        for n, p in params.items()}
-        self.streams = [torch.cuda.Stream(device=device) for _ in range(max(1, int(streams)))]
+        self.streams = [torch.cuda.Stream(device=device) for _ in range(4 if streams is None else max(1, int(streams)))]
+        self._given_streams = streams is not None
         self._programs = {}
         self._events, self._next_event = [], 0      # events are reused from round to round
         self.incoming, self.outgoing = {}, {}
@@ -219,6 +225,8 @@ class GraphNet:
     # ------------------------------------------------------------ rounds as one native call
     def _side_streams(self):
         """The streams of a round.  Its waits between streams take 5 to 12 us each, which only long edges pay for."""
+        if self._given_streams:
+            return self.streams
         flops = sum(6.0 * self.shapes[e[2]][0] * e[4] * math.prod(self.shapes[e[3]][1:]) * math.prod(e[5])
                     for e in self.edges if e[0] == "conv")
         return self.streams if flops >= self.SEVERAL_STREAMS else []

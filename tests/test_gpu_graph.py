@@ -43,6 +43,7 @@ def test_multiscale_graph_round_matches_the_reference(mode):
         img, aux, gout, grads = net.train_round({n: dev(v) for n, v in inputs.items()},
                                                 {n: dev(v) for n, v in targets.items()}, 0.05, "cross_entropy")
         torch.cuda.synchronize()
+        assert net._programs["cross_entropy"][0].streams == 1 + streams
         for n in r_img:
             assert rel_err(host(img[n]), r_img[n]) <= TOL[mode], ("image", n)
         assert np.array_equal(host(aux["m0"]), r_aux["m0"])
@@ -58,16 +59,17 @@ def test_multiscale_graph_round_matches_the_reference(mode):
 
 @pytest.mark.parametrize("mode", ["direct", "fft"])
 def test_rounds_on_one_and_on_several_streams_are_the_same_bits(mode, monkeypatch):
-    """On either side of the size that chooses between them."""
+    """On either side of the size that chooses between them, and where the caller does."""
     g = synth.multiscale_graph()
     inputs, targets, params = synth.graph_tensors(g, 52)
     results = []
-    for least, streams in ((0.0, 4), (0.0, 1), (1e30, 4)):
+    for least, streams, used in ((0.0, None, 5), (1e30, None, 1), (1e30, 4, 5), (0.0, 1, 2), (1e30, 3, 4)):
         monkeypatch.setattr(zgraph.GraphNet, "SEVERAL_STREAMS", least)
         net = zgraph.GraphNet(g, params, mode, streams=streams)
         for _ in range(2):
             img, _, _, grads = net.train_round({n: dev(v) for n, v in inputs.items()}, {n: dev(v) for n, v in targets.items()},
                                                1e-5, "cross_entropy")
+        assert net._programs["cross_entropy"][0].streams == used
         results.append({(n, k): host(v) for d in ({n: {"x": v} for n, v in img.items()}, grads, net.params)
                         for n, gr in d.items() for k, v in gr.items()})
     for r in results[1:]:
@@ -212,12 +214,13 @@ def wide_graph():
 
 @pytest.mark.parametrize("mode", ["direct", "fft"])
 @pytest.mark.parametrize("form", ["multiscale", "wide"])
-def test_round_of_a_graph_as_one_program_matches_the_calls_per_edge(form, mode):
+@pytest.mark.parametrize("streams", [None, 4])
+def test_round_of_a_graph_as_one_program_matches_the_calls_per_edge(form, mode, streams):
     """`forward` and `backward` run the same edges one library call each."""
     import torch
     g = synth.multiscale_graph() if form == "multiscale" else wide_graph()
     inputs, targets, params = synth.graph_tensors(g, 81)
-    one, by_edge = zgraph.GraphNet(g, params, mode), zgraph.GraphNet(g, params, mode)
+    one, by_edge = zgraph.GraphNet(g, params, mode, streams=streams), zgraph.GraphNet(g, params, mode)
     # the second round's images inherit the first's gradients, which agree to 2e-5, through a step of at most about a
     # hundredth of the weights: 2e-7 of them
     eta = 0.01 / max(v.size for v in targets.values())
@@ -231,6 +234,7 @@ def test_round_of_a_graph_as_one_program_matches_the_calls_per_edge(form, mode):
             for k, v in d.items():
                 znn.sgd_update(by_edge.params[n][k], v, eta)
         torch.cuda.synchronize()
+        assert one._programs["square"][0].streams == (5 if streams else 1)
         assert set(got[0]) == set(img) and set(got[3]) == set(grads)
         near = lambda a, b, tol: rel_err(host(a), host(b)) <= tol  # noqa: E731
         for n in img:
@@ -279,9 +283,10 @@ def test_rounds_hold_no_memory_between_them(monkeypatch):
     def rounds():
         res, kept = [], []
         for mode in ("direct", "fft"):
-            net, gnet = znet.Net(layers, in_shape, params, mode), zgraph.GraphNet(g, gparams, mode)
-            for run in (lambda: net.train_round(x, target, 0.05)[3],  # noqa: B023
-                        lambda: gnet.train_round(inputs, targets, 0.05)[3], lambda: net.forward(x)[0][1:]):  # noqa: B023
+            net = znet.Net(layers, in_shape, params, mode)
+            gnet, gone = (zgraph.GraphNet(g, gparams, mode, streams=n) for n in (4, None))
+            for run in (lambda: net.train_round(x, target, 0.05)[3], lambda: gnet.train_round(inputs, targets, 0.05)[3],  # noqa: B023
+                        lambda: gone.train_round(inputs, targets, 0.05)[3], lambda: net.forward(x)[0][1:]):  # noqa: B023
                 torch.cuda.synchronize()
                 before = torch.cuda.memory_allocated()
                 out = run()
@@ -290,7 +295,8 @@ def test_rounds_hold_no_memory_between_them(monkeypatch):
                 res += [host(v) for r in rows if r is not None for v in (r.values() if isinstance(r, dict) else [r])]
                 del out, rows
                 assert torch.cuda.memory_allocated() <= before
-            kept += [net._program("square")[0]._kept_bytes, gnet._programs["square"][0]._kept_bytes]
+            kept += [net._program("square")[0]._kept_bytes] + [n._programs["square"][0]._kept_bytes for n in (gnet, gone)]
+            assert [n._programs["square"][0].streams for n in (gnet, gone)] == [5, 1]
         return res, kept
 
     want, most = rounds()
