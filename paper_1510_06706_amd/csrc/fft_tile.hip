@@ -1412,7 +1412,7 @@ int tile_bwd(const Geom& g, const Tiling& L, const float* gout, const KernelSpec
     const TileResult R = {G, (long)g.f * L.tiles, result, one ? gin : tiles, inv_volume(L), 1, 0, one ? finish : Finish{}};
     if (grad.gw) {
         const TileProduct Q = gradient_product(g, L, grad.U, V, (float2*)((char*)result + tile_node_bytes(g, L, g.f)));
-        rc = products("spectral products backward and of the kernel gradient (tiles)", P, Q, s);
+        rc = products("spectral products backward and of gradient (tiles)", P, Q, s);
         if (rc == ZNN_OK)
             rc = inverse_tiles("inverse fft of gradient tiles and kernel gradients", R, gradient_result(g, L, Q, grad.gw), s);
     } else {

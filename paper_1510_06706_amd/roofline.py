@@ -83,6 +83,8 @@ TILE_STEPS = {
     "spectral products of the kernel gradient (tiles)": "F-wgrad products",
     "inverse fft of image tiles": "F-inv", "inverse fft of gradient tiles": "F-inv",
     "sum of overlapping tiles": "F-add", "inverse fft of kernel gradients (tiles)": "F-wgrad inverse",
+    "spectral products backward and of gradient (tiles)": "F-mac and F-wgrad products",
+    "inverse fft of gradient tiles and kernel gradients": "F-inv and F-wgrad inverse",
 }
 
 
@@ -135,6 +137,8 @@ def work_of_tiles(cfg, tiles, what: str):
     w["F-img and F-ker"] = ("hbm", w["F-img"][1] + w["F-ker"][1])
     w["F-inv"] = ("hbm", fo * (4.0 * no + node) if what == "fwd" else f * ((4.0 * tvol * nt if nt > 1 else 4.0 * n) + node))
     w["F-add"] = ("hbm", 4.0 * f * (tvol * nt + n))
+    for a, b in (("F-mac", "F-wgrad products"), ("F-inv", "F-wgrad inverse")):     # launches of a round that do both
+        w[a + " and " + b] = (w[a][0], w[a][1] + w[b][1])
     return w
 
 

@@ -2,6 +2,7 @@
 closed forms of Table 2 and of the kernels' own operation counts, launches are grouped into the right
 steps, and the committed traffic profile parses."""
 import os
+import re
 
 from paper_1510_06706_amd import roofline as rl
 from paper_1510_06706_amd import synth
@@ -54,6 +55,22 @@ def test_launches_are_grouped_into_steps_and_priced():
     assert rl.step_of("fft c2r x (registers)", "wgrad_memo") == "F-wgrad x"
     assert rl.step_of("direct kernel gradient (MFMA)", "wgrad") == "D-wgrad"
     assert rl.step_of("fft r2c x", "kernel_spectra") == "F-ker"
+
+
+def test_launches_of_the_tiles_have_names_that_a_trace_holds_and_a_step():
+    csrc = os.path.join(ROOT, "paper_1510_06706_amd", "csrc")
+    text = {n: open(os.path.join(csrc, n)).read() for n in os.listdir(csrc)}
+    names = re.findall(r'"((?:fft of|inverse fft of|spectral products|sum of overlapping)[^"]*)"', text["fft_tile.hip"])
+    assert len(set(names)) >= 15
+    for n in names:
+        assert n in rl.TILE_STEPS, n
+    for n in names + re.findall(r'ZNN_LAUNCH\("([^"]*)"', "".join(text.values())):
+        assert len(n) < 56, n
+    # a joined launch has the work of the two
+    w = rl.work_of(synth.CONFIG4, (1, 256, 256), "folded", "bwd", ((1, 32, 32), (1, 12, 12)))
+    for step in set(rl.TILE_STEPS.values()):
+        a, _, b = step.partition(" and ")
+        assert not b or w[step] == (w[a][0], w[a][1] + w[b][1]) and w[a][0] == w[b][0], step
 
 
 def test_committed_traffic_profile_parses():
