@@ -234,8 +234,9 @@ FewFn pick_few4(int u, int jb, bool backward)
     }
 }
 
-// Workgroups from which that is the faster way, measured at 45 to 3330: 3^3 kernels 70 of them 7.7 -> 7.3 us, 160 9.7 -> 7.8; rows of eleven taps 115 14.8 -> 18.6, 180 18.7
-// -> 18.8.  Backward: 3^3 kernels 70 8.7 -> 9.2, 160 12.3 -> 12.2; rows of eleven taps 100 19.0 -> 19.3.
+// Workgroups from which that is the faster way, measured at 45 to 3330: 3^3 kernels 70 of them 7.7 -> 7.3 us, 160 9.7 -> 7.8; rows of eleven taps 115 14.8 -> 18.6, 160 18.5
+// -> 18.4, 200 21.8 -> 18.9, 285 25.4 -> 25.9 (a second workgroup on a few units), 440 32.9 -> 26.8, 865 57.4 -> 42.9; of seven 160 10.8 -> 9.8, 285 14.7 -> 13.8.  Backward: 3^3 kernels
+// 70 8.7 -> 9.2, 160 12.3 -> 12.2; rows of eleven taps 100 19.0 -> 19.3, 160 23.6 -> 19.9, 285 32.8 -> 28.3.
 constexpr long kFourGroups = 160;
 
 template <int U> FewFn pick_few(int jb, bool backward)
@@ -434,7 +435,8 @@ int few_grad_shares(const Geom& g)
 }
 
 // Expected seconds, from 130 layers of 1 to 40 maps and 14^3 to 64^3 voxels: the rows of taps follow each other at the latency of
-// their weights (0.3 us and 0.04 us a tap), and 14e12 multiply-adds a second.
+// their weights (0.3 us and 0.04 us a tap), and 14e12 multiply-adds a second.  That is a thread of one voxel; with four (kFourGroups) 110 passes of large layers take 0.9 of
+// it at the median, where one voxel a thread took 1.15.
 double few_conv_seconds(const Geom& g, bool backward)
 {
     const int U = group_width(g.kx);

@@ -499,9 +499,10 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 
 // Bound by the store of the spectra (8 bytes per frequency) and the transforms; the tile's samples come in as rows of
 // neighbouring lanes, one row, then one column per thread is transformed in registers.  The phases of a workgroup wait for memory and
-// for each other, so what counts is how many workgroups a compute unit holds (finish_geom): four waves per SIMD (128 registers;
-// three where columns of 32 make it 147) and no scratch memory.  At five waves, 96 registers, the inverse spilled 13: kernel gradients of 120 x 120 maps,
-// 24^3, 240 -> 203 us.  Tests of mask bits and addresses that the
+// for each other, so what counts is how many workgroups a compute unit holds (finish_geom): five waves per SIMD forward (88 to 95 registers), four inverse
+// (106; three where columns of 32 make it 147), and no vector register spilled.  Scalar ones are: 13 and 31 (columns of 32) of an inverse, 218 to 324 of one that adds shares, which
+// keeps 36 bytes a lane in scratch memory in two instances, as does the forward kernel for columns of 32 and clipped tiles.  Held to five waves, 96 registers, the inverse spilled
+// 13 vector registers: kernel gradients of 120 x 120 maps, 24^3, 240 -> 203 us without.  Tests of mask bits and addresses that the
 // compiler kept across columns cost 20 to 30 registers and most of the scalar ones.  40 maps of 64^3 in tiles of 16 x 24 x 24:
 // forward 41 -> 37 us, inverse 41 -> 36 us; their kernels 27 -> 19 and 21 -> 16 us.
 template <bool LONG, bool FULL>
@@ -962,8 +963,8 @@ unsigned mask_of(int o, int w, int sp)
 bool has_long(const TileGeom& G) { return G.M[0] > 24 || G.M[1] > 24 || G.M[2] > 24; }
 
 // Fills what follows from the fields set by the caller; returns threads and LDS bytes of a workgroup.  Entries per
-// workgroup: as many as keep the threads of the column passes busiest within 40 KiB of LDS (four workgroups per compute
-// unit; a single larger tile still leaves two), while the launch has two workgroups per compute unit.
+// workgroup: as many as keep the threads of the column passes busiest within 40 KiB of LDS (three workgroups per compute
+// unit or more; a single larger tile still leaves two), while the launch has two workgroups per compute unit.
 void finish_geom(TileGeom& G, long entries, bool inverse, int* threads, size_t* lds, int given = 0)
 {
     G.entries = (int)entries;
@@ -1171,9 +1172,9 @@ size_t spectra_of(const Tiling& L, long entries) { return align256(sizeof(float2
 }  // namespace
 
 // ---------------------------------------------------------------- the tiling of a layer
-// Seconds that a training round spends on tiles, from the rates the kernels reach on layers that fill the chip: transforms
-// 3.0 (forward) and 2.6 TB/s (inverse) of spectra, products 4.5 TB/s and 110 TFLOP/s (result tiles of 16 x 16), the sum of
-// overlapping tiles 4.2 TB/s.  Node spectra count one and a half times: rounds with and without memoized ones.
+// Seconds that a training round spends on tiles: transforms at 3.0 (forward) and 2.6 TB/s (inverse) of spectra, products at 4.5 TB/s and
+// 110 TFLOP/s (result tiles of 16 x 16), the sum of overlapping tiles at 4.2 TB/s.  These are rates of earlier kernels on layers that fill the chip.  Of 306 rounds on the present
+// ones, 4 us a launch included, it says 0.85 times the measured time at the median below 100 us (0.59 to 1.14), 0.90 to 200 us (0.65 to 1.28) and 1.02 above (0.64 to 1.32).  Node spectra count one and a half times: rounds with and without memoized ones.
 static double round_seconds(const Geom& g, const Tiling& L)
 {
     auto up16 = [](double v) { return std::ceil(v / 16.0) * 16.0; };

@@ -51,11 +51,12 @@ def test_passes_stay_within_the_bound_of_fp32_chains(f, fo, n, k, s):
 
 
 @pytest.mark.parametrize("value", [np.inf, np.nan])
-def test_values_that_are_not_finite_reach_the_results_they_belong_to(value):
-    f, fo, n, k = 1, 4, (9, 10, 11), (3, 3, 3)
+@pytest.mark.parametrize("n", [(9, 10, 11), (62, 63, 51)])          # one voxel a thread, four
+def test_values_that_are_not_finite_reach_the_results_they_belong_to(n, value):
+    f, fo, k = 1, 4, (3, 3, 3)
     x, w, g = synth.layer_tensors(synth.LayerShape("t", f, fo, n, k, 1.0, 9201))
-    x[0, 4, 5, 6] = value
-    g[2, 3, 3, 3] = value
+    x[0, 4, 5, 6] = x[0, 1, 2, -3] = value
+    g[2, 3, 3, 3] = g[1, 0, 1, -2] = value
     p = znn.Plan(f, fo, n, k, "direct")
     got = (p.fwd(dev(x), dev(w)), p.bwd(dev(g), dev(w)), p.wgrad(dev(x), dev(np.ones_like(g))))
     ref = (oracle.conv3d_fwd(x, w), oracle.conv3d_bwd(g, w, n), oracle.conv3d_wgrad(x, np.ones_like(g)))
