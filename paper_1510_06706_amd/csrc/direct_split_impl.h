@@ -72,9 +72,166 @@ struct SplitTile {
 
 using SplitFn = void (*)(SplitTile);
 
+// The launch's parameters from memory again: those of the end of a workgroup need not stay in scalar registers from its beginning on.
+template <class Args>
+__device__ __forceinline__ const Args* reload_args()
+{
+    auto args = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    return (const Args*)args;
+}
+
+// Stores what the accumulators hold.  Lane holds maps 4 (lane / 16) + r of voxel lane % 16.  A result's place is that of the lane's first map plus a uniform step, and the
+// derivatives of a voxel tile are loaded together: with a 64-bit product for each place, and each derivative waited for before the next, the stores of
+// a workgroup took 11 000 clocks (now 4200; 12 -> 8 us a launch on the last layer of a net).
+template <int NJ, int NV, bool FINISH, class Args, class VoxelOf>
+__device__ __forceinline__ void store_tiles(const Args& C, const floatx4 (&acc)[NJ][NV], float* out, long dvol, int jg, int wave, int col, int grp, VoxelOf voxel_of)
+{
+    float bias[NJ][4];
+    if (FINISH && C.y) {                            // uniform
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) bias[jt][r] = C.bias[min((jg * NJ + jt) * 16 + grp * 4 + r, C.fM - 1)];
+    }
+#pragma unroll
+    for (int nv = 0; nv < NV; ++nv) {
+        const long vox = voxel_of((wave * NV + nv) * 16 + col);
+        if (vox < 0) continue;
+        const long first = (jg * NJ * 16 + grp * 4) * dvol + vox;
+        float v[NJ][4], d[NJ][4];
+        if (FINISH && C.deriv) {                    // uniform; all loads are in flight together
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    d[jt][r] = C.deriv[(jg * NJ + jt) * 16 + grp * 4 + r < C.fM ? first + (jt * 16 + r) * dvol : vox];
+        }
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt) {
+            const int left = C.fM - (jg * NJ + jt) * 16;            // maps of the tile (uniform)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                v[jt][r] = acc[jt][nv][r];
+                if (FINISH && C.deriv) v[jt][r] = d[jt][r] > 0.f ? v[jt][r] : 0.f;
+                if (left >= 16 || grp * 4 + r < left) {
+                    float* const at = out + first + (jt * 16 + r) * dvol;
+                    *at = v[jt][r];
+                    if (FINISH && C.y) {
+                        const float u = v[jt][r] + bias[jt][r];
+                        C.y[first + (jt * 16 + r) * dvol] = u > 0.f ? u : 0.f;
+                    }
+                }
+            }
+        }
+    }
+}
+
+// An infinity or a NaN among the operands (or the voxel read in place of a zero) makes the parts' products NaN where the
+// product itself may not be: results that are not finite are read back and taken again in fp32, straight from memory, on
+// v_mfma_f32_16x16x4_f32, a voxel tile at a time.  A NaN stays one, so a tile is done when all of these are; the finite ones stand.
+// 40 -> 40 maps, 64^3, 5^3 kernels, forward 560 us on finite values: weights of half the maps NaN 480 us (6.0 ms where a wave took all
+// of its tiles again), all voxels NaN 510, one voxel infinite 800; 80 -> 80, 256^2, 11^2, 430 us: 400, 400 and 2900 us.
+template <int NJ, int NV, class Args, class VoxelOf, class Place>
+__device__ __forceinline__ void retake_tiles(const Args& C, float* out, long svol, long dvol, int jg, int wave, int col, int grp, int ic0, int ic1, int Ttot, int taps,
+                                             const unsigned* from, const int* tofs, VoxelOf voxel_of, Place place)
+{
+    const int maps = min(ic1 * kMaps, C.fK);
+#pragma unroll 1
+    for (int nv = 0; nv < NV; ++nv) {
+        const int t = (wave * NV + nv) * 16 + col;
+        const long vox = voxel_of(t);
+        int tz, ty, tx;
+        place(t < Ttot ? t : 0, tz, ty, tx);
+        const unsigned* const at = from + (tz * C.HY + ty) * C.HX + tx;
+        unsigned wrong = 0;                                     // the lane's results that are
+        floatx4 again[NJ];
+        global_floats row[NJ];                                  // weights of the lane's result map (or the last one, for no result)
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt) {
+            again[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+            row[jt] = (global_floats)C.w + min((jg * NJ + jt) * 16 + (int)col, C.fM - 1) * C.wm;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int j = (jg * NJ + jt) * 16 + grp * 4 + r;
+                if (vox >= 0 && j < C.fM && !(fabsf(out[(long)j * dvol + vox]) <= kLargest)) wrong |= 1u << (jt * 4 + r);
+            }
+        }
+        // whether some of them are not NaN again yet
+        auto open = [&] {
+            unsigned left = wrong;
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (again[jt][r] != again[jt][r]) left &= ~(1u << (jt * 4 + r));
+            return __builtin_amdgcn_ballot_w64(left != 0) != 0;
+        };
+        // Products of `N` input maps at taps t0 to t0 + 15, N of its four by a lane: a result map's weights of these are 64 contiguous bytes.
+        auto add_products = [&](int map, int t0, auto many) {
+            constexpr int N = decltype(many)::value;
+            float v[N][N], w[N][N][NJ];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int q = t0 + 4 * grp + i, tap = min(q, taps - 1);
+                const unsigned o = q < taps ? at[tofs[tap] / kVoxelBytes] : ~0u;
+#pragma unroll
+                for (int h = 0; h < N; ++h) {
+                    const long of = min(map + h, maps - 1);         // uniform
+                    const bool has = q < taps && map + h < maps;
+                    const float x = ((global_floats)C.src + of * svol)[o != ~0u ? o / 4 : 0];
+                    v[i][h] = has && o != ~0u ? x : 0.f;
+#pragma unroll
+                    for (int jt = 0; jt < NJ; ++jt) {
+                        const float y = row[jt][of * C.wk + (C.reflected ? taps - 1 - tap : tap)];
+                        w[i][h][jt] = has ? y : 0.f;
+                    }
+                }
+            }
+#pragma unroll
+            for (int h = 0; h < N; ++h)
+#pragma unroll
+                for (int i = 0; i < N; ++i)
+#pragma unroll
+                    for (int jt = 0; jt < NJ; ++jt) again[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][h][jt], v[i][h], again[jt], 0, 0, 0);
+        };
+        // Where a few products make NaN of them already, no more are needed: whole maps of a net that has diverged.  The walk is bound by
+        // the way to memory, so a step of it requests much.
+        bool more = open();
+        if (more) {
+            add_products(ic0 * kMaps, 0, std::integral_constant<int, 1>{});
+            more = open();
+        }
+        if (more) {
+#pragma unroll
+            for (int jt = 0; jt < NJ; ++jt) again[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int map = ic0 * kMaps; map < maps && more; map += 4)
+                for (int t0 = 0; t0 < taps && more; t0 += 16) {
+                    add_products(map, t0, std::integral_constant<int, 4>{});
+                    more = open();
+                }
+        }
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (wrong >> (jt * 4 + r) & 1) {
+                    const int j = (jg * NJ + jt) * 16 + grp * 4 + r;
+                    const long to = (long)j * dvol + vox;
+                    float s = again[jt][r];
+                    out[to] = s;
+                    if (C.y) {                                          // uniform
+                        s += C.bias[j];
+                        C.y[to] = s > 0.f ? s : 0.f;
+                    }
+                }
+    }
+}
+
 // Bound by the matrix cores (six MFMAs of 16 clocks per 16 x 16 x 32 product).
+// Two waves on a SIMD, by registers; four of 2 x 2 tiles, which are one over that by themselves.
 template <int NJ, int NV, int NW>
-__global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
+__global__ void __launch_bounds__(64 * NW, NJ == 2 && NV == 2 ? 4 : 2) k_conv_split(SplitTile P)
 {
     constexpr int NT = 64 * NW;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -179,21 +336,26 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
         }
     };
 
-    const int wstep = NJ * 3 * 64;                      // packed weights of a step
-    const uintx4* wq = P.wp + ((long)jg * P.nchunk + ic0) * P.steps * wstep + lane;
+    // Few tiles wait for their weights, all of a step's at once before its products are the earliest (29 -> 7 maps, 12^3, 7^3, backward, 2 x 1: 25.1 us, paced 29.8); the
+    // largest tile shapes have no registers for it.
+    constexpr bool PACED = NJ > 1 && NJ * NV > 4 && NJ * NV != 18 && !(NJ == 5 && NV == 2);
+    // packed weights: a uniform place and the lane's offset; 2 x 2 tiles keep to the registers of four waves by one place alone
+    constexpr bool UNIFORM = NJ != 2 || NV != 2;
+    global_bytes wq = (global_bytes)(P.wp + ((long)jg * P.nchunk + ic0) * P.steps * (NJ * 3 * 64)) + (UNIFORM ? 0 : lane * 16);
+    const unsigned wlane = UNIFORM ? lane * 16 : 0;
     for (int ic = ic0; ic < ic1; ++ic) {
         bf16x8 a0[NJ][3], a1[NJ][3];
         uintx4 b0[3], b1[3];
         floatx4 t0[NJ], t1[NJ];
 #pragma unroll
         for (int jt = 0; jt < NJ; ++jt) t0[jt] = t1[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
-        auto weights = [&](bf16x8 (&a)[NJ][3]) {
-#pragma unroll
-            for (int jt = 0; jt < NJ; ++jt)
-#pragma unroll
-                for (int p = 0; p < 3; ++p) a[jt][p] = __builtin_bit_cast(bf16x8, wq[(jt * 3 + p) * 64]);
+        // q-th of the operands of a step, paced in the order that the products need them
+        auto weight = [&](bf16x8 (&a)[NJ][3], int q) __attribute__((always_inline)) {
+            const int jt = PACED ? q % NJ : q / 3, p = PACED ? (3 - q / NJ) % 3 : q % 3;
+            a[jt][p] = __builtin_bit_cast(bf16x8, *(global_quads)(wq + (jt * 3 + p) * 1024 + wlane));
         };
-        weights(a0);
+#pragma unroll
+        for (int q = 0; q < 3 * NJ; ++q) weight(a0, q);
         const float lone = ic & 1 ? -1.f : 1.f;         // sign of a last step without a partner
         __syncthreads();                                // nobody still reads the chunk before
         stage(ic);
@@ -201,35 +363,47 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
 
         lds_ints to = (lds_ints)(lbase + P.hvol * kVoxelBytes) + grp;
         int now = to[0], next = to[kTaps];
-        auto voxels = [&](uintx4 (&b)[3], lds_bytes at) {
-#pragma unroll
-            for (int p = 0; p < 3; ++p) b[p] = reinterpret_cast<lds_quads>(at)[p];
+        auto voxel = [&](uintx4 (&b)[3], lds_bytes at, int q) __attribute__((always_inline)) {
+            const int p = PACED ? (q + 2) % 3 : q;
+            b[p] = reinterpret_cast<lds_quads>(at)[p];
         };
-        voxels(b0, voff[0] + now);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) voxel(b0, voff[0] + now, q);
         // One step: the MFMAs of a voxel tile run while the operands of the next one arrive.  PAR: which register set of
         // the voxel operands the step's first tile is in; sign, before: how add_signed takes its tiles, and those before.
         auto step = [&](bf16x8 (&a)[NJ][3], bf16x8 (&an)[NJ][3], auto sign, auto before, auto par) __attribute__((always_inline)) {
             constexpr int PAR = decltype(par)::value;
-            wq += wstep;
-            weights(an);                                // behind the last step: the next chunk's, or the padding
+            wq += NJ * 3 * 1024;                        // behind the last step: the next chunk's, or the padding
+            if constexpr (UNIFORM) asm volatile("" : "+s"(wq));     // a uniform place it stays
 #pragma unroll
             for (int nv = 0; nv < NV; ++nv) {
                 uintx4 (&b)[3] = ((PAR + nv) & 1) ? b1 : b0;
                 uintx4 (&bn)[3] = ((PAR + nv) & 1) ? b0 : b1;
-                if (nv + 1 < NV) voxels(bn, voff[nv + 1 < NV ? nv + 1 : 0] + now);
-                else {
+                if (nv + 1 == NV) {
                     now = next;
                     to += kTaps;
                     next = to[kTaps];
-                    voxels(bn, voff[0] + now);
                 }
+                const lds_bytes at = voff[(nv + 1) % NV] + now;
+                auto request = [&](int slot) __attribute__((always_inline)) {
+                    if constexpr (!PACED) {
+                        if (nv == 0 && slot < 3 * NJ) weight(an, slot);
+                        if (slot >= 3 * NJ && slot < 3 * NJ + 3) voxel(bn, at, slot - 3 * NJ);
+                        return;
+                    }
+                    if (slot < 3) voxel(bn, at, slot);
+                    // behind them the weights, but for those of few tiles, which have to come from memory in their time
+                    constexpr int WAIT = NJ * NV <= 6 ? 0 : 3;
+                    const int q = nv * (6 * NJ - WAIT) + slot - WAIT;
+                    if (q < 3 * NJ && slot >= WAIT) weight(an, q);
+                };
                 floatx4* into[NJ];
 #pragma unroll
                 for (int jt = 0; jt < NJ; ++jt) into[jt] = &acc[jt][(nv + NV - 1) % NV];
                 floatx4 (&t)[NJ] = (PAR + nv) & 1 ? t1 : t0;
                 floatx4 (&tb)[NJ] = (PAR + nv) & 1 ? t0 : t1;       // the tile before; for the first one, of the step before
-                if (nv == 0) products<NJ, decltype(before)::value>(t, a, b, tb, lone, into);
-                else products<NJ, decltype(sign)::value>(t, a, b, tb, lone, into);
+                if (nv == 0) products<NJ, decltype(before)::value, PACED>(t, a, b, tb, lone, into, request);
+                else products<NJ, decltype(sign)::value, PACED>(t, a, b, tb, lone, into, request);
             }
         };
         constexpr int ODD = NV & 1;
@@ -267,154 +441,12 @@ __global__ void __launch_bounds__(64 * NW, 2) k_conv_split(SplitTile P)
             for (int r = 0; r < 4; ++r) bad = bad || !(fabsf(acc[jt][nv][r]) <= kLargest);
 
     float* const out = gridDim.z > 1 ? P.partial + (long)blockIdx.z * P.fM * dvol : P.dst;
-    // Lane holds maps 4 (lane / 16) + r of voxel lane % 16.  A result's place is that of the lane's first map plus a uniform step, and the
-    // derivatives of a voxel tile are loaded together: with a 64-bit product for each place, and each derivative waited for before the next, the stores of
-    // a workgroup took 11 000 clocks (now 4200; 12 -> 8 us a launch on the last layer of a net).
-    auto store_all = [&](auto finishing) __attribute__((always_inline)) {
-        constexpr bool FINISH = decltype(finishing)::value;
-        float bias[NJ][4];
-        if (FINISH && P.y) {                            // uniform
-#pragma unroll
-            for (int jt = 0; jt < NJ; ++jt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) bias[jt][r] = P.bias[min((jg * NJ + jt) * 16 + grp * 4 + r, P.fM - 1)];
-        }
-#pragma unroll
-        for (int nv = 0; nv < NV; ++nv) {
-            const long vox = voxel_of((wave * NV + nv) * 16 + col);
-            if (vox < 0) continue;
-            const long first = (jg * NJ * 16 + grp * 4) * dvol + vox;
-            float v[NJ][4], d[NJ][4];
-            if (FINISH && P.deriv) {                    // uniform; all loads are in flight together
-#pragma unroll
-                for (int jt = 0; jt < NJ; ++jt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        d[jt][r] = P.deriv[(jg * NJ + jt) * 16 + grp * 4 + r < P.fM ? first + (jt * 16 + r) * dvol : vox];
-            }
-#pragma unroll
-            for (int jt = 0; jt < NJ; ++jt) {
-                const int left = P.fM - (jg * NJ + jt) * 16;            // maps of the tile (uniform)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    v[jt][r] = acc[jt][nv][r];
-                    if (FINISH && P.deriv) v[jt][r] = d[jt][r] > 0.f ? v[jt][r] : 0.f;
-                    if (left >= 16 || grp * 4 + r < left) {
-                        float* const at = out + first + (jt * 16 + r) * dvol;
-                        *at = v[jt][r];
-                        if (FINISH && P.y) {
-                            const float u = v[jt][r] + bias[jt][r];
-                            P.y[first + (jt * 16 + r) * dvol] = u > 0.f ? u : 0.f;
-                        }
-                    }
-                }
-            }
-        }
-    };
     // what follows the sums is decided once, outside the stores
-    if (P.deriv || P.y) store_all(std::true_type{});
-    else store_all(std::false_type{});
+    if (P.deriv || P.y) store_tiles<NJ, NV, true>(P, acc, out, dvol, jg, wave, col, grp, voxel_of);
+    else store_tiles<NJ, NV, false>(P, acc, out, dvol, jg, wave, col, grp, voxel_of);
 
-    // An infinity or a NaN among the operands (or the voxel read in place of a zero) makes the parts' products NaN where the
-    // product itself may not be: results that are not finite are read back and taken again in fp32, straight from memory, on
-    // v_mfma_f32_16x16x4_f32, a voxel tile at a time.  A NaN stays one, so a tile is done when all of these are; the finite ones stand.
-    // 40 -> 40 maps, 64^3, 5^3 kernels, forward 560 us on finite values: weights of half the maps NaN 480 us (6.0 ms where a wave took all
-    // of its tiles again), all voxels NaN 510, one voxel infinite 800; 80 -> 80, 256^2, 11^2, 430 us: 400, 400 and 2900 us.
     if (!__builtin_amdgcn_ballot_w64(bad)) return;
-    // the launch's parameters from memory again: they need not stay in scalar registers for this
-    auto args = __builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(args));
-    const SplitTile& C = *(const SplitTile*)args;
-    const int maps = min(ic1 * kMaps, C.fK);
-#pragma unroll 1
-    for (int nv = 0; nv < NV; ++nv) {
-        const int t = (wave * NV + nv) * 16 + col;
-        const long vox = voxel_of(t);
-        int tz, ty, tx;
-        place(t < Ttot ? t : 0, tz, ty, tx);
-        const unsigned* const at = from + (tz * C.HY + ty) * C.HX + tx;
-        unsigned wrong = 0;                                     // the lane's results that are
-        floatx4 again[NJ];
-        global_floats row[NJ];                                  // weights of the lane's result map (or the last one, for no result)
-#pragma unroll
-        for (int jt = 0; jt < NJ; ++jt) {
-            again[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
-            row[jt] = (global_floats)C.w + min((jg * NJ + jt) * 16 + (int)col, C.fM - 1) * C.wm;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int j = (jg * NJ + jt) * 16 + grp * 4 + r;
-                if (vox >= 0 && j < C.fM && !(fabsf(out[(long)j * dvol + vox]) <= kLargest)) wrong |= 1u << (jt * 4 + r);
-            }
-        }
-        // whether some of them are not NaN again yet
-        auto open = [&] {
-            unsigned left = wrong;
-#pragma unroll
-            for (int jt = 0; jt < NJ; ++jt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (again[jt][r] != again[jt][r]) left &= ~(1u << (jt * 4 + r));
-            return __builtin_amdgcn_ballot_w64(left != 0) != 0;
-        };
-        // Products of `N` input maps at taps t0 to t0 + 15, N of its four by a lane: a result map's weights of these are 64 contiguous bytes.
-        auto add_products = [&](int map, int t0, auto many) {
-            constexpr int N = decltype(many)::value;
-            float v[N][N], w[N][N][NJ];
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const int q = t0 + 4 * grp + i, tap = min(q, taps - 1);
-                const unsigned o = q < taps ? at[tofs[tap] / kVoxelBytes] : ~0u;
-#pragma unroll
-                for (int h = 0; h < N; ++h) {
-                    const long of = min(map + h, maps - 1);         // uniform
-                    const bool has = q < taps && map + h < maps;
-                    const float x = ((global_floats)C.src + of * svol)[o != ~0u ? o / 4 : 0];
-                    v[i][h] = has && o != ~0u ? x : 0.f;
-#pragma unroll
-                    for (int jt = 0; jt < NJ; ++jt) {
-                        const float y = row[jt][of * C.wk + (C.reflected ? taps - 1 - tap : tap)];
-                        w[i][h][jt] = has ? y : 0.f;
-                    }
-                }
-            }
-#pragma unroll
-            for (int h = 0; h < N; ++h)
-#pragma unroll
-                for (int i = 0; i < N; ++i)
-#pragma unroll
-                    for (int jt = 0; jt < NJ; ++jt) again[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][h][jt], v[i][h], again[jt], 0, 0, 0);
-        };
-        // Where a few products make NaN of them already, no more are needed: whole maps of a net that has diverged.  The walk is bound by
-        // the way to memory, so a step of it requests much.
-        bool more = open();
-        if (more) {
-            add_products(ic0 * kMaps, 0, std::integral_constant<int, 1>{});
-            more = open();
-        }
-        if (more) {
-#pragma unroll
-            for (int jt = 0; jt < NJ; ++jt) again[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
-            for (int map = ic0 * kMaps; map < maps && more; map += 4)
-                for (int t0 = 0; t0 < taps && more; t0 += 16) {
-                    add_products(map, t0, std::integral_constant<int, 4>{});
-                    more = open();
-                }
-        }
-#pragma unroll
-        for (int jt = 0; jt < NJ; ++jt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (wrong >> (jt * 4 + r) & 1) {
-                    const int j = (jg * NJ + jt) * 16 + grp * 4 + r;
-                    const long to = (long)j * dvol + vox;
-                    float s = again[jt][r];
-                    out[to] = s;
-                    if (C.y) {                                          // uniform
-                        s += C.bias[j];
-                        C.y[to] = s > 0.f ? s : 0.f;
-                    }
-                }
-    }
+    retake_tiles<NJ, NV>(*reload_args<SplitTile>(), out, svol, dvol, jg, wave, col, grp, ic0, ic1, Ttot, taps, from, tofs, voxel_of, place);
 }
 
 }  // namespace split

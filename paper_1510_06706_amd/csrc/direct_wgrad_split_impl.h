@@ -221,11 +221,15 @@ __global__ void __launch_bounds__(64 * kGradWaves) k_wgrad_split(GradTile P)
             for (int nt = 0; nt < NT; ++nt) {
                 uintx4 (&b)[3] = nt & 1 ? b1 : b0;
                 uintx4 (&bn)[3] = nt & 1 ? b0 : b1;
-                if (nt + 1 < NT) load(bn, buf + boff[nt + 1 < NT ? nt + 1 : 0] + bo);
+                const lds_bytes at = buf + boff[nt + 1 < NT ? nt + 1 : 0] + bo;
+                auto request = [&](int slot) __attribute__((always_inline)) {
+                    const int p = (slot + 2) % 3;       // in the order that the products need them
+                    if (nt + 1 < NT && slot < 3) bn[p] = reinterpret_cast<lds_quads>(at)[p];
+                };
                 floatx4 *into[NJ];
 #pragma unroll
                 for (int jt = 0; jt < NJ; ++jt) into[jt] = &acc[jt][nt ? nt - 1 : 0];
-                products<NJ, 0>(nt & 1 ? t1 : t0, a, b, nt & 1 ? t0 : t1, sign, into);
+                products<NJ, 0, (NJ > 1)>(nt & 1 ? t1 : t0, a, b, nt & 1 ? t0 : t1, sign, into, request);
             }
 #pragma unroll
             for (int jt = 0; jt < NJ; ++jt) add_signed<0>(acc[jt][NT - 1], (NT - 1) & 1 ? t1[jt] : t0[jt], sign);

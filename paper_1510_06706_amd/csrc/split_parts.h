@@ -31,6 +31,10 @@ typedef __attribute__((address_space(3))) const char* lds_bytes;
 typedef __attribute__((address_space(3))) const uintx4* lds_quads;
 typedef __attribute__((address_space(3))) const int* lds_ints;
 typedef __attribute__((address_space(1))) const float* global_floats;
+typedef __attribute__((address_space(1))) const char* global_bytes;
+typedef __attribute__((address_space(1))) const void* global_ptr;
+typedef __attribute__((address_space(3))) void* lds_ptr;
+typedef __attribute__((address_space(1))) const uintx4* global_quads;
 
 constexpr int kPartBytes = 16;      // one part of eight numbers
 constexpr int kVectorBytes = 48;    // three parts of eight numbers
@@ -64,40 +68,41 @@ __device__ __forceinline__ floatx4 mfma(const bf16x8& a, const bf16x8& b, const 
 
 // acc += sign t; SIGN: 1 or -1, or 0 where only `sign` (uniform) says it
 template <int SIGN>
+__device__ __forceinline__ float add_signed(float acc, float t, float sign)
+{
+    return SIGN > 0 ? acc + t : SIGN < 0 ? acc - t : fmaf(t, sign, acc);
+}
+
+template <int SIGN>
 __device__ __forceinline__ void add_signed(floatx4& acc, const floatx4& t, float sign)
 {
-    if (SIGN > 0) acc += t;
-    else if (SIGN < 0) acc -= t;
-    else {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = fmaf(t[r], sign, acc[r]);
-    }
+    for (int r = 0; r < 4; ++r) acc[r] = add_signed<SIGN>(acc[r], t[r], sign);
 }
 
 // Six products of a step, from zero, smallest first, for NJ row tiles and one column tile.  acc += sign before (add_signed) is the
-// column tile before, whose products are done by now: between the instructions of this one they cost nothing.
-template <int NJ, int SIGN>
+// column tile before, whose products are done by now.  An MFMA keeps the matrix core for 16 clocks, of which its wave needs four to issue it: one
+// addition and one request for an operand (request(slot), slot = 0 .. 6 NJ - 1) in between cost nothing, many in a row, or an addition of what
+// the last MFMA has not finished, do.  PACED: in that order, which takes a few registers more (40 -> 40 maps, 64^3, 5^3, 469 -> 461 us forward and 523 -> 511 the gradient);
+// products of a single row tile wait for each other anyway.
+template <int NJ, int SIGN, bool PACED, class Request>
 __device__ __forceinline__ void products(floatx4 (&t)[NJ], const bf16x8 (&a)[NJ][3], const uintx4 (&b)[3], const floatx4 (&before)[NJ],
-                                         float sign, floatx4* const (&acc)[NJ])
+                                         float sign, floatx4* const (&acc)[NJ], Request request)
 {
-    const bf16x8 c0 = __builtin_bit_cast(bf16x8, b[0]), c1 = __builtin_bit_cast(bf16x8, b[1]), c2 = __builtin_bit_cast(bf16x8, b[2]);
-    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+    constexpr int ofA[6] = {0, 2, 1, 0, 1, 0}, ofB[6] = {2, 0, 1, 1, 0, 0};
+    if (!PACED)
+#pragma unroll
+        for (int slot = 0; slot < 6 * NJ; ++slot) request(slot);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) t[j] = mfma(a[j][0], c2, zero);
+    for (int g = 0; g < 6; ++g)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) t[j] = mfma(a[j][2], c0, t[j]);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) add_signed<SIGN>(*acc[j], before[j], sign);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) t[j] = mfma(a[j][1], c1, t[j]);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) t[j] = mfma(a[j][0], c1, t[j]);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) t[j] = mfma(a[j][1], c0, t[j]);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) t[j] = mfma(a[j][0], c0, t[j]);
-    __builtin_amdgcn_sched_barrier(0);
+        for (int j = 0; j < NJ; ++j) {
+            t[j] = mfma(a[j][ofA[g]], __builtin_bit_cast(bf16x8, b[ofB[g]]), g ? t[j] : floatx4{0.f, 0.f, 0.f, 0.f});
+            if (PACED) request(g * NJ + j);
+            if (g >= 1 && g <= 4) (*acc[j])[g - 1] = add_signed<SIGN>((*acc[j])[g - 1], before[j][g - 1], sign);
+            if (PACED || (g == 5 && j == NJ - 1)) __builtin_amdgcn_sched_barrier(0);
+        }
 }
 
 }  // namespace split
