@@ -14,11 +14,14 @@ struct SplitChoice {
     int T[3], H[3], c[3];           // box, halo box, boxes per sublattice (z, y, x)
     int phases, steps, nchunk;
     int cps, splits;                // chunks of eight input maps per workgroup, shares of them
+    bool beside;                    // four more waves stage beside those that multiply (direct_beside_impl.h), else these in between (direct_split_impl.h)
+    int hop, wofs, whop, tables;    // beside, LDS: from one staging buffer to the other (0: one buffer), weights and their second buffer, tables
     size_t lds;
-    double cost;                    // expected clocks
+    double cost, between;           // expected clocks, and those of the best choice whose waves stage in between
 };
 SplitChoice choose_split(const Geom& g, bool backward);
-double split_seconds(const SplitChoice& c);
+void split_place(SplitChoice& c);
+double split_seconds(double clocks);
 size_t split_packed_bytes(const SplitChoice& c);
 PackItem split_pack_item(const Geom& g, const SplitChoice& c, bool backward, const float* w, void* wp);
 int split_pack_weights(const PackItem* items, int n, hipStream_t s);

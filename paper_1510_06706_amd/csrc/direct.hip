@@ -33,11 +33,12 @@ void reduce(const float* partial, float* dst, long count, int splits, bool more,
 
 long result_count(const Geom& g, bool backward) { return backward ? (long)g.f * g.nvol() : (long)g.fo * g.ovol(); }
 
-// ok = false: the vector ALUs take the pass
+// ok = false: the vector ALUs take the pass.  Held against the price of waves that stage in between, which that of the vector ALUs was fitted beside, also where others
+// stage; so what the vector ALUs took they take.
 SplitChoice way(const Geom& g, bool backward)
 {
     SplitChoice c = choose_split(g, backward);
-    if (c.ok && few_conv_seconds(g, backward) < split_seconds(c) + 3e-6) c.ok = false;
+    if (c.ok && few_conv_seconds(g, backward) < split_seconds(c.between) + 3e-6) c.ok = false;
     return c;
 }
 
@@ -50,7 +51,7 @@ bool conv_takes_packed(const Geom& g, bool backward) { return way(g, backward).o
 double conv_seconds(const Geom& g, bool backward)
 {
     const SplitChoice c = way(g, backward);
-    return c.ok ? split_seconds(c) : few_conv_seconds(g, backward);
+    return c.ok ? split_seconds(c.between) : few_conv_seconds(g, backward);         // as the choice between the methods was fitted to (api.hip)
 }
 
 size_t conv_packed_bytes(const Geom& g, bool backward)
@@ -137,18 +138,20 @@ int direct_fwd(const Geom& g, const float* in, const float* w, float* out, void*
 static Geom group_of(const Geom& g, const SplitChoice& c, int first)
 {
     Geom q = g;
-    q.fo = std::min(16 * c.NJ, g.fo - first);
+    q.fo = std::min(16 * c.NJ * c.jgroups, g.fo - first);
     return q;
 }
 
 static size_t share_bytes(const Geom& g, const SplitChoice& c) { return sizeof(float) * result_count(group_of(g, c, 0), false); }
 
-// c.jgroups = 1 and the largest groups whose weights and sums fit, or else the smallest; shares: those of a launch.  Not ok: the weights
-// of sixteen output maps do not fit, and the vector ALUs take the pass.
+// All maps in one launch if their weights and sums fit; else c.jgroups = 1 and the largest groups whose weights and sums fit, or else the smallest; shares: those
+// of a launch.  Not ok: the weights of sixteen output maps do not fit, and the vector ALUs take the pass.
 static SplitChoice choose_groups(const Geom& g, int& shares)
 {
     SplitChoice c = way(g, false);
     if (!c.ok) return c;
+    shares = c.splits;
+    if (split_packed_bytes(c) + (c.splits > 1 ? c.splits * share_bytes(g, c) : 0) <= ZNN_STATIC_SCRATCH_BYTES) return c;
     const int tiles = (g.fo + 15) / 16;
     int groups = (tiles + c.NJ - 1) / c.NJ;
     c.jgroups = 1;
@@ -158,10 +161,12 @@ static SplitChoice choose_groups(const Geom& g, int& shares)
         shares = c.ok && c.splits > 1 ? (int)std::min<size_t>(c.splits, (ZNN_STATIC_SCRATCH_BYTES - packed) / share_bytes(g, c)) : 1;
         if (c.NJ == 1 || (c.ok && shares == c.splits)) break;
     }
-    if (shares > 0) return c;
     // not even the sums of one share: one after another in the accumulators
-    shares = c.splits = 1;
-    c.cps = c.nchunk;
+    if (shares == 0) {
+        shares = c.splits = 1;
+        c.cps = c.nchunk;
+    }
+    if (c.ok) split_place(c);
     return c;
 }
 
@@ -180,7 +185,7 @@ int direct_fwd_groups(const Geom& g, const float* in, const float* w, float* out
     const SplitChoice c = choose_groups(g, shares);
     if (!c.ok) return few_conv(g, false, in, w, out, Finish{}, s);
     float* partial = (float*)((char*)ws + split_packed_bytes(c));
-    for (int first = 0; first < g.fo; first += 16 * c.NJ) {
+    for (int first = 0; first < g.fo; first += 16 * c.NJ * c.jgroups) {
         const Geom q = group_of(g, c, first);
         float* dst = out + (long)first * g.ovol();
         const float* wq = w + (long)first * g.f * g.kvol();

@@ -1,17 +1,19 @@
 // Host side of the split direct kernel (direct_split_impl.h): packing of the weights, search for the workgroup's box, launch.
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
 #include <vector>
 
 #include "direct.h"
-#include "direct_split_impl.h"
+#include "direct_beside_impl.h"
 
 namespace znn {
 
 namespace {
 
+using split::BesideTile;
 using split::SplitFn;
 using split::SplitTile;
 
@@ -120,73 +122,213 @@ Pass pass_of(const Geom& g, bool backward)
     return P;
 }
 
+// Expected clocks of a launch of `groups` workgroups and of the sum of its shares.  Waves that stage in between: fitted to the times of 900 boxes on 22 layers (standard
+// deviation 15 %).
+double clocks_between(const SplitChoice& c, long groups, int spx, double count)
+{
+    const int hvol = c.H[0] * c.H[1] * c.H[2];
+    // clocks of a step of the workgroup: matrix cores, LDS reads (128 bytes a clock), weights from the vector cache (64)
+    const double step = 0.92 * std::max({c.NW / 4 * c.NJ * c.NV * 96.0, c.NW * c.NV * 24.0, c.NW * c.NJ * 48.0}) + 82.0 * c.NW / 4;
+    const int most = (c.NJ <= 2 && c.NJ * c.NV <= 8 ? 12 : 8) / c.NW;       // workgroups whose registers fit a compute unit
+    const int fit = std::max(1, std::min(most, (int)(kLds / c.lds)));
+    const double stage = 4.0 * hvol * (1.0 + 0.06 * (spx - 1));
+    const double fixed = 5200.0 + 11.5 * 16 * c.NV * c.NW * c.NJ;
+    const long per_cu = (groups + kCUs - 1) / kCUs;
+    // a unit with one wave per SIMD has nothing to overlap its waits with, one workgroup nothing for its stages
+    const long both = std::min((long)fit, per_cu);
+    const double alone = both * c.NW < 8 ? 1.38 : 1.0;
+    double cost = per_cu * (fixed + c.cps * (c.steps * step * alone + stage * (both > 1 ? 0.46 : 1.0)));
+    if (c.splits > 1) cost += 7000.0 + count * (c.splits + 1) * 4.0 / 3.0e12 * 2.1e9;
+    return cost;
+}
+
+// The larger of two times, and a little more where they are near each other: neither overlaps the other perfectly.
+double larger(double a, double b)
+{
+    const double p = a * a, q = b * b;
+    return std::sqrt(std::sqrt(p * p + q * q));
+}
+
+// Waves that stage beside: fitted to 5200 choices on 90 layers (standard deviation 12 %).
+double clocks_beside(const SplitChoice& c, long groups, int spx, double count)
+{
+    const int regs = 39 + 41 * c.NJ;
+    const int fit = std::max(1, std::min((int)(512 / ((regs + 7) / 8 * 8) * 4 / (split::kBesideWaves + split::kStagers)), (int)(kLds / c.lds)));
+    const long per_cu = (groups + kCUs - 1) / kCUs, both = std::min<long>(fit, per_cu);
+    const double rounds = (double)groups / kCUs / both;
+    // a step: matrix cores, LDS reads, six products of a tile one behind another
+    const double busy = larger(c.NJ * 70.7 + 50, (1 + c.NJ) * 55.2), step = larger(busy, 6 * larger(16 * c.NJ, 12.3) + 50);
+    const double stage = 1500 + 4.37 * c.H[0] * c.H[1] * c.H[2] * (1 + 0.164 * std::min(3, spx - 1));
+    const double ends = 207 + 115 * c.NJ;
+    const double one = ends + stage + c.cps * larger(c.steps * step + 600.0, stage);
+    const double all = both * (c.cps * c.steps * busy + 6.25 * ends);
+    double cost = std::max(1.0, rounds + 0.92 * (std::ceil(rounds) - rounds)) * larger(one, all);
+    if (c.splits > 1) cost += 4040.0 + count * (c.splits + 1) * 4.0 / 3.0e12 * 1.3e9;
+    // What the least of many is too low by (it is picked for the fit's errors as well), and a tenth more: of those better by less, every tenth was slower.
+    return 1.28 * cost * std::pow(c.splits, 0.115) * std::pow(c.NJ, 0.09);
+}
+
+// Where waves that stage beside pay: one 16-voxel tile a wave, and a launch that fits the chip at once, with one workgroup on a unit or two; with more of them a unit has other
+// workgroups to go on with while one stages, and twice the waves that multiply.  A thread has four voxels in flight: larger halo boxes take more than one time of memory.
+// More groups of maps than have to be (`more`) stage a box as often, shares have little to stage ahead: both take short chunks.  And three or four steps a chunk have nothing
+// to hide a stage behind, where it is done more often.  Of 509 passes of drawn layers these lines and the price take 77, at 0.87 of the time between on average and 1.01 at most;
+// past them: three tiles of maps 0.90 (to 1.20), two voxel tiles 0.91 (to 1.12), three or four shares 0.94, five 0.97, all by the price alone 0.94, with 44 of 288 slower.
+bool worth_beside(const SplitChoice& c, long groups, bool more)
+{
+    const bool brief = c.steps <= 8, lean = groups <= kCUs && !more;
+    return c.H[0] * c.H[1] * c.H[2] <= 4 * 64 * split::kStagers && groups <= 2 * kCUs && (!more || (brief && c.jgroups <= 3 && c.splits == 1)) &&
+           (c.splits == 1 || (brief && c.splits == 2)) && c.steps > (lean ? 1 : 4);
+}
+
+// Beside, a workgroup's LDS: staging buffers and weights (two where there is a chunk to stage behind another), tables.  False: not of this choice.
+bool place_beside(SplitChoice& c)
+{
+    const size_t hvol = (size_t)c.H[0] * c.H[1] * c.H[2], box = hvol * split::kVoxelBytes, weights = (size_t)c.steps * c.NJ * 3 * 1024;
+    const int buffers = c.cps > 1 ? 2 : 1;
+    c.beside = c.NJ <= 2 && c.NV == 1 && c.NW == split::kBesideWaves;
+    c.hop = buffers > 1 ? (int)box : 0;
+    c.whop = buffers > 1 ? (int)weights : 0;
+    c.wofs = (int)(buffers * box);
+    c.tables = (int)(buffers * (box + weights));
+    c.lds = c.tables + hvol * 4 + (size_t)(c.steps + 2) * split::kTaps * 4;
+    c.beside = c.beside && c.lds <= kLds;
+    return c.beside;
+}
+
+bool place_between(SplitChoice& c)
+{
+    const size_t hvol = (size_t)c.H[0] * c.H[1] * c.H[2];
+    c.beside = false;
+    c.lds = hvol * (split::kVoxelBytes + 4) + (size_t)(c.steps + 2) * split::kTaps * 4;
+    return c.lds <= kLds;
+}
+
 // Expected clocks of the launch (and of the sum of its shares) for every box that fits, the least taken.
 SplitChoice search(const Pass& P)
 {
     SplitChoice best = {};
+    double between = 0;
     const Axis &az = P.a[0], &ay = P.a[1], &ax = P.a[2];
     const int taps = az.k * ay.k * ax.k;
     if (taps > kMaxTaps) return best;
-    const int steps = (taps + split::kTaps - 1) / split::kTaps;
-    const int tiles = (P.fM + 15) / 16, nchunk = (P.fK + split::kMaps - 1) / split::kMaps;
-    const int jgroups = (tiles + 4) / 5, NJ = (tiles + jgroups - 1) / jgroups;
-    const int phases = az.phases * ay.phases * ax.phases;
+    SplitChoice c = {};
+    c.steps = (taps + split::kTaps - 1) / split::kTaps;
+    c.nchunk = (P.fK + split::kMaps - 1) / split::kMaps;
+    c.phases = az.phases * ay.phases * ax.phases;
+    const int tiles = (P.fM + 15) / 16, least_groups = (tiles + 4) / 5;
     const double count = (double)P.fM * az.d * ay.d * ax.d;
     const int nvs[6] = {1, 2, 3, 4, 6, 8}, nws[2] = {4, 8};
     const int (&pin)[4] = tuning().conv_tile;
-    for (int NW : nws)
-        for (int NV : nvs) {
-            if (!instance(NJ, NV) || (pin[0] && NV * NW != pin[0])) continue;
-            const int cap = 16 * NV * NW;
-            // clocks of a step of the workgroup: matrix cores, LDS reads (128 bytes a clock), weights from the vector cache (64)
-            const double step = 0.92 * std::max({NW / 4 * NJ * NV * 96.0, NW * NV * 24.0, NW * NJ * 48.0}) + 82.0 * NW / 4;
-            const int most = (NJ <= 2 && NJ * NV <= 8 ? 12 : 8) / NW;       // workgroups whose registers fit a compute unit
-            for (int Tx = 1; Tx <= ax.e && Tx <= cap; ++Tx)
-                for (int Ty = 1; Ty <= ay.e && Tx * Ty <= cap; ++Ty) {
-                    int Tz = std::min(cap / (Tx * Ty), az.e);
-                    if (pin[0]) {
-                        if (Tx != pin[3] || Ty != pin[2] || pin[1] * Ty * Tx > cap) continue;
-                        Tz = pin[1];
-                    }
-                    const int HZ = Tz + az.k - 1, HY = Ty + ay.k - 1, HX = Tx + ax.k - 1;
-                    const long hvol = (long)HZ * HY * HX;
-                    const size_t lds = (size_t)hvol * (split::kVoxelBytes + 4) + (size_t)(steps + 2) * split::kTaps * 4;
-                    if (lds > kLds) continue;
-                    const int fit = std::max(1, std::min(most, (int)(kLds / lds)));
-                    const int cz = (az.e + Tz - 1) / Tz, cy = (ay.e + Ty - 1) / Ty, cx = (ax.e + Tx - 1) / Tx;
-                    const long blocks = (long)cz * cy * cx * phases;
-                    if ((double)blocks * std::max({phases, cx, cy}) >= 4294967296.0) continue;      // fdiv of workgroup numbers
-                    // constants fitted to the times of 900 boxes on 22 layers (standard deviation 15 %)
-                    const double stage = 4.0 * hvol * (1.0 + 0.06 * (ax.sp - 1));
-                    const double fixed = 5200.0 + 11.5 * cap * NJ;
-                    for (int splits = 1, cps = nchunk; ; ) {
-                        const long groups = blocks * jgroups * splits;
-                        const long per_cu = (groups + kCUs - 1) / kCUs;
-                        // a unit with one wave per SIMD has nothing to overlap its waits with, one workgroup nothing for its stages
-                        const long both = std::min((long)fit, per_cu);
-                        const double alone = both * NW < 8 ? 1.38 : 1.0;
-                        double cost = per_cu * (fixed + cps * (steps * step * alone + stage * (both > 1 ? 0.46 : 1.0)));
-                        if (splits > 1) cost += 7000.0 + count * (splits + 1) * 4.0 / 3.0e12 * 2.1e9;
-                        cost -= 0.01 * Tx;
-                        if (!best.ok || cost < best.cost) {
-                            best.ok = true;
-                            best.NJ = NJ; best.jgroups = jgroups; best.NV = NV; best.NW = NW;
-                            best.T[0] = Tz; best.T[1] = Ty; best.T[2] = Tx;
-                            best.H[0] = HZ; best.H[1] = HY; best.H[2] = HX;
-                            best.c[0] = cz; best.c[1] = cy; best.c[2] = cx;
-                            best.phases = phases; best.steps = steps; best.nchunk = nchunk;
-                            best.cps = cps; best.splits = splits;
-                            best.lds = lds; best.cost = cost;
+    for (int most_nj = 5; most_nj >= 1; --most_nj) {
+        c.jgroups = (tiles + most_nj - 1) / most_nj;
+        c.NJ = (tiles + c.jgroups - 1) / c.jgroups;
+        if (c.NJ != most_nj) continue;
+        for (int NW : nws)
+            for (int NV : nvs) {
+                if (!instance(c.NJ, NV)) continue;
+                if (pin[0] && NV * NW != pin[0]) continue;
+                c.NV = NV; c.NW = NW;
+                const int cap = 16 * NV * NW;
+                auto parts = [](int e, int t) { return (e + t - 1) / t; };
+                for (int Tx = 1; Tx <= ax.e && Tx <= cap; ++Tx)
+                    for (int Ty = 1; Ty <= ay.e && Tx * Ty <= cap; ++Ty) {
+                        int Tz = std::min(cap / (Tx * Ty), az.e);
+                        // extents that a smaller one would replace without another box
+                        const bool loose = !pin[0] && ((Tx > 1 && parts(ax.e, Tx - 1) == parts(ax.e, Tx)) || (Ty > 1 && parts(ay.e, Ty - 1) == parts(ay.e, Ty)));
+                        if (pin[0]) {
+                            if (Tx != pin[3] || Ty != pin[2] || pin[1] * Ty * Tx > cap) continue;
+                            Tz = pin[1];
                         }
-                        // the next smaller share of the chunks, while the chip is not full
-                        if (cps == 1 || groups >= 3 * kCUs || tuning().conv_no_split) break;
-                        do ++splits; while ((nchunk + splits - 1) / splits == cps);
-                        cps = (nchunk + splits - 1) / splits;
-                        splits = (nchunk + cps - 1) / cps;
+                        c.T[0] = Tz; c.T[1] = Ty; c.T[2] = Tx;
+                        c.H[0] = Tz + az.k - 1; c.H[1] = Ty + ay.k - 1; c.H[2] = Tx + ax.k - 1;
+                        c.c[0] = (az.e + Tz - 1) / Tz; c.c[1] = (ay.e + Ty - 1) / Ty; c.c[2] = (ax.e + Tx - 1) / Tx;
+                        if ((size_t)c.H[0] * c.H[1] * c.H[2] * (split::kVoxelBytes + 4) > kLds) continue;
+                        const long blocks = (long)c.c[0] * c.c[1] * c.c[2] * c.phases;
+                        if ((double)blocks * std::max({c.phases, c.c[2], c.c[1]}) >= 4294967296.0) continue;      // divisions of workgroup numbers
+                        for (c.splits = 1, c.cps = c.nchunk; ; ) {
+                            const long groups = blocks * c.jgroups * c.splits;
+                            const bool more = c.jgroups > least_groups;
+                            if (!more && place_between(c)) {
+                                c.cost = clocks_between(c, groups, ax.sp, count) - 0.01 * Tx;
+                                if (between == 0 || c.cost < between) between = c.cost;
+                                if (!best.ok || c.cost < best.cost) { best = c; best.ok = true; }
+                            }
+                            if (!loose && worth_beside(c, groups, more) && place_beside(c)) {
+                                c.cost = clocks_beside(c, groups, ax.sp, count) - 0.01 * Tx;
+                                if (!best.ok || c.cost < best.cost) { best = c; best.ok = true; }
+                            }
+                            // the next smaller share of the chunks, while the chip is not full
+                            if (c.cps == 1 || groups >= 3 * kCUs || tuning().conv_no_split) break;
+                            do ++c.splits; while ((c.nchunk + c.splits - 1) / c.splits == c.cps);
+                            c.cps = (c.nchunk + c.splits - 1) / c.splits;
+                            c.splits = (c.nchunk + c.cps - 1) / c.cps;
+                        }
                     }
-                }
-        }
+            }
+    }
+    best.between = between;
     return best;
+}
+
+SplitTile split_args(const Geom& g, const SplitChoice& c, const Pass& p, long total, bool backward, const float* src, const float* w, const void* wp, float* dst,
+                     float* partial, const Finish& finish, int share0)
+{
+    SplitTile P = {};
+    P.src = src; P.wp = (const split::uintx4*)wp; P.dst = dst;
+    P.w = w; P.wm = backward ? g.kvol() : g.f * g.kvol(); P.wk = backward ? g.f * g.kvol() : g.kvol(); P.reflected = backward ? 1 : 0;
+    P.fK = p.fK; P.fM = p.fM;
+    P.sz = p.a[0].s; P.sy = p.a[1].s; P.sx = p.a[2].s;
+    P.pz = p.a[0].p; P.py = p.a[1].p; P.px = p.a[2].p;
+    P.dz = p.a[0].d; P.dy = p.a[1].d; P.dx = p.a[2].d;
+    P.kz = p.a[0].k; P.ky = p.a[1].k; P.kx = p.a[2].k;
+    P.spz = p.a[0].sp; P.spy = p.a[1].sp; P.spx = p.a[2].sp;
+    P.Tz = c.T[0]; P.Ty = c.T[1]; P.Tx = c.T[2];
+    P.HZ = c.H[0]; P.HY = c.H[1]; P.HX = c.H[2]; P.hvol = c.H[0] * c.H[1] * c.H[2];
+    P.cy = c.c[1]; P.cx = c.c[2];
+    P.qy = p.a[1].phases; P.qx = p.a[2].phases; P.phases = c.phases;
+    P.total = (int)total; P.run = (int)((total + 7) / 8);
+    P.nchunk = c.nchunk; P.cps = c.cps; P.steps = c.steps;
+    P.share0 = share0;
+    P.partial = partial;
+    P.y = finish.y; P.bias = finish.bias; P.deriv = finish.deriv;
+    P.dHX = make_fastdiv((unsigned)c.H[2]); P.dHY = make_fastdiv((unsigned)c.H[1]);
+    P.dTX = make_fastdiv((unsigned)c.T[2]); P.dTY = make_fastdiv((unsigned)c.T[1]);
+    P.dKX = make_fastdiv((unsigned)P.kx); P.dKY = make_fastdiv((unsigned)P.ky);
+    P.dPH = make_fastdiv((unsigned)P.phases); P.dQX = make_fastdiv((unsigned)P.qx); P.dQY = make_fastdiv((unsigned)P.qy);
+    P.dCX = make_fastdiv((unsigned)P.cx); P.dCY = make_fastdiv((unsigned)P.cy);
+    return P;
+}
+
+BesideTile beside_args(const Geom& g, const SplitChoice& c, const Pass& p, long total, bool backward, const float* src, const float* w, const void* wp, float* dst,
+                       float* partial, const Finish& finish, int share0, int shares)
+{
+    using split::make_boxdiv;
+    BesideTile P = {};
+    P.total = (int)total; P.run = (int)((total + 7) / 8);
+    P.phases = c.phases; P.qx = p.a[2].phases; P.qy = p.a[1].phases;
+    P.cx = c.c[2]; P.cy = c.c[1];
+    P.dPH = make_boxdiv((unsigned)P.phases); P.dQX = make_boxdiv((unsigned)P.qx); P.dQY = make_boxdiv((unsigned)P.qy);
+    P.dCX = make_boxdiv((unsigned)P.cx); P.dCY = make_boxdiv((unsigned)P.cy);
+    P.Tz = c.T[0]; P.Ty = c.T[1]; P.Tx = c.T[2];
+    P.spz = p.a[0].sp; P.spy = p.a[1].sp; P.spx = p.a[2].sp;
+    P.nchunk = c.nchunk; P.cps = c.cps; P.share0 = share0;
+    P.hop = c.hop; P.wofs = c.wofs; P.whop = c.whop; P.tables = c.tables;
+    P.sz = p.a[0].s; P.sy = p.a[1].s; P.sx = p.a[2].s;
+    P.pz = p.a[0].p; P.py = p.a[1].p; P.px = p.a[2].p;
+    P.HX = c.H[2]; P.HY = c.H[1]; P.hvol = c.H[0] * c.H[1] * c.H[2];
+    P.dHX = make_boxdiv((unsigned)c.H[2]); P.dHY = make_boxdiv((unsigned)c.H[1]);
+    P.fK = p.fK; P.src = src; P.wp = (const split::uintx4*)wp;
+    P.steps = c.steps;
+    P.kz = p.a[0].k; P.ky = p.a[1].k; P.kx = p.a[2].k;
+    P.dKX = make_boxdiv((unsigned)P.kx); P.dKY = make_boxdiv((unsigned)P.ky);
+    P.dTX = make_boxdiv((unsigned)c.T[2]); P.dTY = make_boxdiv((unsigned)c.T[1]);
+    P.fM = p.fM;
+    P.dz = p.a[0].d; P.dy = p.a[1].d; P.dx = p.a[2].d;
+    P.dst = shares > 1 ? partial : dst;
+    P.share = shares > 1 ? (long)P.fM * P.dz * P.dy * P.dx : 0;
+    P.y = finish.y; P.bias = finish.bias; P.deriv = finish.deriv;
+    P.w = w; P.wm = backward ? g.kvol() : g.f * g.kvol(); P.wk = backward ? g.f * g.kvol() : g.kvol(); P.reflected = backward ? 1 : 0;
+    return P;
 }
 
 }  // namespace
@@ -215,7 +357,13 @@ SplitChoice choose_split(const Geom& g, bool backward)
     return e.choice;
 }
 
-double split_seconds(const SplitChoice& c) { return c.cost / 1.9e9 + 2e-6; }
+// A choice whose tiles of maps or chunks of a share are other ones than the search's: staged as before if that can be.
+void split_place(SplitChoice& c)
+{
+    if (!c.beside || !place_beside(c)) place_between(c);
+}
+
+double split_seconds(double clocks) { return clocks / 1.9e9 + 2e-6; }
 
 // Packed weights; one step of padding behind them, which the kernel fetches ahead.
 size_t split_packed_bytes(const SplitChoice& c)
@@ -260,41 +408,24 @@ int split_conv(const Geom& g, const SplitChoice& c, bool backward, const float* 
                const Finish& finish, hipStream_t s, int share0, int shares)
 {
     const Pass p = pass_of(g, backward);
-    SplitTile P = {};
-    P.src = src; P.wp = (const split::uintx4*)wp; P.dst = dst;
-    P.w = w; P.wm = backward ? g.kvol() : g.f * g.kvol(); P.wk = backward ? g.f * g.kvol() : g.kvol(); P.reflected = backward ? 1 : 0;
-    P.fK = p.fK; P.fM = p.fM;
-    P.sz = p.a[0].s; P.sy = p.a[1].s; P.sx = p.a[2].s;
-    P.pz = p.a[0].p; P.py = p.a[1].p; P.px = p.a[2].p;
-    P.dz = p.a[0].d; P.dy = p.a[1].d; P.dx = p.a[2].d;
-    P.kz = p.a[0].k; P.ky = p.a[1].k; P.kx = p.a[2].k;
-    P.spz = p.a[0].sp; P.spy = p.a[1].sp; P.spx = p.a[2].sp;
-    P.Tz = c.T[0]; P.Ty = c.T[1]; P.Tx = c.T[2];
-    P.HZ = c.H[0]; P.HY = c.H[1]; P.HX = c.H[2]; P.hvol = c.H[0] * c.H[1] * c.H[2];
-    P.cy = c.c[1]; P.cx = c.c[2];
-    P.qy = p.a[1].phases; P.qx = p.a[2].phases; P.phases = c.phases;
     const long total = (long)c.c[0] * c.c[1] * c.c[2] * c.phases;
     if (total >= 2147483640L) return fail(ZNN_EUNSUPPORTED, "too many tiles for one launch");
-    P.total = (int)total; P.run = (int)((total + 7) / 8);
     if (!shares) shares = c.splits;
-    P.nchunk = c.nchunk; P.cps = c.cps; P.steps = c.steps;
-    P.share0 = share0;
-    P.partial = partial;
-    P.y = finish.y; P.bias = finish.bias; P.deriv = finish.deriv;
-    P.dHX = make_fastdiv((unsigned)c.H[2]); P.dHY = make_fastdiv((unsigned)c.H[1]);
-    P.dTX = make_fastdiv((unsigned)c.T[2]); P.dTY = make_fastdiv((unsigned)c.T[1]);
-    P.dKX = make_fastdiv((unsigned)P.kx); P.dKY = make_fastdiv((unsigned)P.ky);
-    P.dPH = make_fastdiv((unsigned)P.phases); P.dQX = make_fastdiv((unsigned)P.qx); P.dQY = make_fastdiv((unsigned)P.qy);
-    P.dCX = make_fastdiv((unsigned)P.cx); P.dCY = make_fastdiv((unsigned)P.cy);
     if (log_enabled())
-        fprintf(stderr, "[znn] conv split (%s): NJ=%d jgroups=%d NV=%d waves=%d tile=%dx%dx%d halo=%dx%dx%d blocks=%ld splits=%d-%d/%d lds=%zu cost=%.0f\n",
+        fprintf(stderr, "[znn] conv split (%s): NJ=%d jgroups=%d NV=%d waves=%d tile=%dx%dx%d halo=%dx%dx%d blocks=%ld splits=%d-%d/%d %s lds=%zu cost=%.0f\n",
                 backward ? "bwd" : "fwd", c.NJ, c.jgroups, c.NV, c.NW, c.T[0], c.T[1], c.T[2], c.H[0], c.H[1], c.H[2], total, share0,
-                share0 + shares, c.splits, c.lds, c.cost);
-    const SplitFn fn = pick(c.NJ, c.NV, c.NW);
-    if (!fn) return fail(ZNN_EUNSUPPORTED, "no kernel instance for tile %dx%d", c.NJ, c.NV);
-    ZNN_LAUNCH(backward ? "direct backward (MFMA)" : "direct forward (MFMA)", s, fn,
-               dim3((unsigned)P.run * 8, (unsigned)c.jgroups, (unsigned)shares), dim3(64 * c.NW), c.lds, P);
-    return check_launch(backward ? "direct backward (MFMA)" : "direct forward (MFMA)");
+                share0 + shares, c.splits, c.beside ? "beside" : "between", c.lds, c.cost);
+    const char* const name = backward ? "direct backward (MFMA)" : "direct forward (MFMA)";
+    const dim3 grid((unsigned)(total + 7) / 8 * 8, (unsigned)c.jgroups, (unsigned)shares);
+    if (c.beside) {
+        ZNN_LAUNCH(name, s, c.NJ == 1 ? split::k_conv_beside<1> : split::k_conv_beside<2>, grid, dim3(64 * (split::kBesideWaves + split::kStagers)), c.lds,
+                   beside_args(g, c, p, total, backward, src, w, wp, dst, partial, finish, share0, shares));
+    } else {
+        const SplitFn fn = pick(c.NJ, c.NV, c.NW);
+        if (!fn) return fail(ZNN_EUNSUPPORTED, "no kernel instance for tile %dx%d", c.NJ, c.NV);
+        ZNN_LAUNCH(name, s, fn, grid, dim3(64 * c.NW), c.lds, split_args(g, c, p, total, backward, src, w, wp, dst, partial, finish, share0));
+    }
+    return check_launch(name);
 }
 
 }  // namespace znn

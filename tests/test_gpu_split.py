@@ -97,6 +97,31 @@ def test_passes_of_wide_layers_run_on_the_split_and_stay_within_its_bound(f, fo,
     passes_within_bound(f, fo, n, k, s, ["direct forward (MFMA)"], ["direct backward (MFMA)"])
 
 
+@pytest.mark.parametrize("f,fo,n,k,s", [
+    # layers whose halo boxes and weights other waves stage: one chunk and several, one and two map tiles in a group, odd and even steps
+    (17, 31, (15, 15, 15), (3, 3, 3), (2, 2, 2)),       # sublattices, groups of maps forward
+    (24, 24, (15, 15, 15), (3, 3, 3), (1, 1, 1)),       # a last map tile of eight
+    (9, 33, (12, 11, 10), (3, 3, 3), (1, 1, 1)),        # chunks of eight maps and one, tiles of one
+    (19, 23, (1, 46, 25), (1, 3, 3), (1, 1, 1)),        # two tiles a workgroup
+    (7, 20, (20, 21, 22), (5, 2, 3), (1, 1, 1)),        # one chunk forward
+    (13, 27, (14, 13, 15), (2, 3, 4), (1, 1, 1)),
+    (7, 11, (15, 24, 41), (2, 6, 6), (1, 1, 1)),        # 18 steps
+])
+def test_passes_of_small_layers_run_on_the_split_within_its_bound_and_as_in_fp32(f, fo, n, k, s):
+    passes_within_bound(f, fo, n, k, s, ["direct forward (MFMA)"], ["direct backward (MFMA)"])
+    x, w, g = tensors(f, fo, n, k, s, 9110)
+    p = znn.Plan(f, fo, n, k, "direct", s)
+    out = p.fwd(dev(x), dev(w)).cpu().numpy()
+    w[fo - 1], there = np.nan, np.arange(fo) == fo - 1              # a map of NaN stands alone
+    got = p.fwd(dev(x), dev(w)).cpu().numpy()
+    assert np.array_equal(got[~there], out[~there]) and np.all(np.isnan(got[there]))
+    x[:, n[0] // 2, n[1] // 2, n[2] // 2], w[fo - 1] = np.inf, w[0]
+    got, ref = p.fwd(dev(x), dev(w)).cpu().numpy(), oracle.conv3d_fwd(x, w, s)
+    for kind in (np.isnan, np.isposinf, np.isneginf):
+        assert np.array_equal(kind(got), kind(ref))
+    p.close()
+
+
 @pytest.mark.parametrize("n,s", [((26, 26, 26), (1, 1, 1)), ((34, 34, 34), (4, 4, 4))])
 @pytest.mark.parametrize("half", [False, True])
 def test_errors_of_the_split_have_no_common_sign(n, s, half):
