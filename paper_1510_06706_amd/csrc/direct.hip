@@ -155,7 +155,7 @@ static SplitChoice choose_groups(const Geom& g, int& shares)
     const int tiles = (g.fo + 15) / 16;
     int groups = (tiles + c.NJ - 1) / c.NJ;
     c.jgroups = 1;
-    for (; ; c.NJ = (tiles + ++groups - 1) / groups) {
+    for (; ; ++groups, c.NJ = (tiles + groups - 1) / groups) {
         const size_t packed = split_packed_bytes(c);
         c.ok = packed <= ZNN_STATIC_SCRATCH_BYTES;
         shares = c.ok && c.splits > 1 ? (int)std::min<size_t>(c.splits, (ZNN_STATIC_SCRATCH_BYTES - packed) / share_bytes(g, c)) : 1;
