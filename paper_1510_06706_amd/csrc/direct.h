@@ -20,7 +20,7 @@ struct SplitChoice {
     double cost, between;           // expected clocks, and those of the best choice whose waves stage in between
 };
 SplitChoice choose_split(const Geom& g, bool backward);
-void split_place(SplitChoice& c);
+bool split_place(SplitChoice& c);
 double split_seconds(double clocks);
 size_t split_packed_bytes(const SplitChoice& c);
 PackItem split_pack_item(const Geom& g, const SplitChoice& c, bool backward, const float* w, void* wp);

@@ -138,20 +138,18 @@ int direct_fwd(const Geom& g, const float* in, const float* w, float* out, void*
 static Geom group_of(const Geom& g, const SplitChoice& c, int first)
 {
     Geom q = g;
-    q.fo = std::min(16 * c.NJ * c.jgroups, g.fo - first);
+    q.fo = std::min(16 * c.NJ, g.fo - first);
     return q;
 }
 
 static size_t share_bytes(const Geom& g, const SplitChoice& c) { return sizeof(float) * result_count(group_of(g, c, 0), false); }
 
-// All maps in one launch if their weights and sums fit; else c.jgroups = 1 and the largest groups whose weights and sums fit, or else the smallest; shares: those
-// of a launch.  Not ok: the weights of sixteen output maps do not fit, and the vector ALUs take the pass.
+// c.jgroups = 1 and the largest groups whose weights and sums fit, or else the smallest; shares: those of a launch.  Not ok: the weights
+// of sixteen output maps do not fit, and the vector ALUs take the pass.
 static SplitChoice choose_groups(const Geom& g, int& shares)
 {
     SplitChoice c = way(g, false);
     if (!c.ok) return c;
-    shares = c.splits;
-    if (split_packed_bytes(c) + (c.splits > 1 ? c.splits * share_bytes(g, c) : 0) <= ZNN_STATIC_SCRATCH_BYTES) return c;
     const int tiles = (g.fo + 15) / 16;
     int groups = (tiles + c.NJ - 1) / c.NJ;
     c.jgroups = 1;
@@ -166,7 +164,7 @@ static SplitChoice choose_groups(const Geom& g, int& shares)
         shares = c.splits = 1;
         c.cps = c.nchunk;
     }
-    if (c.ok) split_place(c);
+    c.ok = c.ok && split_place(c);
     return c;
 }
 
@@ -185,7 +183,7 @@ int direct_fwd_groups(const Geom& g, const float* in, const float* w, float* out
     const SplitChoice c = choose_groups(g, shares);
     if (!c.ok) return few_conv(g, false, in, w, out, Finish{}, s);
     float* partial = (float*)((char*)ws + split_packed_bytes(c));
-    for (int first = 0; first < g.fo; first += 16 * c.NJ * c.jgroups) {
+    for (int first = 0; first < g.fo; first += 16 * c.NJ) {
         const Geom q = group_of(g, c, first);
         float* dst = out + (long)first * g.ovol();
         const float* wq = w + (long)first * g.f * g.kvol();

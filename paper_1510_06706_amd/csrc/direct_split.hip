@@ -357,10 +357,10 @@ SplitChoice choose_split(const Geom& g, bool backward)
     return e.choice;
 }
 
-// A choice whose tiles of maps or chunks of a share are other ones than the search's: staged as before if that can be.
-void split_place(SplitChoice& c)
+// A choice whose tiles of maps or chunks of a share are other ones than the search's: staged as before if that can be.  False: no LDS for it.
+bool split_place(SplitChoice& c)
 {
-    if (!c.beside || !place_beside(c)) place_between(c);
+    return (c.beside && place_beside(c)) || place_between(c);
 }
 
 double split_seconds(double clocks) { return clocks / 1.9e9 + 2e-6; }
