@@ -18,6 +18,7 @@ struct SplitChoice {
     int hop, wofs, whop, tables;    // beside, LDS: from one staging buffer to the other (0: one buffer), weights and their second buffer, tables
     size_t lds;
     double cost, between;           // expected clocks, and those of the best choice whose waves stage in between
+    int boxes;                      // that the search looked at
 };
 SplitChoice choose_split(const Geom& g, bool backward);
 bool split_place(SplitChoice& c);

@@ -124,23 +124,34 @@ Pass pass_of(const Geom& g, bool backward)
 
 // Expected clocks of a launch of `groups` workgroups and of the sum of its shares.  Waves that stage in between: fitted to the times of 900 boxes on 22 layers (standard
 // deviation 15 %).
-double clocks_between(const SplitChoice& c, long groups, int spx, double count)
-{
-    const int hvol = c.H[0] * c.H[1] * c.H[2];
-    // clocks of a step of the workgroup: matrix cores, LDS reads (128 bytes a clock), weights from the vector cache (64)
-    const double step = 0.92 * std::max({c.NW / 4 * c.NJ * c.NV * 96.0, c.NW * c.NV * 24.0, c.NW * c.NJ * 48.0}) + 82.0 * c.NW / 4;
-    const int most = (c.NJ <= 2 && c.NJ * c.NV <= 8 ? 12 : 8) / c.NW;       // workgroups whose registers fit a compute unit
-    const int fit = std::max(1, std::min(most, (int)(kLds / c.lds)));
-    const double stage = 4.0 * hvol * (1.0 + 0.06 * (spx - 1));
-    const double fixed = 5200.0 + 11.5 * 16 * c.NV * c.NW * c.NJ;
-    const long per_cu = (groups + kCUs - 1) / kCUs;
-    // a unit with one wave per SIMD has nothing to overlap its waits with, one workgroup nothing for its stages
-    const long both = std::min((long)fit, per_cu);
-    const double alone = both * c.NW < 8 ? 1.38 : 1.0;
-    double cost = per_cu * (fixed + c.cps * (c.steps * step * alone + stage * (both > 1 ? 0.46 : 1.0)));
-    if (c.splits > 1) cost += 7000.0 + count * (c.splits + 1) * 4.0 / 3.0e12 * 2.1e9;
-    return cost;
-}
+struct ClocksBetween {
+    int NW, most, fit;
+    double step, stage, fixed;
+    // of a choice's tiles and waves
+    explicit ClocksBetween(const SplitChoice& c) : NW(c.NW)
+    {
+        // clocks of a step of the workgroup: matrix cores, LDS reads (128 bytes a clock), weights from the vector cache (64)
+        step = 0.92 * std::max({c.NW / 4 * c.NJ * c.NV * 96.0, c.NW * c.NV * 24.0, c.NW * c.NJ * 48.0}) + 82.0 * c.NW / 4;
+        most = (c.NJ <= 2 && c.NJ * c.NV <= 8 ? 12 : 8) / c.NW;         // workgroups whose registers fit a compute unit
+        fixed = 5200.0 + 11.5 * 16 * c.NV * c.NW * c.NJ;
+        step *= c.steps;
+    }
+    // of its halo box
+    void set_halo(int hvol, int spx) { stage = 4.0 * hvol * (1.0 + 0.06 * (spx - 1)); }
+    void set_lds(size_t lds) { fit = std::max(1, std::min(most, (int)(kLds / lds))); }
+    // no number of shares takes less: all chunks of all workgroups of one share, on units that are never idle
+    double least(long groups, int nchunk) const { return (1 - 1e-9) * groups / kCUs * nchunk * (step + 0.46 * stage); }
+    double operator()(int cps, int splits, long groups, double count) const
+    {
+        const long per_cu = (groups + kCUs - 1) / kCUs;
+        // a unit with one wave per SIMD has nothing to overlap its waits with, one workgroup nothing for its stages
+        const long both = std::min((long)fit, per_cu);
+        const double alone = both * NW < 8 ? 1.38 : 1.0;
+        double cost = per_cu * (fixed + cps * (step * alone + stage * (both > 1 ? 0.46 : 1.0)));
+        if (splits > 1) cost += 7000.0 + count * (splits + 1) * 4.0 / 3.0e12 * 2.1e9;
+        return cost;
+    }
+};
 
 // The larger of two times, and a little more where they are near each other: neither overlaps the other perfectly.
 double larger(double a, double b)
@@ -180,18 +191,20 @@ bool worth_beside(const SplitChoice& c, long groups, bool more)
            (c.splits == 1 || (brief && c.splits == 2)) && c.steps > (lean ? 1 : 4);
 }
 
+// the tiles that k_conv_beside has
+bool beside_tiles(int nj, int nv, int nw) { return nj <= 2 && nv == 1 && nw == split::kBesideWaves; }
+
 // Beside, a workgroup's LDS: staging buffers and weights (two where there is a chunk to stage behind another), tables.  False: not of this choice.
 bool place_beside(SplitChoice& c)
 {
     const size_t hvol = (size_t)c.H[0] * c.H[1] * c.H[2], box = hvol * split::kVoxelBytes, weights = (size_t)c.steps * c.NJ * 3 * 1024;
     const int buffers = c.cps > 1 ? 2 : 1;
-    c.beside = c.NJ <= 2 && c.NV == 1 && c.NW == split::kBesideWaves;
     c.hop = buffers > 1 ? (int)box : 0;
     c.whop = buffers > 1 ? (int)weights : 0;
     c.wofs = (int)(buffers * box);
     c.tables = (int)(buffers * (box + weights));
     c.lds = c.tables + hvol * 4 + (size_t)(c.steps + 2) * split::kTaps * 4;
-    c.beside = c.beside && c.lds <= kLds;
+    c.beside = beside_tiles(c.NJ, c.NV, c.NW) && c.lds <= kLds;
     return c.beside;
 }
 
@@ -203,7 +216,23 @@ bool place_between(SplitChoice& c)
     return c.lds <= kLds;
 }
 
-// Expected clocks of the launch (and of the sum of its shares) for every box that fits, the least taken.
+// The box of output voxels of a choice, and what follows from it.  Boxes in all, 0: no LDS for the halo box, or too many for the kernels' divisions.
+inline long set_box(SplitChoice& c, const Pass& P, int Tz, int Ty, int Tx, int cx)
+{
+    const int Hz = Tz + P.a[0].k - 1, Hy = Ty + P.a[1].k - 1, Hx = Tx + P.a[2].k - 1;
+    if ((size_t)Hz * Hy * Hx * (split::kVoxelBytes + 4) > kLds) return 0;
+    const int cz = (P.a[0].e + Tz - 1) / Tz, cy = (P.a[1].e + Ty - 1) / Ty;
+    const long boxes = (long)cz * cy * cx * c.phases;
+    if ((double)boxes * std::max({c.phases, cx, cy}) >= 4294967296.0) return 0;
+    c.T[0] = Tz; c.T[1] = Ty; c.T[2] = Tx;
+    c.H[0] = Hz; c.H[1] = Hy; c.H[2] = Hx;
+    c.c[0] = cz; c.c[1] = cy; c.c[2] = cx;
+    return boxes;
+}
+
+// Expected clocks of the launch (and of the sum of its shares) for every box that fits, the least taken.  Waves that stage in between take all maps of as few
+// groups as there can be; for waves that stage beside, which have one shape of tiles, more groups are looked at too, where worth_beside can hold at all.  A first call of
+// a shape waits for this: 152 us on average over 12000 passes of drawn layers (400 when every tile shape of every number of groups was walked).
 SplitChoice search(const Pass& P)
 {
     SplitChoice best = {};
@@ -219,54 +248,75 @@ SplitChoice search(const Pass& P)
     const double count = (double)P.fM * az.d * ay.d * ax.d;
     const int nvs[6] = {1, 2, 3, 4, 6, 8}, nws[2] = {4, 8};
     const int (&pin)[4] = tuning().conv_tile;
+    // a launch has at least so many boxes of one tile for each of the waves that multiply
+    const long beside_boxes = c.phases * (((long)az.e * ay.e * ax.e + 16 * split::kBesideWaves - 1) / (16 * split::kBesideWaves));
+    int boxes = 0;
     for (int most_nj = 5; most_nj >= 1; --most_nj) {
         c.jgroups = (tiles + most_nj - 1) / most_nj;
         c.NJ = (tiles + c.jgroups - 1) / c.jgroups;
         if (c.NJ != most_nj) continue;
+        const bool more = c.jgroups > least_groups;
+        SplitChoice easiest = c;            // for worth_beside
+        easiest.splits = 1;
+        for (int d = 0; d < 3; ++d) easiest.H[d] = P.a[d].k;
+        const bool may_beside = beside_tiles(c.NJ, 1, split::kBesideWaves) && worth_beside(easiest, beside_boxes * c.jgroups, more);
+        if (more && !may_beside) continue;
         for (int NW : nws)
             for (int NV : nvs) {
-                if (!instance(c.NJ, NV)) continue;
-                if (pin[0] && NV * NW != pin[0]) continue;
+                const bool beside = may_beside && beside_tiles(c.NJ, NV, NW);
+                if (!instance(c.NJ, NV) || (more && !beside) || (pin[0] && NV * NW != pin[0])) continue;
                 c.NV = NV; c.NW = NW;
                 const int cap = 16 * NV * NW;
-                auto parts = [](int e, int t) { return (e + t - 1) / t; };
-                for (int Tx = 1; Tx <= ax.e && Tx <= cap; ++Tx)
-                    for (int Ty = 1; Ty <= ay.e && Tx * Ty <= cap; ++Ty) {
-                        int Tz = std::min(cap / (Tx * Ty), az.e);
+                ClocksBetween clocks_between(c);
+                for (int Tx = 1; Tx <= ax.e && Tx <= cap; ++Tx) {
+                    const int column = cap / Tx, cx = (ax.e + Tx - 1) / Tx;
+                    for (int Ty = 1; Ty <= ay.e && Ty <= column; ++Ty) {
+                        if (pin[0] && (Tx != pin[3] || Ty != pin[2] || pin[1] * Ty * Tx > cap)) continue;
+                        ++boxes;
+                        const long blocks = set_box(c, P, pin[0] ? pin[1] : az.e > 1 ? std::min(column / Ty, az.e) : 1, Ty, Tx, cx);
+                        if (!blocks) continue;
                         // extents that a smaller one would replace without another box
-                        const bool loose = !pin[0] && ((Tx > 1 && parts(ax.e, Tx - 1) == parts(ax.e, Tx)) || (Ty > 1 && parts(ay.e, Ty - 1) == parts(ay.e, Ty)));
-                        if (pin[0]) {
-                            if (Tx != pin[3] || Ty != pin[2] || pin[1] * Ty * Tx > cap) continue;
-                            Tz = pin[1];
-                        }
-                        c.T[0] = Tz; c.T[1] = Ty; c.T[2] = Tx;
-                        c.H[0] = Tz + az.k - 1; c.H[1] = Ty + ay.k - 1; c.H[2] = Tx + ax.k - 1;
-                        c.c[0] = (az.e + Tz - 1) / Tz; c.c[1] = (ay.e + Ty - 1) / Ty; c.c[2] = (ax.e + Tx - 1) / Tx;
-                        if ((size_t)c.H[0] * c.H[1] * c.H[2] * (split::kVoxelBytes + 4) > kLds) continue;
-                        const long blocks = (long)c.c[0] * c.c[1] * c.c[2] * c.phases;
-                        if ((double)blocks * std::max({c.phases, c.c[2], c.c[1]}) >= 4294967296.0) continue;      // divisions of workgroup numbers
-                        for (c.splits = 1, c.cps = c.nchunk; ; ) {
-                            const long groups = blocks * c.jgroups * c.splits;
-                            const bool more = c.jgroups > least_groups;
-                            if (!more && place_between(c)) {
-                                c.cost = clocks_between(c, groups, ax.sp, count) - 0.01 * Tx;
-                                if (between == 0 || c.cost < between) between = c.cost;
-                                if (!best.ok || c.cost < best.cost) { best = c; best.ok = true; }
+                        auto loose = [&](int d) { return c.T[d] > 1 && (P.a[d].e + c.T[d] - 2) / (c.T[d] - 1) == c.c[d]; };
+                        const bool stages = beside && (pin[0] || (!loose(2) && !loose(1)));
+                        clocks_between.set_halo(c.H[0] * c.H[1] * c.H[2], ax.sp);
+                        // most boxes are beyond the best one whatever their shares
+                        const bool fits = !more && (between == 0 || clocks_between.least(blocks * c.jgroups, c.nchunk) - 0.01 * Tx <= between) && place_between(c);
+                        if (fits) clocks_between.set_lds(c.lds);
+                        else if (!stages) continue;
+                        for (int splits = 1, cps = c.nchunk; ; ) {
+                            const long groups = blocks * c.jgroups * splits;
+                            if (fits) {
+                                const double cost = clocks_between(cps, splits, groups, count) - 0.01 * Tx;
+                                if (between == 0 || cost < between) between = cost;
+                                if (!best.ok || cost < best.cost) {
+                                    c.splits = splits; c.cps = cps;
+                                    place_between(c);
+                                    c.ok = true; c.cost = cost;
+                                    best = c;
+                                }
                             }
-                            if (!loose && worth_beside(c, groups, more) && place_beside(c)) {
-                                c.cost = clocks_beside(c, groups, ax.sp, count) - 0.01 * Tx;
-                                if (!best.ok || c.cost < best.cost) { best = c; best.ok = true; }
+                            if (stages) {
+                                c.splits = splits; c.cps = cps;
+                                if (worth_beside(c, groups, more) && place_beside(c)) {
+                                    const double cost = clocks_beside(c, groups, ax.sp, count) - 0.01 * Tx;
+                                    if (!best.ok || cost < best.cost) {
+                                        c.ok = true; c.cost = cost;
+                                        best = c;
+                                    }
+                                }
                             }
-                            // the next smaller share of the chunks, while the chip is not full
-                            if (c.cps == 1 || groups >= 3 * kCUs || tuning().conv_no_split) break;
-                            do ++c.splits; while ((c.nchunk + c.splits - 1) / c.splits == c.cps);
-                            c.cps = (c.nchunk + c.splits - 1) / c.splits;
-                            c.splits = (c.nchunk + c.cps - 1) / c.cps;
+                            // the next smaller share of the chunks, while the chip is not full; of more groups there are none
+                            if (more || cps == 1 || groups >= 3 * kCUs || tuning().conv_no_split) break;
+                            do ++splits; while ((c.nchunk + splits - 1) / splits == cps);
+                            cps = (c.nchunk + splits - 1) / splits;
+                            splits = (c.nchunk + cps - 1) / cps;
                         }
                     }
+                }
             }
     }
     best.between = between;
+    best.boxes = boxes;
     return best;
 }
 
@@ -412,9 +462,9 @@ int split_conv(const Geom& g, const SplitChoice& c, bool backward, const float* 
     if (total >= 2147483640L) return fail(ZNN_EUNSUPPORTED, "too many tiles for one launch");
     if (!shares) shares = c.splits;
     if (log_enabled())
-        fprintf(stderr, "[znn] conv split (%s): NJ=%d jgroups=%d NV=%d waves=%d tile=%dx%dx%d halo=%dx%dx%d blocks=%ld splits=%d-%d/%d %s lds=%zu cost=%.0f\n",
+        fprintf(stderr, "[znn] conv split (%s): NJ=%d jgroups=%d NV=%d waves=%d tile=%dx%dx%d halo=%dx%dx%d blocks=%ld splits=%d-%d/%d %s lds=%zu cost=%.0f of %d boxes\n",
                 backward ? "bwd" : "fwd", c.NJ, c.jgroups, c.NV, c.NW, c.T[0], c.T[1], c.T[2], c.H[0], c.H[1], c.H[2], total, share0,
-                share0 + shares, c.splits, c.beside ? "beside" : "between", c.lds, c.cost);
+                share0 + shares, c.splits, c.beside ? "beside" : "between", c.lds, c.cost, c.boxes);
     const char* const name = backward ? "direct backward (MFMA)" : "direct forward (MFMA)";
     const dim3 grid((unsigned)(total + 7) / 8 * 8, (unsigned)c.jgroups, (unsigned)shares);
     if (c.beside) {
