@@ -179,16 +179,26 @@ double clocks_beside(const SplitChoice& c, long groups, int spx, double count)
     return 1.28 * cost * std::pow(c.splits, 0.115) * std::pow(c.NJ, 0.09);
 }
 
-// Where waves that stage beside pay: one 16-voxel tile a wave, and a launch that fits the chip at once, with one workgroup on a unit or two; with more of them a unit has other
-// workgroups to go on with while one stages, and twice the waves that multiply.  A thread has four voxels in flight: larger halo boxes take more than one time of memory.
+// Where waves that stage beside pay: one 16-voxel tile a wave, and one workgroup on a unit or two; with more of them a unit has other workgroups to go on with while one
+// stages, and twice the waves that multiply.  A thread has four voxels in flight: larger halo boxes take more than one time of memory.
 // More groups of maps than have to be (`more`) stage a box as often, shares have little to stage ahead: both take short chunks.  And three or four steps a chunk have nothing
-// to hide a stage behind, where it is done more often.  Of 509 passes of drawn layers these lines and the price take 77, at 0.87 of the time between on average and 1.01 at most;
-// past them: three tiles of maps 0.90 (to 1.20), two voxel tiles 0.91 (to 1.12), three or four shares 0.94, five 0.97, all by the price alone 0.94, with 44 of 288 slower.
+// to hide a stage behind, where it is done more often.  Past these lines, by the price: three tiles of maps 0.90 of the time between (to 1.20), two voxel tiles 0.91 (to 1.12),
+// three or four shares 0.94, five 0.97.  Five or six tiles of maps in three groups: 0.79 on average with a workgroup on a unit, 1.01 (to 1.07) with two.
 bool worth_beside(const SplitChoice& c, long groups, bool more)
 {
     const bool brief = c.steps <= 8, lean = groups <= kCUs && !more;
-    return c.H[0] * c.H[1] * c.H[2] <= 4 * 64 * split::kStagers && groups <= 2 * kCUs && (!more || (brief && c.jgroups <= 3 && c.splits == 1)) &&
-           (c.splits == 1 || (brief && c.splits == 2)) && c.steps > (lean ? 1 : 4);
+    return c.H[0] * c.H[1] * c.H[2] <= 4 * 64 * split::kStagers && groups <= (c.NJ * c.jgroups <= 4 ? 2 : 1) * kCUs &&
+           (!more || (brief && c.jgroups <= 3 && c.splits == 1)) && (c.splits == 1 || (brief && c.splits == 2)) && c.steps > (lean ? 1 : 4);
+}
+
+// The best choice of one kind against that of the other.  Where waves in between take shares, the prices are too far off: the sum of few results takes less than its part of
+// the price, and one share walks all chunks one after another.  Time beside / between of 1200 passes of drawn layers that the price alone takes beside: no shares between 0.89
+// (1.03 at most); shares, up to 40 000 results 1.00 (to 1.18), up to 100 000 0.95 (to 1.11), above 0.80 (to 0.98), five or six tiles of maps 0.97 (to 1.25).
+// Of 400 more, which neither the price nor these lines were fitted to, they take 341: 0.885 of the time, 1.006 at most.
+bool take_beside(const SplitChoice& beside, const SplitChoice& between, double count)
+{
+    if (!beside.ok || !between.ok) return beside.ok;
+    return beside.cost < between.cost && (between.splits == 1 || (count >= 1e5 && beside.NJ * beside.jgroups <= 4));
 }
 
 // the tiles that k_conv_beside has
@@ -235,11 +245,10 @@ inline long set_box(SplitChoice& c, const Pass& P, int Tz, int Ty, int Tx, int c
 // a shape waits for this: 152 us on average over 12000 passes of drawn layers (400 when every tile shape of every number of groups was walked).
 SplitChoice search(const Pass& P)
 {
-    SplitChoice best = {};
-    double between = 0;
+    SplitChoice between = {}, other = {};       // the best whose waves stage in between, and beside
     const Axis &az = P.a[0], &ay = P.a[1], &ax = P.a[2];
     const int taps = az.k * ay.k * ax.k;
-    if (taps > kMaxTaps) return best;
+    if (taps > kMaxTaps) return between;
     SplitChoice c = {};
     c.steps = (taps + split::kTaps - 1) / split::kTaps;
     c.nchunk = (P.fK + split::kMaps - 1) / split::kMaps;
@@ -280,29 +289,25 @@ SplitChoice search(const Pass& P)
                         const bool stages = beside && (pin[0] || (!loose(2) && !loose(1)));
                         clocks_between.set_halo(c.H[0] * c.H[1] * c.H[2], ax.sp);
                         // most boxes are beyond the best one whatever their shares
-                        const bool fits = !more && (between == 0 || clocks_between.least(blocks * c.jgroups, c.nchunk) - 0.01 * Tx <= between) && place_between(c);
+                        const bool fits = !more && (!between.ok || clocks_between.least(blocks * c.jgroups, c.nchunk) - 0.01 * Tx <= between.cost) && place_between(c);
                         if (fits) clocks_between.set_lds(c.lds);
                         else if (!stages) continue;
                         for (int splits = 1, cps = c.nchunk; ; ) {
                             const long groups = blocks * c.jgroups * splits;
+                            c.splits = splits; c.cps = cps;
                             if (fits) {
-                                const double cost = clocks_between(cps, splits, groups, count) - 0.01 * Tx;
-                                if (between == 0 || cost < between) between = cost;
-                                if (!best.ok || cost < best.cost) {
-                                    c.splits = splits; c.cps = cps;
+                                c.cost = clocks_between(cps, splits, groups, count) - 0.01 * Tx;
+                                if (!between.ok || c.cost < between.cost) {
                                     place_between(c);
-                                    c.ok = true; c.cost = cost;
-                                    best = c;
+                                    between = c;
+                                    between.ok = true;
                                 }
                             }
-                            if (stages) {
-                                c.splits = splits; c.cps = cps;
-                                if (worth_beside(c, groups, more) && place_beside(c)) {
-                                    const double cost = clocks_beside(c, groups, ax.sp, count) - 0.01 * Tx;
-                                    if (!best.ok || cost < best.cost) {
-                                        c.ok = true; c.cost = cost;
-                                        best = c;
-                                    }
+                            if (stages && worth_beside(c, groups, more) && place_beside(c)) {
+                                c.cost = clocks_beside(c, groups, ax.sp, count) - 0.01 * Tx;
+                                if (!other.ok || c.cost < other.cost) {
+                                    other = c;
+                                    other.ok = true;
                                 }
                             }
                             // the next smaller share of the chunks, while the chip is not full; of more groups there are none
@@ -315,7 +320,8 @@ SplitChoice search(const Pass& P)
                 }
             }
     }
-    best.between = between;
+    SplitChoice best = take_beside(other, between, count) ? other : between;
+    best.between = between.cost;
     best.boxes = boxes;
     return best;
 }
