@@ -63,7 +63,7 @@ constexpr size_t kLds = 160 * 1024;
 constexpr int kMaxTaps = 4096;
 
 // Instances: accumulators (NJ NV tiles) and two sets of weights (24 NJ registers) fit the 256 registers of two waves per SIMD (5 x 2
-// tiles all but four of them).
+// tiles all but two of them).
 constexpr bool instance(int nj, int nv) { return nj >= 1 && nj <= 5 && nj * nv <= (nj <= 2 ? 16 : nj == 3 ? 18 : nj == 4 ? 12 : 10); }
 
 template <int NJ, int NV, int NW> SplitFn instance_of()
