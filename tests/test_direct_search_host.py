@@ -5,6 +5,7 @@ import subprocess
 
 import pytest
 
+from direct_layers import BESIDE
 from paper_1510_06706_amd import build
 
 SOURCE = r"""
@@ -20,7 +21,7 @@ int main()
         g.spz = g.spy = g.spx = s;
         g.oz = g.nz - s * (g.kz - 1); g.oy = g.ny - s * (g.ky - 1); g.ox = g.nx - s * (g.kx - 1);
         const znn::SplitChoice c = znn::choose_split(g, backward != 0);
-        printf("%d %d %d %d %.17g %.17g\n", c.ok, c.NJ, c.beside, c.boxes, c.cost, c.between);
+        printf("%d %d %d %d %.17g %.17g %d %d %d %d\n", c.ok, c.NJ, c.beside, c.boxes, c.cost, c.between, c.jgroups, c.splits, c.cps, c.H[0] * c.H[1] * c.H[2]);
     }
 }
 """
@@ -40,7 +41,8 @@ def search(tmp_path_factory):
         text = "".join("%d %d %d %d %d %d %d %d %d %d\n" % (f, fo, *n, *k, s, b) for f, fo, n, k, s, b in layers)
         r = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True, env={**os.environ, **env})
         rows = [line.split() for line in r.stdout.splitlines()]
-        return [dict(ok=int(a), nj=int(b), beside=int(c), boxes=int(d), cost=float(e), between=float(h)) for a, b, c, d, e, h in rows]
+        return [dict(ok=int(a), nj=int(b), beside=int(c), boxes=int(d), cost=float(e), between=float(h), shape=(int(b), *map(int, rest)))
+                for a, b, c, d, e, h, *rest in rows]
 
     return run
 
@@ -82,6 +84,12 @@ def test_the_search_looks_at_each_box_once(search, f, fo, n, k, s, nj, more):
 ])
 def test_waves_stage_beside_where_that_is_faster(search, beside, layers):
     assert [found["beside"] for found in search(layers)] == [beside] * len(layers)
+
+
+def test_the_tested_passes_stage_beside(search):
+    """Each branch of the kernel has a pass in the tests on the GPU that takes it."""
+    for layer, found in zip(BESIDE, search([layer[:6] for layer in BESIDE])):
+        assert found["ok"] and found["beside"] and found["shape"] == layer[6], (layer, found)
 
 
 @pytest.mark.parametrize("layer", [(40, 40, (24, 24, 24), (3, 3, 3), 1, 0), (20, 28, (23, 31, 35), (3, 5, 5), 1, 1), (130, 17, (1, 90, 77), (1, 7, 7), 1, 0)])

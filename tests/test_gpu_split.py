@@ -11,6 +11,7 @@ import pytest
 import oracle
 from paper_1510_06706_amd import binding as znn
 from paper_1510_06706_amd import synth
+from direct_layers import BESIDE
 
 pytestmark = pytest.mark.gpu
 
@@ -119,6 +120,35 @@ def test_passes_of_small_layers_run_on_the_split_within_its_bound_and_as_in_fp32
     got, ref = p.fwd(dev(x), dev(w)).cpu().numpy(), oracle.conv3d_fwd(x, w, s)
     for kind in (np.isnan, np.isposinf, np.isneginf):
         assert np.array_equal(kind(got), kind(ref))
+    p.close()
+
+
+@pytest.mark.parametrize("f,fo,n,k,s,backward", [layer[:6] for layer in BESIDE])
+def test_passes_that_stage_beside_stay_within_the_bound_and_as_in_fp32(f, fo, n, k, s, backward):
+    s = (s, s, s)
+    x, w, g = tensors(f, fo, n, k, s, 9111)
+    p = znn.Plan(f, fo, n, k, "direct", s)
+    src, of, maps = (g, w.swapaxes(0, 1), f) if backward else (x, w, fo)       # `of`: a view, weights by result map
+
+    def run():
+        return kernels_of(lambda: (p.bwd if backward else p.fwd)(dev(src), dev(w)), "direct backward (MFMA)" if backward else "direct forward (MFMA)").cpu().numpy()
+
+    def exact(a, b):
+        return oracle.conv3d_bwd(a, b, n, s) if backward else oracle.conv3d_fwd(a, b, s)
+
+    out = run()
+    assert np.all(np.abs(out.astype(np.float64) - exact(src, w)) <= bound(exact(np.abs(src), np.abs(w)), src.shape[0], k[0] * k[1] * k[2]))
+    there = np.arange(maps) == maps - 1                             # a map of NaN stands alone
+    kept = of[maps - 1].copy()
+    of[maps - 1] = np.nan
+    got = run()
+    assert np.array_equal(got[~there], out[~there]) and np.all(np.isnan(got[there][np.isnan(exact(src, w)[there])]))
+    of[maps - 1] = kept
+    src[:, src.shape[1] // 2, src.shape[2] // 2, src.shape[3] // 2] = np.inf
+    got, ref = run(), exact(src, w)
+    for kind in (np.isnan, np.isposinf, np.isneginf):
+        assert np.array_equal(kind(got), kind(ref))
+    assert np.array_equal(got[np.isfinite(ref)], out[np.isfinite(ref)])
     p.close()
 
 
