@@ -336,12 +336,13 @@ __global__ void __launch_bounds__(64 * NW, NJ == 2 && NV == 2 ? 4 : 2) k_conv_sp
         }
     };
 
-    // Few tiles wait for their weights, all of a step's at once before its products are the earliest (29 -> 7 maps, 12^3, 7^3, backward, 2 x 1: 25.1 us, paced 29.8); the
-    // largest tile shapes have no registers for it.
+    // Few tiles wait for their weights, all of a step's at once before its products are the earliest (29 -> 7 maps, 12^3, 7^3, backward, 2 x 1: 25.1 us, paced 29.8; 36 passes of
+    // 5 x 1 tiles: paced 1.005 of the time, to 1.05); the largest tile shapes have no registers for it.
     constexpr bool LARGE = NJ * NV == 18 || (NJ == 5 && NV == 2);
-    constexpr bool PACED = NJ > 1 && NJ * NV > 4 && !LARGE;
-    // Packed weights: a uniform place and the lane's offset.  2 x 2 tiles keep to the registers of four waves by one place alone; 5 x 2 tiles take 0.992 of the time by it.
-    constexpr bool UNIFORM = (NJ != 2 || NV != 2) && (NJ != 5 || NV != 2);
+    constexpr bool PACED = NJ > 1 && NJ * NV > 5 && !LARGE;
+    // Packed weights: a uniform place and the lane's offset, or the lane's place alone.  By that 2 x 2 tiles keep to the registers of four waves, 5 x 2 tiles take 0.992 of the
+    // time (44 passes) and 2 x 1 tiles 0.979 (40 passes; 17 -> 17 maps, 16 x 10 x 11, 7^3, backward, 29.1 -> 28.2 us).
+    constexpr bool UNIFORM = (NJ != 2 || NV > 2) && (NJ != 5 || NV != 2);
     global_bytes wq = (global_bytes)(P.wp + ((long)jg * P.nchunk + ic0) * P.steps * (NJ * 3 * 64)) + (UNIFORM ? 0 : lane * 16);
     const unsigned wlane = UNIFORM ? lane * 16 : 0;
     for (int ic = ic0; ic < ic1; ++ic) {
@@ -441,8 +442,8 @@ __global__ void __launch_bounds__(64 * NW, NJ == 2 && NV == 2 ? 4 : 2) k_conv_sp
 #pragma unroll
             for (int r = 0; r < 4; ++r) bad = bad || !(fabsf(acc[jt][nv][r]) <= kLargest);
 
-    // The largest tile shapes work out the places of their voxels again, from the thread's number: kept from the start these went to memory (3 x 6 tiles 7 registers, now
-    // none; 5 x 2 tiles 6, now 2).  44 passes each: 0.989 and 0.992 of the time.  Others have registers left for them.
+    // The largest tile shapes work out the places of their voxels again, from the thread's number: kept from the start these went to memory (3 x 6 tiles four registers,
+    // now none; 5 x 2 tiles six, now two).  44 passes each: 0.989 and 0.992 of the time.  Others have registers left for them.
     unsigned thread = threadIdx.x;
     if constexpr (LARGE) asm volatile("" : "+v"(thread));
     const int ecol = thread & 15, egrp = thread >> 4 & 3;
