@@ -153,6 +153,8 @@ struct ClocksBetween {
     }
 };
 
+int least_groups(int tiles) { return (tiles + 4) / 5; }      // of 16-map tiles
+
 // The larger of two times, and a little more where they are near each other: neither overlaps the other perfectly.
 double larger(double a, double b)
 {
@@ -180,21 +182,28 @@ double clocks_beside(const SplitChoice& c, long groups, int spx, double count)
 }
 
 // Where waves that stage beside pay: one 16-voxel tile a wave, and one workgroup on a unit or two; with more of them a unit has other workgroups to go on with while one
-// stages, and twice the waves that multiply.  A thread has four voxels in flight: larger halo boxes take more than one time of memory.
-// More groups of maps than have to be (`more`) stage a box as often, shares have little to stage ahead: both take short chunks.  And three or four steps a chunk have nothing
-// to hide a stage behind, where it is done more often.  Past these lines, by the price: three tiles of maps 0.90 of the time between (to 1.20), two voxel tiles 0.91 (to 1.12),
-// three or four shares 0.94, five 0.97.  Five or six tiles of maps in three groups: 0.79 on average with a workgroup on a unit, 1.01 (to 1.07) with two.
-bool worth_beside(const SplitChoice& c, long groups, bool more)
+// stages, and twice the waves that multiply.  An XCD's units take the workgroups of its run of boxes, so those of the longest run count: 81 boxes of three groups, 243 for
+// 256 units, are 33 for 32 units, one of which took two after another (12 -> 88 maps, 135 x 26, 5^2: 13.1 us, in between 11.1; by 76 boxes 8.8).
+// A thread has four voxels in flight: larger halo boxes take more than one time of memory.
+// More groups of the `tiles` of maps than have to be stage a box as often, shares have little to stage ahead: both take short chunks.  And three or four steps a chunk have
+// nothing to hide a stage behind, where it is done more often; nor has a single chunk of two or three (1.00 of the time, two tiles of maps 1.01).  Past these lines, by
+// the price: three tiles of maps 0.90 of the time between (to 1.20), two voxel tiles 0.91 (to 1.12), three or four shares 0.94, five 0.97.  Groups of two tiles of maps
+// with a workgroup on a unit 0.79 on average; with two 1.00 (to 1.03) where a tile is empty, 1.01 (to 1.11) where a second chunk takes the LDS of the other, else 0.92.
+bool worth_beside(const SplitChoice& c, long boxes, int tiles)
 {
-    const bool brief = c.steps <= 8, lean = groups <= kCUs && !more;
-    return c.H[0] * c.H[1] * c.H[2] <= 4 * 64 * split::kStagers && groups <= (c.NJ * c.jgroups <= 4 ? 2 : 1) * kCUs &&
-           (!more || (brief && c.jgroups <= 3 && c.splits == 1)) && (c.splits == 1 || (brief && c.splits == 2)) && c.steps > (lean ? 1 : 4);
+    constexpr int units = kCUs / 8;
+    const long groups = (boxes + 7) / 8 * c.jgroups * c.splits;     // of an XCD
+    const bool more = c.jgroups > least_groups(tiles), brief = c.steps <= 8, lean = groups <= units && !more;
+    const bool two = c.NJ * c.jgroups <= 3 || (tiles == 4 && c.cps == 1);
+    return c.H[0] * c.H[1] * c.H[2] <= 4 * 64 * split::kStagers && groups <= (two ? 2 : 1) * units &&
+           (!more || (brief && c.jgroups <= 3 && c.splits == 1)) && (c.splits == 1 || (brief && c.splits == 2)) &&
+           c.steps > (!lean ? 4 : c.cps == 1 ? 3 : 1);
 }
 
 // The best choice of one kind against that of the other.  Where waves in between take shares, the prices are too far off: the sum of few results takes less than its part of
 // the price, and one share walks all chunks one after another.  Time beside / between of 1200 passes of drawn layers that the price alone takes beside: no shares between 0.89
 // (1.03 at most); shares, up to 40 000 results 1.00 (to 1.18), up to 100 000 0.95 (to 1.11), above 0.80 (to 0.98), five or six tiles of maps 0.97 (to 1.25).
-// Of 400 more, which neither the price nor these lines were fitted to, they take 341: 0.885 of the time, 1.006 at most.
+// Of 725 more that the price takes, which neither it nor these lines nor those of worth_beside were fitted to, they leave 670: 0.887 of the time, four above 1.02 (1.08 at most).
 bool take_beside(const SplitChoice& beside, const SplitChoice& between, double count)
 {
     if (!beside.ok || !between.ok) return beside.ok;
@@ -253,7 +262,7 @@ SplitChoice search(const Pass& P)
     c.steps = (taps + split::kTaps - 1) / split::kTaps;
     c.nchunk = (P.fK + split::kMaps - 1) / split::kMaps;
     c.phases = az.phases * ay.phases * ax.phases;
-    const int tiles = (P.fM + 15) / 16, least_groups = (tiles + 4) / 5;
+    const int tiles = (P.fM + 15) / 16;
     const double count = (double)P.fM * az.d * ay.d * ax.d;
     const int nvs[6] = {1, 2, 3, 4, 6, 8}, nws[2] = {4, 8};
     const int (&pin)[4] = tuning().conv_tile;
@@ -264,11 +273,12 @@ SplitChoice search(const Pass& P)
         c.jgroups = (tiles + most_nj - 1) / most_nj;
         c.NJ = (tiles + c.jgroups - 1) / c.jgroups;
         if (c.NJ != most_nj) continue;
-        const bool more = c.jgroups > least_groups;
+        const bool more = c.jgroups > least_groups(tiles);
         SplitChoice easiest = c;            // for worth_beside
         easiest.splits = 1;
+        easiest.cps = c.nchunk;
         for (int d = 0; d < 3; ++d) easiest.H[d] = P.a[d].k;
-        const bool may_beside = beside_tiles(c.NJ, 1, split::kBesideWaves) && worth_beside(easiest, beside_boxes * c.jgroups, more);
+        const bool may_beside = beside_tiles(c.NJ, 1, split::kBesideWaves) && worth_beside(easiest, beside_boxes, tiles);
         if (more && !may_beside) continue;
         for (int NW : nws)
             for (int NV : nvs) {
@@ -303,7 +313,7 @@ SplitChoice search(const Pass& P)
                                     between.ok = true;
                                 }
                             }
-                            if (stages && worth_beside(c, groups, more) && place_beside(c)) {
+                            if (stages && worth_beside(c, blocks, tiles) && place_beside(c)) {
                                 c.cost = clocks_beside(c, groups, ax.sp, count) - 0.01 * Tx;
                                 if (!other.ok || c.cost < other.cost) {
                                     other = c;

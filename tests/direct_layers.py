@@ -8,7 +8,7 @@ BESIDE = [
     (3, 10, (30, 6, 13), (5, 5, 5), 1, 0, (1, 1, 1, 1, 540)),       # four of them
     (25, 2, (13, 32, 34), (4, 5, 3), 2, 1, (2, 1, 1, 1, 550)),      # the same with two map tiles, sublattices
     (6, 41, (31, 15, 9), (1, 5, 5), 2, 0, (1, 3, 1, 1, 640)),       # three groups of maps
-    (37, 17, (18, 34, 17), (2, 3, 4), 1, 1, (1, 3, 1, 3, 360)),     # and three chunks
+    (48, 30, (28, 32, 6), (2, 4, 4), 1, 1, (1, 3, 1, 4, 275)),      # and four chunks
     (56, 28, (16, 33, 13), (5, 1, 5), 2, 1, (2, 2, 1, 4, 495)),     # an even number of chunks
     (85, 17, (11, 9, 22), (5, 2, 2), 1, 1, (2, 3, 1, 3, 120)),      # six map tiles
     (2, 43, (17, 20, 31), (2, 5, 2), 1, 1, (1, 1, 2, 3, 162)),      # two shares of three chunks

@@ -21,7 +21,8 @@ int main()
         g.spz = g.spy = g.spx = s;
         g.oz = g.nz - s * (g.kz - 1); g.oy = g.ny - s * (g.ky - 1); g.ox = g.nx - s * (g.kx - 1);
         const znn::SplitChoice c = znn::choose_split(g, backward != 0);
-        printf("%d %d %d %d %.17g %.17g %d %d %d %d\n", c.ok, c.NJ, c.beside, c.boxes, c.cost, c.between, c.jgroups, c.splits, c.cps, c.H[0] * c.H[1] * c.H[2]);
+        printf("%d %d %d %d %.17g %.17g %d %d %d %d %d\n", c.ok, c.NJ, c.beside, c.boxes, c.cost, c.between, c.c[0] * c.c[1] * c.c[2] * c.phases, c.jgroups,
+               c.splits, c.cps, c.H[0] * c.H[1] * c.H[2]);
     }
 }
 """
@@ -41,8 +42,8 @@ def search(tmp_path_factory):
         text = "".join("%d %d %d %d %d %d %d %d %d %d\n" % (f, fo, *n, *k, s, b) for f, fo, n, k, s, b in layers)
         r = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True, env={**os.environ, **env})
         rows = [line.split() for line in r.stdout.splitlines()]
-        return [dict(ok=int(a), nj=int(b), beside=int(c), boxes=int(d), cost=float(e), between=float(h), shape=(int(b), *map(int, rest)))
-                for a, b, c, d, e, h, *rest in rows]
+        return [dict(ok=int(a), nj=int(b), beside=int(c), boxes=int(d), cost=float(e), between=float(h), launched=int(i), shape=(int(b), *map(int, rest)))
+                for a, b, c, d, e, h, i, *rest in rows]
 
     return run
 
@@ -77,13 +78,22 @@ def test_the_search_looks_at_each_box_once(search, f, fo, n, k, s, nj, more):
     # passes that took 1.05 to 1.25 of their time when waves staged beside: shares of few results, and many tiles of maps
     (0, [(32, 3, (13, 13, 13), (3, 3, 3), 4, 0), (30, 3, (5, 5, 5), (3, 3, 3), 1, 0), (31, 3, (21, 21, 21), (3, 3, 3), 4, 0), (10, 30, (14, 11, 17), (3, 3, 3), 1, 1),
          (40, 3, (20, 20, 20), (3, 3, 3), 4, 0), (48, 48, (11, 11, 11), (3, 3, 3), 1, 0), (48, 30, (19, 29, 19), (3, 3, 3), 4, 0),
-         (36, 94, (1, 38, 63), (1, 5, 5), 1, 0), (85, 7, (1, 77, 114), (1, 5, 5), 1, 1)]),
+         (36, 94, (1, 38, 63), (1, 5, 5), 1, 0), (85, 7, (1, 77, 114), (1, 5, 5), 1, 1),
+         # two workgroups of two tiles of maps on a unit, one after another
+         (10, 63, (1, 245, 67), (1, 5, 5), 1, 0), (14, 52, (1, 190, 49), (1, 5, 5), 1, 0), (33, 5, (21, 38, 17), (1, 5, 5), 1, 1)]),
     # and that took 0.73 to 0.97: no shares, shares of many results, five tiles of maps with a workgroup on a unit
     (1, [(16, 24, (15, 15, 15), (3, 3, 3), 2, 0), (8, 3, (13, 13, 13), (3, 3, 3), 4, 0), (40, 40, (20, 20, 20), (3, 3, 3), 1, 0), (40, 40, (21, 21, 21), (3, 3, 3), 1, 1),
          (14, 88, (13, 13, 9), (1, 5, 5), 1, 0), (90, 15, (11, 11, 16), (3, 3, 3), 1, 1)]),
 ])
 def test_waves_stage_beside_where_that_is_faster(search, beside, layers):
     assert [found["beside"] for found in search(layers)] == [beside] * len(layers)
+
+
+def test_no_xcd_takes_more_than_its_units(search):
+    """81 boxes of three groups are fewer than there are units, but 33 workgroups for the 32 units of seven of the eight XCDs."""
+    for found in search([(12, 88, (1, 135, 26), (1, 5, 5), 1, 0), (71, 7, (1, 30, 41), (1, 5, 5), 1, 1)]):
+        assert found["beside"] and found["shape"][:2] == (2, 3)
+        assert -(-found["launched"] // 8) * 3 <= 32
 
 
 def test_the_tested_passes_stage_beside(search):
