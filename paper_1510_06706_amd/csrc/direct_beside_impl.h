@@ -2,10 +2,10 @@
 // workgroup bring it the halo boxes and the weights of the next chunk.
 //
 // Such a launch has a workgroup on a unit, or two: waves that stage in between leave its matrix cores alone meanwhile, and weights from memory, one step ahead, took 950 clocks
-// a step of 290 (40 -> 40 maps, 24^3, 3^3 kernels: 34 000 of 44 000 clocks a workgroup; by way of LDS 16 300, as long as its reads take).  Two buffers of each, a chunk ahead.
-// What is left at that size is 7 000 clocks to the first data and 7 000 of stores, which all workgroups do at once.
-// Packing included, waves in between -> beside: 22 -> 7 maps, 120 x 143, 9^2, forward 17.4 -> 12.9 us; 16 -> 24, 15^3, 3^3 two apart 10.6 -> 9.0; 7 -> 11, 15 x 24 x 41,
-// 2 x 6 x 6, backward 13.9 -> 10.6.
+// a step of 290 (40 -> 40 maps, 24^3, 3^3 kernels, which the rule leaves in between: 34 000 of 44 000 clocks a workgroup; by way of LDS 16 300, as long as its reads take).
+// Two buffers of each, a chunk ahead.  What is left at that size is 7 000 clocks to the first data and 7 000 of stores, which all workgroups do at once.
+// Packing included, waves in between -> beside: 40 -> 40 maps, 20^3, 3^3, 17.5 -> 13.7 us forward and 21.2 -> 14.3 backward; 22 -> 7, 120 x 143, 9^2, forward 16.6 -> 11.7;
+// 16 -> 24, 15^3, 3^3 two apart 9.7 -> 8.1; 7 -> 11, 15 x 24 x 41, 2 x 6 x 6, backward 13.1 -> 9.9.
 //
 // Tried as well: weights by LDS in several slabs of a chunk, weights straight from memory for three and four voxel tiles a wave, eight waves that multiply, five shares: 1.02 to
 // 1.17 times the time of waves that stage in between.  One workgroup a unit that goes on to its next box while the four waves store the one before: 59^3 two apart
@@ -194,7 +194,8 @@ __global__ void __launch_bounds__(64 * (kBesideWaves + kStagers), (kBesideWaves 
     lds_bytes voff = lbase + ((vz * P.HY + vy) * P.HX + vx) * kVoxelBytes;
     lds_bytes wl = lbase + P.wofs + lane * 16;
 
-    // A chunk's sum is formed on its own: 40 maps, 24^3, 3^3: 7.9e-8 off 64 bits, as five shares are, and in one running sum 1.2e-7.
+    // A chunk's sum is formed on its own, as by shares of one: 40 -> 40 maps, 20^3, 3^3, bit for bit what five shares gave (1.2e-7 of the largest result off 64 bits, 1.5e-7 at
+    // most over six seeds); 24^3: 7.9e-8, and in one running sum 1.2e-7.
     floatx4 acc[NJ][1], sum[NJ];
     for (int ic = ic0; ic < ic1; ++ic) {
         bf16x8 a0[NJ][3], a1[NJ][3];

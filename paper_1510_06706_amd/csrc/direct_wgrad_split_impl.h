@@ -22,7 +22,7 @@
 // Measured against v_mfma_f32_16x16x4_f32 on rows of the images as they are, launches of a call together: 40 -> 40 maps, 64^3, 5^3
 // kernels 960 -> 538 us (161 TFLOP/s of fp32 products); 80 -> 80, 256^2, 11^2: 970 -> 495 us; 24 -> 36, 23 x 75 x 61,
 // 3 x 5 x 5: 223 -> 122 us (rows of odd lengths had 4-byte copies); 120 -> 120, 48^3, 7^3: 9.7 -> 4.2 ms; 40 -> 40, 24^3,
-// 3^3: 36 -> 32 us.  Matrix cores busy 0.54 of the first one's time: the waves of a workgroup begin every step of a
+// 3^3: 36 -> 32 us.  Matrix cores busy 0.55 of the first one's time: the waves of a workgroup begin every step of a
 // tile with its operands, and 3.9 conflict clocks an LDS instruction are a tenth of the time.  Two workgroups of four waves per compute unit, each with half the buffers, would overlap these, but their smaller
 // tiles are copied more often: 542 -> 887 us.
 #pragma once
